@@ -145,7 +145,7 @@ enum {
 
 /* Schedule-dependent counters (not part of the result; excluded from parity). HOST struct. */
 typedef struct dgn_stats {
-    int64_t levels;          /* frontier levels processed                                        */
+    int64_t levels;          /* frontier levels processed (ring sweep of fewer than 64 graphs: settling steps; of more: 0) */
     int64_t tensor_visits;   /* frontier entries and deferred operators expanded, summed over levels */
     int64_t max_frontier;    /* largest frontier                                                 */
     int64_t launches;        /* kernels enqueued by the call                                     */

@@ -39,6 +39,12 @@ constexpr int kBackwardMaxBatch = 60;       // forward passes of the backward pr
 constexpr int kSweepMinGraphs = 64;         // packed batches with at least this many graphs ...
 constexpr int64_t kSweepMaxGraphOps = 1 << 18;   // ... none larger than this use the per-graph sweep
 constexpr u64 kRecycleMagic = 0x44474e5f52435943ull;   // "DGN_RCYC"
+constexpr u64 kRingMagic = 0x44474e5f52494e47ull;      // "DGN_RING": a result of the ring sweep (bitmap, no log)
+constexpr int64_t kRingMaxOps = (int64_t)1 << 17;      // single graphs up to this size ...
+constexpr int64_t kRingSeedWords = 2048;               // targets of a graph that the ring sweep keeps in LDS, at most
+constexpr int64_t kRingShortOps = 16384;               // single graphs (or fewer graphs than the per-graph sweep starts at): up to this
+constexpr int kRingThinDist = 96;                      // size always, up to kRingMaxOps when no input lies further back than this
+constexpr int64_t kRingMaxGraphOps = (int64_t)1 << 18; // ... and graphs of a batch up to this size may take the ring sweep
 constexpr int kSmallLevel = 16384;           // levels expanding fewer entries than this decay the threshold faster
 constexpr int kDefaultDeferPercent = 74;
 constexpr int kDefaultStartShift = 1;       // deferral threshold starts at P >> 1 ...
@@ -149,6 +155,9 @@ struct PruneScratch {
     size_t db_bytes, opbits_bytes;
     RecycleHeader *hdr;     // says which buffers hold the result of the last prune that kept a complete log
     ColourLog log;          // tensors that prune coloured
+    u64 *ring_bits;         // ring sweep: a bit per operator, running counts per word, a record per graph
+    int32_t *ring_cum;
+    int4 *ring_graphs;
     size_t bytes;
 };
 
@@ -179,6 +188,12 @@ PruneScratch prune_scratch(void *mem, int64_t P, int64_t T, int32_t G, int64_t m
     if (lcap < 4096) lcap = 4096;
     S.log.seg_cap = (int32_t)lcap;
     S.log.entries = c.take<int32_t>((size_t)kMaxSeg * (size_t)lcap);
+    if (G > 1 || P <= kRingMaxOps) {
+        const size_t words = (size_t)(P >> 6) + (size_t)G + 1;
+        S.ring_bits = c.take<u64>(words);
+        S.ring_cum = c.take<int32_t>(words);
+        S.ring_graphs = c.take<int4>((size_t)G + 1);
+    }
     S.state = c.take<TravState>(2);
     S.ctr = c.take<TravCounters>(1);
     S.qg = queue_geometry(T, max_entries);
@@ -256,6 +271,8 @@ struct dgn_graph {
     bool topological;       // operator ids verified to be a topological order at build time
     bool multi_producer;    // some tensor is written by more than one operator
     int64_t max_graph_ops;  // largest graph of a packed batch (P for a single graph)
+    bool ring;              // the ring sweep can take these graphs: see ring_sweep.hip for the three numbers
+    int ring_low, ring_dist, ring_span64;
     uint64_t serial;        // unique per handle in this process
     // Hints only, taken from the last prune of this graph; a wrong one costs launches that return at once,
     // or a second batch, and corrects itself.  Kept apart for full prunes [0] and incremental ones [1],
@@ -293,12 +310,13 @@ int finish_build(dgn_graph *h, const GraphLayout &L, const int64_t *op_off_host,
     // worth paying on every build of a big single graph, whose traversal does not depend on it.)  A packed batch
     // gets it in the walk over the edges that checks the graphs' ranges.
     const bool check_topo = (options && options->validate) || h->G >= kSweepMinGraphs;
-    if (h->G > 1) DGN_HIP(launch_check_graph_ranges(h->v, status, check_topo, s));
+    const bool check_ring = h->G > 1 || h->P <= kRingMaxOps;
+    if (check_ring) DGN_HIP(launch_check_graph_ranges(h->v, status, check_topo, s));
     else if (check_topo) DGN_HIP(launch_check_topological(h->v, status, s));
     void *pin = nullptr;
     int rc = pinned_buffer(&pin);
     if (rc) return rc;
-    DGN_HIP(hipMemcpyAsync(pin, status, (kStatusMulti + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    DGN_HIP(hipMemcpyAsync(pin, status, (kStatusRing + 4) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     DGN_HIP(hipStreamSynchronize(s));
     int32_t bits = *static_cast<int32_t *>(pin);
     h->topological = check_topo && (bits & kErrTopo) == 0;
@@ -306,6 +324,15 @@ int finish_build(dgn_graph *h, const GraphLayout &L, const int64_t *op_off_host,
     if (!(options && options->validate)) bits &= ~kErrTopo;
     rc = error_bits_to_code(bits);
     if (rc) return rc;
+    const int32_t *ring = static_cast<int32_t *>(pin) + kStatusRing;
+    // (32-bit byte offsets inside a graph's arrays)
+    h->ring = check_ring && h->P > 0 && h->Ein > 0 && h->Ein < (1 << 30) && h->T < (1 << 29) && ring[0] == 0;
+    h->ring_low = ring[1];
+    h->ring_dist = ring[2];
+    h->ring_span64 = ring[3];
+    for (int32_t i = 0; h->G > 1 && i < h->G; ++i)           // a graph without operators: all its tensors are inputs
+        if (op_off_host[i + 1] == op_off_host[i] && t_off_host[i + 1] - t_off_host[i] > h->ring_low)
+            h->ring_low = (int)(t_off_host[i + 1] - t_off_host[i]);
     h->max_graph_ops = h->P;
     static std::atomic<uint64_t> next_serial{1};
     h->serial = next_serial.fetch_add(1, std::memory_order_relaxed);
@@ -524,6 +551,105 @@ int dgn_prune_workspace(const dgn_graph *g, int32_t num_sets, size_t *scratch_by
     return DGN_OK;
 }
 
+// Waves per graph when the ring sweep takes this call, 0 when it does not.
+//   Which graphs: the sweep walks every operator, 1 024 of them in 2 us (nothing kept) to 13 us (one long chain); the level
+// by level traversal costs about 4.6 us per dependent level of a thin graph and 60 to 100 us before it has done anything.
+// Up to 16 384 operators the sweep was the faster one for every family tried (layered CNN, unrolled RNN, sliding window;
+// 1 and 64 sets): 34 against 106 us at 800 operators, 107 against 119 at 16 000 in the worst case (an unrolled RNN whose
+// chains die out), which at 32 000 is 170 against 121.  Beyond that size only graphs that read nothing older than 96 tensors:
+// they have a level per 96 tensors at least.
+//   How many waves: sixteen take a graph that has a compute unit to itself (20 000 operators in a chain of short hops:
+// 0.28 ms, four waves 0.30, one 0.40); four when all graphs are resident at once that way (1 500 graphs of 20 000 operators:
+// 0.95 ms, one wave 1.03, sixteen 2.13); one beyond (4 096 graphs: 1.18 ms, four waves 1.67).
+static int ring_waves(const dgn_graph *g, const dgn_options *o)
+{
+    if (!g->ring || (o && (o->traversal != 0 || o->incremental || o->recompute_keep))) return 0;
+    const bool many = g->G >= kSweepMinGraphs;               // (such batches were always swept graph by graph)
+    const int64_t most = many ? kRingMaxGraphOps : g->ring_dist <= kRingThinDist ? kRingMaxOps : kRingShortOps;
+    if (g->max_graph_ops > most) return 0;
+    auto fits = [&](int w) {
+        return ((size_t)ring_words(w, g->ring_dist, g->ring_span64) + (size_t)g->ring_low + kRingExtraWords) * sizeof(u64) +
+                   kRingSeedWords * sizeof(uint32_t) <= kRingMaxLds;
+    };
+    if (g->G <= g->num_cus && g->max_graph_ops > 4 * kWave && fits(16)) return 16;
+    if (g->G <= 8 * g->num_cus && fits(4)) return 4;
+    return fits(1) ? 1 : 0;
+}
+
+// dgn_prune of graphs that the ring sweep takes: two launches (three for a packed batch), nothing to clear beforehand.
+static int ring_prune(const dgn_graph *g, int waves, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
+                      const int32_t *tgt_idx, u64 *M, u64 *K, uint8_t *op_flag, int32_t *kept_ops, u64 *kept_masks,
+                      int64_t *kept_count, int64_t *per_query_count, const PruneScratch &S, const dgn_options *options,
+                      dgn_stats *stats, hipStream_t s, u64 *also_M, u64 *also_K)
+{
+    void *pin = nullptr;
+    int rc = pinned_buffer(&pin);
+    if (rc) return rc;
+    hipEvent_t *ev = nullptr;
+    if (options && options->profile && stats) {
+        rc = profile_events(&ev);
+        if (rc) return rc;
+        DGN_HIP(hipEventRecord(ev[0], s));
+    }
+    if (also_M || also_K) {
+        FillRegion more[2] = {{also_M, (size_t)g->T * 8}, {also_K, (size_t)g->P * 8}};
+        DGN_HIP(launch_clear(more, 2, s));
+    }
+    uint8_t *flags = (op_flag && ((uintptr_t)op_flag & 7) == 0 && g->P % 8 == 0) ? op_flag : S.flagbuf;
+    RingArgs a{};
+    a.g = g->v;
+    a.num_sets = num_sets;
+    a.num_targets = num_targets;
+    a.tgt_rowptr = tgt_rowptr;
+    a.tgt_idx = tgt_idx;
+    a.M = M;
+    a.K = K;
+    a.flags = flags;
+    a.flags2 = flags == op_flag ? nullptr : op_flag;
+    a.kept_ops = kept_ops;
+    a.kept_masks = kept_masks;
+    a.kept_count = kept_count;
+    a.pq = per_query_count;
+    a.bits = S.ring_bits;
+    a.cum = S.ring_cum;
+    a.graphs = S.ring_graphs;
+    a.host_status = static_cast<int32_t *>(pin);
+    a.hdr = S.hdr;
+    a.want = RecycleHeader{kRingMagic, g->serial, M, K, kept_ops, kept_count, flags, nullptr, nullptr, {0, 0, 0}};
+    // (many graphs: nearly every word of a batch is written anyway, and the flag has no effect)
+    a.recycle = options && options->recycle && g->G < kSweepMinGraphs;
+    a.low_words = g->ring_low;
+    // targets of a graph that fit in LDS; a graph with more of them sends its targets through M
+    const int64_t avg = num_targets / g->G;
+    a.seed_words = (int32_t)(g->G == 1 ? (avg < kRingSeedWords ? avg : kRingSeedWords)
+                                       : (avg + avg / 2 + 64 < kRingSeedWords ? avg + avg / 2 + 64 : kRingSeedWords));
+    int32_t *status = static_cast<int32_t *>(pin);
+    status[0] = status[1] = status[2] = 0;
+    if (ev) DGN_HIP(hipEventRecord(ev[1], s));
+    DGN_HIP(launch_ring_sweep(a, waves, g->ring_dist, g->ring_span64, g->max_graph_ops, s));
+    if (ev) DGN_HIP(hipEventRecord(ev[2], s));
+    DGN_HIP(hipStreamSynchronize(s));
+    if (stats) {
+        int32_t *user_trace = stats->level_trace;
+        const int64_t user_cap = stats->level_trace_cap;
+        memset(stats, 0, sizeof(*stats));
+        stats->level_trace = user_trace;
+        stats->level_trace_cap = user_cap;
+        stats->launches = g->G > 1 ? 3 : 2;
+        stats->levels = g->G < kSweepMinGraphs ? status[1] : 0;
+        stats->tensor_visits = g->P;
+        stats->recycled = status[2];
+        if (ev) {
+            DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_TRAVERSE], ev[1], ev[2]));
+            if (options->profile == 1) {
+                DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_CLEAR], ev[0], ev[1]));
+                DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_TOTAL], ev[0], ev[2]));
+            }
+        }
+    }
+    return error_bits_to_code(status[0]);
+}
+
 // dgn_prune.  also_M [T] / also_K [P] (or NULL): two more arrays that the call zeroes with M and K -- all of them,
 // or, with recycled buffers, the words that the previous call's log and kept list name (the caller vouches that
 // they hold non-zero words nowhere else).
@@ -550,6 +676,11 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     hipStream_t s = static_cast<hipStream_t>(stream);
     u64 *M = reinterpret_cast<u64 *>(tensor_mask);
     u64 *K = reinterpret_cast<u64 *>(op_mask);
+    const int ring = ring_waves(g, options);
+    if (ring)
+        return ring_prune(g, ring, num_sets, num_targets, tgt_rowptr, tgt_idx, M, K, op_flag, kept_ops,
+                          reinterpret_cast<u64 *>(kept_masks), kept_count, per_query_count, S, options, stats, s,
+                          reinterpret_cast<u64 *>(also_M), reinterpret_cast<u64 *>(also_K));
     const size_t pq_bytes = per_query_count ? sizeof(int64_t) * 64 * (size_t)(g->G > 1 ? g->G : 1) : 0;
     int64_t launches = 0, level_launches = 0;
     // 0 start, 1 cleared, 2 seeded, 3 traversed, 4 counted, 5 scanned, 6 scattered.  An event between two

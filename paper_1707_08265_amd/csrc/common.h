@@ -268,7 +268,7 @@ hipError_t launch_check_csr(const int32_t *rowptr, const int32_t *idx, int32_t n
                             int32_t n_vals, int32_t *error, hipStream_t s);
 hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t *row_of, hipStream_t s);
 hipError_t launch_check_topological(const GraphView &g, int32_t *error, hipStream_t s);
-hipError_t launch_check_graph_ranges(const GraphView &g, int32_t *error, bool also_topological, hipStream_t s);
+hipError_t launch_check_graph_ranges(const GraphView &g, int32_t *status, bool also_topological, hipStream_t s);
 
 // Traversal.
 // operator records and producer words, once per graph; *multi = 1 when some tensor has several producers
@@ -291,6 +291,41 @@ hipError_t launch_narrow(const GraphView &g, TravState *st, TravCounters *ctr, i
 // per-graph per-set counts.
 hipError_t launch_sweep_graphs(const GraphView &g, u64 *M, u64 *K, int64_t *per_query_count, bool multi_producer,
                                hipStream_t s);
+// The same for graphs whose tensors are numbered as they are created and read soon after (see ring_sweep.hip): one
+// workgroup per graph, M of the recent tensors in LDS.  Everything is written in full; nothing needs clearing.
+constexpr size_t kRingMaxLds = 160 * 1024 - 1024;   // LDS of a compute unit less the kernel's own few words
+struct RingArgs {
+    GraphView g;
+    int32_t num_sets;
+    int64_t num_targets;
+    const int32_t *tgt_rowptr, *tgt_idx;
+    u64 *M, *K;
+    uint8_t *flags;          // a byte per operator: K != 0
+    uint8_t *flags2;         // the same once more, or NULL
+    int32_t *kept_ops;
+    u64 *kept_masks;         // may be NULL
+    int64_t *kept_count;
+    int64_t *pq;             // [G * 64], may be NULL
+    u64 *bits;               // [P / 64 + G + 1] a bit per operator, K != 0: words of 64 operators of one graph, graph g's
+                             // from entry g + (its first operator) / 64 on
+    int32_t *cum;            // for every such word: operators of the graph kept in it and above
+    int4 *graphs;            // [G + 1] per graph: operators kept, error bits, settling steps; all graphs
+    int32_t *host_status;    // pinned host memory: error bits, settling steps
+    RecycleHeader *hdr, want;
+    int32_t recycle;         // *hdr may say that the buffers hold this kernel's last result
+    int32_t ring_words, low_words, seed_words;     // LDS: ring, graph inputs (8 bytes each), targets (4 bytes each)
+};
+// what k_check_graph_ranges finds out for it: status words from kStatusRing on
+constexpr int kStatusRing = 20;      // [0] != 0: outputs are not one run; [1] graph inputs, [2] dist, [3] span64 (maxima)
+constexpr int kRingExtraWords = 1 + kWave;
+inline int64_t ring_words(int waves, int dist, int span64)
+{
+    const int64_t need = (int64_t)dist + 3 * (int64_t)waves * span64;
+    int64_t r = 64 * waves;
+    while (r < need) r *= 2;
+    return r;
+}
+hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, hipStream_t s);
 // One sweep over all operators re-deriving K and pushing new bits to the inputs; *changed |= 1 if any.
 hipError_t launch_fix_sweep(const GraphView &g, u64 *M, u64 *K, uint8_t *flags, int32_t *changed, int grid_blocks, hipStream_t s);
 

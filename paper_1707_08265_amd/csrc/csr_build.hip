@@ -281,25 +281,58 @@ __device__ __forceinline__ int find_graph(const int64_t *off, int num_graphs, in
     return lo;
 }
 
+// status[w] = max(status[w], v over the wave), v >= 0: one look, and an atomic only where it would change something
+__device__ __forceinline__ void raise_status(int32_t *status, int v)
+{
+    const int m = wave_max(v);
+    if (lane_id() == 0 && m > load_coherent(status)) atomicMax(status, m);
+}
+
 // also_topological: the topological precondition is checked in the same walk (see k_check_topological), which
 // spares a packed batch a second pass over its input edges.
-__global__ __launch_bounds__(256) void k_check_graph_ranges(GraphView g, int32_t *error, bool also_topological)
+// The walk also finds out whether and how the ring sweep can take the graphs (status words from kStatusRing on; see
+// ring_sweep.hip): are the outputs of every graph one run of tensors that ends with its last one, how many tensors
+// lie before that run, how far below the end of its own outputs does an operator read, and how many outputs do 64
+// neighbouring operators have.  A single graph (op_off == NULL) is walked for this alone.
+__global__ __launch_bounds__(256) void k_check_graph_ranges(GraphView g, int32_t *status, bool also_topological)
 {
     // a wave walks a contiguous stretch of operators 64 at a time, so a lane's graph index only ever steps
     // forward: one binary search per lane, not one per operator
+    const bool batched = g.num_graphs > 1;
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
     const int64_t wave_id = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
     const int64_t per = (((int64_t)g.num_ops + waves - 1) / waves + kWave - 1) / kWave * kWave;
     const int64_t first = wave_id * per, last = min(first + per, (int64_t)g.num_ops);
-    bool bad = false, late = false;
+    bool bad = false, late = false, scattered = false;
+    int low = 0, dist = 0, span64 = 0;
     int gi = -1;
+    int64_t lo = 0, hi = g.num_tensors, o_lo = 0, o_hi = g.num_ops;
+    int32_t shift = 0, t_first = 0;                         // output edge e should be tensor e + shift
     for (int64_t o = first + lane_id(); o < last; o += kWave) {
-        if (gi < 0) gi = find_graph(g.op_off, g.num_graphs, o);
-        while (o >= g.op_off[gi + 1]) ++gi;                 // op_off[num_graphs] == num_ops > o: stops in range
-        const int64_t lo = g.t_off[gi], hi = g.t_off[gi + 1];
+        if (gi < 0 || o >= o_hi) {
+            if (batched) {
+                if (gi < 0) gi = find_graph(g.op_off, g.num_graphs, o);
+                while (o >= g.op_off[gi + 1]) ++gi;         // op_off[num_graphs] == num_ops > o: stops in range
+                lo = g.t_off[gi];
+                hi = g.t_off[gi + 1];
+                o_lo = g.op_off[gi];
+                o_hi = g.op_off[gi + 1];
+            } else {
+                gi = 0;
+            }
+            shift = (int32_t)hi - g.out_rowptr[o_hi];
+            t_first = g.out_rowptr[o_lo] + shift;
+            if (t_first < lo) scattered = true;             // more outputs than tensors
+            low = max(low, t_first - (int32_t)lo);
+        }
+        const int32_t ob = g.out_rowptr[o], oe = g.out_rowptr[o + 1];
         for (int32_t e = g.in_rowptr[o]; e < g.in_rowptr[o + 1]; ++e) {
             const int32_t t = g.in_idx[e];
             if (t < lo || t >= hi) bad = true;
+            if (t >= t_first) {
+                if (t >= ob + shift) scattered = true;      // not written before, if the outputs are one run
+                dist = max(dist, oe + shift - t);
+            }
             if (also_topological && t >= 0 && t < g.num_tensors) {
                 const int32_t pr = g.prod1[t];
                 if (pr >= 0) {
@@ -310,18 +343,26 @@ __global__ __launch_bounds__(256) void k_check_graph_ranges(GraphView g, int32_t
                 }
             }
         }
-        for (int32_t e = g.out_rowptr[o]; e < g.out_rowptr[o + 1]; ++e)
-            if (g.out_idx[e] < lo || g.out_idx[e] >= hi) bad = true;
+        for (int32_t e = ob; e < oe; ++e) {
+            const int32_t t = g.out_idx[e];
+            if (t < lo || t >= hi) bad = true;
+            if (t != e + shift) scattered = true;
+        }
+        if (((o - o_lo) & (kWave - 1)) == 0) span64 = max(span64, g.out_rowptr[min(o + kWave, o_hi)] - ob);
     }
-    if (bad || late) atomicOr(error, (bad ? kErrCrossGraph : 0) | (late ? kErrTopo : 0));
+    if (bad || late) atomicOr(&status[0], (bad ? kErrCrossGraph : 0) | (late ? kErrTopo : 0));
+    raise_status(&status[kStatusRing], scattered ? 1 : 0);
+    raise_status(&status[kStatusRing + 1], low);
+    raise_status(&status[kStatusRing + 2], dist);
+    raise_status(&status[kStatusRing + 3], span64);
 }
 
-hipError_t launch_check_graph_ranges(const GraphView &g, int32_t *error, bool also_topological, hipStream_t s)
+hipError_t launch_check_graph_ranges(const GraphView &g, int32_t *status, bool also_topological, hipStream_t s)
 {
-    if (g.num_ops == 0 || g.num_graphs <= 1) return hipSuccess;
+    if (g.num_ops == 0) return hipSuccess;
     int64_t blocks = ((int64_t)g.num_ops + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_check_graph_ranges, dim3((unsigned)blocks), dim3(256), 0, s, g, error, also_topological);
+    hipLaunchKernelGGL(k_check_graph_ranges, dim3((unsigned)blocks), dim3(256), 0, s, g, status, also_topological);
     return hipGetLastError();
 }
 

@@ -1,0 +1,540 @@
+// Descending sweep of graphs whose tensors are numbered as they are created (operator after operator, no gaps) and
+// whose operators read recent tensors or graph inputs only -- recorded graphs that are long and thin.
+//
+// A tensor's consumers all have larger operator ids than its producer.  A workgroup of W waves walks one graph's
+// operators from the highest id down, 64 W at a time, and keeps M of the tensors around the place it has reached in
+// a ring in LDS: every input edge of the group falls into the ring or on a graph input, and M of the graph inputs
+// lives in LDS for the whole sweep.  So no push ever goes to memory, nothing is hashed, and no output of the walk
+// depends on a load of M: what is read from memory is the adjacency, once, and what is written is every word of M
+// and K, once, in runs of consecutive words.  Target bits are kept in registers (packed tensor and set) and dropped into
+// the ring when it comes to cover their tensor; nothing has to be cleared or seeded before the kernel starts.
+//
+// Dependencies inside a group: every lane ORs M of its operator's outputs, pushes the bits it had not seen into the
+// ring slots of those inputs that the group itself writes, and looks again until no lane sees a new bit; all other
+// inputs get their bits once, when the group is final.  A wave settles on its own first (LDS operations of a wave
+// complete in order, so that needs no barrier); barriers pass the bits on between waves, one more round for every hop
+// that crosses from one wave to another.
+//
+// What a graph must satisfy is found out when it is built (k_check_graph_ranges): operators in topological order,
+// outputs in one run up to the graph's last tensor, at most `low` graph inputs, no input further than `dist` below the
+// end of its operator's own outputs, at most `span64` outputs per 64 operators.  The ring holds dist + 3 W span64 tensors,
+// rounded up to a power of two: the group, everything it reads, and two groups of slack, so that a target bit may arrive
+// one group late.
+//
+// What bounds it.  One wave per graph and few graphs: the chain of LDS round trips, 270 cycles per settling step and
+// 4.4 steps per 64 operators whose inputs are drawn from the last 64 tensors (2 900 cycles per 64 operators in all; the hash
+// tables of k_sweep_graphs took 19 000).  4 096 graphs: the memory, 37 bytes per operator.  Measured on graphs of that
+// family, 64 sets, whole prune: 4 096 graphs of 20 000 operators 3.13 -> 1.18 ms, 96 of 3 001 0.49 -> 0.094, one of 20 000
+// 3.3 -> 0.28 (level by level before), one of 2 000 0.21 -> 0.052.
+#include <type_traits>
+
+#include "common.h"
+
+namespace dgn {
+
+// Per-set counts without a transpose per group: every lane counts, for its own operators, how often each of the 64
+// bits was set, in bit-sliced form (plane i holds bit i of all 64 counters).  Four masks are folded at a time with
+// full adders; only the resulting carry of weight 4 ripples through the higher planes.
+constexpr int kRingPlanes = 13;                     // counters up to 2^13 - 1 words of 64 operators per wave
+
+struct RingCount {
+    u64 plane[kRingPlanes];
+    u64 x0, x1, x2;                                 // masks waiting for the fourth
+};
+
+__device__ __forceinline__ void ring_add(u64 a, u64 b, u64 c, u64 &sum, u64 &carry)
+{
+    const u64 ab = a ^ b;
+    sum = ab ^ c;
+    carry = (ab & c) | (a & b);
+}
+
+__device__ __forceinline__ void ring_fold(RingCount &c, u64 x3, int planes_used)
+{
+    u64 s, ca, cb, cc;
+    ring_add(c.plane[0], c.x0, c.x1, s, ca);
+    ring_add(s, c.x2, x3, c.plane[0], cb);
+    ring_add(c.plane[1], ca, cb, c.plane[1], cc);
+#pragma unroll
+    for (int i = 2; i < kRingPlanes; ++i) {
+        if (i < planes_used) {                      // wave-uniform
+            const u64 t = c.plane[i] & cc;
+            c.plane[i] ^= cc;
+            cc = t;
+        }
+    }
+}
+
+// LDS words by their address: what a lane keeps for a slot is the operand of the LDS instruction itself
+typedef __attribute__((address_space(3))) u64 LdsWord;
+__device__ __forceinline__ LdsWord *lds_word(uint32_t addr) { return (LdsWord *)(uintptr_t)addr; }
+__device__ __forceinline__ u64 lds_read(uint32_t addr)
+{
+    return __hip_atomic_load(lds_word(addr), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_write(uint32_t addr, u64 v)
+{
+    __hip_atomic_store(lds_word(addr), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_or(uint32_t addr, u64 v)
+{
+    (void)__hip_atomic_fetch_or(lds_word(addr), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// What a lane knows of its operator before its turn comes.  Everything is fetched without a branch (lanes without an
+// operator, and inputs past the end of a row, read some neighbour's instead), so that the number of loads in flight is
+// known and a wait for one of them does not become a wait for all.  Offsets are 32-bit byte offsets from uniform bases.
+struct RingRow {
+    int ob, oe, ib, ie;                             // rows in out_idx / in_idx
+    int32_t t[4];                                   // its first four inputs
+};
+
+template <typename T> __device__ __forceinline__ T &at_byte(T *base, uint32_t off)
+{
+    return *reinterpret_cast<T *>(reinterpret_cast<char *>(const_cast<std::remove_const_t<T> *>(base)) + off);
+}
+
+// in_row / out_row: the row pointers of the graph's n operators; i: operator within the graph
+__device__ __forceinline__ void ring_bounds(const int32_t *in_row, const int32_t *out_row, RingRow &r, int i, int n)
+{
+    const uint32_t off = (uint32_t)min(max(i, 0), n - 1) * 4u;
+    r.ob = at_byte(out_row, off);
+    r.oe = at_byte(out_row, off + 4);
+    r.ib = at_byte(in_row, off);
+    r.ie = at_byte(in_row, off + 4);
+}
+
+__device__ __forceinline__ void ring_targets(const GraphView &g, RingRow &r)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r.t[j] = at_byte(g.in_idx, (uint32_t)min(r.ib + j, g.nnz_in - 1) * 4u);
+}
+
+// A zero that the compiler takes for a value of its own in every lane: added to an address that is the same in all lanes,
+// it keeps the load's result in a vector register until it is used (moved to a scalar one at once, as it would be, the
+// wave would wait for the load where it is issued).
+__device__ __forceinline__ uint32_t lane_zero()
+{
+    uint32_t z;
+    asm("v_mov_b32 %0, 0" : "=v"(z));
+    return z;
+}
+
+template <int W>
+__global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
+{
+    constexpr int N = W * kWave;
+    // [R] ring, [low] graph inputs, [1] a word that stays zero, [64] words that take what goes nowhere; targets
+    extern __shared__ u64 ring[];
+    __shared__ int s_flag[3];                       // "a push crossed waves", by round
+    __shared__ int s_total[W];                      // kept operators of each wave's word
+    __shared__ int s_err, s_relax;
+    __shared__ int32_t s_row[kWave + 1];            // the graph's target row pointers
+    const GraphView &g = a.g;
+    const int lane = lane_id(), wave = W > 1 ? (int)(threadIdx.x >> 6) : 0, tid = threadIdx.x;
+    const int gi = blockIdx.x;
+    const bool batched = g.num_graphs > 1;
+    const int64_t o_lo = batched ? g.op_off[gi] : 0;
+    const int n = (int)((batched ? g.op_off[gi + 1] : g.num_ops) - o_lo);
+    const int32_t t_lo = batched ? (int32_t)g.t_off[gi] : 0, t_hi = batched ? (int32_t)g.t_off[gi + 1] : g.num_tensors;
+    const int32_t *in_row = g.in_rowptr + o_lo, *out_row = g.out_rowptr + o_lo;
+    u64 *M = a.M + t_lo, *K = a.K + o_lo;
+    uint8_t *flags = a.flags + o_lo;
+    // outputs end with the graph's last tensor: output edge e is tensor e + shift; tensors below t_first are graph inputs
+    const int32_t shift = t_hi - out_row[n];
+    const int32_t t_first = out_row[0] + shift;
+    // LDS: tensor t sits in the ring at slot t mod R, R a power of two, or among the inputs at t - t_lo
+    const int R = a.ring_words;
+    const uint32_t base = (uint32_t)(uintptr_t)(LdsWord *)ring;
+    const uint32_t low_at = base + (uint32_t)(R - t_lo) * 8u, zero_at = base + (uint32_t)(R + a.low_words) * 8u;
+    const uint32_t nowhere = zero_at + 8u + (uint32_t)lane * 8u;
+    uint32_t *seeds = reinterpret_cast<uint32_t *>(ring + R + a.low_words + 1 + kWave);
+    auto slot_of = [&](int32_t t) { return base + (uint32_t)(t & (R - 1)) * 8u; };
+    auto low_of = [&](int32_t t) { return low_at + (uint32_t)t * 8u; };
+    static_assert(kRingExtraWords == 1 + kWave, "words behind the inputs");
+    const bool found = a.recycle && same_header(*a.hdr, a.want);      // words that were zero need not be written again
+    for (int i = tid; i <= R + a.low_words; i += N) ring[i] = 0;
+    if (tid < 3) s_flag[tid] = 0;
+    if (tid == 0) s_err = s_relax = 0;
+
+    // the graph's targets, packed: tensor relative to t_lo in the upper 26 bits, set in the lower 6
+    for (int q = tid; q <= a.num_sets; q += N) s_row[q] = a.tgt_rowptr[(int64_t)gi * a.num_sets + q];
+    __syncthreads();
+    const int64_t j0 = max(s_row[0], 0), j1 = min((int64_t)s_row[a.num_sets], a.num_targets);
+    const bool from_m = j1 - j0 > a.seed_words || t_hi - t_lo >= (1 << 26);          // too many: by way of M itself
+    if (from_m) {
+        for (int64_t t = tid; t < t_hi - t_lo; t += N) store_coherent(&M[t], (u64)0);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    }
+    __syncthreads();
+    int err = 0, lowest = 0x7fffffff;               // lowest: smallest target of this thread, relative to t_lo
+    for (int64_t j = j0 + tid; j < j1; j += N) {
+        uint32_t packed = 0xffffffffu;
+        int lo = 0, hi = a.num_sets;                // last set whose row starts at or before j
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (s_row[mid] <= j) lo = mid; else hi = mid;
+        }
+        const int32_t t = a.tgt_idx[j];
+        if (!(s_row[lo] <= j && j < s_row[lo + 1])) {
+            // (an entry that belongs to no set)
+        } else if (t < t_lo || t >= t_hi) {
+            err |= t < 0 || t >= g.num_tensors ? kErrIdRange : kErrCrossGraph;
+        } else if (from_m) {
+            (void)atomicOr(&a.M[t], (u64)1 << lo);
+        } else if (t < t_first) {
+            lds_or(low_of(t), (u64)1 << lo);
+        } else {
+            lowest = min(lowest, t - t_lo);
+            packed = ((uint32_t)(t - t_lo) << 6) | (uint32_t)lo;
+        }
+        if (!from_m) seeds[j - j0] = packed;
+    }
+    const int n_seeds = from_m || j1 < j0 ? 0 : (int)(j1 - j0);
+    if (err) atomicOr(&s_err, err);
+    lowest = -wave_max(-lowest);
+    const int32_t lowest_seed = from_m ? -1 : lowest == 0x7fffffff ? lowest : t_lo + lowest;     // (none: beyond every tensor)
+    if (from_m) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (from_m)
+        for (int32_t t = t_lo + tid; t < t_first; t += N) lds_write(low_of(t), load_coherent(&a.M[t]));
+    // target bits of the tensors [from, to), which the ring has come to cover.  A thread looks at the targets that it put
+    // into LDS itself only if they are its wave's (the lowest one is known per wave).
+    auto cover = [&](int32_t from, int32_t to) {
+        if (to <= lowest_seed) return;                       // wave-uniform
+        if (from_m) {
+            for (int32_t t = max(from, t_first) + tid; t < to; t += N) {
+                const u64 m = load_coherent(&a.M[t]);
+                if (m) lds_or(slot_of(t), m);
+            }
+        } else {
+            for (int i = tid; i < n_seeds; i += N) {
+                const uint32_t v = seeds[i];
+                const int32_t t = t_lo + (int32_t)(v >> 6);
+                if (v != 0xffffffffu && t >= from && t < to) lds_or(slot_of(t), (u64)1 << (v & 63));
+            }
+        }
+    };
+    cover(t_hi - R, t_hi);
+    int32_t cov_lo = t_hi - R, cov_hi = cov_lo;              // tensors [cov_lo, cov_hi): their target bits are still to come
+    __syncthreads();
+
+    RingCount cnt;
+#pragma unroll
+    for (int p = 0; p < kRingPlanes; ++p) cnt.plane[p] = 0;
+    cnt.x0 = cnt.x1 = cnt.x2 = 0;
+    const int n_words = (n + kWave - 1) >> 6;
+    const int steps = (n_words + W - 1) / W;
+    const int planes_used = 33 - __builtin_clz((unsigned)steps | 1u);
+    u64 *bits = a.bits + (o_lo >> 6) + gi;                   // this graph's words
+    int32_t *cum = a.cum + (o_lo >> 6) + gi;
+    int done = 0;                                            // operators kept in the groups so far
+    int relax = 0;                                           // settling steps (statistics)
+    int round = 0;
+    int word = n_words - 1 - wave;                           // this wave's word of 64 operators
+    int32_t z_hi = t_hi, z_next = 0;                         // the group's outputs are [z_lo, z_hi); z_next: row pointer as loaded
+    const uint32_t vz = lane_zero();
+    RingRow cur{}, nxt{}, nxt2{};
+    auto group_first = [&](int step) { return (uint32_t)max((n_words - (step + 1) * W) * kWave, 0); };   // first operator
+    if (steps > 0) {
+        ring_bounds(in_row, out_row, cur, word * kWave + lane, n);
+        ring_targets(g, cur);
+        ring_bounds(in_row, out_row, nxt, (word - W) * kWave + lane, n);
+        if (W > 1) z_next = at_byte(out_row, group_first(0) * 4u + vz);
+    }
+    for (int step = 0; step < steps; ++step, word -= W) {
+        const RingRow r = cur;
+        const int32_t z_lo = __builtin_amdgcn_readfirstlane(W > 1 ? z_next : r.ob) + shift;
+        const int i = word * kWave + lane;                   // this lane's operator
+        const bool valid = i < n && (W == 1 || word >= 0);
+        const int n_out = valid ? r.oe - r.ob : 0, n_in = valid ? r.ie - r.ib : 0;
+        // fetch ahead: inputs of the next group (its bounds are here), bounds of the one after
+        ring_targets(g, nxt);
+        ring_bounds(in_row, out_row, nxt2, i - 2 * N, n);
+        if (W > 1) z_next = at_byte(out_row, group_first(step + 1) * 4u + vz);
+        u64 before = ~(u64)0;
+        if (found) before = at_byte(bits, (uint32_t)max(word, 0) * 8u + vz);
+
+        const int32_t z0 = r.ob + shift;
+        const uint32_t s0 = n_out > 0 ? slot_of(z0) : zero_at, s1 = n_out > 1 ? slot_of(z0 + 1) : zero_at;
+        const int32_t wave_lo = W > 1 ? __builtin_amdgcn_readfirstlane(z0) : z_lo;       // outputs of this wave start here
+        const bool many = ballot64(n_out > 2 || n_in > 4) != 0;          // some operator needs the loops over more than that
+        const bool any2 = ballot64(n_in > 2) != 0, any3 = ballot64(n_in > 3) != 0;
+        // Where the inputs' bits go: to the ones that the group itself writes while it settles (in), to all others when
+        // it is final (out); a lane without such an input writes to a word of its own that nobody reads.
+        // own: some input is written by this wave, crosses: by another wave of the group.
+        bool own = false, crosses = false;
+        uint32_t in[4], out[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int32_t t = r.t[j];
+            const bool is = j < n_in, inside = is && t >= z_lo;
+            const uint32_t at = t >= t_first ? slot_of(t) : low_of(t);
+            in[j] = inside ? at : nowhere;
+            out[j] = is && !inside ? at : nowhere;
+            own |= inside && t >= wave_lo;
+            if (W > 1) crosses |= inside && t < wave_lo;
+        }
+        auto push = [&](const uint32_t (&at)[4], u64 bits) {
+            lds_or(at[0], bits);
+            lds_or(at[1], bits);
+            if (any2) lds_or(at[2], bits);
+            if (any3) lds_or(at[3], bits);
+        };
+        u64 k = 0, m0, m1;
+        for (;;) {
+            bool crossed = false;
+            if (!many) {
+                for (;;) {
+                    m0 = lds_read(s0);
+                    m1 = lds_read(s1);
+                    const u64 m = m0 | m1, nb = m & ~k;
+                    k = m;                                   // (the words only ever gain bits)
+                    ++relax;
+                    if (nb) push(in, nb);
+                    if (W > 1) crossed |= nb && crosses;
+                    __builtin_amdgcn_wave_barrier();
+                    if (ballot64(nb && own) == 0) break;
+                }
+            } else {
+                for (;;) {
+                    m0 = lds_read(s0);
+                    m1 = lds_read(s1);
+                    u64 m = m0 | m1;
+                    for (int j = 2; j < n_out; ++j) m |= lds_read(slot_of(z0 + j));
+                    const u64 nb = m & ~k;
+                    k = m;
+                    ++relax;
+                    bool again = nb && own;
+                    if (nb) {
+                        push(in, nb);
+                        if (W > 1) crossed |= crosses;
+                        for (int j = 4; j < n_in; ++j) {
+                            const int32_t t = g.in_idx[r.ib + j];
+                            if (t >= z_lo) {
+                                lds_or(slot_of(t), nb);
+                                again |= t >= wave_lo;
+                                if (W > 1) crossed |= t < wave_lo;
+                            }
+                        }
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    if (ballot64(again) == 0) break;
+                }
+            }
+            if (W == 1) break;
+            const int fl = round % 3;
+            if (tid == 0) s_flag[(round + 1) % 3] = 0;
+            if (ballot64(crossed) != 0 && lane == 0) s_flag[fl] = 1;
+            __syncthreads();
+            ++round;
+            if (s_flag[fl] == 0) break;                      // the same in every thread
+        }
+        if (k) {                                             // the group is final
+            push(out, k);
+            if (many)
+                for (int j = 4; j < n_in; ++j) {
+                    const int32_t t = g.in_idx[r.ib + j];
+                    if (t < z_lo) lds_or(t >= t_first ? slot_of(t) : low_of(t), k);
+                }
+        }
+        cover(cov_lo, cov_hi);
+        const u64 bit_word = ballot64(k != 0);
+        if ((bit_word | before) != 0) {
+            const uint32_t mo = (uint32_t)(z0 - t_lo) * 8u;
+            if (valid) {
+                at_byte(K, (uint32_t)i * 8u) = k;
+                at_byte(flags, (uint32_t)i) = k != 0;
+            }
+            if (n_out > 0) at_byte(M, mo) = m0;
+            if (n_out > 1) at_byte(M, mo + 8) = m1;
+            if (many)
+                for (int j = 2; j < n_out; ++j) at_byte(M, mo + 8u * j) = lds_read(slot_of(z0 + j));
+        }
+        if (valid && a.flags2) a.flags2[o_lo + i] = k != 0;
+        // the outputs' slots now stand for the tensors R below
+        if (n_out > 0) lds_write(s0, 0);
+        if (n_out > 1) lds_write(s1, 0);
+        if (many)
+            for (int j = 2; j < n_out; ++j) lds_write(slot_of(z0 + j), 0);
+        cov_hi = z_hi - R;
+        cov_lo = z_lo - R;
+        z_hi = z_lo;
+        if (a.pq) {
+            switch (step & 3) {                              // uniform
+            case 0: cnt.x0 = k; break;
+            case 1: cnt.x1 = k; break;
+            case 2: cnt.x2 = k; break;
+            default: ring_fold(cnt, k, planes_used); break;
+            }
+        }
+        cur = nxt;
+        nxt = nxt2;
+        // running count over the graph's words, highest first
+        const int c = __popcll(bit_word);
+        int upto = c, all = c;
+        if (W > 1) {
+            if (lane == 0) s_total[wave] = c;
+            __syncthreads();
+            upto = all = 0;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const int cw = s_total[w];
+                if (w <= wave) upto += cw;
+                all += cw;
+            }
+        }
+        if (lane == 0 && (W == 1 || word >= 0)) {
+            at_byte(bits, (uint32_t)word * 8u) = bit_word;
+            at_byte(cum, (uint32_t)word * 4u) = done + upto;       // operators kept in this word and above
+        }
+        done += all;
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    for (int32_t t = t_lo + tid; t < t_first; t += N) a.M[t] = lds_read(low_of(t));
+    if (a.pq) {
+        if (steps & 3) {                                     // masks still waiting: fold them with zeros for the rest
+            if ((steps & 3) < 3) cnt.x2 = 0;
+            if ((steps & 3) < 2) cnt.x1 = 0;
+            ring_fold(cnt, 0, planes_used);
+        }
+        u64 total = 0;                                       // lane q: operators of this wave's words kept for set q
+#pragma unroll
+        for (int p = 0; p < kRingPlanes; ++p)
+            if (p < planes_used)                             // wave-uniform
+                total += (u64)__popcll(wave_transpose64(cnt.plane[p])) << p;
+        if (W > 1) {                                         // (the ring is free now; it has at least N words)
+            ring[tid] = total;
+            __syncthreads();
+            total = 0;
+            if (wave == 0)
+                for (int w = 0; w < W; ++w) total += ring[w * kWave + lane];
+        }
+        if (wave == 0) a.pq[(int64_t)gi * 64 + lane] = (int64_t)total;
+    }
+    if (lane == 0) atomicAdd(&s_relax, relax);
+    __syncthreads();
+    if (tid == 0) {
+        a.graphs[gi] = make_int4(done, s_err, s_relax, found ? 1 : 0);
+        if (!batched) a.kept_count[0] = done;
+    }
+}
+
+// Packed batch: kept_count[1 + g] = operators kept in the graphs before g, [1 + G] and [0] = in all; error bits of all
+// graphs and the largest number of settling steps go to the entry behind the last graph's.  One workgroup.
+__global__ __launch_bounds__(1024) void k_ring_offsets(RingArgs a)
+{
+    __shared__ int wtot[16], s_err, s_relax;
+    const int lane = lane_id(), wave = threadIdx.x >> 6, G = a.g.num_graphs;
+    if (threadIdx.x == 0) s_err = s_relax = 0;
+    __syncthreads();
+    const int per = (G + 1023) / 1024, lo = min((int)threadIdx.x * per, G), hi = min(lo + per, G);
+    int sum = 0, err = 0, relax = 0;
+    for (int i = lo; i < hi; ++i) {
+        const int4 v = a.graphs[i];
+        sum += v.x;
+        err |= v.y;
+        relax = max(relax, v.z);
+    }
+    if (err) atomicOr(&s_err, err);
+    const int wrelax = wave_max(relax);
+    if (lane == 0) atomicMax(&s_relax, wrelax);
+    const int incl = wave_incl_scan(sum);
+    if (lane == kWave - 1) wtot[wave] = incl;
+    __syncthreads();
+    int run = incl - sum, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        if (w < wave) run += wtot[w];
+        all += wtot[w];
+    }
+    for (int i = lo; i < hi; ++i) {
+        a.kept_count[1 + i] = run;
+        run += a.graphs[i].x;
+    }
+    if (threadIdx.x == 0) {
+        a.kept_count[1 + G] = all;
+        a.kept_count[0] = all;
+        a.graphs[G] = make_int4(all, s_err, s_relax, a.graphs[0].w);
+    }
+}
+
+// Ordered compaction from the words and running counts of the sweep: the position of a kept operator is known from its
+// word alone, so a wave takes any word of its graph, four in flight.  The first workgroup also leaves the header
+// for recycling and hands the status to the host.
+constexpr int kRingScatterThreads = 256;
+
+__global__ __launch_bounds__(kRingScatterThreads) void k_ring_scatter(RingArgs a)
+{
+    const GraphView &g = a.g;
+    const int lane = lane_id(), gi = blockIdx.x;
+    const bool batched = g.num_graphs > 1;
+    if (gi == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        const int4 st = a.graphs[batched ? g.num_graphs : 0];
+        RecycleHeader h = a.want;
+        if (!a.recycle || st.y) h.magic = 0;
+        *a.hdr = h;
+        a.host_status[0] = st.y;
+        a.host_status[1] = st.z;
+        a.host_status[2] = st.w;
+    }
+    const int64_t o_lo = batched ? g.op_off[gi] : 0, o_hi = batched ? g.op_off[gi + 1] : g.num_ops;
+    if (o_hi <= o_lo) return;
+    const int64_t first = (o_lo >> 6) + gi, n_words = (o_hi - o_lo + kWave - 1) >> 6;        // the graph's words
+    const int64_t end = a.kept_count[batched ? gi + 2 : 0];
+    const int64_t waves = (int64_t)gridDim.y * (kRingScatterThreads / kWave);
+    const int64_t wave_id = (int64_t)blockIdx.y * (kRingScatterThreads / kWave) + (threadIdx.x >> 6);
+    for (int64_t w0 = wave_id; w0 < n_words; w0 += 4 * waves) {
+        u64 bits[4], k[4];
+        int cum[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int64_t w = w0 + c * waves;
+            bits[c] = w < n_words ? a.bits[first + w] : 0;
+            cum[c] = w < n_words ? a.cum[first + w] : 0;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const bool has = (bits[c] >> lane) & 1;
+            k[c] = has && a.kept_masks ? a.K[o_lo + (w0 + c * waves) * kWave + lane] : 0;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if ((bits[c] >> lane) & 1) {
+                const int64_t pos = end - cum[c] + __popcll(bits[c] & lanemask_lt());
+                a.kept_ops[pos] = (int32_t)(o_lo + (w0 + c * waves) * kWave + lane);
+                if (a.kept_masks) a.kept_masks[pos] = k[c];
+            }
+        }
+    }
+}
+
+template <int W> static hipError_t launch_ring_w(const RingArgs &a, size_t lds, hipStream_t s)
+{
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ring_sweep<W>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingMaxLds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_ring_sweep<W>), dim3((unsigned)a.g.num_graphs), dim3(W * kWave), lds, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, hipStream_t s)
+{
+    a.ring_words = (int32_t)ring_words(waves, dist, span64);
+    const size_t lds = (size_t)(a.ring_words + a.low_words + kRingExtraWords) * sizeof(u64) + (size_t)a.seed_words * sizeof(uint32_t);
+    hipError_t e = waves == 1 ? launch_ring_w<1>(a, lds, s) : waves == 4 ? launch_ring_w<4>(a, lds, s) : launch_ring_w<16>(a, lds, s);
+    if (e != hipSuccess) return e;
+    const int G = a.g.num_graphs;
+    if (G > 1) hipLaunchKernelGGL(k_ring_offsets, dim3(1), dim3(1024), 0, s, a);
+    // a wave per 16 words of the largest graph
+    const int64_t words = (max_graph_ops + 63) / 64 + 1;
+    int64_t split = (words + 63) / 64;
+    if (split > 256) split = 256;
+    hipLaunchKernelGGL(k_ring_scatter, dim3((unsigned)G, (unsigned)split), dim3(kRingScatterThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace dgn

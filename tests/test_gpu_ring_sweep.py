@@ -1,0 +1,117 @@
+"""GPU parity of the ring sweep (graphs whose tensors are numbered as they are created and that read recent tensors or
+graph inputs only): sizes at the edges of words, groups and the ring, operators with more outputs and inputs than a
+lane keeps in registers, graphs without operators, more targets than fit in LDS, recycled buffers."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+from helpers import targets_from_sets
+from test_gpu_parity import assert_same, oracle_prune
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dgn():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_1707_08265_amd as d
+    return d
+
+
+def recorded(rng, num_graphs, ops, window, out_max, in_max, num_inputs, empty_every=0):
+    """Packed graphs of 1..ops operators (exactly `ops` for a single graph), outputs 0..out_max numbered in order, inputs
+    from the last `window` tensors or the graph's inputs; every empty_every-th graph has tensors and no operator."""
+    op_off, t_off, io, it, oo, ot = [0], [0], [], [], [], []
+    for gi in range(num_graphs):
+        P = ops if num_graphs == 1 else int(rng.integers(1, ops + 1))
+        if empty_every and gi % empty_every == 0:
+            P = 0
+        lo = t_off[-1]
+        n_out = rng.integers(0 if out_max > 2 else 1, out_max + 1, P)
+        first = lo + num_inputs + np.cumsum(n_out) - n_out
+        fan = rng.integers(0, in_max + 1, P)
+        op = np.repeat(np.arange(P), fan)
+        back = rng.integers(1, window + 1, op.size)
+        t = np.where(rng.random(op.size) < 0.2, lo + rng.integers(0, num_inputs, op.size), np.maximum(first[op] - back, lo))
+        io.append(op_off[-1] + op)
+        it.append(t)
+        oo.append(op_off[-1] + np.repeat(np.arange(P), n_out))
+        ot.append(lo + num_inputs + np.arange(n_out.sum()))
+        op_off.append(op_off[-1] + P)
+        t_off.append(lo + num_inputs + int(n_out.sum()))
+    cat = lambda xs: np.concatenate(xs).astype(np.int32)  # noqa: E731
+    many = num_graphs > 1
+    return gg.Graph(op_off[-1], t_off[-1], cat(io), cat(it), cat(oo), cat(ot), num_graphs,
+                    np.asarray(op_off, np.int64) if many else None, np.asarray(t_off, np.int64) if many else None, "recorded")
+
+
+def draw_targets(rng, g, Q, most):
+    off = g.graph_tensor_offsets if g.num_graphs > 1 else [0, g.num_tensors]
+    sets = []
+    for gi in range(g.num_graphs):
+        lo, hi = int(off[gi]), int(off[gi + 1])
+        sets += [[int(t) for t in rng.integers(lo, hi, int(rng.integers(0, most + 1)))] for _ in range(Q)]
+    return targets_from_sets(sets, Q)
+
+
+def check(dgn, oracle, g, draws, swept=True):
+    import torch
+    dg = dgn.DeviceGraph.from_coo(g)
+    buf = dgn.PruneBuffers(dg, draws[0].num_sets)
+    for t in (buf.tensor_mask, buf.op_mask, buf.kept_masks, buf.per_query_count, buf.kept_count):
+        t.fill_(-1)
+    buf.op_flag.fill_(7)
+    for i, tg in enumerate(draws):
+        st = dgn.dgn_stats()
+        rc = buf.prune(torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda(), stats=st)
+        assert rc == 0, dgn.dgn_strerror(rc)
+        assert not swept or st.launches <= 3                             # the sweep and the ordered list, no levels
+        assert_same(buf.to_host(), oracle_prune(oracle, g, tg)[1], f"call {i}")
+
+
+# (graphs, operators, window, most outputs, most inputs, graph inputs): one wave, four waves and sixteen waves per graph
+@pytest.mark.parametrize("shape", [
+    (1, 1, 1, 1, 3, 1), (1, 64, 1, 1, 1, 4), (1, 65, 3, 2, 3, 4), (1, 256, 40, 2, 4, 16), (1, 257, 64, 2, 3, 16),
+    (1, 1023, 1, 1, 2, 2), (1, 1025, 90, 2, 4, 16), (1, 4097, 700, 5, 7, 30), (1, 16384, 64, 2, 3, 16),
+    (1, 16385, 64, 2, 3, 16), (3, 2000, 50, 2, 3, 16), (70, 300, 64, 2, 3, 16), (300, 200, 30, 3, 6, 5), (2100, 90, 64, 4, 5, 16)])
+def test_shapes(dgn, oracle, shape):
+    G, P, window, out_max, in_max, low = shape
+    rng = np.random.default_rng(P * 7 + G)
+    g = recorded(rng, G, P, window, out_max, in_max, low, empty_every=9 if G > 9 else 0)
+    Q = 64 if P % 2 else 5
+    check(dgn, oracle, g, [draw_targets(rng, g, Q, 3) for _ in range(4)])
+
+
+@pytest.mark.parametrize("G", [1, 100])
+def test_more_targets_than_fit_in_lds_go_through_the_masks(dgn, oracle, G):
+    rng = np.random.default_rng(G)
+    g = recorded(rng, G, 3000 if G == 1 else 400, 64, 2, 3, 16)
+    draws = [draw_targets(rng, g, 64, 100), draw_targets(rng, g, 64, 1)]
+    if G > 1:                                                            # one graph with far more than the others
+        few = draw_targets(rng, g, 64, 1)
+        n = np.diff(few.tgt_rowptr)
+        sets = [list(few.tgt_idx[a:a + k]) for a, k in zip(few.tgt_rowptr, n)]
+        lo, hi = int(g.graph_tensor_offsets[7]), int(g.graph_tensor_offsets[8])
+        sets[7 * 64 + 3] = [int(t) for t in rng.integers(lo, hi, 900)]
+        draws.append(targets_from_sets(sets, 64))
+    check(dgn, oracle, g, draws + draws[:1])
+
+
+def test_graphs_that_the_ring_cannot_hold_take_another_path(dgn, oracle):
+    """Tensor ids out of order, an unread tensor behind the last output, an input further back than LDS is large."""
+    import torch
+    rng = np.random.default_rng(3)
+    g = recorded(rng, 1, 3000, 64, 2, 3, 16)
+    tg = draw_targets(rng, g, 64, 2)
+    g2, tg2, _ = gg.relabel_tensors(g, tg, 5)
+    g3 = gg.Graph(g.num_ops, g.num_tensors + 1, g.in_op, g.in_tensor, g.out_op, g.out_tensor)
+    far = recorded(rng, 1, 30000, 64, 2, 3, 16)
+    far.in_tensor[-1] = far.out_tensor[0]
+    for h, t in ((g2, tg2), (g3, tg), (far, draw_targets(rng, far, 64, 2))):
+        dg = dgn.DeviceGraph.from_coo(h)
+        buf = dgn.PruneBuffers(dg, 64)
+        st = dgn.dgn_stats()
+        assert buf.prune(torch.from_numpy(t.tgt_rowptr).cuda(), torch.from_numpy(t.tgt_idx).cuda(), stats=st) == 0
+        assert st.launches > 3
+        assert_same(buf.to_host(), oracle_prune(oracle, h, t)[1], "another path")
