@@ -189,7 +189,7 @@ PruneScratch prune_scratch(void *mem, int64_t P, int64_t T, int32_t G, int64_t m
     S.log.seg_cap = (int32_t)lcap;
     S.log.entries = c.take<int32_t>((size_t)kMaxSeg * (size_t)lcap);
     if (G > 1 || P <= kRingMaxOps) {
-        const size_t words = (size_t)(P >> 6) + (size_t)G + 1;
+        const size_t words = (size_t)ring_bit_words(P, G);
         S.ring_bits = c.take<u64>(words);
         S.ring_cum = c.take<int32_t>(words);
         S.ring_graphs = c.take<int4>((size_t)G + 1);
@@ -561,7 +561,8 @@ int dgn_prune_workspace(const dgn_graph *g, int32_t num_sets, size_t *scratch_by
 //   How many waves: sixteen take a graph that has a compute unit to itself (20 000 operators in a chain of short hops:
 // 0.28 ms, four waves 0.30, one 0.40); four when all graphs are resident at once that way (1 500 graphs of 20 000 operators:
 // 0.95 ms, one wave 1.03, sixteen 2.13); one beyond (4 096 graphs: 1.18 ms, four waves 1.67).
-static int ring_waves(const dgn_graph *g, const dgn_options *o)
+// words: words of 64 sets (single graphs), a workgroup each.
+static int ring_waves(const dgn_graph *g, const dgn_options *o, int64_t words = 1)
 {
     if (!g->ring || (o && (o->traversal != 0 || o->incremental || o->recompute_keep))) return 0;
     const bool many = g->G >= kSweepMinGraphs;               // (such batches were always swept graph by graph)
@@ -571,13 +572,15 @@ static int ring_waves(const dgn_graph *g, const dgn_options *o)
         return ((size_t)ring_words(w, g->ring_dist, g->ring_span64) + (size_t)g->ring_low + kRingExtraWords) * sizeof(u64) +
                    kRingSeedWords * sizeof(uint32_t) <= kRingMaxLds;
     };
-    if (g->G <= g->num_cus && g->max_graph_ops > 4 * kWave && fits(16)) return 16;
-    if (g->G <= 8 * g->num_cus && fits(4)) return 4;
+    const int64_t groups = g->G > 1 ? g->G : words;
+    if (groups <= g->num_cus && g->max_graph_ops > 4 * kWave && fits(16)) return 16;
+    if (groups <= 8 * g->num_cus && fits(4)) return 4;
     return fits(1) ? 1 : 0;
 }
 
 // dgn_prune of graphs that the ring sweep takes: two launches (three for a packed batch), nothing to clear beforehand.
-static int ring_prune(const dgn_graph *g, int waves, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
+// words > 1: as many words of 64 sets of a single graph at once, num_sets in all.
+static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
                       const int32_t *tgt_idx, u64 *M, u64 *K, uint8_t *op_flag, int32_t *kept_ops, u64 *kept_masks,
                       int64_t *kept_count, int64_t *per_query_count, const PruneScratch &S, const dgn_options *options,
                       dgn_stats *stats, hipStream_t s, u64 *also_M, u64 *also_K)
@@ -595,10 +598,12 @@ static int ring_prune(const dgn_graph *g, int waves, int32_t num_sets, int64_t n
         FillRegion more[2] = {{also_M, (size_t)g->T * 8}, {also_K, (size_t)g->P * 8}};
         DGN_HIP(launch_clear(more, 2, s));
     }
-    uint8_t *flags = (op_flag && ((uintptr_t)op_flag & 7) == 0 && g->P % 8 == 0) ? op_flag : S.flagbuf;
+    // (words of sets: nothing is recycled, so nobody reads the flags back)
+    uint8_t *flags = words > 1 || (op_flag && ((uintptr_t)op_flag & 7) == 0 && g->P % 8 == 0) ? op_flag : S.flagbuf;
     RingArgs a{};
     a.g = g->v;
     a.num_sets = num_sets;
+    a.words = (int32_t)words;
     a.num_targets = num_targets;
     a.tgt_rowptr = tgt_rowptr;
     a.tgt_idx = tgt_idx;
@@ -621,7 +626,7 @@ static int ring_prune(const dgn_graph *g, int waves, int32_t num_sets, int64_t n
     a.low_words = g->ring_low;
     // targets of a graph that fit in LDS; a graph with more of them sends its targets through M
     const int64_t avg = num_targets / g->G;
-    a.seed_words = (int32_t)(g->G == 1 ? (avg < kRingSeedWords ? avg : kRingSeedWords)
+    a.seed_words = (int32_t)(g->G == 1 /* a word may own any part of them */ ? (avg < kRingSeedWords ? avg : kRingSeedWords)
                                        : (avg + avg / 2 + 64 < kRingSeedWords ? avg + avg / 2 + 64 : kRingSeedWords));
     int32_t *status = static_cast<int32_t *>(pin);
     status[0] = status[1] = status[2] = 0;
@@ -637,7 +642,7 @@ static int ring_prune(const dgn_graph *g, int waves, int32_t num_sets, int64_t n
         stats->level_trace_cap = user_cap;
         stats->launches = g->G > 1 ? 3 : 2;
         stats->levels = g->G < kSweepMinGraphs ? status[1] : 0;
-        stats->tensor_visits = g->P;
+        stats->tensor_visits = g->P * words;
         stats->recycled = status[2];
         if (ev) {
             DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_TRAVERSE], ev[1], ev[2]));
@@ -650,6 +655,28 @@ static int ring_prune(const dgn_graph *g, int waves, int32_t num_sets, int64_t n
     return error_bits_to_code(status[0]);
 }
 
+// What dgn_prune asks of its arguments; lays out its scratch.
+static int check_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
+                       const int32_t *tgt_idx, const uint64_t *tensor_mask, const uint64_t *op_mask, const int32_t *kept_ops,
+                       const uint64_t *kept_masks, const int64_t *kept_count, const int64_t *per_query_count, void *scratch,
+                       size_t scratch_bytes, const dgn_options *options, PruneScratch *S)
+{
+    if (!g) return DGN_ERR_NULL_PTR;
+    if (num_sets < 1 || num_sets > DGN_MAX_SETS) return DGN_ERR_TOO_MANY_SETS;
+    if (num_targets < 0) return DGN_ERR_INVALID_ARG;
+    if (num_targets > kMaxCount) return DGN_ERR_TOO_LARGE;
+    const int rc = check_options(options);
+    if (rc) return rc;
+    if (!tgt_rowptr || (num_targets > 0 && !tgt_idx) || !kept_count || !scratch) return DGN_ERR_NULL_PTR;
+    if ((g->T > 0 && !tensor_mask) || (g->P > 0 && (!op_mask || !kept_ops))) return DGN_ERR_NULL_PTR;
+    *S = prune_scratch(scratch, g->P, g->T, g->G, options ? options->max_queue_entries : 0);
+    if (scratch_bytes < S->bytes) return DGN_ERR_WORKSPACE_TOO_SMALL;
+    if (((uintptr_t)scratch | (uintptr_t)tensor_mask | (uintptr_t)op_mask | (uintptr_t)kept_masks |
+         (uintptr_t)kept_count | (uintptr_t)per_query_count) & 7)
+        return DGN_ERR_INVALID_ARG;
+    return DGN_OK;
+}
+
 // dgn_prune.  also_M [T] / also_K [P] (or NULL): two more arrays that the call zeroes with M and K -- all of them,
 // or, with recycled buffers, the words that the previous call's log and kept list name (the caller vouches that
 // they hold non-zero words nowhere else).
@@ -659,26 +686,17 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
                       size_t scratch_bytes, const dgn_options *options, dgn_stats *stats, dgn_stream stream,
                       uint64_t *also_M, uint64_t *also_K)
 {
-    if (!g) return DGN_ERR_NULL_PTR;
-    if (num_sets < 1 || num_sets > DGN_MAX_SETS) return DGN_ERR_TOO_MANY_SETS;
-    if (num_targets < 0) return DGN_ERR_INVALID_ARG;
-    if (num_targets > kMaxCount) return DGN_ERR_TOO_LARGE;
-    int rc = check_options(options);
+    PruneScratch S{};
+    int rc = check_prune(g, num_sets, num_targets, tgt_rowptr, tgt_idx, tensor_mask, op_mask, kept_ops, kept_masks, kept_count,
+                         per_query_count, scratch, scratch_bytes, options, &S);
     if (rc) return rc;
-    if (!tgt_rowptr || (num_targets > 0 && !tgt_idx) || !kept_count || !scratch) return DGN_ERR_NULL_PTR;
-    if ((g->T > 0 && !tensor_mask) || (g->P > 0 && (!op_mask || !kept_ops))) return DGN_ERR_NULL_PTR;
-    const PruneScratch S = prune_scratch(scratch, g->P, g->T, g->G, options ? options->max_queue_entries : 0);
-    if (scratch_bytes < S.bytes) return DGN_ERR_WORKSPACE_TOO_SMALL;
-    if (((uintptr_t)scratch | (uintptr_t)tensor_mask | (uintptr_t)op_mask | (uintptr_t)kept_masks |
-         (uintptr_t)kept_count | (uintptr_t)per_query_count) & 7)
-        return DGN_ERR_INVALID_ARG;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     u64 *M = reinterpret_cast<u64 *>(tensor_mask);
     u64 *K = reinterpret_cast<u64 *>(op_mask);
     const int ring = ring_waves(g, options);
     if (ring)
-        return ring_prune(g, ring, num_sets, num_targets, tgt_rowptr, tgt_idx, M, K, op_flag, kept_ops,
+        return ring_prune(g, ring, 1, num_sets, num_targets, tgt_rowptr, tgt_idx, M, K, op_flag, kept_ops,
                           reinterpret_cast<u64 *>(kept_masks), kept_count, per_query_count, S, options, stats, s,
                           reinterpret_cast<u64 *>(also_M), reinterpret_cast<u64 *>(also_K));
     const size_t pq_bytes = per_query_count ? sizeof(int64_t) * 64 * (size_t)(g->G > 1 ? g->G : 1) : 0;
@@ -1131,19 +1149,50 @@ int dgn_prune_words(const dgn_graph *g, int64_t num_sets, int64_t num_targets, c
     if (stats) total = *stats;
     total.levels = total.tensor_visits = total.launches = total.level_launches = 0;
     total.max_frontier = 0;
-    for (int64_t w = 0; w < words; ++w) {
-        const int32_t q = (int32_t)((num_sets - w * DGN_MAX_SETS) < DGN_MAX_SETS ? (num_sets - w * DGN_MAX_SETS) : DGN_MAX_SETS);
+    // Graphs that the ring sweep takes: a workgroup per word, as many words at once as have room in the scratch buffer for
+    // what the sweep leaves for the compaction (behind the log, nothing else is in use then).
+    PruneScratch S{};
+    int ring = 0;
+    int64_t at_once = 1;
+    if (words > 1) {
+        const int rc = check_prune(g, DGN_MAX_SETS, num_targets, tgt_rowptr, tgt_idx, tensor_mask, op_mask, kept_ops, kept_masks,
+                                   kept_count, per_query_count, scratch, scratch_bytes, options, &S);
+        if (rc) return rc;
+        if (ring_waves(g, options)) {
+            const size_t per = (size_t)ring_bit_words(g->P, 1);
+            char *room = reinterpret_cast<char *>(S.ring_bits);
+            const size_t bytes = S.bytes - (size_t)(room - static_cast<char *>(scratch));
+            at_once = (int64_t)((bytes - 3 * 256) / (per * (sizeof(u64) + sizeof(int32_t)) + sizeof(int4)));
+            at_once = at_once < 1 ? 1 : at_once < words ? at_once : words;
+            if (at_once > 1) {
+                Carver c(room);
+                S.ring_bits = c.take<u64>(per * (size_t)at_once);
+                S.ring_cum = c.take<int32_t>(per * (size_t)at_once);
+                S.ring_graphs = c.take<int4>((size_t)at_once);
+                ring = ring_waves(g, options, at_once);
+            }
+        }
+    }
+    for (int64_t w = 0; w < words; w += at_once) {
+        const int64_t left = num_sets - w * DGN_MAX_SETS;
+        const int64_t n_words = words - w < at_once ? words - w : at_once;
+        const int32_t q = (int32_t)(left < n_words * DGN_MAX_SETS ? left : n_words * DGN_MAX_SETS);
         // the sets of this word own entries [tgt_rowptr[64w], tgt_rowptr[64w + q]) of tgt_idx: the row
         // pointers hold absolute positions, so the slice is passed as it is and the seed step skips
-        // every entry that lies outside it
+        // every entry that lies outside it (several words at once: so does every word's workgroup)
         dgn_stats one{};
         if (stats) one = *stats;
-        const int rc = dgn_prune(g, q, num_targets, tgt_rowptr + w * DGN_MAX_SETS, tgt_idx,
-                                 tensor_mask ? tensor_mask + w * T : nullptr, op_mask ? op_mask + w * P : nullptr,
-                                 op_flag ? op_flag + w * P : nullptr, kept_ops ? kept_ops + w * P : nullptr,
-                                 kept_masks ? kept_masks + w * P : nullptr, kept_count ? kept_count + w : nullptr,
-                                 per_query_count ? per_query_count + w * 64 : nullptr, scratch, scratch_bytes, options,
-                                 stats ? &one : nullptr, stream);
+        uint64_t *M = tensor_mask ? tensor_mask + w * T : nullptr, *K = op_mask ? op_mask + w * P : nullptr;
+        uint64_t *masks = kept_masks ? kept_masks + w * P : nullptr;
+        uint8_t *flag = op_flag ? op_flag + w * P : nullptr;
+        int32_t *kept = kept_ops ? kept_ops + w * P : nullptr;
+        int64_t *count = kept_count ? kept_count + w : nullptr, *pq = per_query_count ? per_query_count + w * 64 : nullptr;
+        const int rc = ring ? ring_prune(g, ring, n_words, q, num_targets, tgt_rowptr + w * DGN_MAX_SETS, tgt_idx,
+                                         reinterpret_cast<u64 *>(M), reinterpret_cast<u64 *>(K), flag, kept,
+                                         reinterpret_cast<u64 *>(masks), count, pq, S, options, stats ? &one : nullptr,
+                                         static_cast<hipStream_t>(stream), nullptr, nullptr)
+                            : dgn_prune(g, q, num_targets, tgt_rowptr + w * DGN_MAX_SETS, tgt_idx, M, K, flag, kept, masks,
+                                        count, pq, scratch, scratch_bytes, options, stats ? &one : nullptr, stream);
         if (rc != DGN_OK) return rc;
         if (stats) {
             total.levels += one.levels;

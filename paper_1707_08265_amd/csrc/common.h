@@ -296,20 +296,21 @@ hipError_t launch_sweep_graphs(const GraphView &g, u64 *M, u64 *K, int64_t *per_
 constexpr size_t kRingMaxLds = 160 * 1024 - 1024;   // LDS of a compute unit less the kernel's own few words
 struct RingArgs {
     GraphView g;
-    int32_t num_sets;
+    int32_t num_sets;        // per graph; of a single graph any number, 64 to a word
+    int32_t words;           // single graph: words of 64 sets; every output array has a row per word
     int64_t num_targets;
     const int32_t *tgt_rowptr, *tgt_idx;
     u64 *M, *K;
-    uint8_t *flags;          // a byte per operator: K != 0
+    uint8_t *flags;          // a byte per operator: K != 0, or NULL
     uint8_t *flags2;         // the same once more, or NULL
     int32_t *kept_ops;
     u64 *kept_masks;         // may be NULL
     int64_t *kept_count;
     int64_t *pq;             // [G * 64], may be NULL
-    u64 *bits;               // [P / 64 + G + 1] a bit per operator, K != 0: words of 64 operators of one graph, graph g's
+    u64 *bits;               // [ring_bit_words(P, G)], per word of sets: a bit per operator, K != 0: words of 64 operators of one graph, graph g's
                              // from entry g + (its first operator) / 64 on
     int32_t *cum;            // for every such word: operators of the graph kept in it and above
-    int4 *graphs;            // [G + 1] per graph: operators kept, error bits, settling steps; all graphs
+    int4 *graphs;            // [G + 1], or [words]: per graph or word of sets: operators kept, error bits, settling steps; all graphs
     int32_t *host_status;    // pinned host memory: error bits, settling steps
     RecycleHeader *hdr, want;
     int32_t recycle;         // *hdr may say that the buffers hold this kernel's last result
@@ -318,6 +319,8 @@ struct RingArgs {
 // what k_check_graph_ranges finds out for it: status words from kStatusRing on
 constexpr int kStatusRing = 20;      // [0] != 0: outputs are not one run; [1] graph inputs, [2] dist, [3] span64 (maxima)
 constexpr int kRingExtraWords = 1 + kWave;
+// words of 64 operators of G graphs, one of them perhaps ragged in each
+__host__ __device__ inline int64_t ring_bit_words(int64_t P, int64_t G) { return (P >> 6) + G + 1; }
 inline int64_t ring_words(int waves, int dist, int span64)
 {
     const int64_t need = (int64_t)dist + 3 * (int64_t)waves * span64;

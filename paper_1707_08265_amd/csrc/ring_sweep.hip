@@ -21,6 +21,9 @@
 // rounded up to a power of two: the group, everything it reads, and two groups of slack, so that a target bit may arrive
 // one group late.
 //
+// More than 64 sets of a single graph are words of 64 that have nothing to do with each other: a workgroup each.  150 sets
+// on a graph of 20 000 operators, one word after the other before: 0.84 ms -> 0.30.
+//
 // What bounds it.  One wave per graph and few graphs: the chain of LDS round trips, 270 cycles per settling step and
 // 4.4 steps per 64 operators whose inputs are drawn from the last 64 tensors (2 900 cycles per 64 operators in all; the hash
 // tables of k_sweep_graphs took 19 000).  4 096 graphs: the memory, 37 bytes per operator.  Measured on graphs of that
@@ -132,14 +135,17 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
     __shared__ int32_t s_row[kWave + 1];            // the graph's target row pointers
     const GraphView &g = a.g;
     const int lane = lane_id(), wave = W > 1 ? (int)(threadIdx.x >> 6) : 0, tid = threadIdx.x;
-    const int gi = blockIdx.x;
     const bool batched = g.num_graphs > 1;
+    const int gi = batched ? blockIdx.x : 0, wd = batched ? 0 : blockIdx.x;         // graph of a batch, or word of 64 sets
+    const int num_sets = min(a.num_sets - wd * kWave, kWave);
+    const int64_t set0 = batched ? (int64_t)gi * num_sets : (int64_t)wd * kWave;    // first set of this workgroup
     const int64_t o_lo = batched ? g.op_off[gi] : 0;
     const int n = (int)((batched ? g.op_off[gi + 1] : g.num_ops) - o_lo);
     const int32_t t_lo = batched ? (int32_t)g.t_off[gi] : 0, t_hi = batched ? (int32_t)g.t_off[gi + 1] : g.num_tensors;
     const int32_t *in_row = g.in_rowptr + o_lo, *out_row = g.out_rowptr + o_lo;
-    u64 *M = a.M + t_lo, *K = a.K + o_lo;
-    uint8_t *flags = a.flags + o_lo;
+    u64 *all_M = a.M + (int64_t)wd * g.num_tensors;
+    u64 *M = all_M + t_lo, *K = a.K + (int64_t)wd * g.num_ops + o_lo;
+    uint8_t *flags = a.flags ? a.flags + (int64_t)wd * g.num_ops + o_lo : nullptr;
     // outputs end with the graph's last tensor: output edge e is tensor e + shift; tensors below t_first are graph inputs
     const int32_t shift = t_hi - out_row[n];
     const int32_t t_first = out_row[0] + shift;
@@ -158,9 +164,9 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
     if (tid == 0) s_err = s_relax = 0;
 
     // the graph's targets, packed: tensor relative to t_lo in the upper 26 bits, set in the lower 6
-    for (int q = tid; q <= a.num_sets; q += N) s_row[q] = a.tgt_rowptr[(int64_t)gi * a.num_sets + q];
+    for (int q = tid; q <= num_sets; q += N) s_row[q] = a.tgt_rowptr[set0 + q];
     __syncthreads();
-    const int64_t j0 = max(s_row[0], 0), j1 = min((int64_t)s_row[a.num_sets], a.num_targets);
+    const int64_t j0 = max(s_row[0], 0), j1 = min((int64_t)s_row[num_sets], a.num_targets);
     const bool from_m = j1 - j0 > a.seed_words || t_hi - t_lo >= (1 << 26);          // too many: by way of M itself
     if (from_m) {
         for (int64_t t = tid; t < t_hi - t_lo; t += N) store_coherent(&M[t], (u64)0);
@@ -170,7 +176,7 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
     int err = 0, lowest = 0x7fffffff;               // lowest: smallest target of this thread, relative to t_lo
     for (int64_t j = j0 + tid; j < j1; j += N) {
         uint32_t packed = 0xffffffffu;
-        int lo = 0, hi = a.num_sets;                // last set whose row starts at or before j
+        int lo = 0, hi = num_sets;                  // last set whose row starts at or before j
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
             if (s_row[mid] <= j) lo = mid; else hi = mid;
@@ -181,7 +187,7 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
         } else if (t < t_lo || t >= t_hi) {
             err |= t < 0 || t >= g.num_tensors ? kErrIdRange : kErrCrossGraph;
         } else if (from_m) {
-            (void)atomicOr(&a.M[t], (u64)1 << lo);
+            (void)atomicOr(&all_M[t], (u64)1 << lo);
         } else if (t < t_first) {
             lds_or(low_of(t), (u64)1 << lo);
         } else {
@@ -197,14 +203,14 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
     if (from_m) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (from_m)
-        for (int32_t t = t_lo + tid; t < t_first; t += N) lds_write(low_of(t), load_coherent(&a.M[t]));
+        for (int32_t t = t_lo + tid; t < t_first; t += N) lds_write(low_of(t), load_coherent(&all_M[t]));
     // target bits of the tensors [from, to), which the ring has come to cover.  A thread looks at the targets that it put
     // into LDS itself only if they are its wave's (the lowest one is known per wave).
     auto cover = [&](int32_t from, int32_t to) {
         if (to <= lowest_seed) return;                       // wave-uniform
         if (from_m) {
             for (int32_t t = max(from, t_first) + tid; t < to; t += N) {
-                const u64 m = load_coherent(&a.M[t]);
+                const u64 m = load_coherent(&all_M[t]);
                 if (m) lds_or(slot_of(t), m);
             }
         } else {
@@ -226,8 +232,9 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
     const int n_words = (n + kWave - 1) >> 6;
     const int steps = (n_words + W - 1) / W;
     const int planes_used = 33 - __builtin_clz((unsigned)steps | 1u);
-    u64 *bits = a.bits + (o_lo >> 6) + gi;                   // this graph's words
-    int32_t *cum = a.cum + (o_lo >> 6) + gi;
+    const int64_t at_word = (o_lo >> 6) + gi + wd * ring_bit_words(g.num_ops, 1);
+    u64 *bits = a.bits + at_word;                            // this graph's words
+    int32_t *cum = a.cum + at_word;
     int done = 0;                                            // operators kept in the groups so far
     int relax = 0;                                           // settling steps (statistics)
     int round = 0;
@@ -344,7 +351,7 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
             const uint32_t mo = (uint32_t)(z0 - t_lo) * 8u;
             if (valid) {
                 at_byte(K, (uint32_t)i * 8u) = k;
-                at_byte(flags, (uint32_t)i) = k != 0;
+                if (flags) at_byte(flags, (uint32_t)i) = k != 0;
             }
             if (n_out > 0) at_byte(M, mo) = m0;
             if (n_out > 1) at_byte(M, mo + 8) = m1;
@@ -392,7 +399,7 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    for (int32_t t = t_lo + tid; t < t_first; t += N) a.M[t] = lds_read(low_of(t));
+    for (int32_t t = t_lo + tid; t < t_first; t += N) all_M[t] = lds_read(low_of(t));
     if (a.pq) {
         if (steps & 3) {                                     // masks still waiting: fold them with zeros for the rest
             if ((steps & 3) < 3) cnt.x2 = 0;
@@ -411,13 +418,13 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
             if (wave == 0)
                 for (int w = 0; w < W; ++w) total += ring[w * kWave + lane];
         }
-        if (wave == 0) a.pq[(int64_t)gi * 64 + lane] = (int64_t)total;
+        if (wave == 0) a.pq[(int64_t)blockIdx.x * 64 + lane] = (int64_t)total;
     }
     if (lane == 0) atomicAdd(&s_relax, relax);
     __syncthreads();
     if (tid == 0) {
-        a.graphs[gi] = make_int4(done, s_err, s_relax, found ? 1 : 0);
-        if (!batched) a.kept_count[0] = done;
+        a.graphs[blockIdx.x] = make_int4(done, s_err, s_relax, found ? 1 : 0);
+        if (!batched) a.kept_count[wd] = done;
     }
 }
 
@@ -468,10 +475,16 @@ constexpr int kRingScatterThreads = 256;
 __global__ __launch_bounds__(kRingScatterThreads) void k_ring_scatter(RingArgs a)
 {
     const GraphView &g = a.g;
-    const int lane = lane_id(), gi = blockIdx.x;
+    const int lane = lane_id();
     const bool batched = g.num_graphs > 1;
-    if (gi == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-        const int4 st = a.graphs[batched ? g.num_graphs : 0];
+    const int gi = batched ? blockIdx.x : 0, wd = batched ? 0 : blockIdx.x;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        int4 st = a.graphs[batched ? g.num_graphs : 0];
+        for (unsigned w = 1; !batched && w < gridDim.x; ++w) {       // words of sets: errors of all, settling steps added up
+            const int4 more = a.graphs[w];
+            st.y |= more.y;
+            st.z += more.z;
+        }
         RecycleHeader h = a.want;
         if (!a.recycle || st.y) h.magic = 0;
         *a.hdr = h;
@@ -481,8 +494,12 @@ __global__ __launch_bounds__(kRingScatterThreads) void k_ring_scatter(RingArgs a
     }
     const int64_t o_lo = batched ? g.op_off[gi] : 0, o_hi = batched ? g.op_off[gi + 1] : g.num_ops;
     if (o_hi <= o_lo) return;
-    const int64_t first = (o_lo >> 6) + gi, n_words = (o_hi - o_lo + kWave - 1) >> 6;        // the graph's words
-    const int64_t end = a.kept_count[batched ? gi + 2 : 0];
+    const int64_t first = (o_lo >> 6) + gi + wd * ring_bit_words(g.num_ops, 1);              // the graph's words
+    const int64_t n_words = (o_hi - o_lo + kWave - 1) >> 6;
+    const int64_t end = a.kept_count[batched ? gi + 2 : wd];
+    const u64 *K = a.K + (int64_t)wd * g.num_ops;
+    int32_t *kept_ops = a.kept_ops + (int64_t)wd * g.num_ops;
+    u64 *kept_masks = a.kept_masks ? a.kept_masks + (int64_t)wd * g.num_ops : nullptr;
     const int64_t waves = (int64_t)gridDim.y * (kRingScatterThreads / kWave);
     const int64_t wave_id = (int64_t)blockIdx.y * (kRingScatterThreads / kWave) + (threadIdx.x >> 6);
     for (int64_t w0 = wave_id; w0 < n_words; w0 += 4 * waves) {
@@ -497,14 +514,14 @@ __global__ __launch_bounds__(kRingScatterThreads) void k_ring_scatter(RingArgs a
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const bool has = (bits[c] >> lane) & 1;
-            k[c] = has && a.kept_masks ? a.K[o_lo + (w0 + c * waves) * kWave + lane] : 0;
+            k[c] = has && kept_masks ? K[o_lo + (w0 + c * waves) * kWave + lane] : 0;
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             if ((bits[c] >> lane) & 1) {
                 const int64_t pos = end - cum[c] + __popcll(bits[c] & lanemask_lt());
-                a.kept_ops[pos] = (int32_t)(o_lo + (w0 + c * waves) * kWave + lane);
-                if (a.kept_masks) a.kept_masks[pos] = k[c];
+                kept_ops[pos] = (int32_t)(o_lo + (w0 + c * waves) * kWave + lane);
+                if (kept_masks) kept_masks[pos] = k[c];
             }
         }
     }
@@ -517,7 +534,7 @@ template <int W> static hipError_t launch_ring_w(const RingArgs &a, size_t lds, 
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingMaxLds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((k_ring_sweep<W>), dim3((unsigned)a.g.num_graphs), dim3(W * kWave), lds, s, a);
+    hipLaunchKernelGGL((k_ring_sweep<W>), dim3((unsigned)(a.g.num_graphs > 1 ? a.g.num_graphs : a.words)), dim3(W * kWave), lds, s, a);
     return hipGetLastError();
 }
 
@@ -533,7 +550,7 @@ hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_
     const int64_t words = (max_graph_ops + 63) / 64 + 1;
     int64_t split = (words + 63) / 64;
     if (split > 256) split = 256;
-    hipLaunchKernelGGL(k_ring_scatter, dim3((unsigned)G, (unsigned)split), dim3(kRingScatterThreads), 0, s, a);
+    hipLaunchKernelGGL(k_ring_scatter, dim3((unsigned)(G > 1 ? G : a.words), (unsigned)split), dim3(kRingScatterThreads), 0, s, a);
     return hipGetLastError();
 }
 
