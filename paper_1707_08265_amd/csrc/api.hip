@@ -1329,9 +1329,9 @@ int dgn_ignore_mask(const dgn_graph *g, const uint64_t *tensor_mask, const int32
     if (((uintptr_t)tensor_mask | (uintptr_t)kept_masks | (uintptr_t)kept_count | (uintptr_t)ignore_mask |
          (uintptr_t)ignore_count) & 7)
         return DGN_ERR_INVALID_ARG;
-    DGN_HIP(launch_ignore_mask(g->v, kept_ops, reinterpret_cast<const u64 *>(kept_masks), kept_count,
+    DGN_HIP(launch_ignore_mask(g->v, g->multi_producer, kept_ops, reinterpret_cast<const u64 *>(kept_masks), kept_count,
                                reinterpret_cast<const u64 *>(tensor_mask), reinterpret_cast<u64 *>(ignore_mask),
-                               ignore_count, g->num_cus * 8, static_cast<hipStream_t>(stream)));
+                               ignore_count, g->num_cus * 2, static_cast<hipStream_t>(stream)));
     return DGN_OK;
 }
 

@@ -359,7 +359,7 @@ struct CompactArgs {
 hipError_t launch_keep_compact(const CompactArgs &a, hipStream_t s, hipEvent_t *ev = nullptr);
 
 // Read-outs of a prune result (Sec. 3.2): ignore mask from the kept list; per-set operator lists.
-hipError_t launch_ignore_mask(const GraphView &g, const int32_t *kept_ops, const u64 *kept_masks, const int64_t *kept_count,
+hipError_t launch_ignore_mask(const GraphView &g, bool several_producers, const int32_t *kept_ops, const u64 *kept_masks, const int64_t *kept_count,
                               const u64 *M, u64 *ignore, int64_t *ignore_count, int grid_blocks, hipStream_t s);
 size_t set_lists_scratch_bytes(int64_t num_kept);
 hipError_t launch_set_lists(const int32_t *kept_ops, const u64 *kept_masks, int64_t num_kept, int64_t *set_rowptr,
@@ -380,18 +380,18 @@ hipError_t launch_keep_from_list(const GraphView &g, const int32_t *kept, const 
 hipError_t launch_forward_within(const GraphView &g, const int32_t *kept, const int64_t *kept_count, const u64 *B, u64 *F,
                                  int32_t *changed, int grid_blocks, hipStream_t s);
 
-// In-place structures (Algorithm 3).  counters: [0] = number of nodes with exactly one child,
+// In-place structures (Algorithm 3).  counters: [0] = number of nodes in `list`,
 // [1 + r] = doubling round r left some jump pointer alive.
 constexpr int kInplaceMaxRounds = 32;               // 2^32 links: longer than any chain of int32 ids
 struct InplaceBuffers {
     int32_t *child;                                 // the only child of a tensor, -1 none, -2 several
     int32_t *J[2];                                  // jump pointers, double buffered
-    int32_t *linkers;                               // nodes with exactly one child
+    int32_t *list;                                  // the nodes that an operator with one output reads (each once)
     int32_t *counters;
 };
 size_t inplace_scratch_bytes(int64_t T);
 InplaceBuffers inplace_buffers(void *scratch, int64_t T);
-// init, children, links (the state before the first doubling round)
+// init and children (the state before the first doubling round)
 hipError_t launch_inplace_setup(const GraphView &g, const u64 *K, u64 select, const int32_t *kept_ops,
                                 const int64_t *kept_count, int32_t *rename, int64_t *renamed_count,
                                 const InplaceBuffers &b, int grid_blocks, hipStream_t s);

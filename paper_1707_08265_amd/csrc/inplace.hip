@@ -14,11 +14,15 @@
 // Nodes are tensors; Child(x) = distinct tensors written by surviving operators that read x, where an
 // operator survives when (K[o] & select) != 0.  "Exactly one child" is decided without building the
 // sets: child[x] holds the only child seen so far and is set to "many" by whoever brings a second one.
+//
+// Only the two fills go over all tensors (100 M of them: 0.18 ms, the rate of a fill); everything else follows the pruned
+// graph: its nodes with links are listed when they are first offered a child, where a pass over all tensors looked for
+// them before (0.17 ms).  456 000 kept operators with 1.5 M inputs on that graph, whole call: 0.65 -> 0.43 ms.
 #include "common.h"
 
 namespace dgn {
 
-constexpr int kIpThreads = 256;
+constexpr int kIpFillThreads = 256;
 constexpr int kManyChildren = -2;                   // child[x]: -1 none yet, >= 0 the only child so far
 
 // p[0..n) = -1, with 16-byte stores over the aligned bulk
@@ -35,7 +39,7 @@ __device__ __forceinline__ void fill_minus_one(int32_t *p, int64_t n, int64_t gt
     if (gtid < n - done) p[done + gtid] = -1;
 }
 
-__global__ __launch_bounds__(kIpThreads) void k_inplace_init(int32_t *rename, int32_t *child, int64_t T,
+__global__ __launch_bounds__(kIpFillThreads) void k_inplace_init(int32_t *rename, int32_t *child, int64_t T,
                                                               int32_t *counters, int num_counters,
                                                               int64_t *renamed_count)
 {
@@ -49,72 +53,132 @@ __global__ __launch_bounds__(kIpThreads) void k_inplace_init(int32_t *rename, in
     }
 }
 
-// One surviving operator: the tensors it touches become nodes of the graph (rename[x] = x), and each
-// input learns the operator's output(s) as child.  child[x] only moves -1 -> id -> kManyChildren.
-__device__ __forceinline__ void offer_children(const GraphView &g, int64_t o, int32_t *rename, int32_t *child)
+// The claimed nodes of a workgroup are gathered in LDS, so that the list's counter in memory is bumped once per workgroup and
+// step, not once per wave (updates of one address take 11 ns each: a wave each would cost more than the pass itself).
+constexpr int kClaimCap = 4096;
+struct ClaimStage {
+    int32_t *buf;                                   // [kClaimCap]
+    int *count;                                     // claims of the workgroup since the last flush; past kClaimCap they
+                                                    // went to the list one by one
+    int32_t *list;
+    int32_t *list_count;
+};
+
+// 64 operators, one per lane (valid lanes only): the tensors they touch become nodes of the graph (rename[x] = x), and each
+// input learns its operator's output(s) as child.  child[x] only moves -1 -> id -> kManyChildren; the lane whose atomic
+// moved it away from -1 claims x, to exactly one lane per node.
+// The input edges of all lanes are spread evenly over the wave (prefix sum, then a running maximum over the marks where
+// an operator's edges begin): an edge is a chain of dependent accesses -- id, child word, atomic --, and with an operator
+// per lane a wave went through it as often as its operator with the most inputs asks for (0.25 -> 0.18 ms; what is left is
+// about five scattered accesses per edge at the chip's rate for those).
+__device__ __forceinline__ void offer_children(const GraphView &g, bool valid, int64_t o, int32_t *rename, int32_t *child,
+                                               int *s_mark, const ClaimStage &cs)
 {
-    int lo = 0x7fffffff, hi = -1;
-    for (int32_t e = g.out_rowptr[o]; e < g.out_rowptr[o + 1]; ++e) {
-        const int32_t u = g.out_idx[e];
-        rename[u] = u;
-        lo = min(lo, u);
-        hi = max(hi, u);
-    }
-    // An input learns the child on offer.  `seen`: what its child word held a moment ago (a stale value only
-    // costs an atomic).
-    auto offer = [&](int32_t x, int32_t seen) {
-        rename[x] = x;
-        if (hi < 0) return;                                 // an operator without outputs offers nothing
-        if (lo != hi) {                                     // two distinct children at once
-            __hip_atomic_store(&child[x], kManyChildren, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return;
+    constexpr int kNone = -1;                               // an operator without outputs offers nothing
+    const int lane = lane_id();
+    int eb = 0, deg = 0;
+    int32_t offered = kNone;
+    if (valid) {
+        const int4 r = g.orec[o];
+        eb = r.x;
+        deg = r.y;
+        const int n_out = r.w >= 0 ? r.w : -r.w;
+        int lo = 0x7fffffff, hi = -1;
+        for (int j = 0; j < n_out; ++j) {
+            const int32_t u = r.w >= 0 ? r.z + j : g.out_idx[r.z + j];
+            rename[u] = u;
+            lo = min(lo, u);
+            hi = max(hi, u);
         }
-        if (seen == lo || seen == kManyChildren) return;
-        const int32_t old = atomicCAS(&child[x], -1, lo);
-        if (old != -1 && old != lo && old != kManyChildren)
-            __hip_atomic_store(&child[x], kManyChildren, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    const bool look = hi >= 0 && lo == hi;                  // exactly one child on offer: the words are worth a look
-    const int32_t ib = g.in_rowptr[o], ie = g.in_rowptr[o + 1];
-    if (ie - ib <= 4) {
-        for (int32_t e = ib; e < ie; ++e) {
-            const int32_t x = g.in_idx[e];
-            offer(x, look ? child[x] : 0);
+        if (n_out > 0) offered = lo == hi ? lo : kManyChildren;
+    }
+    const int incl = wave_incl_scan(deg), excl = incl - deg;
+    const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    for (int w0 = 0; w0 < total; w0 += kWave) {             // wave-uniform
+        s_mark[lane] = 0;
+        __builtin_amdgcn_wave_barrier();
+        if (deg > 0 && incl > w0 && excl < w0 + kWave) s_mark[max(excl - w0, 0)] = lane + 1;
+        __builtin_amdgcn_wave_barrier();
+        const int owner = max(wave_incl_max(s_mark[lane]) - 1, 0);
+        __builtin_amdgcn_wave_barrier();
+        const int o_eb = __shfl(eb, owner, kWave), o_excl = __shfl(excl, owner, kWave);
+        const int32_t c = __shfl(offered, owner, kWave);
+        bool claimed = false;
+        int32_t x = 0;
+        if (w0 + lane < total) {
+            x = g.in_idx[o_eb + (w0 + lane - o_excl)];
+            rename[x] = x;
+            if (c == kManyChildren) {                       // two distinct children at once
+                __hip_atomic_store(&child[x], kManyChildren, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else if (c != kNone) {
+                const int32_t seen = child[x];              // (a stale value only costs an atomic)
+                if (seen != c && seen != kManyChildren) {
+                    const int32_t old = atomicCAS(&child[x], -1, c);
+                    claimed = old == -1;
+                    if (!claimed && old != c && old != kManyChildren)
+                        __hip_atomic_store(&child[x], kManyChildren, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
         }
-        return;
+        const u64 cm = ballot64(claimed);
+        if (cm) {
+            int base = 0;
+            if (lane == 0) base = atomicAdd(cs.count, __popcll(cm));
+            const int pos = __builtin_amdgcn_readfirstlane(base) + __popcll(cm & lanemask_lt());
+            if (claimed && pos < kClaimCap) cs.buf[pos] = x;
+            const u64 om = ballot64(claimed && pos >= kClaimCap);
+            if (om) {                                       // no room any more: straight into the list
+                int at = 0;
+                if (lane == 0) at = atomicAdd(cs.list_count, __popcll(om));
+                at = __builtin_amdgcn_readfirstlane(at);
+                if (claimed && pos >= kClaimCap) cs.list[at + __popcll(om & lanemask_lt())] = x;
+            }
+        }
     }
-    // Many inputs: four at a time, their ids and then their child words fetched together (past the end the last
-    // input is read again) -- one after the other, an operator with dozens of inputs holds its wave for three
-    // dependent accesses per input.
-    for (int32_t e0 = ib; e0 < ie; e0 += 4) {
-        int32_t x[4], seen[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x[j] = g.in_idx[min(e0 + j, ie - 1)];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) seen[j] = look ? child[x[j]] : 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (e0 + j < ie) offer(x[j], seen[j]);
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Whole workgroup, after every step: the gathered claims go to the list once half of the room is taken, or at the end.
+__device__ __forceinline__ void flush_claims(const ClaimStage &cs, int *s_base, bool last)
+{
+    __syncthreads();
+    const int n = min(*cs.count, kClaimCap);
+    __syncthreads();                                        // everyone has read the count before it changes again
+    if (n == 0 || (n <= kClaimCap / 2 && !last)) return;    // the same in every thread
+    if (threadIdx.x == 0) {
+        *s_base = atomicAdd(cs.list_count, n);
+        *cs.count = 0;
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x) cs.list[*s_base + i] = cs.buf[i];
+    __syncthreads();
 }
 
 // Surviving operators can be a few percent of all: a wave reads 512 masks, packs the ids of the
 // survivors into LDS and works on them 64 at a time, so that the dependent loads of the expansion
 // run with all lanes busy.
+constexpr int kIpThreads = 1024;
 constexpr int kIpWaves = kIpThreads / kWave;
 constexpr int kMaskRounds = 8;                      // masks per lane and step
 
-__global__ __launch_bounds__(kIpThreads) void k_inplace_children(GraphView g, const u64 *K, u64 select,
-                                                                  int32_t *rename, int32_t *child)
+__global__ __launch_bounds__(kIpThreads) void k_inplace_children(GraphView g, const u64 *K, u64 select, int32_t *rename,
+                                                                  int32_t *child, int32_t *list, int32_t *list_count)
 {
     __shared__ int32_t s_ops[kIpWaves][kWave * (kMaskRounds + 1)];
+    __shared__ int32_t s_claims[kClaimCap];
+    __shared__ int s_mark[kIpWaves][kWave];
+    __shared__ int s_count, s_base;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) s_count = 0;
+    __syncthreads();
+    const ClaimStage cs{s_claims, &s_count, list, list_count};
     int32_t *ops = s_ops[wave];
     int count = 0;                                          // wave-uniform
     const int64_t step = (int64_t)kWave * kMaskRounds;
     const int64_t steps = ((int64_t)g.num_ops + step - 1) / step;
-    const int64_t wave_id = (int64_t)blockIdx.x * kIpWaves + wave, num_waves = (int64_t)gridDim.x * kIpWaves;
-    for (int64_t st = wave_id; st < steps; st += num_waves) {
+    const int64_t num_waves = (int64_t)gridDim.x * kIpWaves;
+    for (int64_t st0 = (int64_t)blockIdx.x * kIpWaves; st0 < steps; st0 += num_waves) {      // whole workgroups stay in the loop
+        const int64_t st = st0 + wave;
         u64 k[kMaskRounds];
 #pragma unroll
         for (int r = 0; r < kMaskRounds; ++r) {
@@ -132,12 +196,14 @@ __global__ __launch_bounds__(kIpThreads) void k_inplace_children(GraphView g, co
         __builtin_amdgcn_wave_barrier();
         while (count >= kWave) {
             count -= kWave;
-            offer_children(g, ops[count + lane], rename, child);
+            offer_children(g, true, ops[count + lane], rename, child, s_mark[wave], cs);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+        flush_claims(cs, &s_base, false);
     }
-    if (lane < count) offer_children(g, ops[lane], rename, child);
+    offer_children(g, lane < count, lane < count ? ops[lane] : 0, rename, child, s_mark[wave], cs);
+    flush_claims(cs, &s_base, true);
 }
 
 // The same from the list of kept operators that the prune wrote (ascending ids of the operators with K != 0):
@@ -145,96 +211,68 @@ __global__ __launch_bounds__(kIpThreads) void k_inplace_children(GraphView g, co
 // whose mask misses `select` is skipped.
 __global__ __launch_bounds__(kIpThreads) void k_inplace_children_list(GraphView g, const u64 *K, u64 select,
                                                                        const int32_t *kept_ops, const int64_t *kept_count,
-                                                                       int32_t *rename, int32_t *child)
+                                                                       int32_t *rename, int32_t *child, int32_t *list,
+                                                                       int32_t *list_count)
 {
-    const int64_t kept = kept_count[0];
-    const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < kept; i += gsize) {
-        const int32_t o = kept_ops[i];
-        if ((K[o] & select) != 0) offer_children(g, o, rename, child);
-    }
-}
-
-// link[x] = the only child of x, or -1; nodes with a link are listed (gathered per workgroup in LDS, so
-// that the list's counter is bumped once per thousand entries, not once per wave).  Both jump buffers
-// are set for every node, so that a later round may read the pointer of a node that has no link.
-constexpr int kLinkItems = 4;                       // independent loads per thread and step
-constexpr int kLinkTile = kIpThreads * kLinkItems;
-
-__global__ __launch_bounds__(kIpThreads) void k_inplace_links(const int32_t *rename, const int32_t *child,
-                                                               int64_t T, int32_t *J0, int32_t *J1,
-                                                               int32_t *linkers, int32_t *num_linkers)
-{
-    __shared__ int32_t s_list[2 * kLinkTile];
+    __shared__ int32_t s_claims[kClaimCap];
+    __shared__ int s_mark[kIpWaves][kWave];
     __shared__ int s_count, s_base;
-    const int lane = lane_id();
     if (threadIdx.x == 0) s_count = 0;
     __syncthreads();
-    const int64_t tiles = (T + kLinkTile - 1) / kLinkTile;
-    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {          // whole workgroups stay in the loop
-        int32_t r[kLinkItems];
-#pragma unroll
-        for (int k = 0; k < kLinkItems; ++k) {
-            const int64_t x = t * kLinkTile + k * kIpThreads + threadIdx.x;
-            r[k] = x < T ? rename[x] : -1;
-        }
-#pragma unroll
-        for (int k = 0; k < kLinkItems; ++k) {
-            const int64_t x = t * kLinkTile + k * kIpThreads + threadIdx.x;
-            int32_t link = -1;
-            if (r[k] >= 0) {
-                const int32_t c = child[x];
-                if (c >= 0) link = c;
-                J0[x] = link;
-                J1[x] = -1;
-            }
-            const u64 has = ballot64(link >= 0);
-            if (has) {
-                int base = 0;
-                if (lane == 0) base = atomicAdd(&s_count, __popcll(has));
-                base = __shfl(base, 0, kWave);
-                if (link >= 0) s_list[base + __popcll(has & lanemask_lt())] = (int32_t)x;
-            }
-        }
-        __syncthreads();                                    // this tile's entries are in the list
-        const int n = s_count;                              // at most one tile's worth is added per step
-        __syncthreads();                                    // everyone has read the count before it changes again
-        if (n >= kLinkTile || t + gridDim.x >= tiles) {     // flush: the next tile needs the room, or this was the last
-            if (threadIdx.x == 0) {
-                s_base = n ? atomicAdd(num_linkers, n) : 0;
-                s_count = 0;
-            }
-            __syncthreads();
-            for (int i = threadIdx.x; i < n; i += kIpThreads) linkers[s_base + i] = s_list[i];
-            __syncthreads();
-        }
+    const ClaimStage cs{s_claims, &s_count, list, list_count};
+    const int64_t kept = kept_count[0];
+    const int64_t gsize = (int64_t)gridDim.x * kIpThreads;
+    for (int64_t base = (int64_t)blockIdx.x * kIpThreads; base < kept; base += gsize) {       // whole workgroups stay in the loop
+        const int64_t i = base + threadIdx.x;
+        const int32_t o = i < kept ? kept_ops[i] : 0;
+        const bool valid = i < kept && (K[o] & select) != 0;
+        offer_children(g, valid, o, rename, child, s_mark[threadIdx.x >> 6], cs);
+        flush_claims(cs, &s_base, false);
     }
+    flush_claims(cs, &s_base, true);
 }
 
-__global__ __launch_bounds__(kIpThreads) void k_inplace_round(const int32_t *linkers, const int32_t *num_linkers,
-                                                               const int32_t *Jcur, int32_t *Jnext, int32_t *rename,
-                                                               int32_t *active, int64_t *renamed_count)
+// One doubling round over the claimed nodes.  J_0 is the child word itself (below zero: no link); the later pointers are
+// kept for claimed nodes only, and child tells whether a node has one.  active[-1]: the round before left a pointer
+// alive (first: there is none before).
+__global__ __launch_bounds__(kIpThreads) void k_inplace_round(const int32_t *list, const int32_t *list_count, bool first,
+                                                               const int32_t *child, const int32_t *Jcur, int32_t *Jnext,
+                                                               int32_t *rename, int32_t *active, int64_t *renamed_count)
 {
-    const int n = *num_linkers;
-    const int gsize = gridDim.x * blockDim.x;
+    __shared__ int s_more, s_newly;
+    if (!first && active[-1] == 0) return;                  // (all pointers have run out: so has this round's)
+    const int n = *list_count;
+    const int gsize = gridDim.x * kIpThreads;
+    if ((int)(blockIdx.x * kIpThreads) >= n) return;
+    if (threadIdx.x == 0) s_more = s_newly = 0;
+    __syncthreads();
     bool more = false;
     int newly = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gsize) {
-        const int32_t u = linkers[i];
+    for (int i = blockIdx.x * kIpThreads + threadIdx.x; i < n; i += gsize) {
+        const int32_t u = list[i];
         const int32_t v = Jcur[u];
         int32_t next = -1;
         if (v >= 0) {
-            const int32_t a = rename[u];
+            const int32_t a = rename[u], link = child[v];
+            const int32_t j = first ? link : Jcur[v];       // (not a pointer when v has no link)
             const int32_t old = atomicMin(&rename[v], a);
             if (old == v && a < v) ++newly;                 // v carried its own name until now
-            next = Jcur[v];
+            if (link >= 0) next = j;
         }
         Jnext[u] = next;
         more |= next >= 0;
     }
-    if (ballot64(more) && lane_id() == 0) *active = 1;
+    const u64 mm = ballot64(more);
     const int wnew = wave_sum(newly);
-    if (wnew && lane_id() == 0 && renamed_count) atomicAdd((u64 *)renamed_count, (u64)wnew);
+    if (lane_id() == 0) {                                   // one update of each word in memory per workgroup
+        if (mm) s_more = 1;
+        if (wnew) atomicAdd(&s_newly, wnew);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (s_more) *active = 1;
+        if (s_newly && renamed_count) atomicAdd((u64 *)renamed_count, (u64)s_newly);
+    }
 }
 
 size_t inplace_scratch_bytes(int64_t T)
@@ -251,7 +289,7 @@ InplaceBuffers inplace_buffers(void *scratch, int64_t T)
     b.child = reinterpret_cast<int32_t *>(p); p += (t * 4 + 255) & ~(size_t)255;
     b.J[0] = reinterpret_cast<int32_t *>(p); p += (t * 4 + 255) & ~(size_t)255;
     b.J[1] = reinterpret_cast<int32_t *>(p); p += (t * 4 + 255) & ~(size_t)255;
-    b.linkers = reinterpret_cast<int32_t *>(p); p += (t * 4 + 255) & ~(size_t)255;
+    b.list = reinterpret_cast<int32_t *>(p); p += (t * 4 + 255) & ~(size_t)255;
     b.counters = reinterpret_cast<int32_t *>(p);
     return b;
 }
@@ -261,29 +299,28 @@ hipError_t launch_inplace_setup(const GraphView &g, const u64 *K, u64 select, co
                                 const InplaceBuffers &b, int grid_blocks, hipStream_t s)
 {
     const int64_t T = g.num_tensors, P = g.num_ops;
-    auto blocks_for = [&](int64_t n) {
-        int64_t nb = (n + kIpThreads - 1) / kIpThreads;
-        if (nb > (int64_t)grid_blocks) nb = (int64_t)grid_blocks;
-        return dim3((unsigned)(nb > 0 ? nb : 1));
-    };
-    hipLaunchKernelGGL(k_inplace_init, blocks_for(T), dim3(kIpThreads), 0, s, rename, b.child, T, b.counters,
+    // a thread per 16 bytes and array; the other passes: two workgroups of 1 024 threads per compute unit
+    int64_t nb = (T + kIpFillThreads * 4 - 1) / (kIpFillThreads * 4);
+    nb = nb < 1 ? 1 : nb > grid_blocks ? grid_blocks : nb;
+    hipLaunchKernelGGL(k_inplace_init, dim3((unsigned)nb), dim3(kIpFillThreads), 0, s, rename, b.child, T, b.counters,
                        kInplaceMaxRounds + 1, renamed_count);
+    int64_t blocks = (P + kIpThreads - 1) / kIpThreads;
+    if (blocks > grid_blocks / 4) blocks = grid_blocks / 4;
     if (P > 0 && kept_ops)
-        hipLaunchKernelGGL(k_inplace_children_list, dim3((unsigned)grid_blocks), dim3(kIpThreads), 0, s, g, K, select,
-                           kept_ops, kept_count, rename, b.child);
+        hipLaunchKernelGGL(k_inplace_children_list, dim3((unsigned)blocks), dim3(kIpThreads), 0, s, g, K, select,
+                           kept_ops, kept_count, rename, b.child, b.list, b.counters);
     else if (P > 0)
-        hipLaunchKernelGGL(k_inplace_children, blocks_for(P), dim3(kIpThreads), 0, s, g, K, select, rename, b.child);
-    if (T > 0)
-        hipLaunchKernelGGL(k_inplace_links, blocks_for(T), dim3(kIpThreads), 0, s, rename, b.child, T, b.J[0], b.J[1],
-                           b.linkers, b.counters);
+        hipLaunchKernelGGL(k_inplace_children, dim3((unsigned)blocks), dim3(kIpThreads), 0, s, g, K, select, rename, b.child,
+                           b.list, b.counters);
     return hipGetLastError();
 }
 
 hipError_t launch_inplace_round(int round, int32_t *rename, int64_t *renamed_count, const InplaceBuffers &b,
                                 int grid_blocks, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_inplace_round, dim3((unsigned)grid_blocks), dim3(kIpThreads), 0, s, b.linkers, b.counters,
-                       b.J[round & 1], b.J[(round & 1) ^ 1], rename, b.counters + 1 + round, renamed_count);
+    hipLaunchKernelGGL(k_inplace_round, dim3((unsigned)(grid_blocks / 4)), dim3(kIpThreads), 0, s, b.list, b.counters,
+                       round == 0, b.child, round == 0 ? b.child : b.J[round & 1], b.J[(round & 1) ^ 1], rename,
+                       b.counters + 1 + round, renamed_count);
     return hipGetLastError();
 }
 
