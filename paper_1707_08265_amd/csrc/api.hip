@@ -175,7 +175,8 @@ QueueGeom queue_geometry(int64_t T, int64_t max_entries)
     return QueueGeom{S, (int32_t)seg};
 }
 
-PruneScratch prune_scratch(void *mem, int64_t P, int64_t T, int32_t G, int64_t max_entries)
+// whole_queues: room for full queues also where max_entries makes them smaller
+PruneScratch prune_scratch(void *mem, int64_t P, int64_t T, int32_t G, int64_t max_entries, bool whole_queues = false)
 {
     Carver c(mem);
     PruneScratch S{};
@@ -197,7 +198,8 @@ PruneScratch prune_scratch(void *mem, int64_t P, int64_t T, int32_t G, int64_t m
     S.state = c.take<TravState>(2);
     S.ctr = c.take<TravCounters>(1);
     S.qg = queue_geometry(T, max_entries);
-    const size_t qn = (size_t)S.qg.S * (size_t)S.qg.seg_cap;
+    const QueueGeom room = whole_queues ? queue_geometry(T, 0) : S.qg;
+    const size_t qn = (size_t)room.S * (size_t)room.seg_cap;
     S.q0 = c.take<int32_t>(qn);
     S.q1 = c.take<int32_t>(qn);
     const size_t obw = (size_t)((P + 63) / 64);
@@ -659,7 +661,7 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
 static int check_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
                        const int32_t *tgt_idx, const uint64_t *tensor_mask, const uint64_t *op_mask, const int32_t *kept_ops,
                        const uint64_t *kept_masks, const int64_t *kept_count, const int64_t *per_query_count, void *scratch,
-                       size_t scratch_bytes, const dgn_options *options, PruneScratch *S)
+                       size_t scratch_bytes, const dgn_options *options, PruneScratch *S, bool whole_queues = false)
 {
     if (!g) return DGN_ERR_NULL_PTR;
     if (num_sets < 1 || num_sets > DGN_MAX_SETS) return DGN_ERR_TOO_MANY_SETS;
@@ -669,7 +671,7 @@ static int check_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets
     if (rc) return rc;
     if (!tgt_rowptr || (num_targets > 0 && !tgt_idx) || !kept_count || !scratch) return DGN_ERR_NULL_PTR;
     if ((g->T > 0 && !tensor_mask) || (g->P > 0 && (!op_mask || !kept_ops))) return DGN_ERR_NULL_PTR;
-    *S = prune_scratch(scratch, g->P, g->T, g->G, options ? options->max_queue_entries : 0);
+    *S = prune_scratch(scratch, g->P, g->T, g->G, options ? options->max_queue_entries : 0, whole_queues);
     if (scratch_bytes < S->bytes) return DGN_ERR_WORKSPACE_TOO_SMALL;
     if (((uintptr_t)scratch | (uintptr_t)tensor_mask | (uintptr_t)op_mask | (uintptr_t)kept_masks |
          (uintptr_t)kept_count | (uintptr_t)per_query_count) & 7)
@@ -679,7 +681,7 @@ static int check_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets
 
 // dgn_prune.  also_M [T] / also_K [P] (or NULL): two more arrays that the call zeroes with M and K -- all of them,
 // or, with recycled buffers, the words that the previous call's log and kept list name (the caller vouches that
-// they hold non-zero words nowhere else).
+// they hold non-zero words nowhere else).  Such a caller goes on to use the queues' room for lists of its own.
 static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
                       const int32_t *tgt_idx, uint64_t *tensor_mask, uint64_t *op_mask, uint8_t *op_flag, int32_t *kept_ops,
                       uint64_t *kept_masks, int64_t *kept_count, int64_t *per_query_count, void *scratch,
@@ -688,7 +690,7 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
 {
     PruneScratch S{};
     int rc = check_prune(g, num_sets, num_targets, tgt_rowptr, tgt_idx, tensor_mask, op_mask, kept_ops, kept_masks, kept_count,
-                         per_query_count, scratch, scratch_bytes, options, &S);
+                         per_query_count, scratch, scratch_bytes, options, &S, also_M != nullptr);
     if (rc) return rc;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1213,10 +1215,12 @@ struct BackwardScratch {
     u64 *B, *KB;
     int32_t *kept, *tgt_rowptr, *flags;
     int64_t *kept_count;
+    void *links;            // the lists of the forward stage: in the first stage's queues, which are free by then, or, where
+                            // those are smaller, behind the rest
     size_t bytes;
 };
 
-static BackwardScratch backward_scratch(void *mem, int64_t P, int64_t T, int32_t G)
+static BackwardScratch backward_scratch(void *mem, int64_t P, int64_t T, int64_t Ein, int32_t G)
 {
     BackwardScratch b{};
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -1228,14 +1232,19 @@ static BackwardScratch backward_scratch(void *mem, int64_t P, int64_t T, int32_t
     b.tgt_rowptr = reinterpret_cast<int32_t *>(p); p += 512;
     b.kept_count = reinterpret_cast<int64_t *>(p); p += up(sizeof(int64_t) * (size_t)(G > 1 ? G + 2 : 1));
     b.flags = reinterpret_cast<int32_t *>(p); p += 256;
-    b.bytes = (size_t)(p - static_cast<char *>(mem));
+    const PruneScratch S = prune_scratch(mem, P, T, G, 0);
+    size_t link_bytes = 0;
+    (void)backward_links(nullptr, P, Ein, &link_bytes);
+    const bool inside = link_bytes <= 2 * align256((size_t)S.qg.S * (size_t)S.qg.seg_cap * sizeof(int32_t));
+    b.links = inside ? static_cast<void *>(S.q0) : static_cast<void *>(p);
+    b.bytes = (size_t)(p - static_cast<char *>(mem)) + (inside ? 0 : link_bytes);
     return b;
 }
 
 int dgn_backward_prune_workspace(const dgn_graph *g, size_t *scratch_bytes)
 {
     if (!g || !scratch_bytes) return DGN_ERR_NULL_PTR;
-    *scratch_bytes = backward_scratch(nullptr, g->P, g->T, g->G).bytes;
+    *scratch_bytes = backward_scratch(nullptr, g->P, g->T, g->Ein, g->G).bytes;
     return DGN_OK;
 }
 
@@ -1249,7 +1258,7 @@ int dgn_backward_prune(const dgn_graph *g, int32_t num_pairs, const int32_t *obj
     if (g->G > 1) return DGN_ERR_INVALID_ARG;        // pairs are not tied to the graphs of a packed batch
     if (!obj || !wrt || !kept_count || !scratch) return DGN_ERR_NULL_PTR;
     if ((g->T > 0 && !tensor_mask) || (g->P > 0 && (!op_mask || !kept_ops))) return DGN_ERR_NULL_PTR;
-    const BackwardScratch S = backward_scratch(scratch, g->P, g->T, g->G);
+    const BackwardScratch S = backward_scratch(scratch, g->P, g->T, g->Ein, g->G);
     if (scratch_bytes < S.bytes) return DGN_ERR_WORKSPACE_TOO_SMALL;
     if (((uintptr_t)scratch | (uintptr_t)tensor_mask | (uintptr_t)op_mask | (uintptr_t)kept_masks |
          (uintptr_t)kept_count | (uintptr_t)per_query_count) & 7)
@@ -1276,12 +1285,15 @@ int dgn_backward_prune(const dgn_graph *g, int32_t num_pairs, const int32_t *obj
     uint8_t *stage_flags = nullptr;
     if (!o1.recompute_keep)
         stage_flags = (op_flag && ((uintptr_t)op_flag & 7) == 0 && g->P % 8 == 0)
-                          ? op_flag : prune_scratch(scratch, g->P, g->T, g->G, o1.max_queue_entries).flagbuf;
+                          ? op_flag : prune_scratch(scratch, g->P, g->T, g->G, o1.max_queue_entries, true).flagbuf;
 
     // stage two: forwards from every x_obj, inside the coloured set of stage one
     FillRegion clr[1] = {{S.flags, 256}};
     DGN_HIP(launch_clear(clr, 1, s));
     DGN_HIP(launch_backward_seed(g->T, num_pairs, obj, wrt, nullptr, S.B, F, S.flags, false, s));
+    size_t link_bytes = 0;
+    const BackwardLinks L = backward_links(S.links, g->P, g->Ein, &link_bytes);
+    DGN_HIP(launch_link_kept(g->v, S.kept, S.kept_count, S.KB, F, obj, num_pairs, L, S.flags + 1, g->num_cus, s));
     void *pin = nullptr;
     rc = pinned_buffer(&pin);
     if (rc != DGN_OK) return rc;
@@ -1297,7 +1309,7 @@ int dgn_backward_prune(const dgn_graph *g, int32_t num_pairs, const int32_t *obj
         FillRegion again[1] = {{S.flags + 2, sizeof(int32_t) * (size_t)kBackwardMaxBatch}};
         if (passes) DGN_HIP(launch_clear(again, 1, s));
         for (int i = 0; i < batch; ++i)
-            DGN_HIP(launch_forward_within(g->v, S.kept, S.kept_count, S.B, F, S.flags + 2 + i, grid, s));
+            DGN_HIP(launch_forward_pass(g->v, S.kept_count, S.KB, L, S.flags + 2 + i, g->num_cus, s));
         DGN_HIP(hipMemcpyAsync(host_flags, S.flags, 256, hipMemcpyDeviceToHost, s));
         DGN_HIP(hipStreamSynchronize(s));
         if (host_flags[0] & kErrIdRange) return DGN_ERR_ID_OUT_OF_RANGE;
@@ -1315,7 +1327,10 @@ int dgn_backward_prune(const dgn_graph *g, int32_t num_pairs, const int32_t *obj
 
     // Removal rule and ordered compaction on the marked set.  A marked tensor lies in stage one's coloured set,
     // so only operators of stage one's kept list can have a marked output: K is cleared and written for those.
-    DGN_HIP(launch_keep_from_list(g->v, S.kept, S.kept_count, F, reinterpret_cast<u64 *>(op_mask), stage_flags, grid, s));
+    DGN_HIP(launch_write_marks(g->v, g->multi_producer, S.kept, S.kept_count, L.FO, S.B, F, reinterpret_cast<u64 *>(op_mask),
+                               stage_flags, grid, s));
+    if (g->multi_producer)
+        DGN_HIP(launch_keep_from_list(g->v, S.kept, S.kept_count, F, reinterpret_cast<u64 *>(op_mask), stage_flags, grid, s));
     return keep_compact_impl(g, tensor_mask, false, op_mask, op_flag, kept_ops, kept_masks, kept_count, per_query_count,
                              scratch, S.prune_bytes, stream, stage_flags);
 }

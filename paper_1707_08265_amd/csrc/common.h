@@ -371,14 +371,25 @@ size_t digest_scratch_bytes();
 hipError_t launch_target_digest(int32_t num_sets, int64_t n, const int32_t *tgt_rowptr, int64_t num_targets,
                                 const int32_t *tgt_idx, void *scratch, u64 **digest_dev, hipStream_t s);
 
-// Backward Prune (Algorithm 2): target row pointers 0..n (rowptr_only) or the seeds of the forward stage;
-// one pass of the forward stage over the kept operators of the first stage.
+// Backward Prune (Algorithm 2), forward stage: what its passes work on (see backward.hip), by place in the kept list.
+struct BackwardLinks {
+    u64 *K, *FO;             // [P] K of the first stage; marks that arrive at an operator's inputs
+    int2 *group;             // [P / 64 + 1] per 64 kept operators: first entry and number of entries below
+    int32_t *link;           // [Ein] the producer of an input, or -1, or -2 - the id of an input with several
+    uint8_t *owner;          // [Ein] the operator of the group that reads it
+};
+BackwardLinks backward_links(void *mem, int64_t P, int64_t Ein, size_t *bytes);
+hipError_t launch_link_kept(const GraphView &g, const int32_t *kept, const int64_t *kept_count, u64 *place, const u64 *F,
+                            const int32_t *obj, int num_pairs, const BackwardLinks &b, int32_t *cursor, int num_cus, hipStream_t s);
+hipError_t launch_forward_pass(const GraphView &g, const int64_t *kept_count, const u64 *place, const BackwardLinks &b,
+                               int32_t *changed, int num_cus, hipStream_t s);
+hipError_t launch_write_marks(const GraphView &g, bool several_producers, const int32_t *kept, const int64_t *kept_count,
+                              const u64 *FO, const u64 *B, u64 *F, u64 *K, uint8_t *flags, int grid_blocks, hipStream_t s);
+// Target row pointers 0..n (rowptr_only) or the seeds of the forward stage.
 hipError_t launch_backward_seed(int64_t T, int num_pairs, const int32_t *obj, const int32_t *wrt, int32_t *tgt_rowptr,
                                 const u64 *B, u64 *F, int32_t *flags, bool rowptr_only, hipStream_t s);
 hipError_t launch_keep_from_list(const GraphView &g, const int32_t *kept, const int64_t *kept_count, const u64 *F, u64 *K,
                                  uint8_t *flags, int grid_blocks, hipStream_t s);
-hipError_t launch_forward_within(const GraphView &g, const int32_t *kept, const int64_t *kept_count, const u64 *B, u64 *F,
-                                 int32_t *changed, int grid_blocks, hipStream_t s);
 
 // In-place structures (Algorithm 3).  counters: [0] = number of nodes in `list`,
 // [1 + r] = doubling round r left some jump pointer alive.

@@ -56,6 +56,27 @@ def test_random_small_graphs(dgn, oracle, seed):
     assert_same(out, oracle.backward_prune(_adj(oracle, g), obj, wrt), f"seed {seed}")
 
 
+@pytest.mark.parametrize("multi", [False, True])
+@pytest.mark.parametrize("ops", [63, 64, 65, 1025, 5000])
+def test_forward_stage_on_lists(dgn, oracle, ops, multi):
+    """Groups of 64 kept operators: ragged ones, more input entries than a wave keeps in registers, tensors with several
+    producers; lists inside the first stage's queues and (5 000 operators) behind the rest of the scratch memory, and with
+    queues that an option makes small."""
+    rng = np.random.default_rng(ops + multi)
+    _, rows = random_small_graph(rng, ops, multi_producer=multi)
+    top = max([2] + [t for _, outs in rows for t in outs])
+    rows += [([int(t) for t in rng.integers(0, top + 1, n)], [top + 1 + i]) for i, n in enumerate((700, 70, 300))]
+    g = graph_from_ops(rows, top + 4)
+    obj = rng.integers(0, max(1, g.num_tensors // 3), 64).astype(np.int32)
+    wrt = rng.integers(g.num_tensors // 2, g.num_tensors, 64).astype(np.int32)
+    wrt[:3] = [top + 1, top + 2, top + 3]
+    ref = oracle.backward_prune(_adj(oracle, g), obj, wrt)
+    dg, buf, out = gpu_backward(dgn, g, obj, wrt)
+    assert_same(out, ref, "lists")
+    assert_same(gpu_backward(dgn, g, obj, wrt, buf=buf, dg=dg)[2], ref, "lists again")
+    assert_same(gpu_backward(dgn, g, obj, wrt, buf=buf, dg=dg, max_queue_entries=37)[2], ref, "small queues")
+
+
 @pytest.mark.parametrize("k,scale", [(0, 1.0), (1, 1.0), (2, 0.02), (3, 0.005)])
 def test_parity_configs(dgn, oracle, k, scale):
     g, _ = gg.config(k, scale)
