@@ -34,7 +34,6 @@ constexpr int kWideGroups = 6;              // ... and in the following ones
 constexpr int kMaxBatch = 512;              // launches enqueued between two state read-backs, at most
 constexpr int kTailLevels = 1;              // wide launches enqueued beyond the layout the previous prune needed ...
 constexpr int kExactStreak = 3;             // ... until that layout has fitted exactly this many prunes in a row
-constexpr int kStatusMulti = 16;            // word of the build's status block that says "a tensor has several producers"
 constexpr int kBackwardMaxBatch = 60;       // forward passes of the backward prune between two read-backs, at most
 constexpr int kSweepMinGraphs = 64;         // packed batches with at least this many graphs ...
 constexpr int64_t kSweepMaxGraphOps = 1 << 18;   // ... none larger than this use the per-graph sweep
@@ -121,11 +120,10 @@ struct BuildScratch {
     int32_t *sorted_ops;    // [Eout] operator id of every entry of out_idx
     int32_t *sorted_keys;   // [max(Ein, Eout)] keys of a sort in row order, for the row pointers
     void *sort_tmp;
-    void *scan_tmp;
     size_t bytes;
 };
 
-BuildScratch build_scratch(void *mem, int64_t P, int64_t T, int64_t Ein, int64_t Eout)
+BuildScratch build_scratch(void *mem, int64_t Ein, int64_t Eout)
 {
     Carver c(mem);
     BuildScratch S{};
@@ -134,7 +132,6 @@ BuildScratch build_scratch(void *mem, int64_t P, int64_t T, int64_t Ein, int64_t
     const int64_t emax = Ein > Eout ? Ein : Eout;
     S.sorted_keys = c.take<int32_t>(emax);
     S.sort_tmp = c.take<char>(sort_tmp_bytes(emax));
-    S.scan_tmp = c.take<char>(scan_tmp_bytes((P > T ? P : T) + 1));
     S.bytes = c.off;
     return S;
 }
@@ -297,41 +294,89 @@ struct dgn_graph {
 
 namespace {
 
-int finish_build(dgn_graph *h, const GraphLayout &L, const int64_t *op_off_host, const int64_t *t_off_host,
-                 int32_t *status, const dgn_options *options, hipStream_t s, dgn_graph **out)
+constexpr int kStatusWords = kStatusRing + 4;
+
+// The status words of a build, once everything before them is done.
+int read_status(const int32_t *status, hipStream_t s, const int32_t **out)
 {
-    DGN_HIP(launch_build_records(h->v, L.orec, L.prod1, status + kStatusMulti, s));
+    void *pin = nullptr;
+    const int rc = pinned_buffer(&pin);
+    if (rc) return rc;
+    DGN_HIP(hipMemcpyAsync(pin, status, kStatusWords * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    DGN_HIP(hipStreamSynchronize(s));
+    *out = static_cast<const int32_t *>(pin);
+    return DGN_OK;
+}
+
+// Packed batches, and single graphs that the ring sweep may take, are checked in the walk that makes the records.
+bool walked(const dgn_graph *h) { return h->G > 1 || h->P <= kRingMaxOps; }
+
+// What follows the adjacency.  The kernels find out by themselves whether there is one yet.
+int enqueue_records(const dgn_graph *h, const GraphLayout &L, int32_t *status, const dgn_options *options, hipStream_t s)
+{
+    if (walked(h)) {
+        DGN_HIP(launch_records_and_check(h->v, L.orec, status, h->num_cus, s));
+    } else {
+        DGN_HIP(launch_build_records(h->v, L.orec, status, s));
+        if (options && options->validate) DGN_HIP(launch_check_topological(h->v, status, s));
+    }
+    return DGN_OK;
+}
+
+// Tensor -> producer rows by a stable sort of the outputs in operator order (outputs by tensor: each tensor's producers stay
+// ascending in operator id), or, if only long gaps were left out, from the tensors as they are; then the producer words.
+int build_producers(const dgn_graph *h, const GraphLayout &L, const BuildScratch &S, const int32_t *ops_of_out, bool sorted,
+                    hipStream_t s)
+{
+    const int32_t *keys = h->v.out_idx;
+    if (!sorted) {
+        DGN_HIP(launch_sort_pairs(h->v.out_idx, ops_of_out, S.sorted_keys, L.prod_idx, h->Eout, key_bits_for(h->T), S.sort_tmp, s));
+        keys = S.sorted_keys;
+    }
+    DGN_HIP(launch_row_bounds(keys, h->Eout, (int32_t)h->T, L.prod_rowptr, s));
+    DGN_HIP(launch_build_producers(h->v, L.prod1, S.status + kStatusMulti, s));
+    return DGN_OK;
+}
+
+int copy_offsets(dgn_graph *h, const GraphLayout &L, const int64_t *op_off_host, const int64_t *t_off_host, hipStream_t s)
+{
     if (h->G > 1) {
         DGN_HIP(hipMemcpyAsync(L.op_off, op_off_host, sizeof(int64_t) * (h->G + 1), hipMemcpyHostToDevice, s));
         DGN_HIP(hipMemcpyAsync(L.t_off, t_off_host, sizeof(int64_t) * (h->G + 1), hipMemcpyHostToDevice, s));
         h->v.op_off = L.op_off;
         h->v.t_off = L.t_off;
     }
-    // The topological precondition is checked when the caller asks for validation, and for packed
-    // batches, whose per-graph sweep is only chosen when it holds.  (One random access per edge: not
-    // worth paying on every build of a big single graph, whose traversal does not depend on it.)  A packed batch
-    // gets it in the walk over the edges that checks the graphs' ranges.
-    const bool check_topo = (options && options->validate) || h->G >= kSweepMinGraphs;
-    const bool check_ring = h->G > 1 || h->P <= kRingMaxOps;
-    if (check_ring) DGN_HIP(launch_check_graph_ranges(h->v, status, check_topo, s));
-    else if (check_topo) DGN_HIP(launch_check_topological(h->v, status, s));
-    void *pin = nullptr;
-    int rc = pinned_buffer(&pin);
-    if (rc) return rc;
-    DGN_HIP(hipMemcpyAsync(pin, status, (kStatusRing + 4) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DGN_HIP(hipStreamSynchronize(s));
-    int32_t bits = *static_cast<int32_t *>(pin);
-    h->topological = check_topo && (bits & kErrTopo) == 0;
-    h->multi_producer = static_cast<int32_t *>(pin)[kStatusMulti] != 0;
-    if (!(options && options->validate)) bits &= ~kErrTopo;
-    rc = error_bits_to_code(bits);
-    if (rc) return rc;
-    const int32_t *ring = static_cast<int32_t *>(pin) + kStatusRing;
+    return DGN_OK;
+}
+
+// found: the status words as enqueue_records' kernels left them on an adjacency that is complete.
+int finish_build(dgn_graph *h, const int64_t *op_off_host, const int64_t *t_off_host, int32_t *status, const int32_t *found,
+                 const dgn_options *options, hipStream_t s, dgn_graph **out)
+{
+    const int32_t *ring = found + kStatusRing;
     // (32-bit byte offsets inside a graph's arrays)
-    h->ring = check_ring && h->P > 0 && h->Ein > 0 && h->Ein < (1 << 30) && h->T < (1 << 29) && ring[0] == 0;
+    h->ring = walked(h) && h->P > 0 && h->Ein > 0 && h->Ein < (1 << 30) && h->T < (1 << 29) && ring[0] == 0;
     h->ring_low = ring[1];
     h->ring_dist = ring[2];
     h->ring_span64 = ring[3];
+    h->multi_producer = found[kStatusMulti] != 0;
+    // The topological precondition is checked when the caller asks for validation, and for packed
+    // batches, whose per-graph sweep is only chosen when it holds.  (One random access per edge: not
+    // worth paying on every build of a big single graph, whose traversal does not depend on it.)  Where the walk found
+    // every graph's outputs in one run and no operator that reads too late, it holds.
+    const bool check_topo = (options && options->validate) || h->G >= kSweepMinGraphs;
+    if (check_topo && walked(h) && ring[0] != 0 && found[0] == 0) {
+        FillRegion clr[1] = {{status, kStatusOrder * sizeof(int32_t)}};
+        DGN_HIP(launch_clear(clr, 1, s));
+        DGN_HIP(launch_check_topological(h->v, status, s));
+        const int rc = read_status(status, s, &found);
+        if (rc) return rc;
+    }
+    int32_t bits = found[0];
+    h->topological = check_topo && (bits & kErrTopo) == 0;
+    if (!(options && options->validate)) bits &= ~kErrTopo;
+    const int rc = error_bits_to_code(bits);
+    if (rc) return rc;
     for (int32_t i = 0; h->G > 1 && i < h->G; ++i)           // a graph without operators: all its tensors are inputs
         if (op_off_host[i + 1] == op_off_host[i] && t_off_host[i + 1] - t_off_host[i] > h->ring_low)
             h->ring_low = (int)(t_off_host[i + 1] - t_off_host[i]);
@@ -343,12 +388,84 @@ int finish_build(dgn_graph *h, const GraphLayout &L, const int64_t *op_off_host,
         for (int32_t i = 0; i < h->G; ++i)
             if (op_off_host[i + 1] - op_off_host[i] > h->max_graph_ops) h->max_graph_ops = op_off_host[i + 1] - op_off_host[i];
     }
+    *out = h;
+    return DGN_OK;
+}
+
+// A handle with the compute units of the current device.
+int new_graph(dgn_graph **out)
+{
     int dev = 0, cus = 0;
     DGN_HIP(hipGetDevice(&dev));
     DGN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    dgn_graph *h = new (std::nothrow) dgn_graph();
+    if (!h) return DGN_ERR_INVALID_ARG;
     h->num_cus = cus > 0 ? cus : 256;
     *out = h;
     return DGN_OK;
+}
+
+// The adjacency and what follows it, from edge lists whose workspace is laid out in L and S.
+int build_from_lists(dgn_graph *h, const dgn_coo_desc *d, const GraphLayout &L, const BuildScratch &S, const dgn_options *options,
+                     hipStream_t s, const int32_t **found)
+{
+    const int64_t P = h->P, T = h->T, Ein = h->Ein, Eout = h->Eout;
+    // One pass over both lists (in COO order) checks the ids, notes whether the keys ever decrease and, on the assumption
+    // that they do not, already writes the finished adjacency: a graph recorded operator by operator needs nothing more,
+    // and the host looks at the status once, when the records are made as well.
+    FillRegion clr[1] = {{S.status, 256}};
+    DGN_HIP(launch_clear(clr, 1, s));
+    int rc = copy_offsets(h, L, d->graph_op_offsets, d->graph_tensor_offsets, s);
+    if (rc) return rc;
+    const EdgeList in{d->in_op, d->in_tensor, Ein, (int32_t)P, (int32_t)T, L.in_idx, L.in_rowptr, nullptr, nullptr, nullptr};
+    const EdgeList out{d->out_op, d->out_tensor, Eout, (int32_t)P, (int32_t)T, L.out_idx, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1};
+    DGN_HIP(launch_scan_edges(&in, out, S.status, s));
+    rc = enqueue_records(h, L, S.status, options, s);
+    if (rc) return rc;
+    const int32_t *f = nullptr;
+    rc = read_status(S.status, s, &f);
+    if (rc) return rc;
+    *found = f;
+    if (f[0] & kErrIdRange) return DGN_OK;                    // bad ids: nothing is built from them
+    const bool in_unsorted = f[kStatusInUnsorted], in_gap = f[kStatusInGap], out_unsorted = f[kStatusOutUnsorted];
+    bool out_gap = f[kStatusOutGap], prod_unsorted = f[kStatusProdUnsorted], prod_gap = f[kStatusProdGap];
+    if (!(in_unsorted || in_gap || out_unsorted || out_gap || prod_unsorted || prod_gap)) return DGN_OK;
+    // Otherwise stable sorts: edges by operator (rows keep COO order), row pointers from the sorted keys (first position of
+    // every key): no histogram, no atomics.  The outputs, once in operator order, get the same pass as above: where tensors
+    // are numbered as they are created they are in order by tensor as well, whatever order they came in, and need no second
+    // sort.
+    if (in_unsorted) {
+        DGN_HIP(launch_sort_pairs(d->in_op, d->in_tensor, S.sorted_keys, L.in_idx, Ein, key_bits_for(P), S.sort_tmp, s));
+        DGN_HIP(launch_row_bounds(S.sorted_keys, Ein, (int32_t)P, L.in_rowptr, s));
+    } else if (in_gap) {
+        DGN_HIP(launch_row_bounds(d->in_op, Ein, (int32_t)P, L.in_rowptr, s));
+    }
+    const int32_t *ops_of_out = d->out_op;                    // operator of every entry of out_idx
+    if (out_unsorted) {
+        DGN_HIP(launch_sort_pairs(d->out_op, d->out_tensor, S.sorted_ops, L.out_idx, Eout, key_bits_for(P), S.sort_tmp, s));
+        ops_of_out = S.sorted_ops;
+        DGN_HIP(launch_clear(clr, 1, s));
+        const EdgeList sorted{S.sorted_ops, L.out_idx, Eout, (int32_t)P, (int32_t)T, nullptr, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1};
+        DGN_HIP(launch_scan_edges(nullptr, sorted, S.status, s));
+        rc = enqueue_records(h, L, S.status, options, s);
+        if (rc) return rc;
+        rc = read_status(S.status, s, &f);
+        if (rc) return rc;
+        out_gap = f[kStatusOutGap];
+        prod_unsorted = f[kStatusProdUnsorted];
+        prod_gap = f[kStatusProdGap];
+        if (!(out_gap || prod_unsorted || prod_gap)) return DGN_OK;
+    }
+    if (out_gap) DGN_HIP(launch_row_bounds(ops_of_out, Eout, (int32_t)P, L.out_rowptr, s));
+    if (prod_unsorted || prod_gap) {
+        rc = build_producers(h, L, S, ops_of_out, !prod_unsorted, s);
+        if (rc) return rc;
+    }
+    FillRegion ready[1] = {{S.status, kStatusOrder * sizeof(int32_t)}};
+    DGN_HIP(launch_clear(ready, 1, s));
+    rc = enqueue_records(h, L, S.status, options, s);
+    if (rc) return rc;
+    return read_status(S.status, s, found);
 }
 
 }  // namespace
@@ -382,7 +499,7 @@ int dgn_graph_build_workspace(const dgn_coo_desc *d, size_t *graph_bytes, size_t
                          d->graph_tensor_offsets);
     if (rc) return rc;
     *graph_bytes = graph_layout(nullptr, d->num_ops, d->num_tensors, d->nnz_in, d->nnz_out, d->num_graphs, true).bytes;
-    *scratch_bytes = build_scratch(nullptr, d->num_ops, d->num_tensors, d->nnz_in, d->nnz_out).bytes;
+    *scratch_bytes = build_scratch(nullptr, d->nnz_in, d->nnz_out).bytes;
     return DGN_OK;
 }
 
@@ -405,56 +522,17 @@ int dgn_graph_build(const dgn_coo_desc *d, void *graph_mem, size_t graph_bytes, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t P = d->num_ops, T = d->num_tensors, Ein = d->nnz_in, Eout = d->nnz_out;
     const GraphLayout L = graph_layout(graph_mem, P, T, Ein, Eout, d->num_graphs, true);
-    const BuildScratch S = build_scratch(scratch, P, T, Ein, Eout);
+    const BuildScratch S = build_scratch(scratch, Ein, Eout);
 
-    // One pass per edge list (all three in COO order) checks the ids, notes whether the keys ever decrease
-    // (status[1..3]) and, on the assumption that they do not, already writes the finished rows: a graph
-    // recorded operator by operator needs nothing more.  Reading the flags costs one synchronisation.
-    FillRegion clr[1] = {{S.status, 256}};
-    DGN_HIP(launch_clear(clr, 1, s));
-    DGN_HIP(launch_scan_edges(d->in_op, d->in_tensor, Ein, (int32_t)P, (int32_t)T, L.in_idx, L.in_rowptr, S.status, S.status + 1, S.status + 5, s));
-    DGN_HIP(launch_scan_edges(d->out_op, d->out_tensor, Eout, (int32_t)P, (int32_t)T, L.out_idx, L.out_rowptr, S.status, S.status + 2, S.status + 6, s));
-    DGN_HIP(launch_scan_edges(d->out_tensor, d->out_op, Eout, (int32_t)T, (int32_t)P, L.prod_idx, L.prod_rowptr, S.status, S.status + 3, S.status + 7, s));
-    void *pin = nullptr;
-    rc = pinned_buffer(&pin);
-    if (rc != DGN_OK) return rc;
-    DGN_HIP(hipMemcpyAsync(pin, S.status, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DGN_HIP(hipStreamSynchronize(s));
-    const int32_t *flags = static_cast<const int32_t *>(pin);
-    if (flags[0]) return error_bits_to_code(flags[0]);       // bad ids: nothing is built from them
-    const bool in_sorted = !flags[1], out_sorted = !flags[2];
-    const bool prod_sorted = out_sorted && !flags[3];         // the third sort reads the outputs in operator order
-    // Otherwise stable sorts: edges by operator (rows keep COO order), then outputs by tensor, which leaves each
-    // tensor's producers ascending in operator id; row pointers from the sorted keys (first position of every
-    // key): no histogram, no atomics.
-    // (flags[5..7]: the pass met a long run of empty rows and left the row pointers to launch_row_bounds)
-    if (!in_sorted) {
-        DGN_HIP(launch_sort_pairs(d->in_op, d->in_tensor, S.sorted_keys, L.in_idx, Ein, key_bits_for(P), S.sort_tmp, s));
-        DGN_HIP(launch_row_bounds(S.sorted_keys, Ein, (int32_t)P, L.in_rowptr, s));
-    } else if (flags[5]) {
-        DGN_HIP(launch_row_bounds(d->in_op, Ein, (int32_t)P, L.in_rowptr, s));
-    }
-    const int32_t *ops_of_out = d->out_op;                    // operator of every entry of out_idx
-    if (!out_sorted) {
-        DGN_HIP(launch_sort_pairs(d->out_op, d->out_tensor, S.sorted_ops, L.out_idx, Eout, key_bits_for(P), S.sort_tmp, s));
-        DGN_HIP(launch_row_bounds(S.sorted_ops, Eout, (int32_t)P, L.out_rowptr, s));
-        ops_of_out = S.sorted_ops;
-    } else if (flags[6]) {
-        DGN_HIP(launch_row_bounds(d->out_op, Eout, (int32_t)P, L.out_rowptr, s));
-    }
-    if (!prod_sorted) {
-        DGN_HIP(launch_sort_pairs(L.out_idx, ops_of_out, S.sorted_keys, L.prod_idx, Eout, key_bits_for(T), S.sort_tmp, s));
-        DGN_HIP(launch_row_bounds(S.sorted_keys, Eout, (int32_t)T, L.prod_rowptr, s));
-    } else if (flags[7]) {
-        DGN_HIP(launch_row_bounds(d->out_tensor, Eout, (int32_t)T, L.prod_rowptr, s));
-    }
-
-    dgn_graph *h = new (std::nothrow) dgn_graph();
-    if (!h) return DGN_ERR_INVALID_ARG;
+    dgn_graph *h = nullptr;
+    rc = new_graph(&h);
+    if (rc) return rc;
     h->P = P; h->T = T; h->Ein = Ein; h->Eout = Eout; h->G = d->num_graphs;
     h->v = GraphView{(int32_t)P, (int32_t)T, (int32_t)Ein, (int32_t)Eout, d->num_graphs, L.in_rowptr, L.in_idx,
                      L.out_rowptr, L.out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.prod1};
-    rc = finish_build(h, L, d->graph_op_offsets, d->graph_tensor_offsets, S.status, options, s, out);
+    const int32_t *found = nullptr;
+    rc = build_from_lists(h, d, L, S, options, s, &found);
+    if (!rc) rc = finish_build(h, d->graph_op_offsets, d->graph_tensor_offsets, S.status, found, options, s, out);
     if (rc) delete h;
     return rc;
 }
@@ -466,7 +544,7 @@ int dgn_graph_from_csr_workspace(const dgn_csr_desc *d, size_t *graph_bytes, siz
                          d->graph_tensor_offsets);
     if (rc) return rc;
     *graph_bytes = graph_layout(nullptr, d->num_ops, d->num_tensors, d->nnz_in, d->nnz_out, d->num_graphs, false).bytes;
-    *scratch_bytes = build_scratch(nullptr, d->num_ops, d->num_tensors, d->nnz_in, d->nnz_out).bytes;
+    *scratch_bytes = build_scratch(nullptr, d->nnz_in, d->nnz_out).bytes;
     return DGN_OK;
 }
 
@@ -488,32 +566,46 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t P = d->num_ops, T = d->num_tensors, Ein = d->nnz_in, Eout = d->nnz_out;
     const GraphLayout L = graph_layout(graph_mem, P, T, Ein, Eout, d->num_graphs, false);
-    const BuildScratch S = build_scratch(scratch, P, T, Ein, Eout);
+    const BuildScratch S = build_scratch(scratch, Ein, Eout);
 
-    FillRegion clr[2] = {{L.prod_rowptr, align256((T + 1) * 4)}, {S.status, 256}};
-    DGN_HIP(launch_clear(clr, 2, s));
+    FillRegion clr[1] = {{S.status, 256}};
+    DGN_HIP(launch_clear(clr, 1, s));
     // the borrowed arrays are checked before any kernel trusts them
     DGN_HIP(launch_check_csr(d->in_rowptr, d->in_idx, (int32_t)P, (int32_t)Ein, (int32_t)T, S.status, s));
     DGN_HIP(launch_check_csr(d->out_rowptr, d->out_idx, (int32_t)P, (int32_t)Eout, (int32_t)T, S.status, s));
-    void *pin = nullptr;
-    rc = pinned_buffer(&pin);
+    const int32_t *found = nullptr;
+    rc = read_status(S.status, s, &found);
     if (rc) return rc;
-    DGN_HIP(hipMemcpyAsync(pin, S.status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DGN_HIP(hipStreamSynchronize(s));
-    rc = error_bits_to_code(*static_cast<int32_t *>(pin));
+    rc = error_bits_to_code(found[0]);
     if (rc) return rc;
 
-    DGN_HIP(launch_expand_rows(d->out_rowptr, (int32_t)P, S.sorted_ops, s));
-    DGN_HIP(launch_degree_hist(d->out_idx, nullptr, Eout, (int32_t)T, 1, L.prod_rowptr, S.status, S.status + 3, s));
-    DGN_HIP(launch_exclusive_scan(L.prod_rowptr, L.prod_rowptr, T, S.scan_tmp, s));
-    DGN_HIP(launch_sort_pairs(d->out_idx, S.sorted_ops, nullptr, L.prod_idx, Eout, key_bits_for(T), S.sort_tmp, s));
-
-    dgn_graph *h = new (std::nothrow) dgn_graph();
-    if (!h) return DGN_ERR_INVALID_ARG;
+    dgn_graph *h = nullptr;
+    rc = new_graph(&h);
+    if (rc) return rc;
     h->P = P; h->T = T; h->Ein = Ein; h->Eout = Eout; h->G = d->num_graphs;
     h->v = GraphView{(int32_t)P, (int32_t)T, (int32_t)Ein, (int32_t)Eout, d->num_graphs, d->in_rowptr, d->in_idx,
                      d->out_rowptr, d->out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.prod1};
-    rc = finish_build(h, L, d->graph_op_offsets, d->graph_tensor_offsets, S.status, options, s, out);
+    auto fill = [&]() -> int {
+        int e = copy_offsets(h, L, d->graph_op_offsets, d->graph_tensor_offsets, s);
+        if (e) return e;
+        // the outputs as a list in operator order: its tensors usually ascend as well, and the pass over it is all it takes
+        DGN_HIP(launch_expand_rows(d->out_rowptr, (int32_t)P, S.sorted_ops, s));
+        const EdgeList list{S.sorted_ops, d->out_idx, Eout, (int32_t)P, (int32_t)T, nullptr, nullptr, L.prod_idx, L.prod_rowptr, L.prod1};
+        DGN_HIP(launch_scan_edges(nullptr, list, S.status, s));
+        e = enqueue_records(h, L, S.status, options, s);
+        if (e) return e;
+        e = read_status(S.status, s, &found);
+        if (e || !(found[kStatusProdUnsorted] || found[kStatusProdGap])) return e;
+        e = build_producers(h, L, S, S.sorted_ops, !found[kStatusProdUnsorted], s);
+        if (e) return e;
+        FillRegion ready[1] = {{S.status, kStatusOrder * sizeof(int32_t)}};
+        DGN_HIP(launch_clear(ready, 1, s));
+        e = enqueue_records(h, L, S.status, options, s);
+        if (e) return e;
+        return read_status(S.status, s, &found);
+    };
+    rc = fill();
+    if (!rc) rc = finish_build(h, d->graph_op_offsets, d->graph_tensor_offsets, S.status, found, options, s, out);
     if (rc) delete h;
     return rc;
 }

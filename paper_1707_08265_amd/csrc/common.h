@@ -255,24 +255,45 @@ size_t sort_tmp_bytes(int64_t n);
 hipError_t launch_sort_pairs(const int32_t *keys_in, const int32_t *vals_in, int32_t *keys_out,
                              int32_t *vals_out, int64_t n, int key_bits, void *tmp, hipStream_t s);
 
-// deg[key[e]] += 1 for keys in [0, n_rows); flags keys / vals outside their ranges in *error.
-hipError_t launch_degree_hist(const int32_t *keys, const int32_t *vals, int64_t nnz, int32_t n_rows,
-                              int32_t n_vals, int32_t *deg, int32_t *error, int32_t *unsorted, hipStream_t s);
-// checks an edge list and, assuming its keys are in row order, writes the finished row (idx_out, rowptr)
-hipError_t launch_scan_edges(const int32_t *keys, const int32_t *vals, int64_t nnz, int32_t n_rows, int32_t n_vals,
-                             int32_t *idx_out, int32_t *rowptr, int32_t *error, int32_t *unsorted, int32_t *wide_gap,
-                             hipStream_t s);
+// Status words of a build: [0] error bits, then flags
+enum : int {
+    kStatusInUnsorted = 1,       // the operators of the input edges decrease somewhere
+    kStatusOutUnsorted = 2,      // ... of the output edges
+    kStatusProdUnsorted = 3,     // the tensors of the output edges, taken in operator order
+    kStatusInGap = 5,            // row pointers with a long run of empty rows, left out
+    kStatusOutGap = 6,
+    kStatusProdGap = 7,
+    kStatusOrder = 8,            // (so many words say whether there is an adjacency; the following describe it)
+    kStatusMulti = 16,           // some tensor has several producers
+    kStatusScattered = 17,       // the outputs are not one run of tensors up to the last one
+    kStatusRing = 20,            // what k_records_and_check finds out for the ring sweep: [0] != 0: outputs are not one run or
+                                 // read too early; [1] graph inputs, [2] dist, [3] span64 (maxima)
+};
+// An edge list and where its adjacency goes.  idx / row == NULL: those are in place already.
+struct EdgeList {
+    const int32_t *op, *tensor;
+    int64_t nnz;
+    int32_t num_ops, num_tensors;
+    int32_t *idx, *row;                          // rows by operator
+    int32_t *prod_idx, *prod_row, *prod1;        // outputs: rows by tensor, producer words
+};
+// one pass over the input edges (NULL: the outputs only) and the output edges: checks them and, assuming that they are in
+// order, writes the finished adjacency
+hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s);
+// The kernels from here to launch_check_topological do nothing if the status says that there is no adjacency yet.
+// operator records of a single graph / of graphs that are also checked for range and for the ring sweep
+hipError_t launch_build_records(const GraphView &g, int4 *orec, const int32_t *status, hipStream_t s);
+hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *status, int num_cus, hipStream_t s);
+hipError_t launch_check_topological(const GraphView &g, int32_t *status, hipStream_t s);
+// producer words from prod_rowptr / prod_idx; *multi = 1 when some tensor has several producers
+hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *multi, hipStream_t s);
 // rowptr[0..n_rows] from keys that are in row order (all in range)
 hipError_t launch_row_bounds(const int32_t *keys, int64_t nnz, int32_t n_rows, int32_t *rowptr, hipStream_t s);
 hipError_t launch_check_csr(const int32_t *rowptr, const int32_t *idx, int32_t n_rows, int32_t nnz,
                             int32_t n_vals, int32_t *error, hipStream_t s);
 hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t *row_of, hipStream_t s);
-hipError_t launch_check_topological(const GraphView &g, int32_t *error, hipStream_t s);
-hipError_t launch_check_graph_ranges(const GraphView &g, int32_t *status, bool also_topological, hipStream_t s);
 
 // Traversal.
-// operator records and producer words, once per graph; *multi = 1 when some tensor has several producers
-hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *multi, hipStream_t s);
 hipError_t launch_seed(const GraphView &g, int32_t Q, int64_t num_targets, const int32_t *tgt_rowptr,
                        const int32_t *tgt_idx, u64 *M, TravState *st, TravCounters *ctr, int32_t *q0,
                        const QueueGeom &qg, int32_t theta0, const ColourLog &log, hipStream_t s);
@@ -316,8 +337,6 @@ struct RingArgs {
     int32_t recycle;         // *hdr may say that the buffers hold this kernel's last result
     int32_t ring_words, low_words, seed_words;     // LDS: ring, graph inputs (8 bytes each), targets (4 bytes each)
 };
-// what k_check_graph_ranges finds out for it: status words from kStatusRing on
-constexpr int kStatusRing = 20;      // [0] != 0: outputs are not one run; [1] graph inputs, [2] dist, [3] span64 (maxima)
 constexpr int kRingExtraWords = 1 + kWave;
 // words of 64 operators of G graphs, one of them perhaps ragged in each
 __host__ __device__ inline int64_t ring_bit_words(int64_t P, int64_t G) { return (P >> 6) + G + 1; }

@@ -5,64 +5,9 @@
 
 namespace dgn {
 
-// deg[key] += 1.  Ids outside their range are reported and skipped, so later passes never index
-// out of bounds with them (the sort itself only ever uses masked digits of the keys).
-//
-// The same pass notes whether the keys ever decrease (*unsorted = 1): recorded graphs are usually handed
-// over operator by operator, and edges that are already in row order need no sort at all.
-__global__ __launch_bounds__(256) void k_degree_hist(const int32_t *keys, const int32_t *vals, int64_t nnz,
-                                                      int32_t n_rows, int32_t n_vals, int32_t *deg, int32_t *error,
-                                                      int32_t *unsorted)
-{
-    // Runs of equal keys inside a wave (operator-major COO is one long sequence of such runs) are added
-    // with ONE atomic by the run's first lane: atomics on one address serialise, and an operator with
-    // fan-in 64 would otherwise be 64 of them.
-    const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
-    const int lane = lane_id();
-    bool bad = false, descends = false;
-    for (int64_t base = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~(kWave - 1)); base < nnz; base += gsize) {
-        const int64_t e = base + lane;                      // wave-uniform loop, lanes past the end idle
-        const bool valid = e < nnz;
-        const int32_t k = valid ? keys[e] : -1;
-        const int32_t v = (valid && vals) ? vals[e] : 0;
-        const bool good = valid && k >= 0 && k < n_rows;
-        if (valid && (!good || v < 0 || v >= n_vals)) bad = true;
-        int32_t prev = __shfl_up(k, 1, kWave);
-        if (lane == 0) prev = base > 0 ? keys[base - 1] : k;    // the key just before this wave's first one
-        if (valid && prev > k) descends = true;
-        const u64 gmask = ballot64(good);
-        const bool leader = good && (lane == 0 || !((gmask >> (lane - 1)) & 1) || prev != k);
-        const u64 boundaries = ballot64(leader) | ~gmask;   // a run ends at the next leader or the next bad lane
-        if (leader) {
-            const u64 above = lane == kWave - 1 ? 0 : boundaries >> (lane + 1);
-            const int run = above ? __builtin_ctzll(above) + 1 : kWave - lane;
-            atomicAdd(&deg[k], run);
-        }
-    }
-    if (ballot64(bad) != 0 && lane == 0) atomicOr(error, kErrIdRange);
-    // shuffled input would have every wave report: look first, and store (same value from everyone) only if needed
-    if (ballot64(descends) != 0 && lane == 0 && load_coherent(unsorted) == 0) store_coherent(unsorted, 1);
-}
-
-hipError_t launch_degree_hist(const int32_t *keys, const int32_t *vals, int64_t nnz, int32_t n_rows,
-                              int32_t n_vals, int32_t *deg, int32_t *error, int32_t *unsorted, hipStream_t s)
-{
-    if (nnz == 0) return hipSuccess;
-    int64_t blocks = (nnz + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_degree_hist, dim3((unsigned)blocks), dim3(256), 0, s, keys, vals, nnz, n_rows, n_vals,
-                       deg, error, unsorted);
-    return hipGetLastError();
-}
-
-// One pass over an edge list in the order it was handed over: range check of both ids, whether the keys
-// ever decrease (*unsorted = 1), and -- on the assumption that they do not, which holds for a graph
-// recorded operator by operator -- the finished row: idx_out = the values as they stand, rowptr = first
-// position of every key.  If the keys do decrease somewhere, what was written is simply overwritten by the
-// sort that follows.  No atomic in the common case.
+// rows lo..hi get val; gaps longer than a few rows are filled by the whole wave (call wave-uniformly)
 __device__ __forceinline__ void write_rows(int32_t *rowptr, int lo, int hi, int32_t val)
 {
-    // rows lo..hi get val; gaps longer than a few rows are filled by the whole wave (call wave-uniformly)
     constexpr int kShort = 4;
     for (int r = lo; r <= hi && r < lo + kShort; ++r) rowptr[r] = val;
     u64 longer = ballot64(hi - lo >= kShort);
@@ -75,78 +20,178 @@ __device__ __forceinline__ void write_rows(int32_t *rowptr, int lo, int hi, int3
     }
 }
 
+// The rows that position e closes: (prev, cur].  Keys outside their range close none (the call fails anyway), and a
+// long run of empty rows is left to a pass of its own (*gap): keys in random order jump far at nearly every position, and
+// filling those jumps here would cost more than the sort that follows.  (The rows before a list's first key, often the
+// graph's inputs, occur once.)
 constexpr int kMaxGapHere = 64;
-
-__global__ __launch_bounds__(256) void k_scan_edges(const int32_t *keys, const int32_t *vals, int64_t nnz,
-                                                     int32_t n_rows, int32_t n_vals, int32_t *idx_out, int32_t *rowptr,
-                                                     int32_t *error, int32_t *unsorted, int32_t *wide_gap)
+constexpr int kMaxFirstGap = 8192;
+__device__ __forceinline__ void rows_closed(int32_t prev, int32_t cur, int32_t n_rows, int64_t e, int &lo, int &hi, bool &gap)
 {
-    // a thread takes four neighbouring positions per step, in 16-byte loads and stores where the arrays are aligned
-    // for them: with a single position per thread the pass waits for memory most of its time
+    lo = 0;
+    hi = -1;
+    if (prev >= -1 && prev < n_rows && cur >= 0 && cur <= n_rows) {
+        lo = prev + 1;
+        hi = cur;
+    }
+    if (hi - lo >= (e == 0 ? kMaxFirstGap : kMaxGapHere)) {
+        gap = true;
+        hi = lo - 1;
+    }
+}
+
+// One pass over an edge list in the order it was handed over: range check of both ids, whether the keys ever decrease
+// (*unsorted = 1), and -- on the assumption that they do not, which holds for a graph recorded operator by operator --
+// the finished rows: the operators' row pointers (first position of every operator) and row entries, and for a list of
+// outputs also the tensors' (first position of every tensor, producers) and producer words.  If the keys do decrease
+// somewhere, what was written is overwritten by the sort that follows; a wave that has met such a place writes no more (in
+// a shuffled list: every wave, at its first step, and the pass costs the reading alone).  No atomic in the common case.
+//
+// A stream of 12 bytes per input edge and 28 per output edge and tensor: it is bound by memory.  A thread takes four
+// neighbouring positions per step, in 16-byte accesses where the arrays are aligned for them (one position per thread left
+// the pass waiting for memory).  Outputs take both adjacencies and the producer words from one reading: three passes did
+// that before, 0.99 ms of a 50 M-operator graph and 0.3 more for the producer words; now 1.00 in all = 4.1 TB/s.
+constexpr int kScanThreads = 256;
+
+template <bool kOut>
+__device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int64_t blocks, int32_t *status)
+{
     constexpr int kPer = 4;
-    const bool wide = ((reinterpret_cast<uintptr_t>(keys) | reinterpret_cast<uintptr_t>(vals) |
-                        reinterpret_cast<uintptr_t>(idx_out)) & 15) == 0;
-    const int64_t gsize = (int64_t)gridDim.x * blockDim.x * kPer;
+    const int32_t *ops = l.op, *tensors = l.tensor;
+    const int64_t nnz = l.nnz;
+    const int32_t P = l.num_ops, T = l.num_tensors;
+    const bool copies = l.idx != nullptr;                               // (already in place after a sort)
+    uintptr_t all = reinterpret_cast<uintptr_t>(ops) | reinterpret_cast<uintptr_t>(tensors) | reinterpret_cast<uintptr_t>(l.idx);
+    if (kOut) all |= reinterpret_cast<uintptr_t>(l.prod_idx);
+    const bool wide = (all & 15) == 0;
+    const int64_t gsize = blocks * kScanThreads * kPer;
     const int64_t steps = (nnz + 1 + gsize - 1) / gsize;                // position nnz closes the last rows
-    bool bad = false, descends = false, gap = false;
+    const int32_t shift = (int32_t)(T - nnz);                           // outputs in one run: edge e writes tensor e + shift
+    bool bad = false, gap = false, tgap = false, multi = false, scattered = false;
+    bool down = false, tdown = false;                                   // wave-uniform: operators / tensors decrease somewhere
     for (int64_t st = 0; st < steps; ++st) {                            // whole waves stay in the loop
-        const int64_t e0 = st * gsize + ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * kPer;
-        int32_t k[kPer + 1], v[kPer];                                   // k[j] = key before position e0 + j
-        k[0] = e0 > 0 && e0 <= nnz ? keys[e0 - 1] : -1;
-        if (wide && e0 + kPer <= nnz) {
-            const int4 kk = *reinterpret_cast<const int4 *>(keys + e0);
-            const int4 vv = *reinterpret_cast<const int4 *>(vals + e0);
+        const int64_t e0 = st * gsize + (block * kScanThreads + threadIdx.x) * kPer;
+        int32_t k[kPer + 1], t[kPer + 2];                               // k[j], t[j]: of position e0 + j - 1
+        k[0] = e0 > 0 && e0 <= nnz ? ops[e0 - 1] : -1;
+        if (kOut) t[0] = e0 > 0 && e0 <= nnz ? tensors[e0 - 1] : -1;
+        const bool inner = wide && e0 + kPer <= nnz;
+        if (inner) {
+            const int4 kk = *reinterpret_cast<const int4 *>(ops + e0);
+            const int4 tt = *reinterpret_cast<const int4 *>(tensors + e0);
             k[1] = kk.x; k[2] = kk.y; k[3] = kk.z; k[4] = kk.w;
-            v[0] = vv.x; v[1] = vv.y; v[2] = vv.z; v[3] = vv.w;
-            *reinterpret_cast<int4 *>(idx_out + e0) = vv;
+            t[1] = tt.x; t[2] = tt.y; t[3] = tt.z; t[4] = tt.w;
         } else {
 #pragma unroll
             for (int j = 0; j < kPer; ++j) {
-                const bool edge = e0 + j < nnz;
-                k[j + 1] = edge ? keys[e0 + j] : n_rows;
-                v[j] = edge ? vals[e0 + j] : 0;
-                if (edge) idx_out[e0 + j] = v[j];
+                k[j + 1] = e0 + j < nnz ? ops[e0 + j] : P;
+                t[j + 1] = e0 + j < nnz ? tensors[e0 + j] : T;
             }
         }
+        if (kOut) t[kPer + 1] = e0 + kPer < nnz ? tensors[e0 + kPer] : T;
+        bool d = false, td = false, run = kOut && inner;
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const int64_t e = e0 + j;
-            int lo = 0, hi = -1;
-            if (e <= nnz) {
-                const int32_t prev = k[j], cur = k[j + 1];
-                if (e < nnz) {
-                    if (cur < 0 || cur >= n_rows || v[j] < 0 || v[j] >= n_vals) bad = true;
-                    if (prev > cur) descends = true;
-                }
-                // rows (prev, cur]; keys outside their range write nothing (the call fails anyway)
-                if (prev >= -1 && prev < n_rows && cur >= 0 && cur <= n_rows) {
-                    lo = prev + 1;
-                    hi = cur;
-                }
-                // A long run of empty rows is left to a pass of its own (*wide_gap): keys in random order jump far
-                // at nearly every position, and filling those jumps here would cost more than the sort that follows.
-                if (hi - lo >= kMaxGapHere) {
-                    gap = true;
-                    hi = lo - 1;
+        for (int j = 1; j <= kPer; ++j) {
+            if (e0 + j > nnz) continue;
+            if (k[j] < 0 || k[j] >= P || t[j] < 0 || t[j] >= T) bad = true;
+            d |= k[j - 1] > k[j];
+            if (kOut) {
+                td |= t[j - 1] > t[j];
+                scattered |= t[j] != (int32_t)(e0 + j - 1) + shift;
+                run &= t[j] == t[j - 1] + 1;
+            }
+        }
+        if (kOut) run &= t[kPer + 1] != t[kPer] && t[1] >= 0 && t[kPer] < T;
+        down |= ballot64(d) != 0;
+        if (kOut) tdown |= ballot64(td) != 0;
+        if (!down) {
+            if (copies && inner) {
+                *reinterpret_cast<int4 *>(l.idx + e0) = make_int4(t[1], t[2], t[3], t[4]);
+            } else if (copies) {
+#pragma unroll
+                for (int j = 0; j < kPer; ++j)
+                    if (e0 + j < nnz) l.idx[e0 + j] = t[j + 1];
+            }
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                int lo = 0, hi = -1;
+                if (l.row && e0 + j <= nnz) rows_closed(k[j], k[j + 1], P, e0 + j, lo, hi, gap);
+                write_rows(l.row, lo, hi, (int32_t)(e0 + j));
+            }
+        }
+        if (kOut && !down && !tdown) {
+            if (inner) {
+                *reinterpret_cast<int4 *>(l.prod_idx + e0) = make_int4(k[1], k[2], k[3], k[4]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kPer; ++j)
+                    if (e0 + j < nnz) l.prod_idx[e0 + j] = k[j + 1];
+            }
+            if (run) {                                                  // four new tensors in a row, each with one producer
+                int32_t *row = l.prod_row + t[1], *word = l.prod1 + t[1];
+                if (((reinterpret_cast<uintptr_t>(row) | reinterpret_cast<uintptr_t>(word)) & 15) == 0) {
+                    *reinterpret_cast<int4 *>(row) = make_int4((int)e0, (int)e0 + 1, (int)e0 + 2, (int)e0 + 3);
+                    *reinterpret_cast<int4 *>(word) = make_int4(k[1], k[2], k[3], k[4]);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < kPer; ++j) {
+                        row[j] = (int32_t)e0 + j;
+                        word[j] = k[j + 1];
+                    }
                 }
             }
-            write_rows(rowptr, lo, hi, (int32_t)e);
+            if (ballot64(!run) != 0) {
+#pragma unroll
+                for (int j = 0; j < kPer; ++j) {
+                    int lo = 0, hi = -1;
+                    if (!run && e0 + j <= nnz) rows_closed(t[j], t[j + 1], T, e0 + j, lo, hi, tgap);
+                    write_rows(l.prod_row, lo, hi, (int32_t)(e0 + j));
+                    // producer words: none for the tensors between, and the tensor itself at its first position
+                    write_rows(l.prod1, lo, hi - 1, kNoProducer);
+                    if (lo <= hi && hi < T) {
+                        const bool again = t[j + 2] == hi;
+                        l.prod1[hi] = again ? kMulti : k[j + 1];
+                        multi |= again;
+                    }
+                }
+            }
         }
     }
-    if (ballot64(gap) != 0 && lane_id() == 0 && load_coherent(wide_gap) == 0) store_coherent(wide_gap, 1);
-    if (ballot64(bad) != 0 && lane_id() == 0) atomicOr(error, kErrIdRange);
     // shuffled input would have every wave report: look first, and store (same value from everyone) only if needed
-    if (ballot64(descends) != 0 && lane_id() == 0 && load_coherent(unsorted) == 0) store_coherent(unsorted, 1);
+    auto report = [&](bool v, int32_t *word) {
+        if (ballot64(v) != 0 && lane_id() == 0 && load_coherent(word) == 0) store_coherent(word, 1);
+    };
+    if (ballot64(bad) != 0 && lane_id() == 0) atomicOr(status, kErrIdRange);
+    if (!kOut) {
+        report(down, status + kStatusInUnsorted);
+        report(gap, status + kStatusInGap);
+    } else {
+        report(down, status + kStatusOutUnsorted);
+        report(gap, status + kStatusOutGap);
+        report(tdown, status + kStatusProdUnsorted);
+        report(tgap, status + kStatusProdGap);
+        report(scattered, status + kStatusScattered);
+        report(multi, status + kStatusMulti);
+    }
 }
 
-hipError_t launch_scan_edges(const int32_t *keys, const int32_t *vals, int64_t nnz, int32_t n_rows, int32_t n_vals,
-                             int32_t *idx_out, int32_t *rowptr, int32_t *error, int32_t *unsorted, int32_t *wide_gap,
-                             hipStream_t s)
+// inputs and outputs in one launch; an empty list has one position too (it closes all rows)
+__global__ __launch_bounds__(kScanThreads) void k_scan_edges(EdgeList in, EdgeList out, int in_blocks, int32_t *status)
 {
-    int64_t blocks = (nnz + 1 + 1023) / 1024;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_scan_edges, dim3((unsigned)blocks), dim3(256), 0, s, keys, vals, nnz, n_rows, n_vals, idx_out,
-                       rowptr, error, unsorted, wide_gap);
+    if ((int)blockIdx.x < in_blocks) scan_list<false>(in, blockIdx.x, in_blocks, status);
+    else scan_list<true>(out, (int)blockIdx.x - in_blocks, (int)gridDim.x - in_blocks, status);
+}
+
+static int scan_blocks(int64_t nnz)
+{
+    const int64_t blocks = (nnz + 1 + kScanThreads * 4 - 1) / (kScanThreads * 4);
+    return (int)(blocks < 8192 ? blocks : 8192);
+}
+
+hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s)
+{
+    const int in_blocks = in ? scan_blocks(in->nnz) : 0;
+    hipLaunchKernelGGL(k_scan_edges, dim3((unsigned)(in_blocks + scan_blocks(out.nnz))), dim3(kScanThreads), 0, s,
+                       in ? *in : out, out, in_blocks, status);
     return hipGetLastError();
 }
 
@@ -239,10 +284,20 @@ hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t *ro
     return hipGetLastError();
 }
 
+// Did the pass over the edges leave finished rows (and producer words)?  What it wrote is not to be trusted otherwise: the
+// kernels behind it ask before they use it, so that the host need not wait for the answer in between.
+__device__ __forceinline__ bool adjacency_ready(const int32_t *status, bool producers)
+{
+    int v = status[0] | status[kStatusInUnsorted] | status[kStatusOutUnsorted] | status[kStatusInGap] | status[kStatusOutGap];
+    if (producers) v |= status[kStatusProdUnsorted] | status[kStatusProdGap];
+    return v == 0;
+}
+
 // Topological precondition (Sec. 3.2: operators run in creation order): every producer of an
 // operator's input was created before the operator.
 __global__ __launch_bounds__(256) void k_check_topological(GraphView g, int32_t *error)
 {
+    if (!adjacency_ready(error, true)) return;
     const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
     bool bad = false;
     for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < g.num_ops; o += gsize) {
@@ -281,34 +336,98 @@ __device__ __forceinline__ int find_graph(const int64_t *off, int num_graphs, in
     return lo;
 }
 
-// status[w] = max(status[w], v over the wave), v >= 0: one look, and an atomic only where it would change something
-__device__ __forceinline__ void raise_status(int32_t *status, int v)
+// Operator records (see common.h), once per graph.
+__device__ __forceinline__ int4 record_of(int32_t ib, int32_t ie, int32_t ob, int32_t oe, int32_t first, bool consecutive)
 {
-    const int m = wave_max(v);
-    if (lane_id() == 0 && m > load_coherent(status)) atomicMax(status, m);
+    return consecutive ? make_int4(ib, ie - ib, first, oe - ob) : make_int4(ib, ie - ib, ob, -(oe - ob));
 }
 
-// also_topological: the topological precondition is checked in the same walk (see k_check_topological), which
-// spares a packed batch a second pass over its input edges.
-// The walk also finds out whether and how the ring sweep can take the graphs (status words from kStatusRing on; see
-// ring_sweep.hip): are the outputs of every graph one run of tensors that ends with its last one, how many tensors
-// lie before that run, how far below the end of its own outputs does an operator read, and how many outputs do 64
-// neighbouring operators have.  A single graph (op_off == NULL) is walked for this alone.
-__global__ __launch_bounds__(256) void k_check_graph_ranges(GraphView g, int32_t *status, bool also_topological)
+// Single graphs.  Outputs that are one run of tensors (see scan_list) need no look at out_idx.
+__global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, const int32_t *status)
 {
+    if (!adjacency_ready(status, false)) return;
+    const bool one_run = status[kStatusScattered] == 0;
+    const int32_t shift = g.num_tensors - g.nnz_out;
+    const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < g.num_ops; o += gsize) {
+        const int32_t ib = g.in_rowptr[o], ie = g.in_rowptr[o + 1];
+        const int32_t ob = g.out_rowptr[o], oe = g.out_rowptr[o + 1];
+        int32_t first = oe > ob ? ob + shift : 0;
+        bool consecutive = true;
+        if (!one_run) {
+            first = oe > ob ? g.out_idx[ob] : 0;
+            for (int32_t e = ob + 1; e < oe; ++e) consecutive &= g.out_idx[e] == first + (e - ob);
+        }
+        orec[o] = record_of(ib, ie, ob, oe, first, consecutive);
+    }
+}
+
+hipError_t launch_build_records(const GraphView &g, int4 *orec, const int32_t *status, hipStream_t s)
+{
+    if (g.num_ops == 0) return hipSuccess;
+    int64_t blocks = ((int64_t)g.num_ops + 255) / 256;
+    if (blocks > 8192) blocks = 8192;
+    hipLaunchKernelGGL(k_build_records, dim3((unsigned)blocks), dim3(256), 0, s, g, orec, status);
+    return hipGetLastError();
+}
+
+// Producer words from the tensors' rows (where the pass over the edges did not write them)
+__global__ __launch_bounds__(256) void k_build_producers(GraphView g, int32_t *prod1, int32_t *multi)
+{
+    const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < g.num_tensors; t += gsize) {
+        const int32_t pb = g.prod_rowptr[t], pe = g.prod_rowptr[t + 1];
+        int32_t r = kNoProducer;
+        if (pe - pb == 1) {
+            r = g.prod_idx[pb];
+        } else if (pe - pb > 1) {
+            r = kMulti;
+            *multi = 1;                                     // (the same value from every writer)
+        }
+        prod1[t] = r;
+    }
+}
+
+hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *multi, hipStream_t s)
+{
+    if (g.num_tensors == 0) return hipSuccess;
+    int64_t blocks = ((int64_t)g.num_tensors + 255) / 256;
+    if (blocks > 8192) blocks = 8192;
+    hipLaunchKernelGGL(k_build_producers, dim3((unsigned)blocks), dim3(256), 0, s, g, prod1, multi);
+    return hipGetLastError();
+}
+
+// Records of a packed batch, or of a single graph that the ring sweep may take, and in the same walk over the edges: does
+// every edge of an operator of graph g touch a tensor of graph g, and whether and how the ring sweep can take the graphs
+// (status words from kStatusRing on; see ring_sweep.hip): are the outputs of every graph one run of tensors that ends
+// with its last one, how many tensors lie before that run, how far below the end of its own outputs does an operator read,
+// and how many outputs do 64 neighbouring operators have.  Outputs in one run of which no operator reads its own or a
+// later one are a topological order, which spares a batch the look at every input's producer.
+// The reading of the adjacency bounds it on a large batch (100 000 operators of small graphs: launch and latency).  Workgroups report once each: a look at the status words
+// by every wave was a quarter of the build of a middling batch (27 000 waves: 80 us).
+constexpr int kCheckThreads = 256;
+
+__global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g, int4 *orec, int32_t *status)
+{
+    __shared__ int s_found[6];                      // error, scattered, low, dist, span64
+    if (!adjacency_ready(status, false)) return;
+    if (threadIdx.x < 6) s_found[threadIdx.x] = 0;
+    __syncthreads();
     // a wave walks a contiguous stretch of operators 64 at a time, so a lane's graph index only ever steps
     // forward: one binary search per lane, not one per operator
     const bool batched = g.num_graphs > 1;
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-    const int64_t wave_id = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
+    const int64_t waves = (int64_t)gridDim.x * (kCheckThreads / kWave);
+    const int64_t wave_id = (int64_t)blockIdx.x * (kCheckThreads / kWave) + (threadIdx.x >> 6);
     const int64_t per = (((int64_t)g.num_ops + waves - 1) / waves + kWave - 1) / kWave * kWave;
-    const int64_t first = wave_id * per, last = min(first + per, (int64_t)g.num_ops);
-    bool bad = false, late = false, scattered = false;
+    const int64_t begin = wave_id * per, last = min(begin + per, (int64_t)g.num_ops);
+    bool bad = false, scattered = false;
     int low = 0, dist = 0, span64 = 0;
     int gi = -1;
     int64_t lo = 0, hi = g.num_tensors, o_lo = 0, o_hi = g.num_ops;
     int32_t shift = 0, t_first = 0;                         // output edge e should be tensor e + shift
-    for (int64_t o = first + lane_id(); o < last; o += kWave) {
+    for (int64_t o = begin + lane_id(); o < last; o += kWave) {
+        const int32_t ib = g.in_rowptr[o], ie = g.in_rowptr[o + 1];
+        const int32_t ob = g.out_rowptr[o], oe = g.out_rowptr[o + 1];
         if (gi < 0 || o >= o_hi) {
             if (batched) {
                 if (gi < 0) gi = find_graph(g.op_off, g.num_graphs, o);
@@ -325,44 +444,65 @@ __global__ __launch_bounds__(256) void k_check_graph_ranges(GraphView g, int32_t
             if (t_first < lo) scattered = true;             // more outputs than tensors
             low = max(low, t_first - (int32_t)lo);
         }
-        const int32_t ob = g.out_rowptr[o], oe = g.out_rowptr[o + 1];
-        for (int32_t e = g.in_rowptr[o]; e < g.in_rowptr[o + 1]; ++e) {
-            const int32_t t = g.in_idx[e];
-            if (t < lo || t >= hi) bad = true;
-            if (t >= t_first) {
-                if (t >= ob + shift) scattered = true;      // not written before, if the outputs are one run
-                dist = max(dist, oe + shift - t);
-            }
-            if (also_topological && t >= 0 && t < g.num_tensors) {
-                const int32_t pr = g.prod1[t];
-                if (pr >= 0) {
-                    if (pr >= o) late = true;
-                } else if (pr == kMulti) {
-                    for (int32_t p = g.prod_rowptr[t]; p < g.prod_rowptr[t + 1]; ++p)
-                        if (g.prod_idx[p] >= o) late = true;
-                }
-            }
+        // (an operator without inputs or outputs looks at a neighbour's entry and does not use it)
+        const int32_t none_in = max(g.nnz_in - 1, 0), none_out = max(g.nnz_out - 1, 0);
+        int32_t t[4] = {0, 0, 0, 0}, u[2] = {0, 0};
+        if (g.nnz_in > 0) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) t[j] = g.in_idx[min(ib + j, none_in)];
         }
-        for (int32_t e = ob; e < oe; ++e) {
-            const int32_t t = g.out_idx[e];
-            if (t < lo || t >= hi) bad = true;
-            if (t != e + shift) scattered = true;
+        if (g.nnz_out > 0) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) u[j] = g.out_idx[min(ob + j, none_out)];
         }
+        auto input = [&](int32_t x) {
+            if (x < lo || x >= hi) bad = true;
+            if (x >= t_first) {
+                if (x >= ob + shift) scattered = true;      // not written before, if the outputs are one run
+                dist = max(dist, oe + shift - x);
+            }
+        };
+        bool consecutive = true;
+        const int32_t first = oe > ob ? u[0] : 0;
+        auto output = [&](int32_t e, int32_t y) {
+            if (y < lo || y >= hi) bad = true;
+            if (y != e + shift) scattered = true;
+            consecutive &= y == first + (e - ob);
+        };
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (ib + j < ie) input(t[j]);
+        for (int32_t e = ib + 4; e < ie; ++e) input(g.in_idx[e]);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (ob + j < oe) output(ob + j, u[j]);
+        for (int32_t e = ob + 2; e < oe; ++e) output(e, g.out_idx[e]);
+        orec[o] = record_of(ib, ie, ob, oe, first, consecutive);
         if (((o - o_lo) & (kWave - 1)) == 0) span64 = max(span64, g.out_rowptr[min(o + kWave, o_hi)] - ob);
     }
-    if (bad || late) atomicOr(&status[0], (bad ? kErrCrossGraph : 0) | (late ? kErrTopo : 0));
-    raise_status(&status[kStatusRing], scattered ? 1 : 0);
-    raise_status(&status[kStatusRing + 1], low);
-    raise_status(&status[kStatusRing + 2], dist);
-    raise_status(&status[kStatusRing + 3], span64);
+    const int wlow = wave_max(low), wdist = wave_max(dist), wspan = wave_max(span64);
+    const bool wbad = ballot64(bad) != 0, wscattered = ballot64(scattered) != 0;
+    if (lane_id() == 0) {
+        if (wbad) s_found[0] = 1;
+        if (wscattered) s_found[1] = 1;
+        atomicMax(&s_found[2], wlow);
+        atomicMax(&s_found[3], wdist);
+        atomicMax(&s_found[4], wspan);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_found[0]) atomicOr(&status[0], kErrCrossGraph);
+    if (threadIdx.x < 4) {                                  // one look, and an atomic only where it would change something
+        const int v = s_found[1 + threadIdx.x];
+        if (v > load_coherent(&status[kStatusRing + threadIdx.x])) atomicMax(&status[kStatusRing + threadIdx.x], v);
+    }
 }
 
-hipError_t launch_check_graph_ranges(const GraphView &g, int32_t *status, bool also_topological, hipStream_t s)
+hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *status, int num_cus, hipStream_t s)
 {
     if (g.num_ops == 0) return hipSuccess;
-    int64_t blocks = ((int64_t)g.num_ops + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_check_graph_ranges, dim3((unsigned)blocks), dim3(256), 0, s, g, status, also_topological);
+    int64_t blocks = ((int64_t)g.num_ops + kCheckThreads - 1) / kCheckThreads;
+    if (blocks > 8 * num_cus) blocks = 8 * num_cus;
+    hipLaunchKernelGGL(k_records_and_check, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, status);
     return hipGetLastError();
 }
 

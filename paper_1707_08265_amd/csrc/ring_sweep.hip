@@ -15,7 +15,7 @@
 // complete in order, so that needs no barrier); barriers pass the bits on between waves, one more round for every hop
 // that crosses from one wave to another.
 //
-// What a graph must satisfy is found out when it is built (k_check_graph_ranges): operators in topological order,
+// What a graph must satisfy is found out when it is built (k_records_and_check): operators in topological order,
 // outputs in one run up to the graph's last tensor, at most `low` graph inputs, no input further than `dist` below the
 // end of its operator's own outputs, at most `span64` outputs per 64 operators.  The ring holds dist + 3 W span64 tensors,
 // rounded up to a power of two: the group, everything it reads, and two groups of slack, so that a target bit may arrive

@@ -36,43 +36,6 @@
 namespace dgn {
 
 // ------------------------------------------------------------------------------------------------
-// operator records and producer words, built once per graph
-// ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, int32_t *prod1, int32_t *multi)
-{
-    const int64_t gsize = (int64_t)gridDim.x * blockDim.x, gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int64_t t = gtid; t < g.num_tensors; t += gsize) {
-        const int32_t pb = g.prod_rowptr[t], pe = g.prod_rowptr[t + 1];
-        int32_t r = kNoProducer;
-        if (pe - pb == 1) {
-            r = g.prod_idx[pb];
-        } else if (pe - pb > 1) {
-            r = kMulti;
-            *multi = 1;                                      // (the same value from every writer)
-        }
-        prod1[t] = r;
-    }
-    for (int64_t o = gtid; o < g.num_ops; o += gsize) {
-        const int32_t ib = g.in_rowptr[o], ie = g.in_rowptr[o + 1];
-        const int32_t ob = g.out_rowptr[o], oe = g.out_rowptr[o + 1];
-        const int32_t first = oe > ob ? g.out_idx[ob] : 0;
-        bool consecutive = true;
-        for (int32_t e = ob + 1; e < oe; ++e) consecutive &= g.out_idx[e] == first + (e - ob);
-        orec[o] = consecutive ? make_int4(ib, ie - ib, first, oe - ob) : make_int4(ib, ie - ib, ob, -(oe - ob));
-    }
-}
-
-hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *multi, hipStream_t s)
-{
-    const int64_t n = g.num_tensors > g.num_ops ? g.num_tensors : g.num_ops;
-    if (n == 0) return hipSuccess;
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_build_records, dim3((unsigned)blocks), dim3(256), 0, s, g, orec, prod1, multi);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------------
 // segmented work queues
 //
 // A queue holds operator ids.  It is split into S segments with one push counter each (64 bytes apart):

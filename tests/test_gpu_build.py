@@ -1,0 +1,100 @@
+"""GPU parity of the builder's pass over the edge lists: lists in operator order (finished by it alone), gaps between rows at
+the lengths where they are left to another pass, tensors with several producers, and lists in other orders; the
+adjacency against the oracle's, and records and producer words through a prune that reads them."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+from helpers import targets_from_sets
+from test_gpu_parity import assert_same, oracle_prune
+
+pytestmark = pytest.mark.gpu
+ROWS = ("in_rowptr", "in_idx", "out_rowptr", "out_idx", "prod_rowptr", "prod_idx")
+
+
+@pytest.fixture(scope="module")
+def dgn():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_1707_08265_amd as d
+    return d
+
+
+def listed(rng, writers, first_gap, gap, several):
+    """`writers` operators that write one tensor each, `gap` tensors without producer and as many operators without outputs
+    between two of them here and there, first_gap such tensors and operators before the first; several: some tensors are
+    written by the next operators too."""
+    hole = rng.random(writers) < (0.1 if gap else 0)
+    step = 1 + hole * gap
+    op = first_gap + np.cumsum(step) - step[0]
+    t = first_gap + 1 + np.cumsum(step) - step[0]
+    P, T = int(op[-1]) + 1 + gap, int(t[-1]) + 1 + gap
+    out_op, out_t = op, t
+    if several:
+        more = rng.integers(0, 3, writers) * (rng.random(writers) < 0.3)
+        which = np.repeat(np.arange(writers), 1 + more)
+        out_t = t[which]
+        out_op = op[np.minimum(which + np.arange(which.size) - np.searchsorted(which, which), writers - 1)]
+        order = np.argsort(out_op, kind="stable")
+        out_op, out_t = out_op[order], out_t[order]
+    fan = rng.integers(0, 4, writers)
+    in_op = np.repeat(op, fan)
+    in_t = (rng.random(in_op.size) * np.repeat(t, fan)).astype(np.int64)
+    i32 = lambda a: np.ascontiguousarray(a, dtype=np.int32)  # noqa: E731
+    return gg.Graph(P, T, i32(in_op), i32(in_t), i32(out_op), i32(out_t), name="listed")
+
+
+def check(dgn, oracle, g, rng, what):
+    import torch
+    sets = [[int(x) for x in rng.integers(0, g.num_tensors, 3)] for _ in range(7)]
+    tg = targets_from_sets(sets, 7)
+    adj, ref = oracle_prune(oracle, g, tg)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    for borrowed in (False, True):
+        if borrowed:
+            desc = dgn.make_csr_desc(g.num_ops, g.num_tensors, *(keep := [up(getattr(adj, n)) for n in ROWS[:4]]))
+            rc, mem, scratch = dgn.dgn_graph_from_csr_workspace(desc)
+            mem, scratch = (torch.full((n,), 255, dtype=torch.uint8, device="cuda") for n in (mem, scratch))
+            rc, handle = dgn.dgn_graph_from_csr(desc, mem, mem.numel(), scratch, scratch.numel())
+            assert rc == 0, dgn.dgn_strerror(rc)
+            dg = dgn.DeviceGraph(handle, mem, keep, dgn.dgn_graph_get_sizes(handle)[1])
+        else:
+            dg = dgn.DeviceGraph.from_coo(g)
+        csr = {n: v.cpu().numpy() for n, v in dg.csr().items()}
+        for name in ROWS:
+            assert np.array_equal(csr[name], getattr(adj, name)), f"{what}, borrowed {borrowed}: {name}"
+        buf = dgn.PruneBuffers(dg, 7)
+        rc = buf.prune(up(tg.tgt_rowptr), up(tg.tgt_idx), options=dgn.dgn_options(traversal=1))
+        assert rc == 0
+        assert_same(buf.to_host(), ref, f"{what}, borrowed {borrowed}")
+
+
+@pytest.mark.parametrize("several", [False, True])
+@pytest.mark.parametrize("shape", [(1, 0, 0), (3, 1, 0), (4, 3, 0), (255, 5, 1), (1023, 16, 2), (1024, 0, 63), (1025, 7, 64),
+                                   (3000, 8190, 65), (5000, 8191, 3), (4096, 8192, 0), (140_000, 16, 0), (90_000, 3, 70)])
+def test_lists_in_order(dgn, oracle, shape, several):
+    rng = np.random.default_rng(sum(shape) + several)
+    check(dgn, oracle, listed(rng, *shape, several), rng, f"{shape}")
+
+
+@pytest.mark.parametrize("several", [False, True])
+@pytest.mark.parametrize("order", ["outputs", "inputs", "all", "halves", "tensors", "one"])
+def test_lists_in_other_orders(dgn, oracle, order, several):
+    """Outputs that are back in order by tensor once they are sorted by operator, and outputs that are not."""
+    rng = np.random.default_rng(17 + several)
+    for shape in ((700, 5, 2), (150_000, 16, 0)):
+        g = listed(rng, *shape, several)
+        ni, no = g.nnz_in, g.nnz_out
+        pi, po = np.arange(ni), np.arange(no)
+        if order in ("inputs", "all"):
+            pi = rng.permutation(ni)
+        if order in ("outputs", "all"):
+            po = rng.permutation(no)
+        if order == "halves":                    # two threads' recordings, one behind the other
+            pi, po = np.concatenate([pi[1::2], pi[::2]]), np.concatenate([po[1::2], po[::2]])
+        if order == "one":                       # a single pair out of order
+            po[no // 2], po[no // 2 + 1] = po[no // 2 + 1], po[no // 2]
+        if order == "tensors":                   # operators in order, tensors not
+            g.out_tensor[:] = rng.permutation(g.out_tensor)
+        h = gg.Graph(g.num_ops, g.num_tensors, g.in_op[pi], g.in_tensor[pi], g.out_op[po], g.out_tensor[po], name=order)
+        check(dgn, oracle, h, rng, f"{order} {shape}")
