@@ -324,12 +324,11 @@ int enqueue_records(const dgn_graph *h, const GraphLayout &L, int32_t *status, c
 }
 
 // Tensor -> producer rows by a stable sort of the outputs in operator order (outputs by tensor: each tensor's producers stay
-// ascending in operator id), or, if only long gaps were left out, from the tensors as they are; then the producer words.
-int build_producers(const dgn_graph *h, const GraphLayout &L, const BuildScratch &S, const int32_t *ops_of_out, bool sorted,
-                    hipStream_t s)
+// ascending in operator id), or, if only long gaps were left out, from the list in order by tensor; then the producer words.
+int build_producers(const dgn_graph *h, const GraphLayout &L, const BuildScratch &S, const int32_t *ops_of_out,
+                    const int32_t *keys, hipStream_t s)
 {
-    const int32_t *keys = h->v.out_idx;
-    if (!sorted) {
+    if (!keys) {
         DGN_HIP(launch_sort_pairs(h->v.out_idx, ops_of_out, S.sorted_keys, L.prod_idx, h->Eout, key_bits_for(h->T), S.sort_tmp, s));
         keys = S.sorted_keys;
     }
@@ -431,9 +430,9 @@ int build_from_lists(dgn_graph *h, const dgn_coo_desc *d, const GraphLayout &L, 
     bool out_gap = f[kStatusOutGap], prod_unsorted = f[kStatusProdUnsorted], prod_gap = f[kStatusProdGap];
     if (!(in_unsorted || in_gap || out_unsorted || out_gap || prod_unsorted || prod_gap)) return DGN_OK;
     // Otherwise stable sorts: edges by operator (rows keep COO order), row pointers from the sorted keys (first position of
-    // every key): no histogram, no atomics.  The outputs, once in operator order, get the same pass as above: where tensors
-    // are numbered as they are created they are in order by tensor as well, whatever order they came in, and need no second
-    // sort.
+    // every key): no histogram, no atomics.  The outputs, once in operator order and every operator's tensors ascending, get
+    // the same pass as above: where tensors are numbered as they are created that is the order by tensor, whatever order they
+    // came in, and they need no second sort.
     if (in_unsorted) {
         DGN_HIP(launch_sort_pairs(d->in_op, d->in_tensor, S.sorted_keys, L.in_idx, Ein, key_bits_for(P), S.sort_tmp, s));
         DGN_HIP(launch_row_bounds(S.sorted_keys, Ein, (int32_t)P, L.in_rowptr, s));
@@ -445,7 +444,8 @@ int build_from_lists(dgn_graph *h, const dgn_coo_desc *d, const GraphLayout &L, 
         DGN_HIP(launch_sort_pairs(d->out_op, d->out_tensor, S.sorted_ops, L.out_idx, Eout, key_bits_for(P), S.sort_tmp, s));
         ops_of_out = S.sorted_ops;
         DGN_HIP(launch_clear(clr, 1, s));
-        const EdgeList sorted{S.sorted_ops, L.out_idx, Eout, (int32_t)P, (int32_t)T, nullptr, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1};
+        DGN_HIP(launch_order_rows(S.sorted_ops, L.out_idx, Eout, S.sorted_keys, S.status, s));
+        const EdgeList sorted{S.sorted_ops, S.sorted_keys, Eout, (int32_t)P, (int32_t)T, nullptr, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1};
         DGN_HIP(launch_scan_edges(nullptr, sorted, S.status, s));
         rc = enqueue_records(h, L, S.status, options, s);
         if (rc) return rc;
@@ -456,9 +456,11 @@ int build_from_lists(dgn_graph *h, const dgn_coo_desc *d, const GraphLayout &L, 
         prod_gap = f[kStatusProdGap];
         if (!(out_gap || prod_unsorted || prod_gap)) return DGN_OK;
     }
+    // (a long gap between tensors, but their order known: the keys are the ones that were found to ascend)
+    const int32_t *by_tensor = out_unsorted ? S.sorted_keys : L.out_idx;
     if (out_gap) DGN_HIP(launch_row_bounds(ops_of_out, Eout, (int32_t)P, L.out_rowptr, s));
     if (prod_unsorted || prod_gap) {
-        rc = build_producers(h, L, S, ops_of_out, !prod_unsorted, s);
+        rc = build_producers(h, L, S, ops_of_out, prod_unsorted ? nullptr : by_tensor, s);
         if (rc) return rc;
     }
     FillRegion ready[1] = {{S.status, kStatusOrder * sizeof(int32_t)}};
@@ -596,7 +598,7 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
         if (e) return e;
         e = read_status(S.status, s, &found);
         if (e || !(found[kStatusProdUnsorted] || found[kStatusProdGap])) return e;
-        e = build_producers(h, L, S, S.sorted_ops, !found[kStatusProdUnsorted], s);
+        e = build_producers(h, L, S, S.sorted_ops, found[kStatusProdUnsorted] ? nullptr : d->out_idx, s);
         if (e) return e;
         FillRegion ready[1] = {{S.status, kStatusOrder * sizeof(int32_t)}};
         DGN_HIP(launch_clear(ready, 1, s));

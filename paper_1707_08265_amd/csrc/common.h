@@ -249,7 +249,7 @@ size_t scan_tmp_bytes(int64_t n);
 hipError_t launch_exclusive_scan(const int32_t *in, int32_t *out, int64_t n, void *tmp, hipStream_t s);
 
 // Stable LSD radix sort of (key, val) pairs on the low `key_bits` bits of the keys.
-// Result: vals_out (always) and keys_out (when not NULL).  keys_in / vals_in are not modified.
+// Result: vals_out and keys_out.  keys_in / vals_in are not modified.
 // tmp: scratch of sort_tmp_bytes(n) bytes.
 size_t sort_tmp_bytes(int64_t n);
 hipError_t launch_sort_pairs(const int32_t *keys_in, const int32_t *vals_in, int32_t *keys_out,
@@ -287,6 +287,9 @@ hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *sta
 hipError_t launch_check_topological(const GraphView &g, int32_t *status, hipStream_t s);
 // producer words from prod_rowptr / prod_idx; *multi = 1 when some tensor has several producers
 hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *multi, hipStream_t s);
+// keys[e] = the tensors of a list in operator order, ascending inside every operator's row; flags rows longer than 64
+// (left as they are) as unsorted by tensor, and any change as "scattered"
+hipError_t launch_order_rows(const int32_t *ops, const int32_t *tensors, int64_t nnz, int32_t *keys, int32_t *status, hipStream_t s);
 // rowptr[0..n_rows] from keys that are in row order (all in range)
 hipError_t launch_row_bounds(const int32_t *keys, int64_t nnz, int32_t n_rows, int32_t *rowptr, hipStream_t s);
 hipError_t launch_check_csr(const int32_t *rowptr, const int32_t *idx, int32_t n_rows, int32_t nnz,

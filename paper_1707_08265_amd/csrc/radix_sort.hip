@@ -1,15 +1,17 @@
-// Stable LSD radix sort of (int32 key, int32 value) pairs, 9 bits per pass, for the CSR builder.
+// Stable LSD radix sort of (int32 key, int32 value) pairs, at most 9 bits per pass, for the CSR builder.
 //
 // Per pass: (1) digit counts per tile of 8 192 keys, already summed inside groups of 16 tiles, and each group's totals;
-// (2) a small scan over the groups' totals; (3) a scatter in which every wave ranks its keys against the keys of its
+// (2) a small scan of the groups' totals; (3) a scatter in which every wave ranks its keys against the keys of its
 // lower lanes and earlier rounds (ballot "match" masks): keys of one tile are visited in their stored order, so
 // equal keys keep their relative order.  The tile is sorted inside LDS first, so that it leaves in one run per digit.
 // Only the significant key bits are sorted (ceil(log2(rows)) of them), so 50M operators (26 bits) or 100M
-// tensors (27 bits) cost three passes.  (Eight bits per pass and four passes: 9 % slower on that graph; a pass
-// with 512 digits costs more than one with 256, because a tile then leaves in runs half as long, but not a third more.)
+// tensors (27 bits) cost three passes of nine bits.  (Eight bits per pass and four passes: 9 % slower on that graph; a pass
+// with 512 digits costs more than one with 256, because a tile then leaves in runs half as long and the ranking takes a
+// step more, but not a third more.)  Passes of eight bits where as many of them do (up to 24 bits: 26 M pairs by 24 bits
+// 126 -> 115 us per scatter).
 //
 // What a pass costs, per 110 M pairs on the 50 M-operator graph: counting 0.10 ms (the keys once, at the rate of a
-// copy), the scan 0.015 ms, the scatter 0.51 ms = 3.4 TB/s of 16 bytes per pair.  The scatter's time went, in turn, to
+// copy), the scan 0.005 ms (0.015 in three kernels), the scatter 0.51 ms = 3.4 TB/s of 16 bytes per pair.  The scatter's time went, in turn, to
 // the write-back of half-written cache lines (fixed by giving each die a contiguous range of tiles), to one cache
 // line per digit and tile for the slot table (fixed by the tile-major tables), and to the vector instructions of the
 // ranking (halved by the three-input bit operation and longer tiles).
@@ -17,16 +19,17 @@
 
 namespace dgn {
 
-constexpr int kRadixBits = 9;
-constexpr int kRadix = 1 << kRadixBits;
-constexpr int kSortThreads = 1024;                      // threads of a scattering workgroup; the first kRadix of them
+constexpr int kMaxRadixBits = 9;
+constexpr int kSortThreads = 1024;                      // threads of a scattering workgroup; the first 2^bits of them
                                                         // also keep the books of one digit each
 constexpr int kSortWaves = kSortThreads / kWave;
-constexpr int kDigitWaves = kRadix / kWave;
 constexpr int kSortRounds = 8;                          // keys per lane
 constexpr int kSortTile = kSortThreads * kSortRounds;   // keys per workgroup
 
-__device__ __forceinline__ int digit_of(int32_t key, int shift) { return ((uint32_t)key >> shift) & (kRadix - 1); }
+template <int kBits> __device__ __forceinline__ int digit_of(int32_t key, int shift)
+{
+    return ((uint32_t)key >> shift) & ((1 << kBits) - 1);
+}
 
 // The first output slot of a tile's keys with digit d is the number of keys that sort before them: all keys with a
 // smaller digit, and the keys with digit d of earlier tiles.  It is kept in two tables, both tile-major (a row of
@@ -34,14 +37,18 @@ __device__ __forceinline__ int digit_of(int32_t key, int shift) { return ((uint3
 // both touch one contiguous row -- a digit-major table costs the scatter one cache line per digit and tile, a fifth of
 // all the cache lines it asks for:
 //   table[tile][d]   keys with digit d in the earlier tiles of the tile's group of kHistTiles consecutive tiles,
-//   totals[group][d] first the group's keys with digit d, then (k_col_*) the keys with a smaller digit anywhere plus
+//   totals[group][d] first the group's keys with digit d, then (k_col_apply) the keys with a smaller digit anywhere plus
 //                    those with digit d in earlier groups.
+//   sums[chunk][d]   the keys with digit d in a chunk of consecutive groups, added up by the groups; two of them, so that one pass clears
+//                    the next one's.
 constexpr int kHistTiles = 16;
 constexpr int kColChunks = 64;              // the groups are scanned in up to this many chunks of consecutive groups
 
-__global__ __launch_bounds__(kRadix) void k_sort_hist(const int32_t *keys, int64_t n, int shift,
-                                                             int32_t *table, int32_t *totals)
+template <int kBits>
+__global__ __launch_bounds__(1 << kBits) void k_sort_hist(const int32_t *keys, int64_t n, int shift, int32_t *table,
+                                                          int32_t *totals, int32_t *sums, int per_chunk)
 {
+    constexpr int kRadix = 1 << kBits;
     __shared__ int hist[kHistTiles][kRadix];
 #pragma unroll
     for (int t = 0; t < kHistTiles; ++t) hist[t][threadIdx.x] = 0;
@@ -60,14 +67,14 @@ __global__ __launch_bounds__(kRadix) void k_sort_hist(const int32_t *keys, int64
             for (int q = 0; q < kPerThread / 4; ++q) a[q] = *reinterpret_cast<const int4 *>(keys + i + 4 * q);
 #pragma unroll
             for (int q = 0; q < kPerThread / 4; ++q) {
-                atomicAdd(&hist[t][digit_of(a[q].x, shift)], 1);
-                atomicAdd(&hist[t][digit_of(a[q].y, shift)], 1);
-                atomicAdd(&hist[t][digit_of(a[q].z, shift)], 1);
-                atomicAdd(&hist[t][digit_of(a[q].w, shift)], 1);
+                atomicAdd(&hist[t][digit_of<kBits>(a[q].x, shift)], 1);
+                atomicAdd(&hist[t][digit_of<kBits>(a[q].y, shift)], 1);
+                atomicAdd(&hist[t][digit_of<kBits>(a[q].z, shift)], 1);
+                atomicAdd(&hist[t][digit_of<kBits>(a[q].w, shift)], 1);
             }
         } else {
             for (int r = 0; r < kPerThread; ++r)
-                if (i + r < n) atomicAdd(&hist[t][digit_of(keys[i + r], shift)], 1);
+                if (i + r < n) atomicAdd(&hist[t][digit_of<kBits>(keys[i + r], shift)], 1);
         }
     }
     __syncthreads();
@@ -80,81 +87,62 @@ __global__ __launch_bounds__(kRadix) void k_sort_hist(const int32_t *keys, int64
         run += hist[t][threadIdx.x];
     }
     totals[(int64_t)blockIdx.x * kRadix + threadIdx.x] = run;
+    if (run) atomicAdd(&sums[(int64_t)(blockIdx.x / per_chunk) * kRadix + threadIdx.x], run);
 }
 
-// Exclusive scan of totals[group][d] in the order (d, group), in three small steps: per chunk of consecutive groups
-// the sum of every column; one workgroup turns those into each chunk's start per column (the columns' totals scanned
-// across the digits, plus the earlier chunks of the column); every chunk then walks down its rows.
-// (every walk down a column asks for kColBatch rows at a time: one row per round trip would leave these small
-// kernels waiting for memory most of their time)
+// Exclusive scan of totals[group][d] in the order (d, group): a workgroup per chunk of groups, a thread per digit.  Every
+// workgroup works out its chunk's start by itself from all chunks' sums (the columns' totals scanned across the digits, plus
+// the earlier chunks of the column) and then walks down its rows.
+// (every walk down a column asks for kColBatch rows at a time: one row per round trip would leave this small
+// kernel waiting for memory most of its time)
 constexpr int kColBatch = 8;
 
-__global__ __launch_bounds__(kRadix) void k_col_sums(const int32_t *totals, int64_t groups, int per_chunk,
-                                                            int32_t *chunk_sums)
+template <int kBits>
+__global__ __launch_bounds__(1 << kBits) void k_col_apply(int32_t *totals, int64_t groups, int per_chunk, const int32_t *sums,
+                                                          int chunks, int32_t *next_sums)
 {
-    const int64_t g0 = (int64_t)blockIdx.x * per_chunk;
-    const int rows = (int)min((int64_t)per_chunk, groups - g0);
-    const int32_t *col = totals + g0 * kRadix + threadIdx.x;
-    int sum = 0;
-    for (int r = 0; r < rows; r += kColBatch) {
-        int v[kColBatch];
-#pragma unroll
-        for (int j = 0; j < kColBatch; ++j) v[j] = r + j < rows ? col[(r + j) * kRadix] : 0;
-#pragma unroll
-        for (int j = 0; j < kColBatch; ++j) sum += v[j];
-    }
-    chunk_sums[blockIdx.x * kRadix + threadIdx.x] = sum;
-}
-
-__global__ __launch_bounds__(kRadix) void k_col_bases(int32_t *chunk_sums, int chunks)
-{
+    constexpr int kRadix = 1 << kBits, kDigitWaves = kRadix / kWave;
     __shared__ int s_wtot[kDigitWaves];
     const int d = threadIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
     int v[kColChunks];                                       // the whole column, in registers
 #pragma unroll
-    for (int c = 0; c < kColChunks; ++c) v[c] = c < chunks ? chunk_sums[c * kRadix + d] : 0;
-    int col = 0;
+    for (int c = 0; c < kColChunks; ++c) v[c] = c < chunks ? sums[c * kRadix + d] : 0;
+    next_sums[blockIdx.x * kRadix + d] = 0;
+    int col = 0, earlier = 0;
 #pragma unroll
-    for (int c = 0; c < kColChunks; ++c) col += v[c];
+    for (int c = 0; c < kColChunks; ++c) {
+        if (c < (int)blockIdx.x) earlier += v[c];
+        col += v[c];
+    }
     const int incl = wave_incl_scan(col);
     if (lane == kWave - 1) s_wtot[wave] = incl;
     __syncthreads();
-    int run = incl - col;                                    // keys with a smaller digit
+    int run = incl - col + earlier;                          // keys with a smaller digit, and of this one in earlier chunks
 #pragma unroll
     for (int w = 0; w < kDigitWaves; ++w)
         if (w < wave) run += s_wtot[w];
-#pragma unroll
-    for (int c = 0; c < kColChunks; ++c) {
-        if (c < chunks) chunk_sums[c * kRadix + d] = run;
-        run += v[c];
-    }
-}
-
-__global__ __launch_bounds__(kRadix) void k_col_apply(int32_t *totals, int64_t groups, int per_chunk,
-                                                             const int32_t *chunk_sums)
-{
     const int64_t g0 = (int64_t)blockIdx.x * per_chunk;
     const int rows = (int)min((int64_t)per_chunk, groups - g0);
-    int32_t *col = totals + g0 * kRadix + threadIdx.x;
-    int run = chunk_sums[blockIdx.x * kRadix + threadIdx.x];
+    int32_t *column = totals + g0 * kRadix + d;
     for (int r = 0; r < rows; r += kColBatch) {
-        int v[kColBatch];
+        int x[kColBatch];
 #pragma unroll
-        for (int j = 0; j < kColBatch; ++j) v[j] = r + j < rows ? col[(r + j) * kRadix] : 0;
+        for (int j = 0; j < kColBatch; ++j) x[j] = r + j < rows ? column[(r + j) * kRadix] : 0;
 #pragma unroll
         for (int j = 0; j < kColBatch; ++j) {
-            if (r + j < rows) col[(r + j) * kRadix] = run;
-            run += v[j];
+            if (r + j < rows) column[(r + j) * kRadix] = run;
+            run += x[j];
         }
     }
 }
 
 // (eight waves per SIMD: two workgroups of 1 024 threads per CU, which caps the kernel at 64 vector registers)
-template <bool kWriteKeys>
+template <int kBits>
 __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void k_sort_scatter(const int32_t *keys, const int32_t *vals, int32_t *keys_out, int32_t *vals_out, int64_t n, int shift,
                     const int32_t *table, const int32_t *totals, int64_t num_tiles)
 {
+    constexpr int kRadix = 1 << kBits, kDigitWaves = kRadix / kWave;
     // Workgroups go to the chip's eight dies in turn, each with a second-level cache of its own.  Neighbouring tiles
     // write neighbouring runs of the output (a run is shorter than a cache line), so a die takes a contiguous eighth
     // of the tiles and the two halves of a line meet in one cache.
@@ -191,7 +179,7 @@ void k_sort_scatter(const int32_t *keys, const int32_t *vals, int32_t *keys_out,
         const bool valid = i < count;
         key[r] = valid ? tile_keys[i] : 0;
         val[r] = valid ? tile_vals[i] : 0;
-        const int d = digit_of(key[r], shift);
+        const int d = digit_of<kBits>(key[r], shift);
         // others = the lanes whose digit differs from this lane's in some bit (or that hold no key).  For bit b, m =
         // the lanes that have it set and e = this lane's own bit spread over a word: m ^ e marks the lanes that
         // differ in b.  Kept as two 32-bit halves and as the complement of the usual "peers" mask, this is four
@@ -199,7 +187,7 @@ void k_sort_scatter(const int32_t *keys, const int32_t *vals, int32_t *keys_out,
         const u64 held = ballot64(valid);
         uint32_t others_lo = ~(uint32_t)held, others_hi = ~(uint32_t)(held >> 32);
 #pragma unroll
-        for (int b = 0; b < kRadixBits; ++b) {
+        for (int b = 0; b < kBits; ++b) {
             int32_t e = __builtin_amdgcn_sbfe(d, b, 1);                 // -1 if bit b of d is set, else 0
             asm("" : "+v"(e));                                          // (compare e itself, not d shifted once more)
             const u64 m = ballot64(e != 0);
@@ -244,7 +232,7 @@ void k_sort_scatter(const int32_t *keys, const int32_t *vals, int32_t *keys_out,
     __syncthreads();
     // sort the tile inside LDS, so that the global writes below go out in long contiguous runs per digit
 #pragma unroll
-    for (int r = 0; r < kSortRounds; ++r) rank[r] += wcount[wave][digit_of(key[r], shift)];
+    for (int r = 0; r < kSortRounds; ++r) rank[r] += wcount[wave][digit_of<kBits>(key[r], shift)];
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
@@ -256,8 +244,8 @@ void k_sort_scatter(const int32_t *keys, const int32_t *vals, int32_t *keys_out,
     __syncthreads();
     for (int li = threadIdx.x; li < count; li += kSortThreads) {
         const int32_t k = s_keys[li];
-        const int pos = li + s_delta[digit_of(k, shift)];
-        if (kWriteKeys) keys_out[pos] = k;
+        const int pos = li + s_delta[digit_of<kBits>(k, shift)];
+        keys_out[pos] = k;
         vals_out[pos] = s_vals[li];
     }
 }
@@ -265,21 +253,23 @@ void k_sort_scatter(const int32_t *keys, const int32_t *vals, int32_t *keys_out,
 static inline int64_t sort_tiles(int64_t n) { return (n + kSortTile - 1) / kSortTile; }
 static inline int64_t sort_groups(int64_t tiles) { return (tiles + kHistTiles - 1) / kHistTiles; }
 
-// layout of tmp: keyA[n] valA[n] keyB[n] valB[n] table[groups*kHistTiles][kRadix] totals[groups][kRadix]
-// chunk_sums[kColChunks][kRadix]
+// layout of tmp: keyA[n] valA[n] keyB[n] valB[n] table[groups*kHistTiles][radix] totals[groups][radix]
+// sums[2][kColChunks][radix]
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 size_t sort_tmp_bytes(int64_t n)
 {
+    constexpr size_t kRadix = 1 << kMaxRadixBits;
     const int64_t groups = sort_groups(sort_tiles(n));
-    return 4 * align256((size_t)n * 4) + align256((size_t)(groups * kHistTiles * kRadix) * 4) +
-           align256((size_t)(groups * kRadix) * 4) + align256((size_t)kColChunks * kRadix * 4);
+    return 4 * align256((size_t)n * 4) + align256((size_t)(groups * kHistTiles) * kRadix * 4) +
+           align256((size_t)groups * kRadix * 4) + 2 * align256((size_t)kColChunks * kRadix * 4);
 }
 
-hipError_t launch_sort_pairs(const int32_t *keys_in, const int32_t *vals_in, int32_t *keys_out,
-                             int32_t *vals_out, int64_t n, int key_bits, void *tmp, hipStream_t s)
+template <int kBits>
+static hipError_t sort_passes(const int32_t *keys_in, const int32_t *vals_in, int32_t *keys_out, int32_t *vals_out, int64_t n,
+                              int passes, void *tmp, hipStream_t s)
 {
-    if (n == 0) return hipSuccess;
+    constexpr int kRadix = 1 << kBits;
     const int64_t tiles = sort_tiles(n), groups = sort_groups(tiles);
     const int per_chunk = (int)((groups + kColChunks - 1) / kColChunks);
     const int chunks = (int)((groups + per_chunk - 1) / per_chunk);
@@ -292,32 +282,38 @@ hipError_t launch_sort_pairs(const int32_t *keys_in, const int32_t *vals_in, int
     vbuf[1] = reinterpret_cast<int32_t *>(p); p += align256((size_t)n * 4);
     int32_t *table = reinterpret_cast<int32_t *>(p); p += align256((size_t)(groups * kHistTiles * kRadix) * 4);
     int32_t *totals = reinterpret_cast<int32_t *>(p); p += align256((size_t)(groups * kRadix) * 4);
-    int32_t *chunk_sums = reinterpret_cast<int32_t *>(p);
-
-    if (key_bits < 1) key_bits = 1;
-    const int passes = (key_bits + kRadixBits - 1) / kRadixBits;
+    int32_t *sums[2] = {reinterpret_cast<int32_t *>(p), reinterpret_cast<int32_t *>(p) + kColChunks * kRadix};
+    FillRegion clr[1] = {{sums[0], (size_t)chunks * kRadix * sizeof(int32_t)}};
+    hipError_t e = launch_clear(clr, 1, s);
+    if (e != hipSuccess) return e;
     const int32_t *ksrc = keys_in, *vsrc = vals_in;
     for (int pass = 0; pass < passes; ++pass) {
         const bool last = pass == passes - 1;
-        const int shift = pass * kRadixBits;
+        const int shift = pass * kBits;
         int32_t *kdst = last ? keys_out : kbuf[pass & 1];
         int32_t *vdst = last ? vals_out : vbuf[pass & 1];
-        hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)groups), dim3(kRadix), 0, s, ksrc, n, shift, table, totals);
-        hipLaunchKernelGGL(k_col_sums, dim3(chunks), dim3(kRadix), 0, s, totals, groups, per_chunk, chunk_sums);
-        hipLaunchKernelGGL(k_col_bases, dim3(1), dim3(kRadix), 0, s, chunk_sums, chunks);
-        hipLaunchKernelGGL(k_col_apply, dim3(chunks), dim3(kRadix), 0, s, totals, groups, per_chunk, chunk_sums);
-        if (kdst)
-            hipLaunchKernelGGL(k_sort_scatter<true>, dim3(scatter_grid), dim3(kSortThreads), 0, s, ksrc, vsrc,
-                               kdst, vdst, n, shift, table, totals, tiles);
-        else
-            hipLaunchKernelGGL(k_sort_scatter<false>, dim3(scatter_grid), dim3(kSortThreads), 0, s, ksrc, vsrc,
-                               kdst, vdst, n, shift, table, totals, tiles);
-        const hipError_t e = hipGetLastError();
+        hipLaunchKernelGGL(k_sort_hist<kBits>, dim3((unsigned)groups), dim3(kRadix), 0, s, ksrc, n, shift, table, totals,
+                           sums[pass & 1], per_chunk);
+        hipLaunchKernelGGL(k_col_apply<kBits>, dim3(chunks), dim3(kRadix), 0, s, totals, groups, per_chunk,
+                           sums[pass & 1], chunks, sums[(pass & 1) ^ 1]);
+        hipLaunchKernelGGL(k_sort_scatter<kBits>, dim3(scatter_grid), dim3(kSortThreads), 0, s, ksrc, vsrc, kdst, vdst, n, shift,
+                           table, totals, tiles);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
         ksrc = kdst;
         vsrc = vdst;
     }
     return hipSuccess;
+}
+
+hipError_t launch_sort_pairs(const int32_t *keys_in, const int32_t *vals_in, int32_t *keys_out,
+                             int32_t *vals_out, int64_t n, int key_bits, void *tmp, hipStream_t s)
+{
+    if (n == 0) return hipSuccess;
+    if (key_bits < 1) key_bits = 1;
+    const int passes = (key_bits + kMaxRadixBits - 1) / kMaxRadixBits;
+    return key_bits <= 8 * passes ? sort_passes<8>(keys_in, vals_in, keys_out, vals_out, n, passes, tmp, s)
+                                  : sort_passes<9>(keys_in, vals_in, keys_out, vals_out, n, passes, tmp, s);
 }
 
 }  // namespace dgn

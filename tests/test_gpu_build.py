@@ -77,6 +77,21 @@ def test_lists_in_order(dgn, oracle, shape, several):
     check(dgn, oracle, listed(rng, *shape, several), rng, f"{shape}")
 
 
+@pytest.mark.parametrize("most", [1, 3, 4, 5, 9, 63, 64, 65, 200])
+def test_shuffled_outputs_of_operators_with_many(dgn, oracle, most):
+    """Rows inside and beyond what a thread holds, up to the longest that is ordered without a sort and above."""
+    rng = np.random.default_rng(most)
+    n_out = rng.integers(0, most + 1, 400)
+    n_out[7] = most
+    P, T = n_out.size, int(n_out.sum()) + 3
+    out_op, out_t = np.repeat(np.arange(P), n_out), 3 + np.arange(n_out.sum())
+    in_op = np.arange(P)
+    in_t = (rng.random(P) * (3 + np.cumsum(n_out) - n_out)).astype(np.int64)
+    p = rng.permutation(out_op.size)
+    i32 = lambda a: np.ascontiguousarray(a, dtype=np.int32)  # noqa: E731
+    check(dgn, oracle, gg.Graph(P, T, i32(in_op), i32(in_t), i32(out_op[p]), i32(out_t[p]), name="rows"), rng, f"{most}")
+
+
 @pytest.mark.parametrize("several", [False, True])
 @pytest.mark.parametrize("order", ["outputs", "inputs", "all", "halves", "tensors", "one"])
 def test_lists_in_other_orders(dgn, oracle, order, several):
