@@ -232,6 +232,18 @@ __device__ __forceinline__ uint32_t load_coherent(const uint32_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Sixteen bytes of a stream that nobody reads before the caches have lost it: past them where `stream`.  On streams
+// larger than the last-level cache (256 MB) such stores are 8 to 10 % faster; what fits in it is better left there for the
+// next kernel.
+typedef int Int4Vec __attribute__((ext_vector_type(4)));
+constexpr size_t kStreamBytes = (size_t)256 << 20;
+template <bool stream> __device__ __forceinline__ void store16(void *p, int a, int b, int c, int d)
+{
+    const Int4Vec v = {a, b, c, d};
+    if (stream) __builtin_nontemporal_store(v, reinterpret_cast<Int4Vec *>(p));
+    else *reinterpret_cast<Int4Vec *>(p) = v;
+}
+
 // ---- launch wrappers (each returns a hipError_t; nothing synchronises) -------------------------
 struct FillRegion { void *ptr; size_t bytes; };   // ptr 8-byte aligned, bytes multiple of 8
 hipError_t launch_clear(const FillRegion *regions, int num_regions, hipStream_t s);

@@ -53,7 +53,7 @@ __device__ __forceinline__ void rows_closed(int32_t prev, int32_t cur, int32_t n
 // that before, 0.99 ms of a 50 M-operator graph and 0.3 more for the producer words; now 1.00 in all = 4.1 TB/s.
 constexpr int kScanThreads = 256;
 
-template <bool kOut>
+template <bool kOut, bool kStream>
 __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int64_t blocks, int32_t *status)
 {
     constexpr int kPer = 4;
@@ -105,7 +105,7 @@ __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int6
         if (kOut) tdown |= ballot64(td) != 0;
         if (!down) {
             if (copies && inner) {
-                *reinterpret_cast<int4 *>(l.idx + e0) = make_int4(t[1], t[2], t[3], t[4]);
+                store16<kStream>(l.idx + e0, t[1], t[2], t[3], t[4]);
             } else if (copies) {
 #pragma unroll
                 for (int j = 0; j < kPer; ++j)
@@ -120,7 +120,7 @@ __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int6
         }
         if (kOut && !down && !tdown) {
             if (inner) {
-                *reinterpret_cast<int4 *>(l.prod_idx + e0) = make_int4(k[1], k[2], k[3], k[4]);
+                store16<kStream>(l.prod_idx + e0, k[1], k[2], k[3], k[4]);
             } else {
 #pragma unroll
                 for (int j = 0; j < kPer; ++j)
@@ -129,8 +129,8 @@ __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int6
             if (run) {                                                  // four new tensors in a row, each with one producer
                 int32_t *row = l.prod_row + t[1], *word = l.prod1 + t[1];
                 if (((reinterpret_cast<uintptr_t>(row) | reinterpret_cast<uintptr_t>(word)) & 15) == 0) {
-                    *reinterpret_cast<int4 *>(row) = make_int4((int)e0, (int)e0 + 1, (int)e0 + 2, (int)e0 + 3);
-                    *reinterpret_cast<int4 *>(word) = make_int4(k[1], k[2], k[3], k[4]);
+                    store16<kStream>(row, (int)e0, (int)e0 + 1, (int)e0 + 2, (int)e0 + 3);
+                    store16<kStream>(word, k[1], k[2], k[3], k[4]);
                 } else {
 #pragma unroll
                     for (int j = 0; j < kPer; ++j) {
@@ -175,10 +175,11 @@ __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int6
 }
 
 // inputs and outputs in one launch; an empty list has one position too (it closes all rows)
+template <bool kStream>
 __global__ __launch_bounds__(kScanThreads) void k_scan_edges(EdgeList in, EdgeList out, int in_blocks, int32_t *status)
 {
-    if ((int)blockIdx.x < in_blocks) scan_list<false>(in, blockIdx.x, in_blocks, status);
-    else scan_list<true>(out, (int)blockIdx.x - in_blocks, (int)gridDim.x - in_blocks, status);
+    if ((int)blockIdx.x < in_blocks) scan_list<false, kStream>(in, blockIdx.x, in_blocks, status);
+    else scan_list<true, kStream>(out, (int)blockIdx.x - in_blocks, (int)gridDim.x - in_blocks, status);
 }
 
 static int scan_blocks(int64_t nnz)
@@ -190,8 +191,12 @@ static int scan_blocks(int64_t nnz)
 hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s)
 {
     const int in_blocks = in ? scan_blocks(in->nnz) : 0;
-    hipLaunchKernelGGL(k_scan_edges, dim3((unsigned)(in_blocks + scan_blocks(out.nnz))), dim3(kScanThreads), 0, s,
-                       in ? *in : out, out, in_blocks, status);
+    const dim3 grid((unsigned)(in_blocks + scan_blocks(out.nnz)));
+    const size_t written = (in ? (size_t)in->nnz * 4 : 0) + (size_t)out.nnz * 8 + (size_t)out.num_ops * 8 + (size_t)out.num_tensors * 8;
+    if (written > kStreamBytes)
+        hipLaunchKernelGGL(k_scan_edges<true>, grid, dim3(kScanThreads), 0, s, in ? *in : out, out, in_blocks, status);
+    else
+        hipLaunchKernelGGL(k_scan_edges<false>, grid, dim3(kScanThreads), 0, s, in ? *in : out, out, in_blocks, status);
     return hipGetLastError();
 }
 
@@ -409,12 +414,14 @@ __device__ __forceinline__ int find_graph(const int64_t *off, int num_graphs, in
 }
 
 // Operator records (see common.h), once per graph.
-__device__ __forceinline__ int4 record_of(int32_t ib, int32_t ie, int32_t ob, int32_t oe, int32_t first, bool consecutive)
+template <bool kStream>
+__device__ __forceinline__ void write_record(int4 *p, int32_t ib, int32_t ie, int32_t ob, int32_t oe, int32_t first, bool consecutive)
 {
-    return consecutive ? make_int4(ib, ie - ib, first, oe - ob) : make_int4(ib, ie - ib, ob, -(oe - ob));
+    store16<kStream>(p, ib, ie - ib, consecutive ? first : ob, consecutive ? oe - ob : -(oe - ob));
 }
 
 // Single graphs.  Outputs that are one run of tensors (see scan_list) need no look at out_idx.
+template <bool kStream>
 __global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, const int32_t *status)
 {
     if (!adjacency_ready(status, false)) return;
@@ -430,7 +437,7 @@ __global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, 
             first = oe > ob ? g.out_idx[ob] : 0;
             for (int32_t e = ob + 1; e < oe; ++e) consecutive &= g.out_idx[e] == first + (e - ob);
         }
-        orec[o] = record_of(ib, ie, ob, oe, first, consecutive);
+        write_record<kStream>(&orec[o], ib, ie, ob, oe, first, consecutive);
     }
 }
 
@@ -439,7 +446,10 @@ hipError_t launch_build_records(const GraphView &g, int4 *orec, const int32_t *s
     if (g.num_ops == 0) return hipSuccess;
     int64_t blocks = ((int64_t)g.num_ops + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_build_records, dim3((unsigned)blocks), dim3(256), 0, s, g, orec, status);
+    if ((size_t)g.num_ops * sizeof(int4) > kStreamBytes)
+        hipLaunchKernelGGL(k_build_records<true>, dim3((unsigned)blocks), dim3(256), 0, s, g, orec, status);
+    else
+        hipLaunchKernelGGL(k_build_records<false>, dim3((unsigned)blocks), dim3(256), 0, s, g, orec, status);
     return hipGetLastError();
 }
 
@@ -479,6 +489,7 @@ hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *m
 // by every wave was a quarter of the build of a middling batch (27 000 waves: 80 us).
 constexpr int kCheckThreads = 256;
 
+template <bool kStream>
 __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g, int4 *orec, int32_t *status)
 {
     __shared__ int s_found[6];                      // error, scattered, low, dist, span64
@@ -549,7 +560,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
         for (int j = 0; j < 2; ++j)
             if (ob + j < oe) output(ob + j, u[j]);
         for (int32_t e = ob + 2; e < oe; ++e) output(e, g.out_idx[e]);
-        orec[o] = record_of(ib, ie, ob, oe, first, consecutive);
+        write_record<kStream>(&orec[o], ib, ie, ob, oe, first, consecutive);
         if (((o - o_lo) & (kWave - 1)) == 0) span64 = max(span64, g.out_rowptr[min(o + kWave, o_hi)] - ob);
     }
     const int wlow = wave_max(low), wdist = wave_max(dist), wspan = wave_max(span64);
@@ -574,7 +585,10 @@ hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *sta
     if (g.num_ops == 0) return hipSuccess;
     int64_t blocks = ((int64_t)g.num_ops + kCheckThreads - 1) / kCheckThreads;
     if (blocks > 8 * num_cus) blocks = 8 * num_cus;
-    hipLaunchKernelGGL(k_records_and_check, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, status);
+    if ((size_t)g.num_ops * sizeof(int4) > kStreamBytes)
+        hipLaunchKernelGGL(k_records_and_check<true>, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, status);
+    else
+        hipLaunchKernelGGL(k_records_and_check<false>, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, status);
     return hipGetLastError();
 }
 
