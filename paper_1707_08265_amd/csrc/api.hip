@@ -674,7 +674,7 @@ static int ring_waves(const dgn_graph *g, const dgn_options *o, int64_t words = 
     return fits(1) ? 1 : 0;
 }
 
-// dgn_prune of graphs that the ring sweep takes: two launches (three for a packed batch), nothing to clear beforehand.
+// dgn_prune of graphs that the ring sweep takes: one to three launches, nothing to clear beforehand.
 // words > 1: as many words of 64 sets of a single graph at once, num_sets in all.
 static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
                       const int32_t *tgt_idx, u64 *M, u64 *K, uint8_t *op_flag, int32_t *kept_ops, u64 *kept_masks,
@@ -727,7 +727,8 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
     int32_t *status = static_cast<int32_t *>(pin);
     status[0] = status[1] = status[2] = 0;
     if (ev) DGN_HIP(hipEventRecord(ev[1], s));
-    DGN_HIP(launch_ring_sweep(a, waves, g->ring_dist, g->ring_span64, g->max_graph_ops, s));
+    int launches = 0;
+    DGN_HIP(launch_ring_sweep(a, waves, g->ring_dist, g->ring_span64, g->max_graph_ops, &launches, s));
     if (ev) DGN_HIP(hipEventRecord(ev[2], s));
     DGN_HIP(hipStreamSynchronize(s));
     if (stats) {
@@ -736,7 +737,7 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
         memset(stats, 0, sizeof(*stats));
         stats->level_trace = user_trace;
         stats->level_trace_cap = user_cap;
-        stats->launches = g->G > 1 ? 3 : 2;
+        stats->launches = launches;
         stats->levels = g->G < kSweepMinGraphs ? status[1] : 0;
         stats->tensor_visits = g->P * words;
         stats->recycled = status[2];

@@ -350,6 +350,7 @@ struct RingArgs {
     int32_t *host_status;    // pinned host memory: error bits, settling steps
     RecycleHeader *hdr, want;
     int32_t recycle;         // *hdr may say that the buffers hold this kernel's last result
+    int32_t list_here;       // the sweep makes the ordered list itself
     int32_t ring_words, low_words, seed_words;     // LDS: ring, graph inputs (8 bytes each), targets (4 bytes each)
 };
 constexpr int kRingExtraWords = 1 + kWave;
@@ -362,7 +363,7 @@ inline int64_t ring_words(int waves, int dist, int span64)
     while (r < need) r *= 2;
     return r;
 }
-hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, hipStream_t s);
+hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, int *launches, hipStream_t s);
 // One sweep over all operators re-deriving K and pushing new bits to the inputs; *changed |= 1 if any.
 hipError_t launch_fix_sweep(const GraphView &g, u64 *M, u64 *K, uint8_t *flags, int32_t *changed, int grid_blocks, hipStream_t s);
 

@@ -123,11 +123,23 @@ __device__ __forceinline__ uint32_t lane_zero()
     return z;
 }
 
+// What the last workgroup's thread leaves: the header for recycling, and the status for the host.  st: as in RingArgs::graphs.
+__device__ __forceinline__ void ring_finish(const RingArgs &a, int4 st)
+{
+    RecycleHeader h = a.want;
+    if (!a.recycle || st.y) h.magic = 0;
+    *a.hdr = h;
+    a.host_status[0] = st.y;
+    a.host_status[1] = st.z;
+    a.host_status[2] = st.w;
+}
+
 template <int W>
 __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
 {
     constexpr int N = W * kWave;
-    // [R] ring, [low] graph inputs, [1] a word that stays zero, [64] words that take what goes nowhere; targets
+    // [R] ring, [low] graph inputs, [1] a word that stays zero, [64] words that take what goes nowhere; targets; with the
+    // list made here: running counts per word
     extern __shared__ u64 ring[];
     __shared__ int s_flag[3];                       // "a push crossed waves", by round
     __shared__ int s_total[W];                      // kept operators of each wave's word
@@ -155,6 +167,7 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
     const uint32_t low_at = base + (uint32_t)(R - t_lo) * 8u, zero_at = base + (uint32_t)(R + a.low_words) * 8u;
     const uint32_t nowhere = zero_at + 8u + (uint32_t)lane * 8u;
     uint32_t *seeds = reinterpret_cast<uint32_t *>(ring + R + a.low_words + 1 + kWave);
+    int *s_cum = reinterpret_cast<int *>(seeds + a.seed_words);
     auto slot_of = [&](int32_t t) { return base + (uint32_t)(t & (R - 1)) * 8u; };
     auto low_of = [&](int32_t t) { return low_at + (uint32_t)t * 8u; };
     static_assert(kRingExtraWords == 1 + kWave, "words behind the inputs");
@@ -393,7 +406,8 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
         }
         if (lane == 0 && (W == 1 || word >= 0)) {
             at_byte(bits, (uint32_t)word * 8u) = bit_word;
-            at_byte(cum, (uint32_t)word * 4u) = done + upto;       // operators kept in this word and above
+            if (W > 1 && a.list_here) s_cum[word] = done + upto;            // operators kept in this word and above
+            else at_byte(cum, (uint32_t)word * 4u) = done + upto;
         }
         done += all;
         __builtin_amdgcn_wave_barrier();
@@ -423,8 +437,33 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
     if (lane == 0) atomicAdd(&s_relax, relax);
     __syncthreads();
     if (tid == 0) {
-        a.graphs[blockIdx.x] = make_int4(done, s_err, s_relax, found ? 1 : 0);
+        const int4 st = make_int4(done, s_err, s_relax, found ? 1 : 0);
+        a.graphs[blockIdx.x] = st;
         if (!batched) a.kept_count[wd] = done;
+        if (W > 1 && a.list_here) ring_finish(a, st);
+    }
+    if (W > 1 && a.list_here) {
+        // A small single graph: the ordered list right here, one launch and one gap less (2 000 operators: 52 -> 49 us).
+        // Every wave takes the words that it swept, four in flight, and reads back what its own lanes stored.
+        int w = n_words - 1 - wave;
+        for (int step = 0; step < steps; step += 4, w -= 4 * W) {
+            u64 k[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int i = (w - c * W) * kWave + lane;
+                k[c] = step + c < steps && w - c * W >= 0 && i < n ? K[i] : 0;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const u64 kept = ballot64(k[c] != 0);
+                if (kept == 0) continue;                     // (also past the last word)
+                const int pos = done - s_cum[w - c * W] + __popcll(kept & lanemask_lt());
+                if (k[c]) {
+                    a.kept_ops[pos] = (w - c * W) * kWave + lane;
+                    if (a.kept_masks) a.kept_masks[pos] = k[c];
+                }
+            }
+        }
     }
 }
 
@@ -485,12 +524,7 @@ __global__ __launch_bounds__(kRingScatterThreads) void k_ring_scatter(RingArgs a
             st.y |= more.y;
             st.z += more.z;
         }
-        RecycleHeader h = a.want;
-        if (!a.recycle || st.y) h.magic = 0;
-        *a.hdr = h;
-        a.host_status[0] = st.y;
-        a.host_status[1] = st.z;
-        a.host_status[2] = st.w;
+        ring_finish(a, st);
     }
     const int64_t o_lo = batched ? g.op_off[gi] : 0, o_hi = batched ? g.op_off[gi + 1] : g.num_ops;
     if (o_hi <= o_lo) return;
@@ -538,19 +572,28 @@ template <int W> static hipError_t launch_ring_w(const RingArgs &a, size_t lds, 
     return hipGetLastError();
 }
 
-hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, hipStream_t s)
+constexpr int64_t kRingListOps = 16384;
+
+hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, int *launches, hipStream_t s)
 {
     a.ring_words = (int32_t)ring_words(waves, dist, span64);
-    const size_t lds = (size_t)(a.ring_words + a.low_words + kRingExtraWords) * sizeof(u64) + (size_t)a.seed_words * sizeof(uint32_t);
-    hipError_t e = waves == 1 ? launch_ring_w<1>(a, lds, s) : waves == 4 ? launch_ring_w<4>(a, lds, s) : launch_ring_w<16>(a, lds, s);
-    if (e != hipSuccess) return e;
     const int G = a.g.num_graphs;
-    if (G > 1) hipLaunchKernelGGL(k_ring_offsets, dim3(1), dim3(1024), 0, s, a);
-    // a wave per 16 words of the largest graph
     const int64_t words = (max_graph_ops + 63) / 64 + 1;
-    int64_t split = (words + 63) / 64;
+    size_t lds = (size_t)(a.ring_words + a.low_words + kRingExtraWords) * sizeof(u64) + (size_t)a.seed_words * sizeof(uint32_t);
+    // (a wave of the sweep takes four words in 1.2 us, the launch of a pass of its own costs 6: up to about 20 words per wave)
+    a.list_here = G == 1 && a.words == 1 && waves > 1 && max_graph_ops <= kRingListOps && lds + (size_t)words * sizeof(int) <= kRingMaxLds;
+    if (a.list_here) lds += (size_t)words * sizeof(int);
+    hipError_t e = waves == 1 ? launch_ring_w<1>(a, lds, s) : waves == 4 ? launch_ring_w<4>(a, lds, s) : launch_ring_w<16>(a, lds, s);
+    *launches = a.list_here ? 1 : G > 1 ? 3 : 2;
+    if (e != hipSuccess || a.list_here) return e;
+    if (G > 1) hipLaunchKernelGGL(k_ring_offsets, dim3(1), dim3(1024), 0, s, a);
+    // a wave per 16 words of the largest graph, four in flight; per 4 words, one round trip each, while that fits the chip
+    const int64_t rows = G > 1 ? G : a.words;
+    const int64_t per = rows * ((words + 15) / 16) <= 2048 ? 16 : 64;
+    int64_t split = (words + per - 1) / per;
     if (split > 256) split = 256;
-    hipLaunchKernelGGL(k_ring_scatter, dim3((unsigned)(G > 1 ? G : a.words), (unsigned)split), dim3(kRingScatterThreads), 0, s, a);
+    const dim3 grid((unsigned)rows, (unsigned)split);
+    hipLaunchKernelGGL(k_ring_scatter, grid, dim3(kRingScatterThreads), 0, s, a);
     return hipGetLastError();
 }
 
