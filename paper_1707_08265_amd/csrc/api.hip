@@ -1,6 +1,7 @@
 // C ABI of libdgn: argument checking, workspace layout and kernel sequencing (declared in dgn.h).
 // Host code only decides *which* kernels run and where their buffers live; every step of the path
 // itself (adjacency build, seeding, traversal, removal rule, compaction) is a device kernel.
+#include <math.h>
 #include <new>
 #include <string.h>
 
@@ -27,7 +28,11 @@ inline int hip_fail(hipError_t e)
 
 constexpr int64_t kMaxCount = 2147483646;   // counts must stay below 2^31 - 1
 constexpr int kLevelBlocksPerCU = 5;   // workgroups of a wide level per compute unit
-constexpr int kNarrowCap = 1024;            // frontiers up to this size are walked by one workgroup (one round of its threads)
+// Frontiers up to this size are walked by one workgroup (one round of its threads); in graphs that read nearby only smaller
+// ones.  Those are deep (an unrolled RNN: a level per 30 operators of a step), and a level of several hundred entries takes
+// one workgroup 7 us where the 32 hops of a wide launch take 3 us each: 900 000 operators, 33 targets 262 -> 193 us, two million
+// 220 -> 158.  A power-law graph is through after a few levels (300 000 operators, one target: 137 us, the other way 190).
+constexpr int kNarrowCap = 1024, kNarrowCapNear = 320;
 constexpr int kWidePerGroup = 12;           // wide level launches between two single-workgroup launches
 constexpr int kWideGroupsFirst = 4;         // groups in the first batch (one state read-back per batch) ...
 constexpr int kWideGroups = 6;              // ... and in the following ones
@@ -47,7 +52,11 @@ constexpr int64_t kRingMaxGraphOps = (int64_t)1 << 18; // ... and graphs of a ba
 constexpr int kSmallLevel = 16384;           // levels expanding fewer entries than this decay the threshold faster
 constexpr int kDefaultDeferPercent = 74;
 constexpr int kDefaultStartShift = 1;       // deferral threshold starts at P >> 1 ...
-constexpr int kDefaultFloorShift = 10;      // ... and stops (drops to 0) below P >> 10
+constexpr int kNearFloorShift = 3;          // graphs that read nearby ...
+constexpr int kDeepFloorShift = 10;         // ... and deep ones, unless they are
+constexpr int64_t kNearOps = (int64_t)1 << 22;   // no larger than this and
+constexpr int64_t kManyTargets = 512;       // there are at least so many targets
+constexpr int kDefaultFloorPerRoot = 2;      // ... and stops (drops to 0) below 2 sqrt(P)
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -272,6 +281,7 @@ struct dgn_graph {
     int64_t max_graph_ops;  // largest graph of a packed batch (P for a single graph)
     bool ring;              // the ring sweep can take these graphs: see ring_sweep.hip for the three numbers
     int ring_low, ring_dist, ring_span64;
+    bool reads_near, deep;  // operators read what was written not long / only just before (see the schedule in prune_impl)
     uint64_t serial;        // unique per handle in this process
     // Hints only, taken from the last prune of this graph; a wrong one costs launches that return at once,
     // or a second batch, and corrects itself.  Kept apart for full prunes [0] and incremental ones [1],
@@ -294,7 +304,7 @@ struct dgn_graph {
 
 namespace {
 
-constexpr int kStatusWords = kStatusRing + 4;
+constexpr int kStatusWords = kStatusClose + 1;
 
 // The status words of a build, once everything before them is done.
 int read_status(const int32_t *status, hipStream_t s, const int32_t **out)
@@ -359,6 +369,8 @@ int finish_build(dgn_graph *h, const int64_t *op_off_host, const int64_t *t_off_
     h->ring_dist = ring[2];
     h->ring_span64 = ring[3];
     h->multi_producer = found[kStatusMulti] != 0;
+    h->deep = h->G == 1 && found[kStatusClose] * 2 > found[kStatusSampled];
+    h->reads_near = h->G == 1 && found[kStatusSampled] > 0 && found[kStatusFar] * 2 < found[kStatusSampled];
     // The topological precondition is checked when the caller asks for validation, and for packed
     // batches, whose per-graph sweep is only chosen when it holds.  (One random access per edge: not
     // worth paying on every build of a big single graph, whose traversal does not depend on it.)  Where the walk found
@@ -855,15 +867,30 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
         }
     }
     if (ev) DGN_HIP(hipEventRecord(ev[1], s));
-    // deferral schedule: threshold on the producer id, starting at decay*P and decaying geometrically
+    // Deferral schedule: threshold on the producer id, starting at decay*P and decaying geometrically.  Where operators read
+    // from all over the graph, bits keep coming from everywhere above and waiting for them pays down to a floor: below it, one
+    // launch takes the rest, in which operators are processed again and again, but a launch costs 14 us at least.  Best found between P >> 7 at
+    // 200 000 operators (196 -> 180 us against P >> 10) and P >> 12 at 50 M (673 -> 642; backward prune 1 001 -> 921).
+    // Where operators read what was written shortly before, bits come from nearby and soon one after the other, and
+    // waiting for thresholds far below only makes the levels thin: a short schedule for 200 000 operators in 500 layers, 64 sets
+    // 434 -> 366 us, for 702 000 in 900 1 105 -> 733 (none at all: 426, and a large RNN loses what the thresholds spread
+    // over the chip).  In a graph thousands of levels deep a few hundred targets all over it are as many separate
+    // searches, and the thresholds let them run side by side: an RNN of 1 M operators, 70 targets 348 us, the short way 471, 10 M and
+    // 33 targets 236, 333; with many targets the short way is the better one again (540 000 operators, 550 targets 924 -> 745).
+    // The line between the two kinds: half of the sampled operators reading further back than a 32nd of the graph.  Layers
+    // that read the layer before are near from 33 of them on, whatever skips a fifth of the reads make; with 22 layers the long
+    // schedule is the better one (138 us, the short one 164), with 60 the short one (172, 212).  Uniform sources: 90 %.
     const int defer_percent = options && options->defer_percent ? options->defer_percent : kDefaultDeferPercent;
     const int start_shift = options && options->defer_start_shift ? options->defer_start_shift : kDefaultStartShift;
-    const int floor_shift = options && options->defer_floor_shift ? options->defer_floor_shift : kDefaultFloorShift;
     Schedule sch{1.0f, 0, 0, kSmallLevel};
     if (defer_percent < 100) {
         sch.decay = (float)defer_percent / 100.0f;
         sch.theta0 = (int32_t)(g->P >> start_shift);
-        sch.theta_floor = (int32_t)(g->P >> floor_shift);
+        const int floor_shift = options && options->defer_floor_shift ? options->defer_floor_shift
+                                : !g->reads_near                      ? 0
+                                : !g->deep || (num_targets >= kManyTargets && g->P <= kNearOps) ? kNearFloorShift
+                                                                      : kDeepFloorShift;
+        sch.theta_floor = floor_shift ? (int32_t)(g->P >> floor_shift) : (int32_t)(kDefaultFloorPerRoot * sqrt((double)g->P));
         if (sch.theta_floor < 64) sch.theta_floor = 64;
         if (sch.theta0 < sch.theta_floor) sch.theta0 = 0;
     }
@@ -936,7 +963,8 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     if (grid > max_useful) grid = (int)(max_useful > 0 ? max_useful : 1);
     const bool generic_only = options && options->traversal == 1;
     const int hk = (options && options->incremental) ? 1 : 0;      // which set of layout hints
-    const int narrow_cap = generic_only ? 0 : kNarrowCap;
+    const int small_frontier = g->reads_near ? kNarrowCapNear : kNarrowCap;
+    const int narrow_cap = generic_only ? 0 : small_frontier;
     int launch_no = 0;
     int32_t *user_trace = stats ? stats->level_trace : nullptr;
     const int64_t user_trace_cap = stats ? stats->level_trace_cap : 0;
@@ -1023,7 +1051,7 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
         if (!done) compacted = false;      // the speculative pass ran on unfinished masks
         first = false;
     }
-    g->wide_hint[hk].store(hst->max_frontier > (u64)kNarrowCap ? 1 : 0, std::memory_order_relaxed);
+    g->wide_hint[hk].store(hst->max_frontier > (u64)small_frontier ? 1 : 0, std::memory_order_relaxed);
     {
         const int nr = hst->n_runs < kMaxRuns ? hst->n_runs : kMaxRuns;
         bool exact = batch == 1 && used_runs > 0 && hst->n_runs == used_runs;

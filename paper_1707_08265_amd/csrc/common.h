@@ -280,6 +280,9 @@ enum : int {
     kStatusScattered = 17,       // the outputs are not one run of tensors up to the last one
     kStatusRing = 20,            // what k_records_and_check finds out for the ring sweep: [0] != 0: outputs are not one run or
                                  // read too early; [1] graph inputs, [2] dist, [3] span64 (maxima)
+    kStatusSampled = 24,         // operators of a single graph, outputs in one run, whose first input was looked at ...
+    kStatusFar = 25,             // ... those that read further back than a 32nd of the graph ...
+    kStatusClose = 26,           // ... and those that read less than a 2 048th back
 };
 // An edge list and where its adjacency goes.  idx / row == NULL: those are in place already.
 struct EdgeList {
@@ -294,7 +297,7 @@ struct EdgeList {
 hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s);
 // The kernels from here to launch_check_topological do nothing if the status says that there is no adjacency yet.
 // operator records of a single graph / of graphs that are also checked for range and for the ring sweep
-hipError_t launch_build_records(const GraphView &g, int4 *orec, const int32_t *status, hipStream_t s);
+hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *status, hipStream_t s);
 hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *status, int num_cus, hipStream_t s);
 hipError_t launch_check_topological(const GraphView &g, int32_t *status, hipStream_t s);
 // producer words from prod_rowptr / prod_idx; *multi = 1 when some tensor has several producers

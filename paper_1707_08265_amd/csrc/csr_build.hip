@@ -420,14 +420,38 @@ __device__ __forceinline__ void write_record(int4 *p, int32_t ib, int32_t ie, in
     store16<kStream>(p, ib, ie - ib, consecutive ? first : ob, consecutive ? oe - ob : -(oe - ob));
 }
 
+// How far back do operators read?  Sampled (the first input of a few thousand operators, spread over the graph) for the
+// traversal's schedule (see there).  has: this lane's operator has an input, its first is `t`, and tensors are numbered
+// in creation order from t_first on.  Whole waves.
+__device__ __forceinline__ void sample_reach(bool has, int64_t o, int32_t t, int64_t num_ops, int32_t t_first, int64_t num_outputs,
+                                             int32_t *status)
+{
+    has = has && t >= t_first;                              // (graph inputs have no producer)
+    const float back = (float)o / (float)num_ops - (float)(t - t_first) / (float)num_outputs;
+    const u64 seen = ballot64(has), far = ballot64(has && back > 1.0f / 32), close = ballot64(has && back < 1.0f / 2048);
+    if (lane_id() == 0 && seen) {
+        atomicAdd(&status[kStatusSampled], __popcll(seen));
+        if (far) atomicAdd(&status[kStatusFar], __popcll(far));
+        if (close) atomicAdd(&status[kStatusClose], __popcll(close));
+    }
+}
+constexpr int kSampleWaves = 32;         // (updates of one address take 11 ns each)
+
 // Single graphs.  Outputs that are one run of tensors (see scan_list) need no look at out_idx.
 template <bool kStream>
-__global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, const int32_t *status)
+__global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, int32_t *status)
 {
     if (!adjacency_ready(status, false)) return;
     const bool one_run = status[kStatusScattered] == 0;
     const int32_t shift = g.num_tensors - g.nnz_out;
     const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
+    if (one_run && blockIdx.x < kSampleWaves && threadIdx.x < kWave) {
+        // (neighbouring operators of one place in the graph per wave, the places evenly spread)
+        const int64_t o = (int64_t)((double)g.num_ops * blockIdx.x / min((int)gridDim.x, kSampleWaves)) + threadIdx.x;
+        const bool in_range = o < g.num_ops;
+        const int32_t ib = in_range ? g.in_rowptr[o] : 0, ie = in_range ? g.in_rowptr[o + 1] : 0;
+        sample_reach(ie > ib, o, ie > ib ? g.in_idx[ib] : 0, g.num_ops, shift, g.nnz_out, status);
+    }
     for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < g.num_ops; o += gsize) {
         const int32_t ib = g.in_rowptr[o], ie = g.in_rowptr[o + 1];
         const int32_t ob = g.out_rowptr[o], oe = g.out_rowptr[o + 1];
@@ -441,7 +465,7 @@ __global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, 
     }
 }
 
-hipError_t launch_build_records(const GraphView &g, int4 *orec, const int32_t *status, hipStream_t s)
+hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *status, hipStream_t s)
 {
     if (g.num_ops == 0) return hipSuccess;
     int64_t blocks = ((int64_t)g.num_ops + 255) / 256;
@@ -508,6 +532,8 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
     int gi = -1;
     int64_t lo = 0, hi = g.num_tensors, o_lo = 0, o_hi = g.num_ops;
     int32_t shift = 0, t_first = 0;                         // output edge e should be tensor e + shift
+    // (at the first operators of some of the waves)
+    const bool samples = !batched && status[kStatusScattered] == 0 && wave_id % ((waves + kSampleWaves - 1) / kSampleWaves) == 0;
     for (int64_t o = begin + lane_id(); o < last; o += kWave) {
         const int32_t ib = g.in_rowptr[o], ie = g.in_rowptr[o + 1];
         const int32_t ob = g.out_rowptr[o], oe = g.out_rowptr[o + 1];
@@ -538,6 +564,8 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
 #pragma unroll
             for (int j = 0; j < 2; ++j) u[j] = g.out_idx[min(ob + j, none_out)];
         }
+        if (samples && o - lane_id() == begin)
+            sample_reach(ie > ib, o, t[0], g.num_ops, g.num_tensors - g.nnz_out, g.nnz_out, status);
         auto input = [&](int32_t x) {
             if (x < lo || x >= hi) bad = true;
             if (x >= t_first) {
