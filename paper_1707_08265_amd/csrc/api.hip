@@ -1390,7 +1390,7 @@ int dgn_backward_prune(const dgn_graph *g, int32_t num_pairs, const int32_t *obj
     u64 *F = reinterpret_cast<u64 *>(tensor_mask);
 
     // stage one: what every x_wrt depends on (bit i for pair i), and the operators kept for that
-    DGN_HIP(launch_backward_seed(g->T, num_pairs, obj, wrt, S.tgt_rowptr, nullptr, nullptr, nullptr, true, s));
+    DGN_HIP(launch_pair_rows(num_pairs, S.tgt_rowptr, s));
     dgn_options o1{};
     if (options) o1 = *options;
     o1.profile = 0;
@@ -1411,12 +1411,9 @@ int dgn_backward_prune(const dgn_graph *g, int32_t num_pairs, const int32_t *obj
                           ? op_flag : prune_scratch(scratch, g->P, g->T, g->G, o1.max_queue_entries, true).flagbuf;
 
     // stage two: forwards from every x_obj, inside the coloured set of stage one
-    FillRegion clr[1] = {{S.flags, 256}};
-    DGN_HIP(launch_clear(clr, 1, s));
-    DGN_HIP(launch_backward_seed(g->T, num_pairs, obj, wrt, nullptr, S.B, F, S.flags, false, s));
     size_t link_bytes = 0;
     const BackwardLinks L = backward_links(S.links, g->P, g->Ein, &link_bytes);
-    DGN_HIP(launch_link_kept(g->v, S.kept, S.kept_count, S.KB, F, obj, num_pairs, L, S.flags + 1, g->num_cus, s));
+    DGN_HIP(launch_link_kept(g->v, S.kept, S.kept_count, S.KB, S.B, F, obj, wrt, num_pairs, L, S.flags, g->num_cus, s));
     void *pin = nullptr;
     rc = pinned_buffer(&pin);
     if (rc != DGN_OK) return rc;

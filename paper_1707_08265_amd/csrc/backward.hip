@@ -18,7 +18,7 @@
 // already.  So a pass reads one list of operator numbers from end to end and FO, a few MB (a mark of a tensor is one
 // cache line in an array as large as the graph), each FO is written by one lane, without atomics, and B and F are
 // touched once, when the passes are over.  456 000 kept operators with 1.5 M inputs of a 50 M-operator graph: 17 passes of
-// 60 us before, 8 of 36 now (48 us to make the list, 27 to write the marks); the whole call 1.79 ms -> 0.97.
+// 60 us before, 8 of 36 now (48 us to make the list, 27 to write the marks); the whole call 1.79 ms -> 0.91.
 #include "common.h"
 
 namespace dgn {
@@ -30,30 +30,27 @@ __global__ __launch_bounds__(64) void k_iota(int32_t *rowptr, int n)
     if (i <= n) rowptr[i] = i;
 }
 
-// flags[0] collects error bits; pair i seeds bit i at x_obj when x_obj leads to x_wrt (bit i of B) and
-// the two differ (only children are ever compared with x_wrt: a node is not a route to itself).
-__global__ __launch_bounds__(64) void k_seed_pairs(int64_t T, int num_pairs, const int32_t *obj, const int32_t *wrt,
-                                                   const u64 *B, u64 *F, int32_t *flags)
-{
-    const int i = threadIdx.x;
-    if (i >= num_pairs) return;
-    const int32_t a = obj[i], b = wrt[i];
-    if (a < 0 || a >= T || b < 0 || b >= T) {
-        atomicOr(&flags[0], kErrIdRange);
-        return;
-    }
-    const u64 bit = (u64)1 << i;
-    if (a != b && (B[a] & bit)) atomicOr(&F[a], bit);
-}
-
 constexpr int kFwThreads = 256;
 constexpr int kLinkThreads = 1024;
 constexpr int kLinkWaves = kLinkThreads / kWave;
 
 // The kept list's numbers: op_of[o] = 1 + the place of operator o in the list, in the array that held K of the first stage
-// (zero for all others); K and FO by place.
-__global__ __launch_bounds__(kFwThreads) void k_number_kept(const int32_t *kept, const int64_t *kept_count, u64 *place, u64 *Kc)
+// (zero for all others); K by place.  The first wave also clears the flags (flags[0]: error bits) and sets the seeds: pair i
+// seeds bit i at x_obj when x_obj leads to x_wrt (bit i of B) and the two differ (only children are ever compared with
+// x_wrt: a node is not a route to itself).
+__global__ __launch_bounds__(kFwThreads) void k_number_kept(const int32_t *kept, const int64_t *kept_count, u64 *place, u64 *Kc,
+                                                            int64_t T, int num_pairs, const int32_t *obj, const int32_t *wrt,
+                                                            const u64 *B, u64 *F, int32_t *flags)
 {
+    if (blockIdx.x == 0 && threadIdx.x < kWave) {
+        const int i = threadIdx.x;
+        const int32_t a = i < num_pairs ? obj[i] : 0, b = i < num_pairs ? wrt[i] : 0;
+        const bool bad = i < num_pairs && (a < 0 || a >= T || b < 0 || b >= T);
+        const u64 any_bad = ballot64(bad);
+        flags[i] = i == 0 && any_bad ? kErrIdRange : 0;
+        const u64 bit = (u64)1 << i;
+        if (i < num_pairs && !bad && a != b && (B[a] & bit)) atomicOr(&F[a], bit);
+    }
     const int64_t n = *kept_count;
     const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gsize) {
@@ -264,14 +261,9 @@ hipError_t launch_keep_from_list(const GraphView &g, const int32_t *kept, const 
     return hipGetLastError();
 }
 
-hipError_t launch_backward_seed(int64_t T, int num_pairs, const int32_t *obj, const int32_t *wrt, int32_t *tgt_rowptr,
-                                const u64 *B, u64 *F, int32_t *flags, bool rowptr_only, hipStream_t s)
+hipError_t launch_pair_rows(int num_pairs, int32_t *tgt_rowptr, hipStream_t s)
 {
-    if (rowptr_only) {
-        hipLaunchKernelGGL(k_iota, dim3(2), dim3(64), 0, s, tgt_rowptr, num_pairs);
-    } else {
-        hipLaunchKernelGGL(k_seed_pairs, dim3(1), dim3(64), 0, s, T, num_pairs, obj, wrt, B, F, flags);
-    }
+    hipLaunchKernelGGL(k_iota, dim3(2), dim3(64), 0, s, tgt_rowptr, num_pairs);
     return hipGetLastError();
 }
 
@@ -293,16 +285,17 @@ BackwardLinks backward_links(void *mem, int64_t P, int64_t Ein, size_t *bytes)
     return b;
 }
 
-hipError_t launch_link_kept(const GraphView &g, const int32_t *kept, const int64_t *kept_count, u64 *place, const u64 *F,
-                            const int32_t *obj, int num_pairs, const BackwardLinks &b, int32_t *cursor, int num_cus, hipStream_t s)
+hipError_t launch_link_kept(const GraphView &g, const int32_t *kept, const int64_t *kept_count, u64 *place, const u64 *B, u64 *F,
+                            const int32_t *obj, const int32_t *wrt, int num_pairs, const BackwardLinks &b, int32_t *flags,
+                            int num_cus, hipStream_t s)
 {
-    if (g.num_ops == 0) return hipSuccess;
     const int64_t most = ((int64_t)g.num_ops + kFwThreads - 1) / kFwThreads, grid = num_cus * 8;
-    hipLaunchKernelGGL(k_number_kept, dim3((unsigned)(most < grid ? most : grid)), dim3(kFwThreads), 0, s, kept, kept_count,
-                       place, b.K);
+    hipLaunchKernelGGL(k_number_kept, dim3((unsigned)(most < 1 ? 1 : most < grid ? most : grid)), dim3(kFwThreads), 0, s, kept,
+                       kept_count, place, b.K, (int64_t)g.num_tensors, num_pairs, obj, wrt, B, F, flags);
+    if (g.num_ops == 0) return hipGetLastError();
     const int64_t blocks = ((int64_t)g.num_ops + kLinkThreads - 1) / kLinkThreads;
     hipLaunchKernelGGL(k_link_kept, dim3((unsigned)(blocks < num_cus * 2 ? blocks : num_cus * 2)), dim3(kLinkThreads), 0, s, g,
-                       kept, kept_count, place, F, obj, num_pairs, b, cursor);
+                       kept, kept_count, place, F, obj, num_pairs, b, flags + 1);
     return hipGetLastError();
 }
 

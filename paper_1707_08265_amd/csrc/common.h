@@ -417,15 +417,15 @@ struct BackwardLinks {
     uint8_t *owner;          // [Ein] the operator of the group that reads it
 };
 BackwardLinks backward_links(void *mem, int64_t P, int64_t Ein, size_t *bytes);
-hipError_t launch_link_kept(const GraphView &g, const int32_t *kept, const int64_t *kept_count, u64 *place, const u64 *F,
-                            const int32_t *obj, int num_pairs, const BackwardLinks &b, int32_t *cursor, int num_cus, hipStream_t s);
+// flags: [0] error bits, [1] cleared with the other 62 and used by the call, [2] ... for the passes
+hipError_t launch_link_kept(const GraphView &g, const int32_t *kept, const int64_t *kept_count, u64 *place, const u64 *B, u64 *F,
+                            const int32_t *obj, const int32_t *wrt, int num_pairs, const BackwardLinks &b, int32_t *flags,
+                            int num_cus, hipStream_t s);
 hipError_t launch_forward_pass(const GraphView &g, const int64_t *kept_count, const u64 *place, const BackwardLinks &b,
                                int32_t *changed, int num_cus, hipStream_t s);
 hipError_t launch_write_marks(const GraphView &g, bool several_producers, const int32_t *kept, const int64_t *kept_count,
                               const u64 *FO, const u64 *B, u64 *F, u64 *K, uint8_t *flags, int grid_blocks, hipStream_t s);
-// Target row pointers 0..n (rowptr_only) or the seeds of the forward stage.
-hipError_t launch_backward_seed(int64_t T, int num_pairs, const int32_t *obj, const int32_t *wrt, int32_t *tgt_rowptr,
-                                const u64 *B, u64 *F, int32_t *flags, bool rowptr_only, hipStream_t s);
+hipError_t launch_pair_rows(int num_pairs, int32_t *tgt_rowptr, hipStream_t s);     // target row pointers 0..n
 hipError_t launch_keep_from_list(const GraphView &g, const int32_t *kept, const int64_t *kept_count, const u64 *F, u64 *K,
                                  uint8_t *flags, int grid_blocks, hipStream_t s);
 
