@@ -167,6 +167,14 @@ struct PruneScratch {
     size_t bytes;
 };
 
+// Where the ring sweep keeps its flag bytes: the caller's op_flag when the traversal could clear that in whole 8-byte words
+// (a later call recycles either's result), else the scratch array, if there is one.
+uint8_t *ring_flags(const PruneScratch &S, uint8_t *op_flag, int64_t P)
+{
+    const bool whole = op_flag && ((uintptr_t)op_flag & 7) == 0 && P % 8 == 0;
+    return whole || !S.flagbuf ? op_flag : S.flagbuf;
+}
+
 // Segments: enough of them that no push counter sees more than a few hundred waves per level, few
 // enough that tiny graphs do not pay for empty segments.  Total capacity 2T + slack: a level can hold
 // more than T entries because the frontier is not deduplicated (beyond that, the overflow path runs).
@@ -224,6 +232,25 @@ PruneScratch prune_scratch(void *mem, int64_t P, int64_t T, int32_t G, int64_t m
     if (S.pq_replicas == 1) S.pq_part = nullptr;
     S.bytes = c.off;
     return S;
+}
+
+// Lays out everything behind the log again for the ring sweep of several words of 64 sets at once, `words` of them or as many
+// as have room (returned; below two nothing is changed).  Flag bytes have no place in that layout: nothing is recycled, so
+// nobody reads them back.
+int64_t words_scratch(PruneScratch &S, void *scratch, int64_t P, int64_t words)
+{
+    const size_t per = (size_t)ring_bit_words(P, 1);
+    char *room = reinterpret_cast<char *>(S.ring_bits);
+    const size_t bytes = S.bytes - (size_t)(room - static_cast<char *>(scratch));
+    int64_t at_once = (int64_t)((bytes - 3 * 256) / (per * (sizeof(u64) + sizeof(int32_t)) + sizeof(int4)));
+    if (at_once > words) at_once = words;
+    if (at_once < 2) return 1;
+    Carver c(room);
+    S.ring_bits = c.take<u64>(per * (size_t)at_once);
+    S.ring_cum = c.take<int32_t>(per * (size_t)at_once);
+    S.ring_graphs = c.take<int4>((size_t)at_once);
+    S.flagbuf = nullptr;
+    return at_once;
 }
 
 // One small pinned buffer per host thread for status read-backs (never freed: a few hundred bytes).
@@ -687,7 +714,8 @@ static int ring_waves(const dgn_graph *g, const dgn_options *o, int64_t words = 
 }
 
 // dgn_prune of graphs that the ring sweep takes: one to three launches, nothing to clear beforehand.
-// words > 1: as many words of 64 sets of a single graph at once, num_sets in all.
+// words > 1: as many words of 64 sets of a single graph at once, num_sets in all.  S.flagbuf == NULL: no flag bytes but
+// the caller's are kept.
 static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
                       const int32_t *tgt_idx, u64 *M, u64 *K, uint8_t *op_flag, int32_t *kept_ops, u64 *kept_masks,
                       int64_t *kept_count, int64_t *per_query_count, const PruneScratch &S, const dgn_options *options,
@@ -706,8 +734,7 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
         FillRegion more[2] = {{also_M, (size_t)g->T * 8}, {also_K, (size_t)g->P * 8}};
         DGN_HIP(launch_clear(more, 2, s));
     }
-    // (words of sets: nothing is recycled, so nobody reads the flags back)
-    uint8_t *flags = words > 1 || (op_flag && ((uintptr_t)op_flag & 7) == 0 && g->P % 8 == 0) ? op_flag : S.flagbuf;
+    uint8_t *flags = ring_flags(S, op_flag, g->P);
     RingArgs a{};
     a.g = g->v;
     a.num_sets = num_sets;
@@ -1284,18 +1311,8 @@ int dgn_prune_words(const dgn_graph *g, int64_t num_sets, int64_t num_targets, c
                                    kept_count, per_query_count, scratch, scratch_bytes, options, &S);
         if (rc) return rc;
         if (ring_waves(g, options)) {
-            const size_t per = (size_t)ring_bit_words(g->P, 1);
-            char *room = reinterpret_cast<char *>(S.ring_bits);
-            const size_t bytes = S.bytes - (size_t)(room - static_cast<char *>(scratch));
-            at_once = (int64_t)((bytes - 3 * 256) / (per * (sizeof(u64) + sizeof(int32_t)) + sizeof(int4)));
-            at_once = at_once < 1 ? 1 : at_once < words ? at_once : words;
-            if (at_once > 1) {
-                Carver c(room);
-                S.ring_bits = c.take<u64>(per * (size_t)at_once);
-                S.ring_cum = c.take<int32_t>(per * (size_t)at_once);
-                S.ring_graphs = c.take<int4>((size_t)at_once);
-                ring = ring_waves(g, options, at_once);
-            }
+            at_once = words_scratch(S, scratch, g->P, words);
+            if (at_once > 1) ring = ring_waves(g, options, at_once);
         }
     }
     for (int64_t w = 0; w < words; w += at_once) {

@@ -102,7 +102,6 @@ def test_more_targets_than_fit_in_lds_go_through_the_masks(dgn, oracle, G):
 # words than the scratch buffer has room for at once (hardly any tensors), targets that go through the masks
 @pytest.mark.parametrize("shape", [(3001, 2, 150, 4), (20000, 2, 129, 2), (1, 1, 65, 1), (9000, 0, 20000, 1), (700, 3, 640, 90)])
 def test_words_of_sets(dgn, oracle, shape):
-    import torch
     P, out_max, sets, most = shape
     rng = np.random.default_rng(P + sets)
     g = recorded(rng, 1, P, 64, max(out_max, 1), 3, 16)
@@ -111,28 +110,55 @@ def test_words_of_sets(dgn, oracle, shape):
         g = gg.Graph(P, 17, g.in_op, g.in_tensor % 16, g.out_op[keep], np.full(int(keep.sum()), 16, np.int32))
     tg = targets_from_sets([[int(t) for t in rng.integers(0, g.num_tensors, int(rng.integers(0, most + 1)))]
                             for _ in range(sets)], 64)
-    W, T = (sets + 63) // 64, g.num_tensors
+    launches = prune_words(dgn, oracle, g, tg, sets)
+    assert launches <= 2 * -(-sets // 6400)                              # two for a hundred words at once, at least
+
+
+def prune_words(dgn, oracle, g, tg, sets, flags=True):
+    """One call of dgn_prune_words, every word against the oracle; how many kernels it launched."""
+    import torch
+    W, P, T = (sets + 63) // 64, g.num_ops, g.num_tensors
     dg = dgn.DeviceGraph.from_coo(g)
     new = lambda n, t: torch.full((W, n), -1 if t != torch.uint8 else 7, dtype=t, device="cuda")  # noqa: E731
-    out = {"tensor_mask": new(T, torch.int64), "op_mask": new(P, torch.int64), "op_flag": new(P, torch.uint8),
+    out = {"tensor_mask": new(T, torch.int64), "op_mask": new(P, torch.int64), "op_flag": new(P, torch.uint8) if flags else None,
            "kept_ops": new(P, torch.int32), "kept_masks": new(P, torch.int64), "kept_count": new(1, torch.int64),
            "per_query_count": new(64, torch.int64)}
     rc, nbytes = dgn.dgn_prune_workspace(dg.handle, 64)
     scratch = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda")
     ptr, idx = torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda()
-    rc = dgn.dgn_prune_words(dg.handle, sets, idx.numel(), ptr, idx, *out.values(), scratch, nbytes)
+    st = dgn.dgn_stats()
+    rc = dgn.dgn_prune_words(dg.handle, sets, idx.numel(), ptr, idx, *out.values(), scratch, nbytes, stats=st)
     assert rc == 0, dgn.dgn_strerror(rc)
-    host = {k: v.cpu().numpy() for k, v in out.items()}
+    host = {k: v.cpu().numpy() for k, v in out.items() if v is not None}
     for w in range(W):
         rows = tg.tgt_rowptr[64 * w:64 * w + 65]
         one = targets_from_sets([list(tg.tgt_idx[a:b]) for a, b in zip(rows, rows[1:])], 64)
         ref = oracle_prune(oracle, g, one)[1]
         n = int(host["kept_count"][w, 0])
         assert n == int(ref.kept_count[0])
-        for name in ("tensor_mask", "op_mask", "op_flag", "per_query_count"):
+        for name in ("tensor_mask", "op_mask", "per_query_count") + (("op_flag",) if flags else ()):
             assert np.array_equal(host[name][w].view(getattr(ref, name).dtype)[:getattr(ref, name).size], getattr(ref, name)), (name, w)
         assert np.array_equal(host["kept_ops"][w, :n], ref.kept_ops[:n])
         assert np.array_equal(host["kept_masks"][w, :n].view(np.uint64), ref.kept_masks[:n])
+    return int(st.launches)
+
+
+@pytest.mark.parametrize("flags", [True, False])
+def test_words_of_sets_with_a_single_word_left_over(dgn, oracle, flags):
+    """One word more than the scratch buffer has room for at once, no whole number of 8-byte words of flags: the last word is
+    swept alone in the layout for many, which has no place for flag bytes (see test_scratch_layout.py)."""
+    P = 20001
+    rng = np.random.default_rng(P)
+    g = recorded(rng, 1, P, 64, 2, 3, 16)
+    dg = dgn.DeviceGraph.from_coo(g)
+    _, nbytes = dgn.dgn_prune_workspace(dg.handle, 64)
+    log = 512 + 64 * 64 + 64 * 4 * max(4096, g.num_tensors // 256)       # the header and the log come first
+    at_once = (nbytes - log - 768) // ((P // 64 + 2) * 12 + 16)
+    assert at_once > 100
+    for words, launches in ((at_once, 2), (at_once + 1, 4)):
+        sets = 64 * words - 5
+        tg = targets_from_sets([[int(rng.integers(0, g.num_tensors))] for _ in range(sets)], 64)
+        assert prune_words(dgn, oracle, g, tg, sets, flags) == launches
 
 
 def test_graphs_that_the_ring_cannot_hold_take_another_path(dgn, oracle):
