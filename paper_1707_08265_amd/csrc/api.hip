@@ -52,11 +52,12 @@ constexpr int64_t kRingMaxGraphOps = (int64_t)1 << 18; // ... and graphs of a ba
 constexpr int kSmallLevel = 16384;           // levels expanding fewer entries than this decay the threshold faster
 constexpr int kDefaultDeferPercent = 74;
 constexpr int kDefaultStartShift = 1;       // deferral threshold starts at P >> 1 ...
-constexpr int kNearFloorShift = 3;          // graphs that read nearby ...
-constexpr int kDeepFloorShift = 10;         // ... and deep ones, unless they are
-constexpr int64_t kNearOps = (int64_t)1 << 22;   // no larger than this and
-constexpr int64_t kManyTargets = 512;       // there are at least so many targets
-constexpr int kDefaultFloorPerRoot = 2;      // ... and stops (drops to 0) below 2 sqrt(P)
+constexpr int kDefaultFloorShift = 10;      // ... and stops (drops to 0) below P >> 10 or, in large graphs,
+constexpr int kDefaultFloorPerRoot = 2;     // below 2 sqrt(P); earlier, at
+constexpr int kNearFloorShift = 3;          // P >> 3, in graphs that read nearby, and where there are many targets:
+constexpr int64_t kLayeredTargets = 256;    // in graphs of a few dozen layers or more
+constexpr int64_t kDeepTargets = 512;       // in deep graphs no larger than
+constexpr int64_t kDeepOps = (int64_t)1 << 22;
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -298,6 +299,9 @@ int check_options(const dgn_options *o)
 
 }  // namespace
 
+// How far back half of the operators read at most (sampled, single graphs with their outputs in one run of tensors)
+enum class Reach { unknown, layers /* a 32nd of the graph */, near /* a 192nd */, deep /* a 2 048th */ };
+
 struct dgn_graph {
     GraphView v;
     int64_t P, T, Ein, Eout;
@@ -308,7 +312,7 @@ struct dgn_graph {
     int64_t max_graph_ops;  // largest graph of a packed batch (P for a single graph)
     bool ring;              // the ring sweep can take these graphs: see ring_sweep.hip for the three numbers
     int ring_low, ring_dist, ring_span64;
-    bool reads_near, deep;  // operators read what was written not long / only just before (see the schedule in prune_impl)
+    Reach reach;            // how far back the operators of a single graph read (see the schedule in prune_impl)
     uint64_t serial;        // unique per handle in this process
     // Hints only, taken from the last prune of this graph; a wrong one costs launches that return at once,
     // or a second batch, and corrects itself.  Kept apart for full prunes [0] and incremental ones [1],
@@ -331,7 +335,7 @@ struct dgn_graph {
 
 namespace {
 
-constexpr int kStatusWords = kStatusClose + 1;
+constexpr int kStatusWords = kStatusWithin2048 + 1;
 
 // The status words of a build, once everything before them is done.
 int read_status(const int32_t *status, hipStream_t s, const int32_t **out)
@@ -396,8 +400,9 @@ int finish_build(dgn_graph *h, const int64_t *op_off_host, const int64_t *t_off_
     h->ring_dist = ring[2];
     h->ring_span64 = ring[3];
     h->multi_producer = found[kStatusMulti] != 0;
-    h->deep = h->G == 1 && found[kStatusClose] * 2 > found[kStatusSampled];
-    h->reads_near = h->G == 1 && found[kStatusSampled] > 0 && found[kStatusFar] * 2 < found[kStatusSampled];
+    auto most = [&](int word) { return h->G == 1 && found[word] * 2 > found[kStatusSampled]; };
+    h->reach = most(kStatusWithin2048) ? Reach::deep : most(kStatusWithin192) ? Reach::near
+             : most(kStatusWithin32) ? Reach::layers : Reach::unknown;
     // The topological precondition is checked when the caller asks for validation, and for packed
     // batches, whose per-graph sweep is only chosen when it holds.  (One random access per edge: not
     // worth paying on every build of a big single graph, whose traversal does not depend on it.)  Where the walk found
@@ -894,30 +899,37 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
         }
     }
     if (ev) DGN_HIP(hipEventRecord(ev[1], s));
-    // Deferral schedule: threshold on the producer id, starting at decay*P and decaying geometrically.  Where operators read
-    // from all over the graph, bits keep coming from everywhere above and waiting for them pays down to a floor: below it, one
-    // launch takes the rest, in which operators are processed again and again, but a launch costs 14 us at least.  Best found between P >> 7 at
-    // 200 000 operators (196 -> 180 us against P >> 10) and P >> 12 at 50 M (673 -> 642; backward prune 1 001 -> 921).
-    // Where operators read what was written shortly before, bits come from nearby and soon one after the other, and
-    // waiting for thresholds far below only makes the levels thin: a short schedule for 200 000 operators in 500 layers, 64 sets
-    // 434 -> 366 us, for 702 000 in 900 1 105 -> 733 (none at all: 426, and a large RNN loses what the thresholds spread
-    // over the chip).  In a graph thousands of levels deep a few hundred targets all over it are as many separate
-    // searches, and the thresholds let them run side by side: an RNN of 1 M operators, 70 targets 348 us, the short way 471, 10 M and
-    // 33 targets 236, 333; with many targets the short way is the better one again (540 000 operators, 550 targets 924 -> 745).
-    // The line between the two kinds: half of the sampled operators reading further back than a 32nd of the graph.  Layers
-    // that read the layer before are near from 33 of them on, whatever skips a fifth of the reads make; with 22 layers the long
-    // schedule is the better one (138 us, the short one 164), with 60 the short one (172, 212).  Uniform sources: 90 %.
+    // Deferral schedule: threshold on the producer id, starting at decay*P and decaying geometrically down to a floor.  Bits
+    // that keep coming from above are worth waiting for; below the floor, one launch takes the rest, in which
+    // operators are processed again and again, but a launch costs 14 us at least.
+    //   P >> 10 loses nowhere: higher floors are faster for some targets of a power-law graph and slower for others
+    // (400 000 operators, 2 sqrt(P): 64 sets of one target 196 -> 233 us, of 8 223 -> 207).  From 4 M operators on 2 sqrt(P) is the
+    // lower one, and never slower (20 M, one set of 8: 320 -> 252; 50 M, 64 sets: 662 -> 643; backward prune 1 001 -> 921).
+    //   Where operators read what was written shortly before, bits come soon one after the other, and waiting for thresholds
+    // far below only makes the levels thin: P >> 3 for 200 000 operators in 500 layers, 64 sets 405 -> 300 us, for
+    // 702 000 in 900 layers 1 123 -> 740, for 18 000 in 300 layers 262 -> 190.  The line lies at some 218 layers, each reading
+    // mostly the one before: with 100 layers and a handful of targets what is left below P >> 3 is too little to
+    // spread over the chip (300 wide, 8 targets: 152 us, P >> 3 310), with 200 it still is for some (800 wide: 332, 412).
+    //   From some 30 layers on, it pays as well once there are many targets: at 224 and more P >> 3 was the faster one for each of six
+    // shapes (120 layers of 600, 288 targets 307 -> 249), around 150 not for all (264, 286).
+    //   In a graph thousands of levels deep a few hundred targets all over it are as many separate searches, and the
+    // thresholds let them run side by side: an RNN of 1 M operators, 70 targets 348 us, the short way 471, 10 M and
+    // 33 targets 236, 333; with many targets the short way is the better one (544 of them: 80 000 operators 183 -> 137,
+    // 200 000 190 -> 134, 450 000 907 -> 753, 800 000 286 -> 225; larger ones not tried).
     const int defer_percent = options && options->defer_percent ? options->defer_percent : kDefaultDeferPercent;
     const int start_shift = options && options->defer_start_shift ? options->defer_start_shift : kDefaultStartShift;
     Schedule sch{1.0f, 0, 0, kSmallLevel};
     if (defer_percent < 100) {
         sch.decay = (float)defer_percent / 100.0f;
         sch.theta0 = (int32_t)(g->P >> start_shift);
-        const int floor_shift = options && options->defer_floor_shift ? options->defer_floor_shift
-                                : !g->reads_near                      ? 0
-                                : !g->deep || (num_targets >= kManyTargets && g->P <= kNearOps) ? kNearFloorShift
-                                                                      : kDeepFloorShift;
-        sch.theta_floor = floor_shift ? (int32_t)(g->P >> floor_shift) : (int32_t)(kDefaultFloorPerRoot * sqrt((double)g->P));
+        const bool soon = g->reach == Reach::near || (g->reach == Reach::layers && num_targets >= kLayeredTargets) ||
+                          (g->reach == Reach::deep && num_targets >= kDeepTargets && g->P <= kDeepOps);
+        sch.theta_floor = (int32_t)(g->P >> (soon ? kNearFloorShift : kDefaultFloorShift));
+        if (g->reach != Reach::deep && !soon) {
+            const double root = kDefaultFloorPerRoot * sqrt((double)g->P);
+            if (root < sch.theta_floor) sch.theta_floor = (int32_t)root;
+        }
+        if (options && options->defer_floor_shift) sch.theta_floor = (int32_t)(g->P >> options->defer_floor_shift);
         if (sch.theta_floor < 64) sch.theta_floor = 64;
         if (sch.theta0 < sch.theta_floor) sch.theta0 = 0;
     }
@@ -990,7 +1002,7 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     if (grid > max_useful) grid = (int)(max_useful > 0 ? max_useful : 1);
     const bool generic_only = options && options->traversal == 1;
     const int hk = (options && options->incremental) ? 1 : 0;      // which set of layout hints
-    const int small_frontier = g->reads_near ? kNarrowCapNear : kNarrowCap;
+    const int small_frontier = g->reach >= Reach::near ? kNarrowCapNear : kNarrowCap;
     const int narrow_cap = generic_only ? 0 : small_frontier;
     int launch_no = 0;
     int32_t *user_trace = stats ? stats->level_trace : nullptr;

@@ -281,8 +281,9 @@ enum : int {
     kStatusRing = 20,            // what k_records_and_check finds out for the ring sweep: [0] != 0: outputs are not one run or
                                  // read too early; [1] graph inputs, [2] dist, [3] span64 (maxima)
     kStatusSampled = 24,         // operators of a single graph, outputs in one run, whose first input was looked at ...
-    kStatusFar = 25,             // ... those that read further back than a 32nd of the graph ...
-    kStatusClose = 26,           // ... and those that read less than a 2 048th back
+    kStatusWithin32 = 25,        // ... those that read less than a 32nd of the graph back,
+    kStatusWithin192 = 26,       // ... a 192nd,
+    kStatusWithin2048 = 27,      // ... a 2 048th
 };
 // An edge list and where its adjacency goes.  idx / row == NULL: those are in place already.
 struct EdgeList {

@@ -428,12 +428,16 @@ __device__ __forceinline__ void sample_reach(bool has, int64_t o, int32_t t, int
 {
     has = has && t >= t_first;                              // (graph inputs have no producer)
     const float back = (float)o / (float)num_ops - (float)(t - t_first) / (float)num_outputs;
-    const u64 seen = ballot64(has), far = ballot64(has && back > 1.0f / 32), close = ballot64(has && back < 1.0f / 2048);
-    if (lane_id() == 0 && seen) {
-        atomicAdd(&status[kStatusSampled], __popcll(seen));
-        if (far) atomicAdd(&status[kStatusFar], __popcll(far));
-        if (close) atomicAdd(&status[kStatusClose], __popcll(close));
-    }
+    const u64 seen = ballot64(has);
+    auto within = [&](float part, int word) {
+        const u64 m = ballot64(has && back < part);
+        if (lane_id() == 0 && m) atomicAdd(&status[word], __popcll(m));
+    };
+    if (seen == 0) return;
+    if (lane_id() == 0) atomicAdd(&status[kStatusSampled], __popcll(seen));
+    within(1.0f / 32, kStatusWithin32);
+    within(1.0f / 192, kStatusWithin192);
+    within(1.0f / 2048, kStatusWithin2048);
 }
 constexpr int kSampleWaves = 32;         // (updates of one address take 11 ns each)
 

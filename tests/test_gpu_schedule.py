@@ -1,0 +1,55 @@
+"""Which deferral schedule a graph gets, read from the level trace: results never depend on it, times do (the measurements
+stand beside the rule in api.hip)."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dgn():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_1707_08265_amd as d
+    return d
+
+
+def targets(g, family, per_set, sets):
+    """In the last fifth; an unrolled RNN's anywhere (its chains of operators are short)."""
+    return gg.targets_range(3, sets, per_set, per_set, 16 if family == "rnn" else int(g.num_tensors * 0.8), g.num_tensors)
+
+
+def thresholds(dgn, g, tg, **knobs):
+    import torch
+    buf = dgn.PruneBuffers(dgn.DeviceGraph.from_coo(g), tg.num_sets)
+    trace = np.full((512, 4), -7, np.int32)
+    st = dgn.dgn_stats()
+    st.level_trace, st.level_trace_cap = trace.ctypes.data, trace.shape[0]
+    rc = buf.prune(torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda(),
+                   options=dgn.dgn_options(traversal=1, **knobs), stats=st)
+    assert rc == 0, dgn.dgn_strerror(rc)
+    return trace[:int(st.levels), 2]
+
+
+# (family, sizes, targets per set, sets, waits only down to an eighth of the graph): layers too few for that, a handful of
+# targets in a hundred layers and many of them, enough layers, reads from all over the graph, an RNN with few and many targets
+@pytest.mark.parametrize("family,size,per_set,sets,soon", [
+    ("cnn", (24, 700), 8, 1, False), ("cnn", (24, 700), 8, 64, False), ("cnn", (100, 300), 8, 1, False),
+    ("cnn", (100, 300), 8, 64, True), ("cnn", (150, 120), 1, 64, False), ("cnn", (250, 200), 8, 1, True),
+    ("cnn", (250, 200), 1, 64, True), ("powerlaw", (200_000,), 1, 64, False), ("rnn", (400, 200), 4, 64, False),
+    ("rnn", (400, 200), 9, 64, True)])
+def test_floor_of_the_thresholds(dgn, family, size, per_set, sets, soon):
+    g = gg.cnn(*size, 5)[0] if family == "cnn" else gg.rnn(*size, 5) if family == "rnn" else gg.powerlaw(*size, 5)
+    tg = targets(g, family, per_set, sets)
+    theta = thresholds(dgn, g, tg)
+    lowest = int(theta[theta > 0].min())
+    floor = max(64, g.num_ops >> 10)
+    assert lowest >= g.num_ops >> 3 if soon else lowest < 4 * floor, theta     # (one level takes at most 0.7 of a threshold)
+    # nothing is known of a graph whose tensors are numbered in another order, and a floor of the caller's stands
+    g2, t2, _ = gg.relabel_tensors(g, tg, 7)
+    theta = thresholds(dgn, g2, t2)
+    assert int(theta[theta > 0].min()) < 4 * floor, theta
+    theta = thresholds(dgn, g, tg, defer_floor_shift=2)
+    assert int(theta[theta > 0].min()) >= g.num_ops >> 2, theta
