@@ -44,11 +44,13 @@ constexpr int kSweepMinGraphs = 64;         // packed batches with at least this
 constexpr int64_t kSweepMaxGraphOps = 1 << 18;   // ... none larger than this use the per-graph sweep
 constexpr u64 kRecycleMagic = 0x44474e5f52435943ull;   // "DGN_RCYC"
 constexpr u64 kRingMagic = 0x44474e5f52494e47ull;      // "DGN_RING": a result of the ring sweep (bitmap, no log)
-constexpr int64_t kRingMaxOps = (int64_t)1 << 17;      // single graphs up to this size ...
 constexpr int64_t kRingSeedWords = 2048;               // targets of a graph that the ring sweep keeps in LDS, at most
-constexpr int64_t kRingShortOps = 16384;               // single graphs (or fewer graphs than the per-graph sweep starts at): up to this
-constexpr int kRingThinDist = 96;                      // size always, up to kRingMaxOps when no input lies further back than this
-constexpr int64_t kRingMaxGraphOps = (int64_t)1 << 18; // ... and graphs of a batch up to this size may take the ring sweep
+// Which graphs may take the ring sweep (see ring_waves):
+constexpr int64_t kRingMaxOps = (int64_t)1 << 17;      // single graphs: at most this size, and
+constexpr int64_t kRingShortOps = 16384;               // (or fewer graphs than the per-graph sweep starts at) up to this size, or
+constexpr int64_t kRingThinOps = 20480;                // to this, times the words of sets, when no input lies further back
+constexpr int kRingThinDist = 96;                      // than this
+constexpr int64_t kRingMaxGraphOps = (int64_t)1 << 18; // graphs of a larger batch
 constexpr int kSmallLevel = 16384;           // levels expanding fewer entries than this decay the threshold faster
 constexpr int kDefaultDeferPercent = 74;
 constexpr int kDefaultStartShift = 1;       // deferral threshold starts at P >> 1 ...
@@ -693,27 +695,39 @@ int dgn_prune_workspace(const dgn_graph *g, int32_t num_sets, size_t *scratch_by
 
 // Waves per graph when the ring sweep takes this call, 0 when it does not.
 //   Which graphs: the sweep walks every operator, 1 024 of them in 2 us (nothing kept) to 13 us (one long chain); the level
-// by level traversal costs about 4.6 us per dependent level of a thin graph and 60 to 100 us before it has done anything.
-// Up to 16 384 operators the sweep was the faster one for every family tried (layered CNN, unrolled RNN, sliding window;
-// 1 and 64 sets): 34 against 106 us at 800 operators, 107 against 119 at 16 000 in the worst case (an unrolled RNN whose
-// chains die out), which at 32 000 is 170 against 121.  Beyond that size only graphs that read nothing older than 96 tensors:
-// they have a level per 96 tensors at least.
+// by level traversal costs about 4.6 us per dependent level of a thin graph and 60 to 100 us before it has done anything,
+// but it ends where the chains do.  Up to 16 384 operators the sweep was never slower for any family tried (layered CNN,
+// unrolled RNN, sliding window, power law; 1 to 64 sets): 34 against 106 us at 800 operators, at worst 71 against 69 (RNN 30 wide,
+// 15 000 operators).  That holds with sixteen waves on the graph; where they need more LDS than there is, because
+// its operators read far back, four or one lose (35 layers of 324: 208 against 168 us, power law of 6 000: 235, 137).
+//   Beyond that size it depends on what is kept, which nobody knows before.  A recorded chain of short hops (window of 64)
+// of 20 000 operators: 282 against 3 300 us; an RNN as narrow, whose chains die out: 134 against 123, at 24 000 146 against 129, at
+// 64 000 287 against 125, at 120 000 450 against 128.  So the line for graphs that read nothing older than 96 tensors lies where such an RNN
+// loses a tenth (with a single target 87 against 74).  Several words of sets are swept in the time of one, where the traversal
+// takes them one after the other.
 //   How many waves: sixteen take a graph that has a compute unit to itself (20 000 operators in a chain of short hops:
 // 0.28 ms, four waves 0.30, one 0.40); four when all graphs are resident at once that way (1 500 graphs of 20 000 operators:
-// 0.95 ms, one wave 1.03, sixteen 2.13); one beyond (4 096 graphs: 1.18 ms, four waves 1.67).
+// 0.95 ms, one wave 1.03, sixteen 2.13); one beyond (4 096 graphs: 1.18 ms, four waves 1.67).  Batches of 64 graphs and more
+// were always swept, with hash tables and one wave per graph before, and take what fits.
 // words: words of 64 sets (single graphs), a workgroup each.
 static int ring_waves(const dgn_graph *g, const dgn_options *o, int64_t words = 1)
 {
     if (!g->ring || (o && (o->traversal != 0 || o->incremental || o->recompute_keep))) return 0;
     const bool many = g->G >= kSweepMinGraphs;               // (such batches were always swept graph by graph)
-    const int64_t most = many ? kRingMaxGraphOps : g->ring_dist <= kRingThinDist ? kRingMaxOps : kRingShortOps;
+    const bool thin = g->ring_dist <= kRingThinDist;
+    const int64_t most = many   ? kRingMaxGraphOps
+                         : thin ? (words > kRingMaxOps / kRingThinOps ? kRingMaxOps : kRingThinOps * words)
+                                : kRingShortOps;
     if (g->max_graph_ops > most) return 0;
     auto fits = [&](int w) {
         return ((size_t)ring_words(w, g->ring_dist, g->ring_span64) + (size_t)g->ring_low + kRingExtraWords) * sizeof(u64) +
                    kRingSeedWords * sizeof(uint32_t) <= kRingMaxLds;
     };
     const int64_t groups = g->G > 1 ? g->G : words;
-    if (groups <= g->num_cus && g->max_graph_ops > 4 * kWave && fits(16)) return 16;
+    if (groups <= g->num_cus && g->max_graph_ops > 4 * kWave) {
+        if (fits(16)) return 16;
+        if (!many && words == 1) return 0;
+    }
     if (groups <= 8 * g->num_cus && fits(4)) return 4;
     return fits(1) ? 1 : 0;
 }
@@ -1322,9 +1336,10 @@ int dgn_prune_words(const dgn_graph *g, int64_t num_sets, int64_t num_targets, c
         const int rc = check_prune(g, DGN_MAX_SETS, num_targets, tgt_rowptr, tgt_idx, tensor_mask, op_mask, kept_ops, kept_masks,
                                    kept_count, per_query_count, scratch, scratch_bytes, options, &S);
         if (rc) return rc;
-        if (ring_waves(g, options)) {
+        if (ring_waves(g, options, words)) {
             at_once = words_scratch(S, scratch, g->P, words);
             if (at_once > 1) ring = ring_waves(g, options, at_once);
+            if (!ring) at_once = 1;
         }
     }
     for (int64_t w = 0; w < words; w += at_once) {

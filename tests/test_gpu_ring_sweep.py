@@ -178,3 +178,26 @@ def test_graphs_that_the_ring_cannot_hold_take_another_path(dgn, oracle):
         assert buf.prune(torch.from_numpy(t.tgt_rowptr).cuda(), torch.from_numpy(t.tgt_idx).cuda(), stats=st) == 0
         assert st.launches > 3
         assert_same(buf.to_host(), oracle_prune(oracle, h, t)[1], "another path")
+
+
+# Which single graphs are swept (the measurements stand beside the rule in api.hip): sixteen waves have room for what the
+# operators read (dozens of wide layers and a power law of 6 000 read further back), or several words share the
+# sweep; beyond 16 384 operators only where everything is read at once, and few where chains may die out.
+@pytest.mark.parametrize("family,size,words,swept", [
+    ("cnn", (80, 150), 1, True), ("cnn", (35, 324), 1, False), ("cnn", (35, 324), 2, True), ("powerlaw", (3000,), 1, True),
+    ("powerlaw", (6000,), 1, False), ("powerlaw", (6000,), 2, True), ("cnn", (200, 90), 1, False), ("layered", (20000,), 1, True),
+    ("rnn", (200, 80), 1, True), ("rnn", (300, 80), 1, False), ("rnn", (300, 80), 2, True), ("rnn", (700, 80), 2, False),
+    ("rnn", (1500, 80), 1, False)])
+def test_which_single_graphs_are_swept(dgn, oracle, family, size, words, swept):
+    import torch
+    g = gg.cnn(*size, 5)[0] if family == "cnn" else getattr(gg, family)(*size, 5)
+    tg = gg.targets_range(3, 64 * words, 1, 3, 16, g.num_tensors)
+    if words > 1:
+        launches = prune_words(dgn, oracle, g, tg, 64 * words)
+    else:
+        buf = dgn.PruneBuffers(dgn.DeviceGraph.from_coo(g), 64)
+        st = dgn.dgn_stats()
+        assert buf.prune(torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda(), stats=st) == 0
+        assert_same(buf.to_host(), oracle_prune(oracle, g, tg)[1], "single word")
+        launches = st.launches
+    assert (launches <= 2) == swept, launches
