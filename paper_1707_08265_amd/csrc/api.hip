@@ -32,6 +32,8 @@ constexpr int kLevelBlocksPerCU = 5;   // workgroups of a wide level per compute
 // ones.  Those are deep (an unrolled RNN: a level per 30 operators of a step), and a level of several hundred entries takes
 // one workgroup 7 us where the 32 hops of a wide launch take 3 us each: 900 000 operators, 33 targets 262 -> 193 us, two million
 // 220 -> 158.  A power-law graph is through after a few levels (300 000 operators, one target: 137 us, the other way 190).
+// A prune that starts with the one workgroup lets it have frontiers up to kNarrowCap in any graph: often it is through then,
+// and where nothing is known the other way is 48 wide launches ahead (300 000 operators, 64 sets, first prune 145 us, 252).
 constexpr int kNarrowCap = 1024, kNarrowCapNear = 320;
 constexpr int kWidePerGroup = 12;           // wide level launches between two single-workgroup launches
 constexpr int kWideGroupsFirst = 4;         // groups in the first batch (one state read-back per batch) ...
@@ -1028,15 +1030,15 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     // The record of a single-workgroup launch is a complete state (it leaves no tallies to fold in), so every
     // batch ends with one, and that record is what is read back.
     bool last_was_narrow = false;
-    auto narrow = [&]() -> int {
-        DGN_HIP(launch_narrow(g->v, S.state, S.ctr, launch_no, S.q0, S.q1, S.qg, S.DB, flags, M, K, narrow_cap, sch, log, trace, s));
+    auto narrow = [&](int cap) -> int {
+        DGN_HIP(launch_narrow(g->v, S.state, S.ctr, launch_no, S.q0, S.q1, S.qg, S.DB, flags, M, K, cap, sch, log, trace, s));
         ++launch_no; ++launches;
         last_was_narrow = true;
         return DGN_OK;
     };
     auto read_state = [&]() -> int {
         if (!last_was_narrow) {
-            const int e = narrow();
+            const int e = narrow(narrow_cap);
             if (e) return e;
         }
         DGN_HIP(hipMemcpyAsync(pin, S.state, 2 * sizeof(TravState), hipMemcpyDeviceToHost, s));
@@ -1047,8 +1049,9 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     };
     // A graph that needed wide levels last time starts with them at once: the wide kernel's second hop takes
     // the first two levels in one launch, where the single-workgroup kernel would stop after the first.
-    if (!generic_only && !g->wide_hint[hk].load(std::memory_order_relaxed)) {
-        rc = narrow();
+    const bool starts_wide = generic_only || g->wide_hint[hk].load(std::memory_order_relaxed) != 0;
+    if (!starts_wide) {
+        rc = narrow(kNarrowCap);
         if (rc) return rc;
         rc = read_state();
         if (rc) return rc;
@@ -1061,7 +1064,7 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
             ++launch_no; ++launches; ++level_launches;
         }
         last_was_narrow = false;
-        return narrow();
+        return narrow(narrow_cap);
     };
     bool first = true;
     int batch = 0;
@@ -1086,7 +1089,8 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
         } else {
             // unknown graph, or the layout fell short: groups of wide levels with the single-workgroup kernel
             // after each; a batch right after a hinted one is small (the hint was nearly right)
-            const int groups = first ? kWideGroupsFirst : (hint_runs > 0 && batch == 1) ? 1 : kWideGroups;
+            const bool learns = first && starts_wide && !generic_only;     // (one workgroup did all of the call before)
+            const int groups = learns ? 1 : first ? kWideGroupsFirst : (hint_runs > 0 && batch == 1) ? 1 : kWideGroups;
             for (int i = 0; i < groups; ++i) {
                 rc = group(kWidePerGroup);
                 if (rc) return rc;
@@ -1104,7 +1108,10 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
         if (!done) compacted = false;      // the speculative pass ran on unfinished masks
         first = false;
     }
-    g->wide_hint[hk].store(hst->max_frontier > (u64)small_frontier ? 1 : 0, std::memory_order_relaxed);
+    // (a graph that reads nearby and was started wide stays so until its frontiers are far smaller: a wide launch goes many hops,
+    // so its frontiers say little about those of the other start, and the way would change with every call)
+    const u64 wide_above = (u64)(starts_wide && small_frontier == kNarrowCapNear ? kNarrowCapNear / 4 : small_frontier);
+    g->wide_hint[hk].store(hst->max_frontier > wide_above ? 1 : 0, std::memory_order_relaxed);
     {
         const int nr = hst->n_runs < kMaxRuns ? hst->n_runs : kMaxRuns;
         bool exact = batch == 1 && used_runs > 0 && hst->n_runs == used_runs;

@@ -53,3 +53,26 @@ def test_floor_of_the_thresholds(dgn, family, size, per_set, sets, soon):
     assert int(theta[theta > 0].min()) < 4 * floor, theta
     theta = thresholds(dgn, g, tg, defer_floor_shift=2)
     assert int(theta[theta > 0].min()) >= g.num_ops >> 2, theta
+
+
+@pytest.mark.parametrize("size,per_set,sets", [((2000, 139), 4, 64), ((700, 150), 4, 64), ((60, 300), 6, 17), ((400, 200), 8, 64)])
+def test_repeated_prunes_settle_on_one_way(dgn, oracle, size, per_set, sets):
+    """Frontiers of a few hundred in a deep graph: the first prune may be done by the one workgroup, later ones start with wide
+    launches, and from then on nothing changes any more (no call takes the other way, or a second batch)."""
+    import torch
+    g = gg.rnn(*size, 5)
+    tg = gg.targets_range(3, sets, 1, per_set, 16, g.num_tensors)
+    buf = dgn.PruneBuffers(dgn.DeviceGraph.from_coo(g), sets)
+    ptr, idx = torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda()
+    seen = []
+    for _ in range(12):
+        st = dgn.dgn_stats()
+        assert buf.prune(ptr, idx, stats=st) == 0
+        seen.append((int(st.launches), int(st.level_launches), int(st.max_frontier)))
+    if seen[0][2] <= 1024:
+        assert seen[0][1] == 0, seen                        # one workgroup, no wide launch ahead of knowing
+    # (the spare launches behind the layout go once it has fitted a few times)
+    assert max(n for n, _, _ in seen[1:]) <= 20 and len({n for n, _, _ in seen[7:]}) == 1, seen
+    adj = oracle.build_adjacency(g.num_ops, g.num_tensors, g.in_op, g.in_tensor, g.out_op, g.out_tensor)
+    ref = oracle.forward_prune(adj, sets, tg.tgt_rowptr, tg.tgt_idx)
+    assert np.array_equal(buf.to_host()["kept_masks"][:int(ref.kept_count[0])], ref.kept_masks[:int(ref.kept_count[0])])
