@@ -35,6 +35,8 @@ constexpr int kLevelBlocksPerCU = 5;   // workgroups of a wide level per compute
 // A prune that starts with the one workgroup lets it have frontiers up to kNarrowCap in any graph: often it is through then,
 // and where nothing is known the other way is 48 wide launches ahead (300 000 operators, 64 sets, first prune 145 us, 252).
 constexpr int kNarrowCap = 1024, kNarrowCapNear = 320;
+constexpr int kNarrowLevels = 12;           // done by the one workgroup in so few levels, a prune is left to it (100 000 operators
+                                            // in 12 levels 127 us, wide 138; 36 000 in 13 144, wide 111)
 constexpr int kWidePerGroup = 12;           // wide level launches between two single-workgroup launches
 constexpr int kWideGroupsFirst = 4;         // groups in the first batch (one state read-back per batch) ...
 constexpr int kWideGroups = 6;              // ... and in the following ones
@@ -1111,7 +1113,8 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     // (a graph that reads nearby and was started wide stays so until its frontiers are far smaller: a wide launch goes many hops,
     // so its frontiers say little about those of the other start, and the way would change with every call)
     const u64 wide_above = (u64)(starts_wide && small_frontier == kNarrowCapNear ? kNarrowCapNear / 4 : small_frontier);
-    g->wide_hint[hk].store(hst->max_frontier > wide_above ? 1 : 0, std::memory_order_relaxed);
+    const bool few_levels = level_launches == 0 && hst->slot[(launch_no - 1) & 1].level <= kNarrowLevels;
+    g->wide_hint[hk].store(hst->max_frontier > wide_above && !few_levels ? 1 : 0, std::memory_order_relaxed);
     {
         const int nr = hst->n_runs < kMaxRuns ? hst->n_runs : kMaxRuns;
         bool exact = batch == 1 && used_runs > 0 && hst->n_runs == used_runs;

@@ -55,7 +55,7 @@ def test_floor_of_the_thresholds(dgn, family, size, per_set, sets, soon):
     assert int(theta[theta > 0].min()) >= g.num_ops >> 2, theta
 
 
-@pytest.mark.parametrize("size,per_set,sets", [((2000, 139), 4, 64), ((700, 150), 4, 64), ((60, 300), 6, 17), ((400, 200), 8, 64)])
+@pytest.mark.parametrize("size,per_set,sets", [((2000, 139), 4, 64), ((700, 150), 4, 64), ((60, 300), 6, 17), ((400, 200), 8, 64), ((1000, 100), 8, 64)])
 def test_repeated_prunes_settle_on_one_way(dgn, oracle, size, per_set, sets):
     """Frontiers of a few hundred in a deep graph: the first prune may be done by the one workgroup, later ones start with wide
     launches, and from then on nothing changes any more (no call takes the other way, or a second batch)."""
