@@ -145,21 +145,23 @@ enum {
 
 /* Schedule-dependent counters (not part of the result; excluded from parity). HOST struct. */
 typedef struct dgn_stats {
-    int64_t levels;          /* frontier levels processed (ring sweep of fewer than 64 graphs: settling steps; of more: 0) */
+    int64_t levels;          /* frontier levels processed.  Graphs that one workgroup each sweeps have none (small ones, and
+                                packed batches of small ones): settling steps for fewer than 64 graphs, else 0   */
     int64_t tensor_visits;   /* frontier entries and deferred operators expanded, summed over levels */
-    int64_t max_frontier;    /* largest frontier                                                 */
+    int64_t max_frontier;    /* largest frontier; 0 for graphs that are swept                         */
     int64_t launches;        /* kernels enqueued by the call                                     */
     int64_t level_launches;  /* of which frontier-level kernels                                  */
     int32_t *level_trace;    /* IN, optional HOST buffer: per level 4 ints (frontier size, entries and
                                 operators expanded, deferral threshold or -1, low 32 bits of the device
                                 wall clock in 10 ns ticks when the level was finished), for the first
-                                level_trace_cap levels (at most 4096)                                    */
+                                level_trace_cap levels (at most 4096).  With it, fewer than 64 graphs are
+                                traversed level by level also where they would be swept                 */
     int64_t level_trace_cap; /* IN: capacity of level_trace in levels                                     */
     int64_t reserved;        /* dgn_backward_prune: passes of its forward stage; 0 otherwise                */
     int64_t recycled;        /* 1 when options->recycle found the previous result in place and the call
                                 zeroed only what that result had set                               */
     int64_t atomic_updates;  /* 64-bit atomic ORs the traversal issued (one per input edge of an operator that
-                                gained bits, plus the seeds); 0 for a packed batch swept per graph      */
+                                gained bits, plus the seeds); 0 for graphs that are swept                */
     float phase_ms[DGN_NUM_PHASES];   /* filled when options->profile is 1 (all) or 2 (traversal); zero otherwise */
 } dgn_stats;
 

@@ -714,10 +714,11 @@ int dgn_prune_workspace(const dgn_graph *g, int32_t num_sets, size_t *scratch_by
 // 0.95 ms, one wave 1.03, sixteen 2.13); one beyond (4 096 graphs: 1.18 ms, four waves 1.67).  Batches of 64 graphs and more
 // were always swept, with hash tables and one wave per graph before, and take what fits.
 // words: words of 64 sets (single graphs), a workgroup each.
-static int ring_waves(const dgn_graph *g, const dgn_options *o, int64_t words = 1)
+static int ring_waves(const dgn_graph *g, const dgn_options *o, const dgn_stats *stats, int64_t words = 1)
 {
     if (!g->ring || (o && (o->traversal != 0 || o->incremental || o->recompute_keep))) return 0;
     const bool many = g->G >= kSweepMinGraphs;               // (such batches were always swept graph by graph)
+    if (!many && stats && stats->level_trace && stats->level_trace_cap > 0) return 0;     // asks for levels: there are none here
     const bool thin = g->ring_dist <= kRingThinDist;
     const int64_t most = many   ? kRingMaxGraphOps
                          : thin ? (words > kRingMaxOps / kRingThinOps ? kRingMaxOps : kRingThinOps * words)
@@ -853,7 +854,7 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     hipStream_t s = static_cast<hipStream_t>(stream);
     u64 *M = reinterpret_cast<u64 *>(tensor_mask);
     u64 *K = reinterpret_cast<u64 *>(op_mask);
-    const int ring = ring_waves(g, options);
+    const int ring = ring_waves(g, options, stats);
     if (ring)
         return ring_prune(g, ring, 1, num_sets, num_targets, tgt_rowptr, tgt_idx, M, K, op_flag, kept_ops,
                           reinterpret_cast<u64 *>(kept_masks), kept_count, per_query_count, S, options, stats, s,
@@ -1346,9 +1347,9 @@ int dgn_prune_words(const dgn_graph *g, int64_t num_sets, int64_t num_targets, c
         const int rc = check_prune(g, DGN_MAX_SETS, num_targets, tgt_rowptr, tgt_idx, tensor_mask, op_mask, kept_ops, kept_masks,
                                    kept_count, per_query_count, scratch, scratch_bytes, options, &S);
         if (rc) return rc;
-        if (ring_waves(g, options, words)) {
+        if (ring_waves(g, options, stats, words)) {
             at_once = words_scratch(S, scratch, g->P, words);
-            if (at_once > 1) ring = ring_waves(g, options, at_once);
+            if (at_once > 1) ring = ring_waves(g, options, stats, at_once);
             if (!ring) at_once = 1;
         }
     }

@@ -180,6 +180,30 @@ def test_graphs_that_the_ring_cannot_hold_take_another_path(dgn, oracle):
         assert_same(buf.to_host(), oracle_prune(oracle, h, t)[1], "another path")
 
 
+@pytest.mark.parametrize("G", [1, 8])
+def test_a_caller_that_asks_for_the_level_trace_gets_it(dgn, oracle, G):
+    """The sweep has no levels: with a trace buffer the same graphs are traversed level by level."""
+    import torch
+    rng = np.random.default_rng(G)
+    g = recorded(rng, G, 2000, 64, 2, 3, 16)
+    tg = draw_targets(rng, g, 7, 3)
+    buf = dgn.PruneBuffers(dgn.DeviceGraph.from_coo(g), 7)
+    ptr, idx = torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda()
+    trace = np.full((4096, 4), -77, np.int32)
+    for call in range(4):                                                # in turn with calls that are swept
+        st = dgn.dgn_stats()
+        if call % 2:
+            st.level_trace, st.level_trace_cap = trace.ctypes.data, trace.shape[0]
+        assert buf.prune(ptr, idx, stats=st) == 0
+        assert (st.launches > 3) == bool(call % 2)
+        assert_same(buf.to_host(), oracle_prune(oracle, g, tg)[1], f"call {call}")
+        if call % 2:
+            rows = trace[:int(st.levels)]
+            assert 0 < len(rows) < 4096 and (rows[:, 0] >= 0).all() and (rows[:, 1] >= 0).all() and (trace[len(rows):] == -77).all()
+            assert rows[:, 0].max() == st.max_frontier > 0 and st.atomic_updates > 0
+            trace.fill(-77)
+
+
 # Which single graphs are swept (the measurements stand beside the rule in api.hip): sixteen waves have room for what the
 # operators read (dozens of wide layers and a power law of 6 000 read further back), or several words share the
 # sweep; beyond 16 384 operators only where everything is read at once, and few where chains may die out.
