@@ -141,6 +141,8 @@ enum {
     DGN_PHASE_SCATTER = 5,   /* ordered scatter of the kept operators (+ per-graph offsets)       */
     DGN_PHASE_TOTAL = 6,     /* first kernel start to last kernel end                             */
     DGN_NUM_PHASES = 8
+    /* Graphs that one workgroup each sweeps: seeds, removal rule and counts are part of the sweep, which is
+     * DGN_PHASE_TRAVERSE (and makes the ordered list of a small single graph); DGN_PHASE_SCAN adds up a batch's graphs */
 };
 
 /* Schedule-dependent counters (not part of the result; excluded from parity). HOST struct. */

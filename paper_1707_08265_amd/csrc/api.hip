@@ -54,7 +54,7 @@ constexpr int64_t kRingMaxOps = (int64_t)1 << 17;      // single graphs: at most
 constexpr int64_t kRingShortOps = 16384;               // (or fewer graphs than the per-graph sweep starts at) up to this size, or
 constexpr int64_t kRingThinOps = 20480;                // to this, times the words of sets, when no input lies further back
 constexpr int kRingThinDist = 96;                      // than this
-constexpr int64_t kRingMaxGraphOps = (int64_t)1 << 18; // graphs of a larger batch
+// (graphs of a larger batch: kRingMaxGraphOps)
 constexpr int kSmallLevel = 16384;           // levels expanding fewer entries than this decay the threshold faster
 constexpr int kDefaultDeferPercent = 74;
 constexpr int kDefaultStartShift = 1;       // deferral threshold starts at P >> 1 ...
@@ -748,15 +748,19 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
     void *pin = nullptr;
     int rc = pinned_buffer(&pin);
     if (rc) return rc;
+    // 0 start, 1 cleared, 2 swept, 3 counted (batches), 4 listed; profile = 2: those around the sweep alone
     hipEvent_t *ev = nullptr;
+    const bool all = options && options->profile == 1;
+    int launches = 0;
     if (options && options->profile && stats) {
         rc = profile_events(&ev);
         if (rc) return rc;
-        DGN_HIP(hipEventRecord(ev[0], s));
+        if (all) DGN_HIP(hipEventRecord(ev[0], s));
     }
     if (also_M || also_K) {
         FillRegion more[2] = {{also_M, (size_t)g->T * 8}, {also_K, (size_t)g->P * 8}};
         DGN_HIP(launch_clear(more, 2, s));
+        ++launches;
     }
     uint8_t *flags = ring_flags(S, op_flag, g->P);
     RingArgs a{};
@@ -790,9 +794,9 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
     int32_t *status = static_cast<int32_t *>(pin);
     status[0] = status[1] = status[2] = 0;
     if (ev) DGN_HIP(hipEventRecord(ev[1], s));
-    int launches = 0;
-    DGN_HIP(launch_ring_sweep(a, waves, g->ring_dist, g->ring_span64, g->max_graph_ops, &launches, s));
-    if (ev) DGN_HIP(hipEventRecord(ev[2], s));
+    int sweep_launches = 0;
+    DGN_HIP(launch_ring_sweep(a, waves, g->ring_dist, g->ring_span64, g->max_graph_ops, &sweep_launches, s, ev ? ev + 2 : nullptr, all));
+    launches += sweep_launches;
     DGN_HIP(hipStreamSynchronize(s));
     if (stats) {
         int32_t *user_trace = stats->level_trace;
@@ -806,9 +810,11 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
         stats->recycled = status[2];
         if (ev) {
             DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_TRAVERSE], ev[1], ev[2]));
-            if (options->profile == 1) {
+            if (all) {
                 DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_CLEAR], ev[0], ev[1]));
-                DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_TOTAL], ev[0], ev[2]));
+                DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_SCAN], ev[2], ev[3]));
+                DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_SCATTER], ev[3], ev[4]));
+                DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_TOTAL], ev[0], ev[4]));
             }
         }
     }

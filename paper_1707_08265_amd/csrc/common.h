@@ -358,6 +358,7 @@ struct RingArgs {
     int32_t ring_words, low_words, seed_words;     // LDS: ring, graph inputs (8 bytes each), targets (4 bytes each)
 };
 constexpr int kRingExtraWords = 1 + kWave;
+constexpr int64_t kRingMaxGraphOps = (int64_t)1 << 18;   // the largest graph that is ever swept
 // words of 64 operators of G graphs, one of them perhaps ragged in each
 __host__ __device__ inline int64_t ring_bit_words(int64_t P, int64_t G) { return (P >> 6) + G + 1; }
 inline int64_t ring_words(int waves, int dist, int span64)
@@ -367,7 +368,9 @@ inline int64_t ring_words(int waves, int dist, int span64)
     while (r < need) r *= 2;
     return r;
 }
-hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, int *launches, hipStream_t s);
+// ev (or NULL): ev[0] is recorded behind the sweep; with `all`, ev[1] behind the per-graph counts and ev[2] behind the list
+hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, int *launches, hipStream_t s,
+                             hipEvent_t *ev, bool all);
 // One sweep over all operators re-deriving K and pushing new bits to the inputs; *changed |= 1 if any.
 hipError_t launch_fix_sweep(const GraphView &g, u64 *M, u64 *K, uint8_t *flags, int32_t *changed, int grid_blocks, hipStream_t s);
 

@@ -39,6 +39,7 @@ namespace dgn {
 // bits was set, in bit-sliced form (plane i holds bit i of all 64 counters).  Four masks are folded at a time with
 // full adders; only the resulting carry of weight 4 ripples through the higher planes.
 constexpr int kRingPlanes = 13;                     // counters up to 2^13 - 1 words of 64 operators per wave
+static_assert(kRingMaxGraphOps / kWave < (1 << kRingPlanes), "a single wave counts all words of the largest graph");
 
 struct RingCount {
     u64 plane[kRingPlanes];
@@ -574,7 +575,8 @@ template <int W> static hipError_t launch_ring_w(const RingArgs &a, size_t lds, 
 
 constexpr int64_t kRingListOps = 16384;
 
-hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, int *launches, hipStream_t s)
+hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, int *launches, hipStream_t s,
+                             hipEvent_t *ev, bool all)
 {
     a.ring_words = (int32_t)ring_words(waves, dist, span64);
     const int G = a.g.num_graphs;
@@ -585,8 +587,21 @@ hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_
     if (a.list_here) lds += (size_t)words * sizeof(int);
     hipError_t e = waves == 1 ? launch_ring_w<1>(a, lds, s) : waves == 4 ? launch_ring_w<4>(a, lds, s) : launch_ring_w<16>(a, lds, s);
     *launches = a.list_here ? 1 : G > 1 ? 3 : 2;
-    if (e != hipSuccess || a.list_here) return e;
-    if (G > 1) hipLaunchKernelGGL(k_ring_offsets, dim3(1), dim3(1024), 0, s, a);
+    auto mark = [&](int i) {
+        if (e == hipSuccess && ev && (i == 0 || all)) e = hipEventRecord(ev[i], s);
+    };
+    mark(0);
+    if (e != hipSuccess) return e;
+    if (G > 1) {
+        hipLaunchKernelGGL(k_ring_offsets, dim3(1), dim3(1024), 0, s, a);
+        e = hipGetLastError();
+    }
+    mark(1);
+    if (e != hipSuccess) return e;
+    if (a.list_here) {
+        mark(2);
+        return e;
+    }
     // a wave per 16 words of the largest graph, four in flight; per 4 words, one round trip each, while that fits the chip
     const int64_t rows = G > 1 ? G : a.words;
     const int64_t per = rows * ((words + 15) / 16) <= 2048 ? 16 : 64;
@@ -594,7 +609,9 @@ hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_
     if (split > 256) split = 256;
     const dim3 grid((unsigned)rows, (unsigned)split);
     hipLaunchKernelGGL(k_ring_scatter, grid, dim3(kRingScatterThreads), 0, s, a);
-    return hipGetLastError();
+    e = hipGetLastError();
+    mark(2);
+    return e;
 }
 
 }  // namespace dgn

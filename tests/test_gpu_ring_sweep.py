@@ -204,6 +204,27 @@ def test_a_caller_that_asks_for_the_level_trace_gets_it(dgn, oracle, G):
             trace.fill(-77)
 
 
+@pytest.mark.parametrize("G,ops", [(1, 2000), (1, 20000), (8, 2000), (100, 500)])
+def test_phase_times_of_a_sweep(dgn, G, ops):
+    """profile = 1: the kernels behind the sweep are phases of their own, and all phases add up; profile = 2: the sweep alone."""
+    import torch
+    rng = np.random.default_rng(G + ops)
+    g = recorded(rng, G, ops, 64, 2, 3, 16)
+    tg = draw_targets(rng, g, 7, 3)
+    buf = dgn.PruneBuffers(dgn.DeviceGraph.from_coo(g), 7)
+    ptr, idx = torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda()
+    for profile in (1, 2):
+        st = dgn.dgn_stats()
+        assert buf.prune(ptr, idx, options=dgn.dgn_options(profile=profile), stats=st) == 0
+        ms = list(st.phase_ms)
+        assert st.launches <= 3 and ms[2] > 0                            # DGN_PHASE_TRAVERSE
+        if profile == 2:
+            assert [m for i, m in enumerate(ms) if i != 2 and m != 0] == []
+        else:
+            assert ms[1] == ms[3] == 0 and (ms[5] > 0 or st.launches == 1) and (ms[4] > 0 or G == 1)
+            assert abs(sum(ms[:6]) - ms[6]) < 0.01 + 0.02 * ms[6]
+
+
 # Which single graphs are swept (the measurements stand beside the rule in api.hip): sixteen waves have room for what the
 # operators read (dozens of wide layers and a power law of 6 000 read further back), or several words share the
 # sweep; beyond 16 384 operators only where everything is read at once, and few where chains may die out.
