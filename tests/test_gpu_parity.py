@@ -236,11 +236,12 @@ def test_deep_chain_many_levels(dgn, oracle):
     ops = np.arange(n, dtype=np.int32)
     g = gg.Graph(n, n + 1, ops, ops, ops, ops + 1)
     tg = targets_from_sets([[n], [n // 2]])
-    st = dgn.dgn_stats()
-    _, _, out = gpu_prune(dgn, g, tg, stats=st)
     _, r = oracle_prune(oracle, g, tg)
-    assert_same(out, r, "chain")
-    assert st.levels >= n
+    for knobs in ({}, {"traversal": 2}):                    # swept (a settling step per operator), and level by level
+        st = dgn.dgn_stats()
+        _, _, out = gpu_prune(dgn, g, tg, stats=st, **knobs)
+        assert_same(out, r, f"chain {knobs}")
+        assert st.levels >= n and (st.max_frontier > 0) == bool(knobs)
 
 
 def test_relabelled_tensors(dgn, oracle):
@@ -283,10 +284,13 @@ def test_schedule_knobs_do_not_change_results(dgn, oracle, k, scale):
     for knobs in (dict(defer_percent=100), dict(defer_percent=50), dict(defer_percent=95),
                   dict(traversal=1), dict(traversal=1, defer_percent=60), dict(traversal=2), dict(traversal=2, defer_percent=70),
                   dict(traversal=2, defer_percent=90, defer_start_shift=3, defer_floor_shift=14),
-                  dict(max_queue_entries=1000), dict(max_queue_entries=37, traversal=1)):
+                  dict(max_queue_entries=1000), dict(max_queue_entries=37, traversal=1),
+                  # (the few small graphs of configuration 4 are swept unless a traversal is asked for)
+                  dict(traversal=2, defer_percent=100), dict(traversal=2, defer_percent=95), dict(traversal=2, max_queue_entries=1000)):
         st = dgn.dgn_stats()
         _, _, out = gpu_prune(dgn, g, tg, stats=st, **knobs)
         assert_same(out, r, f"cfg{k} {knobs}")
+        assert st.launches > 3 or (k == 4 and "traversal" not in knobs)
 
 
 # ---- the workloads at their full sizes, in the launch configuration bench.py times ---------------
@@ -363,15 +367,31 @@ def _pack(graphs_and_sets, Q):
     return g, targets_from_sets(sets, Q)
 
 
+def _check_hash_sweep(dgn, oracle, g, tg, what):
+    """The same batch with a tensor more at the end of every graph, which no operator touches: its outputs are no longer one
+    run up to the last tensor, so the sweep with hash tables takes it instead of the one with a ring."""
+    off = g.graph_tensor_offsets
+    move = lambda t: (t + np.searchsorted(off, t, side="right") - 1).astype(np.int32)  # noqa: E731
+    g2 = gg.Graph(g.num_ops, g.num_tensors + g.num_graphs, g.in_op, move(g.in_tensor), g.out_op, move(g.out_tensor), g.num_graphs,
+                  g.graph_op_offsets, off + np.arange(g.num_graphs + 1), "spare")
+    t2 = gg.Targets(tg.num_sets, tg.tgt_rowptr, move(tg.tgt_idx))
+    st = dgn.dgn_stats()
+    _, _, out = gpu_prune(dgn, g2, t2, stats=st)
+    assert_same(out, oracle_prune(oracle, g2, t2)[1], f"{what}, hash tables")
+    assert st.levels == 0 and st.launches > 3
+
+
 def test_packed_batches_use_the_per_graph_sweep(dgn, oracle):
-    """Batches of >= 64 topologically numbered graphs take the one-wave-per-graph sweep; same results."""
+    """Batches of >= 64 topologically numbered graphs are swept graph by graph, those whose tensors are numbered as they are
+    created with a ring, others with hash tables; same results."""
     # equal-sized layered graphs
     g, tg = gg.batch_layered(96, 700, 4242, num_sets=64)
     st = dgn.dgn_stats()
     _, _, out = gpu_prune(dgn, g, tg, stats=st)
     _, r = oracle_prune(oracle, g, tg)
     assert_same(out, r, "batch 96x700")
-    assert st.levels == 0                     # no frontier levels were run
+    assert st.levels == 0 and st.launches <= 3                # no frontier levels were run
+    _check_hash_sweep(dgn, oracle, g, tg, "batch 96x700")
     _, _, out = gpu_prune(dgn, g, tg, recompute_keep=True)
     assert_same(out, r, "batch 96x700 recompute_keep")
     _, _, out = gpu_prune(dgn, g, tg, traversal=1)          # and the generic traversal agrees
@@ -390,7 +410,8 @@ def test_packed_batches_use_the_per_graph_sweep(dgn, oracle):
     _, _, out = gpu_prune(dgn, g, tg, validate=True, stats=st)
     _, r = oracle_prune(oracle, g, tg)
     assert_same(out, r, "ragged batch")
-    assert st.levels == 0
+    assert st.levels == 0 and st.launches <= 3
+    _check_hash_sweep(dgn, oracle, g, tg, "ragged batch")
     # graphs whose operator order is NOT topological fall back to the frontier traversal
     parts = []
     for i in range(70):
@@ -443,7 +464,7 @@ def test_swept_batches_with_tensors_written_by_several_operators(dgn, oracle):
     _, _, out = gpu_prune(dgn, g, tg, validate=True, stats=st)       # the order is topological: validation passes
     _, r = oracle_prune(oracle, g, tg)
     assert_same(out, r, "swept batch with re-written tensors")
-    assert st.levels == 0                                            # and the sweep was taken
+    assert st.levels == 0 and st.launches > 3                        # and the sweep was taken
     _, _, out = gpu_prune(dgn, g, tg, traversal=1)
     assert_same(out, r, "the same through the frontier traversal")
 
@@ -466,7 +487,7 @@ def _hub_graph(rng, num_ops, num_inputs, wide):
 
 @pytest.mark.parametrize("wide", [False, True])
 def test_swept_batches_with_hub_tensors_and_wide_operators(dgn, oracle, wide):
-    """The sweep's side paths: a producer with more in-group readers than it registers (masks resolved lane by
+    """The side paths of the sweep with hash tables: a producer with more in-group readers than it registers (masks resolved lane by
     lane instead of by relaxation) and groups with too many input edges for the tables (walked one operator at
     a time, straight to memory), mixed with ordinary groups in the same graphs."""
     rng = np.random.default_rng(91 + wide)
@@ -487,6 +508,7 @@ def test_swept_batches_with_hub_tensors_and_wide_operators(dgn, oracle, wide):
     _, r = oracle_prune(oracle, g, tg)
     assert_same(out, r, f"swept batch with hubs (wide={wide})")
     assert st.levels == 0
+    _check_hash_sweep(dgn, oracle, g, tg, f"swept batch with hubs (wide={wide})")
 
 
 def test_more_than_64_sets_run_word_by_word(dgn, oracle):

@@ -117,9 +117,11 @@ def test_flag_bytes_in_scratch_are_cleared_even_when_the_count_pass_does_not_rea
     assert recycled == [0, 0, 1], recycled
 
 
-def test_recycled_prunes_of_a_small_packed_batch(dgn, oracle):
-    """Eight packed graphs go through the frontier traversal (the per-graph sweep starts at 64 graphs): the log,
-    the per-graph kept offsets and the per-graph set counts must all survive recycling."""
+@pytest.mark.parametrize("traversal", [0, 2])
+def test_recycled_prunes_of_a_small_packed_batch(dgn, oracle, traversal):
+    """Eight packed graphs, swept by a workgroup each (which recycles from a bit per operator) or, asked for, through the
+    frontier traversal (which keeps a log): that, the per-graph kept offsets and the per-graph set counts must all survive
+    recycling."""
     g, tg = gg.config(4, 0.002)
     assert 1 < g.num_graphs < 64
     dg = dgn.DeviceGraph.from_coo(g)
@@ -137,7 +139,8 @@ def test_recycled_prunes_of_a_small_packed_batch(dgn, oracle):
         draws.append(gg.Targets(Q, rowptr, np.asarray([t for x in sets for t in x], np.int32)))
     seen = []
     for i, t in enumerate(draws):
-        st = _prune(dgn, buf, t)
+        st = _prune(dgn, buf, t, **({"traversal": traversal} if traversal else {}))
+        assert (st.launches <= 3) == (traversal == 0)
         ref = oracle.forward_prune(adj, Q, t.tgt_rowptr, t.tgt_idx, G, g.graph_op_offsets)
         assert_same(buf.to_host(), ref, f"call {i}")
         seen.append(int(st.recycled))
@@ -200,11 +203,13 @@ def test_random_graphs_random_call_sequences(dgn, oracle, multi):
             r = rng.random()
             if r < 0.2:
                 knobs["traversal"] = int(rng.integers(1, 3))
-            elif r < 0.4:
+            elif r < 0.4:                                   # (traversal = 2: graphs as small as these would be swept)
                 knobs["defer_percent"] = int(rng.integers(30, 99))
                 knobs["defer_floor_shift"] = int(rng.integers(1, 12))
+                knobs["traversal"] = 2
             elif r < 0.5:
                 knobs["max_queue_entries"] = int(rng.integers(1, 64))
+                knobs["traversal"] = 2
             elif r < 0.6 and not incremental:
                 knobs["recompute_keep"] = 1
             _prune(dgn, buf, t, **knobs)
