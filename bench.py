@@ -267,19 +267,22 @@ def main():
     # these extra steps also take the per-level trace (device clock at the start of every launch): the time from one
     # wide launch to the next is the level kernel's own duration, without the two single-workgroup launches that
     # the events around the traversal include
+    # (graphs that are swept have no levels: asking for the trace would have them traversed instead)
     traced = bool(args.trace_levels)
-    st.level_trace, st.level_trace_cap = trace.ctypes.data, trace.shape[0]
+    swept = not traced and launches_total <= 3
+    if not swept:
+        st.level_trace, st.level_trace_cap = trace.ctypes.data, trace.shape[0]
     wide_us = []
     for i in range(5):
         rc = buf.prune(rowptr, idx, options=opts, stats=st)
         assert rc == 0, d.dgn_strerror(rc)
         phases_all[i] = list(st.phase_ms)
-        nl = min(int(st.levels), trace.shape[0])
+        nl = 0 if swept else min(int(st.levels), trace.shape[0])
         if nl >= 2:
             wide = trace[:nl, 2] != -1
             dt = ((trace[1:nl, 3].astype(np.int64) - trace[:nl - 1, 3].astype(np.int64)) & 0xFFFFFFFF) / 100.0
             wide_us += dt[wide[1:] & wide[:-1]].tolist()
-    narrow_levels = int((trace[:min(int(st.levels), trace.shape[0]), 2] == -1).sum())
+    narrow_levels = int((trace[:nl, 2] == -1).sum())
     if not traced:
         st.level_trace, st.level_trace_cap = None, 0
     level_us_device_clock = float(np.mean(wide_us)) if wide_us else None
@@ -530,8 +533,9 @@ def main():
     alg = {
         # all of M and K, or (recycled buffers) the log and the kept list read, their M, K and marker words zeroed
         # (a packed batch swept per graph stores K of every operator: only M is cleared)
-        "k_clear": (12 * T_c + 13 * P_k) if recycled else (8 * T) if levels_total == 0 and g.num_graphs >= 64
-                   else (8 * T + 8 * P),
+        # (and one swept with a ring needs nothing cleared)
+        "k_clear": 0 if swept else (12 * T_c + 13 * P_k) if recycled
+                   else (8 * T) if levels_total == 0 and g.num_graphs >= 64 else (8 * T + 8 * P),
         # the traversal's bytes per wide launch (the launches the events and the profiler time)
         "k_level": traversal_bytes / wide,
         # stand-alone: K from M; large single graphs: keep flags (P bytes) read, K of the kept operators, bitmap

@@ -94,7 +94,8 @@ typedef struct dgn_options {
                                 instead of using the K the traversal accumulated (same values)   */
     int32_t traversal;       /* 0 = automatic; 1 = one kernel launch per frontier level, nothing else;
                                 2 = one launch per wide level plus the single-workgroup kernel for
-                                small frontiers (what 0 chooses for a single graph)               */
+                                small frontiers (what 0 chooses for a large single graph; small ones, and
+                                packed batches of small ones, it sweeps with a workgroup or wave each)  */
     int32_t profile;         /* prune: 1 = bracket each phase with HIP events on `stream` and report
                                 the elapsed times in dgn_stats.phase_ms (needs stats != NULL); an
                                 event between two kernels leaves the stream idle for a few
@@ -120,13 +121,14 @@ typedef struct dgn_options {
                                 since it last passed it to this library, and that, if the last such call
                                 was a dgn_prune of this graph with this tensor_mask, op_mask, op_flag,
                                 kept_ops and kept_count, those are still as that call left them.  The call then
-                                zeroes only the words that call set (it finds them through a log the
-                                earlier call kept in `scratch`, and checks on the device that graph and
-                                buffers are the same) instead of all of tensor_mask and op_mask, and keeps
-                                such a log itself.  Where no complete log is found (first call with this
-                                flag, other buffers, a prune that coloured more than a quarter of the
-                                tensors, packed batches swept per graph, after an incremental call)
-                                everything is cleared as without the flag.  Outputs are the same either
+                                zeroes only the words that call set (it finds them through a log, or for
+                                graphs that are swept a bit per operator, that the earlier call kept in
+                                `scratch`, and checks on the device that graph and buffers are the same)
+                                instead of all of tensor_mask and op_mask, and keeps such a log itself.
+                                Where no complete log is found (first call with this flag, other buffers,
+                                a prune that coloured more than a quarter of the tensors, swept batches of
+                                64 graphs and more, after an incremental call) everything is cleared as
+                                without the flag.  Outputs are the same either
                                 way.  Do not set it on the first call with a scratch buffer whose contents
                                 are undefined                                                          */
 } dgn_options;
@@ -249,7 +251,8 @@ int dgn_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets, const i
  *   (the same pointers may be NULL as for dgn_prune).  scratch: as for dgn_prune (reused by every word).
  *   stats: sums over the words (max_frontier: the maximum).
  * Single graphs only (DGN_ERR_INVALID_ARG for a packed batch).  The call synchronises the stream
- * before it returns.  After an error the outputs of every word are undefined. */
+ * before it returns.  When it reports DGN_ERR_ID_OUT_OF_RANGE, the words before the first with such a target are
+ * complete; the outputs of the others are undefined. */
 int dgn_prune_words(const dgn_graph *g, int64_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
                     const int32_t *tgt_idx, uint64_t *tensor_mask, uint64_t *op_mask, uint8_t *op_flag,
                     int32_t *kept_ops, uint64_t *kept_masks, int64_t *kept_count, int64_t *per_query_count,

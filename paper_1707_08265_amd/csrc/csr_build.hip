@@ -1,4 +1,5 @@
-// CSR builder support: row-degree histograms with id range checks, and the validation passes.
+// CSR builder: the pass over the edge lists that checks them and writes the rows, the order of shuffled outputs, row pointers
+// of sorted lists, operator records and producer words, and the validation passes.
 // The adjacency follows the edge definition of Sec. 2.2 of the paper: an operator with the tensors it
 // reads and the tensors it writes; Parent(x) of Algorithm 1 = inputs of every operator that writes x.
 #include "common.h"

@@ -114,8 +114,8 @@ def test_words_of_sets(dgn, oracle, shape):
     assert launches <= 2 * -(-sets // 6400)                              # two for a hundred words at once, at least
 
 
-def prune_words(dgn, oracle, g, tg, sets, flags=True):
-    """One call of dgn_prune_words, every word against the oracle; how many kernels it launched."""
+def prune_words(dgn, oracle, g, tg, sets, flags=True, code=0, good=None):
+    """One call of dgn_prune_words, every word (or the first `good`) against the oracle; how many kernels it launched."""
     import torch
     W, P, T = (sets + 63) // 64, g.num_ops, g.num_tensors
     dg = dgn.DeviceGraph.from_coo(g)
@@ -128,9 +128,9 @@ def prune_words(dgn, oracle, g, tg, sets, flags=True):
     ptr, idx = torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda()
     st = dgn.dgn_stats()
     rc = dgn.dgn_prune_words(dg.handle, sets, idx.numel(), ptr, idx, *out.values(), scratch, nbytes, stats=st)
-    assert rc == 0, dgn.dgn_strerror(rc)
+    assert rc == code, dgn.dgn_strerror(rc)
     host = {k: v.cpu().numpy() for k, v in out.items() if v is not None}
-    for w in range(W):
+    for w in range(W if good is None else good):
         rows = tg.tgt_rowptr[64 * w:64 * w + 65]
         one = targets_from_sets([list(tg.tgt_idx[a:b]) for a, b in zip(rows, rows[1:])], 64)
         ref = oracle_prune(oracle, g, one)[1]
@@ -159,6 +159,17 @@ def test_words_of_sets_with_a_single_word_left_over(dgn, oracle, flags):
         sets = 64 * words - 5
         tg = targets_from_sets([[int(rng.integers(0, g.num_tensors))] for _ in range(sets)], 64)
         assert prune_words(dgn, oracle, g, tg, sets, flags) == launches
+
+
+@pytest.mark.parametrize("recorded_order", [True, False])
+def test_words_before_a_bad_target_are_complete(dgn, oracle, recorded_order):
+    rng = np.random.default_rng(6)
+    g = recorded(rng, 1, 2000, 64, 2, 3, 16)
+    if not recorded_order:                                               # (word by word then)
+        g = gg.Graph(g.num_ops, g.num_tensors + 1, g.in_op, g.in_tensor, g.out_op, g.out_tensor)
+    sets = [[int(t) for t in rng.integers(0, g.num_tensors, 2)] for _ in range(64 * 4)]
+    sets[64 * 2 + 5][1] = g.num_tensors + 3
+    prune_words(dgn, oracle, g, targets_from_sets(sets, 64), len(sets), code=dgn.DGN_ERR_ID_OUT_OF_RANGE, good=2)
 
 
 def test_graphs_that_the_ring_cannot_hold_take_another_path(dgn, oracle):
