@@ -50,10 +50,12 @@ constexpr u64 kRecycleMagic = 0x44474e5f52435943ull;   // "DGN_RCYC"
 constexpr u64 kRingMagic = 0x44474e5f52494e47ull;      // "DGN_RING": a result of the ring sweep (bitmap, no log)
 constexpr int64_t kRingSeedWords = 2048;               // targets of a graph that the ring sweep keeps in LDS, at most
 // Which graphs may take the ring sweep (see ring_waves):
-constexpr int64_t kRingMaxOps = (int64_t)1 << 17;      // single graphs: at most this size, and
-constexpr int64_t kRingShortOps = 16384;               // (or fewer graphs than the per-graph sweep starts at) up to this size, or
-constexpr int64_t kRingThinOps = 20480;                // to this, times the words of sets, when no input lies further back
-constexpr int kRingThinDist = 96;                      // than this
+constexpr int64_t kRingMaxOps = (int64_t)1 << 17;      // single graphs, or fewer than the per-graph sweep starts at: at most this
+constexpr int64_t kRingShortOps = 16384;               // size, and, times the words of sets, up to this
+constexpr int64_t kRingAboutOps = 4096;                // ... to this when operators read from all over the graph,
+constexpr int64_t kRingThinOps = 20480;                // ... to this when no input lies further back
+constexpr int kRingThinDist = 96;                      // than this, or to any size once a prune has taken
+constexpr int kRingLongLevel = 256;                    // more than a level per so many operators of the largest graph
 // (graphs of a larger batch: kRingMaxGraphOps)
 constexpr int kSmallLevel = 16384;           // levels expanding fewer entries than this decay the threshold faster
 constexpr int kDefaultDeferPercent = 74;
@@ -319,6 +321,7 @@ struct dgn_graph {
     bool ring;              // the ring sweep can take these graphs: see ring_sweep.hip for the three numbers
     int ring_low, ring_dist, ring_span64;
     Reach reach;            // how far back the operators of a single graph read (see the schedule in prune_impl)
+    bool reads_about;       // half of the operators (of all graphs) read further back than an eighth of their graph, or nobody knows
     uint64_t serial;        // unique per handle in this process
     // Hints only, taken from the last prune of this graph; a wrong one costs launches that return at once,
     // or a second batch, and corrects itself.  Kept apart for full prunes [0] and incremental ones [1],
@@ -328,6 +331,8 @@ struct dgn_graph {
     //   hint_runs, hint_run_len: how that prune alternated between stretches of wide levels and the
     //     single-workgroup kernel (lengths of the first stretches; 0 stretches: unknown); the launches are
     //     laid out the same way instead of in fixed groups.
+    //   long_chains: a prune of this graph took so many levels that the ring sweep is the better way for it (see ring_waves)
+    mutable std::atomic<int> long_chains = {};
     mutable std::atomic<int> wide_hint[2] = {};
     mutable std::atomic<int> hint_runs[2] = {};
     mutable std::atomic<int> hint_run_len[2][dgn::kMaxRuns] = {};
@@ -406,9 +411,11 @@ int finish_build(dgn_graph *h, const int64_t *op_off_host, const int64_t *t_off_
     h->ring_dist = ring[2];
     h->ring_span64 = ring[3];
     h->multi_producer = found[kStatusMulti] != 0;
-    auto most = [&](int word) { return h->G == 1 && found[word] * 2 > found[kStatusSampled]; };
-    h->reach = most(kStatusWithin2048) ? Reach::deep : most(kStatusWithin192) ? Reach::near
-             : most(kStatusWithin32) ? Reach::layers : Reach::unknown;
+    auto most = [&](int word) { return found[word] * 2 > found[kStatusSampled]; };
+    h->reads_about = !most(kStatusWithin8);
+    if (h->G == 1)
+        h->reach = most(kStatusWithin2048) ? Reach::deep : most(kStatusWithin192) ? Reach::near
+                 : most(kStatusWithin32) ? Reach::layers : Reach::unknown;
     // The topological precondition is checked when the caller asks for validation, and for packed
     // batches, whose per-graph sweep is only chosen when it holds.  (One random access per edge: not
     // worth paying on every build of a big single graph, whose traversal does not depend on it.)  Where the walk found
@@ -699,16 +706,19 @@ int dgn_prune_workspace(const dgn_graph *g, int32_t num_sets, size_t *scratch_by
 
 // Waves per graph when the ring sweep takes this call, 0 when it does not.
 //   Which graphs: the sweep walks every operator, 1 024 of them in 2 us (nothing kept) to 13 us (one long chain); the level
-// by level traversal costs about 4.6 us per dependent level of a thin graph and 60 to 100 us before it has done anything,
-// but it ends where the chains do.  Up to 16 384 operators the sweep was never slower for any family tried (layered CNN,
-// unrolled RNN, sliding window, power law; 1 to 64 sets): 34 against 106 us at 800 operators, at worst 71 against 69 (RNN 30 wide,
-// 15 000 operators).  That holds with sixteen waves on the graph; where they need more LDS than there is, because
-// its operators read far back, four or one lose (35 layers of 324: 208 against 168 us, power law of 6 000: 235, 137).
+// by level traversal costs about 4.6 us per dependent level of a thin graph and 60 to 100 us before it has done anything
+// (a first prune 250 to 300 where its frontiers leave the single workgroup), but it ends where the chains do.  Up to 16 384
+// operators the sweep was never the slower one for layered graphs, unrolled RNNs and sliding windows, 1 to 64 sets: 34 against
+// 106 us at 800 operators, 98 against 153 at 8 400 (33 layers of 255), at worst 71 against 69 (RNN 30 wide, 15 000).  With inputs from
+// all over the graph most of a group's pushes cross waves, and the line is at 4 096 (power law of 4 000: 124 against 141
+// us, 4 200: 156, 137, 6 000: 235, 137).  All that with sixteen or four waves; where what is read lies so far back that
+// LDS has room for one alone, it loses (35 layers of 324: 208 against 168).
 //   Beyond that size it depends on what is kept, which nobody knows before.  A recorded chain of short hops (window of 64)
 // of 20 000 operators: 282 against 3 300 us; an RNN as narrow, whose chains die out: 134 against 123, at 24 000 146 against 129, at
 // 64 000 287 against 125, at 120 000 450 against 128.  So the line for graphs that read nothing older than 96 tensors lies where such an RNN
-// loses a tenth (with a single target 87 against 74).  Several words of sets are swept in the time of one, where the traversal
-// takes them one after the other.
+// loses a tenth (with a single target 87 against 74); beyond, a graph is traversed until a prune has shown that it has long
+// chains: a level per 256 operators (at 4.6 us each 18 us per 1 024; the narrow RNNs take 6 to 20 levels in all).
+// Several words of sets are swept in the time of one, where the traversal takes them one after the other.
 //   How many waves: sixteen take a graph that has a compute unit to itself (20 000 operators in a chain of short hops:
 // 0.28 ms, four waves 0.30, one 0.40); four when all graphs are resident at once that way (1 500 graphs of 20 000 operators:
 // 0.95 ms, one wave 1.03, sixteen 2.13); one beyond (4 096 graphs: 1.18 ms, four waves 1.67).  Batches of 64 graphs and more
@@ -720,9 +730,11 @@ static int ring_waves(const dgn_graph *g, const dgn_options *o, const dgn_stats 
     const bool many = g->G >= kSweepMinGraphs;               // (such batches were always swept graph by graph)
     if (!many && stats && stats->level_trace && stats->level_trace_cap > 0) return 0;     // asks for levels: there are none here
     const bool thin = g->ring_dist <= kRingThinDist;
-    const int64_t most = many   ? kRingMaxGraphOps
-                         : thin ? (words > kRingMaxOps / kRingThinOps ? kRingMaxOps : kRingThinOps * words)
-                                : kRingShortOps;
+    int64_t most = thin ? kRingThinOps : g->reads_about ? kRingAboutOps : kRingShortOps;
+    most = words > kRingMaxOps / most ? kRingMaxOps : most * words;
+    if (!thin && most > kRingShortOps) most = kRingShortOps;
+    if (thin && g->long_chains.load(std::memory_order_relaxed)) most = kRingMaxOps;
+    if (many) most = kRingMaxGraphOps;
     if (g->max_graph_ops > most) return 0;
     auto fits = [&](int w) {
         return ((size_t)ring_words(w, g->ring_dist, g->ring_span64) + (size_t)g->ring_low + kRingExtraWords) * sizeof(u64) +
@@ -731,7 +743,7 @@ static int ring_waves(const dgn_graph *g, const dgn_options *o, const dgn_stats 
     const int64_t groups = g->G > 1 ? g->G : words;
     if (groups <= g->num_cus && g->max_graph_ops > 4 * kWave) {
         if (fits(16)) return 16;
-        if (!many && words == 1) return 0;
+        if (!many) return fits(4) ? 4 : 0;
     }
     if (groups <= 8 * g->num_cus && fits(4)) return 4;
     return fits(1) ? 1 : 0;
@@ -1133,6 +1145,8 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
         g->exact_streak[hk].store(exact ? g->exact_streak[hk].load(std::memory_order_relaxed) + 1 : 0,
                                   std::memory_order_relaxed);
     }
+    if ((int64_t)hst->slot[(launch_no - 1) & 1].level * kRingLongLevel > g->max_graph_ops && !generic_only && hk == 0)
+        g->long_chains.store(1, std::memory_order_relaxed);
     if (recycle && (hst->error & (kErrOverflow | kErrLogFull))) {
         // the log is incomplete; a compaction enqueued ahead may have called it complete
         FillRegion hz[1] = {{S.hdr, sizeof(RecycleHeader)}};

@@ -280,10 +280,11 @@ enum : int {
     kStatusScattered = 17,       // the outputs are not one run of tensors up to the last one
     kStatusRing = 20,            // what k_records_and_check finds out for the ring sweep: [0] != 0: outputs are not one run or
                                  // read too early; [1] graph inputs, [2] dist, [3] span64 (maxima)
-    kStatusSampled = 24,         // operators of a single graph, outputs in one run, whose first input was looked at ...
-    kStatusWithin32 = 25,        // ... those that read less than a 32nd of the graph back,
-    kStatusWithin192 = 26,       // ... a 192nd,
-    kStatusWithin2048 = 27,      // ... a 2 048th
+    kStatusSampled = 24,         // operators whose first input was looked at (their graph's outputs are one run) ...
+    kStatusWithin8 = 25,         // ... those that read less than an eighth of their graph back,
+    kStatusWithin32 = 26,        // ... a 32nd,
+    kStatusWithin192 = 27,       // ... a 192nd,
+    kStatusWithin2048 = 28,      // ... a 2 048th
 };
 // An edge list and where its adjacency goes.  idx / row == NULL: those are in place already.
 struct EdgeList {

@@ -422,8 +422,8 @@ __device__ __forceinline__ void write_record(int4 *p, int32_t ib, int32_t ie, in
 }
 
 // How far back do operators read?  Sampled (the first input of a few thousand operators, spread over the graph) for the
-// traversal's schedule (see there).  has: this lane's operator has an input, its first is `t`, and tensors are numbered
-// in creation order from t_first on.  Whole waves.
+// traversal's schedule and the choice between it and the sweep.  has: this lane's operator has an input, its first is `t`; o is
+// its number among its graph's num_ops operators, whose num_outputs outputs are numbered in creation order from t_first on.
 __device__ __forceinline__ void sample_reach(bool has, int64_t o, int32_t t, int64_t num_ops, int32_t t_first, int64_t num_outputs,
                                              int32_t *status)
 {
@@ -436,6 +436,7 @@ __device__ __forceinline__ void sample_reach(bool has, int64_t o, int32_t t, int
     };
     if (seen == 0) return;
     if (lane_id() == 0) atomicAdd(&status[kStatusSampled], __popcll(seen));
+    within(1.0f / 8, kStatusWithin8);
     within(1.0f / 32, kStatusWithin32);
     within(1.0f / 192, kStatusWithin192);
     within(1.0f / 2048, kStatusWithin2048);
@@ -537,8 +538,9 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
     int gi = -1;
     int64_t lo = 0, hi = g.num_tensors, o_lo = 0, o_hi = g.num_ops;
     int32_t shift = 0, t_first = 0;                         // output edge e should be tensor e + shift
-    // (at the first operators of some of the waves)
-    const bool samples = !batched && status[kStatusScattered] == 0 && wave_id % ((waves + kSampleWaves - 1) / kSampleWaves) == 0;
+    // (at the first operators of some of the waves; a batch of 64 graphs and more goes one way whatever it reads)
+    const bool samples = (batched ? g.num_graphs < 64 : status[kStatusScattered] == 0) &&
+                         wave_id % ((waves + kSampleWaves - 1) / kSampleWaves) == 0;
     for (int64_t o = begin + lane_id(); o < last; o += kWave) {
         const int32_t ib = g.in_rowptr[o], ie = g.in_rowptr[o + 1];
         const int32_t ob = g.out_rowptr[o], oe = g.out_rowptr[o + 1];
@@ -570,7 +572,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
             for (int j = 0; j < 2; ++j) u[j] = g.out_idx[min(ob + j, none_out)];
         }
         if (samples && o - lane_id() == begin)
-            sample_reach(ie > ib, o, t[0], g.num_ops, g.num_tensors - g.nnz_out, g.nnz_out, status);
+            sample_reach(ie > ib, o - o_lo, t[0], o_hi - o_lo, t_first, hi - t_first, status);
         auto input = [&](int32_t x) {
             if (x < lo || x >= hi) bad = true;
             if (x >= t_first) {

@@ -236,12 +236,12 @@ def test_phase_times_of_a_sweep(dgn, G, ops):
             assert abs(sum(ms[:6]) - ms[6]) < 0.01 + 0.02 * ms[6]
 
 
-# Which single graphs are swept (the measurements stand beside the rule in api.hip): sixteen waves have room for what the
-# operators read (dozens of wide layers and a power law of 6 000 read further back), or several words share the
-# sweep; beyond 16 384 operators only where everything is read at once, and few where chains may die out.
+# Which single graphs are swept (the measurements stand beside the rule in api.hip): there is room for four waves and what the
+# operators read (35 layers of 324: for one only), and few operators if they read from all over; beyond 16 384 operators
+# only where everything is read at once, and few where chains may die out; more with several words of sets.
 @pytest.mark.parametrize("family,size,words,swept", [
-    ("cnn", (80, 150), 1, True), ("cnn", (35, 324), 1, False), ("cnn", (35, 324), 2, True), ("powerlaw", (3000,), 1, True),
-    ("powerlaw", (6000,), 1, False), ("powerlaw", (6000,), 2, True), ("cnn", (200, 90), 1, False), ("layered", (20000,), 1, True),
+    ("cnn", (80, 150), 1, True), ("cnn", (33, 255), 1, True), ("cnn", (20, 400), 1, True), ("cnn", (35, 324), 1, False),
+    ("powerlaw", (4000,), 1, True), ("powerlaw", (4200,), 1, False), ("powerlaw", (6000,), 2, True), ("cnn", (200, 90), 1, False), ("layered", (20000,), 1, True),
     ("rnn", (200, 80), 1, True), ("rnn", (300, 80), 1, False), ("rnn", (300, 80), 2, True), ("rnn", (700, 80), 2, False),
     ("rnn", (1500, 80), 1, False)])
 def test_which_single_graphs_are_swept(dgn, oracle, family, size, words, swept):
@@ -257,3 +257,17 @@ def test_which_single_graphs_are_swept(dgn, oracle, family, size, words, swept):
         assert_same(buf.to_host(), oracle_prune(oracle, g, tg)[1], "single word")
         launches = st.launches
     assert (launches <= 2) == swept, launches
+
+
+@pytest.mark.parametrize("family,size,swept", [("layered", (30000,), True), ("batch", (4, 25000), True), ("rnn", (400, 80), False)])
+def test_long_thin_graphs_are_swept_once_a_prune_has_shown_their_chains(dgn, oracle, family, size, swept):
+    import torch
+    g = gg.batch_layered(*size, 5)[0] if family == "batch" else getattr(gg, family)(*size, 5)
+    tg = draw_targets(np.random.default_rng(3), g, 9, 2)
+    buf = dgn.PruneBuffers(dgn.DeviceGraph.from_coo(g), 9)
+    ref = oracle_prune(oracle, g, tg)[1]
+    for call in range(3):
+        st = dgn.dgn_stats()
+        assert buf.prune(torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda(), stats=st) == 0
+        assert_same(buf.to_host(), ref, f"call {call}")
+        assert (st.launches <= 3) == (swept and call > 0), (call, st.launches)
