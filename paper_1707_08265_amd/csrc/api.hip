@@ -947,6 +947,7 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     // 702 000 in 900 layers 1 123 -> 740, for 18 000 in 300 layers 262 -> 190.  The line lies at some 218 layers, each reading
     // mostly the one before: with 100 layers and a handful of targets what is left below P >> 3 is too little to
     // spread over the chip (300 wide, 8 targets: 152 us, P >> 3 310), with 200 it still is for some (800 wide: 332, 412).
+    // The one place beyond where it loses: 850 to 1 000 layers of 100 to 300 and a single set, 380 -> 410 (800 wide 765 -> 520).
     //   From some 30 layers on, it pays as well once there are many targets: at 224 and more P >> 3 was the faster one for each of six
     // shapes (120 layers of 600, 288 targets 307 -> 249), around 150 not for all (264, 286).
     //   In a graph thousands of levels deep a few hundred targets all over it are as many separate searches, and the

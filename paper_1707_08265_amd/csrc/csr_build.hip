@@ -51,7 +51,8 @@ __device__ __forceinline__ void rows_closed(int32_t prev, int32_t cur, int32_t n
 // A stream of 12 bytes per input edge and 28 per output edge and tensor: it is bound by memory.  A thread takes four
 // neighbouring positions per step, in 16-byte accesses where the arrays are aligned for them (one position per thread left
 // the pass waiting for memory).  Outputs take both adjacencies and the producer words from one reading: three passes did
-// that before, 0.99 ms of a 50 M-operator graph and 0.3 more for the producer words; now 1.00 in all = 4.1 TB/s.
+// that before, 0.99 ms of a 50 M-operator graph and 0.3 more for the producer words; then 1.00 in all, with its stores past the
+// caches 0.91 = 4.5 TB/s.
 constexpr int kScanThreads = 256;
 
 template <bool kOut, bool kStream>
