@@ -62,7 +62,9 @@ constexpr int kDefaultDeferPercent = 74;
 constexpr int kDefaultStartShift = 1;       // deferral threshold starts at P >> 1 ...
 constexpr int kDefaultFloorShift = 10;      // ... and stops (drops to 0) below P >> 10 or, in large graphs,
 constexpr int kDefaultFloorPerRoot = 2;     // below 2 sqrt(P); earlier, at
-constexpr int kNearFloorShift = 3;          // P >> 3, in graphs that read nearby, and where there are many targets:
+constexpr int kNearFloorShift = 3;          // P >> 3, in graphs that read nearby, but in many hundred layers not for
+constexpr int kFewSets = 8;                 // so few sets and
+constexpr double kFewSetsOps = 450000;      // so few operators times the root of their number; and where there are many targets,
 constexpr int64_t kLayeredTargets = 256;    // in graphs of a few dozen layers or more
 constexpr int64_t kDeepTargets = 512;       // in deep graphs no larger than
 constexpr int64_t kDeepOps = (int64_t)1 << 22;
@@ -308,7 +310,7 @@ int check_options(const dgn_options *o)
 }  // namespace
 
 // How far back half of the operators read at most (sampled, single graphs with their outputs in one run of tensors)
-enum class Reach { unknown, layers /* a 32nd of the graph */, near /* a 192nd */, deep /* a 2 048th */ };
+enum class Reach { unknown, layers /* a 32nd of the graph */, near /* a 192nd */, nearer /* a 640th */, deep /* a 2 048th */ };
 
 struct dgn_graph {
     GraphView v;
@@ -414,8 +416,8 @@ int finish_build(dgn_graph *h, const int64_t *op_off_host, const int64_t *t_off_
     auto most = [&](int word) { return found[word] * 2 > found[kStatusSampled]; };
     h->reads_about = !most(kStatusWithin8);
     if (h->G == 1)
-        h->reach = most(kStatusWithin2048) ? Reach::deep : most(kStatusWithin192) ? Reach::near
-                 : most(kStatusWithin32) ? Reach::layers : Reach::unknown;
+        h->reach = most(kStatusWithin2048) ? Reach::deep : most(kStatusWithin640) ? Reach::nearer
+                 : most(kStatusWithin192) ? Reach::near : most(kStatusWithin32) ? Reach::layers : Reach::unknown;
     // The topological precondition is checked when the caller asks for validation, and for packed
     // batches, whose per-graph sweep is only chosen when it holds.  (One random access per edge: not
     // worth paying on every build of a big single graph, whose traversal does not depend on it.)  Where the walk found
@@ -947,7 +949,10 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     // 702 000 in 900 layers 1 123 -> 740, for 18 000 in 300 layers 262 -> 190.  The line lies at some 218 layers, each reading
     // mostly the one before: with 100 layers and a handful of targets what is left below P >> 3 is too little to
     // spread over the chip (300 wide, 8 targets: 152 us, P >> 3 310), with 200 it still is for some (800 wide: 332, 412).
-    // The one place beyond where it loses: 850 to 1 000 layers of 100 to 300 and a single set, 380 -> 410 (800 wide 765 -> 520).
+    //   With some 700 to 800 layers and more it depends on how wide the levels are.  One set, 892 layers: 298 wide 375 us,
+    // P >> 3 410; 500 wide 415, 425; 1 000 layers of 600: 648, 477.  Four sets: 200 wide 426, 440; 300 wide 525, 471.  Eight:
+    // 100 wide 400, 406; 156 wide 425, 416.  So the line lies at 450 000 operators over the root of the sets; beyond eight
+    // sets P >> 3 was never the slower one (17 sets, 100 wide 450, 424; 64 sets, 50 wide 403, 386; RNN of 20 000, 64 sets 128, 110).
     //   From some 30 layers on, it pays as well once there are many targets: at 224 and more P >> 3 was the faster one for each of six
     // shapes (120 layers of 600, 288 targets 307 -> 249), around 150 not for all (264, 286).
     //   In a graph thousands of levels deep a few hundred targets all over it are as many separate searches, and the
@@ -960,10 +965,13 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     if (defer_percent < 100) {
         sch.decay = (float)defer_percent / 100.0f;
         sch.theta0 = (int32_t)(g->P >> start_shift);
-        const bool soon = g->reach == Reach::near || (g->reach == Reach::layers && num_targets >= kLayeredTargets) ||
+        const bool soon = g->reach == Reach::near ||
+                          (g->reach == Reach::nearer &&
+                           (num_sets > kFewSets || (double)g->P * (double)g->P * num_sets > kFewSetsOps * kFewSetsOps)) ||
+                          (g->reach == Reach::layers && num_targets >= kLayeredTargets) ||
                           (g->reach == Reach::deep && num_targets >= kDeepTargets && g->P <= kDeepOps);
         sch.theta_floor = (int32_t)(g->P >> (soon ? kNearFloorShift : kDefaultFloorShift));
-        if (g->reach != Reach::deep && !soon) {
+        if (g->reach < Reach::deep && !soon) {
             const double root = kDefaultFloorPerRoot * sqrt((double)g->P);
             if (root < sch.theta_floor) sch.theta_floor = (int32_t)root;
         }

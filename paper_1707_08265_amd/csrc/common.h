@@ -284,7 +284,8 @@ enum : int {
     kStatusWithin8 = 25,         // ... those that read less than an eighth of their graph back,
     kStatusWithin32 = 26,        // ... a 32nd,
     kStatusWithin192 = 27,       // ... a 192nd,
-    kStatusWithin2048 = 28,      // ... a 2 048th
+    kStatusWithin640 = 28,       // ... a 640th,
+    kStatusWithin2048 = 29,      // ... a 2 048th
 };
 // An edge list and where its adjacency goes.  idx / row == NULL: those are in place already.
 struct EdgeList {

@@ -440,6 +440,7 @@ __device__ __forceinline__ void sample_reach(bool has, int64_t o, int32_t t, int
     within(1.0f / 8, kStatusWithin8);
     within(1.0f / 32, kStatusWithin32);
     within(1.0f / 192, kStatusWithin192);
+    within(1.0f / 640, kStatusWithin640);
     within(1.0f / 2048, kStatusWithin2048);
 }
 constexpr int kSampleWaves = 32;         // (updates of one address take 11 ns each)

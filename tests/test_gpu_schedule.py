@@ -34,12 +34,14 @@ def thresholds(dgn, g, tg, **knobs):
 
 
 # (family, sizes, targets per set, sets, waits only down to an eighth of the graph): layers too few for that, a handful of
-# targets in a hundred layers and many of them, enough layers, reads from all over the graph, an RNN with few and many targets
+# targets in a hundred layers and many of them, enough layers, so many of them that sets and width count as well, reads from all over the graph, an RNN with few and
+# many targets
 @pytest.mark.parametrize("family,size,per_set,sets,soon", [
     ("cnn", (24, 700), 8, 1, False), ("cnn", (24, 700), 8, 64, False), ("cnn", (100, 300), 8, 1, False),
     ("cnn", (100, 300), 8, 64, True), ("cnn", (150, 120), 1, 64, False), ("cnn", (250, 200), 8, 1, True),
-    ("cnn", (250, 200), 1, 64, True), ("powerlaw", (200_000,), 1, 64, False), ("rnn", (400, 200), 4, 64, False),
-    ("rnn", (400, 200), 9, 64, True)])
+    ("cnn", (250, 200), 1, 64, True), ("cnn", (500, 200), 8, 1, True), ("cnn", (950, 100), 8, 1, False),
+    ("cnn", (950, 100), 4, 4, False), ("cnn", (950, 100), 8, 9, True), ("cnn", (950, 500), 8, 1, True),
+    ("powerlaw", (200_000,), 1, 64, False), ("rnn", (400, 200), 4, 64, False), ("rnn", (400, 200), 9, 64, True)])
 def test_floor_of_the_thresholds(dgn, family, size, per_set, sets, soon):
     g = gg.cnn(*size, 5)[0] if family == "cnn" else gg.rnn(*size, 5) if family == "rnn" else gg.powerlaw(*size, 5)
     tg = targets(g, family, per_set, sets)
