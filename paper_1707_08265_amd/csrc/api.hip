@@ -860,11 +860,13 @@ static int check_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets
 // dgn_prune.  also_M [T] / also_K [P] (or NULL): two more arrays that the call zeroes with M and K -- all of them,
 // or, with recycled buffers, the words that the previous call's log and kept list name (the caller vouches that
 // they hold non-zero words nowhere else).  Such a caller goes on to use the queues' room for lists of its own.
+// sets, targets: what the schedule goes by: num_sets and num_targets, or, for a word of several, those of an average word (the
+// same for all, so that they take the same launches: 45 layers of 340, 120 sets of 4 or 5, 320 us, each by its own 420).
 static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
                       const int32_t *tgt_idx, uint64_t *tensor_mask, uint64_t *op_mask, uint8_t *op_flag, int32_t *kept_ops,
                       uint64_t *kept_masks, int64_t *kept_count, int64_t *per_query_count, void *scratch,
                       size_t scratch_bytes, const dgn_options *options, dgn_stats *stats, dgn_stream stream,
-                      uint64_t *also_M, uint64_t *also_K)
+                      uint64_t *also_M, uint64_t *also_K, int64_t sets, int64_t targets)
 {
     PruneScratch S{};
     int rc = check_prune(g, num_sets, num_targets, tgt_rowptr, tgt_idx, tensor_mask, op_mask, kept_ops, kept_masks, kept_count,
@@ -967,9 +969,9 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
         sch.theta0 = (int32_t)(g->P >> start_shift);
         const bool soon = g->reach == Reach::near ||
                           (g->reach == Reach::nearer &&
-                           (num_sets > kFewSets || (double)g->P * (double)g->P * num_sets > kFewSetsOps * kFewSetsOps)) ||
-                          (g->reach == Reach::layers && num_targets >= kLayeredTargets) ||
-                          (g->reach == Reach::deep && num_targets >= kDeepTargets && g->P <= kDeepOps);
+                           (sets > kFewSets || (double)g->P * (double)g->P * (double)sets > kFewSetsOps * kFewSetsOps)) ||
+                          (g->reach == Reach::layers && targets >= kLayeredTargets) ||
+                          (g->reach == Reach::deep && targets >= kDeepTargets && g->P <= kDeepOps);
         sch.theta_floor = (int32_t)(g->P >> (soon ? kNearFloorShift : kDefaultFloorShift));
         if (g->reach < Reach::deep && !soon) {
             const double root = kDefaultFloorPerRoot * sqrt((double)g->P);
@@ -1223,7 +1225,8 @@ int dgn_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets, const i
               const dgn_options *options, dgn_stats *stats, dgn_stream stream)
 {
     return prune_impl(g, num_sets, num_targets, tgt_rowptr, tgt_idx, tensor_mask, op_mask, op_flag, kept_ops, kept_masks,
-                      kept_count, per_query_count, scratch, scratch_bytes, options, stats, stream, nullptr, nullptr);
+                      kept_count, per_query_count, scratch, scratch_bytes, options, stats, stream, nullptr, nullptr, num_sets,
+                      num_targets);
 }
 
 // Removal rule + compaction: K computed from tensor_mask_in (from_tensor_mask), or taken as it stands in op_mask.
@@ -1400,8 +1403,9 @@ int dgn_prune_words(const dgn_graph *g, int64_t num_sets, int64_t num_targets, c
                                          reinterpret_cast<u64 *>(M), reinterpret_cast<u64 *>(K), flag, kept,
                                          reinterpret_cast<u64 *>(masks), count, pq, S, options, stats ? &one : nullptr,
                                          static_cast<hipStream_t>(stream), nullptr, nullptr)
-                            : dgn_prune(g, q, num_targets, tgt_rowptr + w * DGN_MAX_SETS, tgt_idx, M, K, flag, kept, masks,
-                                        count, pq, scratch, scratch_bytes, options, stats ? &one : nullptr, stream);
+                            : prune_impl(g, q, num_targets, tgt_rowptr + w * DGN_MAX_SETS, tgt_idx, M, K, flag, kept, masks,
+                                         count, pq, scratch, scratch_bytes, options, stats ? &one : nullptr, stream,
+                                         nullptr, nullptr, words > 1 ? DGN_MAX_SETS : q, num_targets / words);
         if (rc != DGN_OK) return rc;
         if (stats) {
             total.levels += one.levels;
@@ -1487,7 +1491,7 @@ int dgn_backward_prune(const dgn_graph *g, int32_t num_pairs, const int32_t *obj
     // last count pass the read of all of K.
     int rc = prune_impl(g, num_pairs, num_pairs, S.tgt_rowptr, wrt, reinterpret_cast<uint64_t *>(S.B),
                         reinterpret_cast<uint64_t *>(S.KB), op_flag, S.kept, nullptr, S.kept_count, nullptr, scratch,
-                        S.prune_bytes, &o1, stats, stream, tensor_mask, op_mask);
+                        S.prune_bytes, &o1, stats, stream, tensor_mask, op_mask, num_pairs, num_pairs);
     if (rc != DGN_OK) return rc;
     uint8_t *stage_flags = nullptr;
     if (!o1.recompute_keep)

@@ -57,6 +57,30 @@ def test_floor_of_the_thresholds(dgn, family, size, per_set, sets, soon):
     assert int(theta[theta > 0].min()) >= g.num_ops >> 2, theta
 
 
+@pytest.mark.parametrize("per_set,soon", [(3, False), (8, True)])
+def test_words_of_sets_count_their_own_targets(dgn, per_set, soon):
+    """Two words of 64 sets on 100 layers: 192 targets each are few, whatever the call has in all; 512 are many."""
+    import torch
+    g = gg.cnn(100, 300, 5)[0]
+    tg = targets(g, "cnn", per_set, 128)
+    P, T, words = g.num_ops, g.num_tensors, 2
+    graph = dgn.DeviceGraph.from_coo(g)
+    rc, size = dgn.dgn_prune_workspace(graph.handle, 64)
+    assert rc == 0
+    new = lambda n, t: torch.zeros(words, n, dtype=t, device="cuda")  # noqa: E731
+    trace = np.full((512, 4), -7, np.int32)
+    st = dgn.dgn_stats()
+    st.level_trace, st.level_trace_cap = trace.ctypes.data, trace.shape[0]
+    rc = dgn.dgn_prune_words(graph.handle, 128, len(tg.tgt_idx), torch.from_numpy(tg.tgt_rowptr).cuda(),
+                             torch.from_numpy(tg.tgt_idx).cuda(), new(T, torch.int64), new(P, torch.int64), new(P, torch.uint8),
+                             new(P, torch.int32), new(P, torch.int64), new(1, torch.int64), new(64, torch.int64),
+                             torch.empty(size, dtype=torch.uint8, device="cuda"), size, stats=st)
+    assert rc == 0, dgn.dgn_strerror(rc)
+    theta = trace[:, 2]                                                  # (the last word's levels, at least)
+    lowest = int(theta[theta > 0].min())
+    assert lowest >= P >> 3 if soon else lowest < P >> 6, theta
+
+
 @pytest.mark.parametrize("size,per_set,sets", [((2000, 139), 4, 64), ((700, 150), 4, 64), ((60, 300), 6, 17), ((400, 200), 8, 64), ((1000, 100), 8, 64)])
 def test_repeated_prunes_settle_on_one_way(dgn, oracle, size, per_set, sets):
     """Frontiers of a few hundred in a deep graph: the first prune may be done by the one workgroup, later ones start with wide
