@@ -57,6 +57,9 @@ constexpr int64_t kRingThinOps = 20480;                // ... to this when no in
 constexpr int kRingThinDist = 96;                      // than this, or to any size once a prune has taken
 constexpr int kRingLongLevel = 256;                    // more than a level per so many operators of the largest graph
 // (graphs of a larger batch: kRingMaxGraphOps)
+// When such a graph is swept in segments, and how long they are (see ring_segments):
+constexpr double kRingWordUs = 0.9, kRingSegmentsUs = 6.5, kRingSegmentOpUs = 2.5e-5;
+constexpr int kRingFewWords = 16, kRingManySegs = 64, kRingSegmentsPerCu = 24;
 constexpr int kSmallLevel = 16384;           // levels expanding fewer entries than this decay the threshold faster
 constexpr int kDefaultDeferPercent = 74;
 constexpr int kDefaultStartShift = 1;       // deferral threshold starts at P >> 1 ...
@@ -175,6 +178,7 @@ struct PruneScratch {
     u64 *ring_bits;         // ring sweep: a bit per operator, running counts per word, a record per graph
     int32_t *ring_cum;
     int4 *ring_graphs;
+    const char *end;        // of the buffer
     size_t bytes;
 };
 
@@ -242,6 +246,7 @@ PruneScratch prune_scratch(void *mem, int64_t P, int64_t T, int32_t G, int64_t m
     S.pq_part = c.take<int64_t>(S.pq_part_bytes / sizeof(int64_t));
     if (S.pq_replicas == 1) S.pq_part = nullptr;
     S.bytes = c.off;
+    S.end = mem ? static_cast<const char *>(mem) + S.bytes : nullptr;
     return S;
 }
 
@@ -321,7 +326,7 @@ struct dgn_graph {
     bool multi_producer;    // some tensor is written by more than one operator
     int64_t max_graph_ops;  // largest graph of a packed batch (P for a single graph)
     bool ring;              // the ring sweep can take these graphs: see ring_sweep.hip for the three numbers
-    int ring_low, ring_dist, ring_span64;
+    int ring_low, ring_dist, ring_span64, ring_reach;
     Reach reach;            // how far back the operators of a single graph read (see the schedule in prune_impl)
     bool reads_about;       // half of the operators (of all graphs) read further back than an eighth of their graph, or nobody knows
     uint64_t serial;        // unique per handle in this process
@@ -348,7 +353,7 @@ struct dgn_graph {
 
 namespace {
 
-constexpr int kStatusWords = kStatusWithin2048 + 1;
+constexpr int kStatusWords = kStatusReach + 1;
 
 // The status words of a build, once everything before them is done.
 int read_status(const int32_t *status, hipStream_t s, const int32_t **out)
@@ -412,6 +417,7 @@ int finish_build(dgn_graph *h, const int64_t *op_off_host, const int64_t *t_off_
     h->ring_low = ring[1];
     h->ring_dist = ring[2];
     h->ring_span64 = ring[3];
+    h->ring_reach = found[kStatusReach];
     h->multi_producer = found[kStatusMulti] != 0;
     auto most = [&](int word) { return found[word] * 2 > found[kStatusSampled]; };
     h->reads_about = !most(kStatusWithin8);
@@ -751,6 +757,36 @@ static int ring_waves(const dgn_graph *g, const dgn_options *o, const dgn_stats 
     return fits(1) ? 1 : 0;
 }
 
+// Segments per graph of a ring sweep (laid out in a, in `room` bytes at mem), 1: none.
+//   A graph that is read at most 64 tensors back may be swept in pieces at the same time: what a piece does not know is M of
+// the 64 tensors below its upper end, and it is linear in those, so a second sweep whose sets are those tensors says what they
+// bring (see ring_sweep.hip).  A chain of 0.9 us per 64 operators becomes two sweeps of a few words each, side by side, 10 to 17 us to
+// put them together, and twice the work.  Whole prunes, in one piece / in segments: one graph of 500
+// operators 36.5 / 34.5 us, 2 000 50 / 34.5, 20 000 284 / 50; 150 sets on 20 000 292 / 50; 20 graphs of up to 5 100 operators 98 / 54,
+// 96 of them 97 / 54, 250 graphs of 20 000 309 / 230.  The work (50 ps per operator and two sweeps of it) is what it loses by: 500 graphs of 3 000
+// 86 / 95, 1 000 of 6 000 217 / 302.
+//   Two words of 64 operators per segment up to 1 024 operators, four beyond (2 000: 34.5 us, eight 37; 800: two 35.4, four 37.1); not
+// more than 64 segments (20 000: 52.4 us with 79, 50 with 40), nor than 24 waves of sweeps per compute unit (250 graphs of 20 000: 8 words per
+// segment 271 us, 16 248, 32 230); and what has room.
+static int ring_segments(const dgn_graph *g, int64_t words, char *mem, size_t room, RingArgs &a)
+{
+    if (g->ring_reach > kWave) return 1;
+    const int64_t n_words = (g->max_graph_ops + kWave - 1) / kWave, all_words = (g->P / kWave + 1) * (words + 1);
+    if ((double)n_words * kRingWordUs < kRingSegmentsUs + (double)g->P * (double)(words + 1) * kRingSegmentOpUs) return 1;
+    int shift = n_words <= kRingFewWords ? 1 : 2;
+    while ((n_words >> shift) > kRingManySegs || (all_words >> shift) > kRingSegmentsPerCu * g->num_cus) ++shift;
+    for (;; ++shift) {
+        a.seg_shift = shift;
+        a.seg_words = 1 << shift;
+        const int64_t segs = (n_words + a.seg_words - 1) >> shift;
+        if (segs < 2 || a.seg_words > kRingMaxSegWords) return 1;
+        a.segs = (int32_t)segs;
+        if (ring_segment_scratch(a, nullptr) <= room) break;
+    }
+    (void)ring_segment_scratch(a, mem);
+    return a.segs;
+}
+
 // dgn_prune of graphs that the ring sweep takes: one to three launches, nothing to clear beforehand.
 // words > 1: as many words of 64 sets of a single graph at once, num_sets in all.  S.flagbuf == NULL: no flag bytes but
 // the caller's are kept.
@@ -805,6 +841,14 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
     const int64_t avg = num_targets / g->G;
     a.seed_words = (int32_t)(g->G == 1 /* a word may own any part of them */ ? (avg < kRingSeedWords ? avg : kRingSeedWords)
                                        : (avg + avg / 2 + 64 < kRingSeedWords ? avg + avg / 2 + 64 : kRingSeedWords));
+    a.reach = g->ring_reach;
+    a.count_steps = stats && g->G < kSweepMinGraphs;
+    // (segments have what lies behind one word's records, up to the flag bytes, or behind those of several, up to the end)
+    const bool many = !S.flagbuf;
+    char *room = many ? reinterpret_cast<char *>(S.ring_graphs) + align256((size_t)words * sizeof(int4)) : reinterpret_cast<char *>(S.q0);
+    const char *room_end = many ? S.end : reinterpret_cast<const char *>(S.flagbuf);
+    a.segs = room < room_end ? ring_segments(g, words, room, (size_t)(room_end - room), a) : 1;
+    if (a.segs > 1 && a.seed_words < kWave) a.seed_words = kWave;
     int32_t *status = static_cast<int32_t *>(pin);
     status[0] = status[1] = status[2] = 0;
     if (ev) DGN_HIP(hipEventRecord(ev[1], s));

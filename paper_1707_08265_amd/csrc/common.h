@@ -286,6 +286,7 @@ enum : int {
     kStatusWithin192 = 27,       // ... a 192nd,
     kStatusWithin640 = 28,       // ... a 640th,
     kStatusWithin2048 = 29,      // ... a 2 048th
+    kStatusReach = 30,           // k_records_and_check: how far below an operator's first output its inputs lie at most
 };
 // An edge list and where its adjacency goes.  idx / row == NULL: those are in place already.
 struct EdgeList {
@@ -358,8 +359,22 @@ struct RingArgs {
     int32_t recycle;         // *hdr may say that the buffers hold this kernel's last result
     int32_t list_here;       // the sweep makes the ordered list itself
     int32_t ring_words, low_words, seed_words;     // LDS: ring, graph inputs (8 bytes each), targets (4 bytes each)
+    // graphs swept in segments (segs > 1): each of them seg_words = 1 << seg_shift words of 64 operators
+    int32_t segs, seg_words, seg_shift;
+    int32_t count_steps;     // somebody wants to know the settling steps
+    int32_t reach;           // no operator reads a tensor further below its first output (at most kWave)
+    u64 *b_M, *b_K;          // [T], [P]: which tensors of the boundary above its segment a tensor or operator is reached from
+    u64 *edge;               // [G * segs * (words + 1)][ring_edge_words]: per segment and word: what the boundary below receives, the
+                             // graph's inputs, settling steps; the last word: the same in tensors of the boundary above
+    u64 *own_bits;           // as bits: operators kept for the segment's own targets
+    int32_t *seg_kept;       // [G * segs], batches: operators kept
 };
 constexpr int kRingExtraWords = 1 + kWave;
+__host__ __device__ inline int64_t ring_edge_words(const RingArgs &a) { return kWave + a.low_words + 1; }
+constexpr int kRingSegWaves = 1;
+constexpr int kRingMaxSegs = 1024, kRingMaxSegWords = 256;
+// Lays out what segments leave for each other at `mem` (NULL: the bytes alone); g, words, segs and low_words are set
+size_t ring_segment_scratch(RingArgs &a, void *mem);
 constexpr int64_t kRingMaxGraphOps = (int64_t)1 << 18;   // the largest graph that is ever swept
 // words of 64 operators of G graphs, one of them perhaps ragged in each
 __host__ __device__ inline int64_t ring_bit_words(int64_t P, int64_t G) { return (P >> 6) + G + 1; }

@@ -524,7 +524,7 @@ constexpr int kCheckThreads = 256;
 template <bool kStream>
 __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g, int4 *orec, int32_t *status)
 {
-    __shared__ int s_found[6];                      // error, scattered, low, dist, span64
+    __shared__ int s_found[6];                      // error, scattered, low, dist, span64, reach
     if (!adjacency_ready(status, false)) return;
     if (threadIdx.x < 6) s_found[threadIdx.x] = 0;
     __syncthreads();
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
     const int64_t per = (((int64_t)g.num_ops + waves - 1) / waves + kWave - 1) / kWave * kWave;
     const int64_t begin = wave_id * per, last = min(begin + per, (int64_t)g.num_ops);
     bool bad = false, scattered = false;
-    int low = 0, dist = 0, span64 = 0;
+    int low = 0, dist = 0, span64 = 0, reach = 0;
     int gi = -1;
     int64_t lo = 0, hi = g.num_tensors, o_lo = 0, o_hi = g.num_ops;
     int32_t shift = 0, t_first = 0;                         // output edge e should be tensor e + shift
@@ -580,6 +580,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
             if (x >= t_first) {
                 if (x >= ob + shift) scattered = true;      // not written before, if the outputs are one run
                 dist = max(dist, oe + shift - x);
+                reach = max(reach, ob + shift - x);
             }
         };
         bool consecutive = true;
@@ -600,7 +601,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
         write_record<kStream>(&orec[o], ib, ie, ob, oe, first, consecutive);
         if (((o - o_lo) & (kWave - 1)) == 0) span64 = max(span64, g.out_rowptr[min(o + kWave, o_hi)] - ob);
     }
-    const int wlow = wave_max(low), wdist = wave_max(dist), wspan = wave_max(span64);
+    const int wlow = wave_max(low), wdist = wave_max(dist), wspan = wave_max(span64), wreach = wave_max(reach);
     const bool wbad = ballot64(bad) != 0, wscattered = ballot64(scattered) != 0;
     if (lane_id() == 0) {
         if (wbad) s_found[0] = 1;
@@ -608,12 +609,13 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
         atomicMax(&s_found[2], wlow);
         atomicMax(&s_found[3], wdist);
         atomicMax(&s_found[4], wspan);
+        atomicMax(&s_found[5], wreach);
     }
     __syncthreads();
     if (threadIdx.x == 0 && s_found[0]) atomicOr(&status[0], kErrCrossGraph);
-    if (threadIdx.x < 4) {                                  // one look, and an atomic only where it would change something
-        const int v = s_found[1 + threadIdx.x];
-        if (v > load_coherent(&status[kStatusRing + threadIdx.x])) atomicMax(&status[kStatusRing + threadIdx.x], v);
+    if (threadIdx.x < 5) {                                  // one look, and an atomic only where it would change something
+        const int v = s_found[1 + threadIdx.x], at = threadIdx.x < 4 ? kStatusRing + (int)threadIdx.x : (int)kStatusReach;
+        if (v > load_coherent(&status[at])) atomicMax(&status[at], v);
     }
 }
 

@@ -83,6 +83,30 @@ def test_shapes(dgn, oracle, shape):
     check(dgn, oracle, g, [draw_targets(rng, g, Q, 3) for _ in range(4)])
 
 
+# Graphs read at most 64 tensors back are swept in segments (two launches, or one where the whole graph is one segment):
+# sizes at the edges of words and segments, operators without outputs and with many, more graph inputs than a wave has lanes, the
+# reach that is just too far, batches with short and empty graphs, targets that go through the masks.
+@pytest.mark.parametrize("shape,segments", [
+    ((1, 448, 64, 2, 3, 16), False), ((1, 449, 64, 2, 3, 16), True), ((1, 1024, 64, 2, 3, 1), True), ((1, 1025, 64, 2, 3, 16), True),
+    ((1, 1153, 1, 1, 1, 1), True), ((1, 2049, 64, 6, 7, 100), True), ((1, 3000, 64, 3, 3, 300), True), ((1, 3000, 65, 2, 3, 16), False),
+    ((1, 16321, 30, 1, 2, 5), True), ((1, 20000, 64, 4, 5, 70), True), ((3, 900, 64, 2, 3, 16), None), ((6, 5000, 64, 3, 4, 80), None),
+    ((90, 2500, 64, 2, 3, 16), None), ((260, 4000, 64, 2, 3, 16), None)])
+@pytest.mark.parametrize("Q,most", [(1, 3), (64, 2), (64, 200)])
+def test_segments(dgn, oracle, shape, segments, Q, most):
+    import torch
+    G, P, window, out_max, in_max, low = shape
+    rng = np.random.default_rng(P * 11 + G + Q + most)
+    g = recorded(rng, G, P, window, out_max, in_max, low, empty_every=9 if G > 9 else 0)
+    draws = [draw_targets(rng, g, Q, most if G < 9 else min(most, 40)) for _ in range(2)]
+    check(dgn, oracle, g, draws + draws[:1])
+    if segments is None:
+        return
+    buf = dgn.PruneBuffers(dgn.DeviceGraph.from_coo(g), Q)
+    st = dgn.dgn_stats()
+    assert buf.prune(torch.from_numpy(draws[0].tgt_rowptr).cuda(), torch.from_numpy(draws[0].tgt_idx).cuda(), stats=st) == 0
+    assert st.launches == (2 if segments or P > 16384 else 1) and st.levels > 0
+
+
 @pytest.mark.parametrize("G", [1, 100])
 def test_more_targets_than_fit_in_lds_go_through_the_masks(dgn, oracle, G):
     rng = np.random.default_rng(G)
