@@ -38,8 +38,10 @@ constexpr int kNarrowCap = 1024, kNarrowCapNear = 320;
 constexpr int kNarrowLevels = 12;           // done by the one workgroup in so few levels, a prune is left to it (100 000 operators
                                             // in 12 levels 127 us, wide 138; 36 000 in 13 144, wide 111)
 constexpr int kWidePerGroup = 12;           // wide level launches between two single-workgroup launches
-constexpr int kWideGroupsFirst = 4;         // groups in the first batch (one state read-back per batch) ...
-constexpr int kWideGroups = 6;              // ... and in the following ones
+// Groups in the first batch of a graph not known yet (one state read-back per batch; see first_groups): one or two, then twice as
+// many as before, up to this.
+constexpr int kWideGroups = 6;
+constexpr int64_t kOneGroupOps = (int64_t)1 << 16, kOneGroupFlatOps = (int64_t)1 << 19;
 constexpr int kMaxBatch = 512;              // launches enqueued between two state read-backs, at most
 constexpr int kTailLevels = 1;              // wide launches enqueued beyond the layout the previous prune needed ...
 constexpr int kExactStreak = 3;             // ... until that layout has fitted exactly this many prunes in a row
@@ -901,6 +903,18 @@ static int check_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets
     return DGN_OK;
 }
 
+// Launches enqueued before anything is known of a graph's levels.  One that finds nothing costs 2.4 us, a group of twelve wide
+// ones and the single-workgroup kernel 30; a batch that falls short a wait, a compaction for nothing and another group, 90 to 120.
+// Power-law graphs of up to half a million operators take 8 to 14 levels (300 000 operators, 64 sets, first prune: four groups 327
+// us, two 271, one 234; 1 M takes 13 to 16: 360, 300, 379), graphs of 218 to 750 layers 9 to 13 wide ones (500 x 400: 474, 409, 380), and
+// small graphs of any kind fit more often than not (120 x 200: 309, 250, 220; 1 000 x 40, the deepest: 487, 428, 473).
+// Others, 120 x 600 (359, 305, 404), 900 x 300 (590, 522, 576), an RNN of 400 000 (824, 761, 813), take two.
+static int first_groups(const dgn_graph *g)
+{
+    const bool few = g->P <= kOneGroupOps || g->reach == Reach::near || (g->reach == Reach::unknown && g->P <= kOneGroupFlatOps);
+    return few ? 1 : 2;
+}
+
 // dgn_prune.  also_M [T] / also_K [P] (or NULL): two more arrays that the call zeroes with M and K -- all of them,
 // or, with recycled buffers, the words that the previous call's log and kept list name (the caller vouches that
 // they hold non-zero words nowhere else).  Such a caller goes on to use the queues' room for lists of its own.
@@ -1166,7 +1180,8 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
             // unknown graph, or the layout fell short: groups of wide levels with the single-workgroup kernel
             // after each; a batch right after a hinted one is small (the hint was nearly right)
             const bool learns = first && starts_wide && !generic_only;     // (one workgroup did all of the call before)
-            const int groups = learns ? 1 : first ? kWideGroupsFirst : (hint_runs > 0 && batch == 1) ? 1 : kWideGroups;
+            const int doubled = batch < 4 ? 1 << (batch > 0 ? batch - 1 : 0) : kWideGroups;
+            const int groups = learns ? 1 : first ? first_groups(g) : doubled;
             for (int i = 0; i < groups; ++i) {
                 rc = group(kWidePerGroup);
                 if (rc) return rc;
