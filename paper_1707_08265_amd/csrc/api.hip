@@ -50,6 +50,7 @@ constexpr int kSweepMinGraphs = 64;         // packed batches with at least this
 constexpr int64_t kSweepMaxGraphOps = 1 << 18;   // ... none larger than this use the per-graph sweep
 constexpr u64 kRecycleMagic = 0x44474e5f52435943ull;   // "DGN_RCYC"
 constexpr u64 kRingMagic = 0x44474e5f52494e47ull;      // "DGN_RING": a result of the ring sweep (bitmap, no log)
+constexpr u64 kBandMagic = 0x44474e5f42414e44ull;      // "DGN_BAND": a result of the sweep by layers
 constexpr int64_t kRingSeedWords = 2048;               // targets of a graph that the ring sweep keeps in LDS, at most
 // Which graphs may take the ring sweep (see ring_waves):
 constexpr int64_t kRingMaxOps = (int64_t)1 << 17;      // single graphs, or fewer than the per-graph sweep starts at: at most this
@@ -62,6 +63,14 @@ constexpr int kRingLongLevel = 256;                    // more than a level per 
 // When such a graph is swept in segments, and how long they are (see ring_segments):
 constexpr double kRingWordUs = 0.9, kRingSegmentsUs = 6.5, kRingSegmentOpUs = 2.5e-5;
 constexpr int kRingFewWords = 16, kRingManySegs = 64, kRingSegmentsPerCu = 24;
+// Which single graphs are swept by layers (see band_sweep.hip), of those that the ring sweep leaves: they read the last eighth of the
+// graph mostly, and no more than one operator in 25 what was written just before (layers of 40: one in 100, chains with a window of
+// 64: one in 10).  Whole prunes, level by level / swept, 64 sets of up to 8: 24 layers of 700 161 / 82 us, 60 x 300 173 / 86, 200 x 90
+// 170 / 119, 500 x 400 370 / 216, 1 000 x 40 376 / 284, 1 000 x 800 817 / 661; first prunes of them 300 to 800 / 92 to 674.  With a
+// single set of 4: 24 x 700 96 / 68, 100 x 600 156 / 115, 1 000 x 300 408 / 327, but 300 x 800 212 / 235 and 1 000 x 800 535 / 650, so up
+// to four sets on more than 200 000 operators are left to the levels.
+constexpr int kBandSoonShare = 25;
+constexpr int64_t kBandFewSets = 4, kBandFewSetsOps = 200000;
 constexpr int kSmallLevel = 16384;           // levels expanding fewer entries than this decay the threshold faster
 constexpr int kDefaultDeferPercent = 74;
 constexpr int kDefaultStartShift = 1;       // deferral threshold starts at P >> 1 ...
@@ -331,6 +340,7 @@ struct dgn_graph {
     int ring_low, ring_dist, ring_span64, ring_reach;
     Reach reach;            // how far back the operators of a single graph read (see the schedule in prune_impl)
     bool reads_about;       // half of the operators (of all graphs) read further back than an eighth of their graph, or nobody knows
+    bool layers;            // a single graph, its outputs in one run of tensors, that looks like layers (see band_sweep.hip)
     uint64_t serial;        // unique per handle in this process
     // Hints only, taken from the last prune of this graph; a wrong one costs launches that return at once,
     // or a second batch, and corrects itself.  Kept apart for full prunes [0] and incremental ones [1],
@@ -341,7 +351,9 @@ struct dgn_graph {
     //     single-workgroup kernel (lengths of the first stretches; 0 stretches: unknown); the launches are
     //     laid out the same way instead of in fixed groups.
     //   long_chains: a prune of this graph took so many levels that the ring sweep is the better way for it (see ring_waves)
+    //   no_layers: the plan of the sweep by layers has found that the graph is not of that kind
     mutable std::atomic<int> long_chains = {};
+    mutable std::atomic<int> no_layers = {};
     mutable std::atomic<int> wide_hint[2] = {};
     mutable std::atomic<int> hint_runs[2] = {};
     mutable std::atomic<int> hint_run_len[2][dgn::kMaxRuns] = {};
@@ -355,7 +367,7 @@ struct dgn_graph {
 
 namespace {
 
-constexpr int kStatusWords = kStatusReach + 1;
+constexpr int kStatusWords = kStatusSoon + 1;
 
 // The status words of a build, once everything before them is done.
 int read_status(const int32_t *status, hipStream_t s, const int32_t **out)
@@ -426,6 +438,10 @@ int finish_build(dgn_graph *h, const int64_t *op_off_host, const int64_t *t_off_
     if (h->G == 1)
         h->reach = most(kStatusWithin2048) ? Reach::deep : most(kStatusWithin640) ? Reach::nearer
                  : most(kStatusWithin192) ? Reach::near : most(kStatusWithin32) ? Reach::layers : Reach::unknown;
+    // (operators that read what was written just before: chains, not layers)
+    h->layers = h->G == 1 && h->P > 0 && h->P <= kBandMaxOps && h->Ein > 0 && found[kStatusScattered] == 0 && h->T >= h->Eout &&
+                h->T - h->Eout <= kBandMaxLow && !h->reads_about &&
+                found[kStatusSoon] * kBandSoonShare <= found[kStatusSampled];
     // The topological precondition is checked when the caller asks for validation, and for packed
     // batches, whose per-graph sweep is only chosen when it holds.  (One random access per edge: not
     // worth paying on every build of a big single graph, whose traversal does not depend on it.)  Where the walk found
@@ -881,6 +897,104 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
     return error_bits_to_code(status[0]);
 }
 
+// dgn_prune of a graph that looks like layers (see band_sweep.hip).  *taken: whether it was one; if not, nothing but a clear has
+// happened.
+static int band_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr, const int32_t *tgt_idx,
+                      u64 *M, u64 *K, uint8_t *op_flag, int32_t *kept_ops, u64 *kept_masks, int64_t *kept_count,
+                      int64_t *per_query_count, const PruneScratch &S, const dgn_options *options, dgn_stats *stats, hipStream_t s,
+                      u64 *also_M, u64 *also_K, bool *taken)
+{
+    *taken = false;
+    BandArgs a{};
+    a.g = g->v;
+    if (reinterpret_cast<const char *>(S.q0) + band_scratch(a, nullptr) > reinterpret_cast<const char *>(S.flagbuf)) return DGN_OK;
+    (void)band_scratch(a, S.q0);
+    void *pin = nullptr;
+    int rc = pinned_buffer(&pin);
+    if (rc) return rc;
+    // 0 start, 1 cleared, 2 seeded, 3 swept, 4 counted, 5 scanned, 6 listed; profile = 2: those around the sweep alone
+    hipEvent_t *ev = nullptr;
+    const bool all = options && options->profile == 1;
+    if (options && options->profile && stats) {
+        rc = profile_events(&ev);
+        if (rc) return rc;
+        if (all) DGN_HIP(hipEventRecord(ev[0], s));
+    }
+    const size_t pq_bytes = per_query_count ? sizeof(int64_t) * 64 : 0;
+    a.num_sets = num_sets;
+    a.num_targets = num_targets;
+    a.tgt_rowptr = tgt_rowptr;
+    a.tgt_idx = tgt_idx;
+    a.M = M;
+    a.K = K;
+    a.state = S.state;
+    a.host_status = static_cast<int32_t *>(pin);
+    a.hdr = S.hdr;
+    a.want = RecycleHeader{kBandMagic, g->serial, M, K, kept_ops, kept_count, op_flag, also_M, also_K, {0, 0, 0}};
+    a.recycle = options && options->recycle;
+    for (int i = 0; i < 8; ++i) a.host_status[i] = 0;
+    const FillRegion clear[kBandRegions] = {{M, (size_t)g->T * 8}, {K, (size_t)g->P * 8}, {S.state, 256 + sizeof(TravCounters)},
+                                            {per_query_count, pq_bytes}, {S.pq_part, per_query_count ? S.pq_part_bytes : 0},
+                                            {also_M, (size_t)g->T * 8}, {also_K, (size_t)g->P * 8}};
+    for (int i = 0; i < kBandRegions; ++i) a.clear[i] = clear[i];
+    const bool from_m = num_targets > kBandMaxTargets;
+    // (the backward prune goes on with the flag bytes where the traversal would have kept them)
+    uint8_t *flags = also_M ? ring_flags(S, op_flag, g->P) : op_flag;
+    if (flags != op_flag) {
+        FillRegion more[1] = {{flags, S.db_bytes}};
+        DGN_HIP(launch_clear(more, 1, s));
+    }
+    DGN_HIP(launch_band_plan(a, g->num_cus, s));
+    if (ev && all) DGN_HIP(hipEventRecord(ev[1], s));
+    if (from_m) DGN_HIP(launch_seed(g->v, num_sets, num_targets, tgt_rowptr, tgt_idx, M, S.state, S.ctr, nullptr, S.qg, 0, ColourLog{}, s));
+    if (ev) DGN_HIP(hipEventRecord(ev[2], s));
+    DGN_HIP(launch_band_sweep(a, from_m, s));
+    if (ev) DGN_HIP(hipEventRecord(ev[3], s));
+    CompactArgs ca{};
+    ca.g = g->v;
+    ca.M = M;
+    ca.K = K;
+    ca.op_flag = op_flag ? op_flag : flags;
+    ca.kept_ops = kept_ops;
+    ca.kept_masks = kept_masks;
+    ca.kept_count = kept_count;
+    ca.per_query_count = per_query_count;
+    ca.opbits = S.opbits;
+    ca.block_counts = S.block_counts;
+    ca.pq_part = S.pq_part;
+    ca.pq_replicas = S.pq_replicas;
+    ca.hdr = a.recycle ? S.hdr : nullptr;
+    ca.want = a.want;
+    ca.error = &S.state->error;
+    DGN_HIP(launch_keep_compact(ca, s, ev && all ? ev + 4 : nullptr));
+    if (op_flag && flags != op_flag) DGN_HIP(hipMemcpyAsync(flags, op_flag, (size_t)g->P, hipMemcpyDeviceToDevice, s));
+    DGN_HIP(hipStreamSynchronize(s));
+    const int32_t *status = a.host_status;
+    if (status[kBandTaken] == 0) {
+        g->no_layers.store(1, std::memory_order_relaxed);
+        return DGN_OK;
+    }
+    *taken = true;
+    if (stats) {
+        int32_t *user_trace = stats->level_trace;
+        const int64_t user_cap = stats->level_trace_cap;
+        memset(stats, 0, sizeof(*stats));
+        stats->level_trace = user_trace;
+        stats->level_trace_cap = user_cap;
+        stats->launches = from_m ? 6 : 5;
+        stats->levels = status[kBandTaken] - 1;
+        stats->tensor_visits = g->P;
+        stats->recycled = status[kBandFound];
+        if (ev && all) {
+            for (int i = 0; i < 6; ++i) DGN_HIP(hipEventElapsedTime(&stats->phase_ms[i], ev[i], ev[i + 1]));
+            DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_TOTAL], ev[0], ev[6]));
+        } else if (ev) {
+            DGN_HIP(hipEventElapsedTime(&stats->phase_ms[DGN_PHASE_TRAVERSE], ev[2], ev[3]));
+        }
+    }
+    return error_bits_to_code(status[kBandErrors] | status[kBandErrors + 1] | status[kBandErrors + 2] | status[kBandErrors + 3]);
+}
+
 // What dgn_prune asks of its arguments; lays out its scratch.
 static int check_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr,
                        const int32_t *tgt_idx, const uint64_t *tensor_mask, const uint64_t *op_mask, const int32_t *kept_ops,
@@ -939,6 +1053,16 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
         return ring_prune(g, ring, 1, num_sets, num_targets, tgt_rowptr, tgt_idx, M, K, op_flag, kept_ops,
                           reinterpret_cast<u64 *>(kept_masks), kept_count, per_query_count, S, options, stats, s,
                           reinterpret_cast<u64 *>(also_M), reinterpret_cast<u64 *>(also_K));
+    const bool plain = !(options && (options->traversal != 0 || options->incremental || options->recompute_keep)) &&
+                       !(stats && stats->level_trace && stats->level_trace_cap > 0);
+    const bool few = sets <= kBandFewSets && g->P > kBandFewSetsOps;
+    if (g->layers && plain && !few && !g->no_layers.load(std::memory_order_relaxed)) {
+        bool taken = false;
+        rc = band_prune(g, num_sets, num_targets, tgt_rowptr, tgt_idx, M, K, op_flag, kept_ops, reinterpret_cast<u64 *>(kept_masks),
+                        kept_count, per_query_count, S, options, stats, s, reinterpret_cast<u64 *>(also_M),
+                        reinterpret_cast<u64 *>(also_K), &taken);
+        if (rc || taken) return rc;
+    }
     const size_t pq_bytes = per_query_count ? sizeof(int64_t) * 64 * (size_t)(g->G > 1 ? g->G : 1) : 0;
     int64_t launches = 0, level_launches = 0;
     // 0 start, 1 cleared, 2 seeded, 3 traversed, 4 counted, 5 scanned, 6 scattered.  An event between two

@@ -287,6 +287,7 @@ enum : int {
     kStatusWithin640 = 28,       // ... a 640th,
     kStatusWithin2048 = 29,      // ... a 2 048th
     kStatusReach = 30,           // k_records_and_check: how far below an operator's first output its inputs lie at most
+    kStatusSoon = 31,            // sampled operators whose first input was written just before (kSoonTensors)
 };
 // An edge list and where its adjacency goes.  idx / row == NULL: those are in place already.
 struct EdgeList {
@@ -388,6 +389,32 @@ inline int64_t ring_words(int waves, int dist, int span64)
 // ev (or NULL): ev[0] is recorded behind the sweep; with `all`, ev[1] behind the per-graph counts and ev[2] behind the list
 hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, int *launches, hipStream_t s,
                              hipEvent_t *ev, bool all);
+// The same for one graph of wide layers (see band_sweep.hip): a workgroup per sixteen sets.  The plan clears M and K.
+constexpr int64_t kBandMaxOps = (int64_t)1 << 20;
+constexpr int kBandMaxLow = 8192;         // graph inputs, at most
+constexpr int kBandMaxSteps = 4096;
+constexpr int kBandStepOps = 512, kBandStepOuts = 1024;
+constexpr int64_t kBandMaxTargets = 2048; // that the sweep puts in place itself; more go by way of M and the seed kernel
+constexpr int kBandRegions = 7;
+enum : int { kBandTaken = 0, kBandFound = 1, kBandErrors = 4 /* by sixteen sets */ };
+struct BandArgs {
+    GraphView g;
+    int32_t num_sets;
+    int64_t num_targets;
+    const int32_t *tgt_rowptr, *tgt_idx;
+    u64 *M, *K;
+    TravState *state;        // its error bits
+    int32_t *host_status;    // pinned host memory: 1 + steps or 0 (the graph is not of this kind: nothing written), header found, error bits
+    RecycleHeader *hdr, want;
+    int32_t recycle;
+    FillRegion clear[kBandRegions];
+    uint32_t *entry;         // [P][3]
+    int2 *steps;             // per segment: first operator and tensor of its steps, the highest first
+    int4 *segs;              // steps, how far back its operators read, most outputs in a step, not a 0 if unfit
+};
+size_t band_scratch(BandArgs &a, void *mem);        // lays out the last three (NULL: the bytes alone); g is set
+hipError_t launch_band_plan(const BandArgs &a, int num_cus, hipStream_t s);
+hipError_t launch_band_sweep(const BandArgs &a, bool from_m, hipStream_t s);
 // One sweep over all operators re-deriving K and pushing new bits to the inputs; *changed |= 1 if any.
 hipError_t launch_fix_sweep(const GraphView &g, u64 *M, u64 *K, uint8_t *flags, int32_t *changed, int grid_blocks, hipStream_t s);
 

@@ -424,24 +424,27 @@ __device__ __forceinline__ void write_record(int4 *p, int32_t ib, int32_t ie, in
 
 // How far back do operators read?  Sampled (the first input of a few thousand operators, spread over the graph) for the
 // traversal's schedule and the choice between it and the sweep.  has: this lane's operator has an input, its first is `t`; o is
-// its number among its graph's num_ops operators, whose num_outputs outputs are numbered in creation order from t_first on.
+// its number among its graph's num_ops operators, whose num_outputs outputs are numbered in creation order from t_first on, own the
+// first that it writes.
+constexpr int kSoonTensors = 8;
 __device__ __forceinline__ void sample_reach(bool has, int64_t o, int32_t t, int64_t num_ops, int32_t t_first, int64_t num_outputs,
-                                             int32_t *status)
+                                             int32_t own, int32_t *status)
 {
     has = has && t >= t_first;                              // (graph inputs have no producer)
     const float back = (float)o / (float)num_ops - (float)(t - t_first) / (float)num_outputs;
     const u64 seen = ballot64(has);
-    auto within = [&](float part, int word) {
-        const u64 m = ballot64(has && back < part);
+    auto count = [&](bool is, int word) {
+        const u64 m = ballot64(has && is);
         if (lane_id() == 0 && m) atomicAdd(&status[word], __popcll(m));
     };
     if (seen == 0) return;
     if (lane_id() == 0) atomicAdd(&status[kStatusSampled], __popcll(seen));
-    within(1.0f / 8, kStatusWithin8);
-    within(1.0f / 32, kStatusWithin32);
-    within(1.0f / 192, kStatusWithin192);
-    within(1.0f / 640, kStatusWithin640);
-    within(1.0f / 2048, kStatusWithin2048);
+    count(back < 1.0f / 8, kStatusWithin8);
+    count(back < 1.0f / 32, kStatusWithin32);
+    count(back < 1.0f / 192, kStatusWithin192);
+    count(back < 1.0f / 640, kStatusWithin640);
+    count(back < 1.0f / 2048, kStatusWithin2048);
+    count(own - t <= kSoonTensors, kStatusSoon);
 }
 constexpr int kSampleWaves = 32;         // (updates of one address take 11 ns each)
 
@@ -458,7 +461,8 @@ __global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, 
         const int64_t o = (int64_t)((double)g.num_ops * blockIdx.x / min((int)gridDim.x, kSampleWaves)) + threadIdx.x;
         const bool in_range = o < g.num_ops;
         const int32_t ib = in_range ? g.in_rowptr[o] : 0, ie = in_range ? g.in_rowptr[o + 1] : 0;
-        sample_reach(ie > ib, o, ie > ib ? g.in_idx[ib] : 0, g.num_ops, shift, g.nnz_out, status);
+        sample_reach(ie > ib, o, ie > ib ? g.in_idx[ib] : 0, g.num_ops, shift, g.nnz_out,
+                     (in_range ? g.out_rowptr[o] : 0) + shift, status);
     }
     for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < g.num_ops; o += gsize) {
         const int32_t ib = g.in_rowptr[o], ie = g.in_rowptr[o + 1];
@@ -574,7 +578,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
             for (int j = 0; j < 2; ++j) u[j] = g.out_idx[min(ob + j, none_out)];
         }
         if (samples && o - lane_id() == begin)
-            sample_reach(ie > ib, o - o_lo, t[0], o_hi - o_lo, t_first, hi - t_first, status);
+            sample_reach(ie > ib, o - o_lo, t[0], o_hi - o_lo, t_first, hi - t_first, ob + shift, status);
         auto input = [&](int32_t x) {
             if (x < lo || x >= hi) bad = true;
             if (x >= t_first) {

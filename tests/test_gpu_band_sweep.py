@@ -1,0 +1,141 @@
+"""GPU parity of the sweep by layers: steps at their limits (operators, outputs), segments of the plan with a few operators left
+over, operators with more outputs and inputs than an entry holds, tensors at the ring's edge, parts of 16 sets, and the graphs
+that it must leave to the traversal."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+from test_gpu_parity import assert_same, oracle_prune
+from test_gpu_ring_sweep import draw_targets
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dgn():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_1707_08265_amd as d
+    return d
+
+
+def in_layers(rng, widths, back, out_lo, out_hi, in_max, num_inputs):
+    """Operators of layer l read from layers l - back .. l - 1 and the graph's inputs; outputs numbered in order."""
+    widths = np.asarray(widths)
+    P, start = int(widths.sum()), np.concatenate([[0], np.cumsum(widths)])
+    layer = np.repeat(np.arange(widths.size), widths)
+    n_out = rng.integers(out_lo, out_hi + 1, P)
+    first = num_inputs + np.concatenate([[0], np.cumsum(n_out)])
+    fan = np.where(rng.random(P) < 0.02, in_max, rng.integers(0, 4, P))
+    op = np.repeat(np.arange(P), fan)
+    lo = first[start[np.maximum(layer[op] - np.where(rng.random(op.size) < 0.8, 1, back), 0)]]
+    hi = first[start[layer[op]]]
+    t = np.where((rng.random(op.size) < 0.05) | (hi <= lo), rng.integers(0, num_inputs, op.size),
+                 lo + (rng.random(op.size) * np.maximum(hi - lo, 1)).astype(np.int64))
+    i32 = lambda x: x.astype(np.int32)  # noqa: E731
+    return gg.Graph(P, int(first[-1]), i32(op), i32(t), i32(np.repeat(np.arange(P), n_out)),
+                    i32(num_inputs + np.arange(int(n_out.sum()))), name="layers")
+
+
+def check(dgn, oracle, g, draws, swept=True, dg=None, buf=None):
+    import torch
+    dg = dg or dgn.DeviceGraph.from_coo(g)
+    for i, tg in enumerate(draws):
+        b = buf or dgn.PruneBuffers(dg, tg.num_sets)
+        for t in (b.tensor_mask, b.op_mask, b.kept_masks, b.per_query_count, b.kept_count, b.op_flag):
+            t.fill_(7)
+        b.scratch.fill_(0xAB)
+        for call in range(2):
+            st = dgn.dgn_stats()
+            assert b.prune(torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda(), stats=st) == 0
+            assert_same(b.to_host(), oracle_prune(oracle, g, tg)[1], f"draw {i} call {call}")
+            assert (st.max_frontier == 0 and st.levels > 0) == swept, (st.levels, st.max_frontier)
+
+
+WIDTHS = {
+    "even": [400] * 60, "step": [512] * 40, "step+1": [513] * 40, "wide": [1700] * 30, "narrow": [41] * 900,
+    "ragged": None, "segment": [2048] * 24, "segment+1": [2048] * 24 + [1],
+}
+
+
+@pytest.mark.parametrize("sets", [1, 16, 17, 64])
+@pytest.mark.parametrize("widths", list(WIDTHS))
+def test_layers(dgn, oracle, widths, sets):
+    rng = np.random.default_rng(len(widths) * 100 + sets)
+    w = WIDTHS[widths] or rng.integers(1, 1200, 60)
+    g = in_layers(rng, w, 4, 1, 2, 3, 50)
+    check(dgn, oracle, g, [draw_targets(rng, g, sets, 5)])
+
+
+@pytest.mark.parametrize("out_lo,out_hi,in_max", [(0, 2, 4), (0, 7, 3), (1, 1, 40), (0, 5, 300), (0, 12, 2)])
+def test_operators_with_many_inputs_and_outputs(dgn, oracle, out_lo, out_hi, in_max):
+    rng = np.random.default_rng(out_hi * 7 + in_max)
+    g = in_layers(rng, rng.integers(200, 700, 50), 3, out_lo, out_hi, in_max, 900)
+    check(dgn, oracle, g, [draw_targets(rng, g, q, 9) for q in (3, 40)])
+
+
+@pytest.mark.parametrize("low,reads,swept", [(1, 40_000, True), (8192, 47_000, True), (8193, 1000, False), (5, 49_153, False)])
+def test_how_far_back_and_how_many_graph_inputs(dgn, oracle, low, reads, swept):
+    """500 operators to a layer, one output each; every 1 000th operator reads `reads` tensors back."""
+    rng = np.random.default_rng(low)
+    g = in_layers(rng, [500] * 250, 2, 1, 1, 3, low)
+    e = np.flatnonzero((g.in_op % 1000 == 7) & (g.in_op > reads + 500) & (np.diff(g.in_op, prepend=-1) > 0))
+    g.in_tensor[e] = low + g.in_op[e] - reads
+    check(dgn, oracle, g, [draw_targets(rng, g, 20, 4)], swept)
+
+
+def test_targets_at_the_ends_and_none(dgn, oracle):
+    rng = np.random.default_rng(5)
+    g = in_layers(rng, [300] * 70, 3, 1, 2, 3, 20)
+    T = g.num_tensors
+    from helpers import targets_from_sets
+    draws = [targets_from_sets(s, 3) for s in ([[T - 1], [0], [T - 1, T - 1, 20]], [[], [], []], [[3], [19], []], [[T // 2], [T // 2 + 1], [40]])]
+    check(dgn, oracle, g, draws)
+    many = gg.targets_range(3, 64, 900, 1000, 0, T)                      # 60 000 targets: in every step
+    check(dgn, oracle, g, [many])
+
+
+def test_bad_targets_and_other_buffers_contents(dgn, oracle):
+    """A target out of range is an error, and the next call is right; traversal, sweep and an incremental call in the same buffers."""
+    import torch
+    rng = np.random.default_rng(6)
+    g = in_layers(rng, [350] * 80, 3, 1, 2, 3, 20)
+    dg = dgn.DeviceGraph.from_coo(g)
+    tg = draw_targets(rng, g, 30, 4)
+    ref = oracle_prune(oracle, g, tg)[1]
+    buf = dgn.PruneBuffers(dg, 30)
+    ptr, idx = torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda()
+    bad = idx.clone()
+    bad[0] = g.num_tensors
+    seen = []
+    for knobs, targets in (({}, idx), ({}, idx), ({}, idx), ({}, bad), ({}, idx), ({"traversal": 2}, idx), ({"traversal": 2}, idx), ({}, idx), ({}, idx),
+                           ({"traversal": 1}, idx)):
+        st = dgn.dgn_stats()
+        rc = buf.prune(ptr, targets, options=dgn.dgn_options(recycle=1, **knobs), stats=st)
+        assert rc == (dgn.DGN_ERR_ID_OUT_OF_RANGE if targets is bad else 0)
+        seen.append(int(st.recycled))
+        if rc == 0:
+            assert_same(buf.to_host(), ref, str(knobs))
+    # (the buffers' first call leaves nothing to recognise, nor does an error or the other way's result)
+    assert seen == [0, 0, 1, 1, 0, 0, 1, 0, 1, 0], seen
+
+
+@pytest.mark.parametrize("make", [lambda: gg.rnn(300, 80, 5), lambda: gg.powerlaw(60_000, 5), lambda: gg.layered(40_000, 5)])
+def test_chains_and_reads_from_all_over_are_traversed(dgn, oracle, make):
+    import torch
+    g = make()
+    tg = draw_targets(np.random.default_rng(3), g, 5, 2)
+    buf = dgn.PruneBuffers(dgn.DeviceGraph.from_coo(g), 5)
+    st = dgn.dgn_stats()
+    assert buf.prune(torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda(), stats=st) == 0
+    assert_same(buf.to_host(), oracle_prune(oracle, g, tg)[1], "traversed")
+    assert st.max_frontier > 0
+
+
+def test_layers_in_which_operators_read_each_other(dgn, oracle):
+    """It looks like layers where it is sampled, but most operators read the one before: left to the traversal, now and later."""
+    rng = np.random.default_rng(8)
+    g = in_layers(rng, [400] * 60, 3, 1, 1, 3, 20)
+    e = np.flatnonzero((np.diff(g.in_op, append=-1) != 0) & (np.diff(g.in_op, prepend=-1) == 0))      # last of several inputs
+    g.in_tensor[e] = 20 + g.in_op[e] - 1
+    check(dgn, oracle, g, [draw_targets(rng, g, 8, 3)], swept=False)
