@@ -16,8 +16,8 @@
 // a barrier is all that separates two of them.  The removal rule's count and list passes follow as behind the traversal.
 //
 // What bounds it: the instructions of a step, 0.3 us for 400 operators and 0.22 for 40, one wave's after the other's: LDS round trips
-// 0.12, the flush to memory 0.07.  500 layers of 400 operators, 64 sets, 525 steps: plan 20 us, sweep 160, count and list 22, whole
-// prune 370 -> 216; 300 of 800 412 -> 249; 200 of 90 170 -> 119.  On the way: target bits read back from M a step at a time 218, looked
+// 0.12, the flush to memory 0.07.  500 layers of 400 operators, 64 sets, 525 steps: plan 20 us, sweep 160, count and list 18, whole
+// prune 370 -> 215; 300 of 800 412 -> 249; 200 of 90 170 -> 119.  On the way: target bits read back from M a step at a time 218, looked
 // for among the held ones in every step 225 (now a scalar compare), addresses by the vector unit instead of buffer offsets 219.
 //
 // What a graph must satisfy the plan finds out on the device: outputs numbered as they are created, in one run up to the last
