@@ -150,7 +150,8 @@ enum {
 /* Schedule-dependent counters (not part of the result; excluded from parity). HOST struct. */
 typedef struct dgn_stats {
     int64_t levels;          /* frontier levels processed.  Graphs that one workgroup each sweeps have none (small ones, and
-                                packed batches of small ones): settling steps for fewer than 64 graphs, else 0   */
+                                packed batches of small ones): settling steps for fewer than 64 graphs, else 0; a
+                                graph that is swept by layers: the steps it was cut into                    */
     int64_t tensor_visits;   /* frontier entries and deferred operators expanded, summed over levels */
     int64_t max_frontier;    /* largest frontier; 0 for graphs that are swept                         */
     int64_t launches;        /* kernels enqueued by the call                                     */
@@ -163,7 +164,8 @@ typedef struct dgn_stats {
     int64_t level_trace_cap; /* IN: capacity of level_trace in levels                                     */
     int64_t reserved;        /* dgn_backward_prune: passes of its forward stage; 0 otherwise                */
     int64_t recycled;        /* 1 when options->recycle found the previous result in place and the call
-                                zeroed only what that result had set                               */
+                                zeroed only what that result had set (a graph that is swept by layers: found
+                                it in place; there everything is cleared, which costs no more)     */
     int64_t atomic_updates;  /* 64-bit atomic ORs the traversal issued (one per input edge of an operator that
                                 gained bits, plus the seeds); 0 for graphs that are swept                */
     float phase_ms[DGN_NUM_PHASES];   /* filled when options->profile is 1 (all) or 2 (traversal); zero otherwise */
