@@ -62,7 +62,9 @@ constexpr int kRingLongLevel = 256;                    // more than a level per 
 // (graphs of a larger batch: kRingMaxGraphOps)
 // When such a graph is swept in segments, and how long they are (see ring_segments):
 constexpr double kRingWordUs = 0.9, kRingSegmentsUs = 6.5, kRingSegmentOpUs = 2.5e-5;
-constexpr int kRingFewWords = 16, kRingManySegs = 64, kRingSegmentsPerCu = 24;
+constexpr double kRingManyWordUs = 0.71, kRingManySegWordUs = 1.06, kRingManyUs = 2.0, kRingManyOpUs = 0.9e-5, kRingManyTargetUs = 0.007;
+constexpr double kRingFromMUs = 15.0, kRingFromMTargetUs = 0.0028;
+constexpr int kRingFewWords = 16, kRingManySegs = 64, kRingSegmentsPerCu = 24, kRingFewSegmentsPerCu = 2;
 // Which single graphs are swept by layers (see band_sweep.hip), of those that the ring sweep leaves: they read the last eighth of the
 // graph mostly, and no more than one operator in 25 what was written just before (layers of 40: one in 100, chains with a window of
 // 64: one in 10).  Whole prunes, level by level / swept, 64 sets of up to 8: 24 layers of 700 161 / 82 us, 60 x 300 173 / 86, 200 x 90
@@ -786,11 +788,19 @@ static int ring_waves(const dgn_graph *g, const dgn_options *o, const dgn_stats 
 //   Two words of 64 operators per segment up to 1 024 operators, four beyond (2 000: 34.5 us, eight 37; 800: two 35.4, four 37.1); not
 // more than 64 segments (20 000: 52.4 us with 79, 50 with 40), nor than 24 waves of sweeps per compute unit (250 graphs of 20 000: 8 words per
 // segment 271 us, 16 248, 32 230); and what has room.
+//   Every segment looks at all targets of its graph.  With up to two workgroups per compute unit (one, if the targets go by way of
+// M) eight waves each do (2 000 operators: 8 192 targets 66 us in one piece / 49, one wave 91; 64 000 112 / 96, 411; 40 graphs of 800 with
+// 4 096 each 73 / 69, 78), else the one that sweeps: more of them are in each other's way (250 graphs of 5 000, 256 targets each: 148 /
+// 91, eight 118).  What is gained then was fitted to 250 batches of 8 to 600 graphs, with 2 us in its favour: the chain without that
+// of a segment, less the operators and the targets (250 graphs of 1 000, which have room for two segments each, 1 024 targets: 59 /
+// 66).  More than kRingSeedWords targets go by way of M, which is slow in one piece as well (250 graphs of 1 000, 4 096 each: 161 / 105; 96
+// of 3 000: 16 384 188 / 188, 25 600 219 / 293).
 static int ring_segments(const dgn_graph *g, int64_t words, char *mem, size_t room, RingArgs &a)
 {
     if (g->ring_reach > kWave) return 1;
     const int64_t n_words = (g->max_graph_ops + kWave - 1) / kWave, all_words = (g->P / kWave + 1) * (words + 1);
-    if ((double)n_words * kRingWordUs < kRingSegmentsUs + (double)g->P * (double)(words + 1) * kRingSegmentOpUs) return 1;
+    const double swept = (double)g->P * (double)(words + 1);
+    if ((double)n_words * kRingWordUs < kRingSegmentsUs + swept * kRingSegmentOpUs) return 1;
     int shift = n_words <= kRingFewWords ? 1 : 2;
     while ((n_words >> shift) > kRingManySegs || (all_words >> shift) > kRingSegmentsPerCu * g->num_cus) ++shift;
     for (;; ++shift) {
@@ -801,6 +811,13 @@ static int ring_segments(const dgn_graph *g, int64_t words, char *mem, size_t ro
         a.segs = (int32_t)segs;
         if (ring_segment_scratch(a, nullptr) <= room) break;
     }
+    const int64_t targets = a.num_targets / (g->G * words);  // (of an average graph or word)
+    const bool from_m = targets > kRingSeedWords;
+    a.few_segs = (int64_t)g->G * a.segs * (words + 1) <= (int64_t)(from_m ? 1 : kRingFewSegmentsPerCu) * g->num_cus;
+    const double targets_us = from_m ? (double)targets * kRingFromMTargetUs - kRingFromMUs : (double)targets * kRingManyTargetUs;
+    if (!a.few_segs && (double)n_words * kRingManyWordUs + kRingManyUs <
+                           (double)a.seg_words * kRingManySegWordUs + swept * kRingManyOpUs + targets_us)
+        return 1;
     (void)ring_segment_scratch(a, mem);
     return a.segs;
 }

@@ -362,6 +362,7 @@ struct RingArgs {
     int32_t ring_words, low_words, seed_words;     // LDS: ring, graph inputs (8 bytes each), targets (4 bytes each)
     // graphs swept in segments (segs > 1): each of them seg_words = 1 << seg_shift words of 64 operators
     int32_t segs, seg_words, seg_shift;
+    int32_t few_segs;        // so few that each has kRingPlaceWaves waves to put its targets in place
     int32_t count_steps;     // somebody wants to know the settling steps
     int32_t reach;           // no operator reads a tensor further below its first output (at most kWave)
     u64 *b_M, *b_K;          // [T], [P]: which tensors of the boundary above its segment a tensor or operator is reached from
@@ -372,7 +373,7 @@ struct RingArgs {
 };
 constexpr int kRingExtraWords = 1 + kWave;
 __host__ __device__ inline int64_t ring_edge_words(const RingArgs &a) { return kWave + a.low_words + 1; }
-constexpr int kRingSegWaves = 1;
+constexpr int kRingSegWaves = 1, kRingPlaceWaves = 8;
 constexpr int kRingMaxSegs = 1024, kRingMaxSegWords = 256;
 // Lays out what segments leave for each other at `mem` (NULL: the bytes alone); g, words, segs and low_words are set
 size_t ring_segment_scratch(RingArgs &a, void *mem);

@@ -25,9 +25,9 @@
 // on a graph of 20 000 operators, one word after the other before: 0.84 ms -> 0.30.
 //
 // Segments.  Where no operator reads further back than 64 tensors, a graph is cut into segments of a few words that are swept
-// at the same time, a wave each.  What a segment lacks is M of the 64 tensors at its upper boundary, and everything in it is
-// an OR of what its own targets give and of some of those 64: so it is swept twice, once with the targets that lie in it, once
-// with the 64 tensors as 64 sets, whose masks then say which of them reach what.  k_ring_join works out M of the boundaries
+// at the same time, a wave each (eight, or one, put its targets in place before).  What a segment lacks is M of the 64 tensors at
+// its upper boundary, and everything in it is an OR of what its own targets give and of some of those 64: so it is swept twice, once
+// with the targets that lie in it, once with the 64 tensors as 64 sets, whose masks then say which of them reach what.  k_ring_join works out M of the boundaries
 // from the top down and adds what they bring; in a batch k_ring_carry has done so before, per graph, and counted.
 // Which graphs, how long and what it measured: ring_segments in api.hip.
 //
@@ -122,6 +122,12 @@ __device__ __forceinline__ void ring_targets(const GraphView &g, RingRow &r)
     for (int j = 0; j < 4; ++j) r.t[j] = at_byte(g.in_idx, (uint32_t)min(r.ib + j, g.nnz_in - 1) * 4u);
 }
 
+__device__ __forceinline__ void wave_fence()                 // LDS accesses of a wave complete in order: for the compiler alone
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // A zero that the compiler takes for a value of its own in every lane: added to an address that is the same in all lanes,
 // it keeps the load's result in a vector register until it is used (moved to a scalar one at once, as it would be, the
 // wave would wait for the load where it is issued).
@@ -150,16 +156,20 @@ __device__ __forceinline__ void ring_finish(const RingArgs &a, int4 st)
     a.host_status[2] = st.w;
 }
 
-template <int W, bool kSeg>
-__global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
+// W waves sweep.  H = 0: whole graphs; else a segment of one (W = 1), whose targets H waves put in place before.
+template <int W, int H>
+__global__ __launch_bounds__((H > W ? H : W) * kWave) void k_ring_sweep(RingArgs a)
 {
-    constexpr int N = W * kWave;
+    constexpr bool kSeg = H > 0;
+    static_assert(!kSeg || W == 1, "a wave per segment");
+    constexpr int N = W * kWave, kPlace = (H > W ? H : W) * kWave;         // threads that sweep, and that put the targets in place
     // [R] ring, [low] graph inputs, [1] a word that stays zero, [64] words that take what goes nowhere; targets; with the
     // list made here: running counts per word
     extern __shared__ u64 ring[];
     __shared__ int s_flag[3];                       // "a push crossed waves", by round
     __shared__ int s_total[W];                      // kept operators of each wave's word
     __shared__ int s_err, s_relax;
+    __shared__ int s_lowest, s_own;                 // segments: the lowest target and how many
     __shared__ int32_t s_row[kWave + 1];            // the graph's target row pointers
     const GraphView &g = a.g;
     const int lane = lane_id(), wave = W > 1 ? (int)(threadIdx.x >> 6) : 0, tid = threadIdx.x;
@@ -212,48 +222,104 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
         ring_bounds(in_row, out_row, nxt, (word - W) * kWave + lane, n);
         if (W > 1) z_next = at_byte(out_row, group_first(0) * 4u + vz);
     };
-    if (W > 1 || kSeg) first_bounds();
-    for (int i = tid; i <= R + a.low_words; i += N) ring[i] = 0;
+    if (W > 1 || (kSeg && tid < N)) first_bounds();
+    for (int i = tid; i <= R + a.low_words; i += kPlace) ring[i] = 0;
     if (tid < 3) s_flag[tid] = 0;
-    if (tid == 0) s_err = s_relax = 0;
+    if (tid == 0) s_err = s_relax = s_own = 0;
+    if (tid == 0) s_lowest = 0x7fffffff;
 
     // the graph's targets, packed: tensor relative to t_lo in the upper 26 bits, set in the lower 6
     if (!boundary)
-        for (int q = tid; q <= num_sets; q += N) s_row[q] = a.tgt_rowptr[set0 + q];
+        for (int q = tid; q <= num_sets; q += kPlace) s_row[q] = a.tgt_rowptr[set0 + q];
     __syncthreads();
     const int64_t j0 = boundary ? 0 : max(s_row[0], 0), j1 = boundary ? 0 : min((int64_t)s_row[num_sets], a.num_targets);
     const bool from_m = j1 - j0 > a.seed_words || t_end - t_lo >= (1 << 26);         // too many: by way of M itself
     if (from_m) {
         if (kSeg && seg == 0)
-            for (int64_t t = tid; t < t_first - t_lo; t += N) store_coherent(&M[t], (u64)0);
-        for (int64_t t = (kSeg ? t_mine - t_lo : 0) + tid; t < t_hi - t_lo; t += N) store_coherent(&M[t], (u64)0);
+            for (int64_t t = tid; t < t_first - t_lo; t += kPlace) store_coherent(&M[t], (u64)0);
+        for (int64_t t = (kSeg ? t_mine - t_lo : 0) + tid; t < t_hi - t_lo; t += kPlace) store_coherent(&M[t], (u64)0);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     }
     __syncthreads();
     int err = 0, lowest = 0x7fffffff;               // lowest: smallest target of this thread, relative to t_lo
-    for (int64_t j = j0 + tid; j < j1; j += N) {
-        uint32_t packed = 0xffffffffu;
-        int lo = 0, hi = num_sets;                  // last set whose row starts at or before j
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (s_row[mid] <= j) lo = mid; else hi = mid;
+    if constexpr (kSeg) {
+        // Every segment looks at all of its graph's targets and keeps its own.  Its one wave takes 0.35 us for 64 of them (0.8 with a
+        // branch for every one), so that where few workgroups run there are more waves for this than for the sweep.  Rows of 64
+        // four at a time, their loads and searches side by side and without branches.
+        auto look = [&](auto rows, int64_t first_j) {
+            constexpr int kRows = decltype(rows)::value;
+            int32_t t[kRows], j[kRows], lo[kRows];
+#pragma unroll
+            for (int c = 0; c < kRows; ++c) {
+                j[c] = (int32_t)min(first_j + c * kWave + lane, j1 - 1);
+                t[c] = a.tgt_idx[j[c]];
+                lo[c] = 0;
+            }
+#pragma unroll
+            for (int half = kWave / 2; half > 0; half >>= 1) {
+                if (half >= num_sets) continue;              // uniform
+                int32_t row[kRows];
+#pragma unroll
+                for (int c = 0; c < kRows; ++c) row[c] = s_row[min(lo[c] + half, num_sets)];
+#pragma unroll
+                for (int c = 0; c < kRows; ++c) lo[c] += lo[c] + half < num_sets && row[c] <= j[c] ? half : 0;
+            }
+            int32_t begin[kRows], end[kRows];
+#pragma unroll
+            for (int c = 0; c < kRows; ++c) {
+                begin[c] = s_row[lo[c]];
+                end[c] = s_row[lo[c] + 1];
+            }
+#pragma unroll
+            for (int c = 0; c < kRows; ++c) {
+                const bool is = first_j + c * kWave + lane < j1 && begin[c] <= j[c] && j[c] < end[c];      // (else it belongs to no set)
+                const bool inside = t[c] >= t_lo && t[c] < t_end;
+                if (is && !inside) err |= t[c] < 0 || t[c] >= g.num_tensors ? kErrIdRange : kErrCrossGraph;
+                const bool low = is && inside && t[c] < t_first && seg == 0, mine = is && t[c] >= t_mine && t[c] < t_hi;
+                if (from_m) {
+                    if (low || mine) (void)atomicOr(&all_M[t[c]], (u64)1 << lo[c]);
+                    continue;
+                }
+                if (low) lds_or(low_of(t[c]), (u64)1 << lo[c]);
+                const u64 which = ballot64(mine);
+                if (which == 0) continue;
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&s_own, __popcll(which));
+                at = __builtin_amdgcn_readfirstlane(at) + __popcll(which & lanemask_lt());
+                if (mine) {
+                    lowest = min(lowest, t[c] - t_lo);
+                    seeds[at] = ((uint32_t)(t[c] - t_lo) << 6) | (uint32_t)lo[c];
+                }
+            }
+        };
+        constexpr int kRows = 4;
+        for (int64_t first_j = j0 + (tid & ~(kWave - 1)) * kRows; first_j < j1; first_j += kRows * kPlace) {
+            if (j1 - first_j <= kWave) look(std::integral_constant<int, 1>{}, first_j);
+            else look(std::integral_constant<int, kRows>{}, first_j);
         }
-        const int32_t t = a.tgt_idx[j];
-        if (!(s_row[lo] <= j && j < s_row[lo + 1])) {
-            // (an entry that belongs to no set)
-        } else if (t < t_lo || t >= t_end) {
-            err |= t < 0 || t >= g.num_tensors ? kErrIdRange : kErrCrossGraph;
-        } else if (kSeg && (t < t_first ? seg > 0 : t < t_mine || t >= t_hi)) {
-            // (another segment's)
-        } else if (from_m) {
-            (void)atomicOr(&all_M[t], (u64)1 << lo);
-        } else if (t < t_first) {
-            lds_or(low_of(t), (u64)1 << lo);
-        } else {
-            lowest = min(lowest, t - t_lo);
-            packed = ((uint32_t)(t - t_lo) << 6) | (uint32_t)lo;
+    } else {
+        for (int64_t j = j0 + tid; j < j1; j += N) {
+            uint32_t packed = 0xffffffffu;
+            int lo = 0, hi = num_sets;                  // last set whose row starts at or before j
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (s_row[mid] <= j) lo = mid; else hi = mid;
+            }
+            const int32_t t = a.tgt_idx[j];
+            if (!(s_row[lo] <= j && j < s_row[lo + 1])) {
+                // (an entry that belongs to no set)
+            } else if (t < t_lo || t >= t_end) {
+                err |= t < 0 || t >= g.num_tensors ? kErrIdRange : kErrCrossGraph;
+            } else if (from_m) {
+                (void)atomicOr(&all_M[t], (u64)1 << lo);
+            } else if (t < t_first) {
+                lds_or(low_of(t), (u64)1 << lo);
+            } else {
+                lowest = min(lowest, t - t_lo);
+                packed = ((uint32_t)(t - t_lo) << 6) | (uint32_t)lo;
+            }
+            if (!from_m) seeds[j - j0] = packed;
         }
-        if (!from_m) seeds[j - j0] = packed;
     }
     if (boundary && tid < a.reach && t_hi - a.reach + tid >= t_first) {           // bit i: the i-th tensor of the boundary above
         lowest = t_hi - a.reach + tid - t_lo;
@@ -261,12 +327,20 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
     } else if (boundary && tid < a.reach) {
         seeds[tid] = 0xffffffffu;
     }
-    const int n_seeds = kSeg && boundary ? a.reach : from_m || j1 < j0 ? 0 : (int)(j1 - j0);
     if (err) atomicOr(&s_err, err);
     lowest = -wave_max(-lowest);
-    const int32_t lowest_seed = from_m ? -1 : lowest == 0x7fffffff ? lowest : t_lo + lowest;     // (none: beyond every tensor)
+    if (kSeg && lane == 0) atomicMin(&s_lowest, lowest);
     if (from_m) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
+    if (kSeg) {
+        if (tid >= N) return;                                // (what follows is one wave's)
+        lowest = s_lowest;
+    }
+    const int32_t lowest_seed = from_m ? -1 : lowest == 0x7fffffff ? lowest : t_lo + lowest;     // (none: beyond every tensor)
+    const int n_seeds = kSeg ? (boundary ? a.reach : s_own) : from_m || j1 < j0 ? 0 : (int)(j1 - j0);
+    auto sync = [&]() {
+        if constexpr (kSeg) wave_fence(); else __syncthreads();
+    };
     if (from_m && seg == 0)
         for (int32_t t = t_lo + tid; t < t_first; t += N) lds_write(low_of(t), load_coherent(&all_M[t]));
     // target bits of the tensors [from, to), which the ring has come to cover.  A thread looks at the targets that it put
@@ -288,7 +362,7 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
     };
     cover(t_hi - R, t_hi);
     int32_t cov_lo = t_hi - R, cov_hi = cov_lo;              // tensors [cov_lo, cov_hi): their target bits are still to come
-    __syncthreads();
+    sync();
 
     RingCount cnt;
 #pragma unroll
@@ -388,7 +462,7 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
             const int fl = round % 3;
             if (tid == 0) s_flag[(round + 1) % 3] = 0;
             if (ballot64(crossed) != 0 && lane == 0) s_flag[fl] = 1;
-            __syncthreads();
+            sync();
             ++round;
             if (s_flag[fl] == 0) break;                      // the same in every thread
         }
@@ -436,13 +510,13 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
         const int c = __popcll(bit_word);
         int upto = c, all = c;
         if (kSeg) {
-            __syncthreads();
+            sync();
             if (lane == 0 && word >= 0 && !boundary) at_byte(bits, (uint32_t)word * 8u) = bit_word;
             continue;
         }
         if (W > 1) {
             if (lane == 0) s_total[wave] = c;
-            __syncthreads();
+            sync();
             upto = all = 0;
 #pragma unroll
             for (int w = 0; w < W; ++w) {
@@ -459,7 +533,7 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
         done += all;
         __builtin_amdgcn_wave_barrier();
     }
-    __syncthreads();
+    sync();
     if (kSeg) {
         // what k_ring_join needs: the bits that the segment below receives, the graph's inputs (a segment's part of them; the
         // lowest one's goes to M, where the others' are added), and the settling steps
@@ -493,7 +567,7 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
                 total += (u64)__popcll(wave_transpose64(cnt.plane[p])) << p;
         if (W > 1) {                                         // (the ring is free now; it has at least N words)
             ring[tid] = total;
-            __syncthreads();
+            sync();
             total = 0;
             if (wave == 0)
                 for (int w = 0; w < W; ++w) total += ring[w * kWave + lane];
@@ -501,7 +575,7 @@ __global__ __launch_bounds__(W * kWave) void k_ring_sweep(RingArgs a)
         if (wave == 0) a.pq[(int64_t)blockIdx.x * 64 + lane] = (int64_t)total;
     }
     if (lane == 0) atomicAdd(&s_relax, relax);
-    __syncthreads();
+    sync();
     if (tid == 0) {
         const int4 st = make_int4(done, s_err, s_relax, found ? 1 : 0);
         a.graphs[blockIdx.x] = st;
@@ -633,12 +707,6 @@ __global__ __launch_bounds__(kRingScatterThreads) void k_ring_scatter(RingArgs a
 // and lanes that want the same one share the read; entry v of table n sits at v ^ (n mod 4), which spreads the writes as well.
 struct alignas(16) RingPair { u64 m, through; };
 constexpr int kPairTable = 16 * 16;
-
-__device__ __forceinline__ void wave_fence()                 // LDS accesses of a wave complete in order: for the compiler alone
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 __device__ __forceinline__ u64 word_or(u64 a, u64 b) { return a | b; }
 __device__ __forceinline__ RingPair word_or(const RingPair &a, const RingPair &b) { return {a.m | b.m, a.through | b.through}; }
@@ -1020,16 +1088,17 @@ size_t ring_segment_scratch(RingArgs &a, void *mem)
     return off;
 }
 
-template <int W, bool kSeg> static hipError_t launch_ring_w(const RingArgs &a, size_t lds, hipStream_t s)
+template <int W, int H> static hipError_t launch_ring_w(const RingArgs &a, size_t lds, hipStream_t s)
 {
+    constexpr bool kSeg = H > 0;
     if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ring_sweep<W, kSeg>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ring_sweep<W, H>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingMaxLds);
         if (e != hipSuccess) return e;
     }
     const unsigned rows = (unsigned)(a.g.num_graphs > 1 ? a.g.num_graphs : a.words);
     const dim3 grid = kSeg ? dim3((unsigned)a.g.num_graphs, (unsigned)a.segs, (unsigned)a.words + 1) : dim3(rows);
-    hipLaunchKernelGGL((k_ring_sweep<W, kSeg>), grid, dim3(W * kWave), lds, s, a);
+    hipLaunchKernelGGL((k_ring_sweep<W, H>), grid, dim3((H > W ? H : W) * kWave), lds, s, a);
     return hipGetLastError();
 }
 
@@ -1045,8 +1114,8 @@ hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_
     // (a wave of the sweep takes four words in 1.2 us, the launch of a pass of its own costs 6: up to about 20 words per wave)
     a.list_here = a.segs <= 1 && G == 1 && a.words == 1 && waves > 1 && max_graph_ops <= kRingListOps && lds + (size_t)words * sizeof(int) <= kRingMaxLds;
     if (a.list_here) lds += (size_t)words * sizeof(int);
-    hipError_t e = a.segs > 1 ? launch_ring_w<kRingSegWaves, true>(a, lds, s) : waves == 1 ? launch_ring_w<1, false>(a, lds, s)
-                 : waves == 4 ? launch_ring_w<4, false>(a, lds, s) : launch_ring_w<16, false>(a, lds, s);
+    hipError_t e = a.segs > 1 ? (a.few_segs ? launch_ring_w<kRingSegWaves, kRingPlaceWaves>(a, lds, s) : launch_ring_w<kRingSegWaves, 1>(a, lds, s))
+                 : waves == 1 ? launch_ring_w<1, 0>(a, lds, s) : waves == 4 ? launch_ring_w<4, 0>(a, lds, s) : launch_ring_w<16, 0>(a, lds, s);
     *launches = a.list_here ? 1 : G > 1 ? 3 : 2;
     auto mark = [&](int i) {
         if (e == hipSuccess && ev && (i == 0 || all)) e = hipEventRecord(ev[i], s);

@@ -107,6 +107,52 @@ def test_segments(dgn, oracle, shape, segments, Q, most):
     assert st.launches == (2 if segments or P > 16384 else 1) and st.levels > 0
 
 
+# Targets are looked for in rows of 64, four rows at a time, by one wave of a segment or eight (batches: (260, 2000) is the one wave's);
+# 2 048 fit in LDS, more go through the masks.
+@pytest.mark.parametrize("G,ops", [(1, 460), (1, 5000), (6, 1500), (260, 2000)])
+@pytest.mark.parametrize("targets", [1, 64, 65, 257, 2047, 2048, 2049, 5000])
+def test_segments_and_the_number_of_targets(dgn, oracle, G, ops, targets):
+    """All in one set of each graph, or spread over 64 unevenly with empty ones among them; a bad one among them is an error."""
+    import torch
+    rng = np.random.default_rng(G + ops + targets)
+    g = recorded(rng, G, ops, 64, 2, 3, 16)
+    off = np.array([0, g.num_tensors]) if G == 1 else np.asarray(g.graph_tensor_offsets)
+    for sets in (1, 64):
+        lists = []
+        for lo, hi in zip(off, off[1:]):
+            t = rng.integers(lo, hi, targets)
+            cuts = np.sort(rng.integers(0, targets + 1, sets - 1)) if sets > 1 else []
+            lists += [[int(x) for x in part] for part in np.split(t, cuts)]
+        check(dgn, oracle, g, [targets_from_sets(lists, sets)], G < 64)
+    bad = targets_from_sets(lists, sets)
+    bad.tgt_idx[-1] = g.num_tensors
+    buf = dgn.PruneBuffers(dgn.DeviceGraph.from_coo(g), sets)
+    assert buf.prune(torch.from_numpy(bad.tgt_rowptr).cuda(), torch.from_numpy(bad.tgt_idx).cuda()) == dgn.DGN_ERR_ID_OUT_OF_RANGE
+
+
+@pytest.mark.parametrize("G,ops", [(1, 800), (8, 800)])
+def test_many_targets_cost_no_multiple_of_a_prune(dgn, G, ops):
+    """32 000 targets of a graph against 64, both in segments: a little over twice as long; looked at one after the other by the one
+    wave of each segment they took ten times and more."""
+    import time
+    import torch
+    rng = np.random.default_rng(G)
+    g = recorded(rng, G, ops, 64, 2, 3, 16)
+    off = np.array([0, g.num_tensors]) if G == 1 else np.asarray(g.graph_tensor_offsets)
+    dg, took = dgn.DeviceGraph.from_coo(g), []
+    for per_set in (1, 500):
+        idx = np.concatenate([rng.integers(lo, hi, 64 * per_set) for lo, hi in zip(off, off[1:])]).astype(np.int32)
+        ptr = np.arange(0, 64 * G + 1, dtype=np.int32) * per_set
+        buf, ptr, idx = dgn.PruneBuffers(dg, 64), torch.from_numpy(ptr).cuda(), torch.from_numpy(idx).cuda()
+        best = 1.0
+        for _ in range(20):
+            t = time.perf_counter()
+            assert buf.prune(ptr, idx) == 0
+            best = min(best, time.perf_counter() - t)
+        took.append(best)
+    assert took[1] < 5 * took[0], took
+
+
 @pytest.mark.parametrize("G", [1, 100])
 def test_more_targets_than_fit_in_lds_go_through_the_masks(dgn, oracle, G):
     rng = np.random.default_rng(G)
