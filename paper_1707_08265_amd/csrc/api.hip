@@ -69,10 +69,20 @@ constexpr int kRingFewWords = 16, kRingManySegs = 64, kRingSegmentsPerCu = 24, k
 // graph mostly, and no more than one operator in 25 what was written just before (layers of 40: one in 100, chains with a window of
 // 64: one in 10).  Whole prunes, level by level / swept, 64 sets of up to 8: 24 layers of 700 161 / 82 us, 60 x 300 173 / 86, 200 x 90
 // 170 / 119, 500 x 400 370 / 216, 1 000 x 40 376 / 284, 1 000 x 800 817 / 661; first prunes of them 300 to 800 / 92 to 674.  With a
-// single set of 4: 24 x 700 96 / 68, 100 x 600 156 / 115, 1 000 x 300 408 / 327, but 300 x 800 212 / 235 and 1 000 x 800 535 / 650, so up
-// to four sets on more than 200 000 operators are left to the levels.
+// single set of 4: 24 x 700 96 / 64, 100 x 600 159 / 111, 500 x 400 255 / 209, but 300 x 667 206 / 226, 300 x 800 210 / 232, 500 x 700 267 /
+// 337 and 1 000 x 600 471 / 591, so up to four sets on more than 200 000 operators are left to the levels.  That line is drawn for wide
+// layers: 1 000 narrow ones would gain beyond it as well (1 000 x 210 424 / 291, 1 000 x 300 407 / 324).  At four sets the two ways meet (300 x
+// 667 234 / 227, 500 x 700 332 / 339, 1 000 x 600 567 / 594), from five on the sweep is the faster one or takes the same time (255 / 228,
+// 345 / 340, 586 / 595; eight: 265 / 230, 370 / 340, 617 / 597).
+//   More than kBandMaxTargets targets go by way of M, and a step of the sweep takes half as long again; the levels take no longer than
+// with few.  Up to 50 000 operators and 8 000 for every set the sweep is the faster one or takes the same time (100 x 500 128 / 112; 1 000 x 40
+// 350 / 355; four sets on 100 x 600 150 / 134, eight on 300 x 200 183 / 167, but on 200 x 600 190 / 212 and 450 x 700 304 / 421; five on 1 000 x 600
+// 523 / 787), with sixteen sets and more up to 300 000 (32 sets, 500 x 400 328 / 284, 1 000 x 300 500 / 425; 64 sets 345 / 284, 535 / 425,
+// but 1 000 x 600 680 / 788, 1 000 x 800 822 / 872; sixteen are the limit: 500 x 400 308 / 275, 300 x 667 260 / 300), and with five and more
+// where there are some 700 layers and more (eight sets on 1 000 x 250 449 / 406).
 constexpr int kBandSoonShare = 25;
 constexpr int64_t kBandFewSets = 4, kBandFewSetsOps = 200000;
+constexpr int64_t kBandFromMOps = 50000, kBandFromMSetOps = 8000, kBandFromMManySets = 16, kBandFromMMaxOps = 300000;
 constexpr int kSmallLevel = 16384;           // levels expanding fewer entries than this decay the threshold faster
 constexpr int kDefaultDeferPercent = 74;
 constexpr int kDefaultStartShift = 1;       // deferral threshold starts at P >> 1 ...
@@ -914,6 +924,16 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
     return error_bits_to_code(status[0]);
 }
 
+// The largest graph that is swept by layers, for so many sets and targets (see kBandSoonShare).
+static int64_t band_most_ops(const dgn_graph *g, int64_t sets, int64_t num_targets)
+{
+    if (num_targets > kBandMaxTargets) {
+        const bool many = sets >= kBandFromMManySets || (sets > kBandFewSets && g->reach == Reach::nearer);
+        return many ? kBandFromMMaxOps : kBandFromMOps + sets * kBandFromMSetOps;
+    }
+    return sets <= kBandFewSets ? kBandFewSetsOps : kBandMaxOps;
+}
+
 // dgn_prune of a graph that looks like layers (see band_sweep.hip).  *taken: whether it was one; if not, nothing but a clear has
 // happened.
 static int band_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr, const int32_t *tgt_idx,
@@ -1072,8 +1092,7 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
                           reinterpret_cast<u64 *>(also_M), reinterpret_cast<u64 *>(also_K));
     const bool plain = !(options && (options->traversal != 0 || options->incremental || options->recompute_keep)) &&
                        !(stats && stats->level_trace && stats->level_trace_cap > 0);
-    const bool few = sets <= kBandFewSets && g->P > kBandFewSetsOps;
-    if (g->layers && plain && !few && !g->no_layers.load(std::memory_order_relaxed)) {
+    if (g->layers && plain && g->P <= band_most_ops(g, sets, num_targets) && !g->no_layers.load(std::memory_order_relaxed)) {
         bool taken = false;
         rc = band_prune(g, num_sets, num_targets, tgt_rowptr, tgt_idx, M, K, op_flag, kept_ops, reinterpret_cast<u64 *>(kept_masks),
                         kept_count, per_query_count, S, options, stats, s, reinterpret_cast<u64 *>(also_M),

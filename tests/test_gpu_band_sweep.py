@@ -5,8 +5,9 @@ import numpy as np
 import pytest
 
 import graphgen as gg
+from helpers import targets_from_sets
 from test_gpu_parity import assert_same, oracle_prune
-from test_gpu_ring_sweep import draw_targets
+from test_gpu_ring_sweep import draw_targets, prune_words
 
 pytestmark = pytest.mark.gpu
 
@@ -88,7 +89,6 @@ def test_targets_at_the_ends_and_none(dgn, oracle):
     rng = np.random.default_rng(5)
     g = in_layers(rng, [300] * 70, 3, 1, 2, 3, 20)
     T = g.num_tensors
-    from helpers import targets_from_sets
     draws = [targets_from_sets(s, 3) for s in ([[T - 1], [0], [T - 1, T - 1, 20]], [[], [], []], [[3], [19], []], [[T // 2], [T // 2 + 1], [40]])]
     check(dgn, oracle, g, draws)
     many = gg.targets_range(3, 64, 900, 1000, 0, T)                      # 60 000 targets: in every step
@@ -139,3 +139,26 @@ def test_layers_in_which_operators_read_each_other(dgn, oracle):
     e = np.flatnonzero((np.diff(g.in_op, append=-1) != 0) & (np.diff(g.in_op, prepend=-1) == 0))      # last of several inputs
     g.in_tensor[e] = 20 + g.in_op[e] - 1
     check(dgn, oracle, g, [draw_targets(rng, g, 8, 3)], swept=False)
+
+
+# With more targets than the sweep holds, a step takes half as long again (the measurements stand beside the rule in api.hip): few sets on
+# many operators are left to the levels, and so are the words of a call with so many targets on the largest graphs.
+@pytest.mark.parametrize("layers,width,sets,targets,swept", [
+    (200, 500, 5, 2000, True), (200, 600, 5, 3000, False), (100, 500, 1, 3000, True), (100, 600, 1, 3000, False), (200, 600, 16, 3000, True),
+    (1000, 210, 8, 3000, True), (300, 700, 8, 3000, False), (500, 700, 64, 3000, False), (500, 700, 64, 1500, True)])
+def test_more_targets_than_the_sweep_holds(dgn, oracle, layers, width, sets, targets, swept):
+    rng = np.random.default_rng(layers + sets)
+    g = in_layers(rng, [width] * layers, 3, 1, 2, 3, 50)
+    cuts = np.sort(rng.integers(0, targets + 1, sets - 1))
+    tg = targets_from_sets([[int(t) for t in part] for part in np.split(rng.integers(0, g.num_tensors, targets), cuts)], sets)
+    check(dgn, oracle, g, [tg], swept)
+
+
+@pytest.mark.parametrize("per_set,launches", [(5, 3 * 5), (20, None)])
+def test_words_of_sets_on_many_layers(dgn, oracle, per_set, launches):
+    """Each word is swept by itself, five launches; with 3 000 targets in all, of which a word might own most, on 350 000 operators none is."""
+    rng = np.random.default_rng(per_set)
+    g = in_layers(rng, [700] * 500, 3, 1, 2, 3, 50)
+    tg = targets_from_sets([[int(t) for t in rng.integers(0, g.num_tensors, per_set)] for _ in range(150)], 64)
+    took = prune_words(dgn, oracle, g, tg, 150)
+    assert took == launches if launches else took > 3 * 6
