@@ -70,10 +70,10 @@ constexpr int kRingFewWords = 16, kRingManySegs = 64, kRingSegmentsPerCu = 24, k
 // 64: one in 10).  Whole prunes, level by level / swept, 64 sets of up to 8: 24 layers of 700 161 / 82 us, 60 x 300 173 / 86, 200 x 90
 // 170 / 119, 500 x 400 370 / 216, 1 000 x 40 376 / 284, 1 000 x 800 817 / 661; first prunes of them 300 to 800 / 92 to 674.  With a
 // single set of 4: 24 x 700 96 / 64, 100 x 600 159 / 111, 500 x 400 255 / 209, but 300 x 667 206 / 226, 300 x 800 210 / 232, 500 x 700 267 /
-// 337 and 1 000 x 600 471 / 591, so up to four sets on more than 200 000 operators are left to the levels.  That line is drawn for wide
-// layers: 1 000 narrow ones would gain beyond it as well (1 000 x 210 424 / 291, 1 000 x 300 407 / 324).  At four sets the two ways meet (300 x
-// 667 234 / 227, 500 x 700 332 / 339, 1 000 x 600 567 / 594), from five on the sweep is the faster one or takes the same time (255 / 228,
-// 345 / 340, 586 / 595; eight: 265 / 230, 370 / 340, 617 / 597).
+// 337 and 1 000 x 600 471 / 591, so up to four sets on more than 200 000 operators are left to the levels, or on more than 300 000 where
+// there are some 600 layers and more, which fit a step each then (600 x 450 317 / 245, 1 000 x 210 424 / 291, 1 000 x 300 407 / 324, but 700 x
+// 560 362 / 415).  At four sets the two ways meet (300 x 667 234 / 227, 500 x 700 332 / 339, 1 000 x 600 567 / 594), from five on the sweep is
+// the faster one or takes the same time (255 / 228, 345 / 340, 586 / 595; eight: 265 / 230, 370 / 340, 617 / 597).
 //   More than kBandMaxTargets targets go by way of M, and a step of the sweep takes half as long again; the levels take no longer than
 // with few.  Up to 50 000 operators and 8 000 for every set the sweep is the faster one or takes the same time (100 x 500 128 / 112; 1 000 x 40
 // 350 / 355; four sets on 100 x 600 150 / 134, eight on 300 x 200 183 / 167, but on 200 x 600 190 / 212 and 450 x 700 304 / 421; five on 1 000 x 600
@@ -81,7 +81,7 @@ constexpr int kRingFewWords = 16, kRingManySegs = 64, kRingSegmentsPerCu = 24, k
 // but 1 000 x 600 680 / 788, 1 000 x 800 822 / 872; sixteen are the limit: 500 x 400 308 / 275, 300 x 667 260 / 300), and with five and more
 // where there are some 700 layers and more (eight sets on 1 000 x 250 449 / 406).
 constexpr int kBandSoonShare = 25;
-constexpr int64_t kBandFewSets = 4, kBandFewSetsOps = 200000;
+constexpr int64_t kBandFewSets = 4, kBandFewSetsOps = 200000, kBandFewSetsDeepOps = 300000, kBandLastWordDeepOps = 400000;
 constexpr int64_t kBandFromMOps = 50000, kBandFromMSetOps = 8000, kBandFromMManySets = 16, kBandFromMMaxOps = 300000;
 constexpr int kSmallLevel = 16384;           // levels expanding fewer entries than this decay the threshold faster
 constexpr int kDefaultDeferPercent = 74;
@@ -924,14 +924,17 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
     return error_bits_to_code(status[0]);
 }
 
-// The largest graph that is swept by layers, for so many sets and targets (see kBandSoonShare).
-static int64_t band_most_ops(const dgn_graph *g, int64_t sets, int64_t num_targets)
+// The largest graph that is swept by layers, for so many sets and targets (see kBandSoonShare).  The last word of several goes by its
+// own sets as well (65 sets, 1 000 x 800 1 284 us with that one set swept, 1 065 with it left to the levels, 500 x 700 667 / 579, 300 x 667
+// 430 / 402, but 1 000 x 210 577 / 666, 1 000 x 300 640 / 715, 800 x 500 653 / 656).
+static int64_t band_most_ops(const dgn_graph *g, int64_t sets, int64_t num_targets, bool last_word)
 {
+    const bool deep = g->reach == Reach::nearer;
     if (num_targets > kBandMaxTargets) {
-        const bool many = sets >= kBandFromMManySets || (sets > kBandFewSets && g->reach == Reach::nearer);
+        const bool many = sets >= kBandFromMManySets || (sets > kBandFewSets && deep);
         return many ? kBandFromMMaxOps : kBandFromMOps + sets * kBandFromMSetOps;
     }
-    return sets <= kBandFewSets ? kBandFewSetsOps : kBandMaxOps;
+    return sets > kBandFewSets ? kBandMaxOps : !deep ? kBandFewSetsOps : last_word ? kBandLastWordDeepOps : kBandFewSetsDeepOps;
 }
 
 // dgn_prune of a graph that looks like layers (see band_sweep.hip).  *taken: whether it was one; if not, nothing but a clear has
@@ -1092,7 +1095,7 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
                           reinterpret_cast<u64 *>(also_M), reinterpret_cast<u64 *>(also_K));
     const bool plain = !(options && (options->traversal != 0 || options->incremental || options->recompute_keep)) &&
                        !(stats && stats->level_trace && stats->level_trace_cap > 0);
-    if (g->layers && plain && g->P <= band_most_ops(g, sets, num_targets) && !g->no_layers.load(std::memory_order_relaxed)) {
+    if (g->layers && plain && g->P <= band_most_ops(g, num_sets, num_targets, num_sets < sets) && !g->no_layers.load(std::memory_order_relaxed)) {
         bool taken = false;
         rc = band_prune(g, num_sets, num_targets, tgt_rowptr, tgt_idx, M, K, op_flag, kept_ops, reinterpret_cast<u64 *>(kept_masks),
                         kept_count, per_query_count, S, options, stats, s, reinterpret_cast<u64 *>(also_M),

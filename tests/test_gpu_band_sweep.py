@@ -154,11 +154,20 @@ def test_more_targets_than_the_sweep_holds(dgn, oracle, layers, width, sets, tar
     check(dgn, oracle, g, [tg], swept)
 
 
-@pytest.mark.parametrize("per_set,launches", [(5, 3 * 5), (20, None)])
-def test_words_of_sets_on_many_layers(dgn, oracle, per_set, launches):
-    """Each word is swept by itself, five launches; with 3 000 targets in all, of which a word might own most, on 350 000 operators none is."""
+@pytest.mark.parametrize("sets,per_set,launches", [(150, 5, 3 * 5), (150, 20, None), (69, 3, 2 * 5), (66, 3, None)])
+def test_words_of_sets_on_many_layers(dgn, oracle, sets, per_set, launches):
+    """Each word is swept by itself, five launches; with 3 000 targets in all, of which a word might own most, on 350 000 operators none
+    is, nor a last word of two sets."""
     rng = np.random.default_rng(per_set)
     g = in_layers(rng, [700] * 500, 3, 1, 2, 3, 50)
-    tg = targets_from_sets([[int(t) for t in rng.integers(0, g.num_tensors, per_set)] for _ in range(150)], 64)
-    took = prune_words(dgn, oracle, g, tg, 150)
-    assert took == launches if launches else took > 3 * 6
+    tg = targets_from_sets([[int(t) for t in rng.integers(0, g.num_tensors, per_set)] for _ in range(sets)], 64)
+    took = prune_words(dgn, oracle, g, tg, sets)
+    assert took == launches if launches else took > 6 * -(-sets // 64)
+
+
+@pytest.mark.parametrize("layers,width,sets,swept", [(200, 1000, 4, True), (201, 1000, 4, False), (201, 1000, 5, True), (201, 1000, 63, True),
+                                                     (1000, 201, 1, True), (1000, 300, 1, True), (1000, 301, 1, False), (1000, 301, 5, True)])
+def test_few_sets_on_many_operators(dgn, oracle, layers, width, sets, swept):
+    rng = np.random.default_rng(layers + sets)
+    g = in_layers(rng, [width] * layers, 3, 1, 2, 3, 50)
+    check(dgn, oracle, g, [draw_targets(rng, g, sets, 9)], swept)
