@@ -938,13 +938,14 @@ static int64_t band_most_ops(const dgn_graph *g, int64_t sets, int64_t num_targe
 }
 
 // dgn_prune of a graph that looks like layers (see band_sweep.hip).  *taken: whether it was one; if not, nothing but a clear has
-// happened.
+// happened.  *launches: kernels enqueued.
 static int band_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets, const int32_t *tgt_rowptr, const int32_t *tgt_idx,
                       u64 *M, u64 *K, uint8_t *op_flag, int32_t *kept_ops, u64 *kept_masks, int64_t *kept_count,
                       int64_t *per_query_count, const PruneScratch &S, const dgn_options *options, dgn_stats *stats, hipStream_t s,
-                      u64 *also_M, u64 *also_K, bool *taken)
+                      u64 *also_M, u64 *also_K, bool *taken, int64_t *launches)
 {
     *taken = false;
+    *launches = 0;
     BandArgs a{};
     a.g = g->v;
     if (reinterpret_cast<const char *>(S.q0) + band_scratch(a, nullptr) > reinterpret_cast<const char *>(S.flagbuf)) return DGN_OK;
@@ -983,6 +984,7 @@ static int band_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     if (flags != op_flag) {
         FillRegion more[1] = {{flags, S.db_bytes}};
         DGN_HIP(launch_clear(more, 1, s));
+        ++*launches;
     }
     DGN_HIP(launch_band_plan(a, g->num_cus, s));
     if (ev && all) DGN_HIP(hipEventRecord(ev[1], s));
@@ -1008,6 +1010,7 @@ static int band_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     ca.error = &S.state->error;
     DGN_HIP(launch_keep_compact(ca, s, ev && all ? ev + 4 : nullptr));
     if (op_flag && flags != op_flag) DGN_HIP(hipMemcpyAsync(flags, op_flag, (size_t)g->P, hipMemcpyDeviceToDevice, s));
+    *launches += from_m ? 6 : 5;                            // plan, seeds, sweep, count, scan, list
     DGN_HIP(hipStreamSynchronize(s));
     const int32_t *status = a.host_status;
     if (status[kBandTaken] == 0) {
@@ -1021,7 +1024,7 @@ static int band_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
         memset(stats, 0, sizeof(*stats));
         stats->level_trace = user_trace;
         stats->level_trace_cap = user_cap;
-        stats->launches = from_m ? 6 : 5;
+        stats->launches = *launches;
         stats->levels = status[kBandTaken] - 1;
         stats->tensor_visits = g->P;
         stats->recycled = status[kBandFound];
@@ -1095,15 +1098,15 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
                           reinterpret_cast<u64 *>(also_M), reinterpret_cast<u64 *>(also_K));
     const bool plain = !(options && (options->traversal != 0 || options->incremental || options->recompute_keep)) &&
                        !(stats && stats->level_trace && stats->level_trace_cap > 0);
+    int64_t launches = 0, level_launches = 0;
     if (g->layers && plain && g->P <= band_most_ops(g, num_sets, num_targets, num_sets < sets) && !g->no_layers.load(std::memory_order_relaxed)) {
         bool taken = false;
         rc = band_prune(g, num_sets, num_targets, tgt_rowptr, tgt_idx, M, K, op_flag, kept_ops, reinterpret_cast<u64 *>(kept_masks),
                         kept_count, per_query_count, S, options, stats, s, reinterpret_cast<u64 *>(also_M),
-                        reinterpret_cast<u64 *>(also_K), &taken);
+                        reinterpret_cast<u64 *>(also_K), &taken, &launches);
         if (rc || taken) return rc;
     }
     const size_t pq_bytes = per_query_count ? sizeof(int64_t) * 64 * (size_t)(g->G > 1 ? g->G : 1) : 0;
-    int64_t launches = 0, level_launches = 0;
     // 0 start, 1 cleared, 2 seeded, 3 traversed, 4 counted, 5 scanned, 6 scattered.  An event between two
     // kernels costs a few microseconds of idle stream, so profile = 2 records only the two around the traversal.
     hipEvent_t *ev = nullptr;

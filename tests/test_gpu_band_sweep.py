@@ -171,3 +171,30 @@ def test_few_sets_on_many_operators(dgn, oracle, layers, width, sets, swept):
     rng = np.random.default_rng(layers + sets)
     g = in_layers(rng, [width] * layers, 3, 1, 2, 3, 50)
     check(dgn, oracle, g, [draw_targets(rng, g, sets, 9)], swept)
+
+
+@pytest.mark.parametrize("flags", ["none", "unaligned", "ragged", "whole"])
+def test_backward_prune_with_flag_bytes_of_its_own(dgn, oracle, flags):
+    """The first stage of a backward prune keeps flag bytes in its scratch where the caller's cannot be cleared in whole words (then one more
+    launch clears them): no op_flag, one at an odd address, a number of operators that is no multiple of 8."""
+    import torch
+    rng = np.random.default_rng(len(flags))
+    g = in_layers(rng, [300] * 70 + ([5] if flags == "ragged" else []), 3, 1, 2, 3, 20)
+    obj = rng.integers(0, 20, 50).astype(np.int32)
+    wrt = rng.integers(g.num_tensors - 600, g.num_tensors, 50).astype(np.int32)
+    ref = oracle.backward_prune(oracle.build_adjacency(g.num_ops, g.num_tensors, g.in_op, g.in_tensor, g.out_op, g.out_tensor), obj, wrt)
+    buf = dgn.BackwardPruneBuffers(dgn.DeviceGraph.from_coo(g), 64)
+    big = torch.full((g.num_ops + 16,), 77, dtype=torch.uint8, device="cuda")
+    if flags != "ragged":
+        buf.op_flag = {"none": None, "unaligned": big[3:3 + g.num_ops], "whole": big[8:8 + g.num_ops]}[flags]
+    for call in range(3):                                    # (the last one with recycled buffers)
+        st = dgn.dgn_stats()
+        assert buf.backward_prune(torch.from_numpy(obj).cuda(), torch.from_numpy(wrt).cuda(), stats=st) == 0
+        assert st.max_frontier == 0 and st.launches == (5 if flags == "whole" else 6)
+        own, buf.op_flag = buf.op_flag, buf.op_flag if buf.op_flag is not None else torch.zeros_like(big[:g.num_ops])
+        out = buf.to_host()
+        buf.op_flag = own
+        for name in ("tensor_mask", "op_mask", "kept_ops", "kept_masks", "kept_count", "per_query_count") + (("op_flag",) if own is not None else ()):
+            assert np.array_equal(out[name], getattr(ref, name)), (name, call)
+    if flags in ("unaligned", "whole"):
+        assert int((big == 77).sum()) == 16                  # nothing written outside
