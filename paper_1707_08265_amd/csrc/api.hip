@@ -292,6 +292,16 @@ int64_t words_scratch(PruneScratch &S, void *scratch, int64_t P, int64_t words)
     return at_once;
 }
 
+// What the segments of a ring sweep may use: what lies behind one word's records, up to the flag bytes, or behind those of several, up
+// to the end (flagbuf == NULL: laid out by words_scratch).
+struct Room { char *at; size_t bytes; };
+Room segments_room(const PruneScratch &S, int64_t words)
+{
+    char *at = S.flagbuf ? reinterpret_cast<char *>(S.q0) : reinterpret_cast<char *>(S.ring_graphs) + align256((size_t)words * sizeof(int4));
+    const char *end = S.flagbuf ? reinterpret_cast<const char *>(S.flagbuf) : S.end;
+    return {at, at < end ? (size_t)(end - at) : 0};
+}
+
 // One small pinned buffer per host thread for status read-backs (never freed: a few hundred bytes).
 int pinned_buffer(void **out)
 {
@@ -787,7 +797,7 @@ static int ring_waves(const dgn_graph *g, const dgn_options *o, const dgn_stats 
     return fits(1) ? 1 : 0;
 }
 
-// Segments per graph of a ring sweep (laid out in a, in `room` bytes at mem), 1: none.
+// Segments per graph of a ring sweep (laid out in a, in `room`), 1: none.
 //   A graph that is read at most 64 tensors back may be swept in pieces at the same time: what a piece does not know is M of
 // the 64 tensors below its upper end, and it is linear in those, so a second sweep whose sets are those tensors says what they
 // bring (see ring_sweep.hip).  A chain of 0.9 us per 64 operators becomes two sweeps of a few words each, side by side, 10 to 17 us to
@@ -805,7 +815,7 @@ static int ring_waves(const dgn_graph *g, const dgn_options *o, const dgn_stats 
 // of a segment, less the operators and the targets (250 graphs of 1 000, which have room for two segments each, 1 024 targets: 59 /
 // 66).  More than kRingSeedWords targets go by way of M, which is slow in one piece as well (250 graphs of 1 000, 4 096 each: 161 / 105; 96
 // of 3 000: 16 384 188 / 188, 25 600 219 / 293).
-static int ring_segments(const dgn_graph *g, int64_t words, char *mem, size_t room, RingArgs &a)
+static int ring_segments(const dgn_graph *g, int64_t words, Room room, RingArgs &a)
 {
     if (g->ring_reach > kWave) return 1;
     const int64_t n_words = (g->max_graph_ops + kWave - 1) / kWave, all_words = (g->P / kWave + 1) * (words + 1);
@@ -819,7 +829,7 @@ static int ring_segments(const dgn_graph *g, int64_t words, char *mem, size_t ro
         const int64_t segs = (n_words + a.seg_words - 1) >> shift;
         if (segs < 2 || a.seg_words > kRingMaxSegWords) return 1;
         a.segs = (int32_t)segs;
-        if (ring_segment_scratch(a, nullptr) <= room) break;
+        if (ring_segment_scratch(a, nullptr) <= room.bytes) break;
     }
     const int64_t targets = a.num_targets / (g->G * words);  // (of an average graph or word)
     const bool from_m = targets > kRingSeedWords;
@@ -828,7 +838,7 @@ static int ring_segments(const dgn_graph *g, int64_t words, char *mem, size_t ro
     if (!a.few_segs && (double)n_words * kRingManyWordUs + kRingManyUs <
                            (double)a.seg_words * kRingManySegWordUs + swept * kRingManyOpUs + targets_us)
         return 1;
-    (void)ring_segment_scratch(a, mem);
+    (void)ring_segment_scratch(a, room.at);
     return a.segs;
 }
 
@@ -888,11 +898,7 @@ static int ring_prune(const dgn_graph *g, int waves, int64_t words, int32_t num_
                                        : (avg + avg / 2 + 64 < kRingSeedWords ? avg + avg / 2 + 64 : kRingSeedWords));
     a.reach = g->ring_reach;
     a.count_steps = stats && g->G < kSweepMinGraphs;
-    // (segments have what lies behind one word's records, up to the flag bytes, or behind those of several, up to the end)
-    const bool many = !S.flagbuf;
-    char *room = many ? reinterpret_cast<char *>(S.ring_graphs) + align256((size_t)words * sizeof(int4)) : reinterpret_cast<char *>(S.q0);
-    const char *room_end = many ? S.end : reinterpret_cast<const char *>(S.flagbuf);
-    a.segs = room < room_end ? ring_segments(g, words, room, (size_t)(room_end - room), a) : 1;
+    a.segs = ring_segments(g, words, segments_room(S, words), a);
     if (a.segs > 1 && a.seed_words < kWave) a.seed_words = kWave;
     int32_t *status = static_cast<int32_t *>(pin);
     status[0] = status[1] = status[2] = 0;

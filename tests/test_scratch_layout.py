@@ -1,4 +1,4 @@
-"""Scratch layouts of the library, checked on the host: what one call of the ring sweep writes must not overlap."""
+"""Scratch layouts of the library, checked on the host: what one call of a sweep writes must not overlap."""
 import os
 import subprocess
 
