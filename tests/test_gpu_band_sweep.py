@@ -96,7 +96,7 @@ def test_targets_at_the_ends_and_none(dgn, oracle):
 
 
 def test_bad_targets_and_other_buffers_contents(dgn, oracle):
-    """A target out of range is an error, and the next call is right; traversal, sweep and an incremental call in the same buffers."""
+    """A target out of range is an error, and the next call is right; sweep, wide levels and one launch per level in the same buffers."""
     import torch
     rng = np.random.default_rng(6)
     g = in_layers(rng, [350] * 80, 3, 1, 2, 3, 20)
@@ -173,6 +173,26 @@ def test_few_sets_on_many_operators(dgn, oracle, layers, width, sets, swept):
     check(dgn, oracle, g, [draw_targets(rng, g, sets, 9)], swept)
 
 
+@pytest.mark.parametrize("sets", [1, 16, 64])
+@pytest.mark.parametrize("targets", [512, 513, 1025, 1537, 2047, 2048, 2049, 3000])
+def test_targets_of_one_workgroup(dgn, oracle, targets, sets):
+    """All of a call's targets in one set, or spread unevenly over 16 (one workgroup's) or 64: a thread holds one to four of them; 2 049
+    go by way of M.  And with a bad one among them."""
+    import torch
+    rng = np.random.default_rng(targets + sets)
+    g = in_layers(rng, [300] * 70, 3, 1, 2, 3, 20)
+    cuts = np.sort(rng.integers(0, targets + 1, sets - 1))
+    tg = targets_from_sets([[int(t) for t in part] for part in np.split(rng.integers(0, g.num_tensors, targets), cuts)], sets)
+    dg, buf = dgn.DeviceGraph.from_coo(g), None
+    check(dgn, oracle, g, [tg], dg=dg)
+    buf = dgn.PruneBuffers(dg, sets)
+    for place, bad in ((0, -1), (targets - 1, g.num_tensors), (targets // 2, 2**31 - 1)):
+        wrong = tg.tgt_idx.copy()
+        wrong[place] = bad
+        assert buf.prune(torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(wrong).cuda()) == dgn.DGN_ERR_ID_OUT_OF_RANGE
+        check(dgn, oracle, g, [tg], dg=dg, buf=buf)
+
+
 @pytest.mark.parametrize("flags", ["none", "unaligned", "ragged", "whole"])
 def test_backward_prune_with_flag_bytes_of_its_own(dgn, oracle, flags):
     """The first stage of a backward prune keeps flag bytes in its scratch where the caller's cannot be cleared in whole words (then one more
@@ -198,3 +218,36 @@ def test_backward_prune_with_flag_bytes_of_its_own(dgn, oracle, flags):
             assert np.array_equal(out[name], getattr(ref, name)), (name, call)
     if flags in ("unaligned", "whole"):
         assert int((big == 77).sum()) == 16                  # nothing written outside
+
+
+@pytest.mark.parametrize("layers,reads,swept", [(60, 20, False), (60, 30, True), (330, 30, False), (6, 7, True)])
+def test_short_steps(dgn, oracle, layers, reads, swept):
+    """Layers of 400 in which every operator also reads the tensor `reads` before its own, where no sample is taken: steps of so many.  More
+    than 64 steps of fewer than 24 operators, or more than 4 096 steps, are left to the traversal, now and later."""
+    rng = np.random.default_rng(reads)
+    g = in_layers(rng, [400] * layers, 3, 1, 1, 3, 20)
+    ops = np.arange(reads, g.num_ops, dtype=np.int32) if reads > 7 else np.arange(g.num_ops - 200, g.num_ops, dtype=np.int32)
+    op, t = np.concatenate([g.in_op, ops]), np.concatenate([g.in_tensor, (20 + ops - reads).astype(np.int32)])
+    order = np.argsort(op, kind="stable")                    # (behind the operator's other inputs)
+    g = gg.Graph(g.num_ops, g.num_tensors, op[order].astype(np.int32), t[order].astype(np.int32), g.out_op, g.out_tensor, name="short steps")
+    check(dgn, oracle, g, [draw_targets(rng, g, 8, 3)], swept)
+
+
+def test_an_incremental_call_between_swept_ones(dgn, oracle):
+    """It has levels, and leaves nothing that the next call recognises."""
+    import torch
+    rng = np.random.default_rng(9)
+    g = in_layers(rng, [350] * 80, 3, 1, 2, 3, 20)
+    dg, buf = dgn.DeviceGraph.from_coo(g), None
+    sets = [[[int(t) for t in rng.integers(0, g.num_tensors, 3)] for _ in range(30)] for _ in range(2)]
+    first, added, both = [targets_from_sets(s, 30) for s in (sets[0], sets[1], [a + b for a, b in zip(*sets)])]
+    buf = dgn.PruneBuffers(dg, 30)
+    seen = []
+    for tg, ref, knobs in ((first, first, {}), (first, first, {}), (added, both, {"incremental": 1}), (first, first, {}), (first, first, {}),
+                           (added, both, {"incremental": 1}), (added, added, {"traversal": 2}), (added, added, {})):
+        st = dgn.dgn_stats()
+        rc = buf.prune(torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda(), options=dgn.dgn_options(**knobs), stats=st)
+        assert rc == 0 and (st.max_frontier == 0) == (not knobs)
+        assert_same(buf.to_host(), oracle_prune(oracle, g, ref)[1], str(knobs))
+        seen.append(int(st.recycled))
+    assert seen == [0, 0, 0, 0, 1, 0, 0, 0], seen

@@ -286,11 +286,14 @@ def test_schedule_knobs_do_not_change_results(dgn, oracle, k, scale):
                   dict(traversal=2, defer_percent=90, defer_start_shift=3, defer_floor_shift=14),
                   dict(max_queue_entries=1000), dict(max_queue_entries=37, traversal=1),
                   # (the few small graphs of configuration 4 are swept unless a traversal is asked for)
-                  dict(traversal=2, defer_percent=100), dict(traversal=2, defer_percent=95), dict(traversal=2, max_queue_entries=1000)):
+                  # (and configuration 1 by layers, where its scratch has room)
+                  dict(traversal=2, defer_percent=100), dict(traversal=2, defer_percent=95), dict(traversal=2, max_queue_entries=1000),
+                  dict(traversal=2, defer_percent=50)):
         st = dgn.dgn_stats()
         _, _, out = gpu_prune(dgn, g, tg, stats=st, **knobs)
         assert_same(out, r, f"cfg{k} {knobs}")
         assert st.launches > 3 or (k == 4 and "traversal" not in knobs)
+        assert (st.max_frontier > 0) == (k == 3 or "traversal" in knobs or (k == 1 and "max_queue_entries" in knobs)), knobs
 
 
 # ---- the workloads at their full sizes, in the launch configuration bench.py times ---------------

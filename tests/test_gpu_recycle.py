@@ -39,17 +39,19 @@ def _prune(dgn, buf, t, **knobs):
     return st
 
 
-@pytest.mark.parametrize("k,scale", [(0, 1.0), (1, 0.2), (2, 0.02), (3, 0.02)])
-def test_recycled_prunes_match_the_oracle(dgn, oracle, k, scale):
+# (configuration 1 is swept by layers and keeps no log unless a traversal is asked for)
+@pytest.mark.parametrize("k,scale,knobs", [(0, 1.0, {}), (1, 0.2, {}), (1, 0.2, {"traversal": 2}), (2, 0.02, {}), (3, 0.02, {})])
+def test_recycled_prunes_match_the_oracle(dgn, oracle, k, scale, knobs):
     g, tg = gg.config(k, scale)
     dg = dgn.DeviceGraph.from_coo(g)
     buf = dgn.PruneBuffers(dg, tg.num_sets)                 # recycles from its second call on
     adj, _ = oracle_prune(oracle, g, tg)
     seen = []
     for i, t in enumerate(_draws(g, tg, 6)):
-        st = _prune(dgn, buf, t)
+        st = _prune(dgn, buf, t, **knobs)
         ref = oracle.forward_prune(adj, t.num_sets, t.tgt_rowptr, t.tgt_idx, g.num_graphs, g.graph_op_offsets)
         assert_same(buf.to_host(), ref, f"cfg{k} call {i}")
+        assert (st.max_frontier > 0) == (k in (2, 3) or "traversal" in knobs)
         seen.append(int(st.recycled))
     print(f"cfg{k}: recycled per call {seen}", flush=True)
     # call 0 has no flag, call 1 finds no log yet; from then on the previous result is found -- unless a prune
@@ -318,7 +320,8 @@ def test_other_buffers_or_another_graph_are_not_mistaken_for_the_previous_result
     torch.cuda.synchronize()
 
 
-def test_two_host_threads_prune_the_same_graph_on_their_own_streams(dgn, oracle):
+@pytest.mark.parametrize("traversal", [0, 2])               # swept by layers, which writes no hints, and level by level
+def test_two_host_threads_prune_the_same_graph_on_their_own_streams(dgn, oracle, traversal):
     """The graph handle is shared (its launch-layout hints are the only thing calls write to it), buffers,
     scratch and stream are each thread's own: the calls may overlap on the GPU and every result must still be
     the oracle's."""
@@ -341,7 +344,7 @@ def test_two_host_threads_prune_the_same_graph_on_their_own_streams(dgn, oracle)
                 order = list(range(len(draws))) if k == 0 else list(reversed(range(len(draws))))
                 for rep in range(3):
                     for i in order:
-                        rc = buf.prune(*dev_targets[i], stream=stream)
+                        rc = buf.prune(*dev_targets[i], options=dgn.dgn_options(traversal=traversal), stream=stream)
                         assert rc == 0, dgn.dgn_strerror(rc)
                         stream.synchronize()
                         assert_same(buf.to_host(), refs[i], f"thread {k} rep {rep} draw {i}")

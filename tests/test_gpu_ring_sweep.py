@@ -107,6 +107,23 @@ def test_segments(dgn, oracle, shape, segments, Q, most):
     assert st.launches == (2 if segments or P > 16384 else 1) and st.levels > 0
 
 
+@pytest.mark.parametrize("G,ops,segments", [(20, 5000, True), (40, 2500, True), (5, 400, False)])
+def test_batches_in_segments(dgn, oracle, G, ops, segments):
+    """Settling steps are added up over all segments' sweeps of all graphs, six for every word here; in one piece they are the largest
+    graph's alone, one for every word of all."""
+    import torch
+    rng = np.random.default_rng(G + ops)
+    g = recorded(rng, G, ops, 64, 2, 3, 16)
+    tg = draw_targets(rng, g, 64, 2)
+    buf = dgn.PruneBuffers(dgn.DeviceGraph.from_coo(g), 64)
+    st = dgn.dgn_stats()
+    assert buf.prune(torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda(), stats=st) == 0
+    assert_same(buf.to_host(), oracle_prune(oracle, g, tg)[1], "batch")
+    words = -(-np.diff(np.asarray(g.graph_op_offsets)) // 64)
+    print(f"{G} graphs of up to {ops}: {int(st.levels)} settling steps, {int(words.sum())} words, the largest {int(words.max())}", flush=True)
+    assert (st.levels > 3 * words.sum()) == segments
+
+
 # Targets are looked for in rows of 64, four rows at a time, by one wave of a segment or eight (batches: (260, 2000) is the one wave's);
 # 2 048 fit in LDS, more go through the masks.
 @pytest.mark.parametrize("G,ops", [(1, 460), (1, 5000), (6, 1500), (260, 2000)])
