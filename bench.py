@@ -112,7 +112,9 @@ def other_config(d, torch, np, gg, orc, k, steps, warmup, with_oracle):
     res = {"workload": f"configs[{k}] {g.name}", "num_ops": g.num_ops, "num_sets": tg.num_sets, "num_graphs": g.num_graphs,
            "ms_per_step": round(ms, 4), "gteps": round(E / (ms * 1e-3) / 1e9, 3), "build_ms": round(build_ms, 3),
            "levels": int(st.levels), "operator_visits": int(st.tensor_visits), "launches": int(st.launches),
-           "kept_ops": int(out["kept_count"][0]), "output_buffers": "recycled" if st.recycled else "cleared in full",
+           "kept_ops": int(out["kept_count"][0]),
+           # (a graph that is swept by layers, five launches and no frontier: everything is cleared, found in place or not)
+           "output_buffers": "recycled" if st.recycled and (st.max_frontier > 0 or st.launches < 5) else "cleared in full",
            "bit_exact_vs_oracle": None, "oracle": None}
     del buf, dg, graph_mem
     torch.cuda.empty_cache()

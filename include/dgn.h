@@ -95,7 +95,9 @@ typedef struct dgn_options {
     int32_t traversal;       /* 0 = automatic; 1 = one kernel launch per frontier level, nothing else;
                                 2 = one launch per wide level plus the single-workgroup kernel for
                                 small frontiers (what 0 chooses for a large single graph; small ones, and
-                                packed batches of small ones, it sweeps with a workgroup or wave each)  */
+                                packed batches of small ones, it sweeps with a workgroup or wave each, and single
+                                ones of up to 2^20 operators in wide layers a layer at a time, sixteen sets to a
+                                workgroup)                                                              */
     int32_t profile;         /* prune: 1 = bracket each phase with HIP events on `stream` and report
                                 the elapsed times in dgn_stats.phase_ms (needs stats != NULL); an
                                 event between two kernels leaves the stream idle for a few
@@ -103,7 +105,8 @@ typedef struct dgn_options {
                                 (phase_ms[DGN_PHASE_TRAVERSE] alone is filled)                      */
     int32_t defer_percent;   /* prune: geometric decay (percent, 1..99) of the producer-id threshold
                                 below which frontier entries wait for more bits; 100 = never defer,
-                                0 = library default.  A schedule only: results do not depend on it */
+                                0 = library default.  A schedule only: results do not depend on it,
+                                and graphs that are swept (see traversal) have none                    */
     int32_t max_queue_entries; /* prune: cap on the frontier queues (0 = one entry per tensor).  A
                                 smaller cap only forces the overflow fix-up path (testing aid);
                                 results do not depend on it */
@@ -127,8 +130,8 @@ typedef struct dgn_options {
                                 instead of all of tensor_mask and op_mask, and keeps such a log itself.
                                 Where no complete log is found (first call with this flag, other buffers,
                                 a prune that coloured more than a quarter of the tensors, swept batches of
-                                64 graphs and more, after an incremental call) everything is cleared as
-                                without the flag.  Outputs are the same either
+                                64 graphs and more, graphs swept by layers, after an incremental call) everything
+                                is cleared as without the flag.  Outputs are the same either
                                 way.  Do not set it on the first call with a scratch buffer whose contents
                                 are undefined                                                          */
 } dgn_options;
@@ -144,7 +147,8 @@ enum {
     DGN_PHASE_TOTAL = 6,     /* first kernel start to last kernel end                             */
     DGN_NUM_PHASES = 8
     /* Graphs that one workgroup each sweeps: seeds, removal rule and counts are part of the sweep, which is
-     * DGN_PHASE_TRAVERSE (and makes the ordered list of a small single graph); DGN_PHASE_SCAN adds up a batch's graphs */
+     * DGN_PHASE_TRAVERSE (and makes the ordered list of a small single graph); DGN_PHASE_SCAN adds up a batch's graphs.
+     * A graph that is swept by layers: DGN_PHASE_CLEAR is the plan with the clear, DGN_PHASE_SEED empty up to 2 048 targets */
 };
 
 /* Schedule-dependent counters (not part of the result; excluded from parity). HOST struct. */

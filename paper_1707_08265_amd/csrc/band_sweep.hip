@@ -11,8 +11,9 @@
 // before b reads from (in its segment of 8 192 operators): a running maximum, and then a chain of one LDS access per step.
 // Its other workgroups clear M and K.
 //   k_band_sweep: eight waves process a step's operators (two LDS reads, up to four ORs), the other eight take M of the
-// step before and its K out of LDS to memory, and put target bits, which they hold in registers, in place two steps ahead (more than
-// 2 048 targets go by way of M and the seed kernel).  Operators are fetched eight steps ahead; no step waits for memory, and
+// step before and its K out of LDS to memory, and put target bits, which they hold in registers, in place two steps ahead (a call of
+// more than 2 048 targets, of all its words, sends them by way of M and the seed kernel, since one workgroup may own them all: steps of
+// 0.42 us instead of 0.3).  Operators are fetched eight steps ahead; no step waits for memory, and
 // a barrier is all that separates two of them.  The removal rule's count and list passes follow as behind the traversal.
 //
 // What bounds it: the instructions of a step, 0.3 us for 400 operators and 0.22 for 40, one wave's after the other's: LDS round trips
@@ -21,9 +22,9 @@
 // for among the held ones in every step 225 (now a scalar compare), addresses by the vector unit instead of buffer offsets 219.
 //
 // What a graph must satisfy the plan finds out on the device: outputs numbered as they are created, in one run up to the last
-// tensor, inputs written before, at most kBandMaxSteps steps of kBandMeanOps operators or more, and everything read no further
-// back than LDS holds.  If not, nothing but the clear has happened, and the host traverses the graph level by level instead, now and
-// from then on.  Which graphs are tried: kBandSoonShare in api.hip.
+// tensor, inputs written before, at most kBandMaxSteps steps, of kBandMeanOps operators or more on average where there are more than
+// kBandFewSteps, and everything read no further back than LDS holds.  If not, nothing but the clear has happened, and the host traverses the graph level by level instead, now and
+// from then on.  Which graphs are tried: kBandSoonShare and band_most_ops in api.hip.
 #include "common.h"
 
 namespace dgn {

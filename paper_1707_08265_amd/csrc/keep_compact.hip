@@ -312,8 +312,8 @@ constexpr int kFoldPqOutputs = 256;      // up to this many per-set counters are
 // Every thread owns one contiguous run of counts: it sums the run, the block scans the 1024 sums, the thread
 // walks its run again and writes the prefixes -- two rounds of independent loads whatever m is.  With few
 // per-set counters further workgroups sum their replicas meanwhile (kFoldPqPerBlock counters each, a wave takes four), which saves a
-// launch.  Latency bounds it: with the sums in the first workgroup, before the scan, 9.6 us for 98 tiles, now 5.7; whole prunes 3 to 6 us
-// less (RNN of 10 M 284 -> 279, 50 M operators 666 -> 660).
+// launch.  Latency bounds it: with the sums in the first workgroup, before the scan, 9.6 us for 98 tiles, now 5.7 (of a whole prune of 10 M
+// or 50 M operators that is less than two runs differ by).
 constexpr int kFoldPqPerBlock = 64;
 __global__ __launch_bounds__(1024) void k_scan_tiles(int32_t *counts, int64_t m, int64_t *kept_count, CompactArgs a)
 {
