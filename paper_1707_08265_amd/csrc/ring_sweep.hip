@@ -225,8 +225,11 @@ __global__ __launch_bounds__((H > W ? H : W) * kWave) void k_ring_sweep(RingArgs
     if (W > 1 || (kSeg && tid < N)) first_bounds();
     for (int i = tid; i <= R + a.low_words; i += kPlace) ring[i] = 0;
     if (tid < 3) s_flag[tid] = 0;
-    if (tid == 0) s_err = s_relax = s_own = 0;
-    if (tid == 0) s_lowest = 0x7fffffff;
+    if (tid == 0) s_err = s_relax = 0;
+    if (kSeg && tid == 0) {
+        s_own = 0;
+        s_lowest = 0x7fffffff;
+    }
 
     // the graph's targets, packed: tensor relative to t_lo in the upper 26 bits, set in the lower 6
     if (!boundary)
@@ -330,14 +333,16 @@ __global__ __launch_bounds__((H > W ? H : W) * kWave) void k_ring_sweep(RingArgs
     if (err) atomicOr(&s_err, err);
     lowest = -wave_max(-lowest);
     if (kSeg && lane == 0) atomicMin(&s_lowest, lowest);
+    auto lowest_of = [&](int low) { return from_m ? -1 : low == 0x7fffffff ? low : t_lo + low; };        // (none: beyond every tensor)
+    int32_t lowest_seed = lowest_of(lowest);
+    int n_seeds = from_m || j1 < j0 ? 0 : (int)(j1 - j0);
     if (from_m) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
-    if (kSeg) {
+    if constexpr (kSeg) {
         if (tid >= N) return;                                // (what follows is one wave's)
-        lowest = s_lowest;
+        lowest_seed = lowest_of(s_lowest);
+        n_seeds = boundary ? a.reach : s_own;
     }
-    const int32_t lowest_seed = from_m ? -1 : lowest == 0x7fffffff ? lowest : t_lo + lowest;     // (none: beyond every tensor)
-    const int n_seeds = kSeg ? (boundary ? a.reach : s_own) : from_m || j1 < j0 ? 0 : (int)(j1 - j0);
     auto sync = [&]() {
         if constexpr (kSeg) wave_fence(); else __syncthreads();
     };
