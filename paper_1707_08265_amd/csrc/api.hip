@@ -407,29 +407,48 @@ int read_status(const int32_t *status, hipStream_t s, const int32_t **out)
 // Packed batches, and single graphs that the ring sweep may take, are checked in the walk that makes the records.
 bool walked(const dgn_graph *h) { return h->G > 1 || h->P <= kRingMaxOps; }
 
-// What follows the adjacency.  The kernels find out by themselves whether there is one yet.
-int enqueue_records(const dgn_graph *h, const GraphLayout &L, int32_t *status, const dgn_options *options, hipStream_t s)
+// What follows the adjacency.  The kernels find out by themselves whether there is one yet.  made: single graphs that are not walked
+// have their records.
+int enqueue_records(const dgn_graph *h, const GraphLayout &L, int32_t *status, const dgn_options *options, hipStream_t s, bool made = false)
 {
     if (walked(h)) {
         DGN_HIP(launch_records_and_check(h->v, L.orec, status, h->num_cus, s));
     } else {
-        DGN_HIP(launch_build_records(h->v, L.orec, status, s));
+        if (made) DGN_HIP(launch_sample_reach(h->v, status, s));
+        else DGN_HIP(launch_build_records(h->v, L.orec, status, s));
         if (options && options->validate) DGN_HIP(launch_check_topological(h->v, status, s));
     }
     return DGN_OK;
 }
 
+// Rows by l.op of a list in no order, whose ids are checked unless they are known to be good.
+int sort_rows(const EdgeList &l, const BuildScratch &S, bool buckets, bool good, hipStream_t s)
+{
+    const RowPlan plan = plan_rows(l.nnz, l.num_ops, key_bits_for(l.num_ops));
+    if (buckets && plan.use) {
+        DGN_HIP(launch_bucket_rows(plan, l, false, S.status, S.sort_tmp, s));
+        return DGN_OK;
+    }
+    if (!good) DGN_HIP(launch_check_ids(l, S.status, s));
+    DGN_HIP(launch_sort_pairs(l.op, l.tensor, S.sorted_keys, l.idx, l.nnz, key_bits_for(l.num_ops), S.sort_tmp, s));
+    DGN_HIP(launch_row_bounds(S.sorted_keys, l.nnz, l.num_ops, l.row, S.status, s));
+    return DGN_OK;
+}
+
 // Tensor -> producer rows by a stable sort of the outputs in operator order (outputs by tensor: each tensor's producers stay
 // ascending in operator id), or, if only long gaps were left out, from the list in order by tensor; then the producer words.
+// buckets: by way of buckets where that is the shorter way (kStatusOversize then says whether it was one).
 int build_producers(const dgn_graph *h, const GraphLayout &L, const BuildScratch &S, const int32_t *ops_of_out,
-                    const int32_t *keys, hipStream_t s)
+                    const int32_t *keys, bool buckets, hipStream_t s)
 {
-    if (!keys) {
-        DGN_HIP(launch_sort_pairs(h->v.out_idx, ops_of_out, S.sorted_keys, L.prod_idx, h->Eout, key_bits_for(h->T), S.sort_tmp, s));
-        keys = S.sorted_keys;
+    if (keys) {
+        DGN_HIP(launch_row_bounds(keys, h->Eout, (int32_t)h->T, L.prod_rowptr, S.status, s));
+    } else {
+        const EdgeList list{h->v.out_idx, ops_of_out, h->Eout, (int32_t)h->T, (int32_t)h->P, L.prod_idx, L.prod_rowptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+        const int rc = sort_rows(list, S, buckets, true, s);
+        if (rc) return rc;
     }
-    DGN_HIP(launch_row_bounds(keys, h->Eout, (int32_t)h->T, L.prod_rowptr, s));
-    DGN_HIP(launch_build_producers(h->v, L.prod1, S.status + kStatusMulti, s));
+    DGN_HIP(launch_build_producers(h->v, L.prod1, S.status, s));
     return DGN_OK;
 }
 
@@ -510,6 +529,73 @@ int new_graph(dgn_graph **out)
     return DGN_OK;
 }
 
+// What is left of an adjacency when the pass over the edge lists has found (f) that they are not in order, as its status words say.
+// Stable sorts: edges by operator, rows keep COO order; no histogram of the rows, no atomics on memory.  buckets: by way of
+// buckets where that is the shorter way; (*found)[kStatusOversize] then says that it was not one after all.
+int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, const GraphLayout &L, const BuildScratch &S, bool buckets,
+               const int32_t (&f)[kStatusOrder], const dgn_options *options, hipStream_t s, const int32_t **found)
+{
+    const int64_t P = h->P, T = h->T, Eout = h->Eout;
+    FillRegion clr[1] = {{S.status, 256}};
+    const bool out_unsorted = f[kStatusOutUnsorted];
+    bool out_gap = f[kStatusOutGap], prod_unsorted = f[kStatusProdUnsorted], prod_gap = f[kStatusProdGap];
+    FillRegion order[1] = {{S.status, kStatusOrder * sizeof(int32_t)}};
+    DGN_HIP(launch_clear(out_unsorted ? clr : order, 1, s));
+    int rc = DGN_OK;
+    if (f[kStatusInUnsorted]) {
+        rc = sort_rows(in, S, buckets, false, s);
+        if (rc) return rc;
+    } else if (f[kStatusInGap]) {
+        DGN_HIP(launch_row_bounds(in.op, in.nnz, (int32_t)P, L.in_rowptr, S.status, s));
+    }
+    const int32_t *ops_of_out = out.op;                       // operator of every entry of out_idx
+    if (out_unsorted) {
+        const RowPlan plan = plan_rows(Eout, P, key_bits_for(P));
+        ops_of_out = S.sorted_ops;
+        if (buckets && plan.use) {
+            // where tensors are numbered as they are created, this is all
+            EdgeList with = out;
+            with.orec = walked(h) ? nullptr : L.orec;
+            with.in_row = L.in_rowptr;
+            DGN_HIP(launch_bucket_rows(plan, with, true, S.status, S.sort_tmp, s));
+            rc = enqueue_records(h, L, S.status, options, s, true);
+            if (rc) return rc;
+            rc = read_status(S.status, s, found);
+            if (rc || (*found)[0] || (*found)[kStatusOversize] || !(*found)[kStatusPending]) return rc;
+            DGN_HIP(launch_expand_rows(L.out_rowptr, (int32_t)P, S.sorted_ops, s));
+            DGN_HIP(launch_clear(clr, 1, s));
+        } else {
+            DGN_HIP(launch_check_ids(out, S.status, s));
+            DGN_HIP(launch_sort_pairs(out.op, out.tensor, S.sorted_ops, L.out_idx, Eout, key_bits_for(P), S.sort_tmp, s));
+        }
+        // The outputs, once in operator order and every operator's tensors ascending, get the same pass as the lists did: where
+        // tensors ascend with their operators that is the order by tensor, whatever order they came in, and they need no
+        // second sort.
+        DGN_HIP(launch_order_rows(S.sorted_ops, L.out_idx, Eout, S.sorted_keys, S.status, s));
+        const EdgeList sorted{S.sorted_ops, S.sorted_keys, Eout, (int32_t)P, (int32_t)T, nullptr, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1, nullptr, nullptr};
+        DGN_HIP(launch_scan_edges(nullptr, sorted, S.status, s));
+        rc = enqueue_records(h, L, S.status, options, s);
+        if (rc) return rc;
+        rc = read_status(S.status, s, found);
+        if (rc) return rc;
+        out_gap = (*found)[kStatusOutGap];
+        prod_unsorted = (*found)[kStatusProdUnsorted];
+        prod_gap = (*found)[kStatusProdGap];
+        if ((*found)[0] || (*found)[kStatusOversize] || !(out_gap || prod_unsorted || prod_gap)) return DGN_OK;
+        DGN_HIP(launch_clear(order, 1, s));
+    }
+    // (a long gap between tensors, but their order known: the keys are the ones that were found to ascend)
+    const int32_t *by_tensor = out_unsorted ? S.sorted_keys : L.out_idx;
+    if (out_gap) DGN_HIP(launch_row_bounds(ops_of_out, Eout, (int32_t)P, L.out_rowptr, S.status, s));
+    if (prod_unsorted || prod_gap) {
+        rc = build_producers(h, L, S, ops_of_out, prod_unsorted ? nullptr : by_tensor, buckets, s);
+        if (rc) return rc;
+    }
+    rc = enqueue_records(h, L, S.status, options, s);
+    if (rc) return rc;
+    return read_status(S.status, s, found);
+}
+
 // The adjacency and what follows it, from edge lists whose workspace is laid out in L and S.
 int build_from_lists(dgn_graph *h, const dgn_coo_desc *d, const GraphLayout &L, const BuildScratch &S, const dgn_options *options,
                      hipStream_t s, const int32_t **found)
@@ -522,58 +608,24 @@ int build_from_lists(dgn_graph *h, const dgn_coo_desc *d, const GraphLayout &L, 
     DGN_HIP(launch_clear(clr, 1, s));
     int rc = copy_offsets(h, L, d->graph_op_offsets, d->graph_tensor_offsets, s);
     if (rc) return rc;
-    const EdgeList in{d->in_op, d->in_tensor, Ein, (int32_t)P, (int32_t)T, L.in_idx, L.in_rowptr, nullptr, nullptr, nullptr};
-    const EdgeList out{d->out_op, d->out_tensor, Eout, (int32_t)P, (int32_t)T, L.out_idx, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1};
+    const EdgeList in{d->in_op, d->in_tensor, Ein, (int32_t)P, (int32_t)T, L.in_idx, L.in_rowptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+    const EdgeList out{d->out_op, d->out_tensor, Eout, (int32_t)P, (int32_t)T, L.out_idx, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1, nullptr, nullptr};
     DGN_HIP(launch_scan_edges(&in, out, S.status, s));
     rc = enqueue_records(h, L, S.status, options, s);
     if (rc) return rc;
-    const int32_t *f = nullptr;
-    rc = read_status(S.status, s, &f);
+    rc = read_status(S.status, s, found);
     if (rc) return rc;
-    *found = f;
+    int32_t f[kStatusOrder];
+    for (int i = 0; i < kStatusOrder; ++i) f[i] = (*found)[i];
     if (f[0] & kErrIdRange) return DGN_OK;                    // bad ids: nothing is built from them
-    const bool in_unsorted = f[kStatusInUnsorted], in_gap = f[kStatusInGap], out_unsorted = f[kStatusOutUnsorted];
-    bool out_gap = f[kStatusOutGap], prod_unsorted = f[kStatusProdUnsorted], prod_gap = f[kStatusProdGap];
-    if (!(in_unsorted || in_gap || out_unsorted || out_gap || prod_unsorted || prod_gap)) return DGN_OK;
-    // Otherwise stable sorts: edges by operator (rows keep COO order), row pointers from the sorted keys (first position of
-    // every key): no histogram, no atomics.  The outputs, once in operator order and every operator's tensors ascending, get
-    // the same pass as above: where tensors are numbered as they are created that is the order by tensor, whatever order they
-    // came in, and they need no second sort.
-    if (in_unsorted) {
-        DGN_HIP(launch_sort_pairs(d->in_op, d->in_tensor, S.sorted_keys, L.in_idx, Ein, key_bits_for(P), S.sort_tmp, s));
-        DGN_HIP(launch_row_bounds(S.sorted_keys, Ein, (int32_t)P, L.in_rowptr, s));
-    } else if (in_gap) {
-        DGN_HIP(launch_row_bounds(d->in_op, Ein, (int32_t)P, L.in_rowptr, s));
-    }
-    const int32_t *ops_of_out = d->out_op;                    // operator of every entry of out_idx
-    if (out_unsorted) {
-        DGN_HIP(launch_sort_pairs(d->out_op, d->out_tensor, S.sorted_ops, L.out_idx, Eout, key_bits_for(P), S.sort_tmp, s));
-        ops_of_out = S.sorted_ops;
-        DGN_HIP(launch_clear(clr, 1, s));
-        DGN_HIP(launch_order_rows(S.sorted_ops, L.out_idx, Eout, S.sorted_keys, S.status, s));
-        const EdgeList sorted{S.sorted_ops, S.sorted_keys, Eout, (int32_t)P, (int32_t)T, nullptr, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1};
-        DGN_HIP(launch_scan_edges(nullptr, sorted, S.status, s));
-        rc = enqueue_records(h, L, S.status, options, s);
-        if (rc) return rc;
-        rc = read_status(S.status, s, &f);
-        if (rc) return rc;
-        out_gap = f[kStatusOutGap];
-        prod_unsorted = f[kStatusProdUnsorted];
-        prod_gap = f[kStatusProdGap];
-        if (!(out_gap || prod_unsorted || prod_gap)) return DGN_OK;
-    }
-    // (a long gap between tensors, but their order known: the keys are the ones that were found to ascend)
-    const int32_t *by_tensor = out_unsorted ? S.sorted_keys : L.out_idx;
-    if (out_gap) DGN_HIP(launch_row_bounds(ops_of_out, Eout, (int32_t)P, L.out_rowptr, s));
-    if (prod_unsorted || prod_gap) {
-        rc = build_producers(h, L, S, ops_of_out, prod_unsorted ? nullptr : by_tensor, s);
-        if (rc) return rc;
-    }
-    FillRegion ready[1] = {{S.status, kStatusOrder * sizeof(int32_t)}};
-    DGN_HIP(launch_clear(ready, 1, s));
-    rc = enqueue_records(h, L, S.status, options, s);
-    if (rc) return rc;
-    return read_status(S.status, s, found);
+    if (!(f[kStatusInUnsorted] || f[kStatusInGap] || f[kStatusOutUnsorted] || f[kStatusOutGap] || f[kStatusProdUnsorted] ||
+          f[kStatusProdGap]))
+        return DGN_OK;
+    rc = sort_lists(h, in, out, L, S, true, f, options, s, found);
+    if (rc || !(*found)[kStatusOversize]) return rc;
+    FillRegion flag[1] = {{S.status + kStatusOversize, (kStatusPending - kStatusOversize) * sizeof(int32_t)}};
+    DGN_HIP(launch_clear(flag, 1, s));
+    return sort_lists(h, in, out, L, S, false, f, options, s, found);
 }
 
 }  // namespace
@@ -698,13 +750,13 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
         if (e) return e;
         // the outputs as a list in operator order: its tensors usually ascend as well, and the pass over it is all it takes
         DGN_HIP(launch_expand_rows(d->out_rowptr, (int32_t)P, S.sorted_ops, s));
-        const EdgeList list{S.sorted_ops, d->out_idx, Eout, (int32_t)P, (int32_t)T, nullptr, nullptr, L.prod_idx, L.prod_rowptr, L.prod1};
+        const EdgeList list{S.sorted_ops, d->out_idx, Eout, (int32_t)P, (int32_t)T, nullptr, nullptr, L.prod_idx, L.prod_rowptr, L.prod1, nullptr, nullptr};
         DGN_HIP(launch_scan_edges(nullptr, list, S.status, s));
         e = enqueue_records(h, L, S.status, options, s);
         if (e) return e;
         e = read_status(S.status, s, &found);
         if (e || !(found[kStatusProdUnsorted] || found[kStatusProdGap])) return e;
-        e = build_producers(h, L, S, S.sorted_ops, found[kStatusProdUnsorted] ? nullptr : d->out_idx, s);
+        e = build_producers(h, L, S, S.sorted_ops, found[kStatusProdUnsorted] ? nullptr : d->out_idx, false, s);
         if (e) return e;
         FillRegion ready[1] = {{S.status, kStatusOrder * sizeof(int32_t)}};
         DGN_HIP(launch_clear(ready, 1, s));

@@ -267,6 +267,28 @@ size_t sort_tmp_bytes(int64_t n);
 hipError_t launch_sort_pairs(const int32_t *keys_in, const int32_t *vals_in, int32_t *keys_out,
                              int32_t *vals_out, int64_t n, int key_bits, void *tmp, hipStream_t s);
 
+// rows lo..hi get val; gaps longer than a few rows are filled by the whole wave (call wave-uniformly)
+__device__ __forceinline__ void write_rows(int32_t *rowptr, int lo, int hi, int32_t val)
+{
+    constexpr int kShort = 4;
+    for (int r = lo; r <= hi && r < lo + kShort; ++r) rowptr[r] = val;
+    u64 longer = ballot64(hi - lo >= kShort);
+    while (longer) {
+        const int src = __builtin_ctzll(longer);
+        longer &= longer - 1;
+        const int s_lo = __shfl(lo, src, kWave) + kShort, s_hi = __shfl(hi, src, kWave);
+        const int32_t s_val = __shfl(val, src, kWave);
+        for (int r = s_lo + lane_id(); r <= s_hi; r += kWave) rowptr[r] = s_val;
+    }
+}
+
+// Operator records (see common.h), once per graph.
+template <bool kStream>
+__device__ __forceinline__ void write_record(int4 *p, int32_t ib, int32_t ie, int32_t ob, int32_t oe, int32_t first, bool consecutive)
+{
+    store16<kStream>(p, ib, ie - ib, consecutive ? first : ob, consecutive ? oe - ob : -(oe - ob));
+}
+
 // Status words of a build: [0] error bits, then flags
 enum : int {
     kStatusInUnsorted = 1,       // the operators of the input edges decrease somewhere
@@ -276,6 +298,8 @@ enum : int {
     kStatusOutGap = 6,
     kStatusProdGap = 7,
     kStatusOrder = 8,            // (so many words say whether there is an adjacency; the following describe it)
+    kStatusOversize = 8,         // lists that were to be sorted by buckets have a bucket that is too large: they are sorted as a whole
+    kStatusPending = 10,         // ... and rows by tensor that do not follow from the rows by operator
     kStatusMulti = 16,           // some tensor has several producers
     kStatusScattered = 17,       // the outputs are not one run of tensors up to the last one
     kStatusRing = 20,            // what k_records_and_check finds out for the ring sweep: [0] != 0: outputs are not one run or
@@ -296,22 +320,35 @@ struct EdgeList {
     int32_t num_ops, num_tensors;
     int32_t *idx, *row;                          // rows by operator
     int32_t *prod_idx, *prod_row, *prod1;        // outputs: rows by tensor, producer words
+    int4 *orec;                                  // outputs by way of buckets: operator records (NULL: not here), from the rows of the inputs
+    const int32_t *in_row;
 };
+// Rows of a list in no order by way of buckets of 2^row_bits rows: `passes` sorting passes of pass_bits bits bring it into
+// buckets, a workgroup of `threads` each does the rest (see radix_sort.hip).  use: that is fewer passes over memory than the sort takes.
+struct RowPlan { bool use; int row_bits, passes, pass_bits, threads; int64_t buckets; };
+RowPlan plan_rows(int64_t nnz, int64_t rows, int key_bits);
+// l.row, l.idx and, with `producers`, the rows by tensor, producer words and records.  kErrIdRange: there are ids out of range;
+// kStatusOversize: nothing was written; kStatusPending: the rows by operator are written, those by tensor are not.  tmp: scratch of sort_tmp_bytes(l.nnz) bytes.
+hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producers, int32_t *status, void *tmp, hipStream_t s);
+// kErrIdRange if an edge of the list has an id out of range
+hipError_t launch_check_ids(const EdgeList &l, int32_t *status, hipStream_t s);
 // one pass over the input edges (NULL: the outputs only) and the output edges: checks them and, assuming that they are in
 // order, writes the finished adjacency
 hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s);
 // The kernels from here to launch_check_topological do nothing if the status says that there is no adjacency yet.
+// what launch_build_records notes about how far back operators read, where their records are written already
+hipError_t launch_sample_reach(const GraphView &g, int32_t *status, hipStream_t s);
 // operator records of a single graph / of graphs that are also checked for range and for the ring sweep
 hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *status, hipStream_t s);
 hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *status, int num_cus, hipStream_t s);
 hipError_t launch_check_topological(const GraphView &g, int32_t *status, hipStream_t s);
-// producer words from prod_rowptr / prod_idx; *multi = 1 when some tensor has several producers
-hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *multi, hipStream_t s);
+// producer words from prod_rowptr / prod_idx; kStatusMulti when some tensor has several producers
+hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *status, hipStream_t s);
 // keys[e] = the tensors of a list in operator order, ascending inside every operator's row; flags rows longer than 64
 // (left as they are) as unsorted by tensor, and any change as "scattered"
 hipError_t launch_order_rows(const int32_t *ops, const int32_t *tensors, int64_t nnz, int32_t *keys, int32_t *status, hipStream_t s);
-// rowptr[0..n_rows] from keys that are in row order (all in range)
-hipError_t launch_row_bounds(const int32_t *keys, int64_t nnz, int32_t n_rows, int32_t *rowptr, hipStream_t s);
+// rowptr[0..n_rows] from keys that are in row order; nothing if the status has an error (all are in range)
+hipError_t launch_row_bounds(const int32_t *keys, int64_t nnz, int32_t n_rows, int32_t *rowptr, const int32_t *status, hipStream_t s);
 hipError_t launch_check_csr(const int32_t *rowptr, const int32_t *idx, int32_t n_rows, int32_t nnz,
                             int32_t n_vals, int32_t *error, hipStream_t s);
 hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t *row_of, hipStream_t s);

@@ -1,17 +1,16 @@
-// Stable LSD radix sort of (int32 key, int32 value) pairs, at most 9 bits per pass, for the CSR builder.
+// Stable sorts of (int32 key, int32 value) pairs for the CSR builder: an LSD radix sort of at most 9 bits per pass, and rows by way
+// of buckets, which sorts the high bits that way and the rest inside a workgroup (second half of this file).
 //
 // Per pass: (1) digit counts per tile of 8 192 keys, already summed inside groups of 16 tiles, and each group's totals;
 // (2) a small scan of the groups' totals; (3) a scatter in which every wave ranks its keys against the keys of its
 // lower lanes and earlier rounds (ballot "match" masks): keys of one tile are visited in their stored order, so
 // equal keys keep their relative order.  The tile is sorted inside LDS first, so that it leaves in one run per digit.
-// Only the significant key bits are sorted (ceil(log2(rows)) of them), so 50M operators (26 bits) or 100M
-// tensors (27 bits) cost three passes of nine bits.  (Eight bits per pass and four passes: 9 % slower on that graph; a pass
-// with 512 digits costs more than one with 256, because a tile then leaves in runs half as long and the ranking takes a
-// step more, but not a third more.)  Passes of eight bits where as many of them do (up to 24 bits: 26 M pairs by 24 bits
-// 126 -> 115 us per scatter).
+// Only the significant key bits are sorted.  (A whole sort of 26 bits in eight bits per pass and four passes: 9 % slower than three
+// of nine; a pass with 512 digits costs more than one with 256, because a tile then leaves in runs half as long and the ranking
+// takes a step more, but not a third more.)
 //
-// What a pass costs, per 110 M pairs on the 50 M-operator graph: counting 0.10 ms (the keys once, at the rate of a
-// copy), the scan 0.005 ms (0.015 in three kernels), the scatter 0.51 ms = 3.4 TB/s of 16 bytes per pair.  The scatter's time went, in turn, to
+// What a pass costs, per 32 M pairs: counting 27 us (the keys once, at the rate of a copy), the scan 5, the scatter 131 us = 3.9 TB/s
+// of 16 bytes per pair with eight bits (126 with seven: it is memory that bounds it).  The scatter's time went, in turn, to
 // the write-back of half-written cache lines (fixed by giving each die a contiguous range of tiles), to one cache
 // line per digit and tile for the slot table (fixed by the tile-major tables), and to the vector instructions of the
 // ranking (halved by the three-input bit operation and longer tiles).
@@ -44,18 +43,21 @@ template <int kBits> __device__ __forceinline__ int digit_of(int32_t key, int sh
 constexpr int kHistTiles = 16;
 constexpr int kColChunks = 64;              // the groups are scanned in up to this many chunks of consecutive groups
 
+constexpr int kHistThreads = 1024;
+
 template <int kBits>
-__global__ __launch_bounds__(1 << kBits) void k_sort_hist(const int32_t *keys, int64_t n, int shift, int32_t *table,
-                                                          int32_t *totals, int32_t *sums, int per_chunk)
+__global__ __launch_bounds__(kHistThreads) void k_sort_hist(const int32_t *keys, int64_t n, int shift, int32_t *table,
+                                                                     int32_t *totals, int32_t *sums, int per_chunk,
+                                                                     uint32_t num_rows, int32_t *status)
 {
-    constexpr int kRadix = 1 << kBits;
+    constexpr int kRadix = 1 << kBits, kThreads = kHistThreads;
     __shared__ int hist[kHistTiles][kRadix];
-#pragma unroll
-    for (int t = 0; t < kHistTiles; ++t) hist[t][threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < kHistTiles * kRadix; i += kThreads) (&hist[0][0])[i] = 0;
     __syncthreads();
     const int64_t tile0 = (int64_t)blockIdx.x * kHistTiles;
+    uint32_t most = 0;                                       // the largest key, for the check (status not NULL)
     const bool wide = (reinterpret_cast<uintptr_t>(keys) & 15) == 0;
-    constexpr int kPerThread = kSortTile / kRadix;           // keys of a tile that one thread counts
+    constexpr int kPerThread = kSortTile / kThreads;         // keys of a tile that one thread counts
     static_assert(kPerThread % 4 == 0, "a thread counts whole 16-byte groups of keys");
     for (int t = 0; t < kHistTiles; ++t) {
         // the order inside a tile does not matter for its counts: a thread takes neighbouring keys
@@ -67,17 +69,23 @@ __global__ __launch_bounds__(1 << kBits) void k_sort_hist(const int32_t *keys, i
             for (int q = 0; q < kPerThread / 4; ++q) a[q] = *reinterpret_cast<const int4 *>(keys + i + 4 * q);
 #pragma unroll
             for (int q = 0; q < kPerThread / 4; ++q) {
+                most = max(max(most, max((uint32_t)a[q].x, (uint32_t)a[q].y)), max((uint32_t)a[q].z, (uint32_t)a[q].w));
                 atomicAdd(&hist[t][digit_of<kBits>(a[q].x, shift)], 1);
                 atomicAdd(&hist[t][digit_of<kBits>(a[q].y, shift)], 1);
                 atomicAdd(&hist[t][digit_of<kBits>(a[q].z, shift)], 1);
                 atomicAdd(&hist[t][digit_of<kBits>(a[q].w, shift)], 1);
             }
         } else {
-            for (int r = 0; r < kPerThread; ++r)
-                if (i + r < n) atomicAdd(&hist[t][digit_of<kBits>(keys[i + r], shift)], 1);
+            for (int r = 0; r < kPerThread; ++r) {
+                if (i + r >= n) break;
+                most = max(most, (uint32_t)keys[i + r]);
+                atomicAdd(&hist[t][digit_of<kBits>(keys[i + r], shift)], 1);
+            }
         }
     }
     __syncthreads();
+    if (status && ballot64(most >= num_rows) != 0 && lane_id() == 0) atomicOr(status, kErrIdRange);
+    if (threadIdx.x >= kRadix) return;
     // the table has a row for each of the group's kHistTiles tiles, also past the last tile
     int32_t *row = table + tile0 * kRadix + threadIdx.x;
     int run = 0;
@@ -136,6 +144,28 @@ __global__ __launch_bounds__(1 << kBits) void k_col_apply(int32_t *totals, int64
     }
 }
 
+// The lanes that hold a key (valid) with the same digit as this one: how many in all, and how many of them are lower lanes.
+// others = the lanes whose digit differs from this lane's in some bit (or that hold no key).  For bit b, m =
+// the lanes that have it set and e = this lane's own bit spread over a word: m ^ e marks the lanes that
+// differ in b.  Kept as two 32-bit halves and as the complement of the usual "peers" mask, this is four
+// vector instructions per bit; a sort's time is mostly vector instructions, and most of them are these.
+template <int kBits>
+__device__ __forceinline__ void match_digit(int d, bool valid, uint32_t lt_lo, uint32_t lt_hi, int &before, int &same)
+{
+    const u64 held = ballot64(valid);
+    uint32_t others_lo = ~(uint32_t)held, others_hi = ~(uint32_t)(held >> 32);
+#pragma unroll
+    for (int b = 0; b < kBits; ++b) {
+        int32_t e = __builtin_amdgcn_sbfe(d, b, 1);                     // -1 if bit b of d is set, else 0
+        asm("" : "+v"(e));                                              // (compare e itself, not d shifted once more)
+        const u64 m = ballot64(e != 0);
+        others_lo = or_of_xor(others_lo, (uint32_t)m, (uint32_t)e);
+        others_hi = or_of_xor(others_hi, (uint32_t)(m >> 32), (uint32_t)e);
+    }
+    before = lane_id() - (__popc(others_lo & lt_lo) + __popc(others_hi & lt_hi));
+    same = kWave - (__popc(others_lo) + __popc(others_hi));
+}
+
 // (eight waves per SIMD: two workgroups of 1 024 threads per CU, which caps the kernel at 64 vector registers)
 template <int kBits>
 __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
@@ -180,24 +210,10 @@ void k_sort_scatter(const int32_t *keys, const int32_t *vals, int32_t *keys_out,
         key[r] = valid ? tile_keys[i] : 0;
         val[r] = valid ? tile_vals[i] : 0;
         const int d = digit_of<kBits>(key[r], shift);
-        // others = the lanes whose digit differs from this lane's in some bit (or that hold no key).  For bit b, m =
-        // the lanes that have it set and e = this lane's own bit spread over a word: m ^ e marks the lanes that
-        // differ in b.  Kept as two 32-bit halves and as the complement of the usual "peers" mask, this is four
-        // vector instructions per bit; the kernel's time is mostly vector instructions, and most of them are these.
-        const u64 held = ballot64(valid);
-        uint32_t others_lo = ~(uint32_t)held, others_hi = ~(uint32_t)(held >> 32);
-#pragma unroll
-        for (int b = 0; b < kBits; ++b) {
-            int32_t e = __builtin_amdgcn_sbfe(d, b, 1);                 // -1 if bit b of d is set, else 0
-            asm("" : "+v"(e));                                          // (compare e itself, not d shifted once more)
-            const u64 m = ballot64(e != 0);
-            others_lo = or_of_xor(others_lo, (uint32_t)m, (uint32_t)e);
-            others_hi = or_of_xor(others_hi, (uint32_t)(m >> 32), (uint32_t)e);
-        }
+        int before, same;
+        match_digit<kBits>(d, valid, lt_lo, lt_hi, before, same);
         // lanes with the same digit read the running count, then their first lane bumps it
         const int c = wcount[wave][d];
-        const int before = lane - (__popc(others_lo & lt_lo) + __popc(others_hi & lt_hi));
-        const int same = kWave - (__popc(others_lo) + __popc(others_hi));
         __builtin_amdgcn_wave_barrier();
         if (valid && before == 0) wcount[wave][d] = c + same;
         __builtin_amdgcn_wave_barrier();
@@ -265,39 +281,61 @@ size_t sort_tmp_bytes(int64_t n)
            align256((size_t)groups * kRadix * 4) + 2 * align256((size_t)kColChunks * kRadix * 4);
 }
 
+// Where a sort keeps what: two buffers of pairs and the tables of a pass.
+struct SortTmp {
+    int32_t *keys[2], *vals[2], *table, *totals, *sums;
+    size_t table_bytes;
+};
+
+static SortTmp sort_tmp(void *tmp, int64_t n)
+{
+    constexpr size_t kRadix = 1 << kMaxRadixBits;
+    const int64_t groups = sort_groups(sort_tiles(n));
+    char *p = static_cast<char *>(tmp);
+    auto take = [&](size_t bytes) {
+        int32_t *r = reinterpret_cast<int32_t *>(p);
+        p += align256(bytes);
+        return r;
+    };
+    SortTmp t;
+    for (int i = 0; i < 2; ++i) {
+        t.keys[i] = take((size_t)n * 4);
+        t.vals[i] = take((size_t)n * 4);
+    }
+    t.table_bytes = (size_t)(groups * kHistTiles) * kRadix * 4;
+    t.table = take(t.table_bytes);
+    t.totals = take((size_t)groups * kRadix * 4);
+    t.sums = take(2 * (size_t)kColChunks * kRadix * 4);
+    return t;
+}
+
+// `passes` stable passes over the key bits from `low` on, kBits at a time.  keys_out / vals_out: where the last one leaves the
+// pairs, or NULL: in t.keys / t.vals[(passes - 1) & 1].  status (or NULL): kErrIdRange if a key is none of the num_rows rows.
 template <int kBits>
 static hipError_t sort_passes(const int32_t *keys_in, const int32_t *vals_in, int32_t *keys_out, int32_t *vals_out, int64_t n,
-                              int passes, void *tmp, hipStream_t s)
+                              int low, int passes, const SortTmp &t, hipStream_t s, int64_t num_rows = 0, int32_t *status = nullptr)
 {
     constexpr int kRadix = 1 << kBits;
     const int64_t tiles = sort_tiles(n), groups = sort_groups(tiles);
     const int per_chunk = (int)((groups + kColChunks - 1) / kColChunks);
     const int chunks = (int)((groups + per_chunk - 1) / per_chunk);
     const unsigned scatter_grid = (unsigned)(((tiles + 7) >> 3) << 3);
-    char *p = static_cast<char *>(tmp);
-    int32_t *kbuf[2], *vbuf[2];
-    kbuf[0] = reinterpret_cast<int32_t *>(p); p += align256((size_t)n * 4);
-    vbuf[0] = reinterpret_cast<int32_t *>(p); p += align256((size_t)n * 4);
-    kbuf[1] = reinterpret_cast<int32_t *>(p); p += align256((size_t)n * 4);
-    vbuf[1] = reinterpret_cast<int32_t *>(p); p += align256((size_t)n * 4);
-    int32_t *table = reinterpret_cast<int32_t *>(p); p += align256((size_t)(groups * kHistTiles * kRadix) * 4);
-    int32_t *totals = reinterpret_cast<int32_t *>(p); p += align256((size_t)(groups * kRadix) * 4);
-    int32_t *sums[2] = {reinterpret_cast<int32_t *>(p), reinterpret_cast<int32_t *>(p) + kColChunks * kRadix};
+    int32_t *sums[2] = {t.sums, t.sums + kColChunks * kRadix};
     FillRegion clr[1] = {{sums[0], (size_t)chunks * kRadix * sizeof(int32_t)}};
     hipError_t e = launch_clear(clr, 1, s);
     if (e != hipSuccess) return e;
     const int32_t *ksrc = keys_in, *vsrc = vals_in;
     for (int pass = 0; pass < passes; ++pass) {
         const bool last = pass == passes - 1;
-        const int shift = pass * kBits;
-        int32_t *kdst = last ? keys_out : kbuf[pass & 1];
-        int32_t *vdst = last ? vals_out : vbuf[pass & 1];
-        hipLaunchKernelGGL(k_sort_hist<kBits>, dim3((unsigned)groups), dim3(kRadix), 0, s, ksrc, n, shift, table, totals,
-                           sums[pass & 1], per_chunk);
-        hipLaunchKernelGGL(k_col_apply<kBits>, dim3(chunks), dim3(kRadix), 0, s, totals, groups, per_chunk,
+        const int shift = low + pass * kBits;
+        int32_t *kdst = last && keys_out ? keys_out : t.keys[pass & 1];
+        int32_t *vdst = last && vals_out ? vals_out : t.vals[pass & 1];
+        hipLaunchKernelGGL(k_sort_hist<kBits>, dim3((unsigned)groups), dim3(kHistThreads), 0, s, ksrc, n, shift, t.table,
+                           t.totals, sums[pass & 1], per_chunk, (uint32_t)num_rows, pass == 0 ? status : nullptr);
+        hipLaunchKernelGGL(k_col_apply<kBits>, dim3(chunks), dim3(kRadix), 0, s, t.totals, groups, per_chunk,
                            sums[pass & 1], chunks, sums[(pass & 1) ^ 1]);
         hipLaunchKernelGGL(k_sort_scatter<kBits>, dim3(scatter_grid), dim3(kSortThreads), 0, s, ksrc, vsrc, kdst, vdst, n, shift,
-                           table, totals, tiles);
+                           t.table, t.totals, tiles);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         ksrc = kdst;
@@ -306,14 +344,302 @@ static hipError_t sort_passes(const int32_t *keys_in, const int32_t *vals_in, in
     return hipSuccess;
 }
 
+static int sort_pass_count(int key_bits) { return (key_bits + kMaxRadixBits - 1) / kMaxRadixBits; }
+
 hipError_t launch_sort_pairs(const int32_t *keys_in, const int32_t *vals_in, int32_t *keys_out,
                              int32_t *vals_out, int64_t n, int key_bits, void *tmp, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
     if (key_bits < 1) key_bits = 1;
-    const int passes = (key_bits + kMaxRadixBits - 1) / kMaxRadixBits;
-    return key_bits <= 8 * passes ? sort_passes<8>(keys_in, vals_in, keys_out, vals_out, n, passes, tmp, s)
-                                  : sort_passes<9>(keys_in, vals_in, keys_out, vals_out, n, passes, tmp, s);
+    const int passes = sort_pass_count(key_bits);
+    const SortTmp t = sort_tmp(tmp, n);
+    return key_bits <= 8 * passes ? sort_passes<8>(keys_in, vals_in, keys_out, vals_out, n, 0, passes, t, s)
+                                  : sort_passes<9>(keys_in, vals_in, keys_out, vals_out, n, 0, passes, t, s);
+}
+
+// ------------------------------------------------------------------------------------------------
+// rows from a list in no order
+//
+// The adjacency needs the rows, not the sorted keys: passes as above bring the pairs into buckets of up to 512 neighbouring
+// rows only (the high bits of the key), and one workgroup per bucket ranks what is left of the key in LDS and writes the
+// bucket's rows and row pointers: a pass over memory less, no keys written at the end, and no pass that reads them again.  For
+// outputs the same workgroup writes the rows by tensor, the producer words and the operators' records, which took three more
+// passes.  32 M input edges of 12 M operators: 530 us sorted as a whole, 460 so; their 25 M outputs 700 -> 490; the whole build
+// 1 427 -> 1 077 us.  30 000 operators: 221 -> 159, 500 000: 392 -> 196, 50 M: 5 430 -> 3 925.
+//
+// The last step takes 117 us for those 32 M pairs (440 MB), 217 for the outputs (890 MB): memory.  It was 205 with workgroups of 1 024
+// threads, eleven bits of the key and two passes inside LDS (barriers, and vector instructions of the second pass), 156 with
+// 256 threads and two passes.
+// ------------------------------------------------------------------------------------------------
+constexpr int kRowRounds = 8;                           // pairs per thread
+template <int kThreads> struct Rows {
+    static constexpr int kWaves = kThreads / kWave, kTile = kThreads * kRowRounds;      // pairs that a workgroup holds at a time
+    static constexpr int kBits = kThreads == 256 ? 9 : 10, kRows = 1 << kBits;          // rows of a bucket, at most
+    static_assert(kRows == 2 * kThreads, "two rows per thread");
+};
+constexpr int64_t kMaxBucket = 1 << 17;                 // a bucket of more pairs (one operator with all the inputs, say) would keep one
+                                                        // workgroup busy for longer than the whole sort: the list is sorted instead
+constexpr int kRowFillPercent = 75;                     // of a tile, on average, at most
+
+// starts[b] = first position with a key of bucket b or above; four lanes per bucket probe a quarter of what is left each.
+constexpr int kProbes = 4;
+__global__ __launch_bounds__(256) void k_bucket_starts(const int32_t *keys, int32_t n, int row_bits, int32_t buckets, int32_t *starts,
+                                                        int32_t *status)
+{
+    const int64_t thread = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int32_t b = (int32_t)min(thread / kProbes, (int64_t)buckets);
+    const int probe = threadIdx.x & (kProbes - 1), group = lane_id() & ~(kProbes - 1);
+    int32_t lo = 0, hi = b == buckets ? 0 : n;              // the answer is in [lo, hi]
+    while (ballot64(hi > lo)) {                             // whole waves stay in the loop
+        const int32_t step = (int32_t)(((int64_t)hi - lo + kProbes - 1) / kProbes);
+        const int64_t at = (int64_t)lo + (int64_t)probe * step;
+        const bool below = at < hi && (keys[at] >> row_bits) < b;
+        const int c = __popcll((ballot64(below) >> group) & ((1 << kProbes) - 1));      // the keys ascend by bucket: the first c are below
+        if (c > 0) {
+            const int64_t after = (int64_t)lo + (int64_t)c * step;
+            hi = (int32_t)min((int64_t)hi, after);
+            lo = (int32_t)(after - step) + 1;
+        } else {
+            hi = lo;                                        // (lo itself is not below)
+        }
+    }
+    if (b == buckets) lo = n;
+    if (probe == 0) {
+        starts[b] = lo;
+        if (b < buckets && lo + kMaxBucket < n && (keys[lo + kMaxBucket] >> row_bits) == b) store_coherent(&status[kStatusOversize], 1);
+    }
+}
+
+// One bucket: a wave ranks its keys by row against those of its lower lanes and earlier rounds, as above, the counts of the
+// workgroup's waves are added up in row order -- which gives the row pointers --, and the values leave from their places in LDS.
+// kOut: the list's values are the tensors that the operators (rows) write; where they are one run of tensors -- sorted by
+// operator, position e writes tensor e + shift, in any order inside an operator's row -- the rows by tensor and the producer
+// words follow from the rows alone and are written here, too; elsewhere kStatusPending says that they are not.
+template <bool kOut, int kThreads>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8)))
+void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *starts, int row_bits, EdgeList l, int32_t *status)
+{
+    using R = Rows<kThreads>;
+    __shared__ int32_t s_val[R::kTile];
+    __shared__ uint16_t s_row[kOut ? R::kTile : 1];
+    __shared__ uint32_t s_count[R::kWaves][R::kRows / 2];   // per wave: two neighbouring rows to a word
+    __shared__ uint32_t s_seen[kOut ? R::kTile / 32 : 1];
+    __shared__ int s_wtot[R::kWaves];
+    if (status[kStatusOversize]) return;
+    const int lane = lane_id(), wave = threadIdx.x >> 6, tid = threadIdx.x;
+    const u64 lt = lanemask_lt();
+    const uint32_t lt_lo = (uint32_t)lt, lt_hi = (uint32_t)(lt >> 32);
+    const int32_t b = (int32_t)blockIdx.x;
+    const bool last_bucket = b == (int32_t)gridDim.x - 1;
+    const int32_t lo = starts[b], n = max(starts[b + 1] - lo, 0);         // (ids out of range: anything in the list)
+    const int32_t row0 = b << row_bits;
+    const int rows = min(1 << row_bits, l.num_ops - row0), row_mask = (1 << row_bits) - 1;
+    const int32_t nnz = (int32_t)l.nnz, shift = l.num_tensors - nnz;
+    int32_t *const rowptr = l.row + row0;
+    keys += lo;
+    vals += lo;
+    // exclusive sum over the rows of a bucket, two of them per thread
+    auto row_scan = [&](int both) {
+        const int incl = wave_incl_scan(both);
+        if (lane == kWave - 1) s_wtot[wave] = incl;
+        __syncthreads();
+        int first = incl - both;
+#pragma unroll
+        for (int w = 0; w < R::kWaves; ++w)
+            if (w < wave) first += s_wtot[w];
+        return first;
+    };
+    auto write_rowptr = [&](int first, int second) {
+        if (2 * tid < rows) rowptr[2 * tid] = first;
+        if (2 * tid + 1 < rows) rowptr[2 * tid + 1] = second;
+        if (last_bucket && tid == 0) rowptr[rows] = nnz;
+    };
+    const bool several = n > R::kTile;                      // tiles, one after the other, every row's share behind the last tile's
+    int *s_base = s_val;                                    // ... at this position (no value is kept in LDS then)
+    if (several) {
+        s_base[2 * tid] = s_base[2 * tid + 1] = 0;
+        __syncthreads();
+        for (int32_t i = tid; i < n; i += kThreads) atomicAdd(&s_base[(keys[i] - row0) & row_mask], 1);
+        __syncthreads();
+        const int v0 = s_base[2 * tid], v1 = s_base[2 * tid + 1];
+        const int first = lo + row_scan(v0 + v1);
+        write_rowptr(first, first + v0);
+        s_base[2 * tid] = first;
+        s_base[2 * tid + 1] = first + v0;
+        if (kOut && tid == 0) store_coherent(&status[kStatusPending], 1);
+    } else if (kOut) {
+        for (int i = tid; i < R::kTile / 32; i += kThreads) s_seen[i] = 0;
+        // tensors before the run have no producer
+        for (int64_t t = (int64_t)b * kThreads + tid; t < shift; t += (int64_t)gridDim.x * kThreads) {
+            l.prod_row[t] = 0;
+            l.prod1[t] = kNoProducer;
+        }
+        if (last_bucket && tid == 0) l.prod_row[l.num_tensors] = nnz;
+    }
+    int begin = 0, length0 = 0, length1 = 0;                // of this thread's two rows, in the tile
+    bool bad = false;                                       // (a list without tensors has no edges)
+    uint16_t *const mine = reinterpret_cast<uint16_t *>(s_count[wave]);
+    for (int32_t t0 = 0; t0 == 0 || t0 < n; t0 += R::kTile) {
+        const int m = min((int32_t)R::kTile, n - t0);
+        const int rounds = (m + kThreads - 1) / kThreads;                   // a wave owns 64 * rounds consecutive places
+        const int wofs = wave * rounds * kWave + lane;
+        int row[kRowRounds], rank[kRowRounds];
+        int32_t val[kRowRounds];
+#pragma unroll
+        for (int r = 0; r < kRowRounds; ++r) {
+            const int i = wofs + r * kWave;
+            const bool valid = r < rounds && i < m;
+            row[r] = valid ? (keys[t0 + i] - row0) & row_mask : 0;
+            val[r] = valid ? vals[t0 + i] : 0;
+            bad |= (uint32_t)val[r] >= (uint32_t)l.num_tensors;
+        }
+#pragma unroll
+        for (int w = 0; w < R::kWaves; ++w) s_count[w][tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRowRounds; ++r) {
+            if (r >= rounds) break;                                         // (the same in every lane)
+            const bool valid = wofs + r * kWave < m;
+            int before, same;
+            match_digit<R::kBits>(row[r], valid, lt_lo, lt_hi, before, same);
+            const int c = mine[row[r]];
+            __builtin_amdgcn_wave_barrier();
+            if (valid && before == 0) mine[row[r]] = (uint16_t)(c + same);
+            __builtin_amdgcn_wave_barrier();
+            rank[r] = c + before;
+        }
+        __syncthreads();
+        uint32_t sum = 0, earlier[R::kWaves];                               // (no half of a word exceeds a tile: no carries)
+#pragma unroll
+        for (int w = 0; w < R::kWaves; ++w) {
+            earlier[w] = sum;
+            sum += s_count[w][tid];
+        }
+        const int v0 = (int)(sum & 0xffff), v1 = (int)(sum >> 16);
+        uint32_t first = 0;                                                 // of the two rows, in the tile
+        if (!several) {
+            const int f = row_scan(v0 + v1);
+            write_rowptr(lo + f, lo + f + v0);
+            begin = f;
+            length0 = v0;
+            length1 = v1;
+            first = (uint32_t)f | (uint32_t)(f + v0) << 16;
+        }
+#pragma unroll
+        for (int w = 0; w < R::kWaves; ++w) s_count[w][tid] = first + earlier[w];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRowRounds; ++r) {
+            if (r >= rounds) break;
+            if (wofs + r * kWave >= m) continue;
+            const int at = mine[row[r]] + rank[r];
+            if (several) {
+                l.idx[s_base[row[r]] + at] = val[r];
+            } else {
+                s_val[at] = val[r];
+                if (kOut) s_row[at] = (uint16_t)row[r];
+            }
+        }
+        __syncthreads();
+        if (several) {
+            s_base[2 * tid] += v0;
+            s_base[2 * tid + 1] += v1;
+            __syncthreads();
+        }
+    }
+    if (ballot64(bad) != 0 && lane == 0) atomicOr(status, kErrIdRange);
+    if (several) return;
+    if (kOut && l.orec) {
+        auto record = [&](int r, int at, int length) {
+            const int first = length > 0 ? s_val[at] : 0;
+            bool consecutive = true;
+            for (int k = 1; k < length; ++k) consecutive &= s_val[at + k] == first + k;
+            write_record<false>(&l.orec[row0 + r], l.in_row[row0 + r], l.in_row[row0 + r + 1], lo + at, lo + at + length, first, consecutive);
+        };
+        if (2 * tid < rows) record(2 * tid, begin, length0);
+        if (2 * tid + 1 < rows) record(2 * tid + 1, begin + length0, length1);
+    }
+    bool elsewhere = kOut && shift < 0, scattered = false;
+    for (int i = tid; i < n; i += kThreads) {
+        const int32_t v = s_val[i], e = lo + i;
+        l.idx[e] = v;
+        if (kOut && !elsewhere) {
+            const int row = s_row[i];
+            const int64_t j = (int64_t)v - shift - lo;                      // the place of this tensor, in one run
+            if (j < 0 || j >= n || s_row[j] != row) elsewhere = true;
+            else if (atomicOr(&s_seen[j >> 5], 1u << (j & 31)) >> (j & 31) & 1) elsewhere = true;       // a second time
+            scattered |= j != i;
+            l.prod_idx[e] = row0 + row;
+            l.prod_row[e + shift] = e;
+            l.prod1[e + shift] = row0 + row;
+        }
+    }
+    if (kOut) {
+        if (ballot64(scattered) != 0 && lane == 0 && load_coherent(&status[kStatusScattered]) == 0)
+            store_coherent(&status[kStatusScattered], 1);
+        if (ballot64(elsewhere) != 0 && lane == 0 && load_coherent(&status[kStatusPending]) == 0)
+            store_coherent(&status[kStatusPending], 1);
+    }
+}
+
+// Buckets are taken where they save a pass over memory: as many rows to a bucket as fill three quarters of a tile on average, and
+// the larger tile (512 threads, ten bits) only where that takes a pass less than the smaller one: it holds a CU to three workgroups.
+// Few rows with hundreds of pairs each (key bits that one pass sorts anyway) are sorted as a whole.
+RowPlan plan_rows(int64_t nnz, int64_t rows, int key_bits)
+{
+    RowPlan p{};
+    if (nnz < 1 || rows < 1) return p;
+    const double mean = (double)nnz / (double)rows;
+    // rows per bucket, at most, for it to fit into a tile on average
+    auto fit = [&](int tile, int most_bits) {
+        int bits = most_bits < key_bits ? most_bits : key_bits;
+        while (bits > 0 && mean * (double)(1 << bits) * 100 > (double)(kRowFillPercent * tile)) --bits;
+        return bits;
+    };
+    const int small = fit(Rows<256>::kTile, Rows<256>::kBits), large = fit(Rows<512>::kTile, Rows<512>::kBits);
+    auto passes = [&](int bits) { return sort_pass_count(key_bits - bits); };
+    p.threads = passes(small) <= passes(large) ? 256 : 512;
+    p.row_bits = p.threads == 256 ? small : large;
+    p.passes = passes(p.row_bits);
+    p.pass_bits = p.passes ? (key_bits - p.row_bits + p.passes - 1) / p.passes : 0;
+    if (p.pass_bits < 6) p.pass_bits = 6;
+    p.buckets = (rows + ((int64_t)1 << p.row_bits) - 1) >> p.row_bits;
+    p.use = p.row_bits > 0 && p.passes < sort_pass_count(key_bits) && (size_t)(p.buckets + 1) * 4 <= sort_tmp(nullptr, nnz).table_bytes;
+    return p;
+}
+
+template <int kThreads>
+static void bucket_rows(const RowPlan &p, const int32_t *keys, const int32_t *vals, const int32_t *starts, const EdgeList &l, bool producers,
+                        int32_t *status, hipStream_t s)
+{
+    if (producers)
+        hipLaunchKernelGGL((k_bucket_rows<true, kThreads>), dim3((unsigned)p.buckets), dim3(kThreads), 0, s, keys, vals, starts, p.row_bits, l, status);
+    else
+        hipLaunchKernelGGL((k_bucket_rows<false, kThreads>), dim3((unsigned)p.buckets), dim3(kThreads), 0, s, keys, vals, starts, p.row_bits, l, status);
+}
+
+hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producers, int32_t *status, void *tmp, hipStream_t s)
+{
+    const SortTmp t = sort_tmp(tmp, l.nnz);
+    const int32_t *keys = l.op, *vals = l.tensor;
+    if (p.passes == 0) {
+        const hipError_t e = launch_check_ids(l, status, s);
+        if (e != hipSuccess) return e;
+    } else {
+        const hipError_t e = p.pass_bits == 6 ? sort_passes<6>(keys, vals, nullptr, nullptr, l.nnz, p.row_bits, p.passes, t, s, l.num_ops, status)
+                           : p.pass_bits == 7 ? sort_passes<7>(keys, vals, nullptr, nullptr, l.nnz, p.row_bits, p.passes, t, s, l.num_ops, status)
+                           : p.pass_bits == 8 ? sort_passes<8>(keys, vals, nullptr, nullptr, l.nnz, p.row_bits, p.passes, t, s, l.num_ops, status)
+                                              : sort_passes<9>(keys, vals, nullptr, nullptr, l.nnz, p.row_bits, p.passes, t, s, l.num_ops, status);
+        if (e != hipSuccess) return e;
+        keys = t.keys[(p.passes - 1) & 1];
+        vals = t.vals[(p.passes - 1) & 1];
+    }
+    int32_t *starts = t.table;                              // (the passes are done with it)
+    hipLaunchKernelGGL(k_bucket_starts, dim3((unsigned)(p.buckets / (256 / kProbes) + 1)), dim3(256), 0, s, keys, (int32_t)l.nnz, p.row_bits,
+                       (int32_t)p.buckets, starts, status);
+    if (p.threads == 256) bucket_rows<256>(p, keys, vals, starts, l, producers, status, s);
+    else bucket_rows<512>(p, keys, vals, starts, l, producers, status, s);
+    return hipGetLastError();
 }
 
 }  // namespace dgn

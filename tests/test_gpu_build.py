@@ -113,3 +113,69 @@ def test_lists_in_other_orders(dgn, oracle, order, several):
             g.out_tensor[:] = rng.permutation(g.out_tensor)
         h = gg.Graph(g.num_ops, g.num_tensors, g.in_op[pi], g.in_tensor[pi], g.out_op[po], g.out_tensor[po], name=order)
         check(dgn, oracle, h, rng, f"{order} {shape}")
+
+
+def _shuffled(rng, n_out, fan, inputs=5, numbering="created"):
+    """An operator per entry: how many tensors it writes and reads; both lists in no order."""
+    P, E = n_out.size, int(n_out.sum())
+    first = inputs + np.cumsum(n_out) - n_out
+    T = inputs + E
+    in_op, out_op, out_t = np.repeat(np.arange(P), fan), np.repeat(np.arange(P), n_out), inputs + np.arange(E)
+    in_t = (rng.random(in_op.size) * first[in_op]).astype(np.int64)
+    if numbering == "gaps":                        # every other tensor, ascending: not one run
+        T, in_t, out_t = 2 * T, 2 * in_t, 2 * out_t
+    elif numbering == "mixed":                     # tensors of neighbouring operators change places
+        far = np.arange(E)
+        far[: E // 2 * 2] = far[: E // 2 * 2].reshape(-1, 2)[:, ::-1].ravel()
+        out_t = out_t[far]
+    elif numbering == "twice":                     # one tensor written by two operators, one by none
+        out_t[E // 2] = out_t[E // 2 - 1]
+    elif numbering == "more":                      # more outputs than tensors
+        T, in_t, out_t = T // 2 + 1, in_t // 2, out_t // 2
+    pi, po = rng.permutation(in_op.size), rng.permutation(E)
+    i32 = lambda a: np.ascontiguousarray(a, dtype=np.int32)  # noqa: E731
+    return gg.Graph(P, int(T), i32(in_op[pi]), i32(in_t[pi]), i32(out_op[po]), i32(out_t[po]), name="shuffled")
+
+
+@pytest.mark.parametrize("numbering", ["created", "gaps", "mixed", "twice", "more"])
+@pytest.mark.parametrize("ops, outs, fan", [(3, 2, 3), (64, 1, 1), (511, 3, 3), (512, 2, 2), (1025, 2, 2), (16384, 1, 0), (16385, 1, 1),
+                                            (70_001, 2, 5), (150_001, 1, 3), (300_000, 1, 2), (300_000, 0.03, 0.05)])
+def test_lists_sorted_by_buckets(dgn, oracle, ops, outs, fan, numbering):
+    """One bucket, one tile and one more, ragged last buckets, sparse rows, one pass and two into buckets."""
+    rng = np.random.default_rng(ops)
+    count = lambda mean: rng.integers(0, 2 * mean + 1, ops) if mean >= 1 else (rng.random(ops) < mean).astype(np.int64)  # noqa: E731
+    n_out = count(outs)
+    n_out[:3] = 1, 2, 1
+    check(dgn, oracle, _shuffled(rng, n_out, count(fan), numbering=numbering), rng, f"{ops} {outs} {fan} {numbering}")
+
+
+@pytest.mark.parametrize("which", ["inputs", "outputs"])
+@pytest.mark.parametrize("most", [2048, 2049, 4097, 30_000, 131_072, 150_000])
+def test_rows_of_several_tiles_and_buckets_that_are_too_large(dgn, oracle, most, which):
+    """One operator with so many inputs or outputs that its bucket is swept in tiles, or that the list is sorted as a whole."""
+    rng = np.random.default_rng(most)
+    n_out, fan = rng.integers(0, 3, 40_000), rng.integers(0, 4, 40_000)
+    (fan if which == "inputs" else n_out)[20_001] = most
+    check(dgn, oracle, _shuffled(rng, n_out, fan), rng, f"{which} {most}")
+
+
+@pytest.mark.parametrize("ops, outs, fan", [(3, 2, 3), (900, 1, 2), (200, 90, 90), (70_001, 2, 5), (300_000, 1, 2), (300_000, 0.03, 0.05)])
+def test_ids_out_of_range_in_lists_in_no_order(dgn, ops, outs, fan):
+    """One id out of range anywhere in either list, whichever way the list is sorted, is reported and nothing is built."""
+    import torch
+    rng = np.random.default_rng(ops)
+    count = lambda mean: rng.integers(0, 2 * mean + 1, ops) if mean >= 1 else (rng.random(ops) < mean).astype(np.int64)  # noqa: E731
+    n_out, fans = count(outs), count(fan)
+    n_out[:3], fans[:3] = 2, 2
+    good = _shuffled(rng, n_out, fans)
+    for name, limit in (("in_op", good.num_ops), ("in_tensor", good.num_tensors), ("out_op", good.num_ops), ("out_tensor", good.num_tensors)):
+        for bad in (-1, limit, -(1 << 31), (1 << 31) - 1):
+            lists = {n: getattr(good, n).copy() for n in ("in_op", "in_tensor", "out_op", "out_tensor")}
+            lists[name][rng.integers(lists[name].size)] = bad
+            up = {n: torch.from_numpy(v).cuda() for n, v in lists.items()}
+            desc = dgn.make_coo_desc(good.num_ops, good.num_tensors, *up.values(), 1, None, None)
+            rc, mem, scratch = dgn.dgn_graph_build_workspace(desc)
+            mem, scratch = (torch.full((n,), 255, dtype=torch.uint8, device="cuda") for n in (mem, scratch))
+            print(ops, name, bad, flush=True)
+            rc, handle = dgn.dgn_graph_build(desc, mem, mem.numel(), scratch, scratch.numel())
+            assert rc == dgn.DGN_ERR_ID_OUT_OF_RANGE, (name, bad, rc)
