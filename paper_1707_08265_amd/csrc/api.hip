@@ -421,12 +421,12 @@ int enqueue_records(const dgn_graph *h, const GraphLayout &L, int32_t *status, c
     return DGN_OK;
 }
 
-// Rows by l.op of a list in no order, whose ids are checked unless they are known to be good.
-int sort_rows(const EdgeList &l, const BuildScratch &S, bool buckets, bool good, hipStream_t s)
+// Rows by l.op of a list in no order, whose ids are checked unless they are known to be good.  big: status word.
+int sort_rows(const EdgeList &l, const BuildScratch &S, bool buckets, bool good, int big, hipStream_t s)
 {
     const RowPlan plan = plan_rows(l.nnz, l.num_ops, key_bits_for(l.num_ops));
     if (buckets && plan.use) {
-        DGN_HIP(launch_bucket_rows(plan, l, false, S.status, S.sort_tmp, s));
+        DGN_HIP(launch_bucket_rows(plan, l, false, S.status + big, S.status, S.sort_tmp, s));
         return DGN_OK;
     }
     if (!good) DGN_HIP(launch_check_ids(l, S.status, s));
@@ -445,7 +445,7 @@ int build_producers(const dgn_graph *h, const GraphLayout &L, const BuildScratch
         DGN_HIP(launch_row_bounds(keys, h->Eout, (int32_t)h->T, L.prod_rowptr, S.status, s));
     } else {
         const EdgeList list{h->v.out_idx, ops_of_out, h->Eout, (int32_t)h->T, (int32_t)h->P, L.prod_idx, L.prod_rowptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-        const int rc = sort_rows(list, S, buckets, true, s);
+        const int rc = sort_rows(list, S, buckets, true, kStatusBig + 2, s);
         if (rc) return rc;
     }
     DGN_HIP(launch_build_producers(h->v, L.prod1, S.status, s));
@@ -543,7 +543,7 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
     DGN_HIP(launch_clear(out_unsorted ? clr : order, 1, s));
     int rc = DGN_OK;
     if (f[kStatusInUnsorted]) {
-        rc = sort_rows(in, S, buckets, false, s);
+        rc = sort_rows(in, S, buckets, false, kStatusBig, s);
         if (rc) return rc;
     } else if (f[kStatusInGap]) {
         DGN_HIP(launch_row_bounds(in.op, in.nnz, (int32_t)P, L.in_rowptr, S.status, s));
@@ -557,7 +557,7 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
             EdgeList with = out;
             with.orec = walked(h) ? nullptr : L.orec;
             with.in_row = L.in_rowptr;
-            DGN_HIP(launch_bucket_rows(plan, with, true, S.status, S.sort_tmp, s));
+            DGN_HIP(launch_bucket_rows(plan, with, true, S.status + kStatusBig + 1, S.status, S.sort_tmp, s));
             rc = enqueue_records(h, L, S.status, options, s, true);
             if (rc) return rc;
             rc = read_status(S.status, s, found);

@@ -300,6 +300,7 @@ enum : int {
     kStatusOrder = 8,            // (so many words say whether there is an adjacency; the following describe it)
     kStatusOversize = 8,         // lists that were to be sorted by buckets have a bucket that is too large: they are sorted as a whole
     kStatusPending = 10,         // ... and rows by tensor that do not follow from the rows by operator
+    kStatusBig = 11,             // ... how many of them are large: inputs, outputs, outputs by tensor
     kStatusMulti = 16,           // some tensor has several producers
     kStatusScattered = 17,       // the outputs are not one run of tensors up to the last one
     kStatusRing = 20,            // what k_records_and_check finds out for the ring sweep: [0] != 0: outputs are not one run or
@@ -329,7 +330,8 @@ struct RowPlan { bool use; int row_bits, passes, pass_bits, threads; int64_t buc
 RowPlan plan_rows(int64_t nnz, int64_t rows, int key_bits);
 // l.row, l.idx and, with `producers`, the rows by tensor, producer words and records.  kErrIdRange: there are ids out of range;
 // kStatusOversize: nothing was written; kStatusPending: the rows by operator are written, those by tensor are not.  tmp: scratch of sort_tmp_bytes(l.nnz) bytes.
-hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producers, int32_t *status, void *tmp, hipStream_t s);
+// num_big: a word of the status, zero before.
+hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producers, int32_t *num_big, int32_t *status, void *tmp, hipStream_t s);
 // kErrIdRange if an edge of the list has an id out of range
 hipError_t launch_check_ids(const EdgeList &l, int32_t *status, hipStream_t s);
 // one pass over the input edges (NULL: the outputs only) and the output edges: checks them and, assuming that they are in

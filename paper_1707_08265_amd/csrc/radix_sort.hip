@@ -377,14 +377,17 @@ template <int kThreads> struct Rows {
     static constexpr int kBits = kThreads == 256 ? 9 : 10, kRows = 1 << kBits;          // rows of a bucket, at most
     static_assert(kRows == 2 * kThreads, "two rows per thread");
 };
-constexpr int64_t kMaxBucket = 1 << 17;                 // a bucket of more pairs (one operator with all the inputs, say) would keep one
-                                                        // workgroup busy for longer than the whole sort: the list is sorted instead
+// A bucket of more than a tile is done a tile after the other by its workgroup; one of more than kSerialTiles (an operator with very
+// many inputs, say) by as many workgroups as it has tiles, in a launch of its own.  There are few such buckets: with more than
+// kMaxBig of them, or one of more than kMaxBucket pairs (a tile adds up the counts of all the bucket's tiles), the list is sorted as a whole.
+constexpr int kSerialTiles = 8, kMaxBig = 64, kBigBlocks = 256;
+constexpr int64_t kMaxBucket = 1 << 21;
 constexpr int kRowFillPercent = 75;                     // of a tile, on average, at most
 
-// starts[b] = first position with a key of bucket b or above; four lanes per bucket probe a quarter of what is left each.
+// starts[b] = first position with a key of bucket b or above, big = the buckets of more than `most` pairs; four lanes per bucket probe a quarter of what is left each.
 constexpr int kProbes = 4;
-__global__ __launch_bounds__(256) void k_bucket_starts(const int32_t *keys, int32_t n, int row_bits, int32_t buckets, int32_t *starts,
-                                                        int32_t *status)
+__global__ __launch_bounds__(256) void k_bucket_starts(const int32_t *keys, int32_t n, int row_bits, int32_t buckets, int32_t most,
+                                                        int32_t *starts, int32_t *big, int32_t *num_big, int32_t *status)
 {
     const int64_t thread = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int32_t b = (int32_t)min(thread / kProbes, (int64_t)buckets);
@@ -406,7 +409,121 @@ __global__ __launch_bounds__(256) void k_bucket_starts(const int32_t *keys, int3
     if (b == buckets) lo = n;
     if (probe == 0) {
         starts[b] = lo;
-        if (b < buckets && lo + kMaxBucket < n && (keys[lo + kMaxBucket] >> row_bits) == b) store_coherent(&status[kStatusOversize], 1);
+        auto more_than = [&](int64_t pairs) { return lo + pairs < n && (keys[lo + pairs] >> row_bits) == b; };
+        if (b < buckets && more_than(most)) {
+            const int at = atomicAdd(num_big, 1);
+            if (at < kMaxBig) big[at] = b;
+            if (at >= kMaxBig || more_than(kMaxBucket)) store_coherent(&status[kStatusOversize], 1);
+        }
+    }
+}
+
+// The pairs of a tile in registers, ranked: rank[r] = keys of the same row before this one among those of its wave, counted in
+// `count` (per wave, two neighbouring rows to a word).  Whole workgroup; ends with a barrier.
+struct TilePairs {
+    int row[kRowRounds], rank[kRowRounds];
+    int32_t val[kRowRounds];
+    int rounds, first;                                      // a wave owns 64 * rounds consecutive places of the tile
+};
+
+template <int kThreads>
+__device__ __forceinline__ void rank_tile(const int32_t *keys, const int32_t *vals, int m, int32_t row0, int row_mask, int32_t num_tensors,
+                                          uint32_t (*count)[Rows<kThreads>::kRows / 2], TilePairs &p, bool &bad)
+{
+    using R = Rows<kThreads>;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const u64 lt = lanemask_lt();
+    const uint32_t lt_lo = (uint32_t)lt, lt_hi = (uint32_t)(lt >> 32);
+    uint16_t *const mine = reinterpret_cast<uint16_t *>(count[wave]);
+    p.rounds = (m + kThreads - 1) / kThreads;
+    p.first = wave * p.rounds * kWave + lane;
+#pragma unroll
+    for (int r = 0; r < kRowRounds; ++r) {
+        const int i = p.first + r * kWave;
+        const bool valid = r < p.rounds && i < m;
+        p.row[r] = valid ? (keys[i] - row0) & row_mask : 0;
+        p.val[r] = valid ? vals[i] : 0;
+        bad |= (uint32_t)p.val[r] >= (uint32_t)num_tensors;
+    }
+#pragma unroll
+    for (int w = 0; w < R::kWaves; ++w) count[w][threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRowRounds; ++r) {
+        if (r >= p.rounds) break;                                           // (the same in every lane)
+        const bool valid = p.first + r * kWave < m;
+        int before, same;
+        match_digit<R::kBits>(p.row[r], valid, lt_lo, lt_hi, before, same);
+        const int c = mine[p.row[r]];
+        __builtin_amdgcn_wave_barrier();
+        if (valid && before == 0) mine[p.row[r]] = (uint16_t)(c + same);
+        __builtin_amdgcn_wave_barrier();
+        p.rank[r] = c + before;
+    }
+    __syncthreads();
+}
+
+// Exclusive sum over the rows of a bucket, two of them per thread.  Whole workgroup; one barrier.
+template <int kThreads>
+__device__ __forceinline__ int row_scan(int both, int *s_wtot)
+{
+    const int wave = threadIdx.x >> 6, incl = wave_incl_scan(both);
+    if (lane_id() == kWave - 1) s_wtot[wave] = incl;
+    __syncthreads();
+    int first = incl - both;
+#pragma unroll
+    for (int w = 0; w < Rows<kThreads>::kWaves; ++w)
+        if (w < wave) first += s_wtot[w];
+    return first;
+}
+
+// Adds up the counts of the waves: every wave's count becomes the place (from first[0], first[1] on) of its keys of the row.  v0, v1: the
+// workgroup's counts of this thread's two rows.  Ends with a barrier.
+template <int kThreads, typename First>
+__device__ __forceinline__ void place_rows(uint32_t (*count)[Rows<kThreads>::kRows / 2], int &v0, int &v1, First first)
+{
+    using R = Rows<kThreads>;
+    uint32_t sum = 0, earlier[R::kWaves];                                   // (no half of a word exceeds a tile: no carries)
+#pragma unroll
+    for (int w = 0; w < R::kWaves; ++w) {
+        earlier[w] = sum;
+        sum += count[w][threadIdx.x];
+    }
+    v0 = (int)(sum & 0xffff);
+    v1 = (int)(sum >> 16);
+    const uint32_t at = first(v0, v1);
+#pragma unroll
+    for (int w = 0; w < R::kWaves; ++w) count[w][threadIdx.x] = at + earlier[w];
+    __syncthreads();
+}
+
+// How often the rows of a bucket occur among n keys.  Most may be of one row: its lanes add together.  Whole workgroup; the counts are
+// zero before; ends with a barrier.
+template <int kThreads>
+__device__ __forceinline__ void count_rows(const int32_t *keys, int32_t n, int32_t row0, int row_mask, int *s_rows)
+{
+    for (int32_t i0 = threadIdx.x & ~(kWave - 1); i0 < n; i0 += kThreads) {  // (whole waves)
+        const int32_t i = i0 + lane_id();
+        const int row = i < n ? (keys[i] - row0) & row_mask : -1;
+        const int most = __builtin_amdgcn_readfirstlane(row);
+        const u64 m = ballot64(row == most);
+        if (lane_id() == 0) atomicAdd(&s_rows[most], __popcll(m));
+        else if (row >= 0 && row != most) atomicAdd(&s_rows[row], 1);
+    }
+    __syncthreads();
+}
+
+// Big buckets: f(bucket, its first pair, its pairs, tile, its first tile in the table) for every tile of theirs that workgroup
+// `block` of `blocks` takes.
+template <int kThreads, typename F>
+__device__ __forceinline__ void big_tiles(const int32_t *starts, const int32_t *big, int num_big, int block, int blocks, F f)
+{
+    int table0 = 0;
+    for (int e = 0; e < num_big; ++e) {
+        const int32_t b = big[e], lo = starts[b], n = starts[b + 1] - lo;
+        const int tiles = (n + Rows<kThreads>::kTile - 1) / Rows<kThreads>::kTile;
+        for (int t = ((block - table0) % blocks + blocks) % blocks; t < tiles; t += blocks) f(b, lo, n, t, table0);
+        table0 += tiles;
     }
 }
 
@@ -417,60 +534,60 @@ __global__ __launch_bounds__(256) void k_bucket_starts(const int32_t *keys, int3
 // words follow from the rows alone and are written here, too; elsewhere kStatusPending says that they are not.
 template <bool kOut, int kThreads>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8)))
-void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *starts, int row_bits, EdgeList l, int32_t *status)
+void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *starts, int32_t buckets, int row_bits, const int32_t *big,
+                   const int32_t *num_big, int32_t *big_table, EdgeList l, int32_t *status)
 {
     using R = Rows<kThreads>;
     __shared__ int32_t s_val[R::kTile];
     __shared__ uint16_t s_row[kOut ? R::kTile : 1];
-    __shared__ uint32_t s_count[R::kWaves][R::kRows / 2];   // per wave: two neighbouring rows to a word
+    __shared__ uint32_t s_count[R::kWaves][R::kRows / 2];
     __shared__ uint32_t s_seen[kOut ? R::kTile / 32 : 1];
     __shared__ int s_wtot[R::kWaves];
-    if (status[kStatusOversize]) return;
+    if (status[kStatusOversize] || status[0]) return;       // (a key that is no row: the starts need not ascend)
     const int lane = lane_id(), wave = threadIdx.x >> 6, tid = threadIdx.x;
-    const u64 lt = lanemask_lt();
-    const uint32_t lt_lo = (uint32_t)lt, lt_hi = (uint32_t)(lt >> 32);
+    const int row_mask = (1 << row_bits) - 1;
+    int *s_base = s_val;                                    // of a bucket of several tiles (no value is kept in LDS then)
+    if (blockIdx.x >= (unsigned)buckets) {                  // the rows of big buckets are counted by tiles
+        big_tiles<kThreads>(starts, big, *num_big, (int)(blockIdx.x - buckets), kBigBlocks, [&](int32_t b, int32_t lo, int32_t n, int t, int table0) {
+            const int32_t at = lo + t * R::kTile;
+            s_base[2 * tid] = s_base[2 * tid + 1] = 0;
+            __syncthreads();
+            count_rows<kThreads>(keys + at, min((int32_t)R::kTile, lo + n - at), b << row_bits, row_mask, s_base);
+            reinterpret_cast<int2 *>(big_table + (int64_t)(table0 + t) * R::kRows)[tid] = make_int2(s_base[2 * tid], s_base[2 * tid + 1]);
+            __syncthreads();
+        });
+        return;
+    }
     const int32_t b = (int32_t)blockIdx.x;
-    const bool last_bucket = b == (int32_t)gridDim.x - 1;
-    const int32_t lo = starts[b], n = max(starts[b + 1] - lo, 0);         // (ids out of range: anything in the list)
+    const bool last_bucket = b == buckets - 1;
+    const int32_t lo = starts[b], n = starts[b + 1] - lo;
     const int32_t row0 = b << row_bits;
-    const int rows = min(1 << row_bits, l.num_ops - row0), row_mask = (1 << row_bits) - 1;
+    const int rows = min(1 << row_bits, l.num_ops - row0);
     const int32_t nnz = (int32_t)l.nnz, shift = l.num_tensors - nnz;
     int32_t *const rowptr = l.row + row0;
     keys += lo;
     vals += lo;
-    // exclusive sum over the rows of a bucket, two of them per thread
-    auto row_scan = [&](int both) {
-        const int incl = wave_incl_scan(both);
-        if (lane == kWave - 1) s_wtot[wave] = incl;
-        __syncthreads();
-        int first = incl - both;
-#pragma unroll
-        for (int w = 0; w < R::kWaves; ++w)
-            if (w < wave) first += s_wtot[w];
-        return first;
-    };
     auto write_rowptr = [&](int first, int second) {
         if (2 * tid < rows) rowptr[2 * tid] = first;
         if (2 * tid + 1 < rows) rowptr[2 * tid + 1] = second;
         if (last_bucket && tid == 0) rowptr[rows] = nnz;
     };
     const bool several = n > R::kTile;                      // tiles, one after the other, every row's share behind the last tile's
-    int *s_base = s_val;                                    // ... at this position (no value is kept in LDS then)
     if (several) {
+        if (kOut && tid == 0) store_coherent(&status[kStatusPending], 1);
+        if (n > kSerialTiles * R::kTile) return;            // (k_big_rows)
         s_base[2 * tid] = s_base[2 * tid + 1] = 0;
         __syncthreads();
-        for (int32_t i = tid; i < n; i += kThreads) atomicAdd(&s_base[(keys[i] - row0) & row_mask], 1);
-        __syncthreads();
+        count_rows<kThreads>(keys, n, row0, row_mask, s_base);
         const int v0 = s_base[2 * tid], v1 = s_base[2 * tid + 1];
-        const int first = lo + row_scan(v0 + v1);
+        const int first = lo + row_scan<kThreads>(v0 + v1, s_wtot);
         write_rowptr(first, first + v0);
         s_base[2 * tid] = first;
         s_base[2 * tid + 1] = first + v0;
-        if (kOut && tid == 0) store_coherent(&status[kStatusPending], 1);
     } else if (kOut) {
         for (int i = tid; i < R::kTile / 32; i += kThreads) s_seen[i] = 0;
         // tensors before the run have no producer
-        for (int64_t t = (int64_t)b * kThreads + tid; t < shift; t += (int64_t)gridDim.x * kThreads) {
+        for (int64_t t = (int64_t)b * kThreads + tid; t < shift; t += (int64_t)buckets * kThreads) {
             l.prod_row[t] = 0;
             l.prod1[t] = kNoProducer;
         }
@@ -478,72 +595,33 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
     }
     int begin = 0, length0 = 0, length1 = 0;                // of this thread's two rows, in the tile
     bool bad = false;                                       // (a list without tensors has no edges)
-    uint16_t *const mine = reinterpret_cast<uint16_t *>(s_count[wave]);
+    const uint16_t *const mine = reinterpret_cast<const uint16_t *>(s_count[wave]);
     for (int32_t t0 = 0; t0 == 0 || t0 < n; t0 += R::kTile) {
         const int m = min((int32_t)R::kTile, n - t0);
-        const int rounds = (m + kThreads - 1) / kThreads;                   // a wave owns 64 * rounds consecutive places
-        const int wofs = wave * rounds * kWave + lane;
-        int row[kRowRounds], rank[kRowRounds];
-        int32_t val[kRowRounds];
+        TilePairs p;
+        rank_tile<kThreads>(keys + t0, vals + t0, m, row0, row_mask, l.num_tensors, s_count, p, bad);
+        place_rows<kThreads>(s_count, length0, length1, [&](int v0, int v1) -> uint32_t {
+            if (several) return 0;
+            begin = row_scan<kThreads>(v0 + v1, s_wtot);
+            write_rowptr(lo + begin, lo + begin + v0);
+            return (uint32_t)begin | (uint32_t)(begin + v0) << 16;
+        });
 #pragma unroll
         for (int r = 0; r < kRowRounds; ++r) {
-            const int i = wofs + r * kWave;
-            const bool valid = r < rounds && i < m;
-            row[r] = valid ? (keys[t0 + i] - row0) & row_mask : 0;
-            val[r] = valid ? vals[t0 + i] : 0;
-            bad |= (uint32_t)val[r] >= (uint32_t)l.num_tensors;
-        }
-#pragma unroll
-        for (int w = 0; w < R::kWaves; ++w) s_count[w][tid] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < kRowRounds; ++r) {
-            if (r >= rounds) break;                                         // (the same in every lane)
-            const bool valid = wofs + r * kWave < m;
-            int before, same;
-            match_digit<R::kBits>(row[r], valid, lt_lo, lt_hi, before, same);
-            const int c = mine[row[r]];
-            __builtin_amdgcn_wave_barrier();
-            if (valid && before == 0) mine[row[r]] = (uint16_t)(c + same);
-            __builtin_amdgcn_wave_barrier();
-            rank[r] = c + before;
-        }
-        __syncthreads();
-        uint32_t sum = 0, earlier[R::kWaves];                               // (no half of a word exceeds a tile: no carries)
-#pragma unroll
-        for (int w = 0; w < R::kWaves; ++w) {
-            earlier[w] = sum;
-            sum += s_count[w][tid];
-        }
-        const int v0 = (int)(sum & 0xffff), v1 = (int)(sum >> 16);
-        uint32_t first = 0;                                                 // of the two rows, in the tile
-        if (!several) {
-            const int f = row_scan(v0 + v1);
-            write_rowptr(lo + f, lo + f + v0);
-            begin = f;
-            length0 = v0;
-            length1 = v1;
-            first = (uint32_t)f | (uint32_t)(f + v0) << 16;
-        }
-#pragma unroll
-        for (int w = 0; w < R::kWaves; ++w) s_count[w][tid] = first + earlier[w];
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < kRowRounds; ++r) {
-            if (r >= rounds) break;
-            if (wofs + r * kWave >= m) continue;
-            const int at = mine[row[r]] + rank[r];
+            if (r >= p.rounds) break;
+            if (p.first + r * kWave >= m) continue;
+            const int at = mine[p.row[r]] + p.rank[r];
             if (several) {
-                l.idx[s_base[row[r]] + at] = val[r];
+                l.idx[s_base[p.row[r]] + at] = p.val[r];
             } else {
-                s_val[at] = val[r];
-                if (kOut) s_row[at] = (uint16_t)row[r];
+                s_val[at] = p.val[r];
+                if (kOut) s_row[at] = (uint16_t)p.row[r];
             }
         }
         __syncthreads();
         if (several) {
-            s_base[2 * tid] += v0;
-            s_base[2 * tid + 1] += v1;
+            s_base[2 * tid] += length0;
+            s_base[2 * tid + 1] += length1;
             __syncthreads();
         }
     }
@@ -582,6 +660,59 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
     }
 }
 
+// Big buckets, a workgroup per tile: the counts of the bucket's tiles give its rows and where this tile's share of each begins.
+template <int kThreads>
+__global__ __launch_bounds__(kThreads)
+void k_big_rows(const int32_t *keys, const int32_t *vals, const int32_t *starts, int32_t buckets, int row_bits, const int32_t *big,
+                const int32_t *num_big, const int32_t *big_table, EdgeList l, int32_t *status)
+{
+    using R = Rows<kThreads>;
+    __shared__ uint32_t s_count[R::kWaves][R::kRows / 2];
+    __shared__ int s_base[R::kRows];
+    __shared__ int s_wtot[R::kWaves];
+    const int found = *num_big;
+    if (found == 0 || status[kStatusOversize] || status[0]) return;
+    const int wave = threadIdx.x >> 6, tid = threadIdx.x;
+    bool bad = false;
+    big_tiles<kThreads>(starts, big, found, (int)blockIdx.x, kBigBlocks, [&](int32_t b, int32_t lo, int32_t n, int t, int table0) {
+        const int tiles = (n + R::kTile - 1) / R::kTile;
+        const int32_t row0 = b << row_bits;
+        const int rows = min(1 << row_bits, l.num_ops - row0);
+        int all0 = 0, all1 = 0, before0 = 0, before1 = 0;   // of this thread's two rows: in the bucket, in earlier tiles
+        const int2 *table = reinterpret_cast<const int2 *>(big_table + (int64_t)table0 * R::kRows) + tid;
+#pragma unroll 8
+        for (int k = 0; k < tiles; ++k) {
+            const int2 c = table[(int64_t)k * (R::kRows / 2)];
+            all0 += c.x;
+            all1 += c.y;
+            before0 += k < t ? c.x : 0;
+            before1 += k < t ? c.y : 0;
+        }
+        const int first = lo + row_scan<kThreads>(all0 + all1, s_wtot);
+        if (t == 0) {
+            if (2 * tid < rows) l.row[row0 + 2 * tid] = first;
+            if (2 * tid + 1 < rows) l.row[row0 + 2 * tid + 1] = first + all0;
+            if (b == buckets - 1 && tid == 0) l.row[l.num_ops] = (int32_t)l.nnz;
+        }
+        s_base[2 * tid] = first + before0;
+        s_base[2 * tid + 1] = first + all0 + before1;
+        const int32_t at = lo + t * R::kTile;
+        const int m = min((int32_t)R::kTile, lo + n - at);
+        TilePairs p;
+        rank_tile<kThreads>(keys + at, vals + at, m, row0, (1 << row_bits) - 1, l.num_tensors, s_count, p, bad);
+        int v0, v1;
+        place_rows<kThreads>(s_count, v0, v1, [](int, int) -> uint32_t { return 0; });
+        const uint16_t *mine = reinterpret_cast<const uint16_t *>(s_count[wave]);
+#pragma unroll
+        for (int r = 0; r < kRowRounds; ++r) {
+            if (r >= p.rounds) break;
+            if (p.first + r * kWave < m) l.idx[s_base[p.row[r]] + mine[p.row[r]] + p.rank[r]] = p.val[r];
+        }
+        __syncthreads();
+    });
+    if (ballot64(bad) != 0 && lane_id() == 0) atomicOr(status, kErrIdRange);
+}
+
 // Buckets are taken where they save a pass over memory: as many rows to a bucket as fill three quarters of a tile on average, and
 // the larger tile (512 threads, ten bits) only where that takes a pass less than the smaller one: it holds a CU to three workgroups.
 // Few rows with hundreds of pairs each (key bits that one pass sorts anyway) are sorted as a whole.
@@ -609,16 +740,29 @@ RowPlan plan_rows(int64_t nnz, int64_t rows, int key_bits)
 }
 
 template <int kThreads>
-static void bucket_rows(const RowPlan &p, const int32_t *keys, const int32_t *vals, const int32_t *starts, const EdgeList &l, bool producers,
-                        int32_t *status, hipStream_t s)
+static hipError_t bucket_rows(const RowPlan &p, const int32_t *keys, const int32_t *vals, int32_t *big_table, const EdgeList &l, bool producers,
+                              int32_t *num_big, int32_t *status, const SortTmp &t, hipStream_t s)
 {
+    const int32_t buckets = (int32_t)p.buckets;
+    int32_t *starts = t.table, *big = t.totals;             // (the passes are done with them)
+    hipLaunchKernelGGL(k_bucket_starts, dim3((unsigned)(buckets / (256 / kProbes) + 1)), dim3(256), 0, s, keys, (int32_t)l.nnz, p.row_bits,
+                       buckets, kSerialTiles * Rows<kThreads>::kTile, starts, big, num_big, status);
+    // (a short list has no big bucket)
+    const bool may_be_big = l.nnz > kSerialTiles * Rows<kThreads>::kTile;
+    const dim3 grid((unsigned)(buckets + (may_be_big ? kBigBlocks : 0)));
     if (producers)
-        hipLaunchKernelGGL((k_bucket_rows<true, kThreads>), dim3((unsigned)p.buckets), dim3(kThreads), 0, s, keys, vals, starts, p.row_bits, l, status);
+        hipLaunchKernelGGL((k_bucket_rows<true, kThreads>), grid, dim3(kThreads), 0, s, keys, vals, starts, buckets, p.row_bits, big, num_big,
+                           big_table, l, status);
     else
-        hipLaunchKernelGGL((k_bucket_rows<false, kThreads>), dim3((unsigned)p.buckets), dim3(kThreads), 0, s, keys, vals, starts, p.row_bits, l, status);
+        hipLaunchKernelGGL((k_bucket_rows<false, kThreads>), grid, dim3(kThreads), 0, s, keys, vals, starts, buckets, p.row_bits, big, num_big,
+                           big_table, l, status);
+    if (may_be_big)
+        hipLaunchKernelGGL(k_big_rows<kThreads>, dim3(kBigBlocks), dim3(kThreads), 0, s, keys, vals, starts, buckets, p.row_bits, big, num_big,
+                           big_table, l, status);
+    return hipGetLastError();
 }
 
-hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producers, int32_t *status, void *tmp, hipStream_t s)
+hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producers, int32_t *num_big, int32_t *status, void *tmp, hipStream_t s)
 {
     const SortTmp t = sort_tmp(tmp, l.nnz);
     const int32_t *keys = l.op, *vals = l.tensor;
@@ -634,12 +778,10 @@ hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producer
         keys = t.keys[(p.passes - 1) & 1];
         vals = t.vals[(p.passes - 1) & 1];
     }
-    int32_t *starts = t.table;                              // (the passes are done with it)
-    hipLaunchKernelGGL(k_bucket_starts, dim3((unsigned)(p.buckets / (256 / kProbes) + 1)), dim3(256), 0, s, keys, (int32_t)l.nnz, p.row_bits,
-                       (int32_t)p.buckets, starts, status);
-    if (p.threads == 256) bucket_rows<256>(p, keys, vals, starts, l, producers, status, s);
-    else bucket_rows<512>(p, keys, vals, starts, l, producers, status, s);
-    return hipGetLastError();
+    // counts of the big buckets' tiles: a byte per pair and a row per tile begun, in the buffer that the last pass read
+    int32_t *big_table = t.keys[p.passes & 1];
+    return p.threads == 256 ? bucket_rows<256>(p, keys, vals, big_table, l, producers, num_big, status, t, s)
+                            : bucket_rows<512>(p, keys, vals, big_table, l, producers, num_big, status, t, s);
 }
 
 }  // namespace dgn

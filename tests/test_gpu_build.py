@@ -150,12 +150,13 @@ def test_lists_sorted_by_buckets(dgn, oracle, ops, outs, fan, numbering):
 
 
 @pytest.mark.parametrize("which", ["inputs", "outputs"])
-@pytest.mark.parametrize("most", [2048, 2049, 4097, 30_000, 131_072, 150_000])
-def test_rows_of_several_tiles_and_buckets_that_are_too_large(dgn, oracle, most, which):
-    """One operator with so many inputs or outputs that its bucket is swept in tiles, or that the list is sorted as a whole."""
+@pytest.mark.parametrize("most, rows", [(2048, 1), (2049, 1), (4097, 2), (14_000, 1), (30_000, 1), (30_000, 3), (131_072, 1), (17_000, 70)])
+def test_rows_of_several_tiles_and_many_large_buckets(dgn, oracle, most, rows, which):
+    """Operators with so many inputs or outputs that their bucket is done in tiles by one workgroup or by several, and so many of
+    them that the list is sorted as a whole."""
     rng = np.random.default_rng(most)
     n_out, fan = rng.integers(0, 3, 40_000), rng.integers(0, 4, 40_000)
-    (fan if which == "inputs" else n_out)[20_001] = most
+    (fan if which == "inputs" else n_out)[39_999 - 571 * np.arange(rows)] = most
     check(dgn, oracle, _shuffled(rng, n_out, fan), rng, f"{which} {most}")
 
 
