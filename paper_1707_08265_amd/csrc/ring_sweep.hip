@@ -652,8 +652,10 @@ __global__ __launch_bounds__(1024) void k_ring_offsets(RingArgs a)
 }
 
 // Ordered compaction from the words and running counts of the sweep: the position of a kept operator is known from its
-// word alone, so a wave takes any word of its graph, four in flight.  The first workgroup also leaves the header
-// for recycling and hands the status to the host.
+// word alone, so a wave takes any four words of its graph at a time.  Memory bounds it: neighbouring words go to one wave and
+// neighbouring waves, so that the lines that two words share are written at one time in one cache (4 096 graphs of 20 000 operators:
+// 345 us with the words dealt to the waves in turn, 298 = 4.5 TB/s so).  The first workgroup also leaves the header for recycling and
+// hands the status to the host.
 constexpr int kRingScatterThreads = 256;
 
 __global__ __launch_bounds__(kRingScatterThreads) void k_ring_scatter(RingArgs a)
@@ -679,27 +681,28 @@ __global__ __launch_bounds__(kRingScatterThreads) void k_ring_scatter(RingArgs a
     const u64 *K = a.K + (int64_t)wd * g.num_ops;
     int32_t *kept_ops = a.kept_ops + (int64_t)wd * g.num_ops;
     u64 *kept_masks = a.kept_masks ? a.kept_masks + (int64_t)wd * g.num_ops : nullptr;
-    const int64_t waves = (int64_t)gridDim.y * (kRingScatterThreads / kWave);
-    const int64_t wave_id = (int64_t)blockIdx.y * (kRingScatterThreads / kWave) + (threadIdx.x >> 6);
-    for (int64_t w0 = wave_id; w0 < n_words; w0 += 4 * waves) {
+    constexpr int kStep = kRingScatterThreads / kWave * 4;
+    const int64_t per = ((n_words + gridDim.y - 1) / gridDim.y + kStep - 1) / kStep * kStep;  // words of this workgroup
+    const int64_t stop = min(n_words, (blockIdx.y + 1) * per);
+    for (int64_t w0 = blockIdx.y * per + (threadIdx.x >> 6) * 4; w0 < stop; w0 += kStep) {
         u64 bits[4], k[4];
         int cum[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int64_t w = w0 + c * waves;
-            bits[c] = w < n_words ? a.bits[first + w] : 0;
-            cum[c] = w < n_words ? a.cum[first + w] : 0;
+            const int64_t w = w0 + c;
+            bits[c] = w < stop ? a.bits[first + w] : 0;
+            cum[c] = w < stop ? a.cum[first + w] : 0;
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const bool has = (bits[c] >> lane) & 1;
-            k[c] = has && kept_masks ? K[o_lo + (w0 + c * waves) * kWave + lane] : 0;
+            k[c] = has && kept_masks ? K[o_lo + (w0 + c) * kWave + lane] : 0;
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             if ((bits[c] >> lane) & 1) {
                 const int64_t pos = end - cum[c] + __popcll(bits[c] & lanemask_lt());
-                kept_ops[pos] = (int32_t)(o_lo + (w0 + c * waves) * kWave + lane);
+                kept_ops[pos] = (int32_t)(o_lo + (w0 + c) * kWave + lane);
                 if (kept_masks) kept_masks[pos] = k[c];
             }
         }
