@@ -562,7 +562,7 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
             if (rc) return rc;
             rc = read_status(S.status, s, found);
             if (rc || (*found)[0] || (*found)[kStatusOversize] || !(*found)[kStatusPending]) return rc;
-            DGN_HIP(launch_expand_rows(L.out_rowptr, (int32_t)P, S.sorted_ops, s));
+            DGN_HIP(launch_expand_rows(L.out_rowptr, (int32_t)P, (int32_t)Eout, S.sorted_ops, S.status, s));
             DGN_HIP(launch_clear(clr, 1, s));
         } else {
             DGN_HIP(launch_check_ids(out, S.status, s));
@@ -728,34 +728,29 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
     const GraphLayout L = graph_layout(graph_mem, P, T, Ein, Eout, d->num_graphs, false);
     const BuildScratch S = build_scratch(scratch, Ein, Eout);
 
-    FillRegion clr[1] = {{S.status, 256}};
-    DGN_HIP(launch_clear(clr, 1, s));
-    // the borrowed arrays are checked before any kernel trusts them
-    DGN_HIP(launch_check_csr(d->in_rowptr, d->in_idx, (int32_t)P, (int32_t)Ein, (int32_t)T, S.status, s));
-    DGN_HIP(launch_check_csr(d->out_rowptr, d->out_idx, (int32_t)P, (int32_t)Eout, (int32_t)T, S.status, s));
-    const int32_t *found = nullptr;
-    rc = read_status(S.status, s, &found);
-    if (rc) return rc;
-    rc = error_bits_to_code(found[0]);
-    if (rc) return rc;
-
     dgn_graph *h = nullptr;
     rc = new_graph(&h);
     if (rc) return rc;
     h->P = P; h->T = T; h->Ein = Ein; h->Eout = Eout; h->G = d->num_graphs;
     h->v = GraphView{(int32_t)P, (int32_t)T, (int32_t)Ein, (int32_t)Eout, d->num_graphs, d->in_rowptr, d->in_idx,
                      d->out_rowptr, d->out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.prod1};
+    const int32_t *found = nullptr;
     auto fill = [&]() -> int {
+        FillRegion clr[1] = {{S.status, 256}};
+        DGN_HIP(launch_clear(clr, 1, s));
         int e = copy_offsets(h, L, d->graph_op_offsets, d->graph_tensor_offsets, s);
         if (e) return e;
+        // The borrowed arrays are checked before any kernel trusts them: what follows asks the status first, or reads a list that has no
+        // valid entry then.
+        DGN_HIP(launch_check_csr(h->v, S.status, s));
         // the outputs as a list in operator order: its tensors usually ascend as well, and the pass over it is all it takes
-        DGN_HIP(launch_expand_rows(d->out_rowptr, (int32_t)P, S.sorted_ops, s));
+        DGN_HIP(launch_expand_rows(d->out_rowptr, (int32_t)P, (int32_t)Eout, S.sorted_ops, S.status, s));
         const EdgeList list{S.sorted_ops, d->out_idx, Eout, (int32_t)P, (int32_t)T, nullptr, nullptr, L.prod_idx, L.prod_rowptr, L.prod1, nullptr, nullptr};
         DGN_HIP(launch_scan_edges(nullptr, list, S.status, s));
         e = enqueue_records(h, L, S.status, options, s);
         if (e) return e;
         e = read_status(S.status, s, &found);
-        if (e || !(found[kStatusProdUnsorted] || found[kStatusProdGap])) return e;
+        if (e || (found[0] & (kErrCsr | kErrIdRange)) || !(found[kStatusProdUnsorted] || found[kStatusProdGap])) return e;
         e = build_producers(h, L, S, S.sorted_ops, found[kStatusProdUnsorted] ? nullptr : d->out_idx, false, s);
         if (e) return e;
         FillRegion ready[1] = {{S.status, kStatusOrder * sizeof(int32_t)}};

@@ -351,9 +351,8 @@ hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *s
 hipError_t launch_order_rows(const int32_t *ops, const int32_t *tensors, int64_t nnz, int32_t *keys, int32_t *status, hipStream_t s);
 // rowptr[0..n_rows] from keys that are in row order; nothing if the status has an error (all are in range)
 hipError_t launch_row_bounds(const int32_t *keys, int64_t nnz, int32_t n_rows, int32_t *rowptr, const int32_t *status, hipStream_t s);
-hipError_t launch_check_csr(const int32_t *rowptr, const int32_t *idx, int32_t n_rows, int32_t nnz,
-                            int32_t n_vals, int32_t *error, hipStream_t s);
-hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t *row_of, hipStream_t s);
+hipError_t launch_check_csr(const GraphView &g, int32_t *error, hipStream_t s);
+hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz, int32_t *row_of, const int32_t *status, hipStream_t s);
 
 // Traversal.
 hipError_t launch_seed(const GraphView &g, int32_t Q, int64_t num_targets, const int32_t *tgt_rowptr,

@@ -325,12 +325,10 @@ hipError_t launch_check_ids(const EdgeList &l, int32_t *status, hipStream_t s)
     return hipGetLastError();
 }
 
-// Borrowed CSR: rowptr[0] == 0, monotone, rowptr[n_rows] == nnz, every idx in [0, n_vals).
-__global__ __launch_bounds__(256) void k_check_csr(const int32_t *rowptr, const int32_t *idx, int32_t n_rows,
-                                                    int32_t nnz, int32_t n_vals, int32_t *error)
+// Borrowed CSR: rowptr[0] == 0, monotone, rowptr[n_rows] == nnz, every idx in [0, n_vals).  Inputs and outputs in one launch.
+__device__ __forceinline__ int check_csr(const int32_t *rowptr, const int32_t *idx, int32_t n_rows, int32_t nnz, int32_t n_vals, int64_t gtid,
+                                         int64_t gsize)
 {
-    const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
-    const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int bad = 0;
     for (int64_t r = gtid; r <= n_rows; r += gsize) {
         const int32_t a = rowptr[r];
@@ -343,33 +341,47 @@ __global__ __launch_bounds__(256) void k_check_csr(const int32_t *rowptr, const 
         const int32_t v = idx[e];
         if (v < 0 || v >= n_vals) bad |= kErrIdRange;
     }
+    return bad;
+}
+
+__global__ __launch_bounds__(256) void k_check_csr(GraphView g, int32_t *error)
+{
+    const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
+    const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int bad = check_csr(g.in_rowptr, g.in_idx, g.num_ops, g.nnz_in, g.num_tensors, gtid, gsize) |
+                    check_csr(g.out_rowptr, g.out_idx, g.num_ops, g.nnz_out, g.num_tensors, gtid, gsize);
     if (bad) atomicOr(error, bad);
 }
 
-hipError_t launch_check_csr(const int32_t *rowptr, const int32_t *idx, int32_t n_rows, int32_t nnz,
-                            int32_t n_vals, int32_t *error, hipStream_t s)
+hipError_t launch_check_csr(const GraphView &g, int32_t *error, hipStream_t s)
 {
-    int64_t work = (int64_t)n_rows + 1 > nnz ? (int64_t)n_rows + 1 : nnz;
+    const int64_t nnz = g.nnz_in > g.nnz_out ? g.nnz_in : g.nnz_out;
+    const int64_t work = (int64_t)g.num_ops + 1 > nnz ? (int64_t)g.num_ops + 1 : nnz;
     int64_t blocks = (work + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_check_csr, dim3((unsigned)blocks), dim3(256), 0, s, rowptr, idx, n_rows, nnz, n_vals, error);
+    hipLaunchKernelGGL(k_check_csr, dim3((unsigned)blocks), dim3(256), 0, s, g, error);
     return hipGetLastError();
 }
 
-// row_of[e] = r for every entry e of row r (operator id of every entry of a borrowed out CSR)
-__global__ __launch_bounds__(256) void k_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t *row_of)
+// row_of[e] = r for every entry e of row r (operator id of every entry of an out CSR); -1 everywhere if the CSR is none, or an index of it is
+// out of range (status[0]): the pass over this list then reports that again, and touches nothing
+__global__ __launch_bounds__(256) void k_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz, int32_t *row_of, const int32_t *status)
 {
-    const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n_rows; r += gsize)
+    const int64_t gsize = (int64_t)gridDim.x * blockDim.x, gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (status[0] & (kErrCsr | kErrIdRange)) {
+        for (int64_t e = gtid; e < nnz; e += gsize) row_of[e] = -1;
+        return;
+    }
+    for (int64_t r = gtid; r < n_rows; r += gsize)
         for (int32_t e = rowptr[r]; e < rowptr[r + 1]; ++e) row_of[e] = (int32_t)r;
 }
 
-hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t *row_of, hipStream_t s)
+hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz, int32_t *row_of, const int32_t *status, hipStream_t s)
 {
     if (n_rows == 0) return hipSuccess;
     int64_t blocks = ((int64_t)n_rows + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_expand_rows, dim3((unsigned)blocks), dim3(256), 0, s, rowptr, n_rows, row_of);
+    hipLaunchKernelGGL(k_expand_rows, dim3((unsigned)blocks), dim3(256), 0, s, rowptr, n_rows, nnz, row_of, status);
     return hipGetLastError();
 }
 

@@ -180,3 +180,33 @@ def test_ids_out_of_range_in_lists_in_no_order(dgn, ops, outs, fan):
             print(ops, name, bad, flush=True)
             rc, handle = dgn.dgn_graph_build(desc, mem, mem.numel(), scratch, scratch.numel())
             assert rc == dgn.DGN_ERR_ID_OUT_OF_RANGE, (name, bad, rc)
+
+
+@pytest.mark.parametrize("validate", [0, 1])
+@pytest.mark.parametrize("ops", [1, 700, 150_000])
+def test_faults_of_a_borrowed_csr_are_reported_wherever_they_are(dgn, oracle, ops, validate):
+    """The arrays are checked by the device and what follows is enqueued behind that: no kernel trusts rows that are none."""
+    import torch
+    rng = np.random.default_rng(ops)
+    g = listed(rng, ops, 0, 0, False)
+    adj = oracle.build_adjacency(g.num_ops, g.num_tensors, g.in_op, g.in_tensor, g.out_op, g.out_tensor)
+    good = {n: np.ascontiguousarray(getattr(adj, n)) for n in ROWS[:4]}
+    cases = [("out_rowptr", 0, 1, "csr"), ("out_rowptr", g.num_ops, -7, "csr"), ("in_rowptr", g.num_ops, (1 << 31) - 1, "csr"),
+             ("out_rowptr", g.num_ops // 2, (1 << 31) - 1, "csr"), ("in_rowptr", g.num_ops // 2, -1, "csr"),
+             ("out_idx", g.nnz_out // 2, -1, "id"), ("out_idx", g.nnz_out - 1, g.num_tensors, "id"), (None, 0, 0, None)]
+    if g.nnz_in:
+        cases += [("in_idx", g.nnz_in - 1, g.num_tensors, "id"), ("in_idx", 0, -(1 << 31), "id")]
+    for name, at, value, what in cases:
+        arrays = {n: v.copy() for n, v in good.items()}
+        if name:
+            arrays[name][at] = value
+        keep = [torch.from_numpy(v).cuda() for v in arrays.values()]
+        desc = dgn.make_csr_desc(g.num_ops, g.num_tensors, *keep)
+        rc, mem, scratch = dgn.dgn_graph_from_csr_workspace(desc)
+        mem, scratch = (torch.full((n,), 255, dtype=torch.uint8, device="cuda") for n in (mem, scratch))
+        print(ops, name, at, value, flush=True)
+        rc, handle = dgn.dgn_graph_from_csr(desc, mem, mem.numel(), scratch, scratch.numel(), dgn.dgn_options(validate=validate))
+        want = {"csr": dgn.DGN_ERR_BAD_CSR, "id": dgn.DGN_ERR_ID_OUT_OF_RANGE, None: dgn.DGN_OK}[what]
+        assert rc == want, (name, at, value, rc)
+        if handle:
+            dgn.dgn_graph_destroy(handle)
