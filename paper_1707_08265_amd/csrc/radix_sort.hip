@@ -85,15 +85,28 @@ __global__ __launch_bounds__(kHistThreads) void k_sort_hist(const int32_t *keys,
     }
     __syncthreads();
     if (status && ballot64(most >= num_rows) != 0 && lane_id() == 0) atomicOr(status, kErrIdRange);
-    if (threadIdx.x >= kRadix) return;
     // the table has a row for each of the group's kHistTiles tiles, also past the last tile
-    int32_t *row = table + tile0 * kRadix + threadIdx.x;
+    const bool keeps_digit = threadIdx.x < kRadix;
     int run = 0;
+    if (keeps_digit) {
+        int32_t *row = table + tile0 * kRadix + threadIdx.x;
 #pragma unroll
-    for (int t = 0; t < kHistTiles; ++t) {
-        row[t * kRadix] = run;
-        run += hist[t][threadIdx.x];
+        for (int t = 0; t < kHistTiles; ++t) {
+            row[t * kRadix] = run;
+            run += hist[t][threadIdx.x];
+        }
     }
+    if (gridDim.x == 1) {                                    // a list of one group: k_col_apply has nothing to add up but the digits
+        __shared__ int s_wtot[kThreads / kWave];
+        const int incl = wave_incl_scan(run);
+        if (lane_id() == kWave - 1) s_wtot[threadIdx.x >> 6] = incl;
+        __syncthreads();
+        int first = incl - run;
+        for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) first += s_wtot[w];
+        if (keeps_digit) totals[threadIdx.x] = first;
+        return;
+    }
+    if (!keeps_digit) return;
     totals[(int64_t)blockIdx.x * kRadix + threadIdx.x] = run;
     if (run) atomicAdd(&sums[(int64_t)(blockIdx.x / per_chunk) * kRadix + threadIdx.x], run);
 }
@@ -322,7 +335,7 @@ static hipError_t sort_passes(const int32_t *keys_in, const int32_t *vals_in, in
     const unsigned scatter_grid = (unsigned)(((tiles + 7) >> 3) << 3);
     int32_t *sums[2] = {t.sums, t.sums + kColChunks * kRadix};
     FillRegion clr[1] = {{sums[0], (size_t)chunks * kRadix * sizeof(int32_t)}};
-    hipError_t e = launch_clear(clr, 1, s);
+    hipError_t e = groups > 1 ? launch_clear(clr, 1, s) : hipSuccess;
     if (e != hipSuccess) return e;
     const int32_t *ksrc = keys_in, *vsrc = vals_in;
     for (int pass = 0; pass < passes; ++pass) {
@@ -332,8 +345,9 @@ static hipError_t sort_passes(const int32_t *keys_in, const int32_t *vals_in, in
         int32_t *vdst = last && vals_out ? vals_out : t.vals[pass & 1];
         hipLaunchKernelGGL(k_sort_hist<kBits>, dim3((unsigned)groups), dim3(kHistThreads), 0, s, ksrc, n, shift, t.table,
                            t.totals, sums[pass & 1], per_chunk, (uint32_t)num_rows, pass == 0 ? status : nullptr);
-        hipLaunchKernelGGL(k_col_apply<kBits>, dim3(chunks), dim3(kRadix), 0, s, t.totals, groups, per_chunk,
-                           sums[pass & 1], chunks, sums[(pass & 1) ^ 1]);
+        if (groups > 1)
+            hipLaunchKernelGGL(k_col_apply<kBits>, dim3(chunks), dim3(kRadix), 0, s, t.totals, groups, per_chunk,
+                               sums[pass & 1], chunks, sums[(pass & 1) ^ 1]);
         hipLaunchKernelGGL(k_sort_scatter<kBits>, dim3(scatter_grid), dim3(kSortThreads), 0, s, ksrc, vsrc, kdst, vdst, n, shift,
                            t.table, t.totals, tiles);
         e = hipGetLastError();
