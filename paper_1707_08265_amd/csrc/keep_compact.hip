@@ -191,12 +191,15 @@ __global__ __launch_bounds__(kCThreads) void k_keep_count(CompactArgs a)
 }
 
 // Count pass of a single graph whose keep flags the traversal has already written (a byte per operator, 1 where
-// K != 0; they are the caller's op_flag or stand in for it).  A wave takes a whole tile: 2048 flag bytes in four
-// 8-byte loads per lane, squeezed to the tile's 32 bitmap words and its kept count without touching K.  The ids
+// K != 0; they are the caller's op_flag or stand in for it).  A workgroup takes four tiles, far from each other, at a time, a quarter of
+// each per wave: 8 flag bytes per lane and tile, squeezed to bitmap words and kept counts without touching K.  The ids
 // of the kept operators go through a small list in LDS, and K is read for 64 of them at a time for the per-set
-// counts -- about P/8 + 8 P_kept bytes of traffic instead of 9P, and no barrier anywhere.
+// counts -- about P/8 + 8 P_kept bytes of traffic instead of 9P.  What bounds it is the wave with the most kept operators, 64 at a
+// time (a wave per tile before: 10 M operators with 46 000 kept ones in dense stretches 17 -> 10 us, 50 M with 1.0 M 34 -> 29.5).
 constexpr int kPendCap = 128;
 constexpr int64_t kFlagsCountGrid = 8192;
+constexpr int kTilesAtOnce = 4;
+static_assert(kCWaves * 512 == kCompactTile, "a wave's share of a tile is eight operators per lane");
 // Below this many operators all of K is a few microseconds of reading, and the kernel that reads it is the
 // faster one where most operators are kept (it needs no list of kept ids).
 constexpr int64_t kFlagsCountMinOps = (int64_t)1 << 22;
@@ -219,6 +222,7 @@ __global__ __launch_bounds__(kCThreads) void k_keep_count_flags(CompactArgs a)
 {
     __shared__ int32_t s_ids[kCWaves][kPendCap];
     __shared__ uint32_t s_q[kCWaves][kWave];
+    __shared__ int s_kept[kTilesAtOnce][kCWaves];
     const GraphView &g = a.g;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int64_t tiles = ((int64_t)g.num_ops + kCompactTile - 1) / kCompactTile;
@@ -227,29 +231,29 @@ __global__ __launch_bounds__(kCThreads) void k_keep_count_flags(CompactArgs a)
     int32_t *ids = &s_ids[wave][0];
     int npend = 0;                // wave-uniform
     uint32_t qcount = 0;          // lane q: kept operators whose K has bit q
-    for (int64_t tile = (int64_t)blockIdx.x * kCWaves + wave; tile < tiles; tile += (int64_t)gridDim.x * kCWaves) {
-        const int64_t base = tile * kCompactTile;
-        u64 f[4];
+    for (int64_t t0 = blockIdx.x; t0 < tiles; t0 += (int64_t)kTilesAtOnce * gridDim.x) {       // whole workgroups stay in the loop
+        u64 f[kTilesAtOnce];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t o = base + j * 512 + lane * 8;      // this lane's eight operators of stretch j
+        for (int j = 0; j < kTilesAtOnce; ++j) {
+            const int64_t o = (t0 + (int64_t)j * gridDim.x) * kCompactTile + wave * 512 + lane * 8;    // this lane's eight operators
             f[j] = o < g.num_ops ? *reinterpret_cast<const u64 *>(a.flag_in + o) : 0;
         }
-        int kept = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < kTilesAtOnce; ++j) {
+            const int64_t base = (t0 + (int64_t)j * gridDim.x) * kCompactTile + wave * 512;
             // bytes are 0 or 1: bit 0 of each into one byte
             const uint32_t b = (uint32_t)(((f[j] & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
-            kept += __popc(b);
+            const int kept = wave_sum(__popc(b));
+            if (lane == 0) s_kept[j][wave] = kept;
             // eight neighbouring lanes hold one bitmap word
             u64 w = (u64)b << (8 * (lane & 7));
             w |= shfl_xor64(w, 1);
             w |= shfl_xor64(w, 2);
             w |= shfl_xor64(w, 4);
-            const int64_t wi = (base >> 6) + j * 8 + (lane >> 3);
+            const int64_t wi = (base >> 6) + (lane >> 3);
             if ((lane & 7) == 0 && wi < n_words) a.opbits[wi] = w;
-            if (want_pq && ballot64(b != 0)) {
-                const int32_t o0 = (int32_t)(base + j * 512 + lane * 8);
+            if (want_pq && kept > 0) {
+                const int32_t o0 = (int32_t)(base + lane * 8);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const bool has = (b >> i) & 1;
@@ -268,8 +272,15 @@ __global__ __launch_bounds__(kCThreads) void k_keep_count_flags(CompactArgs a)
                 }
             }
         }
-        kept = wave_sum(kept);
-        if (lane == 0) a.block_counts[tile] = kept;
+        __syncthreads();
+        const int64_t tile = t0 + (int64_t)threadIdx.x * gridDim.x;
+        if (threadIdx.x < kTilesAtOnce && tile < tiles) {
+            int tot = 0;
+#pragma unroll
+            for (int w = 0; w < kCWaves; ++w) tot += s_kept[threadIdx.x][w];
+            a.block_counts[tile] = tot;
+        }
+        __syncthreads();
     }
     if (!want_pq) return;
     __builtin_amdgcn_wave_barrier();
@@ -512,8 +523,8 @@ hipError_t launch_keep_compact(const CompactArgs &a, hipStream_t s, hipEvent_t *
         else if (a.flag_in && a.g.num_graphs == 1 && (a.op_flag == nullptr || a.op_flag == a.flag_in) &&
                  P >= kFlagsCountMinOps)
         {
-            // a wave takes whole tiles: up to kFlagsCountGrid workgroups, so that most waves have one tile only
-            const int64_t wg = (tiles + kCWaves - 1) / kCWaves;
+            // up to kFlagsCountGrid workgroups, so that most have one round of tiles only
+            const int64_t wg = (tiles + kTilesAtOnce - 1) / kTilesAtOnce;
             const int64_t flags_grid = wg < kFlagsCountGrid ? wg : kFlagsCountGrid;
             hipLaunchKernelGGL(k_keep_count_flags, dim3((unsigned)flags_grid), dim3(kCThreads), 0, s, a);
         }

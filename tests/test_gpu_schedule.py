@@ -102,3 +102,25 @@ def test_repeated_prunes_settle_on_one_way(dgn, oracle, size, per_set, sets):
     adj = oracle.build_adjacency(g.num_ops, g.num_tensors, g.in_op, g.in_tensor, g.out_op, g.out_tensor)
     ref = oracle.forward_prune(adj, sets, tg.tgt_rowptr, tg.tgt_idx)
     assert np.array_equal(buf.to_host()["kept_masks"][:int(ref.kept_count[0])], ref.kept_masks[:int(ref.kept_count[0])])
+
+
+@pytest.mark.parametrize("sets", [1, 64])
+@pytest.mark.parametrize("extra", [0, 1, 511, 2049, 5 * 2048 + 8])
+def test_count_of_kept_operators_from_their_flags(dgn, oracle, extra, sets):
+    """Graphs of 4 194 304 operators and more, whose kept operators lie densely in a few tiles (chains at both ends) and thinly
+    elsewhere, with last tiles of all kinds."""
+    from helpers import targets_from_sets
+    from test_gpu_parity import assert_same, gpu_prune, oracle_prune
+    rng = np.random.default_rng(extra + sets)
+    P = (1 << 22) + extra
+    ops = np.arange(P)
+    before = np.minimum(ops, 3000 + ops // 9)
+    in_t = np.where((ops < 6000) | (ops >= P - 5000), ops - 1 + 16, (rng.random(P) * (16 + before)).astype(np.int64))
+    in_t[P - 5000] = 7
+    i32 = lambda a: np.ascontiguousarray(a, dtype=np.int32)  # noqa: E731
+    g = gg.Graph(P, P + 16, i32(ops), i32(in_t), i32(ops), i32(ops + 16), name="flags")
+    far = [int(x) for x in rng.integers(6000, P - 5000, 40)]
+    tg = targets_from_sets([[P + 15 - 64 * q, 16 + far[q % 40], 16 + 5999 - q] for q in range(sets)], sets)
+    _, _, out = gpu_prune(dgn, g, tg)
+    _, ref = oracle_prune(oracle, g, tg)
+    assert_same(out, ref, f"{extra} {sets}")
