@@ -438,25 +438,47 @@ __global__ __launch_bounds__(kCThreads) void k_scatter(CompactArgs a)
     if (lane < kCWords && word_base + lane < n_words) w = a.opbits[word_base + lane];
     const int c = __popcll(w);
     const int off = wave_incl_scan(c) - c;
+    // (masks of several operators in flight at a time: one after the other, the fullest tiles were what the pass waited for)
     if (kept < kScatterByBitsBelow) {
+        constexpr int kAtOnce = 4;
         int pos = base + off;
         while (w) {
-            const int b = __builtin_ctzll(w);
-            w &= w - 1;
-            const int64_t o = tile_base + (int64_t)lane * kWave + b;
-            a.kept_ops[pos] = (int32_t)o;
-            if (a.kept_masks) a.kept_masks[pos] = a.K[o];
-            ++pos;
+            int64_t o[kAtOnce];
+            u64 k[kAtOnce];
+            bool has[kAtOnce];
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j) {
+                has[j] = w != 0;
+                o[j] = tile_base + (int64_t)lane * kWave + (has[j] ? __builtin_ctzll(w) : 0);
+                w &= w - 1;                                 // (stays zero)
+                k[j] = has[j] && a.kept_masks ? a.K[o[j]] : 0;
+            }
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j) {
+                if (!has[j]) continue;
+                a.kept_ops[pos] = (int32_t)o[j];
+                if (a.kept_masks) a.kept_masks[pos] = k[j];
+                ++pos;
+            }
         }
     } else {
-        for (int wi = 0; wi < kCWords; ++wi) {
-            const u64 word = shfl64(w, wi);
-            const int woff = __shfl(off, wi, kWave);
-            if ((word >> lane) & 1) {
-                const int64_t o = tile_base + (int64_t)wi * kWave + lane;
-                const int pos = base + woff + __popcll(word & lanemask_lt());
-                a.kept_ops[pos] = (int32_t)o;
-                if (a.kept_masks) a.kept_masks[pos] = a.K[o];
+        constexpr int kAtOnce = 8;
+        for (int w0 = 0; w0 < kCWords; w0 += kAtOnce) {
+            u64 k[kAtOnce];
+            bool has[kAtOnce];
+            int pos[kAtOnce];
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j) {
+                const u64 word = shfl64(w, w0 + j);
+                pos[j] = base + __shfl(off, w0 + j, kWave) + __popcll(word & lanemask_lt());
+                has[j] = (word >> lane) & 1;
+                k[j] = has[j] && a.kept_masks ? a.K[tile_base + (int64_t)(w0 + j) * kWave + lane] : 0;
+            }
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j) {
+                if (!has[j]) continue;
+                a.kept_ops[pos[j]] = (int32_t)(tile_base + (int64_t)(w0 + j) * kWave + lane);
+                if (a.kept_masks) a.kept_masks[pos[j]] = k[j];
             }
         }
     }
