@@ -185,7 +185,7 @@ int dgn_graph_build_workspace(const dgn_coo_desc *desc, size_t *graph_bytes, siz
  *   operator -> input tensors   CSR, rows keep the COO order of their edges (stable);
  *   operator -> output tensors  CSR, likewise;
  *   tensor   -> producing operators CSR, rows ascending in operator id.
- * Stable LSD radix sort on the significant key bits plus prefix sums, all inside graph_mem /
+ * Stable sorts on the significant key bits (a list in order needs none), all inside graph_mem /
  * scratch.  Every id is range-checked on the device (-> DGN_ERR_ID_OUT_OF_RANGE); with
  * options->validate the topological precondition is checked too (-> DGN_ERR_NOT_TOPOLOGICAL).
  * The call synchronises the stream once before returning to report those errors.  options may be
