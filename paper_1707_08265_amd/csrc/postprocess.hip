@@ -68,12 +68,14 @@ __global__ __launch_bounds__(kPpThreads) void k_set_count(const u64 *kept_masks,
 
 // The entries of a tile that belong to one set go out together, from neighbouring lanes into neighbouring slots of the
 // set's list.  (A lane per set, each writing its own list entry after entry, sent 64 lanes of a store to 64 cache lines:
-// 11 M entries in 64 us, now 34.)
+// 11 M entries in 64 us, now 34.)  The first workgroup leaves the lists' row pointers; entry 64 * tiles of the table holds the
+// total (a launch of their own was 2 to 4 us of the 107 that in-place names, ignore mask and lists of a small graph take).
 __global__ __launch_bounds__(kPpThreads) void k_set_scatter(const int32_t *kept_ops, const u64 *kept_masks, int64_t n,
                                                              int64_t tiles, const int32_t *table, int32_t *set_ops,
-                                                             int64_t capacity)
+                                                             int64_t capacity, int64_t *set_rowptr)
 {
     const int lane = lane_id();
+    if (blockIdx.x == 0 && threadIdx.x <= kWave) set_rowptr[threadIdx.x] = table[(int64_t)threadIdx.x * tiles];
     const int64_t wave_id = (int64_t)blockIdx.x * (kPpThreads / kWave) + (threadIdx.x >> 6);
     const int64_t num_waves = (int64_t)gridDim.x * (kPpThreads / kWave);
     for (int64_t tile = wave_id; tile < tiles; tile += num_waves) {
@@ -90,12 +92,6 @@ __global__ __launch_bounds__(kPpThreads) void k_set_scatter(const int32_t *kept_
             if (in && pos < capacity) set_ops[pos] = op;
         }
     }
-}
-
-__global__ __launch_bounds__(128) void k_set_rowptr(const int32_t *table, int64_t tiles, int64_t *set_rowptr)
-{
-    const int q = threadIdx.x;
-    if (q <= 64) set_rowptr[q] = tiles > 0 ? table[(int64_t)q * tiles] : 0;    // entry 64*tiles holds the total
 }
 
 size_t set_lists_scratch_bytes(int64_t num_kept)
@@ -130,10 +126,11 @@ hipError_t launch_set_lists(const int32_t *kept_ops, const u64 *kept_masks, int6
         hipError_t e = launch_exclusive_scan(table, table, 64 * tiles, scan_tmp, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_set_scatter, dim3((unsigned)blocks), dim3(kPpThreads), 0, s, kept_ops, kept_masks, num_kept,
-                           tiles, table, set_ops, capacity);
+                           tiles, table, set_ops, capacity, set_rowptr);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_set_rowptr, dim3(1), dim3(128), 0, s, table, tiles, set_rowptr);
-    return hipGetLastError();
+    FillRegion none[1] = {{set_rowptr, (kWave + 1) * sizeof(int64_t)}};
+    return launch_clear(none, 1, s);
 }
 
 }  // namespace dgn
