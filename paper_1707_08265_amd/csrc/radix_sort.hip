@@ -578,6 +578,8 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
     const int32_t row0 = b << row_bits;
     const int rows = min(1 << row_bits, l.num_ops - row0);
     const int32_t nnz = (int32_t)l.nnz, shift = l.num_tensors - nnz;
+    // (once some workgroup has found that the rows by tensor are not to be had here, the others write the rows by operator alone)
+    const bool together = kOut && shift >= 0 && load_coherent(&status[kStatusPending]) == 0;
     int32_t *const rowptr = l.row + row0;
     keys += lo;
     vals += lo;
@@ -598,7 +600,7 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
         write_rowptr(first, first + v0);
         s_base[2 * tid] = first;
         s_base[2 * tid + 1] = first + v0;
-    } else if (kOut) {
+    } else if (together) {
         for (int i = tid; i < R::kTile / 32; i += kThreads) s_seen[i] = 0;
         // tensors before the run have no producer
         for (int64_t t = (int64_t)b * kThreads + tid; t < shift; t += (int64_t)buckets * kThreads) {
@@ -641,7 +643,7 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
     }
     if (ballot64(bad) != 0 && lane == 0) atomicOr(status, kErrIdRange);
     if (several) return;
-    if (kOut && l.orec) {
+    if (together && l.orec) {
         auto record = [&](int r, int at, int length) {
             const int first = length > 0 ? s_val[at] : 0;
             bool consecutive = true;
@@ -651,7 +653,7 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
         if (2 * tid < rows) record(2 * tid, begin, length0);
         if (2 * tid + 1 < rows) record(2 * tid + 1, begin + length0, length1);
     }
-    bool elsewhere = kOut && shift < 0, scattered = false;
+    bool elsewhere = kOut && !together, scattered = false;
     for (int i = tid; i < n; i += kThreads) {
         const int32_t v = s_val[i], e = lo + i;
         l.idx[e] = v;
