@@ -378,10 +378,10 @@ hipError_t launch_sort_pairs(const int32_t *keys_in, const int32_t *vals_in, int
 // rows only (the high bits of the key), and one workgroup per bucket ranks what is left of the key in LDS and writes the
 // bucket's rows and row pointers: a pass over memory less, no keys written at the end, and no pass that reads them again.  For
 // outputs the same workgroup writes the rows by tensor, the producer words and the operators' records, which took three more
-// passes.  32 M input edges of 12 M operators: 530 us sorted as a whole, 460 so; their 25 M outputs 700 -> 490; the whole build
-// 1 427 -> 1 077 us.  30 000 operators: 221 -> 159, 500 000: 392 -> 196, 50 M: 5 430 -> 3 925.
+// passes.  32 M input edges of 12 M operators: 530 us sorted as a whole, 475 so; their 25 M outputs 700 -> 505; the whole build
+// 1 430 -> 1 110 us.  10 000 operators: 181 -> 135, 30 000: 220 -> 143, 500 000: 400 -> 190, 50 M: 5 390 -> 3 940.
 //
-// The last step takes 117 us for those 32 M pairs (440 MB), 217 for the outputs (890 MB): memory.  It was 205 with workgroups of 1 024
+// The last step takes 119 us for those 32 M pairs (440 MB), 226 for the outputs (890 MB): memory.  It was 205 with workgroups of 1 024
 // threads, eleven bits of the key and two passes inside LDS (barriers, and vector instructions of the second pass), 156 with
 // 256 threads and two passes.
 // ------------------------------------------------------------------------------------------------
