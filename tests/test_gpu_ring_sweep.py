@@ -358,3 +358,25 @@ def test_long_thin_graphs_are_swept_once_a_prune_has_shown_their_chains(dgn, ora
         assert buf.prune(torch.from_numpy(tg.tgt_rowptr).cuda(), torch.from_numpy(tg.tgt_idx).cuda(), stats=st) == 0
         assert_same(buf.to_host(), ref, f"call {call}")
         assert (st.launches <= 3) == (swept and call > 0), (call, st.launches)
+
+
+@pytest.mark.parametrize("count,last", [(2701, 64), (2700, 64), (2703, 128), (2701, 63), (2701, 65)])
+def test_wide_operators_at_the_very_end_of_a_large_batch(dgn, oracle, count, last):
+    """So many operators that a wave of the build walks more than 64 of them, and the widest 64 of all are the last ones, which
+    mostly begin in one step of a wave and end in its next: the ring has to hold their outputs."""
+    rng = np.random.default_rng(count + last)
+    P = np.append(np.full(count, 200), last)
+    op_off = np.concatenate([[0], np.cumsum(P)])
+    n_out = np.ones(op_off[-1], np.int64)
+    n_out[-last:] = np.where(np.arange(last) < last - 64, 1, 40)
+    graph = np.repeat(np.arange(count + 1), P)
+    t_off = np.concatenate([[0], np.cumsum(4 + np.add.reduceat(n_out, op_off[:-1]))])
+    first = 4 * (graph + 1) + np.cumsum(n_out) - n_out
+    op, out_op = np.arange(op_off[-1]), np.repeat(np.arange(op_off[-1]), n_out)
+    in_op = np.repeat(op, 2)
+    in_t = np.maximum(first[in_op] - rng.integers(1, 9, in_op.size), t_off[graph[in_op]])
+    out_t = 4 * (graph[out_op] + 1) + np.arange(out_op.size)
+    i32 = lambda a: np.ascontiguousarray(a, dtype=np.int32)  # noqa: E731
+    g = gg.Graph(int(op_off[-1]), int(t_off[-1]), i32(in_op), i32(in_t), i32(out_op), i32(out_t), count + 1, op_off.astype(np.int64),
+                 t_off.astype(np.int64), "wide end")
+    check(dgn, oracle, g, [draw_targets(rng, g, 3, 2)])
