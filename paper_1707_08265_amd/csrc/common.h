@@ -299,6 +299,7 @@ enum : int {
     kStatusProdGap = 7,
     kStatusOrder = 8,            // (so many words say whether there is an adjacency; the following describe it)
     kStatusOversize = 8,         // lists that were to be sorted by buckets have a bucket that is too large: they are sorted as a whole
+    kStatusNoRows = 9,           // ... or ids out of range were found before the buckets were made: there are none
     kStatusPending = 10,         // ... and rows by tensor that do not follow from the rows by operator
     kStatusBig = 11,             // ... how many of them are large: inputs, outputs, outputs by tensor
     kStatusMulti = 16,           // some tensor has several producers

@@ -404,6 +404,8 @@ __global__ __launch_bounds__(256) void k_bucket_starts(const int32_t *keys, int3
                                                         int32_t *starts, int32_t *big, int32_t *num_big, int32_t *status)
 {
     const int64_t thread = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    // For the kernels behind this one, which add to status[0] themselves: all waves of a workgroup have to read the same here.
+    if (thread == 0 && status[0]) status[kStatusNoRows] = 1;
     const int32_t b = (int32_t)min(thread / kProbes, (int64_t)buckets);
     const int probe = threadIdx.x & (kProbes - 1), group = lane_id() & ~(kProbes - 1);
     int32_t lo = 0, hi = b == buckets ? 0 : n;              // the answer is in [lo, hi]
@@ -557,7 +559,7 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
     __shared__ uint32_t s_count[R::kWaves][R::kRows / 2];
     __shared__ uint32_t s_seen[kOut ? R::kTile / 32 : 1];
     __shared__ int s_wtot[R::kWaves];
-    if (status[kStatusOversize] || status[0]) return;       // (a key that is no row: the starts need not ascend)
+    if (status[kStatusOversize] || status[kStatusNoRows]) return;           // (a key that is no row: the starts need not ascend)
     const int lane = lane_id(), wave = threadIdx.x >> 6, tid = threadIdx.x;
     const int row_mask = (1 << row_bits) - 1;
     int *s_base = s_val;                                    // of a bucket of several tiles (no value is kept in LDS then)
@@ -687,7 +689,7 @@ void k_big_rows(const int32_t *keys, const int32_t *vals, const int32_t *starts,
     __shared__ int s_base[R::kRows];
     __shared__ int s_wtot[R::kWaves];
     const int found = *num_big;
-    if (found == 0 || status[kStatusOversize] || status[0]) return;
+    if (found == 0 || status[kStatusOversize] || status[kStatusNoRows]) return;
     const int wave = threadIdx.x >> 6, tid = threadIdx.x;
     bool bad = false;
     big_tiles<kThreads>(starts, big, found, (int)blockIdx.x, kBigBlocks, [&](int32_t b, int32_t lo, int32_t n, int t, int table0) {

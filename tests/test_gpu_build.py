@@ -182,6 +182,44 @@ def test_ids_out_of_range_in_lists_in_no_order(dgn, ops, outs, fan):
             assert rc == dgn.DGN_ERR_ID_OUT_OF_RANGE, (name, bad, rc)
 
 
+@pytest.mark.parametrize("which", ["inputs", "outputs"])
+def test_many_tensors_out_of_range_beside_rows_of_several_tiles(dgn, which):
+    """Workgroups that rank rows report such tensors while others begin with theirs, some of them with buckets of more than one tile:
+    the call says so and writes nothing beside its memory.  The list is longer than the 8 388 608 edges that the first pass has looked at
+    when its last wave has taken its first step (a wave that has met a decrease takes no other)."""
+    import torch
+    rng = np.random.default_rng(5)
+    ops = 4_400_000
+    count = np.full(ops, 2)
+    count[999_999::1_000_000] = 2049, 10_000, 100_000, 17_000
+    one, many = np.arange(ops), np.repeat(np.arange(ops), count)
+    if which == "inputs":
+        in_op, out_op = rng.permutation(many), one
+        in_t = (rng.random(in_op.size) * (5 + in_op)).astype(np.int64)
+        out_t = 5 + one
+    else:
+        order = rng.permutation(many.size)
+        in_op, in_t, out_op, out_t = one, np.zeros(ops, np.int64), many[order], 5 + order
+    num_tensors = 5 + out_op.size
+    bad_list = in_t if which == "inputs" else out_t
+    at = (1 << 23) + rng.choice(bad_list.size - (1 << 23), 3000, replace=False)
+    was = bad_list[at].copy()
+    margin = 1 << 16
+    for bad in (True, False):
+        bad_list[at] = num_tensors + rng.integers(0, 1 << 28, at.size) if bad else was
+        up = [torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda() for a in (in_op, in_t, out_op, out_t)]
+        desc = dgn.make_coo_desc(ops, num_tensors, *up, 1, None, None)
+        rc, *need = dgn.dgn_graph_build_workspace(desc)
+        memory = [torch.full((n + margin,), 0xab, dtype=torch.uint8, device="cuda") for n in need]
+        print(which, bad, flush=True)
+        rc, handle = dgn.dgn_graph_build(desc, memory[0], need[0], memory[1], need[1])
+        assert rc == (dgn.DGN_ERR_ID_OUT_OF_RANGE if bad else dgn.DGN_OK)
+        for m, n in zip(memory, need):
+            assert bool((m[n:] == 0xab).all())
+        if handle:
+            dgn.dgn_graph_destroy(handle)
+
+
 @pytest.mark.parametrize("validate", [0, 1])
 @pytest.mark.parametrize("ops", [1, 700, 150_000])
 def test_faults_of_a_borrowed_csr_are_reported_wherever_they_are(dgn, oracle, ops, validate):
