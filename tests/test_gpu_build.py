@@ -220,6 +220,63 @@ def test_many_tensors_out_of_range_beside_rows_of_several_tiles(dgn, which):
             dgn.dgn_graph_destroy(handle)
 
 
+_LONG = {}
+
+
+def _long_lists(ops, each):
+    """Lists in operator order in which every operator reads and writes `each` tensors: more than 8 388 608 edges, which is what the first
+    pass has looked at when its last wave has taken its first step (a wave that has met a decrease takes no other)."""
+    if (ops, each) not in _LONG:
+        _LONG.clear()
+        op = np.repeat(np.arange(ops, dtype=np.int32), each)
+        t = np.arange(op.size, dtype=np.int32)
+        assert op.size > (1 << 23) + 1000
+        _LONG[ops, each] = op, (np.random.default_rng(ops).random(op.size) * (5 + op.astype(np.int64) * each)).astype(np.int32), 5 + t
+    return _LONG[ops, each]
+
+
+@pytest.mark.parametrize("inputs, outputs", [("shuffled", "ordered"), ("shuffled", "mixed"), ("shuffled", "gaps"), ("shuffled", "shuffled"),
+                                             ("ordered", "shuffled")])
+@pytest.mark.parametrize("ops, each", [(20_000, 460), (4_300_000, 2)])
+def test_ids_out_of_range_late_in_long_lists(dgn, ops, each, inputs, outputs):
+    """Ids that only the sorts come to see, of lists that are sorted as a whole and by buckets: reported, and nothing is made of rows
+    that were not written.  What the memory held stays inside the lists if it is taken for rows by tensor (a row with an entry, a
+    row before it, ...); "mixed" is the list of which the first pass writes no such row, so that no word says "no producer" then."""
+    import torch
+    rng = np.random.default_rng(ops)
+    op, in_t, out_t = _long_lists(ops, each)
+    num_tensors = op.size + 5
+    pi, po = (rng.permutation(op.size) if order == "shuffled" else slice(None) for order in (inputs, outputs))
+    if outputs == "mixed":
+        out_t = 5 + rng.permutation(op.size).astype(np.int32)
+    elif outputs == "gaps":                                    # 70 tensors without producer every thousand
+        out_t = out_t + out_t // 1000 * 70
+        num_tensors = int(out_t[-1]) + 1
+    good = {"in_op": op[pi], "in_tensor": in_t[pi], "out_op": op[po], "out_tensor": out_t[po]}
+    up = {n: torch.from_numpy(np.ascontiguousarray(v)).cuda() for n, v in good.items()}
+    desc = dgn.make_coo_desc(ops, num_tensors, *up.values(), 1, None, None)
+    rc, mem, scratch = dgn.dgn_graph_build_workspace(desc)
+    mem, scratch = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (mem, scratch))
+    words = mem[:mem.numel() // 8 * 8].view(torch.int32)
+    for name in good:
+        if (inputs if name.startswith("in") else outputs) != "shuffled":
+            continue
+        for bad in (ops if name.endswith("op") else num_tensors, 1 << 30):
+            at = op.size - int(rng.integers(1, 1000))
+            print(ops, inputs, outputs, name, bad, at, flush=True)
+            was = int(up[name][at])
+            up[name][at] = bad
+            words[0::2], words[1::2] = 0, 1
+            scratch.fill_(0)
+            rc, handle = dgn.dgn_graph_build(desc, mem, mem.numel(), scratch, scratch.numel())
+            assert rc == dgn.DGN_ERR_ID_OUT_OF_RANGE, (name, bad, rc)
+            assert outputs != "mixed" or not bool((words < 0).any())
+            up[name][at] = was
+    rc, handle = dgn.dgn_graph_build(desc, mem, mem.numel(), scratch, scratch.numel())
+    assert rc == dgn.DGN_OK
+    dgn.dgn_graph_destroy(handle)
+
+
 @pytest.mark.parametrize("validate", [0, 1])
 @pytest.mark.parametrize("ops", [1, 700, 150_000])
 def test_faults_of_a_borrowed_csr_are_reported_wherever_they_are(dgn, oracle, ops, validate):
