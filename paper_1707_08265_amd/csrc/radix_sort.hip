@@ -45,6 +45,44 @@ constexpr int kColChunks = 64;              // the groups are scanned in up to t
 
 constexpr int kHistThreads = 1024;
 
+// Adds the digits of a thread's kPer neighbouring keys to a tile's counts.  In a list that is nearly in order the lanes of a wave
+// mostly have the same digit of the high bits (two of them, where two such lists are interleaved), and an atomic per key has
+// all of them wait for each other: 4 M edges in order but for one took 100 us, in no order 15.  So where many lanes have the digit of
+// one of two, a thread adds up what it has of its first digit and of the next other one, and a wave of one digit alone adds
+// once: 20 us; builds of two recordings one behind the other, 200 000 operators 305 -> 151, 2 M 637 -> 309, 10 M 1 221 -> 921.
+constexpr int kSameDigit = 8;               // lanes, of two, on average
+template <int kPer> __device__ __forceinline__ void count_digits(int *hist, const int (&d)[kPer], int valid)
+{
+    auto lanes_with = [&](int lane) { return __popcll(ballot64(d[0] == __builtin_amdgcn_readlane(d[0], lane))); };
+    const int first = lanes_with(0);
+    if (first + lanes_with(kWave / 2) < 2 * kSameDigit) {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+            if (q < valid) atomicAdd(&hist[d[q]], 1);
+        return;
+    }
+    int count = 0, other = d[0], others = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        count += q < valid && d[q] == d[0];
+        other = other == d[0] && q < valid ? d[q] : other;
+    }
+    if (first == kWave && ballot64(count < kPer) == 0) {
+        if (lane_id() == 0) atomicAdd(&hist[d[0]], kWave * kPer);
+        return;
+    }
+    if (count) atomicAdd(&hist[d[0]], count);
+    if (other == d[0]) return;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) others += q < valid && d[q] == other;
+    atomicAdd(&hist[other], others);
+    if (count + others < valid) {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+            if (q < valid && d[q] != d[0] && d[q] != other) atomicAdd(&hist[d[q]], 1);
+    }
+}
+
 template <int kBits>
 __global__ __launch_bounds__(kHistThreads) void k_sort_hist(const int32_t *keys, int64_t n, int shift, int32_t *table,
                                                                      int32_t *totals, int32_t *sums, int per_chunk,
@@ -62,26 +100,25 @@ __global__ __launch_bounds__(kHistThreads) void k_sort_hist(const int32_t *keys,
     for (int t = 0; t < kHistTiles; ++t) {
         // the order inside a tile does not matter for its counts: a thread takes neighbouring keys
         const int64_t i = (tile0 + t) * kSortTile + (int64_t)threadIdx.x * kPerThread;
-        if (i >= n) break;
+        if (i - (int64_t)lane_id() * kPerThread >= n) break;             // whole waves stay in the loop
+        int32_t a[kPerThread];
         if (wide && i + kPerThread <= n) {
-            int4 a[kPerThread / 4];
 #pragma unroll
-            for (int q = 0; q < kPerThread / 4; ++q) a[q] = *reinterpret_cast<const int4 *>(keys + i + 4 * q);
-#pragma unroll
-            for (int q = 0; q < kPerThread / 4; ++q) {
-                most = max(max(most, max((uint32_t)a[q].x, (uint32_t)a[q].y)), max((uint32_t)a[q].z, (uint32_t)a[q].w));
-                atomicAdd(&hist[t][digit_of<kBits>(a[q].x, shift)], 1);
-                atomicAdd(&hist[t][digit_of<kBits>(a[q].y, shift)], 1);
-                atomicAdd(&hist[t][digit_of<kBits>(a[q].z, shift)], 1);
-                atomicAdd(&hist[t][digit_of<kBits>(a[q].w, shift)], 1);
+            for (int q = 0; q < kPerThread; q += 4) {
+                const int4 v = *reinterpret_cast<const int4 *>(keys + i + q);
+                a[q] = v.x; a[q + 1] = v.y; a[q + 2] = v.z; a[q + 3] = v.w;
             }
         } else {
-            for (int r = 0; r < kPerThread; ++r) {
-                if (i + r >= n) break;
-                most = max(most, (uint32_t)keys[i + r]);
-                atomicAdd(&hist[t][digit_of<kBits>(keys[i + r], shift)], 1);
-            }
+#pragma unroll
+            for (int q = 0; q < kPerThread; ++q) a[q] = i + q < n ? keys[i + q] : 0;
         }
+        int d[kPerThread];
+#pragma unroll
+        for (int q = 0; q < kPerThread; ++q) {
+            most = max(most, (uint32_t)a[q]);
+            d[q] = digit_of<kBits>(a[q], shift);
+        }
+        count_digits(hist[t], d, (int)min(max(n - i, (int64_t)0), (int64_t)kPerThread));
     }
     __syncthreads();
     if (status && ballot64(most >= num_rows) != 0 && lane_id() == 0) atomicOr(status, kErrIdRange);

@@ -149,6 +149,35 @@ def test_lists_sorted_by_buckets(dgn, oracle, ops, outs, fan, numbering):
     check(dgn, oracle, _shuffled(rng, n_out, count(fan), numbering=numbering), rng, f"{ops} {outs} {fan} {numbering}")
 
 
+@pytest.mark.parametrize("order", ["one", "halves", "two", "three", "runs"])
+@pytest.mark.parametrize("ops, outs, fan", [(4097, 2, 2), (12_293, 2, 3), (100_001, 1, 2), (300, 90, 150)])
+def test_lists_nearly_in_order(dgn, oracle, ops, outs, fan, order):
+    """Neighbouring keys have the same digits: in all lanes of a wave, of two recordings or three taken in turn, or of one now and
+    then; sorted by buckets and as a whole (few operators with many tensors)."""
+    rng = np.random.default_rng(ops)
+    n_out = rng.integers(0, 2 * outs + 1, ops)
+    n_out[:3] = 1, 2, 1
+    g = _shuffled(rng, n_out, rng.integers(0, 2 * fan + 1, ops))
+
+    def placed(op, t):
+        by = np.argsort(op, kind="stable")
+        op, t, n = op[by], t[by], op.size
+        p = np.arange(n)
+        if order == "one":
+            p[[n // 2, n // 3]] = p[[n // 3, n // 2]]
+        elif order == "halves":
+            p = np.concatenate([p[1::2], p[::2]])
+        elif order in ("two", "three"):
+            k = 2 if order == "two" else 3
+            p = np.concatenate([p[:n // k * k].reshape(k, -1).T.ravel(), p[n // k * k:]])
+        else:                                          # stretches of 1 to 900 edges change places
+            cut = np.split(p, np.cumsum(rng.integers(1, 901, n // 450)).clip(0, n))
+            p = np.concatenate([cut[i] for i in rng.permutation(len(cut))])
+        return op[p], t[p]
+    h = gg.Graph(g.num_ops, g.num_tensors, *placed(g.in_op, g.in_tensor), *placed(g.out_op, g.out_tensor), name=order)
+    check(dgn, oracle, h, rng, f"{ops} {order}")
+
+
 @pytest.mark.parametrize("which", ["inputs", "outputs"])
 @pytest.mark.parametrize("most, rows", [(2048, 1), (2049, 1), (4097, 2), (14_000, 1), (30_000, 1), (30_000, 3), (131_072, 1), (17_000, 70)])
 def test_rows_of_several_tiles_and_many_large_buckets(dgn, oracle, most, rows, which):
