@@ -437,7 +437,7 @@ int sort_rows(const EdgeList &l, const BuildScratch &S, bool buckets, bool good,
 
 // Tensor -> producer rows by a stable sort of the outputs in operator order (outputs by tensor: each tensor's producers stay
 // ascending in operator id), or, if only long gaps were left out, from the list in order by tensor; then the producer words.
-// buckets: by way of buckets where that is the shorter way (kStatusOversize then says whether it was one).
+// buckets: by way of buckets where that is the shorter way.
 int build_producers(const dgn_graph *h, const GraphLayout &L, const BuildScratch &S, const int32_t *ops_of_out,
                     const int32_t *keys, bool buckets, hipStream_t s)
 {
@@ -530,9 +530,9 @@ int new_graph(dgn_graph **out)
 }
 
 // What is left of an adjacency when the pass over the edge lists has found (f) that they are not in order, as its status words say.
-// Stable sorts: edges by operator, rows keep COO order; no histogram of the rows, no atomics on memory.  buckets: by way of
-// buckets where that is the shorter way; (*found)[kStatusOversize] then says that it was not one after all.
-int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, const GraphLayout &L, const BuildScratch &S, bool buckets,
+// Stable sorts, by way of buckets where that is the shorter way: edges by operator, rows keep COO order; no histogram of the rows, no
+// atomics on memory.
+int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, const GraphLayout &L, const BuildScratch &S,
                const int32_t (&f)[kStatusOrder], const dgn_options *options, hipStream_t s, const int32_t **found)
 {
     const int64_t P = h->P, T = h->T, Eout = h->Eout;
@@ -543,7 +543,7 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
     DGN_HIP(launch_clear(out_unsorted ? clr : order, 1, s));
     int rc = DGN_OK;
     if (f[kStatusInUnsorted]) {
-        rc = sort_rows(in, S, buckets, false, kStatusBig, s);
+        rc = sort_rows(in, S, true, false, kStatusBig, s);
         if (rc) return rc;
     } else if (f[kStatusInGap]) {
         DGN_HIP(launch_row_bounds(in.op, in.nnz, (int32_t)P, L.in_rowptr, S.status, s));
@@ -552,7 +552,7 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
     if (out_unsorted) {
         const RowPlan plan = plan_rows(Eout, P, key_bits_for(P));
         ops_of_out = S.sorted_ops;
-        if (buckets && plan.use) {
+        if (plan.use) {
             // where tensors are numbered as they are created, this is all
             EdgeList with = out;
             with.orec = walked(h) ? nullptr : L.orec;
@@ -561,7 +561,7 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
             rc = enqueue_records(h, L, S.status, options, s, true);
             if (rc) return rc;
             rc = read_status(S.status, s, found);
-            if (rc || (*found)[0] || (*found)[kStatusOversize] || !(*found)[kStatusPending]) return rc;
+            if (rc || (*found)[0] || !(*found)[kStatusPending]) return rc;
             DGN_HIP(launch_expand_rows(L.out_rowptr, (int32_t)P, (int32_t)Eout, S.sorted_ops, S.status, s));
             DGN_HIP(launch_clear(clr, 1, s));
         } else {
@@ -581,14 +581,14 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
         out_gap = (*found)[kStatusOutGap];
         prod_unsorted = (*found)[kStatusProdUnsorted];
         prod_gap = (*found)[kStatusProdGap];
-        if ((*found)[0] || (*found)[kStatusOversize] || !(out_gap || prod_unsorted || prod_gap)) return DGN_OK;
+        if ((*found)[0] || !(out_gap || prod_unsorted || prod_gap)) return DGN_OK;
         DGN_HIP(launch_clear(order, 1, s));
     }
     // (a long gap between tensors, but their order known: the keys are the ones that were found to ascend)
     const int32_t *by_tensor = out_unsorted ? S.sorted_keys : L.out_idx;
     if (out_gap) DGN_HIP(launch_row_bounds(ops_of_out, Eout, (int32_t)P, L.out_rowptr, S.status, s));
     if (prod_unsorted || prod_gap) {
-        rc = build_producers(h, L, S, ops_of_out, prod_unsorted ? nullptr : by_tensor, buckets, s);
+        rc = build_producers(h, L, S, ops_of_out, prod_unsorted ? nullptr : by_tensor, true, s);
         if (rc) return rc;
     }
     rc = enqueue_records(h, L, S.status, options, s);
@@ -621,11 +621,7 @@ int build_from_lists(dgn_graph *h, const dgn_coo_desc *d, const GraphLayout &L, 
     if (!(f[kStatusInUnsorted] || f[kStatusInGap] || f[kStatusOutUnsorted] || f[kStatusOutGap] || f[kStatusProdUnsorted] ||
           f[kStatusProdGap]))
         return DGN_OK;
-    rc = sort_lists(h, in, out, L, S, true, f, options, s, found);
-    if (rc || !(*found)[kStatusOversize]) return rc;
-    FillRegion flag[1] = {{S.status + kStatusOversize, (kStatusPending - kStatusOversize) * sizeof(int32_t)}};
-    DGN_HIP(launch_clear(flag, 1, s));
-    return sort_lists(h, in, out, L, S, false, f, options, s, found);
+    return sort_lists(h, in, out, L, S, f, options, s, found);
 }
 
 }  // namespace

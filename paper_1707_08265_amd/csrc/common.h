@@ -298,9 +298,8 @@ enum : int {
     kStatusOutGap = 6,
     kStatusProdGap = 7,
     kStatusOrder = 8,            // (so many words say whether there is an adjacency; the following describe it)
-    kStatusOversize = 8,         // lists that were to be sorted by buckets have a bucket that is too large: they are sorted as a whole
-    kStatusNoRows = 9,           // ... or ids out of range were found before the buckets were made: there are none
-    kStatusPending = 10,         // ... and rows by tensor that do not follow from the rows by operator
+    kStatusNoRows = 9,           // lists sorted by buckets: ids out of range were found before these were made, there are no rows
+    kStatusPending = 10,         // ... rows by tensor that do not follow from the rows by operator
     kStatusBig = 11,             // ... how many of them are large: inputs, outputs, outputs by tensor
     kStatusMulti = 16,           // some tensor has several producers
     kStatusScattered = 17,       // the outputs are not one run of tensors up to the last one
@@ -330,7 +329,7 @@ struct EdgeList {
 struct RowPlan { bool use; int row_bits, passes, pass_bits, threads; int64_t buckets; };
 RowPlan plan_rows(int64_t nnz, int64_t rows, int key_bits);
 // l.row, l.idx and, with `producers`, the rows by tensor, producer words and records.  kErrIdRange: there are ids out of range;
-// kStatusOversize: nothing was written; kStatusPending: the rows by operator are written, those by tensor are not.  tmp: scratch of sort_tmp_bytes(l.nnz) bytes.
+// kStatusPending: the rows by operator are written, those by tensor are not.  tmp: scratch of sort_tmp_bytes(l.nnz) bytes.
 // num_big: a word of the status, zero before.
 hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producers, int32_t *num_big, int32_t *status, void *tmp, hipStream_t s);
 // kErrIdRange if an edge of the list has an id out of range

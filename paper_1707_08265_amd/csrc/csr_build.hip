@@ -393,7 +393,7 @@ hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz
 __device__ __forceinline__ bool adjacency_ready(const int32_t *status, bool producers)
 {
     int v = status[0] | status[kStatusInUnsorted] | status[kStatusOutUnsorted] | status[kStatusInGap] | status[kStatusOutGap] |
-            status[kStatusOversize] | status[kStatusPending];
+            status[kStatusPending];
     if (producers) v |= status[kStatusProdUnsorted] | status[kStatusProdGap];
     return v == 0;
 }
@@ -531,7 +531,7 @@ hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *status,
 // Producer words from the tensors' rows (where the pass over the edges did not write them)
 __global__ __launch_bounds__(256) void k_build_producers(GraphView g, int32_t *prod1, int32_t *status)
 {
-    if (status[kStatusOversize] || (status[0] & kErrIdRange)) return;       // (no rows: whatever the memory held before)
+    if (status[0] & kErrIdRange) return;                    // (no rows: whatever the memory held before)
     const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < g.num_tensors; t += gsize) {
         const int32_t pb = g.prod_rowptr[t], pe = g.prod_rowptr[t + 1];

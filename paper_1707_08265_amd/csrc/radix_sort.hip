@@ -429,20 +429,19 @@ template <int kThreads> struct Rows {
     static_assert(kRows == 2 * kThreads, "two rows per thread");
 };
 // A bucket of more than a tile is done a tile after the other by its workgroup; one of more than kSerialTiles (an operator with very
-// many inputs, say) by as many workgroups as it has tiles, in a launch of its own.  There are few such buckets: with more than
-// kMaxBig of them, or one of more than kMaxBucket pairs (a tile adds up the counts of all the bucket's tiles), the list is sorted as a whole.
-constexpr int kSerialTiles = 8, kMaxBig = 64, kBigBlocks = 256;
-constexpr int64_t kMaxBucket = 1 << 21;
+// many inputs, say) by as many workgroups as it has tiles, in a launch of its own: any number of them, of any size.
+constexpr int kSerialTiles = 8, kBigBlocks = 1024;
 constexpr int kRowFillPercent = 75;                     // of a tile, on average, at most
 
-// starts[b] = first position with a key of bucket b or above, big = the buckets of more than `most` pairs; four lanes per bucket probe a quarter of what is left each.
+// starts[b] = first position with a key of bucket b or above, big = the buckets of more than `most` pairs (fewer than max_big); four lanes
+// per bucket probe a quarter of what is left each.
 constexpr int kProbes = 4;
 __global__ __launch_bounds__(256) void k_bucket_starts(const int32_t *keys, int32_t n, int row_bits, int32_t buckets, int32_t most,
-                                                        int32_t *starts, int32_t *big, int32_t *num_big, int32_t *status)
+                                                        int32_t *starts, int32_t *big, int32_t max_big, int32_t *num_big, int32_t *status)
 {
     const int64_t thread = (int64_t)blockIdx.x * 256 + threadIdx.x;
     // For the kernels behind this one, which add to status[0] themselves: all waves of a workgroup have to read the same here.
-    if (thread == 0 && status[0]) status[kStatusNoRows] = 1;
+    if (thread == 0 && (status[0] & kErrIdRange)) status[kStatusNoRows] = 1;
     const int32_t b = (int32_t)min(thread / kProbes, (int64_t)buckets);
     const int probe = threadIdx.x & (kProbes - 1), group = lane_id() & ~(kProbes - 1);
     int32_t lo = 0, hi = b == buckets ? 0 : n;              // the answer is in [lo, hi]
@@ -462,11 +461,9 @@ __global__ __launch_bounds__(256) void k_bucket_starts(const int32_t *keys, int3
     if (b == buckets) lo = n;
     if (probe == 0) {
         starts[b] = lo;
-        auto more_than = [&](int64_t pairs) { return lo + pairs < n && (keys[lo + pairs] >> row_bits) == b; };
-        if (b < buckets && more_than(most)) {
+        if (b < buckets && (int64_t)lo + most < n && (keys[lo + most] >> row_bits) == b) {
             const int at = atomicAdd(num_big, 1);
-            if (at < kMaxBig) big[at] = b;
-            if (at >= kMaxBig || more_than(kMaxBucket)) store_coherent(&status[kStatusOversize], 1);
+            if (at < max_big) big[at] = b;                  // (more only of keys that are no rows, and then nothing is made of them)
         }
     }
 }
@@ -555,28 +552,66 @@ __device__ __forceinline__ void place_rows(uint32_t (*count)[Rows<kThreads>::kRo
 template <int kThreads>
 __device__ __forceinline__ void count_rows(const int32_t *keys, int32_t n, int32_t row0, int row_mask, int *s_rows)
 {
-    for (int32_t i0 = threadIdx.x & ~(kWave - 1); i0 < n; i0 += kThreads) {  // (whole waves)
-        const int32_t i = i0 + lane_id();
-        const int row = i < n ? (keys[i] - row0) & row_mask : -1;
-        const int most = __builtin_amdgcn_readfirstlane(row);
-        const u64 m = ballot64(row == most);
-        if (lane_id() == 0) atomicAdd(&s_rows[most], __popcll(m));
-        else if (row >= 0 && row != most) atomicAdd(&s_rows[row], 1);
+    for (int32_t i0 = threadIdx.x; i0 - lane_id() < n; i0 += kThreads * kRowRounds) {     // (whole waves)
+        int row[kRowRounds];
+#pragma unroll
+        for (int r = 0; r < kRowRounds; ++r) row[r] = i0 + r * kThreads < n ? (keys[i0 + r * kThreads] - row0) & row_mask : -1;
+#pragma unroll
+        for (int r = 0; r < kRowRounds; ++r) {
+            const int most = __builtin_amdgcn_readfirstlane(row[r]);
+            const u64 m = ballot64(row[r] == most);
+            if (most < 0) break;                            // (the same in every lane)
+            if (lane_id() == 0) atomicAdd(&s_rows[most], __popcll(m));
+            else if (row[r] >= 0 && row[r] != most) atomicAdd(&s_rows[row[r]], 1);
+        }
     }
     __syncthreads();
 }
 
-// Big buckets: f(bucket, its first pair, its pairs, tile, its first tile in the table) for every tile of theirs that workgroup
-// `block` of `blocks` takes.
+// Big buckets are done in groups of tiles, a workgroup each: one launch counts every group's rows, the next adds up the groups before
+// its own and goes through its tiles one after the other.  With few tiles to a group there are many groups to be added up, with
+// many little is done at a time: the tiles of a group are 1 up to 64 tiles, 2 up to 256, and so on.  Shuffled builds of 10 M operators, 70
+// of them with 17 000 inputs: 745 us, of 200 000 1 058, one of 4 M 854, of 60 M 2 024 (lists sorted as a whole: 939, 1 345, 1 140 and
+// 2 375); 1 024 workgroups, 256 of them 1 290 in the second case.
+template <int kThreads> struct BigBucket {
+    int32_t tiles, group, groups;
+    __device__ __forceinline__ explicit BigBucket(int32_t pairs)
+    {
+        tiles = (pairs + Rows<kThreads>::kTile - 1) / Rows<kThreads>::kTile;
+        group = 1;
+        while (64 * group * group < tiles) group *= 2;
+        groups = (tiles + group - 1) / group;
+    }
+};
+
+// Whole workgroup: f(bucket, group, the table's row of its first group) for every group that workgroup `block` of kBigBlocks takes.
+// s_item: kThreads + 1 words of LDS that f leaves alone.
 template <int kThreads, typename F>
-__device__ __forceinline__ void big_tiles(const int32_t *starts, const int32_t *big, int num_big, int block, int blocks, F f)
+__device__ __forceinline__ void big_groups(const int32_t *starts, const int32_t *big, int num_big, int block, int *s_item, int *s_wtot, F f)
 {
-    int table0 = 0;
-    for (int e = 0; e < num_big; ++e) {
-        const int32_t b = big[e], lo = starts[b], n = starts[b + 1] - lo;
-        const int tiles = (n + Rows<kThreads>::kTile - 1) / Rows<kThreads>::kTile;
-        for (int t = ((block - table0) % blocks + blocks) % blocks; t < tiles; t += blocks) f(b, lo, n, t, table0);
-        table0 += tiles;
+    const int tid = threadIdx.x;
+    int item0 = 0;                                          // the first group of this stretch of buckets, a thread each
+    for (int e0 = 0; e0 < num_big; e0 += kThreads) {
+        int groups = 0;
+        if (e0 + tid < num_big) {
+            const int32_t b = big[e0 + tid];
+            groups = BigBucket<kThreads>(starts[b + 1] - starts[b]).groups;
+        }
+        const int first = row_scan<kThreads>(groups, s_wtot);
+        s_item[tid] = first;
+        if (tid == kThreads - 1) s_item[kThreads] = first + groups;
+        __syncthreads();
+        const int total = s_item[kThreads];
+        for (int i = ((block - item0) % kBigBlocks + kBigBlocks) % kBigBlocks; i < total; i += kBigBlocks) {
+            int lo = 0, hi = kThreads;                      // the last bucket whose groups begin at or before i
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (s_item[mid] <= i) lo = mid; else hi = mid;
+            }
+            f(big[e0 + lo], i - s_item[lo], item0 + s_item[lo]);
+        }
+        item0 += total;
+        __syncthreads();
     }
 }
 
@@ -596,18 +631,20 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
     __shared__ uint32_t s_count[R::kWaves][R::kRows / 2];
     __shared__ uint32_t s_seen[kOut ? R::kTile / 32 : 1];
     __shared__ int s_wtot[R::kWaves];
-    if (status[kStatusOversize] || status[kStatusNoRows]) return;           // (a key that is no row: the starts need not ascend)
+    if (status[kStatusNoRows]) return;                      // (a key that is no row: the starts need not ascend)
     const int lane = lane_id(), wave = threadIdx.x >> 6, tid = threadIdx.x;
     const int row_mask = (1 << row_bits) - 1;
     int *s_base = s_val;                                    // of a bucket of several tiles (no value is kept in LDS then)
-    if (blockIdx.x >= (unsigned)buckets) {                  // the rows of big buckets are counted by tiles
-        big_tiles<kThreads>(starts, big, *num_big, (int)(blockIdx.x - buckets), kBigBlocks, [&](int32_t b, int32_t lo, int32_t n, int t, int table0) {
-            const int32_t at = lo + t * R::kTile;
+    if (blockIdx.x >= (unsigned)buckets) {                  // the rows of big buckets are counted by groups of tiles
+        static_assert(R::kTile >= 3 * kThreads + 1, "counts, groups of buckets");
+        big_groups<kThreads>(starts, big, *num_big, (int)(blockIdx.x - buckets), s_base + 2 * kThreads, s_wtot,
+                             [&](int32_t b, int group, int table0) {
+            const int32_t lo = starts[b], end = starts[b + 1];
+            const int32_t most = BigBucket<kThreads>(end - lo).group * R::kTile, at = lo + group * most;
             s_base[2 * tid] = s_base[2 * tid + 1] = 0;
             __syncthreads();
-            count_rows<kThreads>(keys + at, min((int32_t)R::kTile, lo + n - at), b << row_bits, row_mask, s_base);
-            reinterpret_cast<int2 *>(big_table + (int64_t)(table0 + t) * R::kRows)[tid] = make_int2(s_base[2 * tid], s_base[2 * tid + 1]);
-            __syncthreads();
+            count_rows<kThreads>(keys + at, min(most, end - at), b << row_bits, row_mask, s_base);
+            reinterpret_cast<int2 *>(big_table + (int64_t)(table0 + group) * R::kRows)[tid] = make_int2(s_base[2 * tid], s_base[2 * tid + 1]);
         });
         return;
     }
@@ -715,7 +752,7 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
     }
 }
 
-// Big buckets, a workgroup per tile: the counts of the bucket's tiles give its rows and where this tile's share of each begins.
+// Big buckets, a workgroup per group of tiles: the counts of the bucket's groups give its rows and where this one's share of each begins.
 template <int kThreads>
 __global__ __launch_bounds__(kThreads)
 void k_big_rows(const int32_t *keys, const int32_t *vals, const int32_t *starts, int32_t buckets, int row_bits, const int32_t *big,
@@ -723,47 +760,52 @@ void k_big_rows(const int32_t *keys, const int32_t *vals, const int32_t *starts,
 {
     using R = Rows<kThreads>;
     __shared__ uint32_t s_count[R::kWaves][R::kRows / 2];
-    __shared__ int s_base[R::kRows];
+    __shared__ int s_base[R::kRows], s_item[kThreads + 1];
     __shared__ int s_wtot[R::kWaves];
     const int found = *num_big;
-    if (found == 0 || status[kStatusOversize] || status[kStatusNoRows]) return;
+    if (found == 0 || status[kStatusNoRows]) return;
     const int wave = threadIdx.x >> 6, tid = threadIdx.x;
+    const uint16_t *const mine = reinterpret_cast<const uint16_t *>(s_count[wave]);
     bool bad = false;
-    big_tiles<kThreads>(starts, big, found, (int)blockIdx.x, kBigBlocks, [&](int32_t b, int32_t lo, int32_t n, int t, int table0) {
-        const int tiles = (n + R::kTile - 1) / R::kTile;
+    big_groups<kThreads>(starts, big, found, (int)blockIdx.x, s_item, s_wtot, [&](int32_t b, int group, int table0) {
+        const int32_t lo = starts[b], end = starts[b + 1];
+        const BigBucket<kThreads> k(end - lo);
         const int32_t row0 = b << row_bits;
         const int rows = min(1 << row_bits, l.num_ops - row0);
-        int all0 = 0, all1 = 0, before0 = 0, before1 = 0;   // of this thread's two rows: in the bucket, in earlier tiles
+        int all0 = 0, all1 = 0, before0 = 0, before1 = 0;   // of this thread's two rows: in the bucket, in earlier groups
         const int2 *table = reinterpret_cast<const int2 *>(big_table + (int64_t)table0 * R::kRows) + tid;
 #pragma unroll 8
-        for (int k = 0; k < tiles; ++k) {
-            const int2 c = table[(int64_t)k * (R::kRows / 2)];
+        for (int q = 0; q < k.groups; ++q) {
+            const int2 c = table[(int64_t)q * (R::kRows / 2)];
             all0 += c.x;
             all1 += c.y;
-            before0 += k < t ? c.x : 0;
-            before1 += k < t ? c.y : 0;
+            before0 += q < group ? c.x : 0;
+            before1 += q < group ? c.y : 0;
         }
         const int first = lo + row_scan<kThreads>(all0 + all1, s_wtot);
-        if (t == 0) {
+        if (group == 0) {
             if (2 * tid < rows) l.row[row0 + 2 * tid] = first;
             if (2 * tid + 1 < rows) l.row[row0 + 2 * tid + 1] = first + all0;
             if (b == buckets - 1 && tid == 0) l.row[l.num_ops] = (int32_t)l.nnz;
         }
         s_base[2 * tid] = first + before0;
         s_base[2 * tid + 1] = first + all0 + before1;
-        const int32_t at = lo + t * R::kTile;
-        const int m = min((int32_t)R::kTile, lo + n - at);
-        TilePairs p;
-        rank_tile<kThreads>(keys + at, vals + at, m, row0, (1 << row_bits) - 1, l.num_tensors, s_count, p, bad);
-        int v0, v1;
-        place_rows<kThreads>(s_count, v0, v1, [](int, int) -> uint32_t { return 0; });
-        const uint16_t *mine = reinterpret_cast<const uint16_t *>(s_count[wave]);
+        for (int t = group * k.group; t < min((group + 1) * k.group, k.tiles); ++t) {
+            const int32_t at = lo + t * R::kTile;
+            const int m = min((int32_t)R::kTile, end - at);
+            TilePairs p;
+            rank_tile<kThreads>(keys + at, vals + at, m, row0, (1 << row_bits) - 1, l.num_tensors, s_count, p, bad);
+            int v0, v1;
+            place_rows<kThreads>(s_count, v0, v1, [](int, int) -> uint32_t { return 0; });
 #pragma unroll
-        for (int r = 0; r < kRowRounds; ++r) {
-            if (r >= p.rounds) break;
-            if (p.first + r * kWave < m) l.idx[s_base[p.row[r]] + mine[p.row[r]] + p.rank[r]] = p.val[r];
+            for (int r = 0; r < kRowRounds; ++r) {
+                if (r >= p.rounds) break;
+                if (p.first + r * kWave < m) l.idx[s_base[p.row[r]] + mine[p.row[r]] + p.rank[r]] = p.val[r];
+            }
+            __syncthreads();
+            s_base[2 * tid] += v0;
+            s_base[2 * tid + 1] += v1;
         }
-        __syncthreads();
     });
     if (ballot64(bad) != 0 && lane_id() == 0) atomicOr(status, kErrIdRange);
 }
@@ -798,12 +840,12 @@ template <int kThreads>
 static hipError_t bucket_rows(const RowPlan &p, const int32_t *keys, const int32_t *vals, int32_t *big_table, const EdgeList &l, bool producers,
                               int32_t *num_big, int32_t *status, const SortTmp &t, hipStream_t s)
 {
-    const int32_t buckets = (int32_t)p.buckets;
+    const int32_t buckets = (int32_t)p.buckets, most = kSerialTiles * Rows<kThreads>::kTile;
     int32_t *starts = t.table, *big = t.totals;             // (the passes are done with them)
     hipLaunchKernelGGL(k_bucket_starts, dim3((unsigned)(buckets / (256 / kProbes) + 1)), dim3(256), 0, s, keys, (int32_t)l.nnz, p.row_bits,
-                       buckets, kSerialTiles * Rows<kThreads>::kTile, starts, big, num_big, status);
+                       buckets, most, starts, big, (int32_t)(l.nnz / most) + 1, num_big, status);
     // (a short list has no big bucket)
-    const bool may_be_big = l.nnz > kSerialTiles * Rows<kThreads>::kTile;
+    const bool may_be_big = l.nnz > most;
     const dim3 grid((unsigned)(buckets + (may_be_big ? kBigBlocks : 0)));
     if (producers)
         hipLaunchKernelGGL((k_bucket_rows<true, kThreads>), grid, dim3(kThreads), 0, s, keys, vals, starts, buckets, p.row_bits, big, num_big,
@@ -833,7 +875,7 @@ hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producer
         keys = t.keys[(p.passes - 1) & 1];
         vals = t.vals[(p.passes - 1) & 1];
     }
-    // counts of the big buckets' tiles: a byte per pair and a row per tile begun, in the buffer that the last pass read
+    // counts of the big buckets' groups of tiles, a byte per pair of a tile each: in the buffer that the last pass read
     int32_t *big_table = t.keys[p.passes & 1];
     return p.threads == 256 ? bucket_rows<256>(p, keys, vals, big_table, l, producers, num_big, status, t, s)
                             : bucket_rows<512>(p, keys, vals, big_table, l, producers, num_big, status, t, s);

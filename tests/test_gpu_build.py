@@ -181,11 +181,20 @@ def test_lists_nearly_in_order(dgn, oracle, ops, outs, fan, order):
 @pytest.mark.parametrize("which", ["inputs", "outputs"])
 @pytest.mark.parametrize("most, rows", [(2048, 1), (2049, 1), (4097, 2), (14_000, 1), (30_000, 1), (30_000, 3), (131_072, 1), (17_000, 70)])
 def test_rows_of_several_tiles_and_many_large_buckets(dgn, oracle, most, rows, which):
-    """Operators with so many inputs or outputs that their bucket is done in tiles by one workgroup or by several, and so many of
-    them that the list is sorted as a whole."""
+    """Operators with so many inputs or outputs that their bucket is done in tiles by one workgroup or by several."""
     rng = np.random.default_rng(most)
     n_out, fan = rng.integers(0, 3, 40_000), rng.integers(0, 4, 40_000)
     (fan if which == "inputs" else n_out)[39_999 - 571 * np.arange(rows)] = most
+    check(dgn, oracle, _shuffled(rng, n_out, fan), rng, f"{which} {most}")
+
+
+@pytest.mark.parametrize("which", ["inputs", "outputs"])
+@pytest.mark.parametrize("ops, most, rows", [(40_000, 17_000, 257), (40_000, 34_817, 60), (300_000, 2_100_000, 1), (300_000, 500_000, 3)])
+def test_more_large_buckets_than_threads_and_very_large_ones(dgn, oracle, ops, most, rows, which):
+    """Their tiles are counted in groups, from nine tiles (three groups) to a thousand."""
+    rng = np.random.default_rng(most)
+    n_out, fan = rng.integers(0, 3, ops), rng.integers(0, 4, ops)
+    (fan if which == "inputs" else n_out)[ops - 1 - ops // rows * np.arange(rows)] = most
     check(dgn, oracle, _shuffled(rng, n_out, fan), rng, f"{which} {most}")
 
 
