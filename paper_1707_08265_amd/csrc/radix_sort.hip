@@ -48,14 +48,13 @@ constexpr int kHistThreads = 1024;
 // Adds the digits of a thread's kPer neighbouring keys to a tile's counts.  In a list that is nearly in order the lanes of a wave
 // mostly have the same digit of the high bits (two of them, where two such lists are interleaved), and an atomic per key has
 // all of them wait for each other: 4 M edges in order but for one took 100 us, in no order 15.  So where many lanes have the digit of
-// one of two, a thread adds up what it has of its first digit and of the next other one, and a wave of one digit alone adds
+// the one in the middle, a thread adds up what it has of its first digit and of the next other one, and a wave of one digit alone adds
 // once: 20 us; builds of two recordings one behind the other, 200 000 operators 305 -> 151, 2 M 637 -> 309, 10 M 1 221 -> 921.
-constexpr int kSameDigit = 8;               // lanes, of two, on average
+constexpr int kSameDigit = 8;               // lanes
 template <int kPer> __device__ __forceinline__ void count_digits(int *hist, const int (&d)[kPer], int valid)
 {
-    auto lanes_with = [&](int lane) { return __popcll(ballot64(d[0] == __builtin_amdgcn_readlane(d[0], lane))); };
-    const int first = lanes_with(0);
-    if (first + lanes_with(kWave / 2) < 2 * kSameDigit) {
+    const int same = __popcll(ballot64(d[0] == __builtin_amdgcn_readlane(d[0], kWave / 2)));
+    if (same < kSameDigit) {
 #pragma unroll
         for (int q = 0; q < kPer; ++q)
             if (q < valid) atomicAdd(&hist[d[q]], 1);
@@ -67,7 +66,7 @@ template <int kPer> __device__ __forceinline__ void count_digits(int *hist, cons
         count += q < valid && d[q] == d[0];
         other = other == d[0] && q < valid ? d[q] : other;
     }
-    if (first == kWave && ballot64(count < kPer) == 0) {
+    if (same == kWave && ballot64(count < kPer) == 0) {
         if (lane_id() == 0) atomicAdd(&hist[d[0]], kWave * kPer);
         return;
     }
@@ -97,27 +96,32 @@ __global__ __launch_bounds__(kHistThreads) void k_sort_hist(const int32_t *keys,
     const bool wide = (reinterpret_cast<uintptr_t>(keys) & 15) == 0;
     constexpr int kPerThread = kSortTile / kThreads;         // keys of a tile that one thread counts
     static_assert(kPerThread % 4 == 0, "a thread counts whole 16-byte groups of keys");
-    for (int t = 0; t < kHistTiles; ++t) {
-        // the order inside a tile does not matter for its counts: a thread takes neighbouring keys
-        const int64_t i = (tile0 + t) * kSortTile + (int64_t)threadIdx.x * kPerThread;
-        if (i - (int64_t)lane_id() * kPerThread >= n) break;             // whole waves stay in the loop
-        int32_t a[kPerThread];
+    // the order inside a tile does not matter for its counts: a thread takes neighbouring keys, and asks for the next tile's ahead
+    int32_t next[kPerThread];
+    auto first_of = [&](int t) { return (tile0 + t) * kSortTile + (int64_t)threadIdx.x * kPerThread; };
+    auto ask = [&](int64_t i) {
         if (wide && i + kPerThread <= n) {
 #pragma unroll
             for (int q = 0; q < kPerThread; q += 4) {
                 const int4 v = *reinterpret_cast<const int4 *>(keys + i + q);
-                a[q] = v.x; a[q + 1] = v.y; a[q + 2] = v.z; a[q + 3] = v.w;
+                next[q] = v.x; next[q + 1] = v.y; next[q + 2] = v.z; next[q + 3] = v.w;
             }
         } else {
 #pragma unroll
-            for (int q = 0; q < kPerThread; ++q) a[q] = i + q < n ? keys[i + q] : 0;
+            for (int q = 0; q < kPerThread; ++q) next[q] = i + q < n ? keys[i + q] : 0;
         }
+    };
+    ask(first_of(0));
+    for (int t = 0; t < kHistTiles; ++t) {
+        const int64_t i = first_of(t);
+        if (i - (int64_t)lane_id() * kPerThread >= n) break;             // whole waves stay in the loop
         int d[kPerThread];
 #pragma unroll
         for (int q = 0; q < kPerThread; ++q) {
-            most = max(most, (uint32_t)a[q]);
-            d[q] = digit_of<kBits>(a[q], shift);
+            most = max(most, (uint32_t)next[q]);
+            d[q] = digit_of<kBits>(next[q], shift);
         }
+        if (t + 1 < kHistTiles) ask(first_of(t + 1));
         count_digits(hist[t], d, (int)min(max(n - i, (int64_t)0), (int64_t)kPerThread));
     }
     __syncthreads();
