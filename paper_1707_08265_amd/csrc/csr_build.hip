@@ -41,7 +41,7 @@ __device__ __forceinline__ void rows_closed(int32_t prev, int32_t cur, int32_t n
 constexpr int kScanThreads = 256;
 
 template <bool kOut, bool kStream>
-__device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int64_t blocks, int32_t *status)
+__device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int64_t blocks, uint32_t *s_words, int32_t *status)
 {
     constexpr int kPer = 4;
     const int32_t *ops = l.op, *tensors = l.tensor;
@@ -145,9 +145,6 @@ __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int6
     // Shuffled input has every workgroup report: once each, its words looked at together, and a store (same value from everyone)
     // only where it is needed.  (12 M operators in shuffled order: 145 us with a look at every word by every wave and the whole
     // list read, 125 when the reading ended early, 59 with one look per workgroup.)
-    __shared__ uint32_t s_words;
-    if (threadIdx.x == 0) s_words = 0;
-    __syncthreads();
     uint32_t words = 0;                                                 // bit w: status word w
     auto report = [&](bool v, int word) { words |= ballot64(v) != 0 ? 1u << word : 0; };
     report(down, kOut ? kStatusOutUnsorted : kStatusInUnsorted);
@@ -159,18 +156,22 @@ __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int6
         report(multi, kStatusMulti);
     }
     if (ballot64(bad) != 0 && lane_id() == 0) atomicOr(status, kErrIdRange);
-    if (words && lane_id() == 0) atomicOr(&s_words, words);
-    __syncthreads();
-    words = s_words;
-    if (threadIdx.x < 32 && (words >> threadIdx.x & 1) && load_coherent(status + threadIdx.x) == 0) store_coherent(status + threadIdx.x, 1);
+    if (words == 0) return;                                             // (wave-uniform)
+    uint32_t others = 0;                                                // what other waves of the workgroup report
+    if (lane_id() == 0) others = atomicOr(s_words, words);
+    words &= ~__builtin_amdgcn_readfirstlane(others);
+    if (lane_id() < 32 && (words >> lane_id() & 1) && load_coherent(status + lane_id()) == 0) store_coherent(status + lane_id(), 1);
 }
 
 // inputs and outputs in one launch; an empty list has one position too (it closes all rows)
 template <bool kStream>
 __global__ __launch_bounds__(kScanThreads) void k_scan_edges(EdgeList in, EdgeList out, int in_blocks, int32_t *status)
 {
-    if ((int)blockIdx.x < in_blocks) scan_list<false, kStream>(in, blockIdx.x, in_blocks, status);
-    else scan_list<true, kStream>(out, (int)blockIdx.x - in_blocks, (int)gridDim.x - in_blocks, status);
+    __shared__ uint32_t s_words;                                        // status words that some wave reports
+    if (threadIdx.x == 0) s_words = 0;
+    __syncthreads();
+    if ((int)blockIdx.x < in_blocks) scan_list<false, kStream>(in, blockIdx.x, in_blocks, &s_words, status);
+    else scan_list<true, kStream>(out, (int)blockIdx.x - in_blocks, (int)gridDim.x - in_blocks, &s_words, status);
 }
 
 static int scan_blocks(int64_t nnz)
