@@ -200,7 +200,7 @@ def test_more_large_buckets_than_threads_and_very_large_ones(dgn, oracle, ops, m
 
 @pytest.mark.parametrize("ops, outs, fan", [(3, 2, 3), (900, 1, 2), (200, 90, 90), (70_001, 2, 5), (300_000, 1, 2), (300_000, 0.03, 0.05)])
 def test_ids_out_of_range_in_lists_in_no_order(dgn, ops, outs, fan):
-    """One id out of range anywhere in either list, whichever way the list is sorted, is reported and nothing is built."""
+    """One id out of range anywhere in either list is reported and nothing is built (the first pass sees all of lists this short)."""
     import torch
     rng = np.random.default_rng(ops)
     count = lambda mean: rng.integers(0, 2 * mean + 1, ops) if mean >= 1 else (rng.random(ops) < mean).astype(np.int64)  # noqa: E731

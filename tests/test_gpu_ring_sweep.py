@@ -380,3 +380,28 @@ def test_wide_operators_at_the_very_end_of_a_large_batch(dgn, oracle, count, las
     g = gg.Graph(int(op_off[-1]), int(t_off[-1]), i32(in_op), i32(in_t), i32(out_op), i32(out_t), count + 1, op_off.astype(np.int64),
                  t_off.astype(np.int64), "wide end")
     check(dgn, oracle, g, [draw_targets(rng, g, 3, 2)])
+
+
+@pytest.mark.parametrize("shuffled", ["", "inputs", "outputs", "both"])
+def test_large_ragged_batches_from_lists_in_other_orders(dgn, oracle, shuffled):
+    """Waves of the build walk several times 64 operators and go from graph to graph in any lane: graphs of 0 to 230 operators, the last
+    one a multiple of 64 with wide rows, whose rows come from lists of which one or both are in no order."""
+    rng = np.random.default_rng(len(shuffled))
+    g = recorded(rng, 5400, 230, 20, 3, 5, 4, empty_every=50)
+    wide = recorded(rng, 1, 128, 40, 30, 9, 4)
+    cat = lambda a, b, off: np.concatenate([a, b + off]).astype(np.int32)  # noqa: E731
+    edges = [cat(g.in_op, wide.in_op, g.num_ops), cat(g.in_tensor, wide.in_tensor, g.num_tensors),
+             cat(g.out_op, wide.out_op, g.num_ops), cat(g.out_tensor, wide.out_tensor, g.num_tensors)]
+    for first, which in ((0, "inputs"), (2, "outputs")):
+        if shuffled in (which, "both"):
+            p = rng.permutation(edges[first].size)
+            edges[first], edges[first + 1] = edges[first][p], edges[first + 1][p]
+    P, T = g.num_ops + wide.num_ops, g.num_tensors + wide.num_tensors
+    assert P > 8192 * 64 and P % 64 != 0
+    h = gg.Graph(P, T, *edges, 5401, np.append(g.graph_op_offsets, P), np.append(g.graph_tensor_offsets, T), "ragged")
+    dg = dgn.DeviceGraph.from_coo(h)
+    adj = oracle.build_adjacency(P, T, h.in_op, h.in_tensor, h.out_op, h.out_tensor)
+    for name, v in dg.csr().items():
+        assert np.array_equal(v.cpu().numpy(), getattr(adj, name)), name
+    # (an operator's tensors keep the order of the list: in no order they are not numbered as the sweep needs them)
+    check(dgn, oracle, h, [draw_targets(rng, h, 3, 2)], swept=shuffled in ("", "inputs"))
