@@ -188,8 +188,9 @@ int dgn_graph_build_workspace(const dgn_coo_desc *desc, size_t *graph_bytes, siz
  * Stable sorts on the significant key bits (a list in order needs none), all inside graph_mem /
  * scratch.  Every id is range-checked on the device (-> DGN_ERR_ID_OUT_OF_RANGE); with
  * options->validate the topological precondition is checked too (-> DGN_ERR_NOT_TOPOLOGICAL).
- * The call synchronises the stream once before returning to report those errors.  options may be
- * NULL.  On success *out receives a handle; scratch may be reused afterwards, graph_mem may not. */
+ * The call synchronises the stream before returning to report those errors (once for lists in order,
+ * up to four times for others).  options may be NULL.  On success *out receives a handle; scratch
+ * may be reused afterwards, graph_mem may not. */
 int dgn_graph_build(const dgn_coo_desc *desc, void *graph_mem, size_t graph_bytes, void *scratch,
                     size_t scratch_bytes, const dgn_options *options, dgn_stream stream,
                     dgn_graph **out);

@@ -282,7 +282,7 @@ __device__ __forceinline__ void write_rows(int32_t *rowptr, int lo, int hi, int3
     }
 }
 
-// Operator records (see common.h), once per graph.
+// An operator's record, as GraphView::orec describes it
 template <bool kStream>
 __device__ __forceinline__ void write_record(int4 *p, int32_t ib, int32_t ie, int32_t ob, int32_t oe, int32_t first, bool consecutive)
 {

@@ -582,9 +582,22 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
     const int64_t begin = wave_id * per, last = min(begin + per, (int64_t)g.num_ops);
     bool bad = false, scattered = false;
     int low = 0, dist = 0, span64 = 0, reach = 0;
-    int gi = -1;
+    int gi = 0;
     int64_t lo = 0, hi = g.num_tensors, o_lo = 0, o_hi = g.num_ops;
     int32_t shift = 0, t_first = 0;                         // output edge e should be tensor e + shift
+    auto enter = [&](int64_t o) {                           // the graph of o, gi or one behind it
+        if (batched) {
+            while (o >= g.op_off[gi + 1]) ++gi;             // op_off[num_graphs] == num_ops > o: stops in range
+            lo = g.t_off[gi];
+            hi = g.t_off[gi + 1];
+            o_lo = g.op_off[gi];
+            o_hi = g.op_off[gi + 1];
+        }
+        shift = (int32_t)hi - g.out_rowptr[o_hi];
+        t_first = g.out_rowptr[o_lo] + shift;
+        if (t_first < lo) scattered = true;                 // more outputs than tensors
+        low = max(low, t_first - (int32_t)lo);
+    };
     // (at the first operators of some of the waves; a batch of 64 graphs and more goes one way whatever it reads)
     const bool samples = (batched ? g.num_graphs < 64 : status[kStatusScattered] == 0) &&
                          wave_id % ((waves + kSampleWaves - 1) / kSampleWaves) == 0;
@@ -617,6 +630,9 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
     if (begin < last) {                                     // wave-uniform, as the two below
         next = row_of(begin + lane_id());
         if (begin + kWave < last) after = row_of(begin + kWave + lane_id());
+        const int64_t o = min(begin + lane_id(), last - 1);
+        if (batched) gi = find_graph(g.op_off, g.num_graphs, o);
+        enter(o);                                           // (asked for before the wait for the rows)
         next_entries = entries_of(next);
     }
     for (int64_t base = begin; base < last; base += kWave) {
@@ -630,22 +646,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
             if (base + 2 * kWave < last) after = row_of(o + 2 * kWave);
         }
         if (o >= last) break;                               // (the last step)
-        if (gi < 0 || o >= o_hi) {
-            if (batched) {
-                if (gi < 0) gi = find_graph(g.op_off, g.num_graphs, o);
-                while (o >= g.op_off[gi + 1]) ++gi;         // op_off[num_graphs] == num_ops > o: stops in range
-                lo = g.t_off[gi];
-                hi = g.t_off[gi + 1];
-                o_lo = g.op_off[gi];
-                o_hi = g.op_off[gi + 1];
-            } else {
-                gi = 0;
-            }
-            shift = (int32_t)hi - g.out_rowptr[o_hi];
-            t_first = g.out_rowptr[o_lo] + shift;
-            if (t_first < lo) scattered = true;             // more outputs than tensors
-            low = max(low, t_first - (int32_t)lo);
-        }
+        if (o >= o_hi) enter(o);
         if (samples && o - lane_id() == begin)
             sample_reach(ie > ib, o - o_lo, t[0], o_hi - o_lo, t_first, hi - t_first, ob + shift, status);
         auto input = [&](int32_t x) {
