@@ -576,7 +576,7 @@ __device__ __forceinline__ void count_rows(const int32_t *keys, int32_t n, int32
 // its own and goes through its tiles one after the other.  With few tiles to a group there are many groups to be added up, with
 // many little is done at a time: the tiles of a group are 1 up to 64 tiles, 2 up to 256, and so on.  Shuffled builds of 10 M operators, 70
 // of them with 17 000 inputs: 745 us, of 200 000 1 058, one of 4 M 854, of 60 M 2 024 (lists sorted as a whole: 939, 1 345, 1 140 and
-// 2 375); 1 024 workgroups, 256 of them 1 290 in the second case.
+// 2 375).
 template <int kThreads> struct BigBucket {
     int32_t tiles, group, groups;
     __device__ __forceinline__ explicit BigBucket(int32_t pairs)
