@@ -407,15 +407,20 @@ int read_status(const int32_t *status, hipStream_t s, const int32_t **out)
 // Packed batches, and single graphs that the ring sweep may take, are checked in the walk that makes the records.
 bool walked(const dgn_graph *h) { return h->G > 1 || h->P <= kRingMaxOps; }
 
-// What follows the adjacency.  The kernels find out by themselves whether there is one yet.  made: single graphs that are not walked
-// have their records.
-int enqueue_records(const dgn_graph *h, const GraphLayout &L, int32_t *status, const dgn_options *options, hipStream_t s, bool made = false)
+// The pass over the outputs leaves out the producer words of what may be one run of tensors up to the last.  A batch's outputs hardly
+// ever are: its graphs have inputs of their own.
+bool may_run(const dgn_graph *h) { return h->G == 1; }
+
+// What follows the adjacency.  The kernels find out by themselves whether there is one yet.  words: all producer words are there; none: the
+// outputs are one run, or there is no adjacency yet, so that there are no records to be made.
+int enqueue_records(const dgn_graph *h, const GraphLayout &L, int32_t *status, const dgn_options *options, hipStream_t s, bool words, bool none = false)
 {
+    int32_t *spared = may_run(h) && !words ? L.prod1 : nullptr;
     if (walked(h)) {
-        DGN_HIP(launch_records_and_check(h->v, L.orec, status, h->num_cus, s));
+        DGN_HIP(launch_records_and_check(h->v, L.orec, spared, status, h->num_cus, s));
     } else {
-        if (made) DGN_HIP(launch_sample_reach(h->v, status, s));
-        else DGN_HIP(launch_build_records(h->v, L.orec, status, s));
+        if (none) DGN_HIP(launch_sample_reach(h->v, status, s));
+        else DGN_HIP(launch_build_records(h->v, L.orec, spared, status, s));
         if (options && options->validate) DGN_HIP(launch_check_topological(h->v, status, s));
     }
     return DGN_OK;
@@ -444,7 +449,7 @@ int build_producers(const dgn_graph *h, const GraphLayout &L, const BuildScratch
     if (keys) {
         DGN_HIP(launch_row_bounds(keys, h->Eout, (int32_t)h->T, L.prod_rowptr, S.status, s));
     } else {
-        const EdgeList list{h->v.out_idx, ops_of_out, h->Eout, (int32_t)h->T, (int32_t)h->P, L.prod_idx, L.prod_rowptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+        const EdgeList list{h->v.out_idx, ops_of_out, h->Eout, (int32_t)h->T, (int32_t)h->P, L.prod_idx, L.prod_rowptr, nullptr, nullptr, nullptr, false};
         const int rc = sort_rows(list, S, buckets, true, kStatusBig + 2, s);
         if (rc) return rc;
     }
@@ -474,6 +479,7 @@ int finish_build(dgn_graph *h, const int64_t *op_off_host, const int64_t *t_off_
     h->ring_dist = ring[2];
     h->ring_span64 = ring[3];
     h->ring_reach = found[kStatusReach];
+    h->v.run_shift = found[kStatusNoRun] == 0 ? (int32_t)(h->T - h->Eout) : -1;
     h->multi_producer = found[kStatusMulti] != 0;
     auto most = [&](int word) { return found[word] * 2 > found[kStatusSampled]; };
     h->reads_about = !most(kStatusWithin8);
@@ -554,11 +560,8 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
         ops_of_out = S.sorted_ops;
         if (plan.use) {
             // where tensors are numbered as they are created, this is all
-            EdgeList with = out;
-            with.orec = walked(h) ? nullptr : L.orec;
-            with.in_row = L.in_rowptr;
-            DGN_HIP(launch_bucket_rows(plan, with, true, S.status + kStatusBig + 1, S.status, S.sort_tmp, s));
-            rc = enqueue_records(h, L, S.status, options, s, true);
+            DGN_HIP(launch_bucket_rows(plan, out, true, S.status + kStatusBig + 1, S.status, S.sort_tmp, s));
+            rc = enqueue_records(h, L, S.status, options, s, true, true);
             if (rc) return rc;
             rc = read_status(S.status, s, found);
             if (rc || (*found)[0] || !(*found)[kStatusPending]) return rc;
@@ -572,9 +575,9 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
         // tensors ascend with their operators that is the order by tensor, whatever order they came in, and they need no
         // second sort.
         DGN_HIP(launch_order_rows(S.sorted_ops, L.out_idx, Eout, S.sorted_keys, S.status, s));
-        const EdgeList sorted{S.sorted_ops, S.sorted_keys, Eout, (int32_t)P, (int32_t)T, nullptr, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1, nullptr, nullptr};
+        const EdgeList sorted{S.sorted_ops, S.sorted_keys, Eout, (int32_t)P, (int32_t)T, nullptr, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1, may_run(h)};
         DGN_HIP(launch_scan_edges(nullptr, sorted, S.status, s));
-        rc = enqueue_records(h, L, S.status, options, s);
+        rc = enqueue_records(h, L, S.status, options, s, false);
         if (rc) return rc;
         rc = read_status(S.status, s, found);
         if (rc) return rc;
@@ -591,7 +594,7 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
         rc = build_producers(h, L, S, ops_of_out, prod_unsorted ? nullptr : by_tensor, true, s);
         if (rc) return rc;
     }
-    rc = enqueue_records(h, L, S.status, options, s);
+    rc = enqueue_records(h, L, S.status, options, s, prod_unsorted || prod_gap);
     if (rc) return rc;
     return read_status(S.status, s, found);
 }
@@ -608,10 +611,10 @@ int build_from_lists(dgn_graph *h, const dgn_coo_desc *d, const GraphLayout &L, 
     DGN_HIP(launch_clear(clr, 1, s));
     int rc = copy_offsets(h, L, d->graph_op_offsets, d->graph_tensor_offsets, s);
     if (rc) return rc;
-    const EdgeList in{d->in_op, d->in_tensor, Ein, (int32_t)P, (int32_t)T, L.in_idx, L.in_rowptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-    const EdgeList out{d->out_op, d->out_tensor, Eout, (int32_t)P, (int32_t)T, L.out_idx, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1, nullptr, nullptr};
+    const EdgeList in{d->in_op, d->in_tensor, Ein, (int32_t)P, (int32_t)T, L.in_idx, L.in_rowptr, nullptr, nullptr, nullptr, false};
+    const EdgeList out{d->out_op, d->out_tensor, Eout, (int32_t)P, (int32_t)T, L.out_idx, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1, may_run(h)};
     DGN_HIP(launch_scan_edges(&in, out, S.status, s));
-    rc = enqueue_records(h, L, S.status, options, s);
+    rc = enqueue_records(h, L, S.status, options, s, false);
     if (rc) return rc;
     rc = read_status(S.status, s, found);
     if (rc) return rc;
@@ -685,7 +688,7 @@ int dgn_graph_build(const dgn_coo_desc *d, void *graph_mem, size_t graph_bytes, 
     if (rc) return rc;
     h->P = P; h->T = T; h->Ein = Ein; h->Eout = Eout; h->G = d->num_graphs;
     h->v = GraphView{(int32_t)P, (int32_t)T, (int32_t)Ein, (int32_t)Eout, d->num_graphs, L.in_rowptr, L.in_idx,
-                     L.out_rowptr, L.out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.prod1};
+                     L.out_rowptr, L.out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.prod1, -1};
     const int32_t *found = nullptr;
     rc = build_from_lists(h, d, L, S, options, s, &found);
     if (!rc) rc = finish_build(h, d->graph_op_offsets, d->graph_tensor_offsets, S.status, found, options, s, out);
@@ -729,7 +732,7 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
     if (rc) return rc;
     h->P = P; h->T = T; h->Ein = Ein; h->Eout = Eout; h->G = d->num_graphs;
     h->v = GraphView{(int32_t)P, (int32_t)T, (int32_t)Ein, (int32_t)Eout, d->num_graphs, d->in_rowptr, d->in_idx,
-                     d->out_rowptr, d->out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.prod1};
+                     d->out_rowptr, d->out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.prod1, -1};
     const int32_t *found = nullptr;
     auto fill = [&]() -> int {
         FillRegion clr[1] = {{S.status, 256}};
@@ -741,9 +744,9 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
         DGN_HIP(launch_check_csr(h->v, S.status, s));
         // the outputs as a list in operator order: its tensors usually ascend as well, and the pass over it is all it takes
         DGN_HIP(launch_expand_rows(d->out_rowptr, (int32_t)P, (int32_t)Eout, S.sorted_ops, S.status, s));
-        const EdgeList list{S.sorted_ops, d->out_idx, Eout, (int32_t)P, (int32_t)T, nullptr, nullptr, L.prod_idx, L.prod_rowptr, L.prod1, nullptr, nullptr};
+        const EdgeList list{S.sorted_ops, d->out_idx, Eout, (int32_t)P, (int32_t)T, nullptr, nullptr, L.prod_idx, L.prod_rowptr, L.prod1, may_run(h)};
         DGN_HIP(launch_scan_edges(nullptr, list, S.status, s));
-        e = enqueue_records(h, L, S.status, options, s);
+        e = enqueue_records(h, L, S.status, options, s, false);
         if (e) return e;
         e = read_status(S.status, s, &found);
         if (e || (found[0] & (kErrCsr | kErrIdRange)) || !(found[kStatusProdUnsorted] || found[kStatusProdGap])) return e;
@@ -751,7 +754,7 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
         if (e) return e;
         FillRegion ready[1] = {{S.status, kStatusOrder * sizeof(int32_t)}};
         DGN_HIP(launch_clear(ready, 1, s));
-        e = enqueue_records(h, L, S.status, options, s);
+        e = enqueue_records(h, L, S.status, options, s, true);
         if (e) return e;
         return read_status(S.status, s, &found);
     };

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kLinkThreads) void k_link_kept(GraphView g, const i
         const int64_t i = base + threadIdx.x;                           // whole workgroups stay in the loop
         int eb = 0, deg = 0;
         if (i < n) {
-            const int4 r = g.orec[kept[i]];
+            const int4 r = op_record(g, kept[i]);
             eb = r.x;
             deg = r.y;
         }
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kLinkThreads) void k_link_kept(GraphView g, const i
             const int e = w0 + lane;
             if (e < total) {
                 const int32_t x = g.in_idx[o_eb + (e - o_excl)];
-                const int32_t p = g.prod1[x];
+                const int32_t p = producer_of(g, x);
                 int32_t link = -1;
                 if (p >= 0) link = (int32_t)place[p] - 1;
                 else if (p == kMulti) link = -2 - x;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kFwThreads) void k_write_marks(GraphView g, bool se
     const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gsize) {
         const int32_t o = kept[i];
-        const int4 r = g.orec[o];
+        const int4 r = op_record(g, o);
         const u64 fo = FO[i];
         const int n_out = r.w >= 0 ? r.w : -r.w;
         u64 k = 0;

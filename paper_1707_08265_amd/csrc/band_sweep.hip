@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kBandPlanThreads) void k_band_plan(BandArgs a)
 #pragma unroll
     for (int j = 0; j < kBandPer; ++j) {
         const int32_t o = lo + min(j * kBandPlanThreads + tid, n - 1);
-        rec[j] = g.orec[o];
+        rec[j] = op_record(g, o);
         ob[j] = g.out_rowptr[o];
         oe[j] = g.out_rowptr[o + 1];
     }
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kBandPlanThreads) void k_band_plan(BandArgs a)
         }
     }
 #pragma unroll
-    for (int j = 0; j < kBandPer; ++j) newest[j] = newest[j] >= 0 ? g.prod1[newest[j]] : -1;
+    for (int j = 0; j < kBandPer; ++j) newest[j] = newest[j] >= 0 ? producer_of(g, newest[j]) : -1;
 #pragma unroll
     for (int j = 0; j < kBandPer; ++j)
         if (j * kBandPlanThreads + tid < n) s_begin[j * kBandPlanThreads + tid] = newest[j];
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
                     k = (uint32_t)ring[e.x & 0xffff] | ring[e.x >> 16];
                     k = valid ? k : 0;
                     if (__builtin_expect(valid && e.z >> 16 == kBandMore, 0)) {
-                        const int4 rec = g.orec[from + tid];
+                        const int4 rec = op_record(g, from + tid);
 #pragma unroll 1
                         for (int j = 2; j < rec.w; ++j) k |= ring[band_slot(rec.z + j, t_first)];
                         if (k)

@@ -32,9 +32,13 @@ struct GraphView {
     const int32_t *out_rowptr, *out_idx;
     const int32_t *prod_rowptr, *prod_idx;
     const int64_t *op_off, *t_off;    // [G+1] device copies, NULL when num_graphs == 1
-    // What the traversal reads per operator and per pushed tensor, one access each (see traverse.hip):
+    // What the traversal reads per operator and per pushed tensor (see traverse.hip).  Of graphs whose outputs are one run of tensors
+    // (run_shift >= 0) it follows from the adjacency, and these two are not written.
     const int4 *orec;                 // [P] operator record (first input edge, fan-in, outputs)
     const int32_t *prod1;             // [T] the producer of a tensor, or kMulti / kNoProducer
+    // >= 0: the outputs of operator o are the tensors out_rowptr[o] + run_shift .. out_rowptr[o + 1] + run_shift - 1 (in any order
+    // inside its row), each written by nobody else, so that tensor t is written by prod_idx[t - run_shift]; -1: not so
+    int32_t run_shift;
 };
 
 // Operator record: x = first entry of the operator's row in in_idx, y = its fan-in, and the outputs: w >= 0
@@ -44,6 +48,30 @@ struct GraphView {
 // prod1 values below zero:
 constexpr int32_t kMulti = -2;        // several producers: see prod_rowptr / prod_idx
 constexpr int32_t kNoProducer = -3;   // graph input
+
+// The record of operator o and the producer word of tensor t.  Graphs in one run have neither in memory: their rows say the same, and
+// not writing them spares a build of 50 M operators 1.6 of 5.6 GB (1 183 -> 845 us); a record then is two accesses of 8 bytes
+// side by side instead of one of 16.  kRun: run_shift >= 0, known when the kernel is launched.
+typedef int IntPair __attribute__((ext_vector_type(2), aligned(4)));
+template <bool kRun> __device__ __forceinline__ int4 op_record(const GraphView &g, int32_t o)
+{
+    if (!kRun) return g.orec[o];
+    const IntPair in = *reinterpret_cast<const IntPair *>(g.in_rowptr + o), out = *reinterpret_cast<const IntPair *>(g.out_rowptr + o);
+    return make_int4(in.x, in.y - in.x, out.x + g.run_shift, out.y - out.x);
+}
+template <bool kRun> __device__ __forceinline__ int32_t producer_of(const GraphView &g, int32_t t)
+{
+    if (!kRun) return g.prod1[t];
+    return t >= g.run_shift ? g.prod_idx[t - g.run_shift] : kNoProducer;
+}
+__device__ __forceinline__ int4 op_record(const GraphView &g, int32_t o)
+{
+    return g.run_shift >= 0 ? op_record<true>(g, o) : op_record<false>(g, o);
+}
+__device__ __forceinline__ int32_t producer_of(const GraphView &g, int32_t t)
+{
+    return g.run_shift >= 0 ? producer_of<true>(g, t) : producer_of<false>(g, t);
+}
 
 // Record of one launch of the traversal: the state it started from and whether it ran a level.
 // Launch e writes record e & 1 (one thread, at its start) and reads record (e - 1) & 1, which nobody
@@ -302,7 +330,8 @@ enum : int {
     kStatusPending = 10,         // ... rows by tensor that do not follow from the rows by operator
     kStatusBig = 11,             // ... how many of them are large: inputs, outputs, outputs by tensor
     kStatusMulti = 16,           // some tensor has several producers
-    kStatusScattered = 17,       // the outputs are not one run of tensors up to the last one
+    kStatusScattered = 17,       // the outputs are not one run of tensors up to the last one, or not in this order inside every row
+    kStatusNoRun = 18,           // ... in whatever order inside the rows (see GraphView::run_shift)
     kStatusRing = 20,            // what k_records_and_check finds out for the ring sweep: [0] != 0: outputs are not one run or
                                  // read too early; [1] graph inputs, [2] dist, [3] span64 (maxima)
     kStatusSampled = 24,         // operators whose first input was looked at (their graph's outputs are one run) ...
@@ -321,15 +350,14 @@ struct EdgeList {
     int32_t num_ops, num_tensors;
     int32_t *idx, *row;                          // rows by operator
     int32_t *prod_idx, *prod_row, *prod1;        // outputs: rows by tensor, producer words
-    int4 *orec;                                  // outputs by way of buckets: operator records (NULL: not here), from the rows of the inputs
-    const int32_t *in_row;
+    bool may_run;                                // producer words of tensors where one run up to the last would have them are left out
 };
 // Rows of a list in no order by way of buckets of 2^row_bits rows: `passes` sorting passes of pass_bits bits bring it into
 // buckets, a workgroup of `threads` each does the rest (see radix_sort.hip).  use: that is fewer passes over memory than the sort takes.
 struct RowPlan { bool use; int row_bits, passes, pass_bits, threads; int64_t buckets; };
 RowPlan plan_rows(int64_t nnz, int64_t rows, int key_bits);
-// l.row, l.idx and, with `producers`, the rows by tensor, producer words and records.  kErrIdRange: there are ids out of range;
-// kStatusPending: the rows by operator are written, those by tensor are not.  tmp: scratch of sort_tmp_bytes(l.nnz) bytes.
+// l.row, l.idx and, with `producers`, the rows by tensor.  kErrIdRange: there are ids out of range; kStatusPending: the rows by
+// operator are written, those by tensor are not (the outputs are no run of tensors).  tmp: scratch of sort_tmp_bytes(l.nnz) bytes.
 // num_big: a word of the status, zero before.
 hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producers, int32_t *num_big, int32_t *status, void *tmp, hipStream_t s);
 // kErrIdRange if an edge of the list has an id out of range
@@ -338,11 +366,12 @@ hipError_t launch_check_ids(const EdgeList &l, int32_t *status, hipStream_t s);
 // order, writes the finished adjacency
 hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s);
 // The kernels from here to launch_check_topological do nothing if the status says that there is no adjacency yet.
-// what launch_build_records notes about how far back operators read, where their records are written already
+// what launch_build_records notes about how far back operators read, where there are no records to be made
 hipError_t launch_sample_reach(const GraphView &g, int32_t *status, hipStream_t s);
-// operator records of a single graph / of graphs that are also checked for range and for the ring sweep
-hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *status, hipStream_t s);
-hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *status, int num_cus, hipStream_t s);
+// operator records (unless the outputs are one run) of a single graph / of graphs that are also checked for range and for the ring
+// sweep.  prod1: producer words that the pass over the outputs left out (EdgeList::may_run), or NULL: there are none
+hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *status, hipStream_t s);
+hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *status, int num_cus, hipStream_t s);
 hipError_t launch_check_topological(const GraphView &g, int32_t *status, hipStream_t s);
 // producer words from prod_rowptr / prod_idx; kStatusMulti when some tensor has several producers
 hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *status, hipStream_t s);

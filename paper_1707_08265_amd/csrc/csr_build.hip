@@ -29,15 +29,16 @@ __device__ __forceinline__ void rows_closed(int32_t prev, int32_t cur, int32_t n
 // One pass over an edge list in the order it was handed over: range check of both ids, whether the keys ever decrease
 // (*unsorted = 1), and -- on the assumption that they do not, which holds for a graph recorded operator by operator --
 // the finished rows: the operators' row pointers (first position of every operator) and row entries, and for a list of
-// outputs also the tensors' (first position of every tensor, producers) and producer words.  If the keys do decrease
+// outputs also the tensors' (first position of every tensor, producers) and, unless the outputs are one run of tensors up to the last
+// (EdgeList::may_run), producer words.  If the keys do decrease
 // somewhere, what was written is overwritten by the sort that follows, which also checks every id once more: a wave that has met such a
 // place leaves the rest.  No atomic in the common case.
 //
-// A stream of 12 bytes per input edge and 28 per output edge and tensor: it is bound by memory.  A thread takes four
+// A stream of 12 bytes per input edge and 24 per output edge and tensor: it is bound by memory.  A thread takes four
 // neighbouring positions per step, in 16-byte accesses where the arrays are aligned for them (one position per thread left
 // the pass waiting for memory).  Outputs take both adjacencies and the producer words from one reading: three passes did
 // that before, 0.99 ms of a 50 M-operator graph and 0.3 more for the producer words; then 1.00 in all, with its stores past the
-// caches 0.91 = 4.5 TB/s.
+// caches 0.91, without the producer words of one run 0.81 = 4.9 TB/s.
 constexpr int kScanThreads = 256;
 
 template <bool kOut, bool kStream>
@@ -114,14 +115,15 @@ __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int6
             }
             if (run) {                                                  // four new tensors in a row, each with one producer
                 int32_t *row = l.prod_row + t[1], *word = l.prod1 + t[1];
+                const bool spared = l.may_run && t[1] == (int32_t)e0 + shift;
                 if (((reinterpret_cast<uintptr_t>(row) | reinterpret_cast<uintptr_t>(word)) & 15) == 0) {
                     store16<kStream>(row, (int)e0, (int)e0 + 1, (int)e0 + 2, (int)e0 + 3);
-                    store16<kStream>(word, k[1], k[2], k[3], k[4]);
+                    if (!spared) store16<kStream>(word, k[1], k[2], k[3], k[4]);
                 } else {
 #pragma unroll
                     for (int j = 0; j < kPer; ++j) {
                         row[j] = (int32_t)e0 + j;
-                        word[j] = k[j + 1];
+                        if (!spared) word[j] = k[j + 1];
                     }
                 }
             }
@@ -153,6 +155,7 @@ __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int6
         report(tdown, kStatusProdUnsorted);
         report(tgap, kStatusProdGap);
         report(scattered, kStatusScattered);
+        report(scattered, kStatusNoRun);
         report(multi, kStatusMulti);
     }
     if (ballot64(bad) != 0 && lane_id() == 0) atomicOr(status, kErrIdRange);
@@ -404,13 +407,14 @@ __device__ __forceinline__ bool adjacency_ready(const int32_t *status, bool prod
 __global__ __launch_bounds__(256) void k_check_topological(GraphView g, int32_t *error)
 {
     if (!adjacency_ready(error, true)) return;
+    g.run_shift = error[kStatusNoRun] == 0 ? g.num_tensors - g.nnz_out : -1;
     const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
     bool bad = false;
     for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < g.num_ops; o += gsize) {
         for (int32_t e = g.in_rowptr[o]; e < g.in_rowptr[o + 1]; ++e) {
             const int32_t t = g.in_idx[e];
             if (t < 0 || t >= g.num_tensors) continue;      // reported by the range check
-            const int32_t pr = g.prod1[t];                  // one word instead of two CSR hops
+            const int32_t pr = producer_of(g, t);           // one word instead of two CSR hops
             if (pr >= 0) {
                 if (pr >= o) bad = true;
             } else if (pr == kMulti) {
@@ -479,13 +483,28 @@ __device__ __forceinline__ void sample_single(const GraphView &g, int place, int
                  (in_range ? g.out_rowptr[o] : 0) + shift, status);
 }
 
-// ... where the records are written already
+// ... where there are no records to be made
 __global__ __launch_bounds__(kWave) void k_sample_reach(GraphView g, int32_t *status)
 {
     if (adjacency_ready(status, false) && status[kStatusScattered] == 0) sample_single(g, blockIdx.x, gridDim.x, status);
 }
 
-static int record_blocks(int64_t num_ops) { return (int)(num_ops + 255 < (int64_t)8192 * 256 ? (num_ops + 255) / 256 : 8192); }
+static int record_blocks(int64_t num_ops) { return (int)(num_ops + 255 < (int64_t)2048 * 256 ? (num_ops + 255) / 256 : 2048); }
+
+// The outputs have turned out not to be one run of tensors: producer words that the pass over them left out, taking it for one.  Where no
+// tensor has several producers those are the last ones of the list (a list without gaps from somewhere on); else any whose place says so.
+__device__ __forceinline__ void fill_spared_words(const GraphView &g, int32_t *prod1, const int32_t *status, int64_t gtid, int64_t gsize)
+{
+    if (!prod1 || !adjacency_ready(status, true)) return;
+    const int32_t shift = g.num_tensors - g.nnz_out;
+    int32_t lo = max(0, -shift), hi = g.nnz_out;
+    while (status[kStatusMulti] == 0 && hi > lo) {          // first position e whose tensor is e + shift
+        const int32_t mid = lo + (hi - lo) / 2;
+        if (g.prod_rowptr[mid + shift] == mid) hi = mid; else lo = mid + 1;
+    }
+    for (int64_t e = lo + gtid; e < g.nnz_out; e += gsize)
+        if (g.prod_rowptr[e + shift] == e && g.prod_rowptr[e + shift + 1] == e + 1) prod1[e + shift] = g.prod_idx[e];
+}
 
 hipError_t launch_sample_reach(const GraphView &g, int32_t *status, hipStream_t s)
 {
@@ -495,37 +514,34 @@ hipError_t launch_sample_reach(const GraphView &g, int32_t *status, hipStream_t 
     return hipGetLastError();
 }
 
-// Single graphs.  Outputs that are one run of tensors (see scan_list) need no look at out_idx.
+// Single graphs.  Outputs that are one run of tensors have no records.
 template <bool kStream>
-__global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, int32_t *status)
+__global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, int32_t *prod1, int32_t *status)
 {
     if (!adjacency_ready(status, false)) return;
-    const bool one_run = status[kStatusScattered] == 0;
-    const int32_t shift = g.num_tensors - g.nnz_out;
-    const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
-    if (one_run && blockIdx.x < kSampleWaves && threadIdx.x < kWave)
+    if (status[kStatusScattered] == 0 && blockIdx.x < kSampleWaves && threadIdx.x < kWave)
         sample_single(g, blockIdx.x, min((int)gridDim.x, kSampleWaves), status);
-    for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < g.num_ops; o += gsize) {
+    if (status[kStatusNoRun] == 0) return;
+    const int64_t gsize = (int64_t)gridDim.x * blockDim.x, gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t o = gtid; o < g.num_ops; o += gsize) {
         const int32_t ib = g.in_rowptr[o], ie = g.in_rowptr[o + 1];
         const int32_t ob = g.out_rowptr[o], oe = g.out_rowptr[o + 1];
-        int32_t first = oe > ob ? ob + shift : 0;
+        const int32_t first = oe > ob ? g.out_idx[ob] : 0;
         bool consecutive = true;
-        if (!one_run) {
-            first = oe > ob ? g.out_idx[ob] : 0;
-            for (int32_t e = ob + 1; e < oe; ++e) consecutive &= g.out_idx[e] == first + (e - ob);
-        }
+        for (int32_t e = ob + 1; e < oe; ++e) consecutive &= g.out_idx[e] == first + (e - ob);
         write_record<kStream>(&orec[o], ib, ie, ob, oe, first, consecutive);
     }
+    fill_spared_words(g, prod1, status, gtid, gsize);
 }
 
-hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *status, hipStream_t s)
+hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *status, hipStream_t s)
 {
     if (g.num_ops == 0) return hipSuccess;
     const int blocks = record_blocks(g.num_ops);
     if ((size_t)g.num_ops * sizeof(int4) > kStreamBytes)
-        hipLaunchKernelGGL(k_build_records<true>, dim3((unsigned)blocks), dim3(256), 0, s, g, orec, status);
+        hipLaunchKernelGGL(k_build_records<true>, dim3((unsigned)blocks), dim3(256), 0, s, g, orec, prod1, status);
     else
-        hipLaunchKernelGGL(k_build_records<false>, dim3((unsigned)blocks), dim3(256), 0, s, g, orec, status);
+        hipLaunchKernelGGL(k_build_records<false>, dim3((unsigned)blocks), dim3(256), 0, s, g, orec, prod1, status);
     return hipGetLastError();
 }
 
@@ -556,7 +572,7 @@ hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *s
     return hipGetLastError();
 }
 
-// Records of a packed batch, or of a single graph that the ring sweep may take, and in the same walk over the edges: does
+// Records (unless the outputs are one run) of a packed batch, or of a single graph that the ring sweep may take, and in the same walk over the edges: does
 // every edge of an operator of graph g touch a tensor of graph g, and whether and how the ring sweep can take the graphs
 // (status words from kStatusRing on; see ring_sweep.hip): are the outputs of every graph one run of tensors that ends
 // with its last one, how many tensors lie before that run, how far below the end of its own outputs does an operator read,
@@ -567,10 +583,11 @@ hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *s
 constexpr int kCheckThreads = 256;
 
 template <bool kStream>
-__global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g, int4 *orec, int32_t *status)
+__global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g, int4 *orec, int32_t *prod1, int32_t *status)
 {
     __shared__ int s_found[6];                      // error, scattered, low, dist, span64, reach
     if (!adjacency_ready(status, false)) return;
+    const bool records = status[kStatusNoRun] != 0;
     if (threadIdx.x < 6) s_found[threadIdx.x] = 0;
     __syncthreads();
     // a wave walks a contiguous stretch of operators 64 at a time, so a lane's graph index only ever steps
@@ -672,10 +689,11 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
         for (int j = 0; j < 2; ++j)
             if (ob + j < oe) output(ob + j, u[j]);
         for (int32_t e = ob + 2; e < oe; ++e) output(e, g.out_idx[e]);
-        write_record<kStream>(&orec[o], ib, ie, ob, oe, first, consecutive);
+        if (records) write_record<kStream>(&orec[o], ib, ie, ob, oe, first, consecutive);
         if (((o - o_lo) & (kWave - 1)) == 0)                // (the outputs of 64 operators end where those of the next begin)
             span64 = max(span64, (o + kWave <= o_hi && base + kWave < last ? next.ob : g.out_rowptr[min(o + kWave, o_hi)]) - ob);
     }
+    if (records) fill_spared_words(g, prod1, status, (int64_t)blockIdx.x * kCheckThreads + threadIdx.x, (int64_t)gridDim.x * kCheckThreads);
     const int wlow = wave_max(low), wdist = wave_max(dist), wspan = wave_max(span64), wreach = wave_max(reach);
     const bool wbad = ballot64(bad) != 0, wscattered = ballot64(scattered) != 0;
     if (lane_id() == 0) {
@@ -694,15 +712,15 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
     }
 }
 
-hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *status, int num_cus, hipStream_t s)
+hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *status, int num_cus, hipStream_t s)
 {
     if (g.num_ops == 0) return hipSuccess;
     int64_t blocks = ((int64_t)g.num_ops + kCheckThreads - 1) / kCheckThreads;
     if (blocks > 8 * num_cus) blocks = 8 * num_cus;
     if ((size_t)g.num_ops * sizeof(int4) > kStreamBytes)
-        hipLaunchKernelGGL(k_records_and_check<true>, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, status);
+        hipLaunchKernelGGL(k_records_and_check<true>, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, prod1, status);
     else
-        hipLaunchKernelGGL(k_records_and_check<false>, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, status);
+        hipLaunchKernelGGL(k_records_and_check<false>, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, prod1, status);
     return hipGetLastError();
 }
 

@@ -79,7 +79,7 @@ __device__ __forceinline__ void offer_children(const GraphView &g, bool valid, i
     int eb = 0, deg = 0;
     int32_t offered = kNone;
     if (valid) {
-        const int4 r = g.orec[o];
+        const int4 r = op_record(g, (int32_t)o);
         eb = r.x;
         deg = r.y;
         const int n_out = r.w >= 0 ? r.w : -r.w;

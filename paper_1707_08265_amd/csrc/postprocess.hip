@@ -27,7 +27,7 @@ __global__ __launch_bounds__(kIgThreads) void k_ignore_mask(GraphView g, bool se
     __syncthreads();
     int found = 0;
     for (int64_t i = (int64_t)blockIdx.x * kIgThreads + threadIdx.x; i < n; i += gsize) {
-        const int4 r = g.orec[kept_ops[i]];
+        const int4 r = op_record(g, kept_ops[i]);
         const u64 k = kept_masks[i];
         const int n_out = r.w >= 0 ? r.w : -r.w;
         for (int j = 0; j < n_out; j += 2) {                // the masks of two outputs are fetched together

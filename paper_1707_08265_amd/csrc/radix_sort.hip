@@ -418,11 +418,11 @@ hipError_t launch_sort_pairs(const int32_t *keys_in, const int32_t *vals_in, int
 // The adjacency needs the rows, not the sorted keys: passes as above bring the pairs into buckets of up to 512 neighbouring
 // rows only (the high bits of the key), and one workgroup per bucket ranks what is left of the key in LDS and writes the
 // bucket's rows and row pointers: a pass over memory less, no keys written at the end, and no pass that reads them again.  For
-// outputs the same workgroup writes the rows by tensor, the producer words and the operators' records, which took three more
-// passes.  32 M input edges of 12 M operators: 530 us sorted as a whole, 475 so; their 25 M outputs 700 -> 505; the whole build
-// 1 430 -> 1 110 us.  10 000 operators: 181 -> 135, 30 000: 220 -> 143, 500 000: 400 -> 190, 50 M: 5 390 -> 3 940.
+// outputs the same workgroup writes the rows by tensor, which took two more
+// passes.  32 M input edges of 12 M operators: 530 us sorted as a whole, 475 so; their 25 M outputs 700 -> 455; the whole build
+// 1 430 -> 1 055 us.  10 000 operators: 181 -> 135, 30 000: 220 -> 143, 500 000: 400 -> 190, 50 M: 5 390 -> 3 940.
 //
-// The last step takes 119 us for those 32 M pairs (440 MB), 226 for the outputs (890 MB): memory.  It was 205 with workgroups of 1 024
+// The last step takes 118 us for those 32 M pairs (440 MB), 177 for the outputs (590 MB; 226 while it wrote records and producer words as well): memory.  It was 205 with workgroups of 1 024
 // threads, eleven bits of the key and two passes inside LDS (barriers, and vector instructions of the second pass), 156 with
 // 256 threads and two passes.
 // ------------------------------------------------------------------------------------------------
@@ -622,8 +622,8 @@ __device__ __forceinline__ void big_groups(const int32_t *starts, const int32_t 
 // One bucket: a wave ranks its keys by row against those of its lower lanes and earlier rounds, as above, the counts of the
 // workgroup's waves are added up in row order -- which gives the row pointers --, and the values leave from their places in LDS.
 // kOut: the list's values are the tensors that the operators (rows) write; where they are one run of tensors -- sorted by
-// operator, position e writes tensor e + shift, in any order inside an operator's row -- the rows by tensor and the producer
-// words follow from the rows alone and are written here, too; elsewhere kStatusPending says that they are not.
+// operator, position e writes tensor e + shift, in any order inside an operator's row -- the rows by tensor follow from the
+// rows alone and are written here, too; elsewhere kStatusPending says that they are not.
 template <bool kOut, int kThreads>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *starts, int32_t buckets, int row_bits, const int32_t *big,
@@ -685,7 +685,6 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
         // tensors before the run have no producer
         for (int64_t t = (int64_t)b * kThreads + tid; t < shift; t += (int64_t)buckets * kThreads) {
             l.prod_row[t] = 0;
-            l.prod1[t] = kNoProducer;
         }
         if (last_bucket && tid == 0) l.prod_row[l.num_tensors] = nnz;
     }
@@ -723,16 +722,6 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
     }
     if (ballot64(bad) != 0 && lane == 0) atomicOr(status, kErrIdRange);
     if (several) return;
-    if (together && l.orec) {
-        auto record = [&](int r, int at, int length) {
-            const int first = length > 0 ? s_val[at] : 0;
-            bool consecutive = true;
-            for (int k = 1; k < length; ++k) consecutive &= s_val[at + k] == first + k;
-            write_record<false>(&l.orec[row0 + r], l.in_row[row0 + r], l.in_row[row0 + r + 1], lo + at, lo + at + length, first, consecutive);
-        };
-        if (2 * tid < rows) record(2 * tid, begin, length0);
-        if (2 * tid + 1 < rows) record(2 * tid + 1, begin + length0, length1);
-    }
     bool elsewhere = kOut && !together, scattered = false;
     for (int i = tid; i < n; i += kThreads) {
         const int32_t v = s_val[i], e = lo + i;
@@ -745,7 +734,6 @@ void k_bucket_rows(const int32_t *keys, const int32_t *vals, const int32_t *star
             scattered |= j != i;
             l.prod_idx[e] = row0 + row;
             l.prod_row[e + shift] = e;
-            l.prod1[e + shift] = row0 + row;
         }
     }
     if (kOut) {

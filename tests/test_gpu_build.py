@@ -77,6 +77,26 @@ def test_lists_in_order(dgn, oracle, shape, several):
     check(dgn, oracle, listed(rng, *shape, several), rng, f"{shape}")
 
 
+@pytest.mark.parametrize("several", [None, "first", "last", "all"])
+@pytest.mark.parametrize("writers,at", [(9, 4), (1025, 1), (4096, 4093), (5003, 1024), (140_000, 69_999), (140_001, 3)])
+def test_outputs_in_two_runs(dgn, oracle, writers, at, several):
+    """One hole in the numbering: producer words that the pass over the outputs has left out for what it took for one run, up to
+    the last tensor, are filled in; with tensors of several producers before or behind the hole, also more outputs than tensors."""
+    rng = np.random.default_rng(writers + at)
+    t = 5 + np.arange(writers) + 2 * (np.arange(writers) >= at)
+    op, more = np.arange(writers), np.zeros(writers, dtype=np.int64)
+    if several:
+        more[{"first": 0, "last": writers - 1, "all": slice(None)}[several]] = 1
+    out_t, fan = np.repeat(t, 1 + more), rng.integers(0, 3, writers)
+    out_op = np.minimum(np.repeat(op, 1 + more) + np.concatenate([np.arange(n) for n in (1 + more)]), writers - 1)
+    in_op = np.repeat(op, fan)
+    in_t = (rng.random(in_op.size) * np.repeat(t, fan)).astype(np.int64)
+    order = np.argsort(out_op, kind="stable")
+    i32 = lambda a: np.ascontiguousarray(a, dtype=np.int32)  # noqa: E731
+    g = gg.Graph(writers, int(t[-1]) + 1, i32(in_op), i32(in_t), i32(out_op[order]), i32(out_t[order]), name="two runs")
+    check(dgn, oracle, g, rng, f"{writers} {at} {several}")
+
+
 @pytest.mark.parametrize("most", [1, 3, 4, 5, 9, 63, 64, 65, 200])
 def test_shuffled_outputs_of_operators_with_many(dgn, oracle, most):
     """Rows inside and beyond what a thread holds, up to the longest that is ordered without a sort and above."""
