@@ -163,7 +163,7 @@ GraphLayout graph_layout(void *mem, int64_t P, int64_t T, int64_t Ein, int64_t E
 }
 
 struct BuildScratch {
-    int32_t *status;        // [64] ints; status[0] = error bits
+    int32_t *status;        // [kStatusEnd]; status[0] = error bits
     int32_t *sorted_ops;    // [Eout] operator id of every entry of out_idx
     int32_t *sorted_keys;   // [max(Ein, Eout)] keys of a sort in row order, for the row pointers
     void *sort_tmp;
@@ -174,7 +174,7 @@ BuildScratch build_scratch(void *mem, int64_t Ein, int64_t Eout)
 {
     Carver c(mem);
     BuildScratch S{};
-    S.status = c.take<int32_t>(64);
+    S.status = c.take<int32_t>(kStatusEnd);
     S.sorted_ops = c.take<int32_t>(Eout);
     const int64_t emax = Ein > Eout ? Ein : Eout;
     S.sorted_keys = c.take<int32_t>(emax);
@@ -607,12 +607,11 @@ int build_from_lists(dgn_graph *h, const dgn_coo_desc *d, const GraphLayout &L, 
     // One pass over both lists (in COO order) checks the ids, notes whether the keys ever decrease and, on the assumption
     // that they do not, already writes the finished adjacency: a graph recorded operator by operator needs nothing more,
     // and the host looks at the status once, when the records are made as well.
-    FillRegion clr[1] = {{S.status, 256}};
-    DGN_HIP(launch_clear(clr, 1, s));
     int rc = copy_offsets(h, L, d->graph_op_offsets, d->graph_tensor_offsets, s);
     if (rc) return rc;
     const EdgeList in{d->in_op, d->in_tensor, Ein, (int32_t)P, (int32_t)T, L.in_idx, L.in_rowptr, nullptr, nullptr, nullptr, false};
     const EdgeList out{d->out_op, d->out_tensor, Eout, (int32_t)P, (int32_t)T, L.out_idx, L.out_rowptr, L.prod_idx, L.prod_rowptr, L.prod1, may_run(h)};
+    DGN_HIP(launch_first_look(in, out, S.status, s));
     DGN_HIP(launch_scan_edges(&in, out, S.status, s));
     rc = enqueue_records(h, L, S.status, options, s, false);
     if (rc) return rc;

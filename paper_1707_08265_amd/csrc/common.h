@@ -342,6 +342,9 @@ enum : int {
     kStatusWithin2048 = 29,      // ... a 2 048th
     kStatusReach = 30,           // k_records_and_check: how far below an operator's first output its inputs lie at most
     kStatusSoon = 31,            // sampled operators whose first input was written just before (kSoonTensors)
+    kStatusLeaveIn = 32,         // (not read back) a look at some places has found the operators of the input edges,
+    kStatusLeaveOut = 33,        // of the output edges in no order: the pass over the lists leaves them
+    kStatusEnd = 64,
 };
 // An edge list and where its adjacency goes.  idx / row == NULL: those are in place already.
 struct EdgeList {
@@ -362,6 +365,8 @@ RowPlan plan_rows(int64_t nnz, int64_t rows, int key_bits);
 hipError_t launch_bucket_rows(const RowPlan &p, const EdgeList &l, bool producers, int32_t *num_big, int32_t *status, void *tmp, hipStream_t s);
 // kErrIdRange if an edge of the list has an id out of range
 hipError_t launch_check_ids(const EdgeList &l, int32_t *status, hipStream_t s);
+// clears all status words; long lists that are in no order at a few places already are noted
+hipError_t launch_first_look(const EdgeList &in, const EdgeList &out, int32_t *status, hipStream_t s);
 // one pass over the input edges (NULL: the outputs only) and the output edges: checks them and, assuming that they are in
 // order, writes the finished adjacency
 hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s);

@@ -38,7 +38,7 @@ __device__ __forceinline__ void rows_closed(int32_t prev, int32_t cur, int32_t n
 // neighbouring positions per step, in 16-byte accesses where the arrays are aligned for them (one position per thread left
 // the pass waiting for memory).  Outputs take both adjacencies and the producer words from one reading: three passes did
 // that before, 0.99 ms of a 50 M-operator graph and 0.3 more for the producer words; then 1.00 in all, with its stores past the
-// caches 0.91, without the producer words of one run 0.81 = 4.9 TB/s.
+// caches 0.91, without the producer words of one run 0.81, with a workgroup per piece of the lists 0.77 = 5.1 TB/s.
 constexpr int kScanThreads = 256;
 
 template <bool kOut, bool kStream>
@@ -166,21 +166,53 @@ __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int6
     if (lane_id() < 32 && (words >> lane_id() & 1) && load_coherent(status + lane_id()) == 0) store_coherent(status + lane_id(), 1);
 }
 
-// inputs and outputs in one launch; an empty list has one position too (it closes all rows)
+// inputs and outputs in one launch; an empty list has one position too (it closes all rows).  leave: what k_first_look has found
 template <bool kStream>
-__global__ __launch_bounds__(kScanThreads) void k_scan_edges(EdgeList in, EdgeList out, int in_blocks, int32_t *status)
+__global__ __launch_bounds__(kScanThreads) void k_scan_edges(EdgeList in, EdgeList out, int in_blocks, const int32_t *__restrict__ leave,
+                                                             int32_t *__restrict__ status)
 {
     __shared__ uint32_t s_words;                                        // status words that some wave reports
+    if (leave[(int)blockIdx.x < in_blocks ? 0 : kStatusLeaveOut - kStatusLeaveIn]) return;
     if (threadIdx.x == 0) s_words = 0;
     __syncthreads();
     if ((int)blockIdx.x < in_blocks) scan_list<false, kStream>(in, blockIdx.x, in_blocks, &s_words, status);
     else scan_list<true, kStream>(out, (int)blockIdx.x - in_blocks, (int)gridDim.x - in_blocks, &s_words, status);
 }
 
-static int scan_blocks(int64_t nnz)
+// A workgroup per 1 024 positions, however many: handed out in order they go through the lists like one long stream.  (8 192 per list, each
+// with every 8 192nd piece: 850 us for 50 M operators, 2 048 in all: 975, one each: 797.)  That many would read all of a list in no order before
+// the first of them could say so, so that long ones are looked at in a few places before (12 M operators in shuffled order: 1 100, 1 030
+// with 8 192 per list, 1 016 so).
+constexpr int kScanTile = kScanThreads * 4;
+static int scan_blocks(int64_t nnz) { return (int)((nnz + 1 + kScanTile - 1) / kScanTile); }
+
+// Long lists: a wave looks at 64 neighbouring positions in each of kLooks places.
+constexpr int kLooks = 8;
+constexpr int64_t kLookEdges = (int64_t)8192 * kScanTile;
+__global__ __launch_bounds__(2 * kLooks * kWave) void k_first_look(const int32_t *in_op, int64_t nnz_in, const int32_t *out_op, int64_t nnz_out, int32_t *status)
 {
-    const int64_t blocks = (nnz + 1 + kScanThreads * 4 - 1) / (kScanThreads * 4);
-    return (int)(blocks < 8192 ? blocks : 8192);
+    __shared__ int32_t s_status[kStatusEnd];
+    if (threadIdx.x < kStatusEnd) s_status[threadIdx.x] = 0;
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, list = wave / kLooks, place = wave % kLooks;
+    const int32_t *ops = list ? out_op : in_op;
+    const int64_t nnz = list ? nnz_out : nnz_in;
+    if (nnz > kLookEdges) {
+        const int64_t e = (nnz - 1 - kWave) / (kLooks - 1) * place + lane_id();
+        if (ballot64(ops[e] > ops[e + 1]) != 0 && lane_id() == 0) {
+            s_status[list ? kStatusOutUnsorted : kStatusInUnsorted] = 1;
+            s_status[list ? kStatusLeaveOut : kStatusLeaveIn] = 1;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kStatusEnd) status[threadIdx.x] = s_status[threadIdx.x];
+}
+
+hipError_t launch_first_look(const EdgeList &in, const EdgeList &out, int32_t *status, hipStream_t s)
+{
+    const bool looks = in.nnz > kLookEdges || out.nnz > kLookEdges;
+    hipLaunchKernelGGL(k_first_look, dim3(1), dim3(looks ? 2 * kLooks * kWave : kStatusEnd), 0, s, in.op, in.nnz, out.op, out.nnz, status);
+    return hipGetLastError();
 }
 
 hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s)
@@ -189,9 +221,9 @@ hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *s
     const dim3 grid((unsigned)(in_blocks + scan_blocks(out.nnz)));
     const size_t written = (in ? (size_t)in->nnz * 4 : 0) + (size_t)out.nnz * 8 + (size_t)out.num_ops * 8 + (size_t)out.num_tensors * 8;
     if (written > kStreamBytes)
-        hipLaunchKernelGGL(k_scan_edges<true>, grid, dim3(kScanThreads), 0, s, in ? *in : out, out, in_blocks, status);
+        hipLaunchKernelGGL(k_scan_edges<true>, grid, dim3(kScanThreads), 0, s, in ? *in : out, out, in_blocks, status + kStatusLeaveIn, status);
     else
-        hipLaunchKernelGGL(k_scan_edges<false>, grid, dim3(kScanThreads), 0, s, in ? *in : out, out, in_blocks, status);
+        hipLaunchKernelGGL(k_scan_edges<false>, grid, dim3(kScanThreads), 0, s, in ? *in : out, out, in_blocks, status + kStatusLeaveIn, status);
     return hipGetLastError();
 }
 

@@ -97,6 +97,38 @@ def test_outputs_in_two_runs(dgn, oracle, writers, at, several):
     check(dgn, oracle, g, rng, f"{writers} {at} {several}")
 
 
+@pytest.mark.parametrize("nnz", [8192 * 1024, 8192 * 1024 + 1, 8192 * 1024 + 77])
+@pytest.mark.parametrize("order", ["recorded", "outputs", "inputs", "last"])
+def test_long_lists_are_looked_at_before(dgn, oracle, nnz, order):
+    """Lists up to and beyond the length from which a few places are looked at first: in order, one of them in no order, and a
+    single pair at the end, which that look does not see."""
+    import torch
+    P = (nnz + 1) // 2
+    per = np.full(P, 2)
+    per[0] += nnz - 2 * P
+    op = np.repeat(np.arange(P), per).astype(np.int32)
+    t = np.arange(nnz, dtype=np.int32) + 3
+    in_t = (np.arange(nnz, dtype=np.int64) * 7919 % (op.astype(np.int64) * 2 + 3)).astype(np.int32)
+    rng = np.random.default_rng(nnz)
+    pi, po = np.arange(nnz), np.arange(nnz)
+    if order == "inputs":
+        pi = rng.permutation(nnz)
+    if order == "outputs":
+        po = rng.permutation(nnz)
+    if order == "last":
+        po[[-1, -3]] = po[[-3, -1]]
+    g = gg.Graph(P, nnz + 3, op[pi], in_t[pi], op[po], t[po], name="long")
+    adj = oracle.build_adjacency(g.num_ops, g.num_tensors, g.in_op, g.in_tensor, g.out_op, g.out_tensor)
+    csr = {n: v.cpu().numpy() for n, v in dgn.DeviceGraph.from_coo(g).csr().items()}
+    for name in ROWS:
+        assert np.array_equal(csr[name], getattr(adj, name)), f"{order}: {name}"
+    g.in_op[nnz // 3] = P                                    # an id out of range, wherever the lists are left early
+    from paper_1707_08265_amd import DgnError
+    with pytest.raises(DgnError):
+        dgn.DeviceGraph.from_coo(g)
+    torch.cuda.synchronize()
+
+
 @pytest.mark.parametrize("most", [1, 3, 4, 5, 9, 63, 64, 65, 200])
 def test_shuffled_outputs_of_operators_with_many(dgn, oracle, most):
     """Rows inside and beyond what a thread holds, up to the longest that is ordered without a sort and above."""
