@@ -411,13 +411,21 @@ bool walked(const dgn_graph *h) { return h->G > 1 || h->P <= kRingMaxOps; }
 // ever are: its graphs have inputs of their own.
 bool may_run(const dgn_graph *h) { return h->G == 1; }
 
+// Batches that are swept have no records: what goes operator by operator over such a batch takes its rows, and from 4 instead of 16 bytes per
+// operator which tensors it writes.  (4 096 graphs of 20 000: records and check 741 us with records, 600 so.)
+void place_records(dgn_graph *h, const GraphLayout &L)
+{
+    if (h->G < kSweepMinGraphs) h->v.orec = L.orec;
+    else h->v.ofirst = reinterpret_cast<int32_t *>(L.orec);
+}
+
 // What follows the adjacency.  The kernels find out by themselves whether there is one yet.  words: all producer words are there; none: the
 // outputs are one run, or there is no adjacency yet, so that there are no records to be made.
 int enqueue_records(const dgn_graph *h, const GraphLayout &L, int32_t *status, const dgn_options *options, hipStream_t s, bool words, bool none = false)
 {
     int32_t *spared = may_run(h) && !words ? L.prod1 : nullptr;
     if (walked(h)) {
-        DGN_HIP(launch_records_and_check(h->v, L.orec, spared, status, h->num_cus, s));
+        DGN_HIP(launch_records_and_check(h->v, const_cast<int4 *>(h->v.orec), const_cast<int32_t *>(h->v.ofirst), spared, status, h->num_cus, s));
     } else {
         if (none) DGN_HIP(launch_sample_reach(h->v, status, s));
         else DGN_HIP(launch_build_records(h->v, L.orec, spared, status, s));
@@ -687,7 +695,8 @@ int dgn_graph_build(const dgn_coo_desc *d, void *graph_mem, size_t graph_bytes, 
     if (rc) return rc;
     h->P = P; h->T = T; h->Ein = Ein; h->Eout = Eout; h->G = d->num_graphs;
     h->v = GraphView{(int32_t)P, (int32_t)T, (int32_t)Ein, (int32_t)Eout, d->num_graphs, L.in_rowptr, L.in_idx,
-                     L.out_rowptr, L.out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.prod1, -1};
+                     L.out_rowptr, L.out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, nullptr, nullptr, L.prod1, -1};
+    place_records(h, L);
     const int32_t *found = nullptr;
     rc = build_from_lists(h, d, L, S, options, s, &found);
     if (!rc) rc = finish_build(h, d->graph_op_offsets, d->graph_tensor_offsets, S.status, found, options, s, out);
@@ -731,7 +740,8 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
     if (rc) return rc;
     h->P = P; h->T = T; h->Ein = Ein; h->Eout = Eout; h->G = d->num_graphs;
     h->v = GraphView{(int32_t)P, (int32_t)T, (int32_t)Ein, (int32_t)Eout, d->num_graphs, d->in_rowptr, d->in_idx,
-                     d->out_rowptr, d->out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.prod1, -1};
+                     d->out_rowptr, d->out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, nullptr, nullptr, L.prod1, -1};
+    place_records(h, L);
     const int32_t *found = nullptr;
     auto fill = [&]() -> int {
         FillRegion clr[1] = {{S.status, 256}};

@@ -34,7 +34,8 @@ struct GraphView {
     const int64_t *op_off, *t_off;    // [G+1] device copies, NULL when num_graphs == 1
     // What the traversal reads per operator and per pushed tensor (see traverse.hip).  Of graphs whose outputs are one run of tensors
     // (run_shift >= 0) it follows from the adjacency, and these two are not written.
-    const int4 *orec;                 // [P] operator record (first input edge, fan-in, outputs)
+    const int4 *orec;                 // [P] operator record (first input edge, fan-in, outputs); NULL: by rows and ofirst
+    const int32_t *ofirst;            // [P] batches that are swept: the first output, if an operator's outputs are consecutive, else -1
     const int32_t *prod1;             // [T] the producer of a tensor, or kMulti / kNoProducer
     // >= 0: the outputs of operator o are the tensors out_rowptr[o] + run_shift .. out_rowptr[o + 1] + run_shift - 1 (in any order
     // inside its row), each written by nobody else, so that tensor t is written by prod_idx[t - run_shift]; -1: not so
@@ -51,26 +52,31 @@ constexpr int32_t kNoProducer = -3;   // graph input
 
 // The record of operator o and the producer word of tensor t.  Graphs in one run have neither in memory: their rows say the same, and
 // not writing them spares a build of 50 M operators 1.6 of 5.6 GB (1 183 -> 845 us); a record then is two accesses of 8 bytes
-// side by side instead of one of 16.  kRun: run_shift >= 0, known when the kernel is launched.
+// side by side instead of one of 16.  The traversal's kernels are told which it is (a branch there costs them 7 %).
 typedef int IntPair __attribute__((ext_vector_type(2), aligned(4)));
-template <bool kRun> __device__ __forceinline__ int4 op_record(const GraphView &g, int32_t o)
+enum RowForm : int { kRecords, kRun, kFirst };     // what an operator's record and a tensor's producer are taken from
+__host__ __device__ inline RowForm rows_of(const GraphView &g) { return g.run_shift >= 0 ? kRun : g.orec ? kRecords : kFirst; }
+template <RowForm kForm> __device__ __forceinline__ int4 op_record(const GraphView &g, int32_t o)
 {
-    if (!kRun) return g.orec[o];
+    if (kForm == kRecords) return g.orec[o];
+    const int32_t first = kForm == kFirst ? g.ofirst[o] : 0;
     const IntPair in = *reinterpret_cast<const IntPair *>(g.in_rowptr + o), out = *reinterpret_cast<const IntPair *>(g.out_rowptr + o);
-    return make_int4(in.x, in.y - in.x, out.x + g.run_shift, out.y - out.x);
+    if (kForm == kRun) return make_int4(in.x, in.y - in.x, out.x + g.run_shift, out.y - out.x);
+    return make_int4(in.x, in.y - in.x, first >= 0 ? first : out.x, first >= 0 ? out.y - out.x : out.x - out.y);
 }
-template <bool kRun> __device__ __forceinline__ int32_t producer_of(const GraphView &g, int32_t t)
+template <RowForm kForm> __device__ __forceinline__ int32_t producer_of(const GraphView &g, int32_t t)
 {
-    if (!kRun) return g.prod1[t];
+    if (kForm != kRun) return g.prod1[t];
     return t >= g.run_shift ? g.prod_idx[t - g.run_shift] : kNoProducer;
 }
 __device__ __forceinline__ int4 op_record(const GraphView &g, int32_t o)
 {
-    return g.run_shift >= 0 ? op_record<true>(g, o) : op_record<false>(g, o);
+    const RowForm rows = rows_of(g);
+    return rows == kRun ? op_record<kRun>(g, o) : rows == kRecords ? op_record<kRecords>(g, o) : op_record<kFirst>(g, o);
 }
 __device__ __forceinline__ int32_t producer_of(const GraphView &g, int32_t t)
 {
-    return g.run_shift >= 0 ? producer_of<true>(g, t) : producer_of<false>(g, t);
+    return g.run_shift >= 0 ? producer_of<kRun>(g, t) : producer_of<kRecords>(g, t);
 }
 
 // Record of one launch of the traversal: the state it started from and whether it ran a level.
@@ -376,7 +382,7 @@ hipError_t launch_sample_reach(const GraphView &g, int32_t *status, hipStream_t 
 // operator records (unless the outputs are one run) of a single graph / of graphs that are also checked for range and for the ring
 // sweep.  prod1: producer words that the pass over the outputs left out (EdgeList::may_run), or NULL: there are none
 hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *status, hipStream_t s);
-hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *status, int num_cus, hipStream_t s);
+hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *ofirst, int32_t *prod1, int32_t *status, int num_cus, hipStream_t s);
 hipError_t launch_check_topological(const GraphView &g, int32_t *status, hipStream_t s);
 // producer words from prod_rowptr / prod_idx; kStatusMulti when some tensor has several producers
 hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *status, hipStream_t s);

@@ -615,7 +615,7 @@ hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *s
 constexpr int kCheckThreads = 256;
 
 template <bool kStream>
-__global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g, int4 *orec, int32_t *prod1, int32_t *status)
+__global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g, int4 *orec, int32_t *ofirst, int32_t *prod1, int32_t *status)
 {
     __shared__ int s_found[6];                      // error, scattered, low, dist, span64, reach
     if (!adjacency_ready(status, false)) return;
@@ -721,7 +721,8 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
         for (int j = 0; j < 2; ++j)
             if (ob + j < oe) output(ob + j, u[j]);
         for (int32_t e = ob + 2; e < oe; ++e) output(e, g.out_idx[e]);
-        if (records) write_record<kStream>(&orec[o], ib, ie, ob, oe, first, consecutive);
+        if (records && orec) write_record<kStream>(&orec[o], ib, ie, ob, oe, first, consecutive);
+        else if (records) ofirst[o] = consecutive ? first : -1;
         if (((o - o_lo) & (kWave - 1)) == 0)                // (the outputs of 64 operators end where those of the next begin)
             span64 = max(span64, (o + kWave <= o_hi && base + kWave < last ? next.ob : g.out_rowptr[min(o + kWave, o_hi)]) - ob);
     }
@@ -744,15 +745,15 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
     }
 }
 
-hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *status, int num_cus, hipStream_t s)
+hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *ofirst, int32_t *prod1, int32_t *status, int num_cus, hipStream_t s)
 {
     if (g.num_ops == 0) return hipSuccess;
     int64_t blocks = ((int64_t)g.num_ops + kCheckThreads - 1) / kCheckThreads;
     if (blocks > 8 * num_cus) blocks = 8 * num_cus;
     if ((size_t)g.num_ops * sizeof(int4) > kStreamBytes)
-        hipLaunchKernelGGL(k_records_and_check<true>, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, prod1, status);
+        hipLaunchKernelGGL(k_records_and_check<true>, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, ofirst, prod1, status);
     else
-        hipLaunchKernelGGL(k_records_and_check<false>, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, prod1, status);
+        hipLaunchKernelGGL(k_records_and_check<false>, dim3((unsigned)blocks), dim3(kCheckThreads), 0, s, g, orec, ofirst, prod1, status);
     return hipGetLastError();
 }
 

@@ -71,6 +71,7 @@ struct ClaimStage {
 // an operator's edges begin): an edge is a chain of dependent accesses -- id, child word, atomic --, and with an operator
 // per lane a wave went through it as often as its operator with the most inputs asks for (0.25 -> 0.18 ms; what is left is
 // about five scattered accesses per edge at the chip's rate for those).
+template <RowForm kForm>
 __device__ __forceinline__ void offer_children(const GraphView &g, bool valid, int64_t o, int32_t *rename, int32_t *child,
                                                int *s_mark, const ClaimStage &cs)
 {
@@ -79,13 +80,13 @@ __device__ __forceinline__ void offer_children(const GraphView &g, bool valid, i
     int eb = 0, deg = 0;
     int32_t offered = kNone;
     if (valid) {
-        const int4 r = op_record(g, (int32_t)o);
+        const int4 r = op_record<kForm>(g, (int32_t)o);
         eb = r.x;
         deg = r.y;
-        const int n_out = r.w >= 0 ? r.w : -r.w;
+        const int n_out = kForm == kRun || r.w >= 0 ? r.w : -r.w;
         int lo = 0x7fffffff, hi = -1;
         for (int j = 0; j < n_out; ++j) {
-            const int32_t u = r.w >= 0 ? r.z + j : g.out_idx[r.z + j];
+            const int32_t u = kForm == kRun || r.w >= 0 ? r.z + j : g.out_idx[r.z + j];
             rename[u] = u;
             lo = min(lo, u);
             hi = max(hi, u);
@@ -161,6 +162,7 @@ constexpr int kIpThreads = 1024;
 constexpr int kIpWaves = kIpThreads / kWave;
 constexpr int kMaskRounds = 8;                      // masks per lane and step
 
+template <RowForm kForm>
 __global__ __launch_bounds__(kIpThreads) void k_inplace_children(GraphView g, const u64 *K, u64 select, int32_t *rename,
                                                                   int32_t *child, int32_t *list, int32_t *list_count)
 {
@@ -196,19 +198,20 @@ __global__ __launch_bounds__(kIpThreads) void k_inplace_children(GraphView g, co
         __builtin_amdgcn_wave_barrier();
         while (count >= kWave) {
             count -= kWave;
-            offer_children(g, true, ops[count + lane], rename, child, s_mark[wave], cs);
+            offer_children<kForm>(g, true, ops[count + lane], rename, child, s_mark[wave], cs);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         flush_claims(cs, &s_base, false);
     }
-    offer_children(g, lane < count, lane < count ? ops[lane] : 0, rename, child, s_mark[wave], cs);
+    offer_children<kForm>(g, lane < count, lane < count ? ops[lane] : 0, rename, child, s_mark[wave], cs);
     flush_claims(cs, &s_base, true);
 }
 
 // The same from the list of kept operators that the prune wrote (ascending ids of the operators with K != 0):
 // a pruned graph is a few percent of the recorded one, and the list spares the pass over all of K.  An entry
 // whose mask misses `select` is skipped.
+template <RowForm kForm>
 __global__ __launch_bounds__(kIpThreads) void k_inplace_children_list(GraphView g, const u64 *K, u64 select,
                                                                        const int32_t *kept_ops, const int64_t *kept_count,
                                                                        int32_t *rename, int32_t *child, int32_t *list,
@@ -226,7 +229,7 @@ __global__ __launch_bounds__(kIpThreads) void k_inplace_children_list(GraphView 
         const int64_t i = base + threadIdx.x;
         const int32_t o = i < kept ? kept_ops[i] : 0;
         const bool valid = i < kept && (K[o] & select) != 0;
-        offer_children(g, valid, o, rename, child, s_mark[threadIdx.x >> 6], cs);
+        offer_children<kForm>(g, valid, o, rename, child, s_mark[threadIdx.x >> 6], cs);
         flush_claims(cs, &s_base, false);
     }
     flush_claims(cs, &s_base, true);
@@ -306,11 +309,12 @@ hipError_t launch_inplace_setup(const GraphView &g, const u64 *K, u64 select, co
                        kInplaceMaxRounds + 1, renamed_count);
     int64_t blocks = (P + kIpThreads - 1) / kIpThreads;
     if (blocks > grid_blocks / 4) blocks = grid_blocks / 4;
+    const RowForm rows = rows_of(g);
     if (P > 0 && kept_ops)
-        hipLaunchKernelGGL(k_inplace_children_list, dim3((unsigned)blocks), dim3(kIpThreads), 0, s, g, K, select,
+        hipLaunchKernelGGL(rows == kRun ? k_inplace_children_list<kRun> : rows == kRecords ? k_inplace_children_list<kRecords> : k_inplace_children_list<kFirst>, dim3((unsigned)blocks), dim3(kIpThreads), 0, s, g, K, select,
                            kept_ops, kept_count, rename, b.child, b.list, b.counters);
     else if (P > 0)
-        hipLaunchKernelGGL(k_inplace_children, dim3((unsigned)blocks), dim3(kIpThreads), 0, s, g, K, select, rename, b.child,
+        hipLaunchKernelGGL(rows == kRun ? k_inplace_children<kRun> : rows == kRecords ? k_inplace_children<kRecords> : k_inplace_children<kFirst>, dim3((unsigned)blocks), dim3(kIpThreads), 0, s, g, K, select, rename, b.child,
                            b.list, b.counters);
     return hipGetLastError();
 }

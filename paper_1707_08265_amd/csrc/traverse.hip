@@ -292,7 +292,7 @@ __device__ __forceinline__ bool note_producer(int32_t op, int32_t theta, uint8_t
 // inputs pays the two dependent accesses once, not once per round.  Wave-uniform control flow throughout.
 constexpr int kEdgeRounds = 1;          // (two and four were measured: no gain, more registers)
 
-template <bool kRun>
+template <RowForm kForm>
 __device__ __forceinline__ void expand_edges(const GraphView &g, int eb, int deg, u64 bits, int32_t theta, const Masks &mk,
                                              int *s_incl, WaveStage &ws, const Frontier &f, LevelCounters &lc)
 {
@@ -329,7 +329,7 @@ __device__ __forceinline__ void expand_edges(const GraphView &g, int eb, int deg
             old[r] = ~(u64)0;
             if (ev[r]) {
                 old[r] = atomicOr(&mk.M[u[r]], b[r]);       // (I2)
-                pr[r] = producer_of<kRun>(g, u[r]);         // in flight together with the atomic (which goes first: the earlier it lands, the fewer pushes come late)
+                pr[r] = producer_of<kForm>(g, u[r]);        // in flight together with the atomic (which goes first: the earlier it lands, the fewer pushes come late)
                 lc.atomics++;
             }
         }
@@ -340,10 +340,10 @@ __device__ __forceinline__ void expand_edges(const GraphView &g, int eb, int deg
             const bool first = ev[r] && old[r] == 0;
             if (ev[r] && (b[r] & ~old[r]) != 0) {           // (I3): u gained bits
                 if (pr[r] >= 0) push = note_producer(pr[r], theta, mk.DB, lc);
-                else many = !kRun && pr[r] == kMulti;
+                else many = kForm != kRun && pr[r] == kMulti;
             }
             stage_push(ws, push, pr[r], first, u[r], f);
-            if (!kRun && ballot64(many)) {                           // tensors with several producers: one round per producer rank
+            if (kForm != kRun && ballot64(many)) {                           // tensors with several producers: one round per producer rank
                 int pb = 0, np = 0;
                 if (many) { pb = g.prod_rowptr[u[r]]; np = g.prod_rowptr[u[r] + 1] - pb; }
                 const int rounds = wave_max(np);
@@ -366,7 +366,7 @@ __device__ __forceinline__ void expand_edges(const GraphView &g, int eb, int deg
 // have go to the inputs.  atomic_k: OR into K atomically (launches that process an operator in the launch that
 // noted it, and the fix-up sweep); else K is read and written plainly (see the header).  Returns whether this
 // lane's operator gained bits.
-template <bool kRun>
+template <RowForm kForm>
 __device__ __forceinline__ bool process_ops(const GraphView &g, bool valid, int32_t o, int32_t theta, bool atomic_k,
                                             const Masks &mk, int *s_incl, WaveStage &ws, const Frontier &f,
                                             LevelCounters &lc)
@@ -374,12 +374,12 @@ __device__ __forceinline__ bool process_ops(const GraphView &g, bool valid, int3
     int4 r = make_int4(0, 0, 0, 0);
     u64 kold = 0, k = 0;
     if (valid) {
-        r = op_record<kRun>(g, o);
+        r = op_record<kForm>(g, o);
         kold = load_coherent(&mk.K[o]);
-        const int n_out = kRun || r.w >= 0 ? r.w : -r.w;
+        const int n_out = kForm == kRun || r.w >= 0 ? r.w : -r.w;
         // the masks of the first four outputs are fetched together
         u64 m0 = 0, m1 = 0, m2 = 0, m3 = 0;
-        if (kRun || r.w >= 0) {
+        if (kForm == kRun || r.w >= 0) {
             if (n_out > 0) m0 = load_coherent(&mk.M[r.z]);
             if (n_out > 1) m1 = load_coherent(&mk.M[r.z + 1]);
             if (n_out > 2) m2 = load_coherent(&mk.M[r.z + 2]);
@@ -403,7 +403,7 @@ __device__ __forceinline__ bool process_ops(const GraphView &g, bool valid, int3
         else store_coherent(&mk.K[o], kold | k);
         if (kold == 0) mk.flags[o] = 1;                     // o is kept
     }
-    expand_edges<kRun>(g, r.x, nb ? r.y : 0, nb, theta, mk, s_incl, ws, f, lc);
+    expand_edges<kForm>(g, r.x, nb ? r.y : 0, nb, theta, mk, s_incl, ws, f, lc);
     return nb != 0;
 }
 
@@ -525,7 +525,7 @@ __device__ __forceinline__ uint32_t gather4(uint32_t x) { return ((x & 0x0101010
 
 // The work of block `blk` (< p.nwork) in one level: its share of the queue entries and of the newly opened
 // operator range.  Adds the block's tallies to `tally`.
-template <bool kRun>
+template <RowForm kForm>
 __device__ __forceinline__ void run_level(const GraphView &g, const LevelSlot &in, int n, const LevelPlan &p, int blk,
                                           const int32_t *qin, const QueueGeom &qg, const Frontier &f, const Masks &mk,
                                           LevelShared &sh, SegCounter *tally)
@@ -544,14 +544,14 @@ __device__ __forceinline__ void run_level(const GraphView &g, const LevelSlot &i
             const int i = (e_first * kLevelWaves + wave) * p.per_wave + lane;
             const bool valid = lane < p.per_wave && i < n;
             const int32_t o = valid ? load_item(qin, qg, sh.pref, i) : 0;
-            process_ops<kRun>(g, valid, o, in.theta, atomic_k, mk, &sh.incl[wave][0], ws, f, lc);
+            process_ops<kForm>(g, valid, o, in.theta, atomic_k, mk, &sh.incl[wave][0], ws, f, lc);
         }
     } else {
         for (int base = e_first * kLevelThreads; do_entries && base < n; base += e_blocks * kLevelThreads) {
             const int i = base + threadIdx.x;
             const bool valid = i < n;
             const int32_t o = valid ? load_item(qin, qg, sh.pref, i) : 0;
-            process_ops<kRun>(g, valid, o, in.theta, atomic_k, mk, &sh.incl[wave][0], ws, f, lc);
+            process_ops<kForm>(g, valid, o, in.theta, atomic_k, mk, &sh.incl[wave][0], ws, f, lc);
         }
     }
     // the marker bytes of the newly opened range, a chunk per step: every lane fetches its 1..64 bytes at once and
@@ -618,7 +618,7 @@ __device__ __forceinline__ void run_level(const GraphView &g, const LevelSlot &i
             for (int i0 = 0; i0 < total; i0 += kWave) {
                 const bool valid = i0 + lane < total;
                 const int32_t o = valid ? sh.ops[wave][i0 + lane] : 0;
-                process_ops<kRun>(g, valid, o, in.theta, atomic_k, mk, &sh.incl[wave][0], ws, f, lc);
+                process_ops<kForm>(g, valid, o, in.theta, atomic_k, mk, &sh.incl[wave][0], ws, f, lc);
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -639,7 +639,7 @@ __device__ __forceinline__ void run_level(const GraphView &g, const LevelSlot &i
                 const int32_t o = valid ? ws.buf[(ws.head + lane) & (kStageCap - 1)] : 0;
                 ws.head += take;
                 __builtin_amdgcn_wave_barrier();
-                process_ops<kRun>(g, valid, o, in.theta, atomic_k, mk, &sh.incl[wave][0], ws, f, lc);
+                process_ops<kForm>(g, valid, o, in.theta, atomic_k, mk, &sh.incl[wave][0], ws, f, lc);
                 if (ws.head > gen_end) gen_end = ws.head;   // the ring was flushed under us: nothing of this hop is left
             }
         }
@@ -751,7 +751,7 @@ __device__ __forceinline__ void hand_on_frontier(TravCounters *ctr, int launch_n
     ctr->cnt[launch_no % 3][lane].v = s_pref[lane + 1] - s_pref[lane];
 }
 
-template <bool kRun>
+template <RowForm kForm>
 __global__ __launch_bounds__(kLevelThreads) void k_level(GraphView g, TravState *st, TravCounters *ctr, int launch_no,
                                                           int32_t *q0, int32_t *q1, QueueGeom qg, Masks mk,
                                                           int narrow_cap, Schedule sch, ColourLog log, int4 *trace)
@@ -782,7 +782,7 @@ __global__ __launch_bounds__(kLevelThreads) void k_level(GraphView g, TravState 
     const Frontier f{qout + (int64_t)seg * qg.seg_cap, &ctr->cnt[mine][seg].v, qg.seg_cap, &st->error,
                      log.entries ? log.entries + (int64_t)lseg * log.seg_cap : nullptr, &log.cnt[lseg].v, log.seg_cap,
                      nullptr, 0};
-    run_level<kRun>(g, in, n, p, (int)blockIdx.x, qin, qg, f, mk, sh, ctr->cnt[mine]);
+    run_level<kForm>(g, in, n, p, (int)blockIdx.x, qin, qg, f, mk, sh, ctr->cnt[mine]);
 }
 
 hipError_t launch_level(const GraphView &g, TravState *st, TravCounters *ctr, int launch_no, int32_t *q0, int32_t *q1,
@@ -790,7 +790,7 @@ hipError_t launch_level(const GraphView &g, TravState *st, TravCounters *ctr, in
                         const Schedule &sch, const ColourLog &log, int4 *trace, hipStream_t s)
 {
     if (grid_blocks < 2) grid_blocks = 2;                   // entries and range chunks go to different blocks
-    hipLaunchKernelGGL(g.run_shift >= 0 ? k_level<true> : k_level<false>, dim3((unsigned)grid_blocks), dim3(kLevelThreads), 0, s, g, st, ctr, launch_no, q0, q1,
+    hipLaunchKernelGGL(rows_of(g) == kRun ? k_level<kRun> : rows_of(g) == kRecords ? k_level<kRecords> : k_level<kFirst>, dim3((unsigned)grid_blocks), dim3(kLevelThreads), 0, s, g, st, ctr, launch_no, q0, q1,
                        qg, Masks{M, K, DB, flags}, narrow_cap, sch, log, trace);
     return hipGetLastError();
 }
@@ -803,7 +803,7 @@ constexpr int kNarrowThreads = 1024;
 constexpr int kNarrowWaves = kNarrowThreads / kWave;
 constexpr int kNarrowFront = 1024;      // entries of a queue that the kernel also keeps in LDS
 
-template <bool kRun>
+template <RowForm kForm>
 __global__ __launch_bounds__(kNarrowThreads) void k_narrow(GraphView g, TravState *st, TravCounters *ctr, int launch_no,
                                                             int32_t *q0, int32_t *q1, QueueGeom qg, Masks mk,
                                                             int narrow_cap, Schedule sch, ColourLog log, int4 *trace)
@@ -844,7 +844,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_narrow(GraphView g, TravStat
             const int32_t o = !valid ? 0 : from_lds ? s_front[cur][i] : load_item(qin, qg, s_pref, i);
             // threshold 0: a small queue is latency bound, so nothing is gained by deferring.  What a level notes
             // is processed by the next one, behind a barrier: plain reads and writes of K will do (see the header)
-            process_ops<kRun>(g, valid, o, 0, false, mk, &s_incl[wave][0], ws, f, lc);
+            process_ops<kForm>(g, valid, o, 0, false, mk, &s_incl[wave][0], ws, f, lc);
         }
         flush_entries(ws, f);
         // the block's stores (K, and without the copy in LDS the queue) must have completed before other waves of this
@@ -889,7 +889,7 @@ hipError_t launch_narrow(const GraphView &g, TravState *st, TravCounters *ctr, i
                          const QueueGeom &qg, uint8_t *DB, uint8_t *flags, u64 *M, u64 *K, int narrow_cap, const Schedule &sch,
                          const ColourLog &log, int4 *trace, hipStream_t s)
 {
-    hipLaunchKernelGGL(g.run_shift >= 0 ? k_narrow<true> : k_narrow<false>, dim3(1), dim3(kNarrowThreads), 0, s, g, st, ctr, launch_no, q0, q1, qg,
+    hipLaunchKernelGGL(rows_of(g) == kRun ? k_narrow<kRun> : rows_of(g) == kRecords ? k_narrow<kRecords> : k_narrow<kFirst>, dim3(1), dim3(kNarrowThreads), 0, s, g, st, ctr, launch_no, q0, q1, qg,
                        Masks{M, K, DB, flags}, narrow_cap, sch, log, trace);
     return hipGetLastError();
 }
@@ -898,7 +898,7 @@ hipError_t launch_narrow(const GraphView &g, TravState *st, TravCounters *ctr, i
 // fix-up sweep (only after a queue overflowed): every operator re-derives K from its outputs
 // and pushes what is new to its inputs; repeated by the host until a sweep changes nothing
 // ------------------------------------------------------------------------------------------------
-template <bool kRun>
+template <RowForm kForm>
 __global__ __launch_bounds__(kLevelThreads) void k_fix_sweep(GraphView g, Masks mk, int32_t *changed)
 {
     __shared__ int32_t s_stage[kLevelWaves][kStageCap];
@@ -917,7 +917,7 @@ __global__ __launch_bounds__(kLevelThreads) void k_fix_sweep(GraphView g, Masks 
     for (int64_t tile = tiles - 1 - blockIdx.x; tile >= 0; tile -= gridDim.x) {
         const int64_t o = tile * kLevelThreads + threadIdx.x;
         const bool valid = o < g.num_ops;
-        any |= process_ops<kRun>(g, valid, valid ? (int32_t)o : 0, 0, true, mk, &s_incl[wave][0], ws, f, lc);
+        any |= process_ops<kForm>(g, valid, valid ? (int32_t)o : 0, 0, true, mk, &s_incl[wave][0], ws, f, lc);
         ws.head = ws.tail;
     }
     if (ballot64(any) != 0 && lane_id() == 0) atomicOr(changed, 1);
@@ -926,7 +926,7 @@ __global__ __launch_bounds__(kLevelThreads) void k_fix_sweep(GraphView g, Masks 
 hipError_t launch_fix_sweep(const GraphView &g, u64 *M, u64 *K, uint8_t *flags, int32_t *changed, int grid_blocks, hipStream_t s)
 {
     if (g.num_ops == 0) return hipSuccess;
-    hipLaunchKernelGGL(g.run_shift >= 0 ? k_fix_sweep<true> : k_fix_sweep<false>, dim3((unsigned)grid_blocks), dim3(kLevelThreads), 0, s, g, Masks{M, K, nullptr, flags}, changed);
+    hipLaunchKernelGGL(rows_of(g) == kRun ? k_fix_sweep<kRun> : rows_of(g) == kRecords ? k_fix_sweep<kRecords> : k_fix_sweep<kFirst>, dim3((unsigned)grid_blocks), dim3(kLevelThreads), 0, s, g, Masks{M, K, nullptr, flags}, changed);
     return hipGetLastError();
 }
 
