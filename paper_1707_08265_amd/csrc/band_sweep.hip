@@ -18,7 +18,8 @@
 //
 // What bounds it: the instructions of a step, 0.3 us for 400 operators and 0.22 for 40, one wave's after the other's: LDS round trips
 // 0.12, the flush to memory 0.07.  500 layers of 400 operators, 64 sets, 525 steps: plan 20 us, sweep 160, count and list 18, whole
-// prune 370 -> 215; 300 of 800 412 -> 249; 200 of 90 170 -> 119.  On the way: target bits read back from M a step at a time 218, looked
+// prune 370 -> 213; 300 of 800 412 -> 249; 200 of 90 170 -> 119.  Of that the sweep without its operators is 144, without the flush 132, without
+// either 82, with the flush but not its stores 138.  On the way: target bits read back from M a step at a time 218, looked
 // for among the held ones in every step 225 (now a scalar compare), addresses by the vector unit instead of buffer offsets 219.
 //
 // What a graph must satisfy the plan finds out on the device: outputs numbered as they are created, in one run up to the last
@@ -435,7 +436,6 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
             const uint32_t k = kept[parity * kBandHalf + at];
             const uint32_t slot = at < tensors ? around(from_slot + at) : kBandNowhere + 2 * lane;
             const uint32_t m = ring[slot];
-            ring[slot] = 0;
             if (my_first + kBandHalf < tensors) {
                 const bool is = at + kBandHalf < tensors;
                 const uint32_t slot1 = is ? around(from_slot + at + kBandHalf) : kBandNowhere + 2 * lane + 1;
@@ -443,6 +443,7 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
                 ring[slot1] = 0;
                 __builtin_amdgcn_raw_buffer_store_b16((unsigned short)m1, masks, is ? (at + kBandHalf) * 8 : kPastEnd, from * 8 + slice * 2, 0);
             }
+            ring[slot] = 0;
             __builtin_amdgcn_raw_buffer_store_b16((unsigned short)m, masks, at < tensors ? at * 8 : kPastEnd, from * 8 + slice * 2, 0);
             __builtin_amdgcn_raw_buffer_store_b16((unsigned short)k, op_masks, at < ops ? at * 8 : kPastEnd, op_from * 8 + slice * 2, 0);
         };
@@ -480,7 +481,11 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
             flush_from = y;
             flush_slot -= (uint32_t)tensors;                // (below zero: past the highest number)
             flush_slot = min(flush_slot, flush_slot + (uint32_t)kBandRing);
-            barrier();
+            // (LDS operations of a wave complete in order, and `next` has arrived: the zeros that were stored and the target bits of two steps
+            // ahead are in place before this wave's next barrier, which is soon enough for both)
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
         };
         for (int i0 = s0; i0 < n; i0 += kBandAhead) {
             if (kFromM) {
