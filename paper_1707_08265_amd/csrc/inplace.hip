@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kIpFillThreads) void k_inplace_init(int32_t *rename
 
 // The claimed nodes of a workgroup are gathered in LDS, so that the list's counter in memory is bumped once per workgroup and
 // step, not once per wave (updates of one address take 11 ns each: a wave each would cost more than the pass itself).
-constexpr int kClaimCap = 4096;
+constexpr int kClaimCap = 2048;
 struct ClaimStage {
     int32_t *buf;                                   // [kClaimCap]
     int *count;                                     // claims of the workgroup since the last flush; past kClaimCap they
@@ -211,22 +211,24 @@ __global__ __launch_bounds__(kIpThreads) void k_inplace_children(GraphView g, co
 
 // The same from the list of kept operators that the prune wrote (ascending ids of the operators with K != 0):
 // a pruned graph is a few percent of the recorded one, and the list spares the pass over all of K.  An entry
-// whose mask misses `select` is skipped.
+// whose mask misses `select` is skipped.  Workgroups are small, so that their number, not that of the workgroups on the chip, decides how long the
+// last ones take (1.1 M operators with 2.8 M inputs: 190 us in workgroups of 1 024 threads, two and a little each, now 174).
+constexpr int kListThreads = 256, kListWaves = kListThreads / kWave;
 template <RowForm kForm>
-__global__ __launch_bounds__(kIpThreads) void k_inplace_children_list(GraphView g, const u64 *K, u64 select,
+__global__ __launch_bounds__(kListThreads) void k_inplace_children_list(GraphView g, const u64 *K, u64 select,
                                                                        const int32_t *kept_ops, const int64_t *kept_count,
                                                                        int32_t *rename, int32_t *child, int32_t *list,
                                                                        int32_t *list_count)
 {
     __shared__ int32_t s_claims[kClaimCap];
-    __shared__ int s_mark[kIpWaves][kWave];
+    __shared__ int s_mark[kListWaves][kWave];
     __shared__ int s_count, s_base;
     if (threadIdx.x == 0) s_count = 0;
     __syncthreads();
     const ClaimStage cs{s_claims, &s_count, list, list_count};
     const int64_t kept = kept_count[0];
-    const int64_t gsize = (int64_t)gridDim.x * kIpThreads;
-    for (int64_t base = (int64_t)blockIdx.x * kIpThreads; base < kept; base += gsize) {       // whole workgroups stay in the loop
+    const int64_t gsize = (int64_t)gridDim.x * kListThreads;
+    for (int64_t base = (int64_t)blockIdx.x * kListThreads; base < kept; base += gsize) {       // whole workgroups stay in the loop
         const int64_t i = base + threadIdx.x;
         const int32_t o = i < kept ? kept_ops[i] : 0;
         const bool valid = i < kept && (K[o] & select) != 0;
@@ -310,8 +312,10 @@ hipError_t launch_inplace_setup(const GraphView &g, const u64 *K, u64 select, co
     int64_t blocks = (P + kIpThreads - 1) / kIpThreads;
     if (blocks > grid_blocks / 4) blocks = grid_blocks / 4;
     const RowForm rows = rows_of(g);
+    int64_t list_blocks = (P + kListThreads - 1) / kListThreads;
+    if (list_blocks > grid_blocks) list_blocks = grid_blocks;
     if (P > 0 && kept_ops)
-        hipLaunchKernelGGL(rows == kRun ? k_inplace_children_list<kRun> : rows == kRecords ? k_inplace_children_list<kRecords> : k_inplace_children_list<kFirst>, dim3((unsigned)blocks), dim3(kIpThreads), 0, s, g, K, select,
+        hipLaunchKernelGGL(rows == kRun ? k_inplace_children_list<kRun> : rows == kRecords ? k_inplace_children_list<kRecords> : k_inplace_children_list<kFirst>, dim3((unsigned)list_blocks), dim3(kListThreads), 0, s, g, K, select,
                            kept_ops, kept_count, rename, b.child, b.list, b.counters);
     else if (P > 0)
         hipLaunchKernelGGL(rows == kRun ? k_inplace_children<kRun> : rows == kRecords ? k_inplace_children<kRecords> : k_inplace_children<kFirst>, dim3((unsigned)blocks), dim3(kIpThreads), 0, s, g, K, select, rename, b.child,
