@@ -573,7 +573,7 @@ int sort_lists(const dgn_graph *h, const EdgeList &in, const EdgeList &out, cons
             if (rc) return rc;
             rc = read_status(S.status, s, found);
             if (rc || (*found)[0] || !(*found)[kStatusPending]) return rc;
-            DGN_HIP(launch_expand_rows(L.out_rowptr, (int32_t)P, (int32_t)Eout, S.sorted_ops, S.status, s));
+            DGN_HIP(launch_expand_rows(L.out_rowptr, (int32_t)P, (int32_t)Eout, S.sorted_ops, nullptr, nullptr, (int32_t)T, S.status, s));
             DGN_HIP(launch_clear(clr, 1, s));
         } else {
             DGN_HIP(launch_check_ids(out, S.status, s));
@@ -752,9 +752,9 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
         // valid entry then.
         DGN_HIP(launch_check_csr(h->v, S.status, s));
         // the outputs as a list in operator order: its tensors usually ascend as well, and the pass over it is all it takes
-        DGN_HIP(launch_expand_rows(d->out_rowptr, (int32_t)P, (int32_t)Eout, S.sorted_ops, S.status, s));
+        DGN_HIP(launch_expand_rows(d->out_rowptr, (int32_t)P, (int32_t)Eout, S.sorted_ops, L.prod_idx, L.prod_rowptr, (int32_t)T, S.status, s));
         const EdgeList list{S.sorted_ops, d->out_idx, Eout, (int32_t)P, (int32_t)T, nullptr, nullptr, L.prod_idx, L.prod_rowptr, L.prod1, may_run(h)};
-        DGN_HIP(launch_scan_edges(nullptr, list, S.status, s));
+        DGN_HIP(launch_scan_edges(nullptr, list, S.status, s, h->G == 1));
         e = enqueue_records(h, L, S.status, options, s, false);
         if (e) return e;
         e = read_status(S.status, s, &found);

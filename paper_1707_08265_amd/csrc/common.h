@@ -375,7 +375,8 @@ hipError_t launch_check_ids(const EdgeList &l, int32_t *status, hipStream_t s);
 hipError_t launch_first_look(const EdgeList &in, const EdgeList &out, int32_t *status, hipStream_t s);
 // one pass over the input edges (NULL: the outputs only) and the output edges: checks them and, assuming that they are in
 // order, writes the finished adjacency
-hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s);
+// maybe_left: the outputs' rows by tensor are likely to be there already (kStatusLeaveOut)
+hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s, bool maybe_left = false);
 // The kernels from here to launch_check_topological do nothing if the status says that there is no adjacency yet.
 // what launch_build_records notes about how far back operators read, where there are no records to be made
 hipError_t launch_sample_reach(const GraphView &g, int32_t *status, hipStream_t s);
@@ -391,8 +392,9 @@ hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *s
 hipError_t launch_order_rows(const int32_t *ops, const int32_t *tensors, int64_t nnz, int32_t *keys, int32_t *status, hipStream_t s);
 // rowptr[0..n_rows] from keys that are in row order; nothing if the status has an error (all are in range)
 hipError_t launch_row_bounds(const int32_t *keys, int64_t nnz, int32_t n_rows, int32_t *rowptr, const int32_t *status, hipStream_t s);
-hipError_t launch_check_csr(const GraphView &g, int32_t *error, hipStream_t s);
-hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz, int32_t *row_of, const int32_t *status, hipStream_t s);
+hipError_t launch_check_csr(const GraphView &g, int32_t *status, hipStream_t s);
+hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz, int32_t *row_of, int32_t *run_idx, int32_t *run_row,
+                              int32_t num_tensors, int32_t *status, hipStream_t s);
 
 // Traversal.
 hipError_t launch_seed(const GraphView &g, int32_t Q, int64_t num_targets, const int32_t *tgt_rowptr,

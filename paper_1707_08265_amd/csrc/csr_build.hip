@@ -39,7 +39,7 @@ __device__ __forceinline__ void rows_closed(int32_t prev, int32_t cur, int32_t n
 // the pass waiting for memory).  Outputs take both adjacencies and the producer words from one reading: three passes did
 // that before, 0.99 ms of a 50 M-operator graph and 0.3 more for the producer words; then 1.00 in all, with its stores past the
 // caches 0.91, without the producer words of one run 0.81, with a workgroup per piece of the lists 0.77 = 5.1 TB/s.
-constexpr int kScanThreads = 256;
+constexpr int kScanThreads = 256, kScanTile = kScanThreads * 4;
 
 template <bool kOut, bool kStream>
 __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int64_t blocks, uint32_t *s_words, int32_t *status)
@@ -183,7 +183,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_edges(EdgeList in, EdgeLi
 // with every 8 192nd piece: 850 us for 50 M operators, 2 048 in all: 975, one each: 797.)  That many would read all of a list in no order before
 // the first of them could say so, so that long ones are looked at in a few places before (12 M operators in shuffled order: 1 100, 1 030
 // with 8 192 per list, 1 016 so).
-constexpr int kScanTile = kScanThreads * 4;
 static int scan_blocks(int64_t nnz) { return (int)((nnz + 1 + kScanTile - 1) / kScanTile); }
 
 // Long lists: a wave looks at 64 neighbouring positions in each of kLooks places.
@@ -215,10 +214,12 @@ hipError_t launch_first_look(const EdgeList &in, const EdgeList &out, int32_t *s
     return hipGetLastError();
 }
 
-hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s)
+hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *status, hipStream_t s, bool maybe_left)
 {
     const int in_blocks = in ? scan_blocks(in->nnz) : 0;
-    const dim3 grid((unsigned)(in_blocks + scan_blocks(out.nnz)));
+    int out_blocks = scan_blocks(out.nnz);
+    if (maybe_left && out_blocks > 8192) out_blocks = 8192;             // (those that find the list left cost 0.2 ns each)
+    const dim3 grid((unsigned)(in_blocks + out_blocks));
     const size_t written = (in ? (size_t)in->nnz * 4 : 0) + (size_t)out.nnz * 8 + (size_t)out.num_ops * 8 + (size_t)out.num_tensors * 8;
     if (written > kStreamBytes)
         hipLaunchKernelGGL(k_scan_edges<true>, grid, dim3(kScanThreads), 0, s, in ? *in : out, out, in_blocks, status + kStatusLeaveIn, status);
@@ -361,53 +362,94 @@ hipError_t launch_check_ids(const EdgeList &l, int32_t *status, hipStream_t s)
     return hipGetLastError();
 }
 
-// Borrowed CSR: rowptr[0] == 0, monotone, rowptr[n_rows] == nnz, every idx in [0, n_vals).  Inputs and outputs in one launch.
-__device__ __forceinline__ int check_csr(const int32_t *rowptr, const int32_t *idx, int32_t n_rows, int32_t nnz, int32_t n_vals, int64_t gtid,
-                                         int64_t gsize)
+// Borrowed CSR: rowptr[0] == 0, monotone, rowptr[n_rows] == nnz, every idx in [0, n_vals), and whether the outputs are one run of tensors.
+// All four arrays in one launch, a workgroup per 1 024 entries and four of them per thread: the arrays are read once, at the rate of
+// memory (50 M operators, 1.3 GB: 450 us with 8 192 workgroups and an entry per load, 225 so).
+struct CsrTiles { int32_t in_idx, out_row, out_idx; };                 // first tiles of the arrays behind in_rowptr
+__global__ __launch_bounds__(kScanThreads) void k_check_csr(GraphView g, CsrTiles tiles, int32_t *status)
 {
+    __shared__ int s_scattered;
+    constexpr int kPer = 4;
+    if (threadIdx.x == 0) s_scattered = 0;
+    __syncthreads();
+    const int tile = blockIdx.x;
+    // (an array without entries has no tile, and begins where the next one does)
+    const int which = tile < tiles.in_idx ? 0 : tile < tiles.out_row ? 1 : tile < tiles.out_idx ? 2 : 3;
+    const int first = which == 0 ? 0 : which == 1 ? tiles.in_idx : which == 2 ? tiles.out_row : tiles.out_idx;
+    const bool in = which < 2, rows = which == 0 || which == 2;
+    const int32_t *p = which == 0 ? g.in_rowptr : which == 1 ? g.in_idx : which == 2 ? g.out_rowptr : g.out_idx;
+    const int32_t nnz = in ? g.nnz_in : g.nnz_out;
+    const int64_t n = rows ? (int64_t)g.num_ops + 1 : nnz;
+    const int64_t e0 = (int64_t)(tile - first) * kScanTile + threadIdx.x * kPer;
+    int32_t v[kPer + 1];
+    if (((uintptr_t)p & 15) == 0 && e0 + kPer <= n) {
+        const int4 x = *reinterpret_cast<const int4 *>(p + e0);
+        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+    } else {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) v[j] = e0 + j < n ? p[e0 + j] : 0;
+    }
+    v[kPer] = rows && e0 + kPer < n ? p[e0 + kPer] : 0;
+    const int32_t shift = g.num_tensors - g.nnz_out;
     int bad = 0;
-    for (int64_t r = gtid; r <= n_rows; r += gsize) {
-        const int32_t a = rowptr[r];
-        if (a < 0 || a > nnz) bad |= kErrCsr;
-        if (r == 0 && a != 0) bad |= kErrCsr;
-        if (r == n_rows && a != nnz) bad |= kErrCsr;
-        if (r < n_rows && rowptr[r + 1] < a) bad |= kErrCsr;
+    bool scattered = false;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int64_t e = e0 + j;
+        if (e >= n) break;
+        if (rows) {
+            if (v[j] < 0 || v[j] > nnz || (e == 0 && v[j] != 0) || (e == n - 1 ? v[j] != nnz : v[j + 1] < v[j])) bad |= kErrCsr;
+        } else {
+            if (v[j] < 0 || v[j] >= g.num_tensors) bad |= kErrIdRange;
+            scattered |= v[j] != (int32_t)e + shift;
+        }
     }
-    for (int64_t e = gtid; e < nnz; e += gsize) {
-        const int32_t v = idx[e];
-        if (v < 0 || v >= n_vals) bad |= kErrIdRange;
+    if (bad) atomicOr(status, bad);
+    if (rows || in) return;                                             // (the same in every thread)
+    if (ballot64(scattered) != 0 && lane_id() == 0) s_scattered = 1;
+    __syncthreads();
+    if (threadIdx.x < 2 && s_scattered) {
+        int32_t *word = status + (threadIdx.x ? kStatusScattered : kStatusNoRun);
+        if (load_coherent(word) == 0) store_coherent(word, 1);
     }
-    return bad;
 }
 
-__global__ __launch_bounds__(256) void k_check_csr(GraphView g, int32_t *error)
+hipError_t launch_check_csr(const GraphView &g, int32_t *status, hipStream_t s)
 {
-    const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
-    const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int bad = check_csr(g.in_rowptr, g.in_idx, g.num_ops, g.nnz_in, g.num_tensors, gtid, gsize) |
-                    check_csr(g.out_rowptr, g.out_idx, g.num_ops, g.nnz_out, g.num_tensors, gtid, gsize);
-    if (bad) atomicOr(error, bad);
-}
-
-hipError_t launch_check_csr(const GraphView &g, int32_t *error, hipStream_t s)
-{
-    const int64_t nnz = g.nnz_in > g.nnz_out ? g.nnz_in : g.nnz_out;
-    const int64_t work = (int64_t)g.num_ops + 1 > nnz ? (int64_t)g.num_ops + 1 : nnz;
-    int64_t blocks = (work + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_check_csr, dim3((unsigned)blocks), dim3(256), 0, s, g, error);
+    auto of = [](int64_t n) { return (int32_t)((n + kScanTile - 1) / kScanTile); };
+    CsrTiles t{of((int64_t)g.num_ops + 1), 0, 0};
+    t.out_row = t.in_idx + of(g.nnz_in);
+    t.out_idx = t.out_row + of((int64_t)g.num_ops + 1);
+    hipLaunchKernelGGL(k_check_csr, dim3((unsigned)(t.out_idx + of(g.nnz_out))), dim3(kScanThreads), 0, s, g, t, status);
     return hipGetLastError();
 }
 
 // row_of[e] = r for every entry e of row r (operator id of every entry of an out CSR), long rows by whole waves (a thread takes
 // 0.1 us per entry: 2 000 outputs of one operator 250 us, now 3); -1 everywhere if the CSR is none, or an index of it is
-// out of range (status[0]): the pass over this list then reports that again, and touches nothing
-__global__ __launch_bounds__(256) void k_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz, int32_t *row_of, const int32_t *status)
+// out of range (status[0]): the pass over this list then reports that again, and touches nothing.
+// run_idx, run_row (or NULL): where the outputs are one run of tensors these are the rows by tensor, finished here, and the pass over the
+// list is told to leave it (50 M operators, borrowed: 1 050 -> 672 us with what k_check_csr gains).
+__global__ __launch_bounds__(256) void k_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz, int32_t *row_of, int32_t *run_idx,
+                                                     int32_t *run_row, int32_t num_tensors, int32_t *status)
 {
     const int64_t gsize = (int64_t)gridDim.x * blockDim.x, gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (status[0] & (kErrCsr | kErrIdRange)) {
         for (int64_t e = gtid; e < nnz; e += gsize) row_of[e] = -1;
         return;
+    }
+    const bool run = run_idx && status[kStatusNoRun] == 0;
+    if (run) {
+        const int32_t shift = num_tensors - nnz;
+        for (int64_t t = gtid * 4; t <= num_tensors; t += gsize * 4) {  // (run_row is aligned)
+            auto row = [&](int64_t at) { return (int32_t)max(at - shift, (int64_t)0); };
+            if (t + 4 <= num_tensors) {
+                *reinterpret_cast<int4 *>(run_row + t) = make_int4(row(t), row(t + 1), row(t + 2), row(t + 3));
+            } else {
+                for (int64_t at = t; at <= num_tensors; ++at) run_row[at] = row(at);
+            }
+        }
+        if (gtid == 0) status[kStatusLeaveOut] = 1;
+        row_of = run_idx;
     }
     for (int64_t r = gtid; r - lane_id() < n_rows; r += gsize) {            // whole waves stay in the loop
         const bool is = r < n_rows;
@@ -415,12 +457,14 @@ __global__ __launch_bounds__(256) void k_expand_rows(const int32_t *rowptr, int3
     }
 }
 
-hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz, int32_t *row_of, const int32_t *status, hipStream_t s)
+hipError_t launch_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz, int32_t *row_of, int32_t *run_idx, int32_t *run_row,
+                              int32_t num_tensors, int32_t *status, hipStream_t s)
 {
-    if (n_rows == 0) return hipSuccess;
     int64_t blocks = ((int64_t)n_rows + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_expand_rows, dim3((unsigned)blocks), dim3(256), 0, s, rowptr, n_rows, nnz, row_of, status);
+    const int64_t tensors = run_row ? ((int64_t)num_tensors / 4 + 256) / 256 : 0;
+    if (blocks < tensors) blocks = tensors;
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_expand_rows, dim3((unsigned)blocks), dim3(256), 0, s, rowptr, n_rows, nnz, row_of, run_idx, run_row, num_tensors, status);
     return hipGetLastError();
 }
 

@@ -97,6 +97,40 @@ def test_outputs_in_two_runs(dgn, oracle, writers, at, several):
     check(dgn, oracle, g, rng, f"{writers} {at} {several}")
 
 
+@pytest.mark.parametrize("numbering", ["run", "in rows", "hole"])
+@pytest.mark.parametrize("ops,fan,at", [(1, 0, 1), (3, 0, 0), (1023, 1, 1), (1024, 0, 2), (1025, 2, 3), (5000, 2, 0), (140_000, 1, 1)])
+def test_borrowed_rows_of_any_alignment(dgn, oracle, ops, fan, at, numbering):
+    """Borrowed arrays that begin `at` entries past a 16-byte boundary, with and without inputs, sizes around a workgroup's entries: outputs that
+    are one run of tensors (finished without a pass over them as a list), that are one but for the order inside rows, and that have a hole."""
+    import torch
+    rng = np.random.default_rng(ops + at)
+    n_out = rng.integers(0, 3, ops)
+    n_out[-1] = 2
+    t = 4 + np.arange(n_out.sum())
+    if numbering == "in rows":
+        t[-2:] = t[-2:][::-1]
+    if numbering == "hole":
+        t[len(t) // 2:] += 1
+    out_op, in_op = np.repeat(np.arange(ops), n_out), np.repeat(np.arange(ops), fan)
+    in_t = (rng.random(in_op.size) * 4).astype(np.int64)
+    i32 = lambda a: np.ascontiguousarray(a, dtype=np.int32)  # noqa: E731
+    g = gg.Graph(ops, int(t.max()) + 1, i32(in_op), i32(in_t), i32(out_op), i32(t), name="borrowed")
+    tg = targets_from_sets([[int(x) for x in rng.integers(0, g.num_tensors, 3)] for _ in range(5)], 5)
+    adj, ref = oracle_prune(oracle, g, tg)
+    keep = []
+    for name in ROWS[:4]:
+        a = torch.zeros(getattr(adj, name).size + at, dtype=torch.int32, device="cuda")[at:]
+        keep.append(a.copy_(torch.from_numpy(np.ascontiguousarray(getattr(adj, name)))))
+    dg = dgn.DeviceGraph.from_csr(g.num_ops, g.num_tensors, *keep)
+    csr = {n: v.cpu().numpy() for n, v in dg.csr().items()}
+    for name in ROWS:
+        assert np.array_equal(csr[name], getattr(adj, name)), name
+    buf = dgn.PruneBuffers(dg, 5)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    assert buf.prune(up(tg.tgt_rowptr), up(tg.tgt_idx), options=dgn.dgn_options(traversal=1)) == 0
+    assert_same(buf.to_host(), ref, numbering)
+
+
 @pytest.mark.parametrize("nnz", [8192 * 1024, 8192 * 1024 + 1, 8192 * 1024 + 77])
 @pytest.mark.parametrize("order", ["recorded", "outputs", "inputs", "last"])
 def test_long_lists_are_looked_at_before(dgn, oracle, nnz, order):
