@@ -1029,14 +1029,13 @@ static int band_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     a.tgt_rowptr = tgt_rowptr;
     a.tgt_idx = tgt_idx;
     a.M = M;
-    a.K = K;
     a.state = S.state;
     a.host_status = static_cast<int32_t *>(pin);
     a.hdr = S.hdr;
     a.want = RecycleHeader{kBandMagic, g->serial, M, K, kept_ops, kept_count, op_flag, also_M, also_K, {0, 0, 0}};
     a.recycle = options && options->recycle;
     for (int i = 0; i < 8; ++i) a.host_status[i] = 0;
-    const FillRegion clear[kBandRegions] = {{M, (size_t)g->T * 8}, {K, (size_t)g->P * 8}, {S.state, 256 + sizeof(TravCounters)},
+    const FillRegion clear[kBandRegions] = {{M, (size_t)g->T * 8}, {S.state, 256 + sizeof(TravCounters)},
                                             {per_query_count, pq_bytes}, {S.pq_part, per_query_count ? S.pq_part_bytes : 0},
                                             {also_M, (size_t)g->T * 8}, {also_K, (size_t)g->P * 8}};
     for (int i = 0; i < kBandRegions; ++i) a.clear[i] = clear[i];
@@ -1059,6 +1058,7 @@ static int band_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     ca.M = M;
     ca.K = K;
     ca.op_flag = op_flag ? op_flag : flags;
+    ca.from_tensor_mask = true;                             // (the sweep leaves M alone: see band_sweep.hip)
     ca.kept_ops = kept_ops;
     ca.kept_masks = kept_masks;
     ca.kept_count = kept_count;

@@ -9,18 +9,19 @@
 //   k_band_plan cuts the operators into steps and packs what the sweep needs of an operator into 12 bytes (LDS slots of its
 // outputs and inputs).  A step that ends before operator b may begin at any operator behind the last one that some operator
 // before b reads from (in its segment of 8 192 operators): a running maximum, and then a chain of one LDS access per step.
-// Its other workgroups clear M and K.
+// Its other workgroups clear M.
 //   k_band_sweep: eight waves process a step's operators (two LDS reads, up to four ORs), the other eight take M of the
-// step before and its K out of LDS to memory, and put target bits, which they hold in registers, in place two steps ahead (a call of
+// step before out of LDS to memory, and put target bits, which they hold in registers, in place two steps ahead (a call of
 // more than 2 048 targets, of all its words, sends them by way of M and the seed kernel, since one workgroup may own them all: steps of
-// 0.42 us instead of 0.3).  Operators are fetched eight steps ahead; no step waits for memory, and
-// a barrier is all that separates two of them.  The removal rule's count and list passes follow as behind the traversal.
+// 0.35 us instead of 0.27).  Operators are fetched eight steps ahead; no step waits for memory, and
+// a barrier is all that separates two of them.  The removal rule's passes follow and take K from M: keeping K of a step in LDS and storing
+// it from here cost the sweep 19 us of 161, the count pass's two reads per operator cost 4 more.
 //
-// What bounds it: the instructions of a step, 0.3 us for 400 operators and 0.22 for 40, one wave's after the other's: LDS round trips
-// 0.12, the flush to memory 0.07.  500 layers of 400 operators, 64 sets, 525 steps: plan 20 us, sweep 160, count and list 18, whole
-// prune 370 -> 213; 300 of 800 412 -> 249; 200 of 90 170 -> 119.  Of that the sweep without its operators is 144, without the flush 132, without
-// either 82, with the flush but not its stores 138.  On the way: target bits read back from M a step at a time 218, looked
-// for among the held ones in every step 225 (now a scalar compare), addresses by the vector unit instead of buffer offsets 219.
+// What bounds it: the instructions of a step, 0.27 us for 400 operators, one wave's after the other's: barrier and bounds
+// 0.15, ORs 0.04, the flush's stores (two bytes every eight; in runs of their own as long) 0.03.  500 layers of 400 operators, 64 sets, 525 steps: plan
+// 20 us, sweep 142, count and list 24, whole prune 370 -> 201; 300 of 800 412 -> 223; 200 of 90 170 -> 110; 1 000 of 800, 16 sets, 576.  On
+// the way: bounds of eight steps held in a register instead of LDS reads 168 against 161; target bits read back from M a step at a time 218, looked
+// for among the held ones in every step 225 (now a scalar compare), addresses by the vector unit instead of buffer offsets 219, whole prune, when it took 215.
 //
 // What a graph must satisfy the plan finds out on the device: outputs numbered as they are created, in one run up to the last
 // tensor, inputs written before, at most kBandMaxSteps steps, of kBandMeanOps operators or more on average where there are more than
@@ -38,7 +39,7 @@ constexpr int kBandZero = kBandNowhere + 2 * kWave;                    // one th
 constexpr int kBandStepsAt = (kBandZero + 4) / 2;             // (in 4-byte words) the steps' first operators and tensors
 constexpr int kBandPad = 32;                        // empty ones behind them
 constexpr int kBandMaxSegs = (int)(kBandMaxOps / kBandSegOps);
-constexpr size_t kBandLds = ((size_t)kBandStepsAt + 2 * (kBandMaxSteps + 1 + kBandPad) + kBandMaxSegs + 8 + 18 + kBandStepOps) * sizeof(uint32_t);
+constexpr size_t kBandLds = ((size_t)kBandStepsAt + 2 * (kBandMaxSteps + 1 + kBandPad) + kBandMaxSegs + 8 + 18) * sizeof(uint32_t);
 constexpr uint32_t kBandMore = 0xffff;
 static_assert(kBandZero < kBandMore, "slots have 16 bits");
 static_assert(kBandLds <= kRingMaxLds, "LDS of a compute unit");
@@ -227,7 +228,6 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
     int &s_dist = s_first[kBandMaxSegs + 1], &s_span = s_first[kBandMaxSegs + 2], &s_bad = s_first[kBandMaxSegs + 3];
     int &s_top = s_first[kBandMaxSegs + 4], &s_skip = s_first[kBandMaxSegs + 5], &s_err = s_first[kBandMaxSegs + 6];
     int32_t *s_row = s_first + kBandMaxSegs + 8;            // row pointers of this workgroup's sets
-    uint16_t *kept = reinterpret_cast<uint16_t *>(s_row + 18);               // K of the operators of two steps in turn
     int2 *step = reinterpret_cast<int2 *>(lds + kBandStepsAt);               // [i]: step i is operators [step[i + 1].x, step[i].x), tensors by .y
     uint16_t *M = reinterpret_cast<uint16_t *>(a.M) + slice;                 // (4 per mask)
     if (tid == 0) {
@@ -380,7 +380,6 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
                         band_or(lds, e.z & 0xffff, k);
                         band_or(lds, e.z >> 16, k);
                     }
-                    kept[(u & 1) * kBandHalf + tid] = (uint16_t)k;
                 }
                 entry[u] = fetch(ahead);
                 end = from;
@@ -393,7 +392,6 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
         // tensors
         const int at = tid - kBandHalf;
         const auto masks = __builtin_amdgcn_make_buffer_rsrc(a.M, 0, g.num_tensors * (int)sizeof(u64), kBufferWord);
-        const auto op_masks = __builtin_amdgcn_make_buffer_rsrc(a.K, 0, g.num_ops * (int)sizeof(u64), kBufferWord);
         uint16_t seed[kBandAhead][2] = {};
         // slot of tensor from + lane's place: at most once around the ring
         auto slot_of = [&](int32_t from, int place) {
@@ -428,12 +426,11 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
                 next_target = -wave_max(later);
             }
         };
-        // M of a step's tensors and K of its operators.  A wave's instructions here are what a step waits for, branches above
+        // M of a step's tensors.  A wave's instructions here are what a step waits for, branches above
         // all (reads in one step and stores in the next: 160 -> 193 us for 500 layers of 400).
         auto around = [](uint32_t slot) { return min(slot, slot - (uint32_t)kBandRing); };
-        auto flush = [&](int parity, int32_t from, int tensors, uint32_t from_slot, int32_t op_from, int ops) {
-            if (my_first >= max(tensors, ops)) return;      // uniform
-            const uint32_t k = kept[parity * kBandHalf + at];
+        auto flush = [&](int32_t from, int tensors, uint32_t from_slot) {
+            if (my_first >= tensors) return;                // uniform
             const uint32_t slot = at < tensors ? around(from_slot + at) : kBandNowhere + 2 * lane;
             const uint32_t m = ring[slot];
             if (my_first + kBandHalf < tensors) {
@@ -445,7 +442,6 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
             }
             ring[slot] = 0;
             __builtin_amdgcn_raw_buffer_store_b16((unsigned short)m, masks, at < tensors ? at * 8 : kPastEnd, from * 8 + slice * 2, 0);
-            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)k, op_masks, at < ops ? at * 8 : kPastEnd, op_from * 8 + slice * 2, 0);
         };
         int32_t y0 = uniform(bound(s0, true)), y1 = uniform(bound(s0 + 1, true)), y2 = uniform(bound(s0 + 2, true));
         {
@@ -458,15 +454,15 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
 #pragma unroll
         for (int u = 0; u < kBandAhead; ++u) fetch(uniform(bound(s0 + u + 3, true)), seed[u]);
         // of the step before (none yet): first tensor and operator, how many, slot; [place_from, place_end): two steps ahead
-        int32_t flush_from = y0, ops_from = uniform(bound(s0, false)), place_end = y2, place_from = uniform(bound(s0 + 3, true)),
+        int32_t flush_from = y0, place_end = y2, place_from = uniform(bound(s0 + 3, true)),
                 ahead = uniform(bound(s0 + kBandAhead + 3, true));
-        int tensors = 0, ops = 0;
+        int tensors = 0;
         uint32_t flush_slot = (uint32_t)y0 % (uint32_t)kBandRing;
         barrier();
-        auto one = [&](int i, int parity, uint16_t (&bits)[2]) {
-            const int2 next = step[i + 1];
+        auto one = [&](int i, uint16_t (&bits)[2]) {
+            const int32_t next = bound(i + 1, true);
             const int32_t next_place = kFromM ? bound(i + 4, true) : 0, next_ahead = kFromM ? bound(i + kBandAhead + 4, true) : 0;
-            flush(parity ^ 1, flush_from, tensors, flush_slot, ops_from, ops);
+            flush(flush_from, tensors, flush_slot);
             place(i + 2, place_from, place_end, bits);
             if (kFromM) {
                 fetch(ahead, bits);
@@ -474,9 +470,7 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
                 place_from = uniform(next_place);
                 ahead = uniform(next_ahead);
             }
-            const int32_t x = uniform(next.x), y = uniform(next.y);
-            ops = ops_from - x;
-            ops_from = x;
+            const int32_t y = uniform(next);
             tensors = flush_from - y;
             flush_from = y;
             flush_slot -= (uint32_t)tensors;                // (below zero: past the highest number)
@@ -490,13 +484,13 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
         for (int i0 = s0; i0 < n; i0 += kBandAhead) {
             if (kFromM) {
 #pragma unroll
-                for (int u = 0; u < kBandAhead; ++u) one(i0 + u, u & 1, seed[u]);
+                for (int u = 0; u < kBandAhead; ++u) one(i0 + u, seed[u]);
             } else {                                        // (no loads: the less code the better)
 #pragma unroll 1
-                for (int u = 0; u < kBandAhead; ++u) one(i0 + u, u & 1, seed[0]);
+                for (int u = 0; u < kBandAhead; ++u) one(i0 + u, seed[0]);
             }
         }
-        flush(1, flush_from, tensors, flush_slot, ops_from, ops);
+        flush(flush_from, tensors, flush_slot);
     }
     __syncthreads();
     for (int t = tid; t < t_first; t += N) M[(int64_t)t * 4] = ring[kBandRing + t];

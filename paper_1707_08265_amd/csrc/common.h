@@ -470,20 +470,20 @@ inline int64_t ring_words(int waves, int dist, int span64)
 // ev (or NULL): ev[0] is recorded behind the sweep; with `all`, ev[1] behind the per-graph counts and ev[2] behind the list
 hipError_t launch_ring_sweep(RingArgs a, int waves, int dist, int span64, int64_t max_graph_ops, int *launches, hipStream_t s,
                              hipEvent_t *ev, bool all);
-// The same for one graph of wide layers (see band_sweep.hip): a workgroup per sixteen sets.  The plan clears M and K.
+// The same for one graph of wide layers (see band_sweep.hip): a workgroup per sixteen sets.  The plan clears M.
 constexpr int64_t kBandMaxOps = (int64_t)1 << 20;
 constexpr int kBandMaxLow = 8192;         // graph inputs, at most
 constexpr int kBandMaxSteps = 4096;
 constexpr int kBandStepOps = 512, kBandStepOuts = 1024;
 constexpr int64_t kBandMaxTargets = 2048; // that the sweep puts in place itself; more go by way of M and the seed kernel
-constexpr int kBandRegions = 7;
+constexpr int kBandRegions = 6;
 enum : int { kBandTaken = 0, kBandFound = 1, kBandErrors = 4 /* by sixteen sets */ };
 struct BandArgs {
     GraphView g;
     int32_t num_sets;
     int64_t num_targets;
     const int32_t *tgt_rowptr, *tgt_idx;
-    u64 *M, *K;
+    u64 *M;
     TravState *state;        // its error bits
     int32_t *host_status;    // pinned host memory: 1 + steps or 0 (the graph is not of this kind: nothing written), header found, error bits
     RecycleHeader *hdr, want;

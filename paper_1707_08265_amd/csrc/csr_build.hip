@@ -363,13 +363,14 @@ hipError_t launch_check_ids(const EdgeList &l, int32_t *status, hipStream_t s)
 }
 
 // Borrowed CSR: rowptr[0] == 0, monotone, rowptr[n_rows] == nnz, every idx in [0, n_vals), and whether the outputs are one run of tensors.
-// All four arrays in one launch, a workgroup per 1 024 entries and four of them per thread: the arrays are read once, at the rate of
-// memory (50 M operators, 1.3 GB: 450 us with 8 192 workgroups and an entry per load, 225 so).
+// All four arrays in one launch, a workgroup per 4 096 entries, sixteen bytes per load: the arrays are read once, at the rate of
+// memory (50 M operators, 1.3 GB: 450 us with 8 192 workgroups and an entry per load, 283 so; 366 with 1 024 entries per workgroup).
+constexpr int kCsrTile = 4 * kScanTile;
 struct CsrTiles { int32_t in_idx, out_row, out_idx; };                 // first tiles of the arrays behind in_rowptr
 __global__ __launch_bounds__(kScanThreads) void k_check_csr(GraphView g, CsrTiles tiles, int32_t *status)
 {
     __shared__ int s_scattered;
-    constexpr int kPer = 4;
+    constexpr int kPer = 4, kAtOnce = kCsrTile / kScanTile;
     if (threadIdx.x == 0) s_scattered = 0;
     __syncthreads();
     const int tile = blockIdx.x;
@@ -380,28 +381,36 @@ __global__ __launch_bounds__(kScanThreads) void k_check_csr(GraphView g, CsrTile
     const int32_t *p = which == 0 ? g.in_rowptr : which == 1 ? g.in_idx : which == 2 ? g.out_rowptr : g.out_idx;
     const int32_t nnz = in ? g.nnz_in : g.nnz_out;
     const int64_t n = rows ? (int64_t)g.num_ops + 1 : nnz;
-    const int64_t e0 = (int64_t)(tile - first) * kScanTile + threadIdx.x * kPer;
-    int32_t v[kPer + 1];
-    if (((uintptr_t)p & 15) == 0 && e0 + kPer <= n) {
-        const int4 x = *reinterpret_cast<const int4 *>(p + e0);
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-    } else {
+    int32_t v[kAtOnce][kPer + 1];
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) v[j] = e0 + j < n ? p[e0 + j] : 0;
+    for (int q = 0; q < kAtOnce; ++q) {
+        const int64_t e0 = (int64_t)(tile - first) * kCsrTile + q * kScanTile + threadIdx.x * kPer;
+        if (((uintptr_t)p & 15) == 0 && e0 + kPer <= n) {
+            const int4 x = *reinterpret_cast<const int4 *>(p + e0);
+            v[q][0] = x.x; v[q][1] = x.y; v[q][2] = x.z; v[q][3] = x.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) v[q][j] = e0 + j < n ? p[e0 + j] : 0;
+        }
+        v[q][kPer] = rows && e0 + kPer < n ? p[e0 + kPer] : 0;
     }
-    v[kPer] = rows && e0 + kPer < n ? p[e0 + kPer] : 0;
     const int32_t shift = g.num_tensors - g.nnz_out;
     int bad = 0;
     bool scattered = false;
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const int64_t e = e0 + j;
-        if (e >= n) break;
-        if (rows) {
-            if (v[j] < 0 || v[j] > nnz || (e == 0 && v[j] != 0) || (e == n - 1 ? v[j] != nnz : v[j + 1] < v[j])) bad |= kErrCsr;
-        } else {
-            if (v[j] < 0 || v[j] >= g.num_tensors) bad |= kErrIdRange;
-            scattered |= v[j] != (int32_t)e + shift;
+    for (int q = 0; q < kAtOnce; ++q) {
+        const int64_t e0 = (int64_t)(tile - first) * kCsrTile + q * kScanTile + threadIdx.x * kPer;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int64_t e = e0 + j;
+            const int32_t x = v[q][j];
+            if (e >= n) break;
+            if (rows) {
+                if (x < 0 || x > nnz || (e == 0 && x != 0) || (e == n - 1 ? x != nnz : v[q][j + 1] < x)) bad |= kErrCsr;
+            } else {
+                if (x < 0 || x >= g.num_tensors) bad |= kErrIdRange;
+                scattered |= x != (int32_t)e + shift;
+            }
         }
     }
     if (bad) atomicOr(status, bad);
@@ -416,7 +425,7 @@ __global__ __launch_bounds__(kScanThreads) void k_check_csr(GraphView g, CsrTile
 
 hipError_t launch_check_csr(const GraphView &g, int32_t *status, hipStream_t s)
 {
-    auto of = [](int64_t n) { return (int32_t)((n + kScanTile - 1) / kScanTile); };
+    auto of = [](int64_t n) { return (int32_t)((n + kCsrTile - 1) / kCsrTile); };
     CsrTiles t{of((int64_t)g.num_ops + 1), 0, 0};
     t.out_row = t.in_idx + of(g.nnz_in);
     t.out_idx = t.out_row + of((int64_t)g.num_ops + 1);
@@ -428,7 +437,7 @@ hipError_t launch_check_csr(const GraphView &g, int32_t *status, hipStream_t s)
 // 0.1 us per entry: 2 000 outputs of one operator 250 us, now 3); -1 everywhere if the CSR is none, or an index of it is
 // out of range (status[0]): the pass over this list then reports that again, and touches nothing.
 // run_idx, run_row (or NULL): where the outputs are one run of tensors these are the rows by tensor, finished here, and the pass over the
-// list is told to leave it (50 M operators, borrowed: 1 050 -> 672 us with what k_check_csr gains).
+// list is told to leave it (50 M operators, borrowed: 1 050 -> 590 us with what k_check_csr gains).
 __global__ __launch_bounds__(256) void k_expand_rows(const int32_t *rowptr, int32_t n_rows, int32_t nnz, int32_t *row_of, int32_t *run_idx,
                                                      int32_t *run_row, int32_t num_tensors, int32_t *status)
 {
