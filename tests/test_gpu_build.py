@@ -429,3 +429,31 @@ def test_faults_of_a_borrowed_csr_are_reported_wherever_they_are(dgn, oracle, op
         assert rc == want, (name, at, value, rc)
         if handle:
             dgn.dgn_graph_destroy(handle)
+
+
+@pytest.mark.parametrize("graphs", [63, 64, 65, 200])
+@pytest.mark.parametrize("relabelled", [False, True])
+def test_batches_around_the_number_that_have_no_records(dgn, oracle, graphs, relabelled):
+    """From 64 graphs on a batch has a word per operator in the place of records: levels, in-place pass (from op_mask and from the list) and ignore mask
+    go by it, also where an operator's outputs are not consecutive."""
+    import torch
+    g, tg = gg.batch_layered(graphs, 150, 77 + graphs, num_sets=7, per_set=3)
+    if relabelled:                                           # the tensors of every graph in another order
+        rng = np.random.default_rng(graphs)
+        off = g.graph_tensor_offsets
+        new = np.concatenate([lo + rng.permutation(hi - lo) for lo, hi in zip(off[:-1], off[1:])]).astype(np.int32)
+        g = gg.Graph(g.num_ops, g.num_tensors, g.in_op, new[g.in_tensor], g.out_op, new[g.out_tensor], g.num_graphs, g.graph_op_offsets, off, "relabelled")
+        tg = gg.Targets(tg.num_sets, tg.tgt_rowptr, new[tg.tgt_idx])
+    adj, ref = oracle_prune(oracle, g, tg)
+    dg = dgn.DeviceGraph.from_coo(g)
+    buf = dgn.PruneBuffers(dg, 7)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    assert buf.prune(up(tg.tgt_rowptr), up(tg.tgt_idx), options=dgn.dgn_options(traversal=1)) == 0
+    assert_same(buf.to_host(), ref, "levels")
+    ip, ro = dgn.InplaceBuffers(dg), dgn.ReadoutBuffers(buf)
+    want = oracle.inplace(adj, ref.op_mask, (1 << 64) - 1)
+    for how in ({}, {"kept_ops": buf.kept_ops, "kept_count": buf.kept_count}):
+        assert ip.run(buf.op_mask, **how) == 0
+        assert np.array_equal(ip.rename.cpu().numpy(), want), f"in-place {list(how)}"
+    assert ro.ignore() == 0
+    assert np.array_equal(ro.ignore_mask.cpu().numpy().view(np.uint64), oracle.ignore_mask(adj, ref.op_mask, ref.tensor_mask))
