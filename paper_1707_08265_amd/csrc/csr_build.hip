@@ -578,14 +578,19 @@ static int record_blocks(int64_t num_ops) { return (int)(num_ops + 255 < (int64_
 
 // The outputs have turned out not to be one run of tensors: producer words that the pass over them left out, taking it for one.  Where no
 // tensor has several producers those are the last ones of the list (a list without gaps from somewhere on); else any whose place says so.
+// Where they begin is a chain of reads that every wave waits for: 64 places at a time, 3 reads instead of 18 (200 000 operators, an
+// input tensor every 64: the build 53.9 -> 51.9 us; 5 M 189 -> 186).  A whole wave comes here.
 __device__ __forceinline__ void fill_spared_words(const GraphView &g, int32_t *prod1, const int32_t *status, int64_t gtid, int64_t gsize)
 {
     if (!prod1 || !adjacency_ready(status, true)) return;
     const int32_t shift = g.num_tensors - g.nnz_out;
-    int32_t lo = max(0, -shift), hi = g.nnz_out;
-    while (status[kStatusMulti] == 0 && hi > lo) {          // first position e whose tensor is e + shift
-        const int32_t mid = lo + (hi - lo) / 2;
-        if (g.prod_rowptr[mid + shift] == mid) hi = mid; else lo = mid + 1;
+    int64_t lo = max(0, -shift), hi = g.nnz_out;
+    while (status[kStatusMulti] == 0 && hi > lo) {          // first position e whose tensor is e + shift: 64 looks at a time
+        const int64_t step = (hi - lo + kWave) / kWave;     // (the last look is at hi or behind it)
+        const int64_t at = lo + (lane_id() + 1) * step - 1;
+        const int c = __ffsll((unsigned long long)__ballot(at >= hi || g.prod_rowptr[at + shift] == at)) - 1;
+        hi = min(hi, lo + (c + 1) * step - 1);
+        lo += c * step;
     }
     for (int64_t e = lo + gtid; e < g.nnz_out; e += gsize)
         if (g.prod_rowptr[e + shift] == e && g.prod_rowptr[e + shift + 1] == e + 1) prod1[e + shift] = g.prod_idx[e];

@@ -78,7 +78,7 @@ def test_lists_in_order(dgn, oracle, shape, several):
 
 
 @pytest.mark.parametrize("several", [None, "first", "last", "all"])
-@pytest.mark.parametrize("writers,at", [(9, 4), (1025, 1), (4096, 4093), (5003, 1024), (140_000, 69_999), (140_001, 3)])
+@pytest.mark.parametrize("writers,at", [(9, 4), (63, 62), (64, 1), (65, 64), (1025, 1), (4096, 4093), (5003, 1024), (140_000, 69_999), (140_001, 3)])
 def test_outputs_in_two_runs(dgn, oracle, writers, at, several):
     """One hole in the numbering: producer words that the pass over the outputs has left out for what it took for one run, up to
     the last tensor, are filled in; with tensors of several producers before or behind the hole, also more outputs than tensors."""
