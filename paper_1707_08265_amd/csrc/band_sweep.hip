@@ -49,6 +49,9 @@ constexpr int kBandFewSteps = 64, kBandMeanOps = 24;          // any graph in so
 constexpr int kBandHeld = 4;                        // targets of sixteen sets that a thread keeps
 static_assert(kBandMaxTargets <= kBandHeld * kBandHalf, "all of a call in one workgroup");
 constexpr int kBandAhead = 8;                      // steps that loads are ahead
+// Slots are used again.  Those of a step's tensors are zero two barriers behind the step that follows it: from the third step on for operators,
+// which reach s_dist below the end of theirs (k_band_sweep asks for s_dist and four spans), and for target bits, put in place two steps ahead, here:
+static_assert(5 * kBandStepOuts <= kBandRing, "target bits go into slots that are zero");
 static_assert(kBandPad >= 3 * kBandAhead + 6, "bounds are read so far behind the last step");
 
 constexpr int kEntryBytes = 12;
@@ -475,9 +478,11 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
             flush_from = y;
             flush_slot -= (uint32_t)tensors;                // (below zero: past the highest number)
             flush_slot = min(flush_slot, flush_slot + (uint32_t)kBandRing);
-            // (LDS operations of a wave complete in order, and `next` has arrived: the zeros that were stored and the target bits of two steps
-            // ahead are in place before this wave's next barrier, which is soon enough for both)
-            asm volatile("" ::: "memory");
+            // What this step has stored, zeros and the target bits of two steps ahead, must be in place at this wave's next barrier, not at this one.
+            // LDS operations of a wave complete in order, so that it is enough if a read that follows the stores of the step before has
+            // arrived here: `next`.  The asm takes it, which keeps the wait for it in front of the barrier.  (As compiled it is a wait for all of
+            // them, or with target bits from M for all but one: branches with and without stores meet here.)
+            asm volatile("; bound of the next step: %0" :: "s"(y) : "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
         };
