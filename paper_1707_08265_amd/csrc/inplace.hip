@@ -56,10 +56,11 @@ __global__ __launch_bounds__(kIpFillThreads) void k_inplace_init(int32_t *rename
 
 // The claimed nodes of a workgroup are gathered in LDS, so that the list's counter in memory is bumped once per workgroup and
 // step, not once per wave (updates of one address take 11 ns each: a wave each would cost more than the pass itself).
-constexpr int kClaimCap = 2048;
+// What finds no room goes to the list one wave at a time, so the room is for what a step of most graphs claims.
 struct ClaimStage {
-    int32_t *buf;                                   // [kClaimCap]
-    int *count;                                     // claims of the workgroup since the last flush; past kClaimCap they
+    int32_t *buf;                                   // [room]
+    int room;
+    int *count;                                     // claims of the workgroup since the last flush; past the room they
                                                     // went to the list one by one
     int32_t *list;
     int32_t *list_count;
@@ -127,13 +128,13 @@ __device__ __forceinline__ void offer_children(const GraphView &g, bool valid, i
             int base = 0;
             if (lane == 0) base = atomicAdd(cs.count, __popcll(cm));
             const int pos = __builtin_amdgcn_readfirstlane(base) + __popcll(cm & lanemask_lt());
-            if (claimed && pos < kClaimCap) cs.buf[pos] = x;
-            const u64 om = ballot64(claimed && pos >= kClaimCap);
+            if (claimed && pos < cs.room) cs.buf[pos] = x;
+            const u64 om = ballot64(claimed && pos >= cs.room);
             if (om) {                                       // no room any more: straight into the list
                 int at = 0;
                 if (lane == 0) at = atomicAdd(cs.list_count, __popcll(om));
                 at = __builtin_amdgcn_readfirstlane(at);
-                if (claimed && pos >= kClaimCap) cs.list[at + __popcll(om & lanemask_lt())] = x;
+                if (claimed && pos >= cs.room) cs.list[at + __popcll(om & lanemask_lt())] = x;
             }
         }
     }
@@ -144,9 +145,9 @@ __device__ __forceinline__ void offer_children(const GraphView &g, bool valid, i
 __device__ __forceinline__ void flush_claims(const ClaimStage &cs, int *s_base, bool last)
 {
     __syncthreads();
-    const int n = min(*cs.count, kClaimCap);
+    const int n = min(*cs.count, cs.room);
     __syncthreads();                                        // everyone has read the count before it changes again
-    if (n == 0 || (n <= kClaimCap / 2 && !last)) return;    // the same in every thread
+    if (n == 0 || (n <= cs.room / 2 && !last)) return;    // the same in every thread
     if (threadIdx.x == 0) {
         *s_base = atomicAdd(cs.list_count, n);
         *cs.count = 0;
@@ -159,28 +160,33 @@ __device__ __forceinline__ void flush_claims(const ClaimStage &cs, int *s_base, 
 // Surviving operators can be a few percent of all: a wave reads 512 masks, packs the ids of the
 // survivors into LDS and works on them 64 at a time, so that the dependent loads of the expansion
 // run with all lanes busy.
-constexpr int kIpThreads = 1024;
-constexpr int kIpWaves = kIpThreads / kWave;
+//   Workgroups of 256 threads, with room for a claim per operator of a step; in one of 1 024, with room for every second, waves wait for each other and
+// claims go to the list one wave at a time (4 096 graphs of 20 000, 49 M kept: 4.59 ms, 3.81 so; with half that room 7.41.  256 of 20 000: 312 us, 275;
+// 50 M of a power law 455, 404; 800 000 in layers 155, 120).  Not for chains, whose operators read the same few graph inputs: the more waves
+// go side by side, the more of them meet there (an RNN of 1 M: 176 us, with small workgroups 213; 200 000: 129, 133).
 constexpr int kMaskRounds = 8;                      // masks per lane and step
+constexpr int kMaskThreads = 256, kChainThreads = 1024;
+__host__ __device__ constexpr int mask_room(int threads) { return threads == kChainThreads ? 4096 : threads * kMaskRounds; }
 
-template <RowForm kForm>
-__global__ __launch_bounds__(kIpThreads) void k_inplace_children(GraphView g, const u64 *K, u64 select, int32_t *rename,
+template <RowForm kForm, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_inplace_children(GraphView g, const u64 *K, u64 select, int32_t *rename,
                                                                   int32_t *child, int32_t *list, int32_t *list_count)
 {
-    __shared__ int32_t s_ops[kIpWaves][kWave * (kMaskRounds + 1)];
-    __shared__ int32_t s_claims[kClaimCap];
-    __shared__ int s_mark[kIpWaves][kWave];
+    constexpr int kWaves = kThreads / kWave, kRoom = mask_room(kThreads);
+    __shared__ int32_t s_ops[kWaves][kWave * (kMaskRounds + 1)];
+    __shared__ int32_t s_claims[kRoom];
+    __shared__ int s_mark[kWaves][kWave];
     __shared__ int s_count, s_base;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     if (threadIdx.x == 0) s_count = 0;
     __syncthreads();
-    const ClaimStage cs{s_claims, &s_count, list, list_count};
+    const ClaimStage cs{s_claims, kRoom, &s_count, list, list_count};
     int32_t *ops = s_ops[wave];
     int count = 0;                                          // wave-uniform
     const int64_t step = (int64_t)kWave * kMaskRounds;
     const int64_t steps = ((int64_t)g.num_ops + step - 1) / step;
-    const int64_t num_waves = (int64_t)gridDim.x * kIpWaves;
-    for (int64_t st0 = (int64_t)blockIdx.x * kIpWaves; st0 < steps; st0 += num_waves) {      // whole workgroups stay in the loop
+    const int64_t num_waves = (int64_t)gridDim.x * kWaves;
+    for (int64_t st0 = (int64_t)blockIdx.x * kWaves; st0 < steps; st0 += num_waves) {      // whole workgroups stay in the loop
         const int64_t st = st0 + wave;
         u64 k[kMaskRounds];
 #pragma unroll
@@ -213,19 +219,19 @@ __global__ __launch_bounds__(kIpThreads) void k_inplace_children(GraphView g, co
 // a pruned graph is a few percent of the recorded one, and the list spares the pass over all of K.  An entry
 // whose mask misses `select` is skipped.  Workgroups are small, so that their number, not that of the workgroups on the chip, decides how long the
 // last ones take (1.1 M operators with 2.8 M inputs: 190 us in workgroups of 1 024 threads, two and a little each, now 174).
-constexpr int kListThreads = 256, kListWaves = kListThreads / kWave;
+constexpr int kListThreads = 256, kListWaves = kListThreads / kWave, kListRoom = 2048;
 template <RowForm kForm>
 __global__ __launch_bounds__(kListThreads) void k_inplace_children_list(GraphView g, const u64 *K, u64 select,
                                                                        const int32_t *kept_ops, const int64_t *kept_count,
                                                                        int32_t *rename, int32_t *child, int32_t *list,
                                                                        int32_t *list_count)
 {
-    __shared__ int32_t s_claims[kClaimCap];
+    __shared__ int32_t s_claims[kListRoom];
     __shared__ int s_mark[kListWaves][kWave];
     __shared__ int s_count, s_base;
     if (threadIdx.x == 0) s_count = 0;
     __syncthreads();
-    const ClaimStage cs{s_claims, &s_count, list, list_count};
+    const ClaimStage cs{s_claims, kListRoom, &s_count, list, list_count};
     const int64_t kept = kept_count[0];
     const int64_t gsize = (int64_t)gridDim.x * kListThreads;
     for (int64_t base = (int64_t)blockIdx.x * kListThreads; base < kept; base += gsize) {       // whole workgroups stay in the loop
@@ -237,6 +243,8 @@ __global__ __launch_bounds__(kListThreads) void k_inplace_children_list(GraphVie
     }
     flush_claims(cs, &s_base, true);
 }
+
+constexpr int kIpThreads = 1024;
 
 // One doubling round over the claimed nodes.  J_0 is the child word itself (below zero: no link); the later pointers are
 // kept for claimed nodes only, and child tells whether a node has one.  active[-1]: the round before left a pointer
@@ -302,24 +310,26 @@ InplaceBuffers inplace_buffers(void *scratch, int64_t T)
 
 hipError_t launch_inplace_setup(const GraphView &g, const u64 *K, u64 select, const int32_t *kept_ops,
                                 const int64_t *kept_count, int32_t *rename, int64_t *renamed_count,
-                                const InplaceBuffers &b, int grid_blocks, hipStream_t s)
+                                const InplaceBuffers &b, bool chains, int grid_blocks, hipStream_t s)
 {
     const int64_t T = g.num_tensors, P = g.num_ops;
-    // a thread per 16 bytes and array; the other passes: two workgroups of 1 024 threads per compute unit
+    // fills: a thread per 16 bytes and array; the other passes: as many threads as the chip holds
     const int64_t nb = (T + kIpFillThreads * 4 - 1) / (kIpFillThreads * 4);
     hipLaunchKernelGGL(k_inplace_init, dim3((unsigned)(nb < 1 ? 1 : nb)), dim3(kIpFillThreads), 0, s, rename, b.child, T, b.counters,
                        kInplaceMaxRounds + 1, renamed_count);
-    int64_t blocks = (P + kIpThreads - 1) / kIpThreads;
-    if (blocks > grid_blocks / 4) blocks = grid_blocks / 4;
     const RowForm rows = rows_of(g);
-    int64_t list_blocks = (P + kListThreads - 1) / kListThreads;
-    if (list_blocks > grid_blocks) list_blocks = grid_blocks;
-    if (P > 0 && kept_ops)
-        hipLaunchKernelGGL(rows == kRun ? k_inplace_children_list<kRun> : rows == kRecords ? k_inplace_children_list<kRecords> : k_inplace_children_list<kFirst>, dim3((unsigned)list_blocks), dim3(kListThreads), 0, s, g, K, select,
-                           kept_ops, kept_count, rename, b.child, b.list, b.counters);
-    else if (P > 0)
-        hipLaunchKernelGGL(rows == kRun ? k_inplace_children<kRun> : rows == kRecords ? k_inplace_children<kRecords> : k_inplace_children<kFirst>, dim3((unsigned)blocks), dim3(kIpThreads), 0, s, g, K, select, rename, b.child,
-                           b.list, b.counters);
+    const int threads = kept_ops ? kListThreads : chains ? kChainThreads : kMaskThreads;
+    int64_t blocks = (P + threads - 1) / threads;
+    if (blocks > grid_blocks * 256 / threads) blocks = grid_blocks * 256 / threads;
+    if (P > 0 && kept_ops) {
+        auto k = rows == kRun ? k_inplace_children_list<kRun> : rows == kRecords ? k_inplace_children_list<kRecords> : k_inplace_children_list<kFirst>;
+        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(threads), 0, s, g, K, select, kept_ops, kept_count, rename, b.child, b.list, b.counters);
+    } else if (P > 0) {
+        auto k = rows == kRun       ? chains ? k_inplace_children<kRun, kChainThreads> : k_inplace_children<kRun, kMaskThreads>
+                 : rows == kRecords ? chains ? k_inplace_children<kRecords, kChainThreads> : k_inplace_children<kRecords, kMaskThreads>
+                                    : k_inplace_children<kFirst, kMaskThreads>;            // (batches)
+        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(threads), 0, s, g, K, select, rename, b.child, b.list, b.counters);
+    }
     return hipGetLastError();
 }
 

@@ -116,6 +116,26 @@ def test_long_chain_needs_logarithmic_rounds(dgn, oracle):
     assert count == 0
 
 
+@pytest.mark.parametrize("reads", ["before", "far"])
+@pytest.mark.parametrize("ops", [1, 63, 2047, 2049, 8193, 40_000, 140_001])
+def test_more_nodes_than_a_workgroup_has_room_for(dgn, oracle, ops, reads):
+    """Three inputs of its own for every operator, each a node with one child, after one that was written just before (chains) or anywhere:
+    a step claims several times what its workgroup has room for, in small and in large workgroups."""
+    rng = np.random.default_rng(ops)
+    o = np.arange(ops)
+    low = 3 * ops + 1                                        # graph inputs
+    far = (low + rng.random(ops) * o).astype(np.int64)
+    first = np.where(o == 0, low - 1, low + o - 1 if reads == "before" else np.minimum(far, low + np.maximum(o - 1, 0)))
+    i32 = lambda a: np.ascontiguousarray(a, dtype=np.int32)  # noqa: E731
+    in_t = np.stack([first, 3 * o, 3 * o + 1, 3 * o + 2], axis=1).reshape(-1)
+    g = gg.Graph(ops, low + ops, i32(np.repeat(o, 4)), i32(in_t), i32(o), i32(low + o), name="private inputs")
+    dg = dgn.DeviceGraph.from_coo(g)
+    adj, buf = _adj(oracle, g), dgn.InplaceBuffers(dg)
+    for K in (np.ones(ops, np.uint64), rng.integers(0, 2, ops).astype(np.uint64)):
+        rd, count, _ = gpu_inplace(dgn, dg, K, buf=buf)
+        check(rd, count, oracle.inplace(adj, K, ALL), f"{ops} {reads}")
+
+
 def test_nothing_kept_and_empty_graph(dgn):
     g, _ = gg.config(0, 1.0)
     dg = dgn.DeviceGraph.from_coo(g)
