@@ -117,7 +117,7 @@ def test_long_chain_needs_logarithmic_rounds(dgn, oracle):
 
 
 @pytest.mark.parametrize("reads", ["before", "far"])
-@pytest.mark.parametrize("ops", [1, 63, 2047, 2049, 8193, 40_000, 140_001])
+@pytest.mark.parametrize("ops", [1, 63, 2047, 2049, 8193, 40_000, 131_071, 131_072, 140_001])
 def test_more_nodes_than_a_workgroup_has_room_for(dgn, oracle, ops, reads):
     """Three inputs of its own for every operator, each a node with one child, after one that was written just before (chains) or anywhere:
     a step claims several times what its workgroup has room for, in small and in large workgroups."""
@@ -134,6 +134,18 @@ def test_more_nodes_than_a_workgroup_has_room_for(dgn, oracle, ops, reads):
     for K in (np.ones(ops, np.uint64), rng.integers(0, 2, ops).astype(np.uint64)):
         rd, count, _ = gpu_inplace(dgn, dg, K, buf=buf)
         check(rd, count, oracle.inplace(adj, K, ALL), f"{ops} {reads}")
+
+
+@pytest.mark.parametrize("ops", [16_383, 16_384, 16_400])
+def test_long_lists_of_batches(dgn, oracle, ops):
+    """Batches with as many kept operators as a wave takes more of one after the other, and with one graph less."""
+    g, _ = gg.batch_layered(64, ops, ops, num_sets=1, per_set=1)
+    dg = dgn.DeviceGraph.from_coo(g)
+    adj, buf = _adj(oracle, g), dgn.InplaceBuffers(dg)
+    K = np.ones(g.num_ops, np.uint64)
+    for k in (K, np.where(np.arange(g.num_ops) < ops, 0, K)):
+        rd, count, _ = gpu_inplace(dgn, dg, k, buf=buf)
+        check(rd, count, oracle.inplace(adj, k, ALL), f"{ops}")
 
 
 def test_nothing_kept_and_empty_graph(dgn):
