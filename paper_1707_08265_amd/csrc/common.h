@@ -35,7 +35,7 @@ struct GraphView {
     // What the traversal reads per operator and per pushed tensor (see traverse.hip).  Of graphs whose outputs are one run of tensors
     // (run_shift >= 0) it follows from the adjacency, and these two are not written.
     const int4 *orec;                 // [P] operator record (first input edge, fan-in, outputs); NULL: by rows and ofirst
-    const int32_t *ofirst;            // [P] batches that are swept: the first output, if an operator's outputs are consecutive, else -1
+    const int32_t *ofirst;            // [P] batches that are swept (is_swept in api.hip): the first output, if an operator's outputs are consecutive, else -1
     const int32_t *prod1;             // [T] the producer of a tensor, or kMulti / kNoProducer
     // >= 0: the outputs of operator o are the tensors out_rowptr[o] + run_shift .. out_rowptr[o + 1] + run_shift - 1 (in any order
     // inside its row), each written by nobody else, so that tensor t is written by prod_idx[t - run_shift]; -1: not so

@@ -457,3 +457,46 @@ def test_batches_around_the_number_that_have_no_records(dgn, oracle, graphs, rel
         assert np.array_equal(ip.rename.cpu().numpy(), want), f"in-place {list(how)}"
     assert ro.ignore() == 0
     assert np.array_equal(ro.ignore_mask.cpu().numpy().view(np.uint64), oracle.ignore_mask(adj, ref.op_mask, ref.tensor_mask))
+
+
+@pytest.mark.parametrize("largest", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1])
+@pytest.mark.parametrize("relabelled", [False, True])
+def test_batches_with_a_graph_around_the_largest_that_is_swept(dgn, oracle, largest, relabelled):
+    """A batch of 64 graphs goes level by level, with operator records, if one of them is larger than that, and is swept, without, if none is; both
+    ways the prune that nobody asks for levels, the in-place pass and the ignore mask agree with the oracle."""
+    import torch
+    rng = np.random.default_rng(largest + relabelled)
+    sizes = rng.integers(1, 60, 64)
+    sizes[rng.integers(0, 64)] = largest
+    P, off = int(sizes.sum()), np.concatenate([[0], np.cumsum(sizes)])
+    of = np.repeat(np.arange(64), sizes)
+    n_out, fan = rng.integers(1, 3, P), rng.integers(1, 4, P)
+    first = np.concatenate([[0], np.cumsum(n_out)])[:-1] + 3 * (of + 1)       # three inputs per graph in front of its outputs
+    T = int(n_out.sum()) + 3 * 64
+    t_off = np.concatenate([first[off[:-1]] - 3, [T]]).astype(np.int64)
+    in_op, out_op = np.repeat(np.arange(P), fan), np.repeat(np.arange(P), n_out)
+    back = np.minimum(first[in_op] - t_off[of[in_op]], 300)                   # outputs of the last few operators, or the inputs
+    in_t = first[in_op] - 1 - (rng.random(in_op.size) * back).astype(np.int64)
+    out_t = first[out_op] + np.concatenate([np.arange(n) for n in n_out])
+    new = np.arange(T)
+    if relabelled:
+        new = np.concatenate([lo + rng.permutation(hi - lo) for lo, hi in zip(t_off[:-1], t_off[1:])])
+    i32 = lambda a: np.ascontiguousarray(a, dtype=np.int32)  # noqa: E731
+    g = gg.Graph(P, T, i32(in_op), i32(new[in_t]), i32(out_op), i32(new[out_t]), 64, off.astype(np.int64), t_off, "one large")
+    sets = [[int(new[hi - 1 - rng.integers(0, min(hi - lo, 20))])] for lo, hi in zip(t_off[:-1], t_off[1:]) for _ in range(3)]
+    tg = gg.Targets(3, i32(np.arange(len(sets) + 1)), i32(np.concatenate(sets)))
+    adj, ref = oracle_prune(oracle, g, tg)
+    dg = dgn.DeviceGraph.from_coo(g)
+    buf, st = dgn.PruneBuffers(dg, 3), dgn.dgn_stats()
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    for call in range(2):
+        assert buf.prune(up(tg.tgt_rowptr), up(tg.tgt_idx), stats=st) == 0
+        assert_same(buf.to_host(), ref, f"call {call}")
+        assert (st.levels > 1) == (largest > 1 << 18), st.levels
+    ip, ro = dgn.InplaceBuffers(dg), dgn.ReadoutBuffers(buf)
+    want = oracle.inplace(adj, ref.op_mask, (1 << 64) - 1)
+    for how in ({}, {"kept_ops": buf.kept_ops, "kept_count": buf.kept_count}):
+        assert ip.run(buf.op_mask, **how) == 0
+        assert np.array_equal(ip.rename.cpu().numpy(), want), f"in-place {list(how)}"
+    assert ro.ignore() == 0
+    assert np.array_equal(ro.ignore_mask.cpu().numpy().view(np.uint64), oracle.ignore_mask(adj, ref.op_mask, ref.tensor_mask))
