@@ -132,15 +132,34 @@ int check_sizes(int64_t P, int64_t T, int64_t Ein, int64_t Eout, int32_t G, cons
     return DGN_OK;
 }
 
+// Operators of the largest graph.
+int64_t largest_graph(int64_t P, int32_t G, const int64_t *op_off)
+{
+    if (G == 1) return P;
+    int64_t most = 0;
+    for (int32_t i = 0; i < G; ++i) most = op_off[i + 1] - op_off[i] > most ? op_off[i + 1] - op_off[i] : most;
+    return most;
+}
+
+// Batches that are swept have no records: what goes operator by operator over such a batch takes its rows, and from 4 instead of 16 bytes per
+// operator which tensors it writes.  (4 096 graphs of 20 000: records and check 741 us with records, 600 so.)  A batch with a larger graph than
+// that goes level by level, and has them (64 graphs of 300 000, 64 sets: prune 36.05 ms with records, 36.35 without, build 483 us, 449).  Levels of a swept batch,
+// where an option asks for them or its operators are in no topological order, do without (4 096 graphs of 20 000: 52.6 ms / 54.4, the
+// sweep takes 1.1; 64 in reverse order 1.89 / 1.94, 256 3.10 / 3.10 and their build 797 us / 785).
+bool is_swept(int32_t G, int64_t max_graph_ops) { return G >= kSweepMinGraphs && max_graph_ops <= kSweepMaxGraphOps; }
+static_assert(kRingMaxGraphOps <= kSweepMaxGraphOps, "what takes either sweep has no records");
+
 struct GraphLayout {
     int32_t *in_rowptr, *in_idx, *out_rowptr, *out_idx, *prod_rowptr, *prod_idx;
-    int4 *orec;
+    int4 *orec;             // NULL: a batch that is swept, which has ...
+    int32_t *ofirst;        // ... these
     int32_t *prod1;
     int64_t *op_off, *t_off;
+    int64_t max_graph_ops;
     size_t bytes;
 };
 
-GraphLayout graph_layout(void *mem, int64_t P, int64_t T, int64_t Ein, int64_t Eout, int32_t G, bool own_op_csr)
+GraphLayout graph_layout(void *mem, int64_t P, int64_t T, int64_t Ein, int64_t Eout, int32_t G, const int64_t *op_off, bool own_op_csr)
 {
     Carver c(mem);
     GraphLayout L{};
@@ -152,7 +171,9 @@ GraphLayout graph_layout(void *mem, int64_t P, int64_t T, int64_t Ein, int64_t E
     }
     L.prod_rowptr = c.take<int32_t>(T + 1);
     L.prod_idx = c.take<int32_t>(Eout);
-    L.orec = c.take<int4>(P);
+    L.max_graph_ops = largest_graph(P, G, op_off);
+    if (is_swept(G, L.max_graph_ops)) L.ofirst = c.take<int32_t>(P);
+    else L.orec = c.take<int4>(P);
     L.prod1 = c.take<int32_t>(T);
     if (G > 1) {
         L.op_off = c.take<int64_t>(G + 1);
@@ -412,36 +433,13 @@ bool walked(const dgn_graph *h) { return h->G > 1 || h->P <= kRingMaxOps; }
 // ever are: its graphs have inputs of their own.
 bool may_run(const dgn_graph *h) { return h->G == 1; }
 
-// Operators of the largest graph.
-int64_t largest_graph(int64_t P, int32_t G, const int64_t *op_off)
-{
-    if (G == 1) return P;
-    int64_t most = 0;
-    for (int32_t i = 0; i < G; ++i) most = op_off[i + 1] - op_off[i] > most ? op_off[i + 1] - op_off[i] : most;
-    return most;
-}
-
-// Batches that are swept have no records: what goes operator by operator over such a batch takes its rows, and from 4 instead of 16 bytes per
-// operator which tensors it writes.  (4 096 graphs of 20 000: records and check 741 us with records, 600 so.)  A batch with a larger graph than
-// that goes level by level, and has them (64 graphs of 300 000, 64 sets: prune 36.05 ms with records, 36.35 without, build 483 us, 449).  Levels of a swept batch,
-// where an option asks for them or its operators are in no topological order, do without (4 096 graphs of 20 000: 52.6 ms / 54.4, the
-// sweep takes 1.1; 64 in reverse order 1.89 / 1.94, 256 3.10 / 3.10 and their build 797 us / 785).
-bool is_swept(int32_t G, int64_t max_graph_ops) { return G >= kSweepMinGraphs && max_graph_ops <= kSweepMaxGraphOps; }
-static_assert(kRingMaxGraphOps <= kSweepMaxGraphOps, "what takes either sweep has no records");
-
-void place_records(dgn_graph *h, const GraphLayout &L)
-{
-    if (!is_swept(h->G, h->max_graph_ops)) h->v.orec = L.orec;
-    else h->v.ofirst = reinterpret_cast<int32_t *>(L.orec);
-}
-
 // What follows the adjacency.  The kernels find out by themselves whether there is one yet.  words: all producer words are there; none: the
 // outputs are one run, or there is no adjacency yet, so that there are no records to be made.
 int enqueue_records(const dgn_graph *h, const GraphLayout &L, int32_t *status, const dgn_options *options, hipStream_t s, bool words, bool none = false)
 {
     int32_t *spared = may_run(h) && !words ? L.prod1 : nullptr;
     if (walked(h)) {
-        DGN_HIP(launch_records_and_check(h->v, const_cast<int4 *>(h->v.orec), const_cast<int32_t *>(h->v.ofirst), spared, status, h->num_cus, s));
+        DGN_HIP(launch_records_and_check(h->v, L.orec, L.ofirst, spared, status, h->num_cus, s));
     } else {
         if (none) DGN_HIP(launch_sample_reach(h->v, status, s));
         else DGN_HIP(launch_build_records(h->v, L.orec, spared, status, s));
@@ -675,7 +673,7 @@ int dgn_graph_build_workspace(const dgn_coo_desc *d, size_t *graph_bytes, size_t
     int rc = check_sizes(d->num_ops, d->num_tensors, d->nnz_in, d->nnz_out, d->num_graphs, d->graph_op_offsets,
                          d->graph_tensor_offsets);
     if (rc) return rc;
-    *graph_bytes = graph_layout(nullptr, d->num_ops, d->num_tensors, d->nnz_in, d->nnz_out, d->num_graphs, true).bytes;
+    *graph_bytes = graph_layout(nullptr, d->num_ops, d->num_tensors, d->nnz_in, d->nnz_out, d->num_graphs, d->graph_op_offsets, true).bytes;
     *scratch_bytes = build_scratch(nullptr, d->nnz_in, d->nnz_out).bytes;
     return DGN_OK;
 }
@@ -698,7 +696,7 @@ int dgn_graph_build(const dgn_coo_desc *d, void *graph_mem, size_t graph_bytes, 
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t P = d->num_ops, T = d->num_tensors, Ein = d->nnz_in, Eout = d->nnz_out;
-    const GraphLayout L = graph_layout(graph_mem, P, T, Ein, Eout, d->num_graphs, true);
+    const GraphLayout L = graph_layout(graph_mem, P, T, Ein, Eout, d->num_graphs, d->graph_op_offsets, true);
     const BuildScratch S = build_scratch(scratch, Ein, Eout);
 
     dgn_graph *h = nullptr;
@@ -706,9 +704,8 @@ int dgn_graph_build(const dgn_coo_desc *d, void *graph_mem, size_t graph_bytes, 
     if (rc) return rc;
     h->P = P; h->T = T; h->Ein = Ein; h->Eout = Eout; h->G = d->num_graphs;
     h->v = GraphView{(int32_t)P, (int32_t)T, (int32_t)Ein, (int32_t)Eout, d->num_graphs, L.in_rowptr, L.in_idx,
-                     L.out_rowptr, L.out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, nullptr, nullptr, L.prod1, -1};
-    h->max_graph_ops = largest_graph(P, d->num_graphs, d->graph_op_offsets);
-    place_records(h, L);
+                     L.out_rowptr, L.out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.ofirst, L.prod1, -1};
+    h->max_graph_ops = L.max_graph_ops;
     const int32_t *found = nullptr;
     rc = build_from_lists(h, d, L, S, options, s, &found);
     if (!rc) rc = finish_build(h, d->graph_op_offsets, d->graph_tensor_offsets, S.status, found, options, s, out);
@@ -722,7 +719,7 @@ int dgn_graph_from_csr_workspace(const dgn_csr_desc *d, size_t *graph_bytes, siz
     int rc = check_sizes(d->num_ops, d->num_tensors, d->nnz_in, d->nnz_out, d->num_graphs, d->graph_op_offsets,
                          d->graph_tensor_offsets);
     if (rc) return rc;
-    *graph_bytes = graph_layout(nullptr, d->num_ops, d->num_tensors, d->nnz_in, d->nnz_out, d->num_graphs, false).bytes;
+    *graph_bytes = graph_layout(nullptr, d->num_ops, d->num_tensors, d->nnz_in, d->nnz_out, d->num_graphs, d->graph_op_offsets, false).bytes;
     *scratch_bytes = build_scratch(nullptr, d->nnz_in, d->nnz_out).bytes;
     return DGN_OK;
 }
@@ -744,7 +741,7 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t P = d->num_ops, T = d->num_tensors, Ein = d->nnz_in, Eout = d->nnz_out;
-    const GraphLayout L = graph_layout(graph_mem, P, T, Ein, Eout, d->num_graphs, false);
+    const GraphLayout L = graph_layout(graph_mem, P, T, Ein, Eout, d->num_graphs, d->graph_op_offsets, false);
     const BuildScratch S = build_scratch(scratch, Ein, Eout);
 
     dgn_graph *h = nullptr;
@@ -752,9 +749,8 @@ int dgn_graph_from_csr(const dgn_csr_desc *d, void *graph_mem, size_t graph_byte
     if (rc) return rc;
     h->P = P; h->T = T; h->Ein = Ein; h->Eout = Eout; h->G = d->num_graphs;
     h->v = GraphView{(int32_t)P, (int32_t)T, (int32_t)Ein, (int32_t)Eout, d->num_graphs, d->in_rowptr, d->in_idx,
-                     d->out_rowptr, d->out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, nullptr, nullptr, L.prod1, -1};
-    h->max_graph_ops = largest_graph(P, d->num_graphs, d->graph_op_offsets);
-    place_records(h, L);
+                     d->out_rowptr, d->out_idx, L.prod_rowptr, L.prod_idx, nullptr, nullptr, L.orec, L.ofirst, L.prod1, -1};
+    h->max_graph_ops = L.max_graph_ops;
     const int32_t *found = nullptr;
     auto fill = [&]() -> int {
         FillRegion clr[1] = {{S.status, 256}};

@@ -161,7 +161,7 @@ __device__ __forceinline__ void flush_claims(const ClaimStage &cs, int *s_base, 
 // survivors into LDS and works on them 64 at a time, so that the dependent loads of the expansion
 // run with all lanes busy.
 //   Workgroups of 256 threads, with room for a claim per operator of a step; in one of 1 024, with room for every second, waves wait for each other and
-// claims go to the list one wave at a time (4 096 graphs of 20 000, 49 M kept: 4.59 ms, 3.81 so; with half that room 7.41.  256 of 20 000: 312 us, 275;
+// claims go to the list one wave at a time (4 096 graphs of 20 000, 49 M kept: 4.59 ms, 3.84 to 4.14 so; with half the large ones' room 7.41.  256 of 20 000: 312 us, 275;
 // 50 M of a power law 455, 404; 800 000 in layers 155, 120).  Not for chains, whose operators read the same few graph inputs: the more waves
 // go side by side, the more of them meet there (an RNN of 1 M: 176 us, with small workgroups 213; 200 000: 129, 133).
 constexpr int kMaskRounds = 8;                      // masks per lane and step

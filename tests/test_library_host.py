@@ -62,6 +62,13 @@ def test_workspace_queries_validate_sizes(d):
     rc1, g1, s1 = d.dgn_graph_build_workspace(mk())
     rc2, g2, s2 = d.dgn_graph_build_workspace(mk(P=1000, T=2000, ein=3000, eout=1500))
     assert rc1 == rc2 == 0 and g2 > g1 and s2 > s1 and g1 % 256 == 0 and s2 % 256 == 0
+    # a batch that is swept has a word per operator, not a record: 64 graphs and more, none larger than 2^18 operators
+    def batch(graphs, ops, more=0):
+        oo = np.arange(graphs + 1, dtype=np.int64) * ops
+        oo[-1] += more
+        return d.dgn_graph_build_workspace(mk(P=int(oo[-1]), T=100, G=graphs, oo=oo, to=np.linspace(0, 100, graphs + 1).astype(np.int64)))[1]
+    per_op = lambda graphs, ops, more=0: (batch(graphs, ops, more) - batch(graphs, 0)) / (graphs * ops + more)  # noqa: E731
+    assert abs(per_op(63, 1 << 18) - 24) < 0.1 and abs(per_op(64, 1 << 18) - 12) < 0.1 and abs(per_op(64, 1 << 18, 1) - 24) < 0.1
     # the bench workload fits comfortably in one GPU's memory
     rc, gb, sb = d.dgn_graph_build_workspace(mk(P=50_000_000, T=100_000_000, ein=128_700_000, eout=100_000_000))
     assert rc == 0 and gb < 4 * 2**30 and sb < 4 * 2**30
