@@ -151,7 +151,7 @@ static_assert(kRingMaxGraphOps <= kSweepMaxGraphOps, "what takes either sweep ha
 
 struct GraphLayout {
     int32_t *in_rowptr, *in_idx, *out_rowptr, *out_idx, *prod_rowptr, *prod_idx;
-    int4 *orec;             // NULL: a batch that is swept, which has ...
+    Quad *orec;             // NULL: a batch that is swept, which has ...
     int32_t *ofirst;        // ... these
     int32_t *prod1;
     int64_t *op_off, *t_off;
@@ -173,7 +173,7 @@ GraphLayout graph_layout(void *mem, int64_t P, int64_t T, int64_t Ein, int64_t E
     L.prod_idx = c.take<int32_t>(Eout);
     L.max_graph_ops = largest_graph(P, G, op_off);
     if (is_swept(G, L.max_graph_ops)) L.ofirst = c.take<int32_t>(P);
-    else L.orec = c.take<int4>(P);
+    else L.orec = c.take<Quad>(P);
     L.prod1 = c.take<int32_t>(T);
     if (G > 1) {
         L.op_off = c.take<int64_t>(G + 1);
@@ -213,7 +213,7 @@ struct PruneScratch {
     uint8_t *flagbuf;       // keep flags (a byte per operator) when the caller's op_flag cannot take them
     u64 *opbits;
     int32_t *block_counts;
-    int4 *trace;            // per-level trace records (profiling only)
+    Quad *trace;            // per-level trace records (profiling only)
     int64_t *pq_part;       // replicated per-set counters (few graphs only), NULL otherwise
     int pq_replicas;
     size_t pq_part_bytes;
@@ -222,7 +222,7 @@ struct PruneScratch {
     ColourLog log;          // tensors that prune coloured
     u64 *ring_bits;         // ring sweep: a bit per operator, running counts per word, a record per graph
     int32_t *ring_cum;
-    int4 *ring_graphs;
+    Quad *ring_graphs;
     const char *end;        // of the buffer
     size_t bytes;
 };
@@ -267,7 +267,7 @@ PruneScratch prune_scratch(void *mem, int64_t P, int64_t T, int32_t G, int64_t m
         const size_t words = (size_t)ring_bit_words(P, G);
         S.ring_bits = c.take<u64>(words);
         S.ring_cum = c.take<int32_t>(words);
-        S.ring_graphs = c.take<int4>((size_t)G + 1);
+        S.ring_graphs = c.take<Quad>((size_t)G + 1);
     }
     S.state = c.take<TravState>(2);
     S.ctr = c.take<TravCounters>(1);
@@ -283,7 +283,7 @@ PruneScratch prune_scratch(void *mem, int64_t P, int64_t T, int32_t G, int64_t m
     S.opbits = c.take<u64>(obw);
     S.opbits_bytes = obw * 8;
     S.block_counts = c.take<int32_t>((P + kCompactTile - 1) / kCompactTile + 1);
-    S.trace = c.take<int4>(kTraceLevels);
+    S.trace = c.take<Quad>(kTraceLevels);
     // with fewer than 64 graphs the 64*G per-set counters would be hot words: replicate them
     S.pq_replicas = 1;
     while (S.pq_replicas * 2 * (int64_t)G <= 64) S.pq_replicas *= 2;
@@ -303,13 +303,13 @@ int64_t words_scratch(PruneScratch &S, void *scratch, int64_t P, int64_t words)
     const size_t per = (size_t)ring_bit_words(P, 1);
     char *room = reinterpret_cast<char *>(S.ring_bits);
     const size_t bytes = S.bytes - (size_t)(room - static_cast<char *>(scratch));
-    int64_t at_once = (int64_t)((bytes - 3 * 256) / (per * (sizeof(u64) + sizeof(int32_t)) + sizeof(int4)));
+    int64_t at_once = (int64_t)((bytes - 3 * 256) / (per * (sizeof(u64) + sizeof(int32_t)) + sizeof(Quad)));
     if (at_once > words) at_once = words;
     if (at_once < 2) return 1;
     Carver c(room);
     S.ring_bits = c.take<u64>(per * (size_t)at_once);
     S.ring_cum = c.take<int32_t>(per * (size_t)at_once);
-    S.ring_graphs = c.take<int4>((size_t)at_once);
+    S.ring_graphs = c.take<Quad>((size_t)at_once);
     S.flagbuf = nullptr;
     return at_once;
 }
@@ -319,7 +319,7 @@ int64_t words_scratch(PruneScratch &S, void *scratch, int64_t P, int64_t words)
 struct Room { char *at; size_t bytes; };
 Room segments_room(const PruneScratch &S, int64_t words)
 {
-    char *at = S.flagbuf ? reinterpret_cast<char *>(S.q0) : reinterpret_cast<char *>(S.ring_graphs) + align256((size_t)words * sizeof(int4));
+    char *at = S.flagbuf ? reinterpret_cast<char *>(S.q0) : reinterpret_cast<char *>(S.ring_graphs) + align256((size_t)words * sizeof(Quad));
     const char *end = S.flagbuf ? reinterpret_cast<const char *>(S.flagbuf) : S.end;
     return {at, at < end ? (size_t)(end - at) : 0};
 }
@@ -1349,7 +1349,7 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     int launch_no = 0;
     int32_t *user_trace = stats ? stats->level_trace : nullptr;
     const int64_t user_trace_cap = stats ? stats->level_trace_cap : 0;
-    int4 *trace = (user_trace && user_trace_cap > 0) ? S.trace : nullptr;
+    Quad *trace = (user_trace && user_trace_cap > 0) ? S.trace : nullptr;
     // the stand-alone removal-rule pass rewrites K, which the traversal still needs while unfinished
     const bool speculate = !ca.from_tensor_mask;
     bool done = false, compacted = false;
@@ -1494,7 +1494,7 @@ static int prune_impl(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
             int64_t nrec = stats->levels < user_trace_cap ? stats->levels : user_trace_cap;
             if (nrec > kTraceLevels) nrec = kTraceLevels;
             if (nrec > 0) {
-                DGN_HIP(hipMemcpyAsync(user_trace, S.trace, (size_t)nrec * sizeof(int4), hipMemcpyDeviceToHost, s));
+                DGN_HIP(hipMemcpyAsync(user_trace, S.trace, (size_t)nrec * sizeof(Quad), hipMemcpyDeviceToHost, s));
                 DGN_HIP(hipStreamSynchronize(s));
             }
         }

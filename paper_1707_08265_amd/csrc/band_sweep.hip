@@ -513,7 +513,7 @@ size_t band_scratch(BandArgs &a, void *mem)
     const size_t segs = ((size_t)a.g.num_ops + kBandSegOps - 1) / kBandSegOps;
     a.entry = reinterpret_cast<uint32_t *>(take((size_t)a.g.num_ops * kEntryBytes));
     a.steps = reinterpret_cast<int2 *>(take(segs * kBandSegSteps * sizeof(int2)));
-    a.segs = reinterpret_cast<int4 *>(take(segs * sizeof(int4)));
+    a.segs = reinterpret_cast<Quad *>(take(segs * sizeof(int4)));
     return off;
 }
 

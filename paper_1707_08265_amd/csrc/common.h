@@ -23,6 +23,10 @@ enum : int32_t {
     kErrLogFull = 32,     // internal: the log of coloured tensors overflowed, the next prune clears everything
 };
 
+// Sixteen bytes in memory of the caller, who is asked for eight bytes of alignment.
+typedef int4 Quad __attribute__((aligned(8)));
+typedef uint4 UQuad __attribute__((aligned(8)));
+
 // Adjacency of a built graph as the kernels see it (device pointers).
 struct GraphView {
     int32_t num_ops, num_tensors;
@@ -34,7 +38,7 @@ struct GraphView {
     const int64_t *op_off, *t_off;    // [G+1] device copies, NULL when num_graphs == 1
     // What the traversal reads per operator and per pushed tensor (see traverse.hip).  Of graphs whose outputs are one run of tensors
     // (run_shift >= 0) it follows from the adjacency, and these two are not written.
-    const int4 *orec;                 // [P] operator record (first input edge, fan-in, outputs); NULL: by rows and ofirst
+    const Quad *orec;                 // [P] operator record (first input edge, fan-in, outputs); NULL: by rows and ofirst
     const int32_t *ofirst;            // [P] batches that are swept (is_swept in api.hip): the first output, if an operator's outputs are consecutive, else -1
     const int32_t *prod1;             // [T] the producer of a tensor, or kMulti / kNoProducer
     // >= 0: the outputs of operator o are the tensors out_rowptr[o] + run_shift .. out_rowptr[o + 1] + run_shift - 1 (in any order
@@ -269,7 +273,7 @@ __device__ __forceinline__ uint32_t load_coherent(const uint32_t *p)
 // Sixteen bytes of a stream that nobody reads before the caches have lost it: past them where `stream`.  On streams
 // larger than the last-level cache (256 MB) such stores are 8 to 10 % faster; what fits in it is better left there for the
 // next kernel.
-typedef int Int4Vec __attribute__((ext_vector_type(4)));
+typedef int Int4Vec __attribute__((ext_vector_type(4), aligned(8)));
 constexpr size_t kStreamBytes = (size_t)256 << 20;
 template <bool stream> __device__ __forceinline__ void store16(void *p, int a, int b, int c, int d)
 {
@@ -318,7 +322,7 @@ __device__ __forceinline__ void write_rows(int32_t *rowptr, int lo, int hi, int3
 
 // An operator's record, as GraphView::orec describes it
 template <bool kStream>
-__device__ __forceinline__ void write_record(int4 *p, int32_t ib, int32_t ie, int32_t ob, int32_t oe, int32_t first, bool consecutive)
+__device__ __forceinline__ void write_record(Quad *p, int32_t ib, int32_t ie, int32_t ob, int32_t oe, int32_t first, bool consecutive)
 {
     store16<kStream>(p, ib, ie - ib, consecutive ? first : ob, consecutive ? oe - ob : -(oe - ob));
 }
@@ -382,8 +386,8 @@ hipError_t launch_scan_edges(const EdgeList *in, const EdgeList &out, int32_t *s
 hipError_t launch_sample_reach(const GraphView &g, int32_t *status, hipStream_t s);
 // operator records (unless the outputs are one run) of a single graph / of graphs that are also checked for range and for the ring
 // sweep.  prod1: producer words that the pass over the outputs left out (EdgeList::may_run), or NULL: there are none
-hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *status, hipStream_t s);
-hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *ofirst, int32_t *prod1, int32_t *status, int num_cus, hipStream_t s);
+hipError_t launch_build_records(const GraphView &g, Quad *orec, int32_t *prod1, int32_t *status, hipStream_t s);
+hipError_t launch_records_and_check(const GraphView &g, Quad *orec, int32_t *ofirst, int32_t *prod1, int32_t *status, int num_cus, hipStream_t s);
 hipError_t launch_check_topological(const GraphView &g, int32_t *status, hipStream_t s);
 // producer words from prod_rowptr / prod_idx; kStatusMulti when some tensor has several producers
 hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *status, hipStream_t s);
@@ -404,12 +408,12 @@ hipError_t launch_seed(const GraphView &g, int32_t Q, int64_t num_targets, const
 // deferred operators are waiting.  DB: deferred-operator markers, one byte per operator.
 hipError_t launch_level(const GraphView &g, TravState *st, TravCounters *ctr, int launch_no, int32_t *q0, int32_t *q1,
                         const QueueGeom &qg, uint8_t *DB, uint8_t *flags, u64 *M, u64 *K, int grid_blocks, int narrow_cap,
-                        const Schedule &sch, const ColourLog &log, int4 *trace, hipStream_t s);
+                        const Schedule &sch, const ColourLog &log, Quad *trace, hipStream_t s);
 // One workgroup runs level after level while 0 < frontier <= narrow_cap and nothing is deferred.  It leaves no
 // tallies behind, so the record it writes is the state the host may read.
 hipError_t launch_narrow(const GraphView &g, TravState *st, TravCounters *ctr, int launch_no, int32_t *q0, int32_t *q1,
                          const QueueGeom &qg, uint8_t *DB, uint8_t *flags, u64 *M, u64 *K, int narrow_cap, const Schedule &sch,
-                         const ColourLog &log, int4 *trace, hipStream_t s);
+                         const ColourLog &log, Quad *trace, hipStream_t s);
 // Packed batches of small graphs whose operator ids are a topological order: one wave per graph sweeps
 // its operators once, highest ids first (no frontier at all); fills K and, when pq is not NULL, the
 // per-graph per-set counts.
@@ -434,7 +438,7 @@ struct RingArgs {
     u64 *bits;               // [ring_bit_words(P, G)], per word of sets: a bit per operator, K != 0: words of 64 operators of one graph, graph g's
                              // from entry g + (its first operator) / 64 on
     int32_t *cum;            // for every such word: operators of the graph kept in it and above
-    int4 *graphs;            // [G + 1], or [words]: per graph or word of sets: operators kept, error bits, settling steps; all graphs
+    Quad *graphs;            // [G + 1], or [words]: per graph or word of sets: operators kept, error bits, settling steps; all graphs
     int32_t *host_status;    // pinned host memory: error bits, settling steps
     RecycleHeader *hdr, want;
     int32_t recycle;         // *hdr may say that the buffers hold this kernel's last result
@@ -491,7 +495,7 @@ struct BandArgs {
     FillRegion clear[kBandRegions];
     uint32_t *entry;         // [P][3]
     int2 *steps;             // per segment: first operator and tensor of its steps, the highest first
-    int4 *segs;              // steps, how far back its operators read, most outputs in a step, not a 0 if unfit
+    Quad *segs;              // steps, how far back its operators read, most outputs in a step, not a 0 if unfit
 };
 size_t band_scratch(BandArgs &a, void *mem);        // lays out the last three (NULL: the bytes alone); g is set
 hipError_t launch_band_plan(const BandArgs &a, int num_cus, hipStream_t s);

@@ -449,10 +449,10 @@ __global__ __launch_bounds__(256) void k_expand_rows(const int32_t *rowptr, int3
     const bool run = run_idx && status[kStatusNoRun] == 0;
     if (run) {
         const int32_t shift = num_tensors - nnz;
-        for (int64_t t = gtid * 4; t <= num_tensors; t += gsize * 4) {  // (run_row is aligned)
+        for (int64_t t = gtid * 4; t <= num_tensors; t += gsize * 4) {  // (run_row begins the caller's storage)
             auto row = [&](int64_t at) { return (int32_t)max(at - shift, (int64_t)0); };
             if (t + 4 <= num_tensors) {
-                *reinterpret_cast<int4 *>(run_row + t) = make_int4(row(t), row(t + 1), row(t + 2), row(t + 3));
+                store16<false>(run_row + t, row(t), row(t + 1), row(t + 2), row(t + 3));
             } else {
                 for (int64_t at = t; at <= num_tensors; ++at) run_row[at] = row(at);
             }
@@ -606,7 +606,7 @@ hipError_t launch_sample_reach(const GraphView &g, int32_t *status, hipStream_t 
 
 // Single graphs.  Outputs that are one run of tensors have no records.
 template <bool kStream>
-__global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, int32_t *prod1, int32_t *status)
+__global__ __launch_bounds__(256) void k_build_records(GraphView g, Quad *orec, int32_t *prod1, int32_t *status)
 {
     if (!adjacency_ready(status, false)) return;
     if (status[kStatusScattered] == 0 && blockIdx.x < kSampleWaves && threadIdx.x < kWave)
@@ -624,7 +624,7 @@ __global__ __launch_bounds__(256) void k_build_records(GraphView g, int4 *orec, 
     fill_spared_words(g, prod1, status, gtid, gsize);
 }
 
-hipError_t launch_build_records(const GraphView &g, int4 *orec, int32_t *prod1, int32_t *status, hipStream_t s)
+hipError_t launch_build_records(const GraphView &g, Quad *orec, int32_t *prod1, int32_t *status, hipStream_t s)
 {
     if (g.num_ops == 0) return hipSuccess;
     const int blocks = record_blocks(g.num_ops);
@@ -673,7 +673,7 @@ hipError_t launch_build_producers(const GraphView &g, int32_t *prod1, int32_t *s
 constexpr int kCheckThreads = 256;
 
 template <bool kStream>
-__global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g, int4 *orec, int32_t *ofirst, int32_t *prod1, int32_t *status)
+__global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g, Quad *orec, int32_t *ofirst, int32_t *prod1, int32_t *status)
 {
     __shared__ int s_found[6];                      // error, scattered, low, dist, span64, reach
     if (!adjacency_ready(status, false)) return;
@@ -803,7 +803,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_records_and_check(GraphView g
     }
 }
 
-hipError_t launch_records_and_check(const GraphView &g, int4 *orec, int32_t *ofirst, int32_t *prod1, int32_t *status, int num_cus, hipStream_t s)
+hipError_t launch_records_and_check(const GraphView &g, Quad *orec, int32_t *ofirst, int32_t *prod1, int32_t *status, int num_cus, hipStream_t s)
 {
     if (g.num_ops == 0) return hipSuccess;
     int64_t blocks = ((int64_t)g.num_ops + kCheckThreads - 1) / kCheckThreads;

@@ -363,7 +363,7 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(int32_t *counts, int64_t m,
         }
         return;
     }
-    // runs are a multiple of four counts long and start 16-byte aligned.  Up to kScanVecs int4 per thread (tile
+    // runs are a multiple of four counts long.  Up to kScanVecs int4 per thread (tile
     // counts of 134 million operators) stay in registers between the two passes: all loads in flight at once, one
     // trip to memory in all; longer runs are read twice.
     const int64_t per = (((m + 1023) / 1024) + 3) & ~(int64_t)3;
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(int32_t *counts, int64_t m,
             const int64_t i = lo + 4 * j;
             v[j] = make_int4(0, 0, 0, 0);
             if (i + 4 <= hi) {
-                v[j] = *reinterpret_cast<const int4 *>(counts + i);
+                v[j] = *reinterpret_cast<const Quad *>(counts + i);
             } else if (i < hi) {                         // the ragged end of the array: one by one
                 v[j].x = counts[i];
                 if (i + 1 < hi) v[j].y = counts[i + 1];
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(int32_t *counts, int64_t m,
             const int4 o = make_int4(run, run + v[j].x, run + v[j].x + v[j].y, run + v[j].x + v[j].y + v[j].z);
             run += v[j].x + v[j].y + v[j].z + v[j].w;
             if (i + 4 <= hi) {
-                *reinterpret_cast<int4 *>(counts + i) = o;
+                *reinterpret_cast<Quad *>(counts + i) = o;
             } else if (i < hi) {
                 counts[i] = o.x;
                 if (i + 1 < hi) counts[i + 1] = o.y;

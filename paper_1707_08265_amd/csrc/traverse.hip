@@ -572,7 +572,7 @@ __device__ __forceinline__ void run_level(const GraphView &g, const LevelSlot &i
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 x[q] = make_uint4(0, 0, 0, 0);
-                if (q < parts && op0 + q * 1024 < limit) x[q] = *reinterpret_cast<const uint4 *>(mk.DB + op0 + q * 1024);
+                if (q < parts && op0 + q * 1024 < limit) x[q] = *reinterpret_cast<const UQuad *>(mk.DB + op0 + q * 1024);
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -714,7 +714,7 @@ __device__ __forceinline__ LevelSlot derive_state(const TravState *st, const Tra
 // wave clears the tallies buffer of the NEXT launch (last read by the previous one).  works: this launch
 // runs a wide level; small: the state it starts from is one the single-workgroup kernel takes (or final).
 __device__ __forceinline__ void keep_books(TravState *st, TravCounters *ctr, int launch_no, const LevelSlot &prev_rec,
-                                           const LevelSlot &now, bool works, bool small, int tot_proc, int tot_atomics, int4 *trace)
+                                           const LevelSlot &now, bool works, bool small, int tot_proc, int tot_atomics, Quad *trace)
 {
     const int lane = lane_id();
     const int nxt = (launch_no + 1) % 3;
@@ -754,7 +754,7 @@ __device__ __forceinline__ void hand_on_frontier(TravCounters *ctr, int launch_n
 template <RowForm kForm>
 __global__ __launch_bounds__(kLevelThreads) void k_level(GraphView g, TravState *st, TravCounters *ctr, int launch_no,
                                                           int32_t *q0, int32_t *q1, QueueGeom qg, Masks mk,
-                                                          int narrow_cap, Schedule sch, ColourLog log, int4 *trace)
+                                                          int narrow_cap, Schedule sch, ColourLog log, Quad *trace)
 {
     __shared__ LevelShared sh;
     const int wave = threadIdx.x >> 6;
@@ -787,7 +787,7 @@ __global__ __launch_bounds__(kLevelThreads) void k_level(GraphView g, TravState 
 
 hipError_t launch_level(const GraphView &g, TravState *st, TravCounters *ctr, int launch_no, int32_t *q0, int32_t *q1,
                         const QueueGeom &qg, uint8_t *DB, uint8_t *flags, u64 *M, u64 *K, int grid_blocks, int narrow_cap,
-                        const Schedule &sch, const ColourLog &log, int4 *trace, hipStream_t s)
+                        const Schedule &sch, const ColourLog &log, Quad *trace, hipStream_t s)
 {
     if (grid_blocks < 2) grid_blocks = 2;                   // entries and range chunks go to different blocks
     hipLaunchKernelGGL(rows_of(g) == kRun ? k_level<kRun> : rows_of(g) == kRecords ? k_level<kRecords> : k_level<kFirst>, dim3((unsigned)grid_blocks), dim3(kLevelThreads), 0, s, g, st, ctr, launch_no, q0, q1,
@@ -806,7 +806,7 @@ constexpr int kNarrowFront = 1024;      // entries of a queue that the kernel al
 template <RowForm kForm>
 __global__ __launch_bounds__(kNarrowThreads) void k_narrow(GraphView g, TravState *st, TravCounters *ctr, int launch_no,
                                                             int32_t *q0, int32_t *q1, QueueGeom qg, Masks mk,
-                                                            int narrow_cap, Schedule sch, ColourLog log, int4 *trace)
+                                                            int narrow_cap, Schedule sch, ColourLog log, Quad *trace)
 {
     __shared__ int32_t s_stage[kNarrowWaves][kStageCap];
     __shared__ int32_t s_lstage[kNarrowWaves][kLogStageCap];
@@ -887,7 +887,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_narrow(GraphView g, TravStat
 
 hipError_t launch_narrow(const GraphView &g, TravState *st, TravCounters *ctr, int launch_no, int32_t *q0, int32_t *q1,
                          const QueueGeom &qg, uint8_t *DB, uint8_t *flags, u64 *M, u64 *K, int narrow_cap, const Schedule &sch,
-                         const ColourLog &log, int4 *trace, hipStream_t s)
+                         const ColourLog &log, Quad *trace, hipStream_t s)
 {
     hipLaunchKernelGGL(rows_of(g) == kRun ? k_narrow<kRun> : rows_of(g) == kRecords ? k_narrow<kRecords> : k_narrow<kFirst>, dim3(1), dim3(kNarrowThreads), 0, s, g, st, ctr, launch_no, q0, q1, qg,
                        Masks{M, K, DB, flags}, narrow_cap, sch, log, trace);

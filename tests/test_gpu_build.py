@@ -500,3 +500,69 @@ def test_batches_with_a_graph_around_the_largest_that_is_swept(dgn, oracle, larg
         assert np.array_equal(ip.rename.cpu().numpy(), want), f"in-place {list(how)}"
     assert ro.ignore() == 0
     assert np.array_equal(ro.ignore_mask.cpu().numpy().view(np.uint64), oracle.ignore_mask(adj, ref.op_mask, ref.tensor_mask))
+
+
+@pytest.mark.parametrize("shape", ["small", "large", "layers", "batch"])
+@pytest.mark.parametrize("source", ["ordered", "hole", "shuffled", "borrowed", "borrowed hole"])
+def test_memory_at_eight_bytes(dgn, oracle, shape, source):
+    """Storage, scratch and outputs that begin eight bytes past a 16-byte boundary, which is all that the interface asks for: graphs that are swept, in
+    layers, traversed, and packed batches."""
+    import torch
+    rng = np.random.default_rng(len(shape) + len(source))
+    if shape == "batch":
+        g, tg = gg.batch_layered(70, 333, 5, num_sets=7, per_set=3)
+    else:
+        ops = {"small": 2003, "large": 140_003, "layers": 24_000}[shape]
+        o, n_out = np.arange(ops), rng.integers(1, 3, ops)
+        first = 5 + np.concatenate([[0], np.cumsum(n_out)])
+        op = np.repeat(o, 2)
+        lo = first[np.maximum(op // 400 - 2, 0) * 400] if shape == "layers" else np.zeros(op.size)
+        hi = first[op // 400 * 400] if shape == "layers" else first[op]
+        in_t = np.where(hi > lo, lo + rng.random(op.size) * (hi - lo), rng.integers(0, 5, op.size)).astype(np.int32)
+        g = gg.Graph(ops, int(first[-1]), op.astype(np.int32), in_t, np.repeat(o, n_out).astype(np.int32), np.arange(5, first[-1], dtype=np.int32), name=shape)
+        tg = targets_from_sets([[int(x) for x in rng.integers(0, g.num_tensors, 3)] for _ in range(7)], 7)
+    if "hole" in source and shape != "batch":               # a tensor that nobody writes, behind half of the outputs
+        at = int(g.out_tensor[g.nnz_out // 2])
+        up1 = lambda a: (a + (a >= at)).astype(np.int32)  # noqa: E731
+        g = gg.Graph(g.num_ops, g.num_tensors + 1, g.in_op, up1(g.in_tensor), g.out_op, up1(g.out_tensor), name="hole")
+        tg = gg.Targets(tg.num_sets, tg.tgt_rowptr, up1(tg.tgt_idx))
+    adj, ref = oracle_prune(oracle, g, tg)
+    if source == "shuffled":
+        p, q = rng.permutation(g.nnz_in), rng.permutation(g.nnz_out)
+        g = gg.Graph(g.num_ops, g.num_tensors, g.in_op[p], g.in_tensor[p], g.out_op[q], g.out_tensor[q], g.num_graphs, g.graph_op_offsets,
+                     g.graph_tensor_offsets, "shuffled")
+        adj = oracle.build_adjacency(g.num_ops, g.num_tensors, g.in_op, g.in_tensor, g.out_op, g.out_tensor)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    at8 = lambda n, t=torch.uint8: torch.zeros(n * t.itemsize + 8, dtype=torch.uint8, device="cuda")[8:].view(t)  # noqa: E731
+    print(shape, source, flush=True)
+    if "borrowed" in source:
+        keep = [up(getattr(adj, n)) for n in ROWS[:4]]
+        desc = dgn.make_csr_desc(g.num_ops, g.num_tensors, *keep, g.num_graphs, g.graph_op_offsets, g.graph_tensor_offsets)
+        query, build = dgn.dgn_graph_from_csr_workspace, dgn.dgn_graph_from_csr
+    else:
+        keep, lists = (), [up(a) for a in (g.in_op, g.in_tensor, g.out_op, g.out_tensor)]
+        desc = dgn.make_coo_desc(g.num_ops, g.num_tensors, *lists, g.num_graphs, g.graph_op_offsets, g.graph_tensor_offsets)
+        query, build = dgn.dgn_graph_build_workspace, dgn.dgn_graph_build
+    rc, *sizes = query(desc)
+    mem, scratch = (at8(n) for n in sizes)
+    assert mem.data_ptr() % 16 == scratch.data_ptr() % 16 == 8
+    rc, handle = build(desc, mem, mem.numel(), scratch, scratch.numel())
+    assert rc == 0, dgn.dgn_strerror(rc)
+    dg = dgn.DeviceGraph(handle, mem, keep, dgn.dgn_graph_get_sizes(handle)[1])
+    csr = {n: v.cpu().numpy() for n, v in dg.csr().items()}
+    for name in ROWS:
+        assert np.array_equal(csr[name], getattr(adj, name)), name
+    buf = dgn.PruneBuffers(dg, tg.num_sets)
+    buf.scratch = at8(buf.scratch_bytes)
+    for name in ("tensor_mask", "op_mask", "op_flag", "kept_masks", "kept_count", "per_query_count"):
+        setattr(buf, name, at8(getattr(buf, name).numel(), getattr(buf, name).dtype))
+    for options in (None, None, dgn.dgn_options(traversal=1)):
+        assert buf.prune(up(tg.tgt_rowptr), up(tg.tgt_idx), options=options) == 0
+        assert_same(buf.to_host(), ref, f"levels {options is not None}")
+    ip, ro = dgn.InplaceBuffers(dg), dgn.ReadoutBuffers(buf)
+    ip.scratch = at8(ip.scratch_bytes)
+    for how in ({}, {"kept_ops": buf.kept_ops, "kept_count": buf.kept_count}):
+        assert ip.run(buf.op_mask, **how) == 0
+        assert np.array_equal(ip.rename.cpu().numpy(), oracle.inplace(adj, ref.op_mask, (1 << 64) - 1)), f"in-place {list(how)}"
+    assert ro.ignore() == 0
+    assert np.array_equal(ro.ignore_mask.cpu().numpy().view(np.uint64), oracle.ignore_mask(adj, ref.op_mask, ref.tensor_mask))
