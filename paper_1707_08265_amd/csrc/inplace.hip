@@ -219,19 +219,19 @@ __global__ __launch_bounds__(kThreads) void k_inplace_children(GraphView g, cons
 // a pruned graph is a few percent of the recorded one, and the list spares the pass over all of K.  An entry
 // whose mask misses `select` is skipped.  Workgroups are small, so that their number, not that of the workgroups on the chip, decides how long the
 // last ones take (1.1 M operators of a power law with 2.8 M inputs: 190 us in workgroups of 1 024 threads, two and a little each, now 174).
-//   A wave takes two times 64 entries one after the other, and in a long list of a batch or of chains eight times: such operators read the same few
-// graph inputs, and a wave's later ones see that those have several children already, where all waves at once ask one after the other
-// for the same line.  Whole pass, 1 024 threads and 64 entries each / 256 and 64 / 128 / 512: RNN of 1 M operators, 200 000 kept 313 / 442 / 259 / 163
-// us; 10 M, 515 000 kept 703 / 827 / 594 / 277; 46 000 kept 158 / 169 / 128 / 128, but 500 000 with layers of 100 55 / 53 / 53 / 78; 40 graphs of
-// 300 000 1 930 / 2 050 / 2 260 / 1 240, 64 of them 2 370 / 2 660 / 3 030 / 1 890, 1 024 of 3 000 163 / 160 / 157 / 155, but 96 of 3 000 61 / 58 / 57 /
-// 82.  In layers and power laws 128 are as good as 64 (500 layers of 400 62 / 58 / 60 / 86; 50 M 420 / 340 to 370 / 360 to 390 / 420).
+//   Operators of chains and of a batch's graphs read the same few graph inputs, and all waves at once ask one after the other for the same
+// line.  There a wave takes two times 64 entries one after the other, of long lists eight times: its later ones see that those inputs have
+// several children already.  Whole pass, 1 024 threads and 64 entries each / 256 and 64 / 128 / 512: RNN of 1 M operators, 200 000 kept 313 / 442 /
+// 259 / 163 us; 10 M, 515 000 kept 703 / 827 / 594 / 277; 46 000 kept 158 / 169 / 128 / 128, but of 500 000 with layers of 100 55 / 53 / 53 / 78; 40
+// graphs of 300 000 1 930 / 2 050 / 2 260 / 1 240, 64 of them 2 370 / 2 660 / 3 030 / 1 890, 1 024 of 3 000 163 / 160 / 157 / 155, but 96 of 3 000 61 / 58 /
+// 57 / 82, eight of 2 000 54 / 45 / 47 / 70.  Layers and power laws have no such inputs (50 M, 1 M kept, with the lists 641 us, with 128 entries 662).
 constexpr int kListThreads = 256, kListWaves = kListThreads / kWave, kListRoom = 2048;
-constexpr int kListRounds = 2, kListManyRounds = 8;
-constexpr int64_t kListManyOfChains = (int64_t)1 << 17, kListManyOfBatch = (int64_t)1 << 20;
+constexpr int kListSomeRounds = 2, kListManyRounds = 8;
+constexpr int64_t kListSome = (int64_t)1 << 15, kListManyOfChains = (int64_t)1 << 17, kListManyOfBatch = (int64_t)1 << 20, kListNever = (int64_t)1 << 62;
 template <RowForm kForm>
 __global__ __launch_bounds__(kListThreads) void k_inplace_children_list(GraphView g, const u64 *K, u64 select,
-                                                                       const int32_t *kept_ops, const int64_t *kept_count, int64_t many,
-                                                                       int32_t *rename, int32_t *child, int32_t *list,
+                                                                       const int32_t *kept_ops, const int64_t *kept_count, int64_t some,
+                                                                       int64_t many, int32_t *rename, int32_t *child, int32_t *list,
                                                                        int32_t *list_count)
 {
     __shared__ int32_t s_claims[kListRoom];
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(kListThreads) void k_inplace_children_list(GraphVie
     __syncthreads();
     const ClaimStage cs{s_claims, kListRoom, &s_count, list, list_count};
     const int64_t kept = kept_count[0];
-    const int rounds = kept >= many ? kListManyRounds : kListRounds;
+    const int rounds = kept >= many ? kListManyRounds : kept >= some ? kListSomeRounds : 1;
     const int64_t tile = (int64_t)kListThreads * rounds, gsize = gridDim.x * tile;
     for (int64_t base = blockIdx.x * tile; base < kept; base += gsize) {       // whole workgroups stay in the loop
         const int64_t first = base + (int64_t)(threadIdx.x >> 6) * kWave * rounds + lane_id();
@@ -336,7 +336,8 @@ hipError_t launch_inplace_setup(const GraphView &g, const u64 *K, u64 select, co
     if (P > 0 && kept_ops) {
         auto k = rows == kRun ? k_inplace_children_list<kRun> : rows == kRecords ? k_inplace_children_list<kRecords> : k_inplace_children_list<kFirst>;
         hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(threads), 0, s, g, K, select, kept_ops, kept_count,
-                           chains ? kListManyOfChains : g.num_graphs > 1 ? kListManyOfBatch : (int64_t)1 << 62, rename, b.child, b.list, b.counters);
+                           chains || g.num_graphs > 1 ? kListSome : kListNever,
+                           chains ? kListManyOfChains : g.num_graphs > 1 ? kListManyOfBatch : kListNever, rename, b.child, b.list, b.counters);
     } else if (P > 0) {
         auto k = rows == kRun       ? chains ? k_inplace_children<kRun, kChainThreads> : k_inplace_children<kRun, kMaskThreads>
                  : rows == kRecords ? chains ? k_inplace_children<kRecords, kChainThreads> : k_inplace_children<kRecords, kMaskThreads>

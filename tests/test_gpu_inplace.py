@@ -117,7 +117,7 @@ def test_long_chain_needs_logarithmic_rounds(dgn, oracle):
 
 
 @pytest.mark.parametrize("reads", ["before", "far"])
-@pytest.mark.parametrize("ops", [1, 63, 2047, 2049, 8193, 40_000, 131_071, 131_072, 140_001])
+@pytest.mark.parametrize("ops", [1, 63, 2047, 2049, 8193, 32_767, 32_768, 40_000, 131_071, 131_072, 140_001])
 def test_more_nodes_than_a_workgroup_has_room_for(dgn, oracle, ops, reads):
     """Three inputs of its own for every operator, each a node with one child, after one that was written just before (chains) or anywhere:
     a step claims several times what its workgroup has room for, in small and in large workgroups."""
