@@ -383,7 +383,7 @@ struct dgn_graph {
     bool ring;              // the ring sweep can take these graphs: see ring_sweep.hip for the three numbers
     int ring_low, ring_dist, ring_span64, ring_reach;
     Reach reach;            // how far back the operators of a single graph read (see the schedule in prune_impl)
-    bool chains;            // a single graph whose operators read what was written just before, or nobody knows
+    Meet meet;              // what many operators read at the same time (see the in-place pass)
     bool reads_about;       // half of the operators (of all graphs) read further back than an eighth of their graph, or nobody knows
     bool layers;            // a single graph, its outputs in one run of tensors, that looks like layers (see band_sweep.hip)
     uint64_t serial;        // unique per handle in this process
@@ -509,7 +509,8 @@ int finish_build(dgn_graph *h, const int64_t *op_off_host, const int64_t *t_off_
         h->reach = most(kStatusWithin2048) ? Reach::deep : most(kStatusWithin640) ? Reach::nearer
                  : most(kStatusWithin192) ? Reach::near : most(kStatusWithin32) ? Reach::layers : Reach::unknown;
     // (operators that read what was written just before: chains, not layers)
-    h->chains = h->G == 1 && found[kStatusSoon] * kBandSoonShare >= found[kStatusSampled];
+    const bool chains = found[kStatusSoon] * kBandSoonShare > found[kStatusSampled];
+    h->meet = h->G > 1 ? Meet::batch : found[kStatusSampled] == 0 ? Meet::unknown : chains ? Meet::chains : Meet::nowhere;
     h->layers = h->G == 1 && h->P > 0 && h->P <= kBandMaxOps && h->Ein > 0 && found[kStatusScattered] == 0 && h->T >= h->Eout &&
                 h->T - h->Eout <= kBandMaxLow && !h->reads_about &&
                 found[kStatusSoon] * kBandSoonShare <= found[kStatusSampled];
@@ -1929,7 +1930,7 @@ static int inplace_impl(const dgn_graph *g, const uint64_t *op_mask, uint64_t se
     const InplaceBuffers B = inplace_buffers(scratch, g->T);
     const int grid = g->num_cus * 8;
     DGN_HIP(launch_inplace_setup(g->v, reinterpret_cast<const u64 *>(op_mask), select, kept_ops, kept_count, rename,
-                                 renamed_count, B, g->chains, grid, s));
+                                 renamed_count, B, g->meet, grid, s));
     void *pin = nullptr;
     int rc = pinned_buffer(&pin);
     if (rc != DGN_OK) return rc;

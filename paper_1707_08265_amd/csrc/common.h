@@ -574,10 +574,12 @@ struct InplaceBuffers {
 size_t inplace_scratch_bytes(int64_t T);
 InplaceBuffers inplace_buffers(void *scratch, int64_t T);
 // init and children (the state before the first doubling round)
-// chains: operators mostly read what was written just before, or nobody knows (one graph)
+// What many operators read at the same time: nothing; the inputs of their graph, in chains (operators that read what was written just before)
+// and in packed batches; or nobody knows, where one graph's tensors are not numbered in order.
+enum class Meet { nowhere, unknown, chains, batch };
 hipError_t launch_inplace_setup(const GraphView &g, const u64 *K, u64 select, const int32_t *kept_ops,
                                 const int64_t *kept_count, int32_t *rename, int64_t *renamed_count,
-                                const InplaceBuffers &b, bool chains, int grid_blocks, hipStream_t s);
+                                const InplaceBuffers &b, Meet meet, int grid_blocks, hipStream_t s);
 hipError_t launch_inplace_round(int round, int32_t *rename, int64_t *renamed_count, const InplaceBuffers &b,
                                 int grid_blocks, hipStream_t s);
 

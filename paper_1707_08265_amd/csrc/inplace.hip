@@ -322,7 +322,7 @@ InplaceBuffers inplace_buffers(void *scratch, int64_t T)
 
 hipError_t launch_inplace_setup(const GraphView &g, const u64 *K, u64 select, const int32_t *kept_ops,
                                 const int64_t *kept_count, int32_t *rename, int64_t *renamed_count,
-                                const InplaceBuffers &b, bool chains, int grid_blocks, hipStream_t s)
+                                const InplaceBuffers &b, Meet meet, int grid_blocks, hipStream_t s)
 {
     const int64_t T = g.num_tensors, P = g.num_ops;
     // fills: a thread per 16 bytes and array; the other passes: as many threads as the chip holds
@@ -330,14 +330,15 @@ hipError_t launch_inplace_setup(const GraphView &g, const u64 *K, u64 select, co
     hipLaunchKernelGGL(k_inplace_init, dim3((unsigned)(nb < 1 ? 1 : nb)), dim3(kIpFillThreads), 0, s, rename, b.child, T, b.counters,
                        kInplaceMaxRounds + 1, renamed_count);
     const RowForm rows = rows_of(g);
+    const bool chains = meet == Meet::chains || meet == Meet::unknown;
     const int threads = kept_ops ? kListThreads : chains ? kChainThreads : kMaskThreads;
     int64_t blocks = (P + threads - 1) / threads;
     if (blocks > grid_blocks * 256 / threads) blocks = grid_blocks * 256 / threads;
     if (P > 0 && kept_ops) {
         auto k = rows == kRun ? k_inplace_children_list<kRun> : rows == kRecords ? k_inplace_children_list<kRecords> : k_inplace_children_list<kFirst>;
         hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(threads), 0, s, g, K, select, kept_ops, kept_count,
-                           chains || g.num_graphs > 1 ? kListSome : kListNever,
-                           chains ? kListManyOfChains : g.num_graphs > 1 ? kListManyOfBatch : kListNever, rename, b.child, b.list, b.counters);
+                           meet == Meet::nowhere ? kListNever : kListSome,
+                           meet == Meet::chains ? kListManyOfChains : meet == Meet::batch ? kListManyOfBatch : kListNever, rename, b.child, b.list, b.counters);
     } else if (P > 0) {
         auto k = rows == kRun       ? chains ? k_inplace_children<kRun, kChainThreads> : k_inplace_children<kRun, kMaskThreads>
                  : rows == kRecords ? chains ? k_inplace_children<kRecords, kChainThreads> : k_inplace_children<kRecords, kMaskThreads>
