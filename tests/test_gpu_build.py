@@ -107,16 +107,19 @@ def test_borrowed_rows_of_any_alignment(dgn, oracle, ops, fan, at, numbering):
     n_out = rng.integers(0, 3, ops)
     n_out[-1] = 2
     t = 4 + np.arange(n_out.sum())
+    out_op, in_op = np.repeat(np.arange(ops), n_out), np.repeat(np.arange(ops), fan)
+    own = 4 + np.concatenate([[0], np.cumsum(n_out)])[:-1]   # first output, so that inputs are others' outputs or the four graph inputs
+    in_t = own[in_op] - 1 - (rng.random(in_op.size) * np.minimum(own[in_op], 300)).astype(np.int64)
     if numbering == "in rows":
         t[-2:] = t[-2:][::-1]
     if numbering == "hole":
+        in_t += in_t >= t[len(t) // 2]
         t[len(t) // 2:] += 1
-    out_op, in_op = np.repeat(np.arange(ops), n_out), np.repeat(np.arange(ops), fan)
-    in_t = (rng.random(in_op.size) * 4).astype(np.int64)
     i32 = lambda a: np.ascontiguousarray(a, dtype=np.int32)  # noqa: E731
     g = gg.Graph(ops, int(t.max()) + 1, i32(in_op), i32(in_t), i32(out_op), i32(t), name="borrowed")
     tg = targets_from_sets([[int(x) for x in rng.integers(0, g.num_tensors, 3)] for _ in range(5)], 5)
     adj, ref = oracle_prune(oracle, g, tg)
+    assert fan == 0 or ops < 1000 or np.count_nonzero(ref.op_mask) > 3 * 15, "the prune stops at the targets' own producers"
     keep = []
     for name in ROWS[:4]:
         a = torch.zeros(getattr(adj, name).size + at, dtype=torch.int32, device="cuda")[at:]
@@ -450,6 +453,9 @@ def test_batches_around_the_number_that_have_no_records(dgn, oracle, graphs, rel
     up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
     assert buf.prune(up(tg.tgt_rowptr), up(tg.tgt_idx), options=dgn.dgn_options(traversal=1)) == 0
     assert_same(buf.to_host(), ref, "levels")
+    few = dgn.PruneBuffers(dg, 7)                            # more targets than the queues hold: every operator is looked at until nothing changes
+    assert few.prune(up(tg.tgt_rowptr), up(tg.tgt_idx), options=dgn.dgn_options(traversal=1, max_queue_entries=16)) == 0
+    assert_same(few.to_host(), ref, "queues that overflow")
     ip, ro = dgn.InplaceBuffers(dg), dgn.ReadoutBuffers(buf)
     want = oracle.inplace(adj, ref.op_mask, (1 << 64) - 1)
     for how in ({}, {"kept_ops": buf.kept_ops, "kept_count": buf.kept_count}):
