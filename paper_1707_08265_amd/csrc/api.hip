@@ -1068,7 +1068,7 @@ static int band_prune(const dgn_graph *g, int32_t num_sets, int64_t num_targets,
     ca.M = M;
     ca.K = K;
     ca.op_flag = op_flag ? op_flag : flags;
-    ca.from_tensor_mask = true;                             // (the sweep leaves M alone: see band_sweep.hip)
+    ca.from_tensor_mask = true;                             // (of M and K the sweep writes M only)
     ca.kept_ops = kept_ops;
     ca.kept_masks = kept_masks;
     ca.kept_count = kept_count;

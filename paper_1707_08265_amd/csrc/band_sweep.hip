@@ -15,7 +15,7 @@
 // more than 2 048 targets, of all its words, sends them by way of M and the seed kernel, since one workgroup may own them all: steps of
 // 0.35 us instead of 0.27).  Operators are fetched eight steps ahead; no step waits for memory, and
 // a barrier is all that separates two of them.  The removal rule's passes follow and take K from M: keeping K of a step in LDS and storing
-// it from here cost the sweep 19 us of 161, the count pass's two reads per operator cost 4 more.
+// it from here cost the sweep 19 us of 161; the count pass's two reads per operator cost 4 more (7.8 -> 11.7), the list 1.
 //
 // What bounds it: the instructions of a step, 0.27 us for 400 operators, one wave's after the other's: barrier and bounds
 // 0.15, ORs 0.04, the flush's stores (two bytes every eight; in runs of their own as long) 0.03.  500 layers of 400 operators, 64 sets, 525 steps: plan
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(2 * kBandHalf) void k_band_sweep(BandArgs a)
         }
 #pragma unroll
         for (int u = 0; u < kBandAhead; ++u) fetch(uniform(bound(s0 + u + 3, true)), seed[u]);
-        // of the step before (none yet): first tensor and operator, how many, slot; [place_from, place_end): two steps ahead
+        // of the step before (none yet): first tensor, how many, slot; [place_from, place_end): two steps ahead
         int32_t flush_from = y0, place_end = y2, place_from = uniform(bound(s0 + 3, true)),
                 ahead = uniform(bound(s0 + kBandAhead + 3, true));
         int tensors = 0;

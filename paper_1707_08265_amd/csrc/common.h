@@ -56,7 +56,7 @@ constexpr int32_t kNoProducer = -3;   // graph input
 
 // The record of operator o and the producer word of tensor t.  Graphs in one run have neither in memory: their rows say the same, and
 // not writing them spares a build of 50 M operators 1.6 of 5.6 GB (1 183 -> 845 us); a record then is two accesses of 8 bytes
-// side by side instead of one of 16.  The traversal's kernels are told which it is (a branch there costs them 7 %).
+// in two arrays, so two lines, instead of one of 16.  The traversal's kernels are told which it is (a branch there costs them 7 %).
 typedef int IntPair __attribute__((ext_vector_type(2), aligned(4)));
 enum RowForm : int { kRecords, kRun, kFirst };     // what an operator's record and a tensor's producer are taken from
 __host__ __device__ inline RowForm rows_of(const GraphView &g) { return g.run_shift >= 0 ? kRun : g.orec ? kRecords : kFirst; }

@@ -32,7 +32,8 @@ __device__ __forceinline__ void rows_closed(int32_t prev, int32_t cur, int32_t n
 // outputs also the tensors' (first position of every tensor, producers) and, unless the outputs are one run of tensors up to the last
 // (EdgeList::may_run), producer words.  If the keys do decrease
 // somewhere, what was written is overwritten by the sort that follows, which also checks every id once more: a wave that has met such a
-// place leaves the rest.  No atomic in the common case.
+// place writes nothing.  (The list is read to its end all the same, in pieces handed out in order; of long ones k_first_look sees beforehand whether that
+// is worth it.)  No atomic in the common case.
 //
 // A stream of 12 bytes per input edge and 24 per output edge and tensor: it is bound by memory.  A thread takes four
 // neighbouring positions per step, in 16-byte accesses where the arrays are aligned for them (one position per thread left
@@ -145,8 +146,8 @@ __device__ __forceinline__ void scan_list(const EdgeList &l, int64_t block, int6
         }
     }
     // Shuffled input has every workgroup report: once each, its words looked at together, and a store (same value from everyone)
-    // only where it is needed.  (12 M operators in shuffled order: 145 us with a look at every word by every wave and the whole
-    // list read, 125 when the reading ended early, 59 with one look per workgroup.)
+    // only where it is needed.  (12 M operators in shuffled order, when lists of that length were read here: 125 us with a look at every word
+    // by every wave, 59 with one look per workgroup.  3 M, the whole list read: 39.)
     uint32_t words = 0;                                                 // bit w: status word w
     auto report = [&](bool v, int word) { words |= ballot64(v) != 0 ? 1u << word : 0; };
     report(down, kOut ? kStatusOutUnsorted : kStatusInUnsorted);

@@ -163,7 +163,8 @@ __device__ __forceinline__ void flush_claims(const ClaimStage &cs, int *s_base, 
 //   Workgroups of 256 threads, with room for a claim per operator of a step; in one of 1 024, with room for every second, waves wait for each other and
 // claims go to the list one wave at a time (4 096 graphs of 20 000, 49 M kept: 4.59 ms, 3.84 to 4.14 so; with half the large ones' room 7.41.  256 of 20 000: 312 us, 275;
 // 50 M of a power law 455, 404; 800 000 in layers 155, 120).  Not for chains, whose operators read the same few graph inputs: the more waves
-// go side by side, the more of them meet there (an RNN of 1 M: 176 us, with small workgroups 213; 200 000: 129, 133).
+// go side by side, the more of them meet there (an RNN of 1 M: 176 us, with small workgroups 213; 200 000: 129, 133),
+// nor where nobody knows (Meet::unknown).
 constexpr int kMaskRounds = 8;                      // masks per lane and step
 constexpr int kMaskThreads = 256, kChainThreads = 1024;
 __host__ __device__ constexpr int mask_room(int threads) { return threads == kChainThreads ? 4096 : threads * kMaskRounds; }
@@ -225,6 +226,7 @@ __global__ __launch_bounds__(kThreads) void k_inplace_children(GraphView g, cons
 // 259 / 163 us; 10 M, 515 000 kept 703 / 827 / 594 / 277; 46 000 kept 158 / 169 / 128 / 128, but of 500 000 with layers of 100 55 / 53 / 53 / 78; 40
 // graphs of 300 000 1 930 / 2 050 / 2 260 / 1 240, 64 of them 2 370 / 2 660 / 3 030 / 1 890, 1 024 of 3 000 163 / 160 / 157 / 155, but 96 of 3 000 61 / 58 /
 // 57 / 82, eight of 2 000 54 / 45 / 47 / 70.  Layers and power laws have no such inputs (50 M, 1 M kept, with the lists 641 us, with 128 entries 662).
+// Where nobody knows, 128: an RNN of 1 M 223 / 221 / 175, 5 M of a power law 97 / 90 / 89, 500 layers of 400 72 / 69 / 72.
 constexpr int kListThreads = 256, kListWaves = kListThreads / kWave, kListRoom = 2048;
 constexpr int kListSomeRounds = 2, kListManyRounds = 8;
 constexpr int64_t kListSome = (int64_t)1 << 15, kListManyOfChains = (int64_t)1 << 17, kListManyOfBatch = (int64_t)1 << 20, kListNever = (int64_t)1 << 62;
